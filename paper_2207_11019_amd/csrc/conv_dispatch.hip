@@ -14,24 +14,19 @@ hipError_t conv_wgrad_generic_launch(int dtype, const ConvGeom& g, const void* x
                                      int accumulate, void* ws, hipStream_t s);
 size_t wgrad_generic_ws_bytes(const ConvGeom& g);
 
-bool mfma_fwd_ok(const ConvGeom& g);
-bool mfma_dgrad_ok(const ConvGeom& g);
-bool mfma_wgrad_ok(const ConvGeom& g);
-size_t mfma_fwd_ws_bytes(const ConvGeom& g);
-size_t mfma_dgrad_ws_bytes(const ConvGeom& g);
-size_t mfma_wgrad_ws_bytes(const ConvGeom& g);
-bool mfma_fwd_pools(const ConvGeom& g);
-hipError_t mfma_conv_fwd(const ConvGeom& g, const void* x, const void* w, const float* scale, const float* bias,
-                         const void* add, int relu, void* y, void* ws, hipStream_t st, void* pool_y);
-hipError_t mfma_conv_dgrad(const ConvGeom& g, const void* dz, const void* wt, void* dx, int accumulate, const void* mask,
-                           const float* mscale, void* ws, hipStream_t st, const UnpoolDesc* unpool, const DgradSide* side);
-hipError_t mfma_conv_wgrad(const ConvGeom& g, const void* x, const void* dz, float* dw, float* dbias, const float* rscale,
+bool mfma_fwd_ok(int dtype, const ConvGeom& g);
+bool mfma_dgrad_ok(int dtype, const ConvGeom& g);
+size_t mfma_fwd_ws_bytes(int dtype, const ConvGeom& g);
+size_t mfma_dgrad_ws_bytes(int dtype, const ConvGeom& g);
+bool mfma_fwd_pools(int dtype, const ConvGeom& g);
+hipError_t mfma_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* scale, const float* bias,
+                         const void* add, int relu, void* y, void* ws, bool ws_zeroed, hipStream_t st, void* pool_y);
+hipError_t mfma_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const void* wt, void* dx, int accumulate, const void* mask,
+                           const float* mscale, void* ws, bool ws_zeroed, hipStream_t st, const UnpoolDesc* unpool, const DgradSide* side);
+bool wgrad_mm_ok(int dtype, const ConvGeom& g);
+size_t wgrad_mm_ws_bytes(int dtype, const ConvGeom& g);
+hipError_t wgrad_mm_launch(int dtype, const ConvGeom& g, const void* x, const void* dz, float* dw, float* dbias, const float* rscale,
                            int accumulate, void* ws, hipStream_t st, ReduceDesc* deferred);
-
-bool wgrad_tr_ok(const ConvGeom& g);
-size_t wgrad_tr_ws_bytes(const ConvGeom& g);
-hipError_t wgrad_tr(const ConvGeom& g, const void* x, const void* dz, float* dw, float* dbias, const float* rscale,
-                    int accumulate, void* ws, hipStream_t st, ReduceDesc* deferred);
 
 bool fc_skinny_ok(const ConvGeom& g);
 size_t fc_dgrad_ws_bytes(const ConvGeom& g);
@@ -53,39 +48,54 @@ bool smallk_ok(const ConvGeom& g);
 hipError_t smallk_conv_fwd(const ConvGeom& g, const void* x, const void* w, const float* scale, const float* bias,
                            const void* add, int relu, void* y, hipStream_t st);
 
-size_t fwd_ws_bytes(int dtype, const ConvGeom& g) { return (dtype == LPM_BF16 && mfma_fwd_ok(g)) ? mfma_fwd_ws_bytes(g) : 0; }
+// A filter that covers its whole input makes one output pixel per sample: x is a matrix [m][K] and w [Cout][K] as they lie in
+// memory, so the layer is a 1x1 convolution of K channels.  (As a convolution its data gradient would visit every tap for
+// every input pixel, of which one is real; and the reduction need not be cut at the taps.)
+static ConvGeom fc_view(const ConvGeom& g) {
+    if (g.Do != 1 || g.Ho != 1 || g.Wo != 1 || g.pad != 0 || g.pad_d != 0 || g.D != g.Kd || g.H != g.Kh || g.W != g.Kw || g.taps() == 1) return g;
+    ConvGeom v{g.m, 1, 1, g.K(), 1, 1, g.Cout, 1, 1, 1, 0};
+    return v;
+}
+// (a bf16 data gradient reads the transposed weights, whose layout keeps the taps: no view)
+static ConvGeom dgrad_view(int dtype, const ConvGeom& g) { return dtype == LPM_F32 ? fc_view(g) : g; }
+
+size_t fwd_ws_bytes(int dtype, const ConvGeom& g_) {
+    const ConvGeom g = fc_view(g_);
+    return mfma_fwd_ok(dtype, g) ? mfma_fwd_ws_bytes(dtype, g) : 0;
+}
 size_t dgrad_ws_bytes(int dtype, const ConvGeom& g) {
-    if (dtype == LPM_BF16 && fc_skinny_ok(g)) return std::max(fc_dgrad_ws_bytes(g), mfma_dgrad_ok(g) ? mfma_dgrad_ws_bytes(g) : 0);
-    return (dtype == LPM_BF16 && mfma_dgrad_ok(g)) ? mfma_dgrad_ws_bytes(g) : 0;
+    const ConvGeom v = dgrad_view(dtype, g);
+    const size_t b = mfma_dgrad_ok(dtype, v) ? mfma_dgrad_ws_bytes(dtype, v) : 0;
+    if (dtype == LPM_BF16 && fc_skinny_ok(g)) return std::max(LPM_COUNT_BYTES + fc_dgrad_ws_bytes(g), b);
+    return b;
 }
 size_t wgrad_ws_bytes(int dtype, const ConvGeom& g) {
     if (dtype == LPM_BF16 && fc_skinny_ok(g)) return 0;
-    if (dtype == LPM_BF16 && wgrad_tr_ok(g)) return wgrad_tr_ws_bytes(g);
-    if (dtype == LPM_BF16 && mfma_wgrad_ok(g)) return mfma_wgrad_ws_bytes(g);
+    if (wgrad_mm_ok(dtype, fc_view(g))) return wgrad_mm_ws_bytes(dtype, fc_view(g));
     if (dtype == LPM_BF16 && mfma_wgrad_flat_ok(g)) return mfma_wgrad_flat_ws_bytes(g);
     return wgrad_generic_ws_bytes(g);
 }
 
-bool fwd_can_pool(int dtype, const ConvGeom& g) { return dtype == LPM_BF16 && mfma_fwd_pools(g); }
+bool fwd_can_pool(int dtype, const ConvGeom& g) { return mfma_fwd_pools(dtype, g); }
 
 hipError_t launch_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* scale,
-                           const float* bias, const void* add, int relu, void* y, void* ws, hipStream_t st, void* pool_y) {
+                           const float* bias, const void* add, int relu, void* y, void* ws, hipStream_t st, void* pool_y, bool ws_zeroed) {
     if (pool_y && !fwd_can_pool(dtype, g)) return hipErrorInvalidValue;      // callers ask fwd_can_pool first
-    if (dtype == LPM_BF16 && mfma_fwd_ok(g)) return mfma_conv_fwd(g, x, w, scale, bias, add, relu, y, ws, st, pool_y);
+    if (mfma_fwd_ok(dtype, fc_view(g))) return mfma_conv_fwd(dtype, fc_view(g), x, w, scale, bias, add, relu, y, ws, ws_zeroed, st, pool_y);
     if (dtype == LPM_BF16 && smallk_ok(g)) return smallk_conv_fwd(g, x, w, scale, bias, add, relu, y, st);
     return conv_fwd_generic_launch(dtype, g, x, w, scale, bias, add, relu, y, st);
 }
 
-bool wgrad_fuses_bias(int dtype, const ConvGeom& g) { return dtype == LPM_BF16 && (fc_skinny_ok(g) || mfma_wgrad_ok(g) || mfma_wgrad_flat_ok(g)); }
+bool wgrad_fuses_bias(int dtype, const ConvGeom& g) { return wgrad_mm_ok(dtype, fc_view(g)) || (dtype == LPM_BF16 && (fc_skinny_ok(g) || mfma_wgrad_flat_ok(g))); }
 
 // whether the data gradient wants the [Cin][Kh][Kw][Cout] copy of the weights
-bool dgrad_uses_wt(int dtype, const ConvGeom& g) { return dtype == LPM_BF16 && !fc_skinny_ok(g) && mfma_dgrad_ok(g); }
+bool dgrad_uses_wt(int dtype, const ConvGeom& g) { return dtype == LPM_BF16 && !fc_skinny_ok(g) && mfma_dgrad_ok(dtype, g); }
 
 // the stride-1 MFMA data gradient can route its result through a following (in forward order: preceding) max-pooling
 // (worth it while the kernel is bound by its launch: measured on the 224x224 VGG layers the scattered 2-byte stores
 // in the contraction's epilogue cost more than the separate pooling kernel, so large gradients keep that kernel)
 bool dgrad_can_unpool(int dtype, const ConvGeom& g) {
-    return dtype == LPM_BF16 && !g.is3d() && !fc_skinny_ok(g) && mfma_dgrad_ok(g) && g.stride == 1 &&
+    return dtype == LPM_BF16 && !g.is3d() && !fc_skinny_ok(g) && mfma_dgrad_ok(dtype, g) && g.stride == 1 &&
            (int64_t)g.rows_in() * g.Cin <= ((int64_t)1 << 20);
 }
 
@@ -94,11 +104,12 @@ bool dgrad_has_side(int dtype, const ConvGeom& g) { return dgrad_uses_wt(dtype, 
 
 hipError_t launch_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const void* w, const void* wt, void* dx,
                              int accumulate, const void* mask, const float* mscale, void* ws, hipStream_t st,
-                             const UnpoolDesc* unpool, const DgradSide* side, const float* dzscale) {
+                             const UnpoolDesc* unpool, const DgradSide* side, const float* dzscale, bool ws_zeroed) {
     if (unpool && !(dgrad_can_unpool(dtype, g) && wt)) return hipErrorInvalidValue;      // callers ask dgrad_can_unpool first
     if (side && !(dgrad_has_side(dtype, g) && wt)) return hipErrorInvalidValue;          // ... and dgrad_has_side
-    if (dtype == LPM_BF16 && fc_skinny_ok(g)) return fc_dgrad(g, dz, dzscale, w, dx, accumulate, mask, mscale, ws, st);
-    if (dtype == LPM_BF16 && wt && mfma_dgrad_ok(g)) return mfma_conv_dgrad(g, dz, wt, dx, accumulate, mask, mscale, ws, st, unpool, side);
+    if (dtype == LPM_BF16 && fc_skinny_ok(g)) return fc_dgrad(g, dz, dzscale, w, dx, accumulate, mask, mscale, (char*)ws + LPM_COUNT_BYTES, st);
+    if (dtype == LPM_BF16 && wt && mfma_dgrad_ok(dtype, g)) return mfma_conv_dgrad(dtype, g, dz, wt, dx, accumulate, mask, mscale, ws, ws_zeroed, st, unpool, side);
+    if (dtype == LPM_F32 && !dzscale && !mscale && mfma_dgrad_ok(dtype, fc_view(g))) return mfma_conv_dgrad(dtype, fc_view(g), dz, w, dx, accumulate, mask, mscale, ws, ws_zeroed, st, nullptr, nullptr);
     return conv_dgrad_generic_launch(dtype, g, dz, dzscale, w, dx, accumulate, mask, mscale, st);
 }
 
@@ -106,8 +117,7 @@ hipError_t launch_conv_wgrad(int dtype, const ConvGeom& g, const void* x, const 
                              const float* rscale, int accumulate, void* ws, hipStream_t st, ReduceDesc* deferred) {
     if (deferred) deferred->splits = 0;
     if (dtype == LPM_BF16 && fc_skinny_ok(g)) return fc_wgrad(g, x, dz, dw, dbias, rscale, accumulate, st);
-    if (dtype == LPM_BF16 && wgrad_tr_ok(g)) return wgrad_tr(g, x, dz, dw, dbias, rscale, accumulate, ws, st, deferred);
-    if (dtype == LPM_BF16 && mfma_wgrad_ok(g)) return mfma_conv_wgrad(g, x, dz, dw, dbias, rscale, accumulate, ws, st, deferred);
+    if (wgrad_mm_ok(dtype, fc_view(g))) return wgrad_mm_launch(dtype, fc_view(g), x, dz, dw, dbias, rscale, accumulate, ws, st, deferred);
     if (dtype == LPM_BF16 && mfma_wgrad_flat_ok(g)) return mfma_conv_wgrad_flat(g, x, dz, dw, dbias, rscale, accumulate, ws, st);
     if (dbias || rscale) return hipErrorInvalidValue;      // callers ask wgrad_fuses_bias first
     return conv_wgrad_generic_launch(dtype, g, x, dz, dw, accumulate, ws, st);
@@ -117,7 +127,7 @@ hipError_t launch_conv_wgrad(int dtype, const ConvGeom& g, const void* x, const 
 bool wgrad_staged_ok(int dtype, const ConvGeom& g) {
     if (dtype != LPM_BF16) return false;
     if (fc_staged_ok(g)) return true;
-    if (fc_skinny_ok(g) || !mfma_wgrad_ok(g)) return false;
+    if (fc_skinny_ok(g) || !wgrad_mm_ok(dtype, fc_view(g))) return false;
     const int64_t dw_rmw = (int64_t)g.Cout * g.K() * 8, staged = (g.rows_in() * g.Cin + g.rows_out() * g.Cout) * 2;
     return (int64_t)g.Cout * g.K() >= 32768 && dw_rmw >= 6 * staged;
 }

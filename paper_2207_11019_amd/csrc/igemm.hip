@@ -1,0 +1,874 @@
+// Implicit-GEMM contractions for gfx950 on the matrix cores: convolution forward (eq. 1) and data gradient (eq. 9) of
+// bfloat16 and float layers, two- and three-dimensional, fp32 accumulation.
+//
+//   C[M][N] = A[M][K] * B[N][K]^T
+//   forward  rows = output pixels, A gathered from x  [m][D][H][W][Cin],    B = w  [Cout][taps][Cin]
+//   dgrad    rows = input pixels,  A gathered from dz [m][Do][Ho][Wo][Cout], B = wt [Cin][taps][Cout] (bf16), or, for float
+//            layers, which keep no transposed copy, w [Cout][taps][Cin] read with its reduction index outermost
+//   K runs over (filter tap, channel).  A strided data gradient goes by residue class (d, h, w modulo the stride) of the
+//   input pixel: a class meets the taps of matching parity only, and its rows are written back to their pixels.
+//
+// Structure.  A K tile is 128 bytes of K (64 bf16 or 32 float values) of BM rows of A and BN rows of B, copied straight from
+// global memory to LDS (buffer_load ... lds: no registers, no LDS stores), through a ring of NST stages with one workgroup
+// barrier per tile.  LDS rows are 128 bytes without padding; chunk c (16 bytes) of row r lies at position c ^ (r % 8), so the
+// operand reads of a wavefront (one chunk of 32 consecutive rows per half) fall on distinct banks.  Out-of-range chunks --
+// padding taps, ragged rows -- load zeros through the buffer bounds check.  Whether a row meets a tap is one bit test against
+// a mask made once per row.
+// A channel count that is a multiple of 128 bytes lets a whole K tile lie in one tap (UNI): the tap is wave-uniform.
+// Otherwise every lane follows its own chunk's tap through a table in LDS, so any multiple of 16 bytes of channels works.
+//
+// The matrix instructions are v_mfma_f32_32x32x16_bf16 (a lane supplies 8 consecutive K values of row lane % 32) and
+// v_mfma_f32_32x32x2_f32 (one value; four instructions share a 16-byte chunk, the K order inside a chunk being the same
+// permutation for both operands).  The weights are the instruction's first operand: accumulator element i of a lane is output
+// channel (i/4)*8 + (lane/32)*4 + i%4 of pixel lane % 32, four consecutive channels at a time.
+#include "lpm_internal.h"
+#include "elem.h"
+#include "lds_dma.h"
+#include <algorithm>
+
+namespace lpm {
+
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+
+constexpr unsigned OOB = 0xffffffffu;
+
+enum { MODE_FWD = 0, MODE_DGRAD = 1 /* stride 1 */, MODE_DGRAD_S = 2 /* stride 2..4, by residue class */ };
+
+constexpr int MAX_TAB = 128;              // taps a layer without whole K tiles per tap may have
+
+struct IgemmArgs {
+    const void* A;
+    const void* B;
+    void* C;                // output [M][N]
+    float* part;            // split K: fp32 partial tiles
+    unsigned* count;        // split K: blocks that have stored theirs, per output tile
+    const float* scale;
+    const float* bias;
+    const void* add;
+    const void* mask;       // data gradient: zero the result where this tensor (the producer's output) is <= 0
+    const float* mscale;    // data gradient: then multiply by the producer's per-channel scale
+    void* C2;               // data gradient: the masked, not yet scaled result also goes here (the producer's shortcut), or NULL
+    const float* c2scale;   // ... times this per-channel factor (NULL: 1)
+    int acc2;               // ... added to what C2 holds
+    int relu, accumulate;
+    int M, N;
+    int Hi, Wi, Di, Ci;     // extent of the gathered tensor
+    int Hr, Wr, Dr;         // extent of the row space
+    int Kh, Kw, Kd, stride, pad, pad_d;
+    FastDiv dWr, dHr, dDr, dCc;       // row decoding; chunks per tap
+    unsigned a_bytes, b_bytes, b_pitch;
+    int kt_total, kt_per_split, splits;
+    int free_taps;          // no tap can leave the image: no mask bits needed
+    int tiles_m;            // (strided) row tiles over all classes
+    int cls_tile0[17];      // strided data gradient: first row tile of class c = (pd * s + ph) * s + pw
+    const uint16_t* pool_x; // stride-1 data gradient routed through a 2x2 max-pooling (see UnpoolDesc): its input [m][2*Hr][2*Wr][N]
+    uint16_t* pool_dst;
+    int pool_acc, pool_mask;
+    uint16_t* fwd_pool;     // forward: also store the 2x2 max-pooling of C, [m][Hr/2][Wr/2][N] (Wr = 2, 4, 8 or 16)
+};
+
+// ---- eight consecutive channels of a row -----------------------------------------------------------
+template <typename E> struct Raw8;
+template <> struct Raw8<bf16_t> { uint4 v; };
+template <> struct Raw8<float> { float4 lo, hi; };
+__device__ __forceinline__ Raw8<bf16_t> ld_raw8(const bf16_t* p) { return {*reinterpret_cast<const uint4*>(p)}; }
+__device__ __forceinline__ Raw8<float> ld_raw8(const float* p) {
+    return {*reinterpret_cast<const float4*>(p), *reinterpret_cast<const float4*>(p + 4)};
+}
+__device__ __forceinline__ void un8(const Raw8<bf16_t>& r, float (&f)[8]) {
+    const uint32_t w[4] = {r.v.x, r.v.y, r.v.z, r.v.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) { f[2 * k] = bf2f((uint16_t)(w[k] & 0xffffu)); f[2 * k + 1] = bf2f((uint16_t)(w[k] >> 16)); }
+}
+__device__ __forceinline__ void un8(const Raw8<float>& r, float (&f)[8]) {
+    f[0] = r.lo.x; f[1] = r.lo.y; f[2] = r.lo.z; f[3] = r.lo.w; f[4] = r.hi.x; f[5] = r.hi.y; f[6] = r.hi.z; f[7] = r.hi.w;
+}
+__device__ __forceinline__ void st8(bf16_t* p, const float (&f)[8]) {
+    *reinterpret_cast<uint4*>(p) = make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7]));
+}
+__device__ __forceinline__ void st8(float* p, const float (&f)[8]) {
+    *reinterpret_cast<float4*>(p) = make_float4(f[0], f[1], f[2], f[3]);
+    *reinterpret_cast<float4*>(p + 4) = make_float4(f[4], f[5], f[6], f[7]);
+}
+
+// Strided data gradient: pixel index (in the full tensor) of row `row` of the residue class (pd, ph, pw).
+__device__ __forceinline__ int class_pixel(const IgemmArgs& p, int row, int Hc, int Wc, int ph, int pw, int Dc, int pd) {
+    const int wq = row % Wc, t = row / Wc, hq = t % Hc;
+    int n = t / Hc, img = n;
+    if (p.Dr > 1) { const int dq = n % Dc; n /= Dc; img = n * p.Dr + dq * p.stride + pd; }
+    return (img * p.Hr + hq * p.stride + ph) * p.Wr + wq * p.stride + pw;
+}
+
+// One wavefront's 32 x (32*NIW) piece of the output, held in its private LDS area `tile` (rows of 32*NIW + 4 floats): a lane
+// takes 8 channels of a row at a time, so every tensor access is 16 (float: 32) bytes.  The operands of all the lane's
+// pieces are requested before the first is used.
+template <typename E, int NIW, int MODE>
+__device__ __forceinline__ void store_piece(const IgemmArgs& p, float* tile, int row0, int col0, int rows, int lane,
+                                            int Hc, int Wc, int ph, int pw, int Dc, int pd) {
+    constexpr int PITCH = NIW * 32 + 4, CPR = NIW * 4, RPP = 64 / CPR, NP = 32 / RPP;
+    const int ch = (lane % CPR) * 8, col = col0 + ch;
+    const E* add = (const E*)p.add;
+    const E* msk = (const E*)p.mask;
+    E* out = (E*)p.C;
+    E* out2 = (E*)p.C2;
+    if (p.N & 7) {                           // ragged rows: element by element
+#pragma unroll 1
+        for (int q = 0; q < NP; ++q) {
+            const int r = q * RPP + lane / CPR, row = row0 + r;
+            if (row >= rows) continue;
+            const size_t prow = MODE == MODE_DGRAD_S ? (size_t)class_pixel(p, row, Hc, Wc, ph, pw, Dc, pd) : (size_t)row;
+#pragma unroll 1
+            for (int k = 0; k < 8 && col + k < p.N; ++k) {
+                const size_t o = prow * p.N + col + k;
+                float v = tile[r * PITCH + ch + k];
+                if (p.scale) v *= p.scale[col + k];
+                if (p.bias) v += p.bias[col + k];
+                if (add) v += ld(add, o);
+                if (p.accumulate) v += ld(out, o);
+                if (p.relu) v = fmaxf(v, 0.f);
+                if (msk && !(ld(msk, o) > 0.f)) v = 0.f;
+                if (out2) {
+                    const float u = p.c2scale ? v * p.c2scale[col + k] : v;
+                    st(out2, o, p.acc2 ? u + ld(out2, o) : u);
+                }
+                if (p.mscale) v *= p.mscale[col + k];
+                st(out, o, v);
+            }
+        }
+        return;
+    }
+    const bool cok = col < p.N;
+    float sc[8], bi[8], ms[8], c2[8];
+    auto vec = [&](const float* q, float (&d)[8], float fill) __attribute__((always_inline)) {
+        if (q && cok) un8(ld_raw8(q + col), d);
+        else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) d[k] = fill;
+        }
+    };
+    vec(p.scale, sc, 1.f); vec(p.bias, bi, 0.f); vec(p.mscale, ms, 1.f); vec(p.c2scale, c2, 1.f);
+    if (MODE == MODE_DGRAD && p.pool_x) {
+        // gradient of a 2x2 max-pooling output: to the first maximum of the window (row-major), through the producer's ReLU
+        // and scale where asked; all four window positions are written
+        if constexpr (sizeof(E) == 2) {
+#pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                const int r = q * RPP + lane / CPR, row = row0 + r;
+                if (row >= rows || !cok) continue;
+                const int t = div_by(row, p.dWr), wq = row - t * p.Wr, n = div_by(t, p.dHr), hq = t - n * p.Hr;
+                const size_t base = ((size_t)(n * 2 * p.Hr + 2 * hq) * (2 * p.Wr) + 2 * wq) * p.N + col;
+                const size_t off[4] = {0, (size_t)p.N, (size_t)2 * p.Wr * p.N, (size_t)2 * p.Wr * p.N + p.N};
+                Raw8<bf16_t> xr[4], dr[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    xr[k] = ld_raw8((const bf16_t*)p.pool_x + base + off[k]);
+                    if (p.pool_acc) dr[k] = ld_raw8((const bf16_t*)p.pool_dst + base + off[k]);
+                }
+                float x[4][8], o[4][8], v[8];
+                un8(ld_raw8(tile + r * PITCH + ch), v);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    un8(xr[k], x[k]);
+                    if (p.pool_acc) un8(dr[k], o[k]);
+                    else {
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) o[k][j] = 0.f;
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float mx = fmaxf(fmaxf(x[0][j], x[1][j]), fmaxf(x[2][j], x[3][j]));
+                    float g = bf2f(f2bf(v[j]));          // the value a stored gradient of the pooling output would have had
+                    if (p.pool_mask && !(mx > 0.f)) g = 0.f;
+                    g *= ms[j];
+                    bool found = false;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const bool hit = !found && x[k][j] == mx;
+                        found = found || hit;
+                        o[k][j] += hit ? g : 0.f;
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) st8((bf16_t*)p.pool_dst + base + off[k], o[k]);
+            }
+        }
+        return;
+    }
+    size_t o[NP];
+    bool live[NP];
+    Raw8<E> ra[NP], rc[NP], rm[NP], r2[NP];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+        const int row = row0 + q * RPP + lane / CPR;
+        live[q] = row < rows && cok;
+        const int prow = MODE == MODE_DGRAD_S && live[q] ? class_pixel(p, row, Hc, Wc, ph, pw, Dc, pd) : row;
+        o[q] = live[q] ? (size_t)prow * p.N + col : 0;
+    }
+#pragma unroll
+    for (int q = 0; q < NP; ++q) if (add) ra[q] = ld_raw8(add + o[q]);
+#pragma unroll
+    for (int q = 0; q < NP; ++q) if (p.accumulate) rc[q] = ld_raw8((const E*)out + o[q]);
+#pragma unroll
+    for (int q = 0; q < NP; ++q) if (msk) rm[q] = ld_raw8(msk + o[q]);
+#pragma unroll
+    for (int q = 0; q < NP; ++q) if (out2 && p.acc2) r2[q] = ld_raw8((const E*)out2 + o[q]);
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+        const int r = q * RPP + lane / CPR;
+        float v[8], t[8];
+        un8(ld_raw8(tile + r * PITCH + ch), v);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = v[k] * sc[k] + bi[k];
+        if (add) { un8(ra[q], t);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] += t[k]; }
+        if (p.accumulate) { un8(rc[q], t);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] += t[k]; }
+        if (p.relu) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = fmaxf(v[k], 0.f); }
+        if (msk) { un8(rm[q], t);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = t[k] > 0.f ? v[k] : 0.f; }
+        if (out2) {
+            float u[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) u[k] = v[k] * c2[k];
+            if (p.acc2) { un8(r2[q], t);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) u[k] += t[k]; }
+            if (live[q]) st8(out2 + o[q], u);
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] *= ms[k];
+        if (live[q]) st8(out + o[q], v);
+        if (MODE == MODE_FWD && p.fwd_pool) {
+            if constexpr (sizeof(E) == 2) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = bf2f(f2bf(v[k]));
+                st8(tile + r * PITCH + ch, v);
+            }
+        }
+    }
+    if (MODE == MODE_FWD && p.fwd_pool) {
+        // the piece's 32 rows are whole pairs of image rows: eight pooling windows of rows (r, r+1, r+Wr, r+Wr+1)
+        if constexpr (sizeof(E) == 2) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const int w = lane / CPR;
+            if (w < 8) {
+                const int hw = p.Wr >> 1, py = w / hw, px = w - py * hw, r = 2 * py * p.Wr + 2 * px;
+                if (row0 + r < rows && cok) {
+                    float a[8], b[8], c[8], d[8];
+                    un8(ld_raw8(tile + r * PITCH + ch), a);
+                    un8(ld_raw8(tile + (r + 1) * PITCH + ch), b);
+                    un8(ld_raw8(tile + (r + p.Wr) * PITCH + ch), c);
+                    un8(ld_raw8(tile + (r + p.Wr + 1) * PITCH + ch), d);
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) a[k] = fmaxf(fmaxf(a[k], b[k]), fmaxf(c[k], d[k]));
+                    st8((bf16_t*)p.fwd_pool + (size_t)((row0 >> 2) + w) * p.N + col, a);
+                }
+            }
+        }
+    }
+}
+
+__device__ __forceinline__ unsigned tap_bits(int lo, int hi) { return hi > lo ? (1u << hi) - (1u << lo) : 0u; }
+
+// partial tiles pass between blocks on different XCDs: stores go through to memory, loads do not hit a stale line
+constexpr int AUX_AGENT = 16;
+
+template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, bool UNI, bool BT, int OCC>
+__global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmArgs p) {
+    constexpr int ES = sizeof(E), T = WGM * WGN * 64, RS = T / 8;             // rows a load step covers
+    constexpr int WTM = BM / WGM, WTN = BN / WGN, MI = WTM / 32, NI = WTN / 32;
+    constexpr int A_LD = BM / RS, B_LD = BN / RS, LPT = A_LD + B_LD;
+    constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
+    static_assert(!BT || ES == 4, "float data gradient only");
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];      // NST stages [+ tap table]
+    int4* tab = reinterpret_cast<int4*>(lds + NST * STAGE);
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nt = (p.N + BN - 1) / BN;
+    // (strided: the residue classes differ in work, so their tiles stay in launch order, which deals them to the XCDs in turn)
+    const int tile = MODE == MODE_DGRAD_S ? (int)blockIdx.x : xcd_remap(blockIdx.x, gridDim.x);
+    const int tm = tile / nt, n0 = (tile - tm * nt) * BN;
+    int m0 = tm * BM;
+    int kt0 = blockIdx.z * p.kt_per_split, kt1 = min(p.kt_total, kt0 + p.kt_per_split);
+    int nkd = p.Kd, nkh = p.Kh, nkw = p.Kw, kd0 = 0, kh0 = 0, kw0 = 0, kstep = 1;      // taps visited: first and count per axis
+    int ph = 0, pw = 0, pd = 0, Hc = p.Hr, Wc = p.Wr, Dc = p.Dr, rows = p.M;           // residue class of the rows and its extent
+    int oh = p.pad, ow = p.pad, od = p.pad_d;
+    const int Cc = p.Ci * ES / 16;                                                      // chunks per tap
+    if (MODE == MODE_DGRAD_S) {
+        const int s_ = p.stride, ncls = (p.Dr > 1 ? s_ : 1) * s_ * s_;
+        int c = 0;
+        while (c + 1 < ncls && tm >= p.cls_tile0[c + 1]) ++c;
+        pd = c / (s_ * s_);
+        ph = (c - pd * s_ * s_) / s_; pw = c - (pd * s_ + ph) * s_;
+        Hc = (p.Hr - ph + s_ - 1) / s_; Wc = (p.Wr - pw + s_ - 1) / s_;
+        Dc = p.Dr > 1 ? (p.Dr - pd + s_ - 1) / s_ : 1;
+        rows = (p.M / (p.Dr * p.Hr * p.Wr)) * Dc * Hc * Wc;
+        m0 = (tm - p.cls_tile0[c]) * BM;
+        kstep = s_;
+        kh0 = (ph + p.pad) % s_; kw0 = (pw + p.pad) % s_;
+        kd0 = p.Dr > 1 ? (pd + p.pad_d) % s_ : 0;
+        nkh = kh0 < p.Kh ? (p.Kh - kh0 + s_ - 1) / s_ : 0;
+        nkw = kw0 < p.Kw ? (p.Kw - kw0 + s_ - 1) / s_ : 0;
+        nkd = p.Dr > 1 ? (kd0 < p.Kd ? (p.Kd - kd0 + s_ - 1) / s_ : 0) : 1;
+        // output pixel = class coordinate + (ph + pad - kh) / stride, an exact quotient that falls by one per visited tap
+        oh = (ph + p.pad - kh0) / s_; ow = (pw + p.pad - kw0) / s_; od = p.Dr > 1 ? (pd + p.pad_d - kd0) / s_ : 0;
+        const int kt_cls = (nkd * nkh * nkw * Cc + 7) / 8, per = (kt_cls + (int)gridDim.z - 1) / (int)gridDim.z;
+        kt0 = blockIdx.z * per;
+        kt1 = min(kt_cls, kt0 + per);
+    }
+    const int ntap = nkd * nkh * nkw, nk = max(0, kt1 - kt0);
+    const unsigned tapC = (unsigned)p.Ci * ES;                       // bytes of one tap's channels
+    // byte steps of one visited tap along w, h, d: A moves with the filter (forward) or against it (data gradient)
+    constexpr int SG = MODE == MODE_FWD ? 1 : -1;
+    const unsigned aW = (unsigned)SG * tapC, aH = aW * (unsigned)p.Wi, aD = aH * (unsigned)p.Hi;
+    // (BT: B's rows are the gathered channels, a tap is a column offset)
+    const unsigned bTap = BT ? (unsigned)p.N * ES : tapC;
+    const unsigned bW = bTap * kstep, bH = bW * (unsigned)p.Kw, bD = bH * (unsigned)p.Kh;
+    const unsigned b0 = bTap * (unsigned)((kd0 * p.Kh + kh0) * p.Kw + kw0);
+
+    // A's buffer starts `bias` bytes early, so that the offset of a row's tap (0,0) -- outside the image where there is
+    // padding -- and the tap's own are both non-negative: lane offset + wave-uniform offset.  (Chunks whose tap misses the
+    // image never use them.)
+    const unsigned span = (unsigned)((((nkd - 1) * p.Hi + (nkh - 1)) * p.Wi + (nkw - 1))) * tapC;      // from the first tap to the last
+    const unsigned bias = MODE == MODE_FWD ? (unsigned)((od * p.Hi + oh) * p.Wi + ow) * tapC : (ntap ? span : 0u);
+    const unsigned aoff0 = MODE == MODE_FWD ? 0u : (ntap ? span : 0u);           // wave-uniform offset of the first tap
+    u32x4_ rsA = buffer_words((const unsigned char*)p.A - bias, p.a_bytes + bias), rsB = buffer_words(p.B, p.b_bytes);
+
+    if (!UNI) {
+        for (int t = tid; t < ntap; t += T) {
+            const int td = t / (nkh * nkw), r = t - td * (nkh * nkw), th = r / nkw, tw = r - th * nkw;
+            tab[t] = make_int4((int)(aoff0 + td * aD + th * aH + tw * aW), (int)(b0 + td * bD + th * bH + tw * bW),
+                               p.free_taps ? 1 : (int)((1u << (24 + td)) | (1u << (12 + th)) | (1u << tw)), 0);
+        }
+    }
+    // ---- loader state.  Lane l of a load fills chunk position l % 8 of row l / 8: it fetches chunk (l % 8) ^ (l / 8)
+    const int lrow = lane >> 3, kcol = (lane & 7) ^ lrow;
+    unsigned a_base[A_LD], a_msk[A_LD], b_off[B_LD];
+#pragma unroll
+    for (int i = 0; i < A_LD; ++i) {
+        const int row = m0 + i * RS + wave * 8 + lrow;
+        const bool ok = row < rows;
+        const int rr = ok ? row : 0;
+        int wq, hq, n, dq = 0;
+        if (MODE == MODE_DGRAD_S) {
+            wq = rr % Wc;
+            const int t = rr / Wc;
+            hq = t % Hc; n = t / Hc;
+            if (p.Dr > 1) { const int ns = n / Dc; dq = n - ns * Dc; n = ns; }
+        } else {
+            const int t = div_by(rr, p.dWr);
+            wq = rr - t * p.Wr;
+            n = div_by(t, p.dHr);
+            hq = t - n * p.Hr;
+            if (p.Dr > 1) { const int ns = div_by(n, p.dDr); dq = n - ns * p.Dr; n = ns; }
+        }
+        int h0, w0, d0;
+        unsigned m;
+        if (MODE == MODE_FWD) {
+            h0 = hq * p.stride - oh; w0 = wq * p.stride - ow; d0 = dq * p.stride - od;
+            m = (tap_bits(max(0, -d0), min(nkd, p.Di - d0)) << 24) | (tap_bits(max(0, -h0), min(nkh, p.Hi - h0)) << 12) |
+                tap_bits(max(0, -w0), min(nkw, p.Wi - w0));
+        } else {
+            h0 = hq + oh; w0 = wq + ow; d0 = dq + od;
+            m = (tap_bits(max(0, d0 - p.Di + 1), min(nkd, d0 + 1)) << 24) | (tap_bits(max(0, h0 - p.Hi + 1), min(nkh, h0 + 1)) << 12) |
+                tap_bits(max(0, w0 - p.Wi + 1), min(nkw, w0 + 1));
+        }
+        a_msk[i] = ok ? (p.free_taps ? 0xffffffffu : m) : 0u;
+        a_base[i] = (unsigned)(((n * p.Di + d0) * p.Hi + h0) * p.Wi + w0) * tapC + (MODE == MODE_FWD ? bias : 0u) + (UNI ? (unsigned)kcol * 16u : 0u);
+    }
+    // BT: chunk (lane) of the K tile [32 reduction rows][BN channels]
+    int bt_k[BT ? B_LD : 1], bt_t[BT ? B_LD : 1];          // channel and (non-UNI) tap of the reduction row
+    const int kt_ch = 128 / ES;
+#pragma unroll
+    for (int i = 0; i < B_LD; ++i) {
+        if (BT) {
+            const int idx = i * T + tid, kr = idx / (BN / 4), cc = idx - kr * (BN / 4);
+            b_off[i] = n0 + cc * 4 < p.N ? (unsigned)(n0 + cc * 4) * ES : OOB;
+            const int k = kt0 * kt_ch + kr;
+            bt_t[i] = k / p.Ci; bt_k[i] = k - bt_t[i] * p.Ci;
+        } else {
+            b_off[i] = (unsigned)(n0 + i * RS + wave * 8 + lrow) * p.b_pitch + (UNI ? (unsigned)kcol * 16u : 0u);       // (rows past N lie past the buffer's end)
+        }
+    }
+    // cursor of the next K tile: UNI: tap (wave-uniform) and byte offset in its channels; else the lane's chunk and its tap
+    int c_td = 0, c_th = 0, c_tw = 0;
+    unsigned c_c = 0;
+    int l_t = 0, l_c = 0;
+    if (UNI) {
+        const int per = Cc / 8, t = kt0 / per;
+        c_c = (unsigned)(kt0 - t * per) * 128u;
+        const int td = t / max(1, nkh * nkw), r = t - td * nkh * nkw;
+        c_td = td; c_th = r / max(1, nkw); c_tw = r - c_th * nkw;
+    } else {
+        const int k = kt0 * 8 + kcol;
+        l_t = div_by(k, p.dCc); l_c = k - l_t * Cc;
+        __syncthreads();                    // the tap table
+    }
+    const int step_t = UNI ? 0 : div_by(8, p.dCc), step_c = UNI ? 0 : 8 - step_t * Cc;
+
+    // UNI: the A offsets of the current tap, with the rows that miss the image out of range
+    unsigned a_cur[A_LD], s_a = 0, s_b = 0;
+    auto set_tap = [&]() __attribute__((always_inline)) {
+        s_a = aoff0 + c_td * aD + c_th * aH + c_tw * aW;
+        s_b = b0 + c_td * bD + c_th * bH + c_tw * bW;
+        const unsigned bit = p.free_taps ? 1u : (1u << (24 + c_td)) | (1u << (12 + c_th)) | (1u << c_tw);
+#pragma unroll
+        for (int i = 0; i < A_LD; ++i) a_cur[i] = (a_msk[i] & bit) == bit ? a_base[i] : OOB;
+    };
+    if (UNI) set_tap();
+    // Issues the loads of the next K tile into a stage.  Past the last tile the buffers count as empty: the stage fills with
+    // zeros, the number of loads in flight stays what the waits assume, and the loop below needs no special case at its end.
+    // The loads come in four parts, so that the loop below can put each behind a few matrix instructions.
+    int left = nk;
+    unsigned la = 0, lb = 0;                 // this tile's wave-uniform offsets (UNI), or the lane's (with the tap's bits)
+    unsigned lbit = 0;
+    bool lin = false;
+    auto issue = [&](int st, int part) __attribute__((always_inline)) {
+        unsigned char* sp = lds + st * STAGE + wave * 1024;
+        if (part == 0) {
+            const bool live = left > 0;
+            --left;
+            rsA.z = live ? p.a_bytes + bias : 0u;
+            rsB.z = live ? p.b_bytes : 0u;
+            if (UNI) {
+                la = live ? s_a + c_c : 0u;
+                lb = live && !BT ? s_b + c_c : 0u;
+            } else {
+                lin = l_t < ntap;
+                const int4 e = tab[lin ? l_t : 0];
+                lbit = (unsigned)e.z;
+                la = (unsigned)e.x + (unsigned)l_c * 16u;
+                lb = (unsigned)e.y + (unsigned)l_c * 16u;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < A_LD; ++i) {
+            if (i * 4 / LPT != part) continue;
+            if (UNI) load_to_lds16s(rsA, sp + i * RS * 128, a_cur[i], la);
+            else load_to_lds16(rsA, sp + i * RS * 128, (lin & ((a_msk[i] & lbit) == lbit)) ? a_base[i] + la : OOB);
+        }
+#pragma unroll
+        for (int i = 0; i < B_LD; ++i) {
+            if ((i + A_LD) * 4 / LPT != part) continue;
+            unsigned char* d = sp + A_BYTES + i * RS * 128;
+            if (UNI && BT) {
+                load_to_lds16(rsB, d, b_off[i] == OOB ? OOB : b_off[i] + s_b + (c_c / ES + (unsigned)((i * T + tid) / (BN / 4))) * p.b_pitch);
+            } else if (UNI) {
+                load_to_lds16s(rsB, d, b_off[i], lb);
+            } else if (BT) {
+                const bool bl = (bt_t[i] < ntap) & (b_off[i] != OOB);
+                const unsigned tbb = (unsigned)tab[bt_t[i] < ntap ? bt_t[i] : 0].y;
+                load_to_lds16(rsB, d, bl ? b_off[i] + tbb + (unsigned)bt_k[i] * p.b_pitch : OOB);
+                bt_k[i] += kt_ch;
+                while (bt_k[i] >= p.Ci) { bt_k[i] -= p.Ci; ++bt_t[i]; }
+            } else load_to_lds16(rsB, d, lin ? b_off[i] + lb : OOB);
+        }
+        if (part == 3) {
+            if (UNI) {
+                c_c += 128;
+                if (c_c == tapC) {
+                    c_c = 0;
+                    if (++c_tw == nkw) { c_tw = 0; if (++c_th == nkh) { c_th = 0; ++c_td; } }
+                    set_tap();
+                }
+            } else {
+                l_t += step_t; l_c += step_c;
+                if (l_c >= Cc) { l_c -= Cc; ++l_t; }
+            }
+        }
+    };
+
+    f32x16 acc[MI][NI];
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.f;
+
+    const int wm = wave / WGN, wn = wave - wm * WGN;
+    // operand addresses: row lane % 32 of the wavefront's part, chunk 2*ks + lane/32 of the K tile
+    const int rl = lane & 31, kh_ = lane >> 5;
+    const unsigned rowA = (unsigned)(wm * WTM + rl) * 128u, rowB = (unsigned)(A_BYTES + (wn * WTN + rl) * 128);
+    const unsigned colBT = (unsigned)(A_BYTES + (wn * WTN + rl) * 4);
+
+    // Operands of one K tile, 16 bytes per lane and step.  Two sets: while the matrix cores work on one tile the next one is
+    // read from LDS, and the tiles behind it are on their way there -- with one wavefront per SIMD (a launch of about one block
+    // per CU) nothing else hides the LDS latency.
+    struct Frag { uint4 a[4][MI], b[4][NI]; };
+    auto read = [&](Frag& f, int st, int ks) __attribute__((always_inline)) {
+        const unsigned char* sp = lds + st * STAGE;
+        {
+            const unsigned x = (unsigned)(((ks * 2 + kh_) ^ (lane & 7)) << 4);
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) f.a[ks][mi] = *reinterpret_cast<const uint4*>(sp + rowA + x + mi * 4096);
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) {
+                if (BT) {
+                    const unsigned char* q = sp + colBT + (ks * 2 + kh_) * 4 * (BN * 4) + ni * 128;
+                    f.b[ks][ni] = make_uint4(*reinterpret_cast<const unsigned*>(q), *reinterpret_cast<const unsigned*>(q + BN * 4),
+                                             *reinterpret_cast<const unsigned*>(q + 2 * BN * 4), *reinterpret_cast<const unsigned*>(q + 3 * BN * 4));
+                } else f.b[ks][ni] = *reinterpret_cast<const uint4*>(sp + rowB + x + ni * 4096);
+            }
+        }
+    };
+    auto multiply = [&](const Frag& f, int ks) __attribute__((always_inline)) {
+        {
+            if constexpr (ES == 2) {
+#pragma unroll
+                for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < NI; ++ni)
+                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.b[ks][ni]), __builtin_bit_cast(bf16x8, f.a[ks][mi]), acc[mi][ni], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                        for (int ni = 0; ni < NI; ++ni) {
+                            const unsigned a = j == 0 ? f.a[ks][mi].x : j == 1 ? f.a[ks][mi].y : j == 2 ? f.a[ks][mi].z : f.a[ks][mi].w;
+                            const unsigned b = j == 0 ? f.b[ks][ni].x : j == 1 ? f.b[ks][ni].y : j == 2 ? f.b[ks][ni].z : f.b[ks][ni].w;
+                            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(b), __uint_as_float(a), acc[mi][ni], 0, 0, 0);
+                        }
+            }
+        }
+    };
+    // A tile has landed once only the loads of the NST - 2 tiles behind it are outstanding; every wavefront's earlier operand
+    // reads are complete then, too, so the stage they came from may be loaded again after the barrier.
+    auto meet = [&]() __attribute__((always_inline)) {
+        LPM_WAIT_VM(LPT * (NST - 2));
+        __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt(0)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    if (nk > 0) {
+#pragma unroll
+        for (int i = 0; i < NST - 1; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) issue(i, q);
+        Frag f0, f1;
+        meet();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) issue(NST - 1, q);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) read(f0, 0, ks);
+        int st = 0;                              // stage of the tile being multiplied
+        auto half = [&](const Frag& cur, Frag& nxt) __attribute__((always_inline)) {
+            const int st1 = st == NST - 1 ? 0 : st + 1;
+            meet();
+            read(nxt, st1, 0);
+            // A quarter of the next tile's reads and of the loads behind it go with a quarter of this one's products: the LDS,
+            // the address arithmetic and the matrix cores work side by side (all reads first, and the products would wait
+            // for the LDS queue to drain; all loads first, and the matrix cores would idle meanwhile).
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (ks < 3) read(nxt, st1, ks + 1);
+                multiply(cur, ks);
+                issue(st, ks);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            st = st1;
+        };
+        for (int it = 0; it < nk; it += 2) {     // (an odd count ends with a tile of zeros)
+            half(f0, f1);
+            half(f1, f0);
+        }
+        LPM_WAIT_VM(0);
+    }
+    __syncthreads();                            // the stages are dead: the epilogue takes them
+
+    if (p.splits > 1) {
+        // Every block of an output tile stores its partial sums (in accumulator order, 16 bytes per lane), and the one that
+        // arrives last adds them in split order and carries on with the epilogue.  Stores and loads of the partials bypass the
+        // XCD's own L2 (scope "agent"), so no cache is written back or invalidated: a store counted as done has reached memory.
+        const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(p.part + (size_t)tile * p.splits * (BM * BN), 0, (unsigned)(p.splits * BM * BN * 4), 0x00020000);
+        const unsigned mine = (unsigned)(wave * (MI * NI * 1024) + lane * 4) * 4u;
+        const int me = blockIdx.z;
+        typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const u4 v = {__float_as_uint(acc[mi][ni][4 * q]), __float_as_uint(acc[mi][ni][4 * q + 1]),
+                                  __float_as_uint(acc[mi][ni][4 * q + 2]), __float_as_uint(acc[mi][ni][4 * q + 3])};
+                    __builtin_amdgcn_raw_buffer_store_b128(v, rp, mine + (unsigned)(((mi * NI + ni) * 4 + q) * 1024), (unsigned)(me * BM * BN * 4), AUX_AGENT);
+                }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        int* flag = reinterpret_cast<int*>(lds);
+        if (tid == 0) *flag = (int)__hip_atomic_fetch_add(p.count + tile, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (*flag != p.splits - 1) return;
+        __syncthreads();                        // (flag is read before the area is written again)
+        if (tid == 0) __hip_atomic_store(p.count + tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) {
+                f32x16 sum;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) sum[i] = 0.f;
+                for (int s0 = 0; s0 < p.splits; s0 += 4) {      // four splits' loads before the first add
+                    u4 v[4][4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (s0 + k < p.splits) {
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                v[k][q] = __builtin_amdgcn_raw_buffer_load_b128(rp, mine + (unsigned)(((mi * NI + ni) * 4 + q) * 1024), (unsigned)((s0 + k) * BM * BN * 4), AUX_AGENT);
+                        }
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (s0 + k < p.splits) {
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                sum[4 * q] += __uint_as_float(v[k][q].x); sum[4 * q + 1] += __uint_as_float(v[k][q].y);
+                                sum[4 * q + 2] += __uint_as_float(v[k][q].z); sum[4 * q + 3] += __uint_as_float(v[k][q].w);
+                            }
+                        }
+                }
+                acc[mi][ni] = sum;
+            }
+    }
+
+    // the wavefront's private staging area for the epilogue
+    float* piece = reinterpret_cast<float*>(lds) + wave * (32 * (NI * 32 + 4));
+    static_assert(WGM * WGN * 32 * (NI * 32 + 4) * 4 <= NST * STAGE, "staging fits the dead stages");
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<float4*>(piece + rl * (NI * 32 + 4) + ni * 32 + q * 8 + kh_ * 4) =
+                    make_float4(acc[mi][ni][4 * q], acc[mi][ni][4 * q + 1], acc[mi][ni][4 * q + 2], acc[mi][ni][4 * q + 3]);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        store_piece<E, NI, MODE>(p, piece, m0 + wm * WTM + mi * 32, n0 + wn * WTN, rows, lane, Hc, Wc, ph, pw, Dc, pd);
+    }
+}
+
+// --------------------------------------------------------------------------------------------------
+struct IgemmPlan { int tile; int splits, kt_total, kt_per; int64_t tiles; };
+// Output tiles.  64x64: the launches of a few hundred blocks that small micro-batches make.  128x64, 128x128: half the
+// operand traffic per product once there are enough tiles; 128x128 with eight wavefronts where there is about one tile per
+// CU (two wavefronts per SIMD hide each other's latencies), with four where there are two blocks per CU to do that.
+enum { TILE_64 = 0, TILE_128x64, TILE_128, TILE_128_8W };
+static const int TILE_M[4] = {64, 128, 128, 128}, TILE_N[4] = {64, 64, 128, 128};
+static int64_t tiles_of(int tile, int64_t M, int N) { return ((M + TILE_M[tile] - 1) / TILE_M[tile]) * ((N + TILE_N[tile] - 1) / TILE_N[tile]); }
+
+// kt: K tiles (of the longest residue class)
+static IgemmPlan plan_igemm(int es, int64_t M, int N, int kt) {
+    IgemmPlan pl{};
+    pl.tile = TILE_64;
+    if (es == 2) {
+        // Measured alone on MI355X (us, 64x64 / 128x64 / 128x128 / 128x128 of 8 wavefronts):
+        //   25088 x 256, K 2304: 51 / 46 / 39 / 43     12544 x 256, K 2304: 31 / 25 / 25 / 22      6272 x 512, K 2304: 33 / 25 / 27 / 24
+        //    3136 x 512, K 4608: 26 / 29 / 47 / 34      3136 x 256, K 2304: 13 / 17 / 24 / 21     17496 x 160, K  864: 19 / 15 / 21 / 26
+        const bool wide = N % 128 == 0 || N % 128 > 64;
+        const int64_t n128 = tiles_of(TILE_128, M, N);
+        if (wide && n128 >= 384) pl.tile = TILE_128;
+        else if (wide && n128 >= 180) pl.tile = TILE_128_8W;
+        else if (tiles_of(TILE_128x64, M, N) >= 384) pl.tile = TILE_128x64;
+    }
+    pl.kt_total = std::max(1, kt);
+    pl.tiles = tiles_of(pl.tile, M, N);
+    // about 8 K tiles per block while the tiles alone leave CUs idle: every split costs a pass over partial tiles
+    int s = std::max(1, (pl.kt_total + 4) / 8);
+    const int64_t cap = (M <= 64 ? 1024 : 320) / pl.tiles;
+    s = (int)std::min<int64_t>(s, std::max<int64_t>(1, cap));
+    pl.splits = std::max(1, std::min(s, pl.kt_total));
+    pl.kt_per = (pl.kt_total + pl.splits - 1) / pl.splits;
+    pl.splits = (pl.kt_total + pl.kt_per - 1) / pl.kt_per;
+    return pl;
+}
+
+static size_t plan_ws(const IgemmPlan& pl) {
+    return pl.splits > 1 ? LPM_COUNT_BYTES + (size_t)pl.tiles * pl.splits * TILE_M[pl.tile] * TILE_N[pl.tile] * sizeof(float) : 0;
+}
+
+// byte offsets below 4 GiB (with the rows of a tile past the last one), 31-bit element counts
+static bool fits(int dtype, const ConvGeom& g) {
+    const int64_t es = dtype == LPM_BF16 ? 2 : 4, lim = ((int64_t)1 << 32) - 1, e31 = (int64_t)1 << 31;
+    const int64_t in = g.rows_in() * g.Cin, out = g.rows_out() * g.Cout;
+    return in < e31 && out < e31 && in * es < lim && out * es < lim &&
+           (int64_t)(g.Cout + 256) * g.K() * es < lim && (int64_t)(g.Cin + 256) * g.taps() * g.Cout * es < lim;
+}
+static bool taps_fit(const ConvGeom& g, int ci, int es) {
+    return g.Kd <= 8 && g.Kh <= 12 && g.Kw <= 12 && (((int64_t)ci * es) % 128 == 0 || g.taps() <= MAX_TAB);
+}
+static bool fwd_free(const ConvGeom& g) { return g.pad == 0 && g.pad_d == 0; }      // no tap of a forward pass leaves the image
+
+bool mfma_fwd_ok(int dtype, const ConvGeom& g) {
+    const int es = dtype == LPM_BF16 ? 2 : 4;
+    if ((g.Cin * es) % 16 || !fits(dtype, g)) return false;
+    return taps_fit(g, g.Cin, es) || (fwd_free(g) && ((g.Cin * es) % 128 == 0 || g.taps() <= MAX_TAB));
+}
+// (a strided data gradient goes by residue classes of the image axes: stride^2 classes, stride^3 for a volume -- at most 16)
+bool mfma_dgrad_ok(int dtype, const ConvGeom& g) {
+    const int es = dtype == LPM_BF16 ? 2 : 4;
+    return (g.Cout * es) % 16 == 0 && (dtype == LPM_BF16 || g.Cin % 4 == 0) && g.stride <= 4 && (g.stride <= 2 || !g.is3d()) && fits(dtype, g) && taps_fit(g, g.Cout, es);
+}
+
+static int k_tiles(int64_t taps, int ci, int es) { return (int)((taps * ci * es / 16 + 7) / 8); }
+static IgemmPlan plan_fwd(int dtype, const ConvGeom& g) {
+    const int es = dtype == LPM_BF16 ? 2 : 4;
+    return plan_igemm(es, g.rows_out(), g.Cout, k_tiles(g.taps(), g.Cin, es));
+}
+// taps a residue class of a strided data gradient meets at most
+static IgemmPlan plan_dgrad(int dtype, const ConvGeom& g) {
+    const int es = dtype == LPM_BF16 ? 2 : 4, s = g.stride;
+    const int64_t taps = (int64_t)((g.Kd + s - 1) / s) * ((g.Kh + s - 1) / s) * ((g.Kw + s - 1) / s);
+    int64_t rows = g.rows_in();
+    if (s > 1) rows += 128 * (g.D > 1 ? s * s * s : s * s);          // (every class may end in a ragged tile)
+    return plan_igemm(es, rows, g.Cin, k_tiles(taps, g.Cout, es));
+}
+size_t mfma_fwd_ws_bytes(int dtype, const ConvGeom& g) { return plan_ws(plan_fwd(dtype, g)); }
+size_t mfma_dgrad_ws_bytes(int dtype, const ConvGeom& g) { return plan_ws(plan_dgrad(dtype, g)); }
+
+// whether the forward contraction of this layer can also store the 2x2 max-pooling of its output: the windows of 32
+// consecutive output pixels are whole ones
+bool mfma_fwd_pools(int dtype, const ConvGeom& g) {
+    return dtype == LPM_BF16 && mfma_fwd_ok(dtype, g) && !g.is3d() && !(g.Ho & 1) && (g.Wo == 2 || g.Wo == 4 || g.Wo == 8 || g.Wo == 16) && g.Cout % 8 == 0;
+}
+
+template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, bool UNI, bool BT, int OCC>
+static hipError_t go(const IgemmArgs& a, int64_t tiles, hipStream_t st) {
+    constexpr int bytes = NST * (BM + BN) * 128 + (UNI ? 0 : MAX_TAB * 16);
+    static const hipError_t attr = hipFuncSetAttribute((const void*)igemm_kernel<E, BM, BN, WGM, WGN, NST, MODE, UNI, BT, OCC>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL((igemm_kernel<E, BM, BN, WGM, WGN, NST, MODE, UNI, BT, OCC>), dim3((unsigned)tiles, 1, a.splits), dim3(WGM * WGN * 64), bytes, st, a);
+    return hipGetLastError();
+}
+
+template <typename E, int MODE, bool UNI, bool BT>
+static hipError_t go_tile(const IgemmPlan& pl, const IgemmArgs& a, int64_t tiles, hipStream_t st) {
+    if constexpr (sizeof(E) == 2) {
+        if (pl.tile == TILE_128x64) return go<E, 128, 64, 2, 2, 3, MODE, UNI, BT, 2>(a, tiles, st);
+        if (pl.tile == TILE_128) return go<E, 128, 128, 2, 2, 2, MODE, UNI, BT, 2>(a, tiles, st);
+        if (pl.tile == TILE_128_8W) return go<E, 128, 128, 2, 4, 3, MODE, UNI, BT, 2>(a, tiles, st);
+    }
+    return go<E, 64, 64, 2, 2, 3, MODE, UNI, BT, 2>(a, tiles, st);
+}
+template <typename E, int MODE, bool BT>
+static hipError_t go_uni(const IgemmPlan& pl, const IgemmArgs& a, int64_t tiles, hipStream_t st) {
+    if ((a.Ci * (int)sizeof(E)) % 128 == 0) return go_tile<E, MODE, true, BT>(pl, a, tiles, st);
+    return go_tile<E, MODE, false, BT>(pl, a, tiles, st);
+}
+
+hipError_t launch_zero_counts(void* const* heads, int n, hipStream_t st);
+
+static hipError_t run_igemm(int dtype, int mode, IgemmArgs a, IgemmPlan pl, void* ws, bool ws_zeroed, hipStream_t st) {
+    const int es = dtype == LPM_BF16 ? 2 : 4;
+    a.Di = std::max(a.Di, 1); a.Dr = std::max(a.Dr, 1); a.Kd = std::max(a.Kd, 1);
+    a.dWr = fast_div(a.Wr); a.dHr = fast_div(a.Hr); a.dDr = fast_div(a.Dr); a.dCc = fast_div(a.Ci * es / 16);
+    a.kt_total = pl.kt_total; a.kt_per_split = pl.kt_per; a.splits = pl.splits;
+    const int64_t mt = a.tiles_m ? a.tiles_m : (a.M + TILE_M[pl.tile] - 1) / TILE_M[pl.tile];
+    const int64_t tiles = mt * ((a.N + TILE_N[pl.tile] - 1) / TILE_N[pl.tile]);
+    if (pl.splits > 1) {
+        a.count = (unsigned*)ws;
+        a.part = (float*)((char*)ws + LPM_COUNT_BYTES);
+        if (tiles > (int64_t)(LPM_COUNT_BYTES / 4) || tiles > pl.tiles) return hipErrorInvalidValue;      // (the plan's cap keeps this out)
+        if (!ws_zeroed) {
+            const hipError_t e = launch_zero_counts(&ws, 1, st);
+            if (e != hipSuccess) return e;
+        }
+    }
+    if (mode == MODE_FWD) return dtype == LPM_BF16 ? go_uni<bf16_t, MODE_FWD, false>(pl, a, tiles, st) : go_uni<float, MODE_FWD, false>(pl, a, tiles, st);
+    if (a.stride == 1) return dtype == LPM_BF16 ? go_uni<bf16_t, MODE_DGRAD, false>(pl, a, tiles, st) : go_uni<float, MODE_DGRAD, true>(pl, a, tiles, st);
+    return dtype == LPM_BF16 ? go_uni<bf16_t, MODE_DGRAD_S, false>(pl, a, tiles, st) : go_uni<float, MODE_DGRAD_S, true>(pl, a, tiles, st);
+}
+
+hipError_t mfma_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* scale, const float* bias,
+                         const void* add, int relu, void* y, void* ws, bool ws_zeroed, hipStream_t st, void* pool_y) {
+    if (pool_y && (add || !mfma_fwd_pools(dtype, g))) return hipErrorInvalidValue;
+    const int es = dtype == LPM_BF16 ? 2 : 4;
+    IgemmArgs a{};
+    a.fwd_pool = (uint16_t*)pool_y;
+    a.A = x; a.B = w; a.C = y;
+    a.scale = scale; a.bias = bias; a.add = add; a.relu = relu;
+    a.M = (int)g.rows_out(); a.N = g.Cout;
+    a.Hi = g.H; a.Wi = g.W; a.Di = g.D; a.Ci = g.Cin; a.Hr = g.Ho; a.Wr = g.Wo; a.Dr = g.Do;
+    a.Kh = g.Kh; a.Kw = g.Kw; a.Kd = g.Kd; a.stride = g.stride; a.pad = g.pad; a.pad_d = g.pad_d;
+    a.free_taps = fwd_free(g);
+    a.a_bytes = (unsigned)(g.rows_in() * g.Cin * es);
+    a.b_pitch = (unsigned)((int64_t)g.K() * es);
+    a.b_bytes = (unsigned)((int64_t)g.Cout * g.K() * es);
+    return run_igemm(dtype, MODE_FWD, a, plan_fwd(dtype, g), ws, ws_zeroed, st);
+}
+
+// wt: weights laid out [Cin][taps][Cout] (bf16); float layers pass w itself, [Cout][taps][Cin]
+// side (may be NULL): the gradient is the last contribution to a tensor whose producer's epilogue backward this kernel
+// performs -- see DgradSide
+hipError_t mfma_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const void* wt, void* dx, int accumulate, const void* mask,
+                           const float* mscale, void* ws, bool ws_zeroed, hipStream_t st, const UnpoolDesc* unpool, const DgradSide* side) {
+    if (side && unpool) return hipErrorInvalidValue;
+    const int es = dtype == LPM_BF16 ? 2 : 4;
+    IgemmArgs a{};
+    a.A = dz; a.B = wt; a.C = dx;
+    a.accumulate = accumulate; a.mask = mask; a.mscale = mscale;
+    if (side) { a.add = side->earlier; a.C2 = side->shortcut; a.acc2 = side->shortcut_acc; a.c2scale = side->shortcut_scale; }
+    if (unpool) {
+        a.C = nullptr; a.accumulate = 0; a.mask = nullptr;
+        a.pool_x = (const uint16_t*)unpool->pool_x; a.pool_dst = (uint16_t*)unpool->dst;
+        a.pool_acc = unpool->accumulate; a.pool_mask = unpool->mask; a.mscale = unpool->mscale;
+    }
+    a.M = (int)g.rows_in(); a.N = g.Cin;
+    a.Hi = g.Ho; a.Wi = g.Wo; a.Di = g.Do; a.Ci = g.Cout; a.Hr = g.H; a.Wr = g.W; a.Dr = g.D;
+    a.Kh = g.Kh; a.Kw = g.Kw; a.Kd = g.Kd; a.stride = g.stride; a.pad = g.pad; a.pad_d = g.pad_d;
+    a.a_bytes = (unsigned)(g.rows_out() * g.Cout * es);
+    a.b_pitch = (unsigned)((int64_t)g.taps() * (dtype == LPM_BF16 ? g.Cout : g.Cin) * es);
+    a.b_bytes = (unsigned)((int64_t)g.Cout * g.K() * es);
+    const IgemmPlan pl = plan_dgrad(dtype, g);
+    if (g.stride > 1) {          // row tiles per residue class (d % stride, h % stride, w % stride)
+        const int s = g.stride, ncls = (g.D > 1 ? s : 1) * s * s, bm = TILE_M[pl.tile];
+        int t = 0;
+        for (int c = 0; c < ncls; ++c) {
+            a.cls_tile0[c] = t;
+            const int pd = c / (s * s), ph = (c / s) % s, pw = c % s;
+            const int64_t Dc = g.D > 1 ? (g.D - pd + s - 1) / s : 1, Hc = (g.H - ph + s - 1) / s, Wc = (g.W - pw + s - 1) / s;
+            t += (int)(((int64_t)g.m * Dc * Hc * Wc + bm - 1) / bm);
+        }
+        for (int c = ncls; c <= 16; ++c) a.cls_tile0[c] = t;
+        a.tiles_m = t;
+    }
+    return run_igemm(dtype, MODE_DGRAD, a, pl, ws, ws_zeroed, st);
+}
+
+// clears the arrival counts at the head of up to 16 scratch areas
+struct ZeroArgs { unsigned* head[16]; };
+__global__ void __launch_bounds__(256) zero_counts(ZeroArgs a) {
+    reinterpret_cast<uint4*>(a.head[blockIdx.x])[threadIdx.x] = make_uint4(0, 0, 0, 0);
+}
+hipError_t launch_zero_counts(void* const* heads, int n, hipStream_t st) {
+    static_assert(LPM_COUNT_BYTES == 256 * 16, "one 16-byte store per thread");
+    for (int d = 0; d < n; d += 16) {
+        ZeroArgs a{};
+        const int k = std::min(16, n - d);
+        for (int i = 0; i < k; ++i) a.head[i] = (unsigned*)heads[d + i];
+        hipLaunchKernelGGL(zero_counts, dim3(k), dim3(256), 0, st, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+}  // namespace lpm

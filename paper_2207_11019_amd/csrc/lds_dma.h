@@ -28,15 +28,25 @@ __device__ __forceinline__ void load_to_lds16(u32x4_ rs, const unsigned char* ds
                  : "memory");
     // M0 is not on the clobber list on purpose: the compiler treats it as a reserved register (it rejects the entry with
     // "clobber list contains reserved registers: m0"), which means it never keeps a value in M0 across statements and
-    // writes M0 itself immediately before each instruction of its own that reads it.  Were that to change, the weight
-    // gradients of the patch-based kernel would land in the wrong LDS stage: its layer-level parity tests compare every
-    // output element with the fp64 result and would fail.
+    // writes M0 itself immediately before each instruction of its own that reads it.  Were that to change, tiles
+    // would land in the wrong LDS stage: the layer-level parity tests compare every output element with the fp64 result
+    // and would fail.
+}
+
+// the same with a wave-uniform byte offset beside the lane's own (both count in the bounds check)
+__device__ __forceinline__ void load_to_lds16s(u32x4_ rs, const unsigned char* dst, unsigned off, unsigned soff_) {
+    const unsigned d = (unsigned)(uintptr_t)LPM_LDS_PTR(dst);
+    const unsigned soff = (unsigned)__builtin_amdgcn_readfirstlane((int)soff_);      // (a uniform value may have been kept in a vector register)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :
+                 : "s"(d), "v"(off), "s"(rs), "s"(soff)
+                 : "memory");
 }
 
 // wait until at most min(rem, MAXT) * LPT of this wavefront's loads are outstanding (the count is an immediate)
 template <int LPT, int MAXT>
 __device__ __forceinline__ void wait_tiles_behind(int rem) {
-    static_assert(MAXT <= 6 && MAXT * LPT < 64, "six cases, 6-bit counter");
+    static_assert(MAXT >= 0 && MAXT <= 6 && MAXT * LPT < 64, "six cases, 6-bit counter");
     if (rem >= MAXT) { LPM_WAIT_VM(MAXT * LPT); return; }
     switch (rem) {
         case 0: LPM_WAIT_VM(0); break;

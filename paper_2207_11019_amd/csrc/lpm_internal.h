@@ -60,11 +60,18 @@ struct ConvGeom {
 // All launchers enqueue on `st` and return the launch status.  `dtype` selects the element type of
 // activations / activation gradients / low-precision weights (LPM_F32: float everywhere).
 
+// A forward or data-gradient contraction whose reduction is split over blocks keeps, at the head of its scratch, the number
+// of blocks that have stored their part of every output tile.  The counts are zero between launches: a launch leaves them
+// so, and the launchers clear them first unless the caller says (ws_zeroed) that it has done so since anything else may have
+// written there.
+constexpr size_t LPM_COUNT_BYTES = 4096;
+hipError_t launch_zero_counts(void* const* heads, int n, hipStream_t st);
+
 // y = relu?( scale_c * conv(x, w) + bias_c + add )      (scale, bias, add may be NULL)
 // pool_y (may be NULL; only when fwd_can_pool and add == NULL): also stores the 2x2 max-pooling of y, [m][Ho/2][Wo/2][Cout]
 hipError_t launch_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* scale,
                            const float* bias, const void* add, int relu, void* y, void* ws, hipStream_t st,
-                           void* pool_y = nullptr);
+                           void* pool_y = nullptr, bool ws_zeroed = false);
 bool fwd_can_pool(int dtype, const ConvGeom& g);
 // dx (+)= conv_transpose(dz, w);  then, when given, dx = dx * [mask > 0] * mscale_c -- the epilogue backward of
 // the layer that produced the tensor dx belongs to (mask = that tensor, mscale = that layer's scale)
@@ -83,7 +90,8 @@ struct DgradSide { const void* earlier; void* shortcut; int shortcut_acc; const 
 // channel co of dz by dzscale[co]; wt, when given, must then already carry the factor (wt[ci][kh][kw][co] = w[co][kh][kw][ci] * dzscale[co]).
 hipError_t launch_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const void* w, const void* wt,
                              void* dx, int accumulate, const void* mask, const float* mscale, void* ws, hipStream_t st,
-                             const UnpoolDesc* unpool = nullptr, const DgradSide* side = nullptr, const float* dzscale = nullptr);
+                             const UnpoolDesc* unpool = nullptr, const DgradSide* side = nullptr, const float* dzscale = nullptr,
+                             bool ws_zeroed = false);
 bool dgrad_has_side(int dtype, const ConvGeom& g);
 bool dgrad_can_unpool(int dtype, const ConvGeom& g);
 // dw (+)= sum over pixels of dz (x) x         ws: split-reduction partials (wgrad_ws_bytes)

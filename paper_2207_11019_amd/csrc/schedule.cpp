@@ -183,8 +183,8 @@ int32_t fwd_op(lpm_schedule* s, const RunArgs& a, int32_t z, int32_t j, hipStrea
     const int32_t* lab = sg->loss ? a.labels + (size_t)j * sg->m : nullptr;
     // synchronous step: the loss is the mean over the mini-batch; asynchronous update: over the micro-batch
     const float loss_scale = 1.0f / (float)(ver < 0 ? s->M * sg->m : sg->m);
-    return lpm_stage_forward(sg, in, b.act_out[slot], lab, a.loss_out, ver_params(b, ver), ver_lowp(b, ver), b.stash[slot],
-                             b.fwd_ws, loss_scale, st);
+    return lpm_stage_forward_on(sg, in, b.act_out[slot], lab, a.loss_out, ver_params(b, ver), ver_lowp(b, ver), b.stash[slot],
+                                b.fwd_ws, loss_scale, st, true);
 }
 
 // wst: stream of the weight phase (see lpm_stage_backward_on)
@@ -208,7 +208,7 @@ int32_t bwd_op(lpm_schedule* s, const RunArgs& a, int32_t z, int32_t j, hipStrea
                                  ver < 0 ? j > 0 : 0, b.bwd_ws, st, wst, j & 1, phases, staged ? j : -1,
                                  staged ? s->M : 0, by_layer ? j % LPM_MAX_WINDOW : -1,
                                  (s->cut_fused[(size_t)z] ? LPM_MASK_DX : 0) | (z + 1 < s->Z && s->cut_fused[(size_t)z + 1] ? LPM_DY_IS_DZ : 0),
-                                 wst2);
+                                 wst2, true);
 }
 
 // ver < 0: the one update of the synchronous step; else U_{z,ver}: version ver -> version ver + 1
@@ -488,6 +488,14 @@ int32_t enqueue(lpm_schedule* s, const RunArgs& a) {
     const bool capturing = (a.mode & LPM_GRAPH) != 0;
     int32_t rc;
     if (s->st[(size_t)Z - 1]->loss) LPM_HIP(launch_fill_f32(a.loss_out, 1, 0.f, a.sf));
+    {   // the arrival counts of split reductions, once per run: every launch leaves them at zero
+        std::vector<void*> heads;
+        for (int32_t z = 0; z < Z; ++z) {
+            if (s->st[(size_t)z]->fwd_counts) heads.push_back(a.bufs[z].fwd_ws);
+            if (s->st[(size_t)z]->bwd_counts) heads.push_back((char*)a.bufs[z].bwd_ws + s->st[(size_t)z]->kws_off);
+        }
+        if (!heads.empty()) LPM_HIP(launch_zero_counts(heads.data(), (int)heads.size(), a.sf));
+    }
     if ((a.mode & 15) == LPM_LOCKED && (a.mode & LPM_ASYNC_UPDATE)) {      // plain per-micro-batch SGD
         for (int32_t j = 0; j < M; ++j) {
             for (int32_t z = 0; z < Z; ++z) if ((rc = fwd_op(s, a, z, j, a.sf, j))) return rc;

@@ -14,6 +14,12 @@
 
 using namespace lpm;
 
+// Whether the layer's weight-gradient kernel can sum its bias gradient from dz: a float layer with a scale keeps dz times that
+// scale, whose column sum is not the bias gradient.
+static bool bias_in_wgrad_ok(int dtype, const LayerRt& lr) {
+    return wgrad_fuses_bias(dtype, lr.g) && (dtype == LPM_BF16 || !(lr.d.flags & LPM_SCALE));
+}
+
 static bool misaligned(const void* p) { return ((uintptr_t)p & 255u) != 0; }
 
 extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t first, int32_t last,
@@ -86,7 +92,7 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
         if (!has_weights(l)) {
             if (l.kind == LPM_ATTN) {
                 if (!attn_ok(l.h_in * l.w_in, l.cout)) { delete s; return fail(LPM_ESHAPE, "layer %d: attention over %d positions of %d channels is outside the kernel's limits", i, l.h_in * l.w_in, l.cout); }
-                kws = std::max(kws, align_up(attn_bwd_ws_bytes(microbatch, l.h_in * l.w_in), 256));
+                kws = std::max(kws, align_up(LPM_COUNT_BYTES + attn_bwd_ws_bytes(microbatch, l.h_in * l.w_in), 256));
             }
             continue;
         }
@@ -118,7 +124,8 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
             lr.fcs_dz_off = fcs; fcs += align_up((size_t)LPM_FC_STAGE_SLOTS * lr.g.rows_out() * lr.g.Cout * 2, 256);
         }
         kws = std::max(kws, align_up(dgrad_ws_bytes(dtype, lr.g), 256));
-        kws = std::max(kws, align_up(epi_bwd_ws_bytes(lr.g.rows_out(), l.cout), 256));
+        kws = std::max(kws, align_up(LPM_COUNT_BYTES + epi_bwd_ws_bytes(lr.g.rows_out(), l.cout), 256));
+        if (dgrad_ws_bytes(dtype, lr.g)) s->bwd_counts = true;
         fws = std::max(fws, align_up(fwd_ws_bytes(dtype, lr.g), 256));
     }
     // Epilogue-backward fusion: when a layer's output feeds exactly one later layer through its `src` edge, that
@@ -137,7 +144,7 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
             if (c.add_src == i) { ++n_add; first_add = std::min(first_add, j); }
         }
         if (n_src != 1 || n_other != 0) continue;
-        if ((l.flags & LPM_BIAS) && !wgrad_fuses_bias(dtype, lr.g)) continue;
+        if ((l.flags & LPM_BIAS) && !bias_in_wgrad_ok(dtype, lr)) continue;
         if (l.add_src != LPM_NONE || n_add > 0) {
             // Residual blocks.  The layer adds a shortcut, and / or later layers use its output as their shortcut: the
             // single layer that reads it as its input comes first in layer order, so its data gradient is the last
@@ -157,7 +164,7 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
         const lpm_layer& l = lr.d;
         if (dtype != LPM_BF16 || !has_weights(l) || (l.flags & LPM_RELU) || !(l.flags & LPM_SCALE) || l.add_src != LPM_NONE) continue;
         if (i == s->t_out) continue;
-        if ((l.flags & LPM_BIAS) && !wgrad_fuses_bias(dtype, lr.g)) continue;
+        if ((l.flags & LPM_BIAS) && !bias_in_wgrad_ok(dtype, lr)) continue;
         int n_src = 0, n_add = 0;
         int32_t user = -1;
         for (int32_t j = i + 1; j < last; ++j) {
@@ -220,6 +227,7 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
     }
     s->bwd_ws = std::max<size_t>(2 * gws + kws + wws + fcs, 256);
     s->fwd_ws = std::max<size_t>(fws, 256);
+    s->fwd_counts = fws > 0;
     *out = s;
     return LPM_OK;
 }
@@ -356,6 +364,12 @@ inline const void* tptr(const lpm_stage* s, int32_t t, const void* x, const void
 extern "C" int32_t lpm_stage_forward(lpm_stage* s, const void* x, void* y, const int32_t* labels, float* loss_accum,
                                      const float* params, const void* lowp, void* stash, void* fwd_ws,
                                      float loss_scale, void* stream) {
+    return lpm_stage_forward_on(s, x, y, labels, loss_accum, params, lowp, stash, fwd_ws, loss_scale, stream, false);
+}
+
+// counts_zeroed: the caller has cleared the arrival counts at the head of fwd_ws (a schedule does so once per run)
+int32_t lpm_stage_forward_on(lpm_stage* s, const void* x, void* y, const int32_t* labels, float* loss_accum, const float* params,
+                             const void* lowp, void* stash, void* fwd_ws, float loss_scale, void* stream, bool counts_zeroed) {
     if (!s || !x || !y || !params || !stash || !fwd_ws) return fail(LPM_EINVAL, "NULL argument");
     if (s->dtype == LPM_BF16 && !lowp) return fail(LPM_EINVAL, "lowp is NULL for a bf16 stage");
     if (s->loss && (!labels || !loss_accum)) return fail(LPM_EINVAL, "a loss stage needs labels and loss_accum");
@@ -364,6 +378,7 @@ extern "C" int32_t lpm_stage_forward(lpm_stage* s, const void* x, void* y, const
         return fail(LPM_EALIGN, "device buffers must be 256-byte aligned");
     if (s->loss && (((uintptr_t)labels & 3u) || ((uintptr_t)loss_accum & 3u))) return fail(LPM_EALIGN, "labels / loss_accum must be 4-byte aligned");
     hipStream_t st = (hipStream_t)stream;
+    if (s->fwd_counts && !counts_zeroed) LPM_HIP(launch_zero_counts(&fwd_ws, 1, st));
     for (int32_t i = s->first; i < s->last; ++i) {
         const LayerRt& lr = s->Ly(i);
         const lpm_layer& l = lr.d;
@@ -378,7 +393,7 @@ extern "C" int32_t lpm_stage_forward(lpm_stage* s, const void* x, void* y, const
                 const float* bi = lr.b_off != NO ? params + lr.b_off : nullptr;
                 const void* add = l.add_src != LPM_NONE ? tptr(s, l.add_src, x, y, stash) : nullptr;
                 void* pooled = lr.pool_fwd >= 0 ? const_cast<void*>(tptr(s, lr.pool_fwd, x, y, stash)) : nullptr;
-                LPM_HIP(launch_conv_fwd(s->dtype, lr.g, in, w, sc, bi, add, (l.flags & LPM_RELU) != 0, outp, fwd_ws, st, pooled));
+                LPM_HIP(launch_conv_fwd(s->dtype, lr.g, in, w, sc, bi, add, (l.flags & LPM_RELU) != 0, outp, fwd_ws, st, pooled, true));
                 break;
             }
             case LPM_MAXPOOL2:
@@ -424,7 +439,8 @@ extern "C" int32_t lpm_stage_backward(lpm_stage* s, const void* x, const void* y
 int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const void* dy, void* dx,
                               const float* params, const void* lowp, const void* stash, float* grads,
                               int32_t accumulate, void* bwd_ws, void* stream, void* wstream, int32_t parity,
-                              int32_t phases, int32_t fc_slot, int32_t fc_flush, int32_t layer_slot, int32_t boundary, void* wstream2) {
+                              int32_t phases, int32_t fc_slot, int32_t fc_flush, int32_t layer_slot, int32_t boundary, void* wstream2,
+                              bool counts_zeroed) {
     if ((boundary & LPM_MASK_DX) && !lpm_stage_can_mask_dx(s)) return fail(LPM_EINVAL, "internal: this stage cannot mask its input gradient");
     if ((boundary & LPM_DY_IS_DZ) && !lpm_stage_takes_dz(s)) return fail(LPM_EINVAL, "internal: this stage needs the gradient of its output");
     if (layer_slot >= LPM_MAX_WINDOW) return fail(LPM_EINVAL, "internal: layer event slot out of range");
@@ -439,7 +455,8 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
     const int32_t first = s->first, last = s->last;
     const bool acc = accumulate != 0;
     char* ws = (char*)bwd_ws;
-    void* kws = ws + s->kws_off;
+    void* counts = ws + s->kws_off;              // data-gradient scratch: arrival counts first
+    void* kws = ws + s->kws_off + LPM_COUNT_BYTES;
     void* wws = ws + s->wws_off;
     char* gw = ws + (parity ? s->gws_bytes : 0);
     int32_t prc = lpm_stage_prepare(s);
@@ -453,6 +470,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
     const bool do_data = (phases & LPM_PHASE_DATA) != 0, do_weights = (phases & LPM_PHASE_WEIGHTS) != 0;
     if (!deferred && !(do_data && do_weights)) return fail(LPM_EINVAL, "a captured backward pass cannot be split into phases");
     if (!do_data && (!do_weights || !wstream)) return fail(LPM_EINVAL, "internal: bad phase selection");
+    if (do_data && s->bwd_counts && !counts_zeroed) LPM_HIP(launch_zero_counts(&counts, 1, st));
     // layer_slot >= 0 (the two phases come as separate calls with the same slot): the data phase records, per weight
     // layer, the point in its stream where that layer's output gradient is final, and the weight phase waits for
     // that point before the layer's weight gradient instead of for the end of the data phase
@@ -521,7 +539,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                 const float* sc = lr.s_off != NO ? params + lr.s_off : nullptr;
                 const bool relu = (l.flags & LPM_RELU) != 0;
                 float* dbias = lr.b_off != NO ? grads + lr.b_off : nullptr;
-                const bool bias_in_wgrad = dbias && wgrad_fuses_bias(s->dtype, lr.g);
+                const bool bias_in_wgrad = dbias && bias_in_wgrad_ok(s->dtype, lr);
                 const void* dz = g;
                 const void* bias_g = nullptr;
                 if (lr.fused_in) {
@@ -625,11 +643,11 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                     const void* wt = (s->dtype == LPM_BF16 && lr.lowp_wt_off != NO)
                                          ? (const void*)((const char*)lowp + lr.lowp_wt_off) : nullptr;
                     if (lr.unpool_of >= 0) {
-                        if (do_data && unpool.dst) LPM_HIP(launch_conv_dgrad(s->dtype, lr.g, dz, w, wt, nullptr, 0, nullptr, nullptr, kws, st, &unpool,
-                                                                             nullptr, lr.dz_unscaled ? sc : nullptr));
+                        if (do_data && unpool.dst) LPM_HIP(launch_conv_dgrad(s->dtype, lr.g, dz, w, wt, nullptr, 0, nullptr, nullptr, counts, st, &unpool,
+                                                                             nullptr, lr.dz_unscaled ? sc : nullptr, true));
                     } else if (do_data) {
-                        LPM_HIP(launch_conv_dgrad(s->dtype, lr.g, dz, w, wt, gsrc, gsrc_acc, gmask, gmscale, kws, st, nullptr,
-                                                  use_side ? &side : nullptr, lr.dz_unscaled ? sc : nullptr));
+                        LPM_HIP(launch_conv_dgrad(s->dtype, lr.g, dz, w, wt, gsrc, gsrc_acc, gmask, gmscale, counts, st, nullptr,
+                                                  use_side ? &side : nullptr, lr.dz_unscaled ? sc : nullptr, true));
                     }
                 }
                 break;
@@ -732,7 +750,7 @@ bool lpm_stage_takes_dz(const lpm_stage* s) {
     const LayerRt& lr = s->Ly(i);
     const lpm_layer& l = lr.d;
     if (!has_weights(l) || !(l.flags & LPM_RELU) || (l.flags & LPM_SCALE) || l.add_src != LPM_NONE) return false;
-    return !(l.flags & LPM_BIAS) || wgrad_fuses_bias(s->dtype, lr.g);
+    return !(l.flags & LPM_BIAS) || bias_in_wgrad_ok(s->dtype, lr);
 }
 
 extern "C" int32_t lpm_stage_update(lpm_stage* s, float* params, void* lowp, float* grads, float* momentum,

@@ -56,6 +56,7 @@ struct lpm_stage {
     size_t n_trainable = 0, n_params = 0;   // floats
     size_t lowp_bytes = 0, stash_bytes = 0, fwd_ws = 0, bwd_ws = 0;
     size_t dlogits_off = lpm::NO, kws_off = lpm::NO, wws_off = lpm::NO;   // stash / bwd-scratch offsets
+    bool fwd_counts = false, bwd_counts = false;      // some layer of the pass splits its reduction (LPM_COUNT_BYTES at the head of the scratch)
     size_t gws_bytes = 0;             // size of one copy of the gradient / dz area at the head of the backward scratch
     // Weight gradients are off the critical path of B (nothing in the same pass reads them), so they run on
     // a side stream (borrowed from the library's pool), forked from and joined back into the caller's stream.
@@ -78,7 +79,10 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                               const float* params, const void* lowp, const void* stash, float* grads,
                               int32_t accumulate, void* bwd_ws, void* stream, void* wstream, int32_t parity,
                               int32_t phases, int32_t fc_slot = -1, int32_t fc_flush = 0, int32_t layer_slot = -1,
-                              int32_t boundary = 0, void* wstream2 = nullptr);
+                              int32_t boundary = 0, void* wstream2 = nullptr, bool counts_zeroed = false);
+// F_{z,j}; counts_zeroed: see stage.cpp
+int32_t lpm_stage_forward_on(lpm_stage* s, const void* x, void* y, const int32_t* labels, float* loss_accum, const float* params,
+                             const void* lowp, void* stash, void* fwd_ws, float loss_scale, void* stream, bool counts_zeroed);
 // boundary: a schedule may move the ReLU backward of a stage's last layer into the next stage, whose kernel that
 // writes the gradient w.r.t. its input then masks it with that input (the producer's output) -- one kernel less
 // per cut and micro-batch.  LPM_MASK_DX: this stage masks its dx; LPM_DY_IS_DZ: the gradient this stage receives
