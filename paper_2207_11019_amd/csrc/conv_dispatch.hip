@@ -59,13 +59,19 @@ static ConvGeom fc_view(const ConvGeom& g) {
 // (a bf16 data gradient reads the transposed weights, whose layout keeps the taps: no view)
 static ConvGeom dgrad_view(int dtype, const ConvGeom& g) { return dtype == LPM_F32 ? fc_view(g) : g; }
 
+// A float contraction of a few hundred thousand products (a fully connected layer at eight samples) is one or two tiles of the
+// matrix-core kernel and takes the latency of its K loop, 7-8 us; a group of lanes per output element, 4 us.
+static bool tiny_f32(int dtype, const ConvGeom& g) { return dtype == LPM_F32 && g.rows_out() * g.Cout * g.K() < ((int64_t)1 << 21); }
+static bool fwd_mm(int dtype, const ConvGeom& g) { return mfma_fwd_ok(dtype, g) && !tiny_f32(dtype, g); }
+static bool dgrad_mm(int dtype, const ConvGeom& g) { return mfma_dgrad_ok(dtype, g) && !tiny_f32(dtype, g); }
+
 size_t fwd_ws_bytes(int dtype, const ConvGeom& g_) {
     const ConvGeom g = fc_view(g_);
-    return mfma_fwd_ok(dtype, g) ? mfma_fwd_ws_bytes(dtype, g) : 0;
+    return fwd_mm(dtype, g) ? mfma_fwd_ws_bytes(dtype, g) : 0;
 }
 size_t dgrad_ws_bytes(int dtype, const ConvGeom& g) {
     const ConvGeom v = dgrad_view(dtype, g);
-    const size_t b = mfma_dgrad_ok(dtype, v) ? mfma_dgrad_ws_bytes(dtype, v) : 0;
+    const size_t b = dgrad_mm(dtype, v) ? mfma_dgrad_ws_bytes(dtype, v) : 0;
     if (dtype == LPM_BF16 && fc_skinny_ok(g)) return std::max(LPM_COUNT_BYTES + fc_dgrad_ws_bytes(g), b);
     return b;
 }
@@ -81,7 +87,7 @@ bool fwd_can_pool(int dtype, const ConvGeom& g) { return mfma_fwd_pools(dtype, g
 hipError_t launch_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* scale,
                            const float* bias, const void* add, int relu, void* y, void* ws, hipStream_t st, void* pool_y, bool ws_zeroed) {
     if (pool_y && !fwd_can_pool(dtype, g)) return hipErrorInvalidValue;      // callers ask fwd_can_pool first
-    if (mfma_fwd_ok(dtype, fc_view(g))) return mfma_conv_fwd(dtype, fc_view(g), x, w, scale, bias, add, relu, y, ws, ws_zeroed, st, pool_y);
+    if (fwd_mm(dtype, fc_view(g))) return mfma_conv_fwd(dtype, fc_view(g), x, w, scale, bias, add, relu, y, ws, ws_zeroed, st, pool_y);
     if (dtype == LPM_BF16 && smallk_ok(g)) return smallk_conv_fwd(g, x, w, scale, bias, add, relu, y, st);
     return conv_fwd_generic_launch(dtype, g, x, w, scale, bias, add, relu, y, st);
 }
@@ -109,7 +115,7 @@ hipError_t launch_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const
     if (side && !(dgrad_has_side(dtype, g) && wt)) return hipErrorInvalidValue;          // ... and dgrad_has_side
     if (dtype == LPM_BF16 && fc_skinny_ok(g)) return fc_dgrad(g, dz, dzscale, w, dx, accumulate, mask, mscale, (char*)ws + LPM_COUNT_BYTES, st);
     if (dtype == LPM_BF16 && wt && mfma_dgrad_ok(dtype, g)) return mfma_conv_dgrad(dtype, g, dz, wt, dx, accumulate, mask, mscale, ws, ws_zeroed, st, unpool, side);
-    if (dtype == LPM_F32 && !dzscale && !mscale && mfma_dgrad_ok(dtype, fc_view(g))) return mfma_conv_dgrad(dtype, fc_view(g), dz, w, dx, accumulate, mask, mscale, ws, ws_zeroed, st, nullptr, nullptr);
+    if (dtype == LPM_F32 && !dzscale && !mscale && dgrad_mm(dtype, fc_view(g))) return mfma_conv_dgrad(dtype, fc_view(g), dz, w, dx, accumulate, mask, mscale, ws, ws_zeroed, st, nullptr, nullptr);
     return conv_dgrad_generic_launch(dtype, g, dz, dzscale, w, dx, accumulate, mask, mscale, st);
 }
 
