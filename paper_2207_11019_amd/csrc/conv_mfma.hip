@@ -379,6 +379,9 @@ __global__ void __launch_bounds__(256, 2) wgrad_kernel(WgradArgs p) {
 
 struct WgradPlan { int bk, splits, rt_total, rt_per, co_tiles; };
 
+// threads that share four outputs of a reduction
+__host__ __device__ inline int reduce_lanes(int splits) { return splits > 64 ? 16 : splits > 16 ? 4 : 1; }
+
 struct ReduceBatchArgs {
     ReduceDesc d[LPM_REDUCE_BATCH];
     int64_t first[LPM_REDUCE_BATCH + 1];     // first thread of every reduction (a thread sums four outputs)
@@ -387,9 +390,13 @@ struct ReduceBatchArgs {
 
 // A thread sums four consecutive outputs over the splits with 16-byte loads, eight splits in flight (split s goes to
 // chain s % 4, the chains are added pairwise at the end: a fixed order); the bias part and ragged ends go one by one.
+// With many splits (a layer of few weights and many pixels) a group of `lanes` = 4 or 16 threads shares four outputs: each
+// takes a contiguous part of the splits, and the sums are added by lane exchanges in a fixed order.
+template <int LANES>
 __device__ __forceinline__ void reduce_one(const ReduceDesc& d, int64_t t) {
-    const int64_t i = t * 4;
-    const int s0 = 0, s1 = d.splits;
+    const int part = LANES > 1 ? (int)(t % LANES) : 0;
+    const int64_t i = t / LANES * 4;
+    const int per = (d.splits + LANES - 1) / LANES, s0 = part * per, s1 = min(d.splits, s0 + per);
     if (i >= d.n + d.nb) return;              // padding up to a whole block (whole groups)
     if (i + 4 <= d.n && (d.stride & 3) == 0 && (d.row_len & 3) == 0) {
         float4 c[4];
@@ -411,6 +418,11 @@ __device__ __forceinline__ void reduce_one(const ReduceDesc& d, int64_t t) {
         for (int j = 0; j < 7; ++j) { c[j & 3].x += v[j].x; c[j & 3].y += v[j].y; c[j & 3].z += v[j].z; c[j & 3].w += v[j].w; }
         float4 r = make_float4((c[0].x + c[1].x) + (c[2].x + c[3].x), (c[0].y + c[1].y) + (c[2].y + c[3].y),
                                (c[0].z + c[1].z) + (c[2].z + c[3].z), (c[0].w + c[1].w) + (c[2].w + c[3].w));
+#pragma unroll
+        for (int o = 1; o < LANES; o <<= 1) {
+            r.x += __shfl_xor(r.x, o); r.y += __shfl_xor(r.y, o); r.z += __shfl_xor(r.z, o); r.w += __shfl_xor(r.w, o);
+        }
+        if (part) return;
         if (d.rscale) {                           // (row_len is a multiple of 4 on this path: the four outputs share a row)
             const float f = d.rscale[i / d.row_len];
             r.x *= f; r.y *= f; r.z *= f; r.w *= f;
@@ -423,6 +435,9 @@ __device__ __forceinline__ void reduce_one(const ReduceDesc& d, int64_t t) {
     for (int64_t e = i; e < i + 4 && e < d.n + d.nb; ++e) {
         float acc = 0.f;
         for (int s = s0; s < s1; ++s) acc += d.part[(size_t)s * d.stride + e];
+#pragma unroll
+        for (int o = 1; o < LANES; o <<= 1) acc += __shfl_xor(acc, o);
+        if (part) continue;
         if (e < d.n) {
             if (d.rscale) acc *= d.rscale[e / d.row_len];
             d.dst[e] = d.accumulate ? d.dst[e] + acc : acc;
@@ -437,7 +452,10 @@ __global__ void __launch_bounds__(256) wgrad_reduce_batch(ReduceBatchArgs a) {
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     int k = 0;                                    // (a block never straddles two reductions)
     while (k + 1 < a.count && (int64_t)blockIdx.x * 256 >= a.first[k + 1]) ++k;
-    reduce_one(a.d[k], t - a.first[k]);
+    const int lanes = reduce_lanes(a.d[k].splits);
+    if (lanes == 16) reduce_one<16>(a.d[k], t - a.first[k]);
+    else if (lanes == 4) reduce_one<4>(a.d[k], t - a.first[k]);
+    else reduce_one<1>(a.d[k], t - a.first[k]);
 }
 
 hipError_t launch_reduce_batch(const ReduceDesc* d, int count, hipStream_t st) {
@@ -449,7 +467,7 @@ hipError_t launch_reduce_batch(const ReduceDesc* d, int count, hipStream_t st) {
             a.d[k] = d[done + k];
             a.first[k] = tot;
             // a thread per four outputs, whole blocks per reduction: a block never straddles two of them
-            tot += (((a.d[k].n + a.d[k].nb + 3) / 4 + 255) / 256) * 256;
+            tot += (((a.d[k].n + a.d[k].nb + 3) / 4 * reduce_lanes(a.d[k].splits) + 255) / 256) * 256;
         }
         a.first[k] = tot;
         a.count = k;

@@ -387,7 +387,8 @@ static WgPlan plan_wgrad(int dtype, const ConvGeom& g) {
     const int64_t out_bytes = ((int64_t)g.Cout * g.K() + g.Cout) * 4;
     int64_t sp = std::max<int64_t>(1, 256 / base);
     if (base * sp < 192) sp = std::max<int64_t>(sp, 448 / base);
-    sp = std::min<int64_t>(sp, std::max(1, pl.kt_total / 4));          // at least four K tiles per block
+    // at least eight K tiles per block, four where that leaves fewer than eight ranges: every range costs a pass over dW
+    sp = std::min<int64_t>(sp, std::max(std::max(1, pl.kt_total / 8), std::min(8, pl.kt_total / 4)));
     sp = std::min<int64_t>(sp, std::max<int64_t>(1, (64ll << 20) / out_bytes));
     pl.kt_per = (int)((pl.kt_total + sp - 1) / sp);
     pl.splits = (pl.kt_total + pl.kt_per - 1) / pl.kt_per;
