@@ -22,7 +22,8 @@ bool mfma_fwd_pools(int dtype, const ConvGeom& g);
 hipError_t mfma_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* scale, const float* bias,
                          const void* add, int relu, void* y, void* ws, bool ws_zeroed, hipStream_t st, void* pool_y);
 hipError_t mfma_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const void* wt, void* dx, int accumulate, const void* mask,
-                           const float* mscale, void* ws, bool ws_zeroed, hipStream_t st, const UnpoolDesc* unpool, const DgradSide* side);
+                           const float* mscale, void* ws, bool ws_zeroed, hipStream_t st, const UnpoolDesc* unpool, const DgradSide* side, const float* kscale);
+bool mfma_dgrad_kscale_ok(const ConvGeom& g);
 bool wgrad_mm_ok(int dtype, const ConvGeom& g);
 size_t wgrad_mm_ws_bytes(int dtype, const ConvGeom& g);
 hipError_t wgrad_mm_launch(int dtype, const ConvGeom& g, const void* x, const void* dz, float* dw, float* dbias, const float* rscale,
@@ -56,9 +57,6 @@ static ConvGeom fc_view(const ConvGeom& g) {
     ConvGeom v{g.m, 1, 1, g.K(), 1, 1, g.Cout, 1, 1, 1, 0};
     return v;
 }
-// (a bf16 data gradient reads the transposed weights, whose layout keeps the taps: no view)
-static ConvGeom dgrad_view(int dtype, const ConvGeom& g) { return dtype == LPM_F32 ? fc_view(g) : g; }
-
 // A float contraction of a few hundred thousand products (a fully connected layer at eight samples) is one or two tiles of the
 // matrix-core kernel and takes the latency of its K loop, 7-8 us; a group of lanes per output element, 4 us.
 static bool tiny_f32(int dtype, const ConvGeom& g) { return dtype == LPM_F32 && g.rows_out() * g.Cout * g.K() < ((int64_t)1 << 21); }
@@ -69,9 +67,13 @@ size_t fwd_ws_bytes(int dtype, const ConvGeom& g_) {
     const ConvGeom g = fc_view(g_);
     return fwd_mm(dtype, g) ? mfma_fwd_ws_bytes(dtype, g) : 0;
 }
+// A float data gradient takes the fully connected view unless its epilogue goes by the channels of x; bf16 reads the
+// transposed weights, whose layout keeps the taps.
+static bool f32_dgrad_viewed(const ConvGeom& g, const float* mscale, const DgradSide* side) { return !mscale && !side && dgrad_mm(LPM_F32, fc_view(g)); }
+
 size_t dgrad_ws_bytes(int dtype, const ConvGeom& g) {
-    const ConvGeom v = dgrad_view(dtype, g);
-    const size_t b = dgrad_mm(dtype, v) ? mfma_dgrad_ws_bytes(dtype, v) : 0;
+    size_t b = dgrad_mm(dtype, g) ? mfma_dgrad_ws_bytes(dtype, g) : 0;
+    if (dtype == LPM_F32 && dgrad_mm(dtype, fc_view(g))) b = std::max(b, mfma_dgrad_ws_bytes(dtype, fc_view(g)));
     if (dtype == LPM_BF16 && fc_skinny_ok(g)) return std::max(LPM_COUNT_BYTES + fc_dgrad_ws_bytes(g), b);
     return b;
 }
@@ -106,16 +108,20 @@ bool dgrad_can_unpool(int dtype, const ConvGeom& g) {
 }
 
 // the MFMA data gradient can take over the epilogue backward of a layer with a shortcut (DgradSide)
-bool dgrad_has_side(int dtype, const ConvGeom& g) { return dgrad_uses_wt(dtype, g); }
+bool dgrad_has_side(int dtype, const ConvGeom& g) { return dtype == LPM_F32 ? dgrad_mm(dtype, g) : dgrad_uses_wt(dtype, g); }
+
+// whether the data gradient can apply the layer's scale to a dz that does not carry it (bf16: through the transposed weights)
+bool dgrad_scales_dz(int dtype, const ConvGeom& g) { return dtype == LPM_BF16 || mfma_dgrad_kscale_ok(g); }
 
 hipError_t launch_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const void* w, const void* wt, void* dx,
                              int accumulate, const void* mask, const float* mscale, void* ws, hipStream_t st,
                              const UnpoolDesc* unpool, const DgradSide* side, const float* dzscale, bool ws_zeroed) {
     if (unpool && !(dgrad_can_unpool(dtype, g) && wt)) return hipErrorInvalidValue;      // callers ask dgrad_can_unpool first
-    if (side && !(dgrad_has_side(dtype, g) && wt)) return hipErrorInvalidValue;          // ... and dgrad_has_side
+    if (side && !(dgrad_has_side(dtype, g) && (wt || dtype == LPM_F32))) return hipErrorInvalidValue;          // ... and dgrad_has_side
     if (dtype == LPM_BF16 && fc_skinny_ok(g)) return fc_dgrad(g, dz, dzscale, w, dx, accumulate, mask, mscale, (char*)ws + LPM_COUNT_BYTES, st);
-    if (dtype == LPM_BF16 && wt && mfma_dgrad_ok(dtype, g)) return mfma_conv_dgrad(dtype, g, dz, wt, dx, accumulate, mask, mscale, ws, ws_zeroed, st, unpool, side);
-    if (dtype == LPM_F32 && !dzscale && !mscale && dgrad_mm(dtype, fc_view(g))) return mfma_conv_dgrad(dtype, fc_view(g), dz, w, dx, accumulate, mask, mscale, ws, ws_zeroed, st, nullptr, nullptr);
+    if (dtype == LPM_BF16 && wt && mfma_dgrad_ok(dtype, g)) return mfma_conv_dgrad(dtype, g, dz, wt, dx, accumulate, mask, mscale, ws, ws_zeroed, st, unpool, side, nullptr);
+    if (dtype == LPM_F32 && f32_dgrad_viewed(g, mscale, side)) return mfma_conv_dgrad(dtype, fc_view(g), dz, w, dx, accumulate, mask, nullptr, ws, ws_zeroed, st, nullptr, nullptr, dzscale);
+    if (dtype == LPM_F32 && dgrad_mm(dtype, g)) return mfma_conv_dgrad(dtype, g, dz, w, dx, accumulate, mask, mscale, ws, ws_zeroed, st, nullptr, side, dzscale);
     return conv_dgrad_generic_launch(dtype, g, dz, dzscale, w, dx, accumulate, mask, mscale, st);
 }
 

@@ -36,6 +36,7 @@ constexpr unsigned OOB = 0xffffffffu;
 enum { MODE_FWD = 0, MODE_DGRAD = 1 /* stride 1 */, MODE_DGRAD_S = 2 /* stride 2..4, by residue class */ };
 
 constexpr int MAX_TAB = 128;              // taps a layer without whole K tiles per tap may have
+constexpr int MAX_KSCALE = 2048;          // channels of a float layer whose data gradient applies its scale (LDS)
 
 struct IgemmArgs {
     const void* A;
@@ -45,6 +46,7 @@ struct IgemmArgs {
     unsigned* count;        // split K: blocks that have stored theirs, per output tile
     const float* scale;
     const float* bias;
+    const float* kscale;    // float data gradient: per-channel factor of the gathered tensor (the reduction index), or NULL
     const void* add;
     const void* mask;       // data gradient: zero the result where this tensor (the producer's output) is <= 0
     const float* mscale;    // data gradient: then multiply by the producer's per-channel scale
@@ -282,15 +284,22 @@ __device__ __forceinline__ unsigned tap_bits(int lo, int hi) { return hi > lo ? 
 // partial tiles pass between blocks on different XCDs: stores go through to memory, loads do not hit a stale line
 constexpr int AUX_AGENT = 16;
 
-template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, bool UNI, bool BT, int OCC>
+// layout of B: [N][K] rows; K outermost; K outermost and scaled
+enum { BT_NONE = 0, BT_PLAIN = 1, BT_SCALED = 2 };
+
+template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, bool UNI, int BT, int OCC>
 __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmArgs p) {
     constexpr int ES = sizeof(E), T = WGM * WGN * 64, RS = T / 8;             // rows a load step covers
     constexpr int WTM = BM / WGM, WTN = BN / WGN, MI = WTM / 32, NI = WTN / 32;
     constexpr int A_LD = BM / RS, B_LD = BN / RS, LPT = A_LD + B_LD;
     constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
     static_assert(!BT || ES == 4, "float data gradient only");
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];      // NST stages [+ tap table]
+    // BT: B is read with its reduction index outermost; BT_SCALED: and multiplied by kscale, kept in LDS, on its way to the
+    // matrix cores (the dz of a float layer with a scale is stored without it; 16 multiplications per 16 products)
+    constexpr bool KS = BT == BT_SCALED;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];      // NST stages [+ tap table] [+ kscale]
     int4* tab = reinterpret_cast<int4*>(lds + NST * STAGE);
+    float* ksc = reinterpret_cast<float*>(lds + NST * STAGE + (UNI ? 0 : MAX_TAB * 16));
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nt = (p.N + BN - 1) / BN;
@@ -349,6 +358,9 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
             tab[t] = make_int4((int)(aoff0 + td * aD + th * aH + tw * aW), (int)(b0 + td * bD + th * bH + tw * bW),
                                p.free_taps ? 1 : (int)((1u << (24 + td)) | (1u << (12 + th)) | (1u << tw)), 0);
         }
+    }
+    if (KS) {
+        for (int c = tid; c < p.Ci; c += T) ksc[c] = p.kscale[c];      // (the first K tile's barrier makes it visible)
     }
     // ---- loader state.  Lane l of a load fills chunk position l % 8 of row l / 8: it fetches chunk (l % 8) ^ (l / 8)
     const int lrow = lane >> 3, kcol = (lane & 7) ^ lrow;
@@ -500,6 +512,10 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
     const int rl = lane & 31, kh_ = lane >> 5;
     const unsigned rowA = (unsigned)(wm * WTM + rl) * 128u, rowB = (unsigned)(A_BYTES + (wn * WTN + rl) * 128);
     const unsigned colBT = (unsigned)(A_BYTES + (wn * WTN + rl) * 4);
+    int ks_c[KS ? 4 : 1];                    // channel of the lane's chunk ks in the K tile read next
+#pragma unroll
+    for (int ks = 0; ks < (KS ? 4 : 0); ++ks) ks_c[ks] = (kt0 * kt_ch + (ks * 2 + kh_) * 4) % p.Ci;
+    const int ks_step = KS ? kt_ch % p.Ci : 0;
 
     // Operands of one K tile, 16 bytes per lane and step.  Two sets: while the matrix cores work on one tile the next one is
     // read from LDS, and the tiles behind it are on their way there -- with one wavefront per SIMD (a launch of about one block
@@ -517,7 +533,17 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
                     const unsigned char* q = sp + colBT + (ks * 2 + kh_) * 4 * (BN * 4) + ni * 128;
                     f.b[ks][ni] = make_uint4(*reinterpret_cast<const unsigned*>(q), *reinterpret_cast<const unsigned*>(q + BN * 4),
                                              *reinterpret_cast<const unsigned*>(q + 2 * BN * 4), *reinterpret_cast<const unsigned*>(q + 3 * BN * 4));
+                    if constexpr (KS) {
+                        const float4 k4 = *reinterpret_cast<const float4*>(ksc + ks_c[ks]);
+                        uint4& b = f.b[ks][ni];
+                        b = make_uint4(__float_as_uint(__uint_as_float(b.x) * k4.x), __float_as_uint(__uint_as_float(b.y) * k4.y),
+                                       __float_as_uint(__uint_as_float(b.z) * k4.z), __float_as_uint(__uint_as_float(b.w) * k4.w));
+                    }
                 } else f.b[ks][ni] = *reinterpret_cast<const uint4*>(sp + rowB + x + ni * 4096);
+            }
+            if constexpr (KS) {
+                ks_c[ks] += ks_step;
+                if (ks_c[ks] >= p.Ci) ks_c[ks] -= p.Ci;
             }
         }
     };
@@ -740,6 +766,7 @@ static IgemmPlan plan_dgrad(int dtype, const ConvGeom& g) {
     if (s > 1) rows += 128 * (g.D > 1 ? s * s * s : s * s);          // (every class may end in a ragged tile)
     return plan_igemm(es, rows, g.Cin, k_tiles(taps, g.Cout, es));
 }
+bool mfma_dgrad_kscale_ok(const ConvGeom& g) { return g.Cout <= MAX_KSCALE; }
 size_t mfma_fwd_ws_bytes(int dtype, const ConvGeom& g) { return plan_ws(plan_fwd(dtype, g)); }
 size_t mfma_dgrad_ws_bytes(int dtype, const ConvGeom& g) { return plan_ws(plan_dgrad(dtype, g)); }
 
@@ -749,9 +776,9 @@ bool mfma_fwd_pools(int dtype, const ConvGeom& g) {
     return dtype == LPM_BF16 && mfma_fwd_ok(dtype, g) && !g.is3d() && !(g.Ho & 1) && (g.Wo == 2 || g.Wo == 4 || g.Wo == 8 || g.Wo == 16) && g.Cout % 8 == 0;
 }
 
-template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, bool UNI, bool BT, int OCC>
+template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, bool UNI, int BT, int OCC>
 static hipError_t go(const IgemmArgs& a, int64_t tiles, hipStream_t st) {
-    constexpr int bytes = NST * (BM + BN) * 128 + (UNI ? 0 : MAX_TAB * 16);
+    constexpr int bytes = NST * (BM + BN) * 128 + (UNI ? 0 : MAX_TAB * 16) + (BT == BT_SCALED ? MAX_KSCALE * 4 : 0);
     static const hipError_t attr = hipFuncSetAttribute((const void*)igemm_kernel<E, BM, BN, WGM, WGN, NST, MODE, UNI, BT, OCC>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (attr != hipSuccess) return attr;
@@ -759,7 +786,7 @@ static hipError_t go(const IgemmArgs& a, int64_t tiles, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <typename E, int MODE, bool UNI, bool BT>
+template <typename E, int MODE, bool UNI, int BT>
 static hipError_t go_tile(const IgemmPlan& pl, const IgemmArgs& a, int64_t tiles, hipStream_t st) {
     if constexpr (sizeof(E) == 2) {
         if (pl.tile == TILE_128x64) return go<E, 128, 64, 2, 2, 3, MODE, UNI, BT, 2>(a, tiles, st);
@@ -768,7 +795,7 @@ static hipError_t go_tile(const IgemmPlan& pl, const IgemmArgs& a, int64_t tiles
     }
     return go<E, 64, 64, 2, 2, 3, MODE, UNI, BT, 2>(a, tiles, st);
 }
-template <typename E, int MODE, bool BT>
+template <typename E, int MODE, int BT>
 static hipError_t go_uni(const IgemmPlan& pl, const IgemmArgs& a, int64_t tiles, hipStream_t st) {
     if ((a.Ci * (int)sizeof(E)) % 128 == 0) return go_tile<E, MODE, true, BT>(pl, a, tiles, st);
     return go_tile<E, MODE, false, BT>(pl, a, tiles, st);
@@ -792,9 +819,10 @@ static hipError_t run_igemm(int dtype, int mode, IgemmArgs a, IgemmPlan pl, void
             if (e != hipSuccess) return e;
         }
     }
-    if (mode == MODE_FWD) return dtype == LPM_BF16 ? go_uni<bf16_t, MODE_FWD, false>(pl, a, tiles, st) : go_uni<float, MODE_FWD, false>(pl, a, tiles, st);
-    if (a.stride == 1) return dtype == LPM_BF16 ? go_uni<bf16_t, MODE_DGRAD, false>(pl, a, tiles, st) : go_uni<float, MODE_DGRAD, true>(pl, a, tiles, st);
-    return dtype == LPM_BF16 ? go_uni<bf16_t, MODE_DGRAD_S, false>(pl, a, tiles, st) : go_uni<float, MODE_DGRAD_S, true>(pl, a, tiles, st);
+    if (mode == MODE_FWD) return dtype == LPM_BF16 ? go_uni<bf16_t, MODE_FWD, BT_NONE>(pl, a, tiles, st) : go_uni<float, MODE_FWD, BT_NONE>(pl, a, tiles, st);
+    if (dtype == LPM_BF16) return a.stride == 1 ? go_uni<bf16_t, MODE_DGRAD, BT_NONE>(pl, a, tiles, st) : go_uni<bf16_t, MODE_DGRAD_S, BT_NONE>(pl, a, tiles, st);
+    if (a.kscale) return a.stride == 1 ? go_uni<float, MODE_DGRAD, BT_SCALED>(pl, a, tiles, st) : go_uni<float, MODE_DGRAD_S, BT_SCALED>(pl, a, tiles, st);
+    return a.stride == 1 ? go_uni<float, MODE_DGRAD, BT_PLAIN>(pl, a, tiles, st) : go_uni<float, MODE_DGRAD_S, BT_PLAIN>(pl, a, tiles, st);
 }
 
 hipError_t mfma_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* scale, const float* bias,
@@ -816,15 +844,17 @@ hipError_t mfma_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void
 }
 
 // wt: weights laid out [Cin][taps][Cout] (bf16); float layers pass w itself, [Cout][taps][Cin]
+// kscale: float layers, the per-channel scale that dz does not carry, or NULL
 // side (may be NULL): the gradient is the last contribution to a tensor whose producer's epilogue backward this kernel
 // performs -- see DgradSide
 hipError_t mfma_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const void* wt, void* dx, int accumulate, const void* mask,
-                           const float* mscale, void* ws, bool ws_zeroed, hipStream_t st, const UnpoolDesc* unpool, const DgradSide* side) {
+                           const float* mscale, void* ws, bool ws_zeroed, hipStream_t st, const UnpoolDesc* unpool, const DgradSide* side, const float* kscale) {
+    if (kscale && (dtype == LPM_BF16 || g.Cout > MAX_KSCALE)) return hipErrorInvalidValue;      // (bf16: the transposed copy carries the scale)
     if (side && unpool) return hipErrorInvalidValue;
     const int es = dtype == LPM_BF16 ? 2 : 4;
     IgemmArgs a{};
     a.A = dz; a.B = wt; a.C = dx;
-    a.accumulate = accumulate; a.mask = mask; a.mscale = mscale;
+    a.accumulate = accumulate; a.mask = mask; a.mscale = mscale; a.kscale = kscale;
     if (side) { a.add = side->earlier; a.C2 = side->shortcut; a.acc2 = side->shortcut_acc; a.c2scale = side->shortcut_scale; }
     if (unpool) {
         a.C = nullptr; a.accumulate = 0; a.mask = nullptr;

@@ -6,6 +6,7 @@
 // Layouts: activations [m][H][W][C], weights [Cout][Kh][Kw][Cin].
 #include "lpm_internal.h"
 #include "elem.h"
+#include <algorithm>
 
 namespace lpm {
 
@@ -240,84 +241,100 @@ hipError_t conv_wgrad_generic_launch(int dtype, const ConvGeom& g, const void* x
 // --------------------------------------------------------------------------------------------------
 // epilogue backward (eqs. 8-9 through y = relu(scale*z + bias + add)):
 //   gm = dy * [y > 0];  dz = gm * scale_c;  gadd (+)= gm;  dbias_c (+)= sum_rows gm
-// Block = 64 channels x 4 row lanes; a block covers EPI_ROWS rows and leaves one partial per channel,
-// which bias_reduce adds in block order.
-#define EPI_ROWS 128
-template <typename T>
-__global__ void __launch_bounds__(256) epilogue_bwd_kernel(int64_t rows, int C, const T* __restrict__ dy,
+// A thread owns V consecutive channels (16 bytes; V = 1 where the channel count is no multiple of that) of four rows at a
+// time, all of whose loads are requested before the first is used.  The block's 256 threads are split into channel chunks and
+// row lanes by the channel count (cl_log: log2 of the chunks), so six channels keep as many threads busy as 64.  A block
+// covers epi_rows() rows and leaves one partial per channel, which bias_reduce adds in block order.
+// (Float, 8192 x 64: 18 -> 4 us; a thread used to walk 32 rows, one 4-byte load at a time.)
+template <typename T, int V> struct EpiVec;
+template <typename T> struct EpiVec<T, 1> {
+    static __device__ __forceinline__ void get(const T* p, int64_t i, float (&f)[1]) { f[0] = ld(p, i); }
+    static __device__ __forceinline__ void put(T* p, int64_t i, const float (&f)[1]) { st(p, i, f[0]); }
+};
+template <> struct EpiVec<float, 4> {
+    static __device__ __forceinline__ void get(const float* p, int64_t i, float (&f)[4]) {
+        const float4 v = *reinterpret_cast<const float4*>(p + i);
+        f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+    }
+    static __device__ __forceinline__ void put(float* p, int64_t i, const float (&f)[4]) { *reinterpret_cast<float4*>(p + i) = make_float4(f[0], f[1], f[2], f[3]); }
+};
+template <> struct EpiVec<bf16_t, 8> {
+    static __device__ __forceinline__ void get(const bf16_t* p, int64_t i, float (&f)[8]) {
+        const uint4 v = *reinterpret_cast<const uint4*>(p + i);
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) { f[2 * k] = bf2f((uint16_t)(w[k] & 0xffffu)); f[2 * k + 1] = bf2f((uint16_t)(w[k] >> 16)); }
+    }
+    static __device__ __forceinline__ void put(bf16_t* p, int64_t i, const float (&f)[8]) {
+        *reinterpret_cast<uint4*>(p + i) = make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7]));
+    }
+};
+
+static inline int epi_chunks_log(int C, int V) {           // channel chunks side by side in a block
+    int l = 0;
+    while (l < (V == 8 ? 3 : V == 4 ? 4 : 6) && (V << l) < C) ++l;
+    return l;
+}
+static inline int epi_rows(int cl_log) { return std::max(64, 4 * (256 >> cl_log)); }
+
+template <typename T, int V>
+__global__ void __launch_bounds__(256) epilogue_bwd_kernel(int64_t rows, int C, int cl_log, int block_rows, const T* __restrict__ dy,
                                                            const T* __restrict__ y, const float* __restrict__ scale,
                                                            T* __restrict__ dz, T* __restrict__ gadd, int gadd_acc,
                                                            float* __restrict__ part) {
-    __shared__ float red[4][64];
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    const int c = blockIdx.x * 64 + tx;
-    const int64_t r0 = (int64_t)blockIdx.y * EPI_ROWS;
-    const int64_t r1 = min(rows, r0 + EPI_ROWS);
-    float sum = 0.f;
-    if (c < C) {
-        const float sc = scale ? scale[c] : 1.f;
-        for (int64_t r = r0 + ty; r < r1; r += 4) {
-            const int64_t i = r * C + c;
-            float gm = ld(dy, i);
-            if (y && !(ld(y, i) > 0.f)) gm = 0.f;
-            if (dz) st(dz, i, gm * sc);
-            if (gadd) st(gadd, i, gadd_acc ? ld(gadd, i) + gm : gm);
-            sum += gm;
-        }
-    }
-    if (!part) return;
-    red[ty][tx] = sum;
-    __syncthreads();
-    if (ty == 0 && c < C) part[(int64_t)blockIdx.y * C + c] = (red[0][tx] + red[1][tx]) + (red[2][tx] + red[3][tx]);
-}
-
-// bf16, C % 8 == 0: a thread owns 8 channels (16-byte accesses); block = 8 channel chunks x 32 row lanes.
-__global__ void __launch_bounds__(256) epilogue_bwd_bf16x8(int64_t rows, int C, const uint4* __restrict__ dy,
-                                                           const uint4* __restrict__ y, const float* __restrict__ scale,
-                                                           uint4* __restrict__ dz, uint4* __restrict__ gadd, int gadd_acc,
-                                                           float* __restrict__ part) {
-    __shared__ float red[32][65];
-    const int cx = threadIdx.x & 7, ty = threadIdx.x >> 3;
-    const int c0 = blockIdx.x * 64 + cx * 8;
-    const int64_t r0 = (int64_t)blockIdx.y * EPI_ROWS;
-    const int64_t r1 = min(rows, r0 + EPI_ROWS);
-    const int C8 = C >> 3;
-    float sum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    __shared__ float red[256 * V + 256];
+    typedef EpiVec<T, V> Vec;
+    const int CL = 1 << cl_log, RL = 256 >> cl_log, cx = threadIdx.x & (CL - 1), ty = threadIdx.x >> cl_log;
+    const int cb = blockIdx.x * CL * V, c0 = cb + cx * V;
+    const int64_t r0 = (int64_t)blockIdx.y * block_rows, r1 = min(rows, r0 + block_rows);
+    float sum[V];
+#pragma unroll
+    for (int k = 0; k < V; ++k) sum[k] = 0.f;
     if (c0 < C) {
-        float sc[8];
+        float sc[V];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) sc[k] = scale ? scale[c0 + k] : 1.f;
-        for (int64_t r = r0 + ty; r < r1; r += 32) {
-            const int64_t i = r * C8 + (c0 >> 3);
-            const uint4 g4 = dy[i];
-            uint4 y4 = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
-            if (y) y4 = y[i];
-            uint4 a4 = make_uint4(0, 0, 0, 0);
-            if (gadd && gadd_acc) a4 = gadd[i];
-            const uint32_t gw[4] = {g4.x, g4.y, g4.z, g4.w}, yw[4] = {y4.x, y4.y, y4.z, y4.w}, aw[4] = {a4.x, a4.y, a4.z, a4.w};
-            uint32_t zo[4], go[4];
+        for (int k = 0; k < V; ++k) sc[k] = scale ? scale[c0 + k] : 1.f;
+        for (int64_t rr = r0 + ty; rr < r1; rr += 4 * RL) {
+            float g[4][V], yv[4][V], av[4][V];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                float g0 = bf2f((uint16_t)(gw[k] & 0xffffu)), g1 = bf2f((uint16_t)(gw[k] >> 16));
-                if (!(bf2f((uint16_t)(yw[k] & 0xffffu)) > 0.f)) g0 = 0.f;
-                if (!(bf2f((uint16_t)(yw[k] >> 16)) > 0.f)) g1 = 0.f;
-                sum[2 * k] += g0; sum[2 * k + 1] += g1;
-                zo[k] = pack_bf16x2(g0 * sc[2 * k], g1 * sc[2 * k + 1]);
-                go[k] = pack_bf16x2(g0 + bf2f((uint16_t)(aw[k] & 0xffffu)), g1 + bf2f((uint16_t)(aw[k] >> 16)));
+            for (int u = 0; u < 4; ++u) {
+                const int64_t r = rr + u * RL, i = (r < r1 ? r : rr) * C + c0;
+                Vec::get(dy, i, g[u]);
+                if (y) Vec::get(y, i, yv[u]);
+                if (gadd && gadd_acc) Vec::get(gadd, i, av[u]);
             }
-            if (dz) dz[i] = make_uint4(zo[0], zo[1], zo[2], zo[3]);
-            if (gadd) gadd[i] = make_uint4(go[0], go[1], go[2], go[3]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t r = rr + u * RL, i = r * C + c0;
+                if (r >= r1) continue;
+                float z[V];
+#pragma unroll
+                for (int k = 0; k < V; ++k) {
+                    if (y && !(yv[u][k] > 0.f)) g[u][k] = 0.f;
+                    sum[k] += g[u][k];
+                    z[k] = g[u][k] * sc[k];
+                }
+                if (dz) Vec::put(dz, i, z);
+                if (gadd) {
+                    if (gadd_acc) {
+#pragma unroll
+                        for (int k = 0; k < V; ++k) g[u][k] += av[u][k];
+                    }
+                    Vec::put(gadd, i, g[u]);
+                }
+            }
         }
     }
     if (!part) return;
+    const int pitch = CL * V + 1;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) red[ty][cx * 8 + k] = sum[k];
+    for (int k = 0; k < V; ++k) red[ty * pitch + cx * V + k] = sum[k];
     __syncthreads();
-    if (threadIdx.x < 64 && blockIdx.x * 64 + threadIdx.x < C) {
+    if ((int)threadIdx.x < CL * V && cb + (int)threadIdx.x < C) {
         float acc = 0.f;
-#pragma unroll
-        for (int r = 0; r < 32; ++r) acc += red[r][threadIdx.x];
-        part[(int64_t)blockIdx.y * C + blockIdx.x * 64 + threadIdx.x] = acc;
+#pragma unroll 8
+        for (int r = 0; r < RL; ++r) acc += red[r * pitch + threadIdx.x];
+        part[(int64_t)blockIdx.y * C + cb + threadIdx.x] = acc;
     }
 }
 
@@ -352,31 +369,45 @@ __global__ void __launch_bounds__(256) epilogue_bwd_flat_bf16x8(unsigned chunks,
     if (gadd) gadd[i] = make_uint4(go[0], go[1], go[2], go[3]);
 }
 
-// db[c] (+)= sum over the row blocks' partials, added in block order; 4 lanes per channel
+// db[c] (+)= sum over the row blocks' partials; 16 lanes per channel, each a contiguous part of the blocks in order, the
+// lanes' sums added in lane order
 __global__ void __launch_bounds__(256) bias_reduce(const float* __restrict__ part, float* __restrict__ db, int C,
                                                    int nblocks, int accumulate) {
-    __shared__ float red[4][64];
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    const int c = blockIdx.x * 64 + tx;
+    __shared__ float red[16][17];
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    const int c = blockIdx.x * 16 + tx;
     float acc = 0.f;
     if (c < C) {
-        const int per = (nblocks + 3) / 4;
+        const int per = (nblocks + 15) / 16;
         const int b1 = min(nblocks, (ty + 1) * per);
+#pragma unroll 8
         for (int b = ty * per; b < b1; ++b) acc += part[(int64_t)b * C + c];
     }
     red[ty][tx] = acc;
     __syncthreads();
     if (ty == 0 && c < C) {
-        const float v = (red[0][tx] + red[1][tx]) + (red[2][tx] + red[3][tx]);
+        float v = red[0][tx];
+#pragma unroll
+        for (int k = 1; k < 16; ++k) v += red[k][tx];
         db[c] = accumulate ? db[c] + v : v;
     }
 }
 
-size_t epi_bwd_ws_bytes(int64_t rows, int32_t C) { return (size_t)nblk(rows, EPI_ROWS) * C * sizeof(float); }
+size_t epi_bwd_ws_bytes(int64_t rows, int32_t C) { return (size_t)nblk(rows, 64) * C * sizeof(float); }
+
+template <typename T, int V>
+static unsigned epi_launch(int64_t rows, int32_t C, const void* dy, const void* y, const float* scale, void* dz, void* gadd, int gadd_acc, float* part, hipStream_t s) {
+    const int cl = epi_chunks_log(C, V);
+    int br = epi_rows(cl);
+    while (nblk(rows, br) > 32768) br *= 2;            // (the grid's second extent is limited)
+    const unsigned rb = nblk(rows, br);
+    hipLaunchKernelGGL((epilogue_bwd_kernel<T, V>), dim3(nblk(C, V << cl), rb), dim3(256), 0, s, rows, C, cl, br, (const T*)dy, (const T*)y, scale,
+                       (T*)dz, (T*)gadd, gadd_acc, part);
+    return rb;
+}
 
 hipError_t launch_epilogue_bwd(int dtype, int64_t rows, int32_t C, const void* dy, const void* y, const float* scale,
                                void* dz, void* gadd, int gadd_acc, float* dbias, int db_acc, void* ws, hipStream_t s) {
-    const unsigned rb = nblk(rows, EPI_ROWS);
     float* part = dbias ? (float*)ws : nullptr;
     if (dtype == LPM_BF16 && (C & 7) == 0 && !dbias && rows * (C >> 3) < ((int64_t)1 << 31)) {
         const unsigned chunks = (unsigned)(rows * (C >> 3));
@@ -384,16 +415,12 @@ hipError_t launch_epilogue_bwd(int dtype, int64_t rows, int32_t C, const void* d
                            (const uint4*)dy, (const uint4*)y, scale, (uint4*)dz, (uint4*)gadd, gadd_acc);
         return hipGetLastError();
     }
-    if (dtype == LPM_BF16 && (C & 7) == 0) {
-        hipLaunchKernelGGL(epilogue_bwd_bf16x8, dim3(nblk(C, 64), rb), dim3(256), 0, s, rows, C, (const uint4*)dy,
-                           (const uint4*)y, scale, (uint4*)dz, (uint4*)gadd, gadd_acc, part);
-    } else {
-        LPM_DISPATCH(dtype, hipLaunchKernelGGL(epilogue_bwd_kernel<T>, dim3(nblk(C, 64), rb), dim3(256), 0, s, rows, C,
-                                               (const T*)dy, (const T*)y, scale, (T*)dz, (T*)gadd, gadd_acc, part));
-    }
+    unsigned rb;
+    if (dtype == LPM_BF16) rb = (C & 7) == 0 ? epi_launch<bf16_t, 8>(rows, C, dy, y, scale, dz, gadd, gadd_acc, part, s) : epi_launch<bf16_t, 1>(rows, C, dy, y, scale, dz, gadd, gadd_acc, part, s);
+    else rb = (C & 3) == 0 ? epi_launch<float, 4>(rows, C, dy, y, scale, dz, gadd, gadd_acc, part, s) : epi_launch<float, 1>(rows, C, dy, y, scale, dz, gadd, gadd_acc, part, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !dbias) return e;
-    hipLaunchKernelGGL(bias_reduce, dim3(nblk(C, 64)), dim3(256), 0, s, (const float*)part, dbias, C, (int)rb, db_acc);
+    hipLaunchKernelGGL(bias_reduce, dim3(nblk(C, 16)), dim3(256), 0, s, (const float*)part, dbias, C, (int)rb, db_acc);
     return hipGetLastError();
 }
 

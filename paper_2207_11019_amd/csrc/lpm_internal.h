@@ -92,6 +92,7 @@ hipError_t launch_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const
                              void* dx, int accumulate, const void* mask, const float* mscale, void* ws, hipStream_t st,
                              const UnpoolDesc* unpool = nullptr, const DgradSide* side = nullptr, const float* dzscale = nullptr,
                              bool ws_zeroed = false);
+bool dgrad_scales_dz(int dtype, const ConvGeom& g);
 bool dgrad_has_side(int dtype, const ConvGeom& g);
 bool dgrad_can_unpool(int dtype, const ConvGeom& g);
 // dw (+)= sum over pixels of dz (x) x         ws: split-reduction partials (wgrad_ws_bytes)

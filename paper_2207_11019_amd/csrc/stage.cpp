@@ -14,11 +14,13 @@
 
 using namespace lpm;
 
-// Whether the layer's weight-gradient kernel can sum its bias gradient from dz: a float layer with a scale keeps dz times that
-// scale, whose column sum is not the bias gradient.
+// Whether the layer's weight-gradient kernel can sum its bias gradient from dz: where dz carries a scale its column sum is
+// not the bias gradient.
 static bool bias_in_wgrad_ok(int dtype, const LayerRt& lr) {
-    return wgrad_fuses_bias(dtype, lr.g) && (dtype == LPM_BF16 || !(lr.d.flags & LPM_SCALE));
+    return wgrad_fuses_bias(dtype, lr.g) && (lr.dz_unscaled || !(lr.d.flags & LPM_SCALE));
 }
+// ... or the weight phase can sum it from dz in a kernel of its own
+static bool bias_from_dz_ok(const LayerRt& lr) { return lr.dz_unscaled || !(lr.d.flags & LPM_SCALE); }
 
 static bool misaligned(const void* p) { return ((uintptr_t)p & 255u) != 0; }
 
@@ -111,7 +113,7 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
         }
         // A scaled layer whose weight-gradient kernel also sums the bias gradient keeps dz free of the scale: the bias
         // gradient is then the plain column sum of dz (eq. 8 for the bias), whatever the scale's value -- zero included.
-        lr.dz_unscaled = dtype == LPM_BF16 && (l.flags & LPM_SCALE) && wgrad_fuses_bias(dtype, lr.g);
+        lr.dz_unscaled = (l.flags & LPM_SCALE) && wgrad_fuses_bias(dtype, lr.g) && dgrad_scales_dz(dtype, lr.g);
         if (l.flags & (LPM_RELU | LPM_SCALE)) {          // needs its own dz buffer (it outlives the layer's turn)
             lr.dz_off = gws;
             gws += align_up(o.elems() * (size_t)microbatch * s->esz, 256);
@@ -134,7 +136,7 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
     for (int32_t i = first; i < last; ++i) {
         LayerRt& lr = s->Ly(i);
         const lpm_layer& l = lr.d;
-        if (dtype != LPM_BF16 || !has_weights(l) || !(l.flags & (LPM_RELU | LPM_SCALE))) continue;
+        if (!has_weights(l) || !(l.flags & (LPM_RELU | LPM_SCALE))) continue;
         if (i == s->t_out) continue;           // its gradient arrives from outside the stage
         int n_src = 0, n_other = 0, n_add = 0;
         int32_t consumer = -1, first_add = last;
@@ -144,7 +146,7 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
             if (c.add_src == i) { ++n_add; first_add = std::min(first_add, j); }
         }
         if (n_src != 1 || n_other != 0) continue;
-        if ((l.flags & LPM_BIAS) && !bias_in_wgrad_ok(dtype, lr)) continue;
+        if ((l.flags & LPM_BIAS) && !bias_from_dz_ok(lr)) continue;
         if (l.add_src != LPM_NONE || n_add > 0) {
             // Residual blocks.  The layer adds a shortcut, and / or later layers use its output as their shortcut: the
             // single layer that reads it as its input comes first in layer order, so its data gradient is the last
@@ -162,9 +164,9 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
     for (int32_t i = first; i < last; ++i) {
         LayerRt& lr = s->Ly(i);
         const lpm_layer& l = lr.d;
-        if (dtype != LPM_BF16 || !has_weights(l) || (l.flags & LPM_RELU) || !(l.flags & LPM_SCALE) || l.add_src != LPM_NONE) continue;
+        if (!has_weights(l) || (l.flags & LPM_RELU) || !(l.flags & LPM_SCALE) || l.add_src != LPM_NONE) continue;
         if (i == s->t_out) continue;
-        if ((l.flags & LPM_BIAS) && !bias_in_wgrad_ok(dtype, lr)) continue;
+        if ((l.flags & LPM_BIAS) && !bias_from_dz_ok(lr)) continue;
         int n_src = 0, n_add = 0;
         int32_t user = -1;
         for (int32_t j = i + 1; j < last; ++j) {
@@ -475,13 +477,18 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
     // layer, the point in its stream where that layer's output gradient is final, and the weight phase waits for
     // that point before the layer's weight gradient instead of for the end of the data phase
     const bool by_layer = layer_slot >= 0 && deferred && (do_data != do_weights);
-    // bias_g != NULL: the layer's bias gradient is a plain column sum of bias_g that nothing in the data phase needs;
-    // it runs in the weight phase, ahead of the layer's weight gradient (scratch: the layer's own area)
+    // bias_g != NULL: the layer's bias gradient is a plain column sum of bias_g that nothing in the data phase needs and its
+    // weight-gradient kernel does not make; it runs in the weight phase, ahead of that kernel (scratch: the layer's own area)
     struct WgradJob { const LayerRt* lr; const void* xin; const void* dz; float* wdb; const float* sc; const void* bias_g; float* bias_db; };
     // One weight gradient on stream q.  fc_slot = j >= 0 (of fc_flush = M micro-batches): a layer with staging areas
     // files its operands under slot j and contracts a group of slots at a time; the first group overwrites the accumulator.
     auto one_wgrad = [&](const WgradJob& j, hipStream_t q, ReduceDesc* d) -> hipError_t {
         const LayerRt& lr = *j.lr;
+        if (j.bias_g) {
+            const hipError_t e = launch_epilogue_bwd(s->dtype, lr.g.rows_out(), lr.d.cout, j.bias_g, nullptr, nullptr, nullptr, nullptr, 0,
+                                                     j.bias_db, acc, (char*)wws + lr.wws_off, q);
+            if (e != hipSuccess) return e;
+        }
         if (fc_slot >= 0 && lr.fcs_x_off != NO) {
             if (d) d->splits = 0;
             hipError_t e = stage_operands(lr.g, j.xin, j.dz, ws + lr.fcs_x_off, ws + lr.fcs_dz_off, fc_slot, q);
@@ -542,10 +549,10 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                 const bool bias_in_wgrad = dbias && bias_in_wgrad_ok(s->dtype, lr);
                 const void* dz = g;
                 const void* bias_g = nullptr;
-                if (lr.fused_in) {
-                    dz = gw + lr.dz_off;           // written by the consumer's backward kernel
-                } else if (i == s->t_out && (boundary & LPM_DY_IS_DZ)) {
-                    dz = g;                        // the next stage applied this layer's ReLU mask to what it handed down
+                if (lr.fused_in || (i == s->t_out && (boundary & LPM_DY_IS_DZ))) {
+                    // written by the consumer's backward kernel; or the next stage applied this layer's ReLU mask to what it handed down
+                    dz = lr.fused_in ? (const void*)(gw + lr.dz_off) : g;
+                    if (dbias && !bias_in_wgrad) bias_g = dz;
                 } else {
                     void* gadd = nullptr;
                     int gadd_acc = 0;
@@ -555,7 +562,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                         have[gi(l.add_src)] = 1;
                     }
                     const bool need_dz = relu || sc;
-                    if (!need_dz && !gadd && dbias && !bias_in_wgrad && deferred) {
+                    if (!need_dz && !gadd && dbias && !bias_in_wgrad) {
                         bias_g = g;
                     } else if (need_dz || gadd || (dbias && !bias_in_wgrad)) {
                         if (do_data) LPM_HIP(launch_epilogue_bwd(s->dtype, lr.g.rows_out(), l.cout, g, relu ? yout : nullptr, lr.dz_unscaled ? nullptr : sc,
@@ -633,7 +640,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                     LPM_HIP(frontier(before));
                     if (!wtail.empty())       // weight gradients share one scratch area: keep them in a chain
                         LPM_HIP(hipStreamUpdateCaptureDependencies(st, wtail.data(), wtail.size(), hipStreamAddCaptureDependencies));
-                    LPM_HIP(one_wgrad(WgradJob{&lr, xin, dz, wdb, lr.dz_unscaled ? sc : nullptr, nullptr, nullptr}, st, nullptr));
+                    LPM_HIP(one_wgrad(WgradJob{&lr, xin, dz, wdb, lr.dz_unscaled ? sc : nullptr, bias_g, bias_g ? dbias : nullptr}, st, nullptr));
                     LPM_HIP(frontier(wtail));
                     LPM_HIP(hipStreamUpdateCaptureDependencies(st, before.data(), before.size(), hipStreamSetCaptureDependencies));
                 }
@@ -711,9 +718,6 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
             hipStream_t q = (wst2 && (k++ & 1)) ? wst2 : wst;
             if (by_layer)
                 LPM_HIP(hipStreamWaitEvent(q, s->ev_layer[(size_t)(j.lr - &s->lay[0]) * LPM_MAX_WINDOW + layer_slot], 0));
-            if (j.bias_g)
-                LPM_HIP(launch_epilogue_bwd(s->dtype, j.lr->g.rows_out(), j.lr->d.cout, j.bias_g, nullptr, nullptr, nullptr, nullptr, 0,
-                                            j.bias_db, acc, (char*)wws + j.lr->wws_off, q));
             LPM_HIP(one_wgrad(j, q, &d));
             if (d.splits > 0) red.push_back(d);
         }
@@ -731,7 +735,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
 }
 
 bool lpm_stage_can_mask_dx(const lpm_stage* s) {
-    if (!s || s->dtype != LPM_BF16 || s->first == 0) return false;
+    if (!s || s->first == 0) return false;
     int n = 0;
     for (int32_t i = s->first; i < s->last; ++i) {
         const lpm_layer& l = s->net[(size_t)i];
@@ -744,13 +748,11 @@ bool lpm_stage_can_mask_dx(const lpm_stage* s) {
 }
 
 bool lpm_stage_takes_dz(const lpm_stage* s) {
-    if (!s || s->dtype != LPM_BF16 || s->loss) return false;
+    if (!s || s->loss) return false;
     const int32_t i = s->t_out;
     if (i != s->last - 1) return false;
-    const LayerRt& lr = s->Ly(i);
-    const lpm_layer& l = lr.d;
-    if (!has_weights(l) || !(l.flags & LPM_RELU) || (l.flags & LPM_SCALE) || l.add_src != LPM_NONE) return false;
-    return !(l.flags & LPM_BIAS) || bias_in_wgrad_ok(s->dtype, lr);
+    const lpm_layer& l = s->Ly(i).d;
+    return has_weights(l) && (l.flags & LPM_RELU) && !(l.flags & LPM_SCALE) && l.add_src == LPM_NONE;
 }
 
 extern "C" int32_t lpm_stage_update(lpm_stage* s, float* params, void* lowp, float* grads, float* momentum,
