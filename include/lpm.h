@@ -75,7 +75,7 @@ extern "C" {
 #define LPM_BF16  1
 
 /* ---- schedule modes ---- */
-#define LPM_LOCKED      0   /* F_{0,j}..F_{Z-1,j}, B_{Z-1,j}..B_{0,j} for j=0..M-1 on one stream, then U_z */
+#define LPM_LOCKED      0   /* F_{0,j}..F_{Z-1,j}, B_{Z-1,j}..B_{0,j} for j=0..M-1, one after the other, then U_z */
 #define LPM_OVERLAPPED  1   /* forward chain of micro-batch j+1 runs beside the backward chain of j        */
 #define LPM_PIPELINED   2   /* as OVERLAPPED, and every stage runs on its own pair of streams (owned by the
                                schedule): stages work on different micro-batches at the same time         */
@@ -280,8 +280,9 @@ int32_t lpm_schedule_cut_fused(const lpm_schedule* s, int32_t z);
  *              backward chains; the weight phases run on streams of the library, forked from and joined back
  *              into these.  The first such run on a pair of streams launches a few short probe kernels on them
  *              and synchronises them, to find library streams that do not share a hardware queue with them);
- *              LPM_LOCKED and LPM_PIPELINED use stream_fwd only (PIPELINED forks its own streams from it and
- *              joins them back).
+ *              LPM_LOCKED and LPM_PIPELINED use stream_fwd only: inside a backward operation LOCKED runs the weight
+ *              gradients beside the data gradients, on a library stream found by the same probe and joined back
+ *              at the end of the operation; PIPELINED forks its own streams from stream_fwd and joins them back.
  * Micro-batch j uses slot j % window of stash, act_out and grad_in in every mode.
  * mode | LPM_ASYNC_UPDATE (with LPM_LOCKED or LPM_OVERLAPPED, window <= 2, not with LPM_GRAPH): the
  *   asynchronous parameter update.  Every micro-batch is a mini-batch of its own (loss = mean over its m

@@ -54,6 +54,8 @@ struct lpm_schedule {
     // OVERLAPPED: the weight phases' streams, picked from the pool so that forward, data phases, weight phases and
     // stage 0's weight phase each feed a hardware queue of their own; measured once per (sf, sb) pair
     hipStream_t ov_sf = nullptr, ov_sb = nullptr, ov_w = nullptr, ov_w0 = nullptr;
+    // LOCKED: the stream beside stream_fwd on which a backward operation's weight gradients run
+    hipStream_t lk_sf = nullptr, lk_w = nullptr;
     std::vector<char> cut_fused;         // [Z] the ReLU backward of stage z-1's last layer runs inside stage z's backward kernel
     std::vector<GraphEntry> graphs;
 
@@ -326,6 +328,18 @@ int32_t pick_weight_streams(lpm_schedule* s, hipStream_t sf, hipStream_t sb) {
     return LPM_OK;
 }
 
+// LOCKED: the operations follow each other, but inside B_{z,j} the weight gradients run beside the data phase (see
+// lpm_stage_backward_on), on a pooled stream with a hardware queue of its own.
+int32_t pick_locked_stream(lpm_schedule* s, hipStream_t sf) {
+    if (s->lk_w && s->lk_sf == sf) return LPM_OK;
+    int found = 0;
+    hipStream_t got = nullptr;
+    LPM_HIP(pick_concurrent_streams(&sf, 1, &got, 1, &found));
+    s->lk_w = found ? got : s->st[0]->side;
+    s->lk_sf = sf;
+    return LPM_OK;
+}
+
 // OVERLAPPED, three workers: 0 enqueues the forward chains on sf, 1 the data phases of the backward chains
 // on sb, 2 the weight phases and the updates on the weight streams (ov_w, and ov_w0 for stage 0; see pick_weight_streams).
 // ev_f[j*Z+Z-1]: forward chain j done; ev_b[j*Z+z]: data phase of B_{z,j} done; ev_w[j*Z]: micro-batch j done.
@@ -496,11 +510,16 @@ int32_t enqueue(lpm_schedule* s, const RunArgs& a) {
         }
         if (!heads.empty()) LPM_HIP(launch_zero_counts(heads.data(), (int)heads.size(), a.sf));
     }
+    hipStream_t lw = nullptr;            // (captured: branches of the graph)
+    if ((a.mode & 15) == LPM_LOCKED && !capturing) {
+        if ((rc = pick_locked_stream(s, a.sf))) return rc;
+        lw = s->lk_w;
+    }
     if ((a.mode & 15) == LPM_LOCKED && (a.mode & LPM_ASYNC_UPDATE)) {      // plain per-micro-batch SGD
         for (int32_t j = 0; j < M; ++j) {
             for (int32_t z = 0; z < Z; ++z) if ((rc = fwd_op(s, a, z, j, a.sf, j))) return rc;
             for (int32_t z = Z - 1; z >= 0; --z) {
-                if ((rc = bwd_op(s, a, z, j, a.sf, a.sf, LPM_PHASE_DATA | LPM_PHASE_WEIGHTS, j))) return rc;
+                if ((rc = bwd_op(s, a, z, j, a.sf, lw, LPM_PHASE_DATA | LPM_PHASE_WEIGHTS, j))) return rc;
                 if ((rc = upd_op(s, a, z, a.sf, j))) return rc;
                 if (j == M - 1 && (rc = copy_final_version(s, a, z, a.sf))) return rc;
             }
@@ -510,7 +529,7 @@ int32_t enqueue(lpm_schedule* s, const RunArgs& a) {
     if ((a.mode & 15) == LPM_LOCKED) {
         for (int32_t j = 0; j < M; ++j) {
             for (int32_t z = 0; z < Z; ++z) if ((rc = fwd_op(s, a, z, j, a.sf))) return rc;
-            for (int32_t z = Z - 1; z >= 0; --z) if ((rc = bwd_op(s, a, z, j, a.sf, a.sf))) return rc;
+            for (int32_t z = Z - 1; z >= 0; --z) if ((rc = bwd_op(s, a, z, j, a.sf, lw))) return rc;
         }
         for (int32_t z = 0; z < Z; ++z) if ((rc = upd_op(s, a, z, a.sf))) return rc;
         return LPM_OK;

@@ -59,9 +59,9 @@ struct lpm_stage {
     bool fwd_counts = false, bwd_counts = false;      // some layer of the pass splits its reduction (LPM_COUNT_BYTES at the head of the scratch)
     size_t gws_bytes = 0;             // size of one copy of the gradient / dz area at the head of the backward scratch
     // Weight gradients are off the critical path of B (nothing in the same pass reads them), so they run on
-    // a side stream (borrowed from the library's pool), forked from and joined back into the caller's stream.
+    // a side stream (borrowed from the library's pool), layer by layer as the data phase goes, joined back into the caller's stream.
     hipStream_t side = nullptr;
-    hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+    hipEvent_t ev_join = nullptr;
     hipEvent_t ev_w2_fork = nullptr, ev_w2_join = nullptr;      // a weight phase spread over two streams (lpm_stage_backward_on)
     // per weight layer and micro-batch slot: "this layer's output gradient is final" in the data phase's stream
     // order, for schedules that let the weight phase follow the data phase layer by layer
