@@ -21,265 +21,11 @@
 // v_mfma_f32_32x32x2_f32 (one value; four instructions share a 16-byte chunk, the K order inside a chunk being the same
 // permutation for both operands).  The weights are the instruction's first operand: accumulator element i of a lane is output
 // channel (i/4)*8 + (lane/32)*4 + i%4 of pixel lane % 32, four consecutive channels at a time.
-#include "lpm_internal.h"
-#include "elem.h"
+#include "contraction.h"
 #include "lds_dma.h"
 #include <algorithm>
 
 namespace lpm {
-
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
-
-constexpr unsigned OOB = 0xffffffffu;
-
-enum { MODE_FWD = 0, MODE_DGRAD = 1 /* stride 1 */, MODE_DGRAD_S = 2 /* stride 2..4, by residue class */ };
-
-constexpr int MAX_TAB = 128;              // taps a layer without whole K tiles per tap may have
-constexpr int MAX_KSCALE = 2048;          // channels of a float layer whose data gradient applies its scale (LDS)
-
-struct IgemmArgs {
-    const void* A;
-    const void* B;
-    void* C;                // output [M][N]
-    float* part;            // split K: fp32 partial tiles
-    unsigned* count;        // split K: blocks that have stored theirs, per output tile
-    const float* scale;
-    const float* bias;
-    const float* kscale;    // float data gradient: per-channel factor of the gathered tensor (the reduction index), or NULL
-    const void* add;
-    const void* mask;       // data gradient: zero the result where this tensor (the producer's output) is <= 0
-    const float* mscale;    // data gradient: then multiply by the producer's per-channel scale
-    void* C2;               // data gradient: the masked, not yet scaled result also goes here (the producer's shortcut), or NULL
-    const float* c2scale;   // ... times this per-channel factor (NULL: 1)
-    int acc2;               // ... added to what C2 holds
-    int relu, accumulate;
-    int M, N;
-    int Hi, Wi, Di, Ci;     // extent of the gathered tensor
-    int Hr, Wr, Dr;         // extent of the row space
-    int Kh, Kw, Kd, stride, pad, pad_d;
-    FastDiv dWr, dHr, dDr, dCc;       // row decoding; chunks per tap
-    unsigned a_bytes, b_bytes, b_pitch;
-    int kt_total, kt_per_split, splits;
-    int free_taps;          // no tap can leave the image: no mask bits needed
-    int tiles_m;            // (strided) row tiles over all classes
-    int cls_tile0[17];      // strided data gradient: first row tile of class c = (pd * s + ph) * s + pw
-    const uint16_t* pool_x; // stride-1 data gradient routed through a 2x2 max-pooling (see UnpoolDesc): its input [m][2*Hr][2*Wr][N]
-    uint16_t* pool_dst;
-    int pool_acc, pool_mask;
-    uint16_t* fwd_pool;     // forward: also store the 2x2 max-pooling of C, [m][Hr/2][Wr/2][N] (Wr = 2, 4, 8 or 16)
-};
-
-// ---- eight consecutive channels of a row -----------------------------------------------------------
-template <typename E> struct Raw8;
-template <> struct Raw8<bf16_t> { uint4 v; };
-template <> struct Raw8<float> { float4 lo, hi; };
-__device__ __forceinline__ Raw8<bf16_t> ld_raw8(const bf16_t* p) { return {*reinterpret_cast<const uint4*>(p)}; }
-__device__ __forceinline__ Raw8<float> ld_raw8(const float* p) {
-    return {*reinterpret_cast<const float4*>(p), *reinterpret_cast<const float4*>(p + 4)};
-}
-__device__ __forceinline__ void un8(const Raw8<bf16_t>& r, float (&f)[8]) {
-    const uint32_t w[4] = {r.v.x, r.v.y, r.v.z, r.v.w};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) { f[2 * k] = bf2f((uint16_t)(w[k] & 0xffffu)); f[2 * k + 1] = bf2f((uint16_t)(w[k] >> 16)); }
-}
-__device__ __forceinline__ void un8(const Raw8<float>& r, float (&f)[8]) {
-    f[0] = r.lo.x; f[1] = r.lo.y; f[2] = r.lo.z; f[3] = r.lo.w; f[4] = r.hi.x; f[5] = r.hi.y; f[6] = r.hi.z; f[7] = r.hi.w;
-}
-__device__ __forceinline__ void st8(bf16_t* p, const float (&f)[8]) {
-    *reinterpret_cast<uint4*>(p) = make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7]));
-}
-__device__ __forceinline__ void st8(float* p, const float (&f)[8]) {
-    *reinterpret_cast<float4*>(p) = make_float4(f[0], f[1], f[2], f[3]);
-    *reinterpret_cast<float4*>(p + 4) = make_float4(f[4], f[5], f[6], f[7]);
-}
-
-// Strided data gradient: pixel index (in the full tensor) of row `row` of the residue class (pd, ph, pw).
-__device__ __forceinline__ int class_pixel(const IgemmArgs& p, int row, int Hc, int Wc, int ph, int pw, int Dc, int pd) {
-    const int wq = row % Wc, t = row / Wc, hq = t % Hc;
-    int n = t / Hc, img = n;
-    if (p.Dr > 1) { const int dq = n % Dc; n /= Dc; img = n * p.Dr + dq * p.stride + pd; }
-    return (img * p.Hr + hq * p.stride + ph) * p.Wr + wq * p.stride + pw;
-}
-
-// One wavefront's 32 x (32*NIW) piece of the output, held in its private LDS area `tile` (rows of 32*NIW + 4 floats): a lane
-// takes 8 channels of a row at a time, so every tensor access is 16 (float: 32) bytes.  The operands of all the lane's
-// pieces are requested before the first is used.
-template <typename E, int NIW, int MODE>
-__device__ __forceinline__ void store_piece(const IgemmArgs& p, float* tile, int row0, int col0, int rows, int lane,
-                                            int Hc, int Wc, int ph, int pw, int Dc, int pd) {
-    constexpr int PITCH = NIW * 32 + 4, CPR = NIW * 4, RPP = 64 / CPR, NP = 32 / RPP;
-    const int ch = (lane % CPR) * 8, col = col0 + ch;
-    const E* add = (const E*)p.add;
-    const E* msk = (const E*)p.mask;
-    E* out = (E*)p.C;
-    E* out2 = (E*)p.C2;
-    if (p.N & 7) {                           // ragged rows: element by element
-#pragma unroll 1
-        for (int q = 0; q < NP; ++q) {
-            const int r = q * RPP + lane / CPR, row = row0 + r;
-            if (row >= rows) continue;
-            const size_t prow = MODE == MODE_DGRAD_S ? (size_t)class_pixel(p, row, Hc, Wc, ph, pw, Dc, pd) : (size_t)row;
-#pragma unroll 1
-            for (int k = 0; k < 8 && col + k < p.N; ++k) {
-                const size_t o = prow * p.N + col + k;
-                float v = tile[r * PITCH + ch + k];
-                if (p.scale) v *= p.scale[col + k];
-                if (p.bias) v += p.bias[col + k];
-                if (add) v += ld(add, o);
-                if (p.accumulate) v += ld(out, o);
-                if (p.relu) v = fmaxf(v, 0.f);
-                if (msk && !(ld(msk, o) > 0.f)) v = 0.f;
-                if (out2) {
-                    const float u = p.c2scale ? v * p.c2scale[col + k] : v;
-                    st(out2, o, p.acc2 ? u + ld(out2, o) : u);
-                }
-                if (p.mscale) v *= p.mscale[col + k];
-                st(out, o, v);
-            }
-        }
-        return;
-    }
-    const bool cok = col < p.N;
-    float sc[8], bi[8], ms[8], c2[8];
-    auto vec = [&](const float* q, float (&d)[8], float fill) __attribute__((always_inline)) {
-        if (q && cok) un8(ld_raw8(q + col), d);
-        else {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) d[k] = fill;
-        }
-    };
-    vec(p.scale, sc, 1.f); vec(p.bias, bi, 0.f); vec(p.mscale, ms, 1.f); vec(p.c2scale, c2, 1.f);
-    if (MODE == MODE_DGRAD && p.pool_x) {
-        // gradient of a 2x2 max-pooling output: to the first maximum of the window (row-major), through the producer's ReLU
-        // and scale where asked; all four window positions are written
-        if constexpr (sizeof(E) == 2) {
-#pragma unroll
-            for (int q = 0; q < NP; ++q) {
-                const int r = q * RPP + lane / CPR, row = row0 + r;
-                if (row >= rows || !cok) continue;
-                const int t = div_by(row, p.dWr), wq = row - t * p.Wr, n = div_by(t, p.dHr), hq = t - n * p.Hr;
-                const size_t base = ((size_t)(n * 2 * p.Hr + 2 * hq) * (2 * p.Wr) + 2 * wq) * p.N + col;
-                const size_t off[4] = {0, (size_t)p.N, (size_t)2 * p.Wr * p.N, (size_t)2 * p.Wr * p.N + p.N};
-                Raw8<bf16_t> xr[4], dr[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    xr[k] = ld_raw8((const bf16_t*)p.pool_x + base + off[k]);
-                    if (p.pool_acc) dr[k] = ld_raw8((const bf16_t*)p.pool_dst + base + off[k]);
-                }
-                float x[4][8], o[4][8], v[8];
-                un8(ld_raw8(tile + r * PITCH + ch), v);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    un8(xr[k], x[k]);
-                    if (p.pool_acc) un8(dr[k], o[k]);
-                    else {
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) o[k][j] = 0.f;
-                    }
-                }
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const float mx = fmaxf(fmaxf(x[0][j], x[1][j]), fmaxf(x[2][j], x[3][j]));
-                    float g = bf2f(f2bf(v[j]));          // the value a stored gradient of the pooling output would have had
-                    if (p.pool_mask && !(mx > 0.f)) g = 0.f;
-                    g *= ms[j];
-                    bool found = false;
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const bool hit = !found && x[k][j] == mx;
-                        found = found || hit;
-                        o[k][j] += hit ? g : 0.f;
-                    }
-                }
-#pragma unroll
-                for (int k = 0; k < 4; ++k) st8((bf16_t*)p.pool_dst + base + off[k], o[k]);
-            }
-        }
-        return;
-    }
-    size_t o[NP];
-    bool live[NP];
-    Raw8<E> ra[NP], rc[NP], rm[NP], r2[NP];
-#pragma unroll
-    for (int q = 0; q < NP; ++q) {
-        const int row = row0 + q * RPP + lane / CPR;
-        live[q] = row < rows && cok;
-        const int prow = MODE == MODE_DGRAD_S && live[q] ? class_pixel(p, row, Hc, Wc, ph, pw, Dc, pd) : row;
-        o[q] = live[q] ? (size_t)prow * p.N + col : 0;
-    }
-#pragma unroll
-    for (int q = 0; q < NP; ++q) if (add) ra[q] = ld_raw8(add + o[q]);
-#pragma unroll
-    for (int q = 0; q < NP; ++q) if (p.accumulate) rc[q] = ld_raw8((const E*)out + o[q]);
-#pragma unroll
-    for (int q = 0; q < NP; ++q) if (msk) rm[q] = ld_raw8(msk + o[q]);
-#pragma unroll
-    for (int q = 0; q < NP; ++q) if (out2 && p.acc2) r2[q] = ld_raw8((const E*)out2 + o[q]);
-#pragma unroll
-    for (int q = 0; q < NP; ++q) {
-        const int r = q * RPP + lane / CPR;
-        float v[8], t[8];
-        un8(ld_raw8(tile + r * PITCH + ch), v);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = v[k] * sc[k] + bi[k];
-        if (add) { un8(ra[q], t);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] += t[k]; }
-        if (p.accumulate) { un8(rc[q], t);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] += t[k]; }
-        if (p.relu) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = fmaxf(v[k], 0.f); }
-        if (msk) { un8(rm[q], t);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = t[k] > 0.f ? v[k] : 0.f; }
-        if (out2) {
-            float u[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) u[k] = v[k] * c2[k];
-            if (p.acc2) { un8(r2[q], t);
-#pragma unroll
-                for (int k = 0; k < 8; ++k) u[k] += t[k]; }
-            if (live[q]) st8(out2 + o[q], u);
-        }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] *= ms[k];
-        if (live[q]) st8(out + o[q], v);
-        if (MODE == MODE_FWD && p.fwd_pool) {
-            if constexpr (sizeof(E) == 2) {
-#pragma unroll
-                for (int k = 0; k < 8; ++k) v[k] = bf2f(f2bf(v[k]));
-                st8(tile + r * PITCH + ch, v);
-            }
-        }
-    }
-    if (MODE == MODE_FWD && p.fwd_pool) {
-        // the piece's 32 rows are whole pairs of image rows: eight pooling windows of rows (r, r+1, r+Wr, r+Wr+1)
-        if constexpr (sizeof(E) == 2) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const int w = lane / CPR;
-            if (w < 8) {
-                const int hw = p.Wr >> 1, py = w / hw, px = w - py * hw, r = 2 * py * p.Wr + 2 * px;
-                if (row0 + r < rows && cok) {
-                    float a[8], b[8], c[8], d[8];
-                    un8(ld_raw8(tile + r * PITCH + ch), a);
-                    un8(ld_raw8(tile + (r + 1) * PITCH + ch), b);
-                    un8(ld_raw8(tile + (r + p.Wr) * PITCH + ch), c);
-                    un8(ld_raw8(tile + (r + p.Wr + 1) * PITCH + ch), d);
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) a[k] = fmaxf(fmaxf(a[k], b[k]), fmaxf(c[k], d[k]));
-                    st8((bf16_t*)p.fwd_pool + (size_t)((row0 >> 2) + w) * p.N + col, a);
-                }
-            }
-        }
-    }
-}
-
-__device__ __forceinline__ unsigned tap_bits(int lo, int hi) { return hi > lo ? (1u << hi) - (1u << lo) : 0u; }
 
 // partial tiles pass between blocks on different XCDs: stores go through to memory, loads do not hit a stale line
 constexpr int AUX_AGENT = 16;
@@ -671,24 +417,27 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
             }
     }
 
-    // the wavefront's private staging area for the epilogue
-    float* piece = reinterpret_cast<float*>(lds) + wave * (32 * (NI * 32 + 4));
-    static_assert(WGM * WGN * 32 * (NI * 32 + 4) * 4 <= NST * STAGE, "staging fits the dead stages");
+    // the wavefront's private staging area for the epilogue: a piece of 32 rows per mi.  (The pieces are stored in a loop that
+    // is not unrolled: the epilogue is most of the kernel's code, and a 128x128 data gradient of twice this size no longer
+    // fitted the instruction cache.)
+    constexpr int PIECE = 32 * (NI * 32 + 4);
+    float* piece = reinterpret_cast<float*>(lds) + wave * MI * PIECE;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+    for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<float4*>(piece + rl * (NI * 32 + 4) + ni * 32 + q * 8 + kh_ * 4) =
+                *reinterpret_cast<float4*>(piece + mi * PIECE + rl * (NI * 32 + 4) + ni * 32 + q * 8 + kh_ * 4) =
                     make_float4(acc[mi][ni][4 * q], acc[mi][ni][4 * q + 1], acc[mi][ni][4 * q + 2], acc[mi][ni][4 * q + 3]);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        store_piece<E, NI, MODE>(p, piece, m0 + wm * WTM + mi * 32, n0 + wn * WTN, rows, lane, Hc, Wc, ph, pw, Dc, pd);
-    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll 1
+    for (int mi = 0; mi < MI; ++mi)
+        store_piece<E, NI, MODE>(p, piece + mi * PIECE, m0 + wm * WTM + mi * 32, n0 + wn * WTN, rows, lane, Hc, Wc, ph, pw, Dc, pd);
 }
 
 // --------------------------------------------------------------------------------------------------
@@ -778,7 +527,8 @@ bool mfma_fwd_pools(int dtype, const ConvGeom& g) {
 
 template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, bool UNI, int BT, int OCC>
 static hipError_t go(const IgemmArgs& a, int64_t tiles, hipStream_t st) {
-    constexpr int bytes = NST * (BM + BN) * 128 + (UNI ? 0 : MAX_TAB * 16) + (BT == BT_SCALED ? MAX_KSCALE * 4 : 0);
+    constexpr int stages = NST * (BM + BN) * 128 + (UNI ? 0 : MAX_TAB * 16) + (BT == BT_SCALED ? MAX_KSCALE * 4 : 0);
+    constexpr int epilogue = BM * WGN * (BN / WGN + 4) * 4, bytes = stages > epilogue ? stages : epilogue;
     static const hipError_t attr = hipFuncSetAttribute((const void*)igemm_kernel<E, BM, BN, WGM, WGN, NST, MODE, UNI, BT, OCC>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (attr != hipSuccess) return attr;
@@ -820,6 +570,7 @@ static hipError_t run_igemm(int dtype, int mode, IgemmArgs a, IgemmPlan pl, void
         }
     }
     if (mode == MODE_FWD) return dtype == LPM_BF16 ? go_uni<bf16_t, MODE_FWD, BT_NONE>(pl, a, tiles, st) : go_uni<float, MODE_FWD, BT_NONE>(pl, a, tiles, st);
+    if (mode == MODE_UNPOOL) return go_uni<bf16_t, MODE_UNPOOL, BT_NONE>(pl, a, tiles, st);
     if (dtype == LPM_BF16) return a.stride == 1 ? go_uni<bf16_t, MODE_DGRAD, BT_NONE>(pl, a, tiles, st) : go_uni<bf16_t, MODE_DGRAD_S, BT_NONE>(pl, a, tiles, st);
     if (a.kscale) return a.stride == 1 ? go_uni<float, MODE_DGRAD, BT_SCALED>(pl, a, tiles, st) : go_uni<float, MODE_DGRAD_S, BT_SCALED>(pl, a, tiles, st);
     return a.stride == 1 ? go_uni<float, MODE_DGRAD, BT_PLAIN>(pl, a, tiles, st) : go_uni<float, MODE_DGRAD_S, BT_PLAIN>(pl, a, tiles, st);
@@ -850,7 +601,7 @@ hipError_t mfma_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void
 hipError_t mfma_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const void* wt, void* dx, int accumulate, const void* mask,
                            const float* mscale, void* ws, bool ws_zeroed, hipStream_t st, const UnpoolDesc* unpool, const DgradSide* side, const float* kscale) {
     if (kscale && (dtype == LPM_BF16 || g.Cout > MAX_KSCALE)) return hipErrorInvalidValue;      // (bf16: the transposed copy carries the scale)
-    if (side && unpool) return hipErrorInvalidValue;
+    if (unpool && (side || dtype != LPM_BF16 || g.stride != 1)) return hipErrorInvalidValue;
     const int es = dtype == LPM_BF16 ? 2 : 4;
     IgemmArgs a{};
     a.A = dz; a.B = wt; a.C = dx;
@@ -880,7 +631,7 @@ hipError_t mfma_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const v
         for (int c = ncls; c <= 16; ++c) a.cls_tile0[c] = t;
         a.tiles_m = t;
     }
-    return run_igemm(dtype, MODE_DGRAD, a, pl, ws, ws_zeroed, st);
+    return run_igemm(dtype, unpool ? MODE_UNPOOL : MODE_DGRAD, a, pl, ws, ws_zeroed, st);
 }
 
 // clears the arrival counts at the head of up to 16 scratch areas
