@@ -1,6 +1,7 @@
-// Chooses the contraction kernel for a convolution / FC shape: bf16 MFMA implicit GEMM where the
-// channel counts allow 16-byte K chunks, the shape-generic kernels otherwise (float element type,
-// 3-channel first layer, 10-class head).
+// Chooses the contraction kernel for a convolution / FC shape: matrix-core tiles where the channel counts come in 16-byte
+// chunks (igemm.hip, wgrad.hip), matrix cores fed by per-element gathers where they do not (gather.hip: image inputs, a few
+// feature maps), the shape-generic vector-ALU kernels for what is left (launches of a few thousand products, filters of more
+// than 12 taps an axis, strided data gradients of ragged channels).
 #include "lpm_internal.h"
 #include <algorithm>
 
@@ -40,14 +41,16 @@ bool fc_staged_ok(const ConvGeom& g);
 hipError_t fc_wgrad_staged(const ConvGeom& g, const void* xs, const void* dzs, int slots, float* dw, float* dbias,
                            const float* rscale, int accumulate, hipStream_t st);
 
-bool mfma_wgrad_flat_ok(const ConvGeom& g);
-size_t mfma_wgrad_flat_ws_bytes(const ConvGeom& g);
-hipError_t mfma_conv_wgrad_flat(const ConvGeom& g, const void* x, const void* dz, float* dw, float* dbias,
-                                const float* rscale, int accumulate, void* ws, hipStream_t st);
-
-bool smallk_ok(const ConvGeom& g);
-hipError_t smallk_conv_fwd(const ConvGeom& g, const void* x, const void* w, const float* scale, const float* bias,
+bool gather_fwd_ok(int dtype, const ConvGeom& g);
+bool gather_dgrad_ok(int dtype, const ConvGeom& g);
+bool gather_wgrad_ok(int dtype, const ConvGeom& g);
+size_t gather_wgrad_ws_bytes(const ConvGeom& g);
+hipError_t gather_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* scale, const float* bias,
                            const void* add, int relu, void* y, hipStream_t st);
+hipError_t gather_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const float* dzscale, const void* w, void* dx, int accumulate,
+                             const void* mask, const float* mscale, hipStream_t st);
+hipError_t gather_conv_wgrad(int dtype, const ConvGeom& g, const void* x, const void* dz, float* dw, float* dbias, const float* rscale,
+                             int accumulate, void* ws, hipStream_t st, ReduceDesc* deferred);
 
 // A filter that covers its whole input makes one output pixel per sample: x is a matrix [m][K] and w [Cout][K] as they lie in
 // memory, so the layer is a 1x1 convolution of K channels.  (As a convolution its data gradient would visit every tap for
@@ -80,7 +83,7 @@ size_t dgrad_ws_bytes(int dtype, const ConvGeom& g) {
 size_t wgrad_ws_bytes(int dtype, const ConvGeom& g) {
     if (dtype == LPM_BF16 && fc_skinny_ok(g)) return 0;
     if (wgrad_mm_ok(dtype, fc_view(g))) return wgrad_mm_ws_bytes(dtype, fc_view(g));
-    if (dtype == LPM_BF16 && mfma_wgrad_flat_ok(g)) return mfma_wgrad_flat_ws_bytes(g);
+    if (gather_wgrad_ok(dtype, g)) return gather_wgrad_ws_bytes(g);
     return wgrad_generic_ws_bytes(g);
 }
 
@@ -90,11 +93,11 @@ hipError_t launch_conv_fwd(int dtype, const ConvGeom& g, const void* x, const vo
                            const float* bias, const void* add, int relu, void* y, void* ws, hipStream_t st, void* pool_y, bool ws_zeroed) {
     if (pool_y && !fwd_can_pool(dtype, g)) return hipErrorInvalidValue;      // callers ask fwd_can_pool first
     if (fwd_mm(dtype, fc_view(g))) return mfma_conv_fwd(dtype, fc_view(g), x, w, scale, bias, add, relu, y, ws, ws_zeroed, st, pool_y);
-    if (dtype == LPM_BF16 && smallk_ok(g)) return smallk_conv_fwd(g, x, w, scale, bias, add, relu, y, st);
+    if (gather_fwd_ok(dtype, g)) return gather_conv_fwd(dtype, g, x, w, scale, bias, add, relu, y, st);
     return conv_fwd_generic_launch(dtype, g, x, w, scale, bias, add, relu, y, st);
 }
 
-bool wgrad_fuses_bias(int dtype, const ConvGeom& g) { return wgrad_mm_ok(dtype, fc_view(g)) || (dtype == LPM_BF16 && (fc_skinny_ok(g) || mfma_wgrad_flat_ok(g))); }
+bool wgrad_fuses_bias(int dtype, const ConvGeom& g) { return wgrad_mm_ok(dtype, fc_view(g)) || gather_wgrad_ok(dtype, g) || (dtype == LPM_BF16 && fc_skinny_ok(g)); }
 
 // whether the data gradient wants the [Cin][Kh][Kw][Cout] copy of the weights
 bool dgrad_uses_wt(int dtype, const ConvGeom& g) { return dtype == LPM_BF16 && !fc_skinny_ok(g) && mfma_dgrad_ok(dtype, g); }
@@ -122,6 +125,7 @@ hipError_t launch_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const
     if (dtype == LPM_BF16 && wt && mfma_dgrad_ok(dtype, g)) return mfma_conv_dgrad(dtype, g, dz, wt, dx, accumulate, mask, mscale, ws, ws_zeroed, st, unpool, side, nullptr);
     if (dtype == LPM_F32 && f32_dgrad_viewed(g, mscale, side)) return mfma_conv_dgrad(dtype, fc_view(g), dz, w, dx, accumulate, mask, nullptr, ws, ws_zeroed, st, nullptr, nullptr, dzscale);
     if (dtype == LPM_F32 && dgrad_mm(dtype, g)) return mfma_conv_dgrad(dtype, g, dz, w, dx, accumulate, mask, mscale, ws, ws_zeroed, st, nullptr, side, dzscale);
+    if (gather_dgrad_ok(dtype, g)) return gather_conv_dgrad(dtype, g, dz, dzscale, w, dx, accumulate, mask, mscale, st);
     return conv_dgrad_generic_launch(dtype, g, dz, dzscale, w, dx, accumulate, mask, mscale, st);
 }
 
@@ -130,7 +134,7 @@ hipError_t launch_conv_wgrad(int dtype, const ConvGeom& g, const void* x, const 
     if (deferred) deferred->splits = 0;
     if (dtype == LPM_BF16 && fc_skinny_ok(g)) return fc_wgrad(g, x, dz, dw, dbias, rscale, accumulate, st);
     if (wgrad_mm_ok(dtype, fc_view(g))) return wgrad_mm_launch(dtype, fc_view(g), x, dz, dw, dbias, rscale, accumulate, ws, st, deferred);
-    if (dtype == LPM_BF16 && mfma_wgrad_flat_ok(g)) return mfma_conv_wgrad_flat(g, x, dz, dw, dbias, rscale, accumulate, ws, st);
+    if (gather_wgrad_ok(dtype, g)) return gather_conv_wgrad(dtype, g, x, dz, dw, dbias, rscale, accumulate, ws, st, deferred);
     if (dbias || rscale) return hipErrorInvalidValue;      // callers ask wgrad_fuses_bias first
     return conv_wgrad_generic_launch(dtype, g, x, dz, dw, accumulate, ws, st);
 }

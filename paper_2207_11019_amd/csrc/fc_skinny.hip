@@ -9,8 +9,7 @@
 
 namespace lpm {
 
-hipError_t launch_splitk_epilogue(const float* part, int splits, int64_t MN, int N, const float* scale, const float* bias,
-                                  const void* add, int relu, int accumulate, const void* mask, const float* mscale,
+hipError_t launch_splitk_epilogue(const float* part, int splits, int64_t MN, int N, int accumulate, const void* mask, const float* mscale,
                                   void* C, hipStream_t st);
 
 constexpr int FC_MAX_M = 8;       // beyond this the per-lane accumulators no longer fit the register file
@@ -141,8 +140,7 @@ hipError_t fc_dgrad(const ConvGeom& g, const void* dz, const float* dzscale, con
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // the epilogue's channel index is (element index) % Cin: K is a multiple of Cin
-    return launch_splitk_epilogue((const float*)ws, p.splits, (int64_t)g.m * K, g.Cin, nullptr, nullptr, nullptr, 0, accumulate,
-                                  mask, mscale, dx, st);
+    return launch_splitk_epilogue((const float*)ws, p.splits, (int64_t)g.m * K, g.Cin, accumulate, mask, mscale, dx, st);
 }
 
 // ---- weight gradient: dW[co][k] (+)= rscale[co] * sum_r dz[r][co] * x[r][k];  db[co] (+)= sum_r dz[r][co] ----

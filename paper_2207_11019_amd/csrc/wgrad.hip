@@ -403,9 +403,10 @@ bool wgrad_mm_ok(int dtype, const ConvGeom& g) {
            (g.rows_in() + slack_in) * g.Cin * es < lim && (int64_t)(g.Cout + 128) * g.K() < ((int64_t)1 << 30);
 }
 
+static size_t wg_stride(const ConvGeom& g) { return ((size_t)g.Cout * g.K() + g.Cout + 3) & ~(size_t)3; }      // (16-byte loads in the reduction)
 size_t wgrad_mm_ws_bytes(int dtype, const ConvGeom& g) {
     const WgPlan pl = plan_wgrad(dtype, g);
-    return pl.splits > 1 ? (size_t)pl.splits * ((size_t)g.Cout * g.K() + g.Cout) * sizeof(float) : 0;
+    return pl.splits > 1 ? (size_t)pl.splits * wg_stride(g) * sizeof(float) : 0;
 }
 
 template <typename E, int BM, int BN, int WGM, int WGN, int TAPS, int NST, int OCC>
@@ -428,7 +429,7 @@ hipError_t wgrad_mm_launch(int dtype, const ConvGeom& g, const void* x, const vo
     a.X = x; a.DZ = dz;
     a.out = pl.splits > 1 ? (float*)ws : dw;
     a.db = dbias; a.rscale = rscale;
-    a.part_stride = (size_t)g.Cout * g.K() + g.Cout;
+    a.part_stride = wg_stride(g);
     a.dz_bytes = (unsigned)(g.rows_out() * g.Cout * es); a.x_bytes = (unsigned)(g.rows_in() * g.Cin * es);
     a.Cout = g.Cout; a.Cin = g.Cin; a.Kh = g.Kh; a.Kw = g.Kw; a.Kd = g.Kd;
     a.H = g.H; a.W = g.W; a.D = g.D; a.Ho = g.Ho; a.Wo = g.Wo; a.Do = g.Do;
