@@ -1,0 +1,101 @@
+"""The contraction kernels at the edges of their tiles and dispatch rules, through the C ABI, against PyTorch's convolutions
+in double precision on the CPU: every tile variant, channel counts that are whole 16-byte chunks but no whole K tiles, channel
+counts that are not (gathered operands), strides, volumes, split reductions called twice on the same scratch."""
+import numpy as np
+import pytest
+
+from test_gpu_conv import G, G3
+from harness import rel_err
+
+pytestmark = pytest.mark.gpu
+
+BOTH = [
+    G(2, 9, 7, 24, 40, 3, 1, 1),          # no whole K tile per tap; ragged M and N
+    G(1, 10, 9, 40, 72, 5, 2, 2),         # stride 2, every residue class, N over one tile
+    G(1, 11, 11, 8, 16, 3, 3, 1),         # stride 3: one chunk per tap (float: two)
+    G(3, 4, 4, 64, 72, 4, 1, 0),          # the filter covers its input: seen as 1x1
+    G(2, 4, 4, 512, 64, 3, 1, 1),         # split reduction, one row tile
+    G3(1, 4, 5, 6, 16, 24, 3, 1, 1),      # volume
+    G3(1, 5, 5, 4, 16, 32, 3, 2, 1),      # volume, stride 2
+    G(2, 17, 15, 3, 64, 3, 1, 1),         # gathered: two channel tiles
+    G(1, 95, 97, 3, 65, 3, 2, 1),         # gathered: a channel past two tiles, stride 2
+    G(2, 70, 70, 6, 16, 5, 1, 0),         # gathered: more than one block's row tiles, five K steps and more
+    G(2, 14, 14, 6, 16, 5, 1, 0),         # gathered: the reduction shared by a block's wavefronts
+    G(1, 33, 31, 3, 33, 7, 2, 3),         # gathered: 147 terms
+    G3(1, 9, 8, 7, 1, 32, 3, 1, 1),       # gathered: a volume of one channel
+    G(2, 8, 8, 5, 7, 3, 1, 1),            # fewer than 256 rows
+    G(3, 1, 1, 84, 10, 1, 1, 0),          # head
+]
+BF16 = [
+    G(1, 152, 152, 8, 128, 1, 1, 0),      # 181 tiles of 128x128: eight wavefronts
+    G(3, 128, 128, 8, 128, 1, 1, 0),      # 384 of them: four
+    G(3, 128, 128, 8, 64, 3, 1, 1),       # 384 tiles of 128x64
+    G(3, 127, 128, 64, 72, 1, 1, 0),      # N over half a tile, ragged M
+    G(1, 128, 128, 128, 8, 1, 1, 0),      # the same sizes for the data gradient
+    G(3, 128, 128, 128, 8, 1, 1, 0),
+    G(3, 128, 128, 256, 256, 1, 1, 0),    # 128x128 weight-gradient tiles
+    G(1, 20, 15, 64, 64, 3, 1, 1),        # filter rows over segments of 8 pixels, the last one 7 wide
+    G(1, 20, 13, 72, 40, 3, 1, 1),        # ... 5 wide: single taps
+    G3(1, 3, 6, 8, 64, 64, 3, 1, 1),      # ... volume
+]
+
+
+@pytest.fixture(scope="module")
+def lpm():
+    import torch
+    assert torch.cuda.is_available()
+    import paper_2207_11019_amd as lpm
+    return lpm
+
+
+def _id(c):
+    g = c[1]
+    return "%s_m%d_%s%dx%d_%d_%d_k%d_s%d" % (c[0], g["m"], "d%d_" % g["d"] if "d" in g else "", g["h"], g["w"], g["cin"], g["cout"], g["kh"], g["stride"])
+
+
+@pytest.mark.parametrize("case", [(t, g) for g in BOTH for t in ("bf16", "f32")] + [("bf16", g) for g in BF16], ids=_id)
+def test_contractions(lpm, case):
+    import torch
+    import torch.nn.grad as tg
+    name, g = case
+    print("geometry", name, g, flush=True)
+    bf = name == "bf16"
+    dt, td = (lpm.BF16, torch.bfloat16) if bf else (lpm.F32, torch.float32)
+    gen = torch.Generator().manual_seed(7)
+    D, KD, s = g.get("d", 1), g.get("kd", 1), g["stride"]
+    pad = (g.get("pad_d", 0), g["pad"], g["pad"])
+    st = (s if D > 1 else 1, s, s)
+    # channels last as the kernels take them; double precision, [N][C][D][H][W], for the reference
+    x = torch.randn(g["m"], D, g["h"], g["w"], g["cin"], generator=gen).to(td)
+    w = (torch.randn(g["cout"], KD, g["kh"], g["kw"], g["cin"], generator=gen) / (g["cin"] * KD * g["kh"] * g["kw"]) ** 0.5).to(td)
+    nchw = lambda t: t.double().permute(0, 4, 1, 2, 3).contiguous()
+    nhwc = lambda t: t.permute(0, 2, 3, 4, 1).contiguous()
+    xr, wr = nchw(x), nchw(w)
+    z = torch.nn.functional.conv3d(xr, wr, stride=st, padding=pad)
+    dz = torch.randn(nhwc(z).shape, generator=gen).to(td)
+    add = torch.randn(dz.shape, generator=gen).to(td)
+    sc, bi = torch.rand(g["cout"], generator=gen) + 0.5, torch.randn(g["cout"], generator=gen)
+    dx_ref = nhwc(tg.conv3d_input(xr.shape, wr, nchw(dz), stride=st, padding=pad))
+    dw_ref = nhwc(tg.conv3d_weight(xr, wr.shape, nchw(dz), stride=st, padding=pad))
+
+    dev = lambda t: t.reshape(-1).cuda()
+    xd, wd, dzd, addd, scd, bid = dev(x), dev(w), dev(dz), dev(add), dev(sc), dev(bi)
+    wt = dev(w.permute(4, 1, 2, 3, 0).contiguous()) if bf else None
+    ws = torch.full((max(max(lpm.lpm_conv_ws_bytes(g, dt)), 256),), 0x55, dtype=torch.uint8, device="cuda")
+    err = lambda got, ref: rel_err(got.float().cpu().numpy().astype(np.float64), ref.reshape(-1).numpy())
+    tol = 2e-2 if bf else 2e-5
+
+    y = [torch.empty(dz.numel(), dtype=td, device="cuda") for _ in range(2)]
+    for k in range(2):                    # the second call meets the first one's scratch
+        lpm.lpm_conv_forward(g, dt, xd, wd, scd, bid, addd, True, y[k], ws)
+    dx = [torch.full((x.numel(),), 0.5, dtype=td, device="cuda") for _ in range(2)]
+    for k in range(2):
+        lpm.lpm_conv_dgrad(g, dt, dzd, wd, wt, dx[k], k == 1, ws)
+    dw = [torch.full((w.numel(),), 0.5, dtype=torch.float32, device="cuda") for _ in range(2)]
+    for k in range(2):
+        lpm.lpm_conv_wgrad(g, dt, xd, dzd, dw[k], k == 1, ws)
+    torch.cuda.synchronize()
+    assert err(y[0], (nhwc(z) * sc + bi + add.double()).clamp(min=0)) <= tol
+    assert torch.equal(y[0], y[1])
+    assert err(dx[0], dx_ref) <= tol and err(dx[1], dx_ref + 0.5) <= tol
+    assert err(dw[0], dw_ref) <= (1e-3 if bf else 2e-5) and err(dw[1], dw_ref + 0.5) <= (1e-3 if bf else 2e-5)
