@@ -24,13 +24,13 @@ struct IgemmArgs {
     const float* scale;
     const float* bias;
     const float* kscale;    // float data gradient: per-channel factor of the gathered tensor (the reduction index), or NULL
-    const void* add;
+    const void* add;        // added to the result (data gradient: what the output, or another tensor, holds)
     const void* mask;       // data gradient: zero the result where this tensor (the producer's output) is <= 0
     const float* mscale;    // data gradient: then multiply by the producer's per-channel scale
     void* C2;               // data gradient: the masked, not yet scaled result also goes here (the producer's shortcut), or NULL
     const float* c2scale;   // ... times this per-channel factor (NULL: 1)
     int acc2;               // ... added to what C2 holds
-    int relu, accumulate;
+    int relu;
     int M, N;
     int Hi, Wi, Di, Ci;     // extent of the gathered tensor
     int Hr, Wr, Dr;         // extent of the row space
@@ -79,61 +79,166 @@ __device__ __forceinline__ int class_pixel(const IgemmArgs& p, int row, int Hc, 
     return (img * p.Hr + hq * p.stride + ph) * p.Wr + wq * p.stride + pw;
 }
 
-// One wavefront's 32 x (32*NIW) piece of the output, held in its private LDS area `tile` (rows of 32*NIW + 4 floats): a lane
-// takes 8 channels of a row at a time, so every tensor access is 16 (float: 32) bytes.  The operands of all the lane's
-// pieces are requested before the first is used.
-template <typename E, int NIW, int MODE>
-__device__ __forceinline__ void store_piece(const IgemmArgs& p, float* tile, int row0, int col0, int rows, int lane,
-                                            int Hc, int Wc, int ph, int pw, int Dc, int pd) {
-    constexpr bool FWD = MODE == MODE_FWD;   // (forward: scale, bias, add, relu; data gradient: accumulate, add, mask, C2, mscale)
-    constexpr int PITCH = NIW * 32 + 4, CPR = NIW * 4, RPP = 64 / CPR, NP = 32 / RPP;
-    const int ch = (lane % CPR) * 8, col = col0 + ch;
-    const E* add = (const E*)p.add;
-    const E* msk = (const E*)p.mask;
-    E* out = (E*)p.C;
-    E* out2 = (E*)p.C2;
-    if (p.N & 7) {                           // ragged rows: the lanes take consecutive elements
-        const int nc = min(p.N - col0, NIW * 32), total = nc > 0 ? min(32, rows - row0) * nc : 0;
-#pragma unroll 1
-        for (int i = lane; i < total; i += 64) {
-            const int r = i / nc, c = i - r * nc, row = row0 + r, cc = col0 + c;
-            const size_t prow = MODE == MODE_DGRAD_S ? (size_t)class_pixel(p, row, Hc, Wc, ph, pw, Dc, pd) : (size_t)row;
-            const size_t o = prow * p.N + cc;
-            float v = tile[r * PITCH + c];
-            if (FWD && p.scale) v *= p.scale[cc];
-            if (FWD && p.bias) v += p.bias[cc];
-            if (add) v += ld(add, o);
-            if (!FWD && p.accumulate) v += ld(out, o);
-            if (FWD && p.relu) v = fmaxf(v, 0.f);
-            if (!FWD && msk && !(ld(msk, o) > 0.f)) v = 0.f;
-            if (!FWD && out2) {
-                const float u = p.c2scale ? v * p.c2scale[cc] : v;
-                st(out2, o, p.acc2 ? u + ld(out2, o) : u);
+// A wavefront's part of the output, MI pieces of 32 rows x 32*NIW channels, held in its private LDS area (rows of 32*NIW + 4
+// floats).  A lane takes 8 channels of a row at a time, so every tensor access is 16 (float: 32) bytes.  load() requests the
+// operands of all the lane's chunks; the kernels call it before their main loop where the registers allow, so that a
+// launch of a few K tiles does not end with a memory latency of its own.
+template <typename E, int MI, int NIW, int MODE>
+struct Epilogue {
+    static constexpr bool FWD = MODE == MODE_FWD;      // (forward: scale, bias, add, relu; data gradient: add, mask, C2, mscale)
+    static constexpr int PITCH = NIW * 32 + 4, PIECE = 32 * PITCH, CPR = NIW * 4, RPP = 64 / CPR, NP = 32 / RPP, R = MI * NP;
+    Raw8<E> ra[R], rm[FWD ? 1 : R], r2[FWD ? 1 : R];
+    float f0[8], f1[8];                       // forward: scale, bias; data gradient: mscale, c2scale
+    int o[R];                                 // element offset of the chunk, -1: none
+
+    // row0: the part's first row, in the residue class (pd, ph, pw) of extent (Dc, Hc, Wc) for a strided data gradient
+    __device__ __forceinline__ void load(const IgemmArgs& p, int row0, int col0, int rows, int lane, int Hc, int Wc, int ph, int pw, int Dc, int pd) {
+        if ((p.N & 7) || MODE == MODE_UNPOOL) return;
+        const int col = col0 + (lane % CPR) * 8;
+        const bool cok = col < p.N;
+        auto vec = [&](const float* q, float (&d)[8], float fill) __attribute__((always_inline)) {
+            if (q && cok) un8(ld_raw8(q + col), d);
+            else {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) d[k] = fill;
             }
-            if (!FWD && p.mscale) v *= p.mscale[cc];
-            st(out, o, v);
+        };
+        vec(FWD ? p.scale : p.mscale, f0, 1.f);
+        vec(FWD ? p.bias : p.c2scale, f1, FWD ? 0.f : 1.f);
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int row = row0 + q * RPP + lane / CPR;
+            const bool live = row < rows && cok;
+            const int prow = MODE == MODE_DGRAD_S && live ? class_pixel(p, row, Hc, Wc, ph, pw, Dc, pd) : row;
+            o[q] = live ? prow * p.N + col : -1;
         }
-        return;
+        if (p.add) {
+#pragma unroll
+            for (int q = 0; q < R; ++q) ra[q] = ld_raw8((const E*)p.add + max(o[q], 0));
+        }
+        if (!FWD && p.mask) {
+#pragma unroll
+            for (int q = 0; q < R; ++q) rm[q] = ld_raw8((const E*)p.mask + max(o[q], 0));
+        }
+        if (!FWD && p.C2 && p.acc2) {
+#pragma unroll
+            for (int q = 0; q < R; ++q) r2[q] = ld_raw8((const E*)p.C2 + max(o[q], 0));
+        }
     }
-    const bool cok = col < p.N;
-    float sc[8], bi[8], ms[8], c2[8];
-    auto vec = [&](const float* q, float (&d)[8], float fill) __attribute__((always_inline)) {
-        if (q && cok) un8(ld_raw8(q + col), d);
+
+    __device__ __forceinline__ void store(const IgemmArgs& p, float* area, int row0, int col0, int rows, int lane, int Hc, int Wc, int ph, int pw, int Dc, int pd) {
+        const int ch = (lane % CPR) * 8, col = col0 + ch;
+        const E* add = (const E*)p.add;
+        const E* msk = (const E*)p.mask;
+        E* out = (E*)p.C;
+        E* out2 = (E*)p.C2;
+        if constexpr (MODE == MODE_UNPOOL) {
+            unpool(p, area, row0, col0, rows, lane);
+            return;
+        }
+        if (p.N & 7) {                           // ragged rows: the lanes take consecutive elements
+            const int nc = min(p.N - col0, NIW * 32), total = nc > 0 ? min(32 * MI, rows - row0) * nc : 0;
+#pragma unroll 1
+            for (int i = lane; i < total; i += 64) {
+                const int r = i / nc, c = i - r * nc, row = row0 + r, cc = col0 + c;
+                const size_t prow = MODE == MODE_DGRAD_S ? (size_t)class_pixel(p, row, Hc, Wc, ph, pw, Dc, pd) : (size_t)row;
+                const size_t e = prow * p.N + cc;
+                float v = area[r * PITCH + c];
+                if (FWD && p.scale) v *= p.scale[cc];
+                if (FWD && p.bias) v += p.bias[cc];
+                if (add) v += ld(add, e);
+                if (FWD && p.relu) v = fmaxf(v, 0.f);
+                if (!FWD && msk && !(ld(msk, e) > 0.f)) v = 0.f;
+                if (!FWD && out2) {
+                    const float u = p.c2scale ? v * p.c2scale[cc] : v;
+                    st(out2, e, p.acc2 ? u + ld(out2, e) : u);
+                }
+                if (!FWD && p.mscale) v *= p.mscale[cc];
+                st(out, e, v);
+            }
+            return;
+        }
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            float* t8 = area + (q * RPP + lane / CPR) * PITCH + ch;
+            float v[8], t[8];
+            un8(ld_raw8(t8), v);
+            if (FWD) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = v[k] * f0[k] + f1[k];
+            }
+            if (add) { un8(ra[q], t);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] += t[k]; }
+            if (FWD && p.relu) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = fmaxf(v[k], 0.f); }
+            if (!FWD && msk) { un8(rm[FWD ? 0 : q], t);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = t[k] > 0.f ? v[k] : 0.f; }
+            if (!FWD && out2) {
+                float u[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) u[k] = v[k] * f1[k];
+                if (p.acc2) { un8(r2[FWD ? 0 : q], t);
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) u[k] += t[k]; }
+                if (o[q] >= 0) st8(out2 + o[q], u);
+            }
+            if (!FWD) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] *= f0[k];
+            }
+            if (o[q] >= 0) st8(out + o[q], v);
+            if (FWD && p.fwd_pool) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = bf2f(f2bf(v[k]));
+                st8(t8, v);
+            }
+        }
+        if (FWD && p.fwd_pool) pool(p, area, row0, col0, rows, lane);
+    }
+
+    // forward, 2x2 max-pooling of the stored values: a piece's 32 rows are whole pairs of image rows, eight windows of rows
+    // (r, r+1, r+Wr, r+Wr+1)
+    __device__ __forceinline__ void pool(const IgemmArgs& p, float* area, int row0, int col0, int rows, int lane) {
+        const int ch = (lane % CPR) * 8, col = col0 + ch, w = lane / CPR;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (w >= 8 || col >= p.N) return;
+        const int hw = p.Wr >> 1, py = w / hw, px = w - py * hw, r = 2 * py * p.Wr + 2 * px;
+#pragma unroll 1
+        for (int mi = 0; mi < MI; ++mi) {
+            const int r0 = row0 + mi * 32;
+            if (r0 + r >= rows) return;
+            const float* t = area + mi * PIECE + ch;
+            float a[8], b[8], c[8], d[8];
+            un8(ld_raw8(t + r * PITCH), a);
+            un8(ld_raw8(t + (r + 1) * PITCH), b);
+            un8(ld_raw8(t + (r + p.Wr) * PITCH), c);
+            un8(ld_raw8(t + (r + p.Wr + 1) * PITCH), d);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) a[k] = fmaxf(fmaxf(a[k], b[k]), fmaxf(c[k], d[k]));
+            st8((bf16_t*)p.fwd_pool + (size_t)((r0 >> 2) + w) * p.N + col, a);
+        }
+    }
+
+    // gradient of a 2x2 max-pooling output: to the first maximum of the window (row-major), through the producer's ReLU
+    // and scale where asked; all four window positions are written
+    __device__ __forceinline__ void unpool(const IgemmArgs& p, float* area, int row0, int col0, int rows, int lane) {
+        const int ch = (lane % CPR) * 8, col = col0 + ch;
+        if (col >= p.N) return;
+        float ms[8];
+        if (p.mscale) un8(ld_raw8(p.mscale + col), ms);
         else {
 #pragma unroll
-            for (int k = 0; k < 8; ++k) d[k] = fill;
+            for (int k = 0; k < 8; ++k) ms[k] = 1.f;
         }
-    };
-    if (FWD) { vec(p.scale, sc, 1.f); vec(p.bias, bi, 0.f); }
-    else { vec(p.mscale, ms, 1.f); vec(p.c2scale, c2, 1.f); }
-    if constexpr (MODE == MODE_UNPOOL) {
-        // gradient of a 2x2 max-pooling output: to the first maximum of the window (row-major), through the producer's ReLU
-        // and scale where asked; all four window positions are written
-        static_assert(sizeof(E) == 2, "bf16 only");
 #pragma unroll 1
-        for (int q = 0; q < NP; ++q) {
+        for (int q = 0; q < R; ++q) {
             const int r = q * RPP + lane / CPR, row = row0 + r;
-            if (row >= rows || !cok) continue;
+            if (row >= rows) continue;
             const int t = div_by(row, p.dWr), wq = row - t * p.Wr, n = div_by(t, p.dHr), hq = t - n * p.Hr;
             const size_t base = ((size_t)(n * 2 * p.Hr + 2 * hq) * (2 * p.Wr) + 2 * wq) * p.N + col;
             const size_t off[4] = {0, (size_t)p.N, (size_t)2 * p.Wr * p.N, (size_t)2 * p.Wr * p.N + p.N};
@@ -143,15 +248,15 @@ __device__ __forceinline__ void store_piece(const IgemmArgs& p, float* tile, int
                 xr[k] = ld_raw8((const bf16_t*)p.pool_x + base + off[k]);
                 if (p.pool_acc) dr[k] = ld_raw8((const bf16_t*)p.pool_dst + base + off[k]);
             }
-            float x[4][8], o[4][8], v[8];
-            un8(ld_raw8(tile + r * PITCH + ch), v);
+            float x[4][8], d[4][8], v[8];
+            un8(ld_raw8(area + r * PITCH + ch), v);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 un8(xr[k], x[k]);
-                if (p.pool_acc) un8(dr[k], o[k]);
+                if (p.pool_acc) un8(dr[k], d[k]);
                 else {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) o[k][j] = 0.f;
+                    for (int j = 0; j < 8; ++j) d[k][j] = 0.f;
                 }
             }
 #pragma unroll
@@ -165,98 +270,14 @@ __device__ __forceinline__ void store_piece(const IgemmArgs& p, float* tile, int
                 for (int k = 0; k < 4; ++k) {
                     const bool hit = !found && x[k][j] == mx;
                     found = found || hit;
-                    o[k][j] += hit ? g : 0.f;
+                    d[k][j] += hit ? g : 0.f;
                 }
             }
 #pragma unroll
-            for (int k = 0; k < 4; ++k) st8((bf16_t*)p.pool_dst + base + off[k], o[k]);
-        }
-        return;
-    }
-    size_t o[NP];
-    bool live[NP];
-    Raw8<E> ra[NP], rc[NP], rm[NP], r2[NP];
-#pragma unroll
-    for (int q = 0; q < NP; ++q) {
-        const int row = row0 + q * RPP + lane / CPR;
-        live[q] = row < rows && cok;
-        const int prow = MODE == MODE_DGRAD_S && live[q] ? class_pixel(p, row, Hc, Wc, ph, pw, Dc, pd) : row;
-        o[q] = live[q] ? (size_t)prow * p.N + col : 0;
-    }
-#pragma unroll
-    for (int q = 0; q < NP; ++q) if (add) ra[q] = ld_raw8(add + o[q]);
-#pragma unroll
-    for (int q = 0; q < NP; ++q) if (!FWD && p.accumulate) rc[q] = ld_raw8((const E*)out + o[q]);
-#pragma unroll
-    for (int q = 0; q < NP; ++q) if (!FWD && msk) rm[q] = ld_raw8(msk + o[q]);
-#pragma unroll
-    for (int q = 0; q < NP; ++q) if (!FWD && out2 && p.acc2) r2[q] = ld_raw8((const E*)out2 + o[q]);
-#pragma unroll
-    for (int q = 0; q < NP; ++q) {
-        const int r = q * RPP + lane / CPR;
-        float v[8], t[8];
-        un8(ld_raw8(tile + r * PITCH + ch), v);
-        if (FWD) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = v[k] * sc[k] + bi[k];
-        }
-        if (add) { un8(ra[q], t);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] += t[k]; }
-        if (!FWD && p.accumulate) { un8(rc[q], t);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] += t[k]; }
-        if (FWD && p.relu) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = fmaxf(v[k], 0.f); }
-        if (!FWD && msk) { un8(rm[q], t);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = t[k] > 0.f ? v[k] : 0.f; }
-        if (!FWD && out2) {
-            float u[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) u[k] = v[k] * c2[k];
-            if (p.acc2) { un8(r2[q], t);
-#pragma unroll
-                for (int k = 0; k < 8; ++k) u[k] += t[k]; }
-            if (live[q]) st8(out2 + o[q], u);
-        }
-        if (!FWD) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] *= ms[k];
-        }
-        if (live[q]) st8(out + o[q], v);
-        if (MODE == MODE_FWD && p.fwd_pool) {
-            if constexpr (sizeof(E) == 2) {
-#pragma unroll
-                for (int k = 0; k < 8; ++k) v[k] = bf2f(f2bf(v[k]));
-                st8(tile + r * PITCH + ch, v);
-            }
+            for (int k = 0; k < 4; ++k) st8((bf16_t*)p.pool_dst + base + off[k], d[k]);
         }
     }
-    if (MODE == MODE_FWD && p.fwd_pool) {
-        // the piece's 32 rows are whole pairs of image rows: eight pooling windows of rows (r, r+1, r+Wr, r+Wr+1)
-        if constexpr (sizeof(E) == 2) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const int w = lane / CPR;
-            if (w < 8) {
-                const int hw = p.Wr >> 1, py = w / hw, px = w - py * hw, r = 2 * py * p.Wr + 2 * px;
-                if (row0 + r < rows && cok) {
-                    float a[8], b[8], c[8], d[8];
-                    un8(ld_raw8(tile + r * PITCH + ch), a);
-                    un8(ld_raw8(tile + (r + 1) * PITCH + ch), b);
-                    un8(ld_raw8(tile + (r + p.Wr) * PITCH + ch), c);
-                    un8(ld_raw8(tile + (r + p.Wr + 1) * PITCH + ch), d);
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) a[k] = fmaxf(fmaxf(a[k], b[k]), fmaxf(c[k], d[k]));
-                    st8((bf16_t*)p.fwd_pool + (size_t)((row0 >> 2) + w) * p.N + col, a);
-                }
-            }
-        }
-    }
-}
+};
 
 __device__ __forceinline__ unsigned tap_bits(int lo, int hi) { return hi > lo ? (1u << hi) - (1u << lo) : 0u; }
 

@@ -87,9 +87,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* q, unsigned b
 // launches of too few row tiles to fill the card: the four wavefronts of a block share a tile, each with a quarter of the
 // reduction, and add their sums through LDS.
 template <typename E, int NT, int MODE, bool KSPLIT>
-__global__ void __launch_bounds__(256, MODE == MODE_FWD ? 4 : 2) gather_gemm(const IgemmArgs p, const int ksteps, const int tiles, const FastDiv dKp) {
+__global__ void __launch_bounds__(256, MODE == MODE_FWD ? 3 : 2) gather_gemm(const IgemmArgs p, const int ksteps, const int tiles, const FastDiv dKp) {
     typedef Gathered<E> G;
     constexpr int ES = sizeof(E), EPC = G::N, KS = 2 * EPC, PIECE = 32 * (NT * 32 + 4);
+    typedef Epilogue<E, 1, NT, MODE> Ep;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, rl = lane & 31, half = lane >> 5;
     const int Kp = ksteps * KS, pitch = Kp + EPC, taps = p.Kd * p.Kh * p.Kw, K = taps * p.Ci, n0 = blockIdx.y * (NT * 32);
@@ -185,7 +186,9 @@ __global__ void __launch_bounds__(256, MODE == MODE_FWD ? 4 : 2) gather_gemm(con
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
-        store_piece<E, NT, MODE>(p, piece, t * 32, n0, p.M, lane, 0, 0, 0, 0, 0, 0);
+        Ep ep;
+        ep.load(p, t * 32, n0, p.M, lane, 0, 0, 0, 0, 0, 0);
+        ep.store(p, piece, t * 32, n0, p.M, lane, 0, 0, 0, 0, 0, 0);
     }
 }
 
@@ -408,7 +411,7 @@ hipError_t gather_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const
                              const void* mask, const float* mscale, hipStream_t st) {
     IgemmArgs a{};
     a.A = dz; a.B = w; a.C = dx;
-    a.accumulate = accumulate; a.mask = mask; a.mscale = mscale; a.kscale = dzscale;
+    a.add = accumulate ? dx : nullptr; a.mask = mask; a.mscale = mscale; a.kscale = dzscale;
     a.M = (int)g.rows_in(); a.N = g.Cin;
     a.Hi = g.Ho; a.Wi = g.Wo; a.Di = g.Do; a.Ci = g.Cout; a.Hr = g.H; a.Wr = g.W; a.Dr = g.D;
     a.Kh = g.Kh; a.Kw = g.Kw; a.Kd = g.Kd; a.stride = 1; a.pad = g.pad; a.pad_d = g.pad_d;

@@ -27,6 +27,11 @@
 
 namespace lpm {
 
+// Chunks per lane whose epilogue operands are held across the main loop.  Two: the 64x64 tile (125 registers instead of 98).
+// With the wider tiles too (183-220 registers) they gained alone, but fewer of the other streams' wavefronts fitted beside
+// them: VGG-16/224 7.05 -> 7.18 ms per step.
+constexpr int EARLY_ROWS = 2;
+
 // partial tiles pass between blocks on different XCDs: stores go through to memory, loads do not hit a stale line
 constexpr int AUX_AGENT = 16;
 
@@ -324,6 +329,13 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
+    // The epilogue's operands: requested now where the accumulators leave the registers for it and this block is sure to need
+    // them, so that they arrive under the main loop; a part of a split reduction leaves it to the block that comes last.
+    typedef Epilogue<E, MI, NI, MODE> Ep;
+    Ep ep;
+    const int er0 = m0 + wm * WTM, ec0 = n0 + wn * WTN;
+    const bool early = Ep::R <= EARLY_ROWS && p.splits == 1;
+    if (early) ep.load(p, er0, ec0, rows, lane, Hc, Wc, ph, pw, Dc, pd);
     if (nk > 0) {
 #pragma unroll
         for (int i = 0; i < NST - 1; ++i)
@@ -417,11 +429,9 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
             }
     }
 
-    // the wavefront's private staging area for the epilogue: a piece of 32 rows per mi.  (The pieces are stored in a loop that
-    // is not unrolled: the epilogue is most of the kernel's code, and a 128x128 data gradient of twice this size no longer
-    // fitted the instruction cache.)
-    constexpr int PIECE = 32 * (NI * 32 + 4);
-    float* piece = reinterpret_cast<float*>(lds) + wave * MI * PIECE;
+    // the wavefront's private staging area for the epilogue
+    if (!early) ep.load(p, er0, ec0, rows, lane, Hc, Wc, ph, pw, Dc, pd);
+    float* area = reinterpret_cast<float*>(lds) + wave * MI * Ep::PIECE;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -430,14 +440,12 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
         for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<float4*>(piece + mi * PIECE + rl * (NI * 32 + 4) + ni * 32 + q * 8 + kh_ * 4) =
+                *reinterpret_cast<float4*>(area + mi * Ep::PIECE + rl * Ep::PITCH + ni * 32 + q * 8 + kh_ * 4) =
                     make_float4(acc[mi][ni][4 * q], acc[mi][ni][4 * q + 1], acc[mi][ni][4 * q + 2], acc[mi][ni][4 * q + 3]);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll 1
-    for (int mi = 0; mi < MI; ++mi)
-        store_piece<E, NI, MODE>(p, piece + mi * PIECE, m0 + wm * WTM + mi * 32, n0 + wn * WTN, rows, lane, Hc, Wc, ph, pw, Dc, pd);
+    ep.store(p, area, er0, ec0, rows, lane, Hc, Wc, ph, pw, Dc, pd);
 }
 
 // --------------------------------------------------------------------------------------------------
@@ -605,10 +613,14 @@ hipError_t mfma_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const v
     const int es = dtype == LPM_BF16 ? 2 : 4;
     IgemmArgs a{};
     a.A = dz; a.B = wt; a.C = dx;
-    a.accumulate = accumulate; a.mask = mask; a.mscale = mscale; a.kscale = kscale;
+    a.mask = mask; a.mscale = mscale; a.kscale = kscale;
+    if (accumulate) {                    // dx += : its old values are the addend
+        if (side) return hipErrorInvalidValue;
+        a.add = dx;
+    }
     if (side) { a.add = side->earlier; a.C2 = side->shortcut; a.acc2 = side->shortcut_acc; a.c2scale = side->shortcut_scale; }
     if (unpool) {
-        a.C = nullptr; a.accumulate = 0; a.mask = nullptr;
+        a.C = nullptr; a.add = nullptr; a.mask = nullptr;
         a.pool_x = (const uint16_t*)unpool->pool_x; a.pool_dst = (uint16_t*)unpool->dst;
         a.pool_acc = unpool->accumulate; a.pool_mask = unpool->mask; a.mscale = unpool->mscale;
     }
