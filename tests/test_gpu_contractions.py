@@ -99,3 +99,23 @@ def test_contractions(lpm, case):
     assert torch.equal(y[0], y[1])
     assert err(dx[0], dx_ref) <= tol and err(dx[1], dx_ref + 0.5) <= tol
     assert err(dw[0], dw_ref) <= (1e-3 if bf else 2e-5) and err(dw[1], dw_ref + 0.5) <= (1e-3 if bf else 2e-5)
+
+
+@pytest.mark.parametrize("m,h,w,C", [(2, 1, 1, 8), (1, 3, 11, 24), (2, 8, 8, 40), (1, 5, 4, 264), (3, 4, 4, 96), (1, 23, 23, 128), (1, 31, 31, 32)],
+                         ids=lambda v: str(v))
+def test_attention_bf16(lpm, m, h, w, C):
+    """One attention layer as a stage of its own: one position, positions and channels that fill no tile, more channel groups
+    than wavefronts, several row blocks, the longest rows."""
+    import torch
+    from oracle import lpm_oracle as orc
+    layers = [dict(kind="attn", cin=3 * C, cout=C, kh=1, kw=1, stride=1, pad=0, h_in=h, w_in=w, relu=False, bias=False, scale=False,
+                   src=-1, add_src=None, cut_after=False)]
+    gen = np.random.default_rng(5)
+    bf = lambda a: torch.from_numpy(a).to(torch.bfloat16).double().numpy()
+    x, dy = bf(gen.standard_normal((m, 3 * C, h, w))), bf(gen.standard_normal((m, C, h, w)))
+    net = lpm.Net(layers, [0, 1], m, 1, lpm.BF16, dx_wanted=True)
+    net.step(lpm.pack_act(x, lpm.BF16), None, lpm.pack_act(dy, lpm.BF16), 0.0, 0.0, lpm.LOCKED)
+    torch.cuda.synchronize()
+    y = net.read_act_out(0, 0)
+    assert rel_err(y, orc.attn_fwd(x)) <= 6e-3                     # (one rounding to bf16 of the result)
+    assert rel_err(net.read_grad_in(0, 0), orc.attn_bwd(x, dy)) <= 6e-3
