@@ -570,7 +570,7 @@ hipError_t launch_attn_bwd(int dtype, int32_t m, int32_t P, int32_t C, const voi
         const dim3 grid((unsigned)((P + AM_R - 1) / AM_R), (unsigned)m);
         const size_t lds = 2 * s.tile_bytes() + 2 * s.rows_bytes() + AM_RED;
         hipLaunchKernelGGL(attn_bwd_q_mm, grid, dim3(AM_T), lds, st, P, C, (const bf16_t*)x, (const bf16_t*)dy, (bf16_t*)dx, accumulate, (float*)ws);
-        hipLaunchKernelGGL(attn_bwd_kv_mm, grid, dim3(AM_T), lds, st, P, C, (const bf16_t*)x, (const bf16_t*)dy, (bf16_t*)dx, accumulate, (const float*)ws);
+        launch_last(attn_bwd_kv_mm, grid, dim3(AM_T), lds, st, P, C, (const bf16_t*)x, (const bf16_t*)dy, (bf16_t*)dx, accumulate, (const float*)ws);
         return hipGetLastError();
     }
     const dim3 grid((unsigned)((P + ATT_QB - 1) / ATT_QB), (unsigned)m);
@@ -579,12 +579,12 @@ hipError_t launch_attn_bwd(int dtype, int32_t m, int32_t P, int32_t C, const voi
     if (dtype == LPM_BF16) {
         LPM_ATT_NP(np, hipLaunchKernelGGL((attn_bwd_q_kernel<bf16_t, NP>), grid, dim3(256), lds, st, P, C, (const bf16_t*)x, (const bf16_t*)dy,
                                           (bf16_t*)dx, accumulate, (float*)ws));
-        LPM_ATT_NP(np, hipLaunchKernelGGL((attn_bwd_kv_kernel<bf16_t, NP>), grid, dim3(256), lds, st, P, C, (const bf16_t*)x, (const bf16_t*)dy,
+        LPM_ATT_NP(np, launch_last(attn_bwd_kv_kernel<bf16_t, NP>, grid, dim3(256), lds, st, P, C, (const bf16_t*)x, (const bf16_t*)dy,
                                           (bf16_t*)dx, accumulate, (const float*)ws));
     } else {
         LPM_ATT_NP(np, hipLaunchKernelGGL((attn_bwd_q_kernel<float, NP>), grid, dim3(256), lds, st, P, C, (const float*)x, (const float*)dy,
                                           (float*)dx, accumulate, (float*)ws));
-        LPM_ATT_NP(np, hipLaunchKernelGGL((attn_bwd_kv_kernel<float, NP>), grid, dim3(256), lds, st, P, C, (const float*)x, (const float*)dy,
+        LPM_ATT_NP(np, launch_last(attn_bwd_kv_kernel<float, NP>, grid, dim3(256), lds, st, P, C, (const float*)x, (const float*)dy,
                                           (float*)dx, accumulate, (const float*)ws));
     }
     return hipGetLastError();

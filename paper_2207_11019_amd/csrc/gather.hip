@@ -377,7 +377,7 @@ static hipError_t go(const IgemmArgs& a, int ksteps, int tiles, hipStream_t st) 
     static const hipError_t attr = hipFuncSetAttribute((const void*)gather_gemm<E, NT, MODE, KSPLIT>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
     if (attr != hipSuccess) return attr;
     const int blocks = KSPLIT ? tiles : std::min((tiles + 3) / 4, 1536);
-    hipLaunchKernelGGL((gather_gemm<E, NT, MODE, KSPLIT>), dim3((unsigned)blocks, (unsigned)((a.N + NT * 32 - 1) / (NT * 32))), dim3(256),
+    launch_last(gather_gemm<E, NT, MODE, KSPLIT>, dim3((unsigned)blocks, (unsigned)((a.N + NT * 32 - 1) / (NT * 32))), dim3(256),
                        gather_lds(sizeof(E), NT, ksteps), st, a, ksteps, tiles, fast_div(ksteps * (32 / (int)sizeof(E))));
     return hipGetLastError();
 }

@@ -540,7 +540,7 @@ static hipError_t go(const IgemmArgs& a, int64_t tiles, hipStream_t st) {
     static const hipError_t attr = hipFuncSetAttribute((const void*)igemm_kernel<E, BM, BN, WGM, WGN, NST, MODE, UNI, BT, OCC>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((igemm_kernel<E, BM, BN, WGM, WGN, NST, MODE, UNI, BT, OCC>), dim3((unsigned)tiles, 1, a.splits), dim3(WGM * WGN * 64), bytes, st, a);
+    launch_last(igemm_kernel<E, BM, BN, WGM, WGN, NST, MODE, UNI, BT, OCC>, dim3((unsigned)tiles, 1, a.splits), dim3(WGM * WGN * 64), bytes, st, a);
     return hipGetLastError();
 }
 

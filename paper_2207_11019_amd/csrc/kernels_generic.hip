@@ -84,7 +84,7 @@ hipError_t conv_fwd_generic_launch(int dtype, const ConvGeom& g, const void* x, 
                                    const float* bias, const void* add, int relu, void* y, hipStream_t s) {
     const int64_t total = g.rows_out() * g.Cout;
     const int lanes = group_lanes(g.Cin);
-    LPM_DISPATCH_R(lanes, LPM_DISPATCH(dtype, hipLaunchKernelGGL((conv_fwd_generic<T, R>), dim3(nblk(total * R, 256)), dim3(256), 0, s, g,
+    LPM_DISPATCH_R(lanes, LPM_DISPATCH(dtype, launch_last(conv_fwd_generic<T, R>, dim3(nblk(total * R, 256)), dim3(256), 0, s, g,
                                                                  (const T*)x, (const T*)w, scale, bias, (const T*)add, relu, (T*)y)));
     return hipGetLastError();
 }
@@ -143,7 +143,7 @@ hipError_t conv_dgrad_generic_launch(int dtype, const ConvGeom& g, const void* d
                                      int accumulate, const void* mask, const float* mscale, hipStream_t s) {
     const int64_t total = g.rows_in() * g.Cin;
     const int lanes = group_lanes(g.Cout);
-    LPM_DISPATCH_R(lanes, LPM_DISPATCH(dtype, hipLaunchKernelGGL((conv_dgrad_generic<T, R>), dim3(nblk(total * R, 256)), dim3(256), 0, s, g,
+    LPM_DISPATCH_R(lanes, LPM_DISPATCH(dtype, launch_last(conv_dgrad_generic<T, R>, dim3(nblk(total * R, 256)), dim3(256), 0, s, g,
                                                                  (const T*)dz, dzscale, (const T*)w, (T*)dx, accumulate, (const T*)mask, mscale)));
     return hipGetLastError();
 }
@@ -556,11 +556,11 @@ hipError_t launch_maxpool_bwd(int dtype, int32_t m, int32_t H, int32_t W, int32_
     const int64_t total = (int64_t)m * (H / 2) * (W / 2) * C;
     if (dtype == LPM_BF16 && (C & 7) == 0 && (int64_t)m * H * W * C < ((int64_t)1 << 31)) {
         const unsigned total8 = (unsigned)(total / 8);
-        hipLaunchKernelGGL(maxpool_bwd_bf16x8, dim3((total8 + 255u) / 256u), dim3(256), 0, s, total8, H, W, C / 8, (const uint4*)x,
+        launch_last(maxpool_bwd_bf16x8, dim3((total8 + 255u) / 256u), dim3(256), 0, s, total8, H, W, C / 8, (const uint4*)x,
                            (const uint4*)y, (const uint4*)dy, (uint4*)dx, accumulate, mask, mscale);
         return hipGetLastError();
     }
-    LPM_DISPATCH(dtype, hipLaunchKernelGGL(maxpool_bwd_kernel<T>, dim3(nblk(total, 256)), dim3(256), 0, s, m, H, W, C,
+    LPM_DISPATCH(dtype, launch_last(maxpool_bwd_kernel<T>, dim3(nblk(total, 256)), dim3(256), 0, s, m, H, W, C,
                                            (const T*)x, (const T*)y, (const T*)dy, (T*)dx, accumulate, mask, mscale));
     return hipGetLastError();
 }
@@ -599,7 +599,7 @@ hipError_t launch_gap_fwd(int dtype, int32_t m, int32_t HW, int32_t C, const voi
 
 hipError_t launch_gap_bwd(int dtype, int32_t m, int32_t HW, int32_t C, const void* dy, void* dx, int accumulate,
                           const void* mask, const float* mscale, hipStream_t s) {
-    LPM_DISPATCH(dtype, hipLaunchKernelGGL(gap_bwd_kernel<T>, dim3(nblk((int64_t)m * HW * C, 256)), dim3(256), 0, s, m, HW,
+    LPM_DISPATCH(dtype, launch_last(gap_bwd_kernel<T>, dim3(nblk((int64_t)m * HW * C, 256)), dim3(256), 0, s, m, HW,
                                            C, (const T*)dy, (T*)dx, accumulate, (const T*)mask, mscale));
     return hipGetLastError();
 }
@@ -685,7 +685,7 @@ __global__ void __launch_bounds__(1024) softmax_ce_kernel(int m, int C, const T*
 
 hipError_t launch_softmax_ce(int dtype, int32_t m, int32_t C, const void* logits, const int32_t* labels, float loss_scale,
                              void* dlogits, float* loss_accum, hipStream_t s) {
-    LPM_DISPATCH(dtype, hipLaunchKernelGGL(softmax_ce_kernel<T>, dim3(1), dim3(1024), 0, s, m, C, (const T*)logits, labels,
+    LPM_DISPATCH(dtype, launch_last(softmax_ce_kernel<T>, dim3(1), dim3(1024), 0, s, m, C, (const T*)logits, labels,
                                            loss_scale, (T*)dlogits, loss_accum));
     return hipGetLastError();
 }

@@ -34,7 +34,7 @@ __global__ void __launch_bounds__(256) splitk_epilogue(const float* __restrict__
 
 hipError_t launch_splitk_epilogue(const float* part, int splits, int64_t MN, int N, int accumulate, const void* mask, const float* mscale,
                                   void* C, hipStream_t st) {
-    hipLaunchKernelGGL(splitk_epilogue, dim3((unsigned)((MN + 255) / 256)), dim3(256), 0, st, part, splits, MN, N, accumulate,
+    launch_last(splitk_epilogue, dim3((unsigned)((MN + 255) / 256)), dim3(256), 0, st, part, splits, MN, N, accumulate,
                        (const uint16_t*)mask, mscale, (uint16_t*)C);
     return hipGetLastError();
 }
@@ -141,7 +141,8 @@ hipError_t launch_reduce_batch(const ReduceDesc* d, int count, hipStream_t st) {
         a.count = k;
         done += k;
         if (tot == 0) continue;
-        hipLaunchKernelGGL(wgrad_reduce_batch, dim3((unsigned)tot), dim3(256), 0, st, a);
+        if (done < count) hipLaunchKernelGGL(wgrad_reduce_batch, dim3((unsigned)tot), dim3(256), 0, st, a);
+        else launch_last(wgrad_reduce_batch, dim3((unsigned)tot), dim3(256), 0, st, a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

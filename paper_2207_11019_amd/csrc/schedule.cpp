@@ -49,6 +49,7 @@ struct lpm_schedule {
     std::vector<hipEvent_t> ev_f;   // [Z*M]  F_{z,j} done (index j*Z + z)
     std::vector<hipEvent_t> ev_b;   // [Z*M]  data phase of B_{z,j} done
     std::vector<hipEvent_t> ev_w;   // [Z*M]  all of B_{z,j} done (weight phase included)
+    std::vector<hipEvent_t> pt_b;   // [Z*M]  OVERLAPPED: the event that marks the end of the data phase of B_{z,j}: ev_b or one of the stage's own
     hipEvent_t ev_fork = nullptr;
     std::vector<hipStream_t> sf, sb;     // PIPELINED: per-stage forward / backward streams (borrowed from the pool)
     // OVERLAPPED: the weight phases' streams, picked from the pool so that forward, data phases, weight phases and
@@ -116,6 +117,7 @@ extern "C" int32_t lpm_schedule_create(lpm_stage* const* stages, int32_t Z, int3
     s->ev_f.assign((size_t)n_microbatch * Z, nullptr);
     s->ev_b.assign((size_t)n_microbatch * Z, nullptr);
     s->ev_w.assign((size_t)n_microbatch * Z, nullptr);
+    s->pt_b.assign((size_t)n_microbatch * Z, nullptr);
     s->sf.assign((size_t)Z, nullptr);
     s->sb.assign((size_t)Z, nullptr);
     s->cut_fused.assign((size_t)Z, 0);
@@ -176,7 +178,7 @@ struct RunArgs {
 inline float* ver_params(const lpm_stage_buffers& b, int32_t ver) { return (ver > 0 && (ver & 1)) ? b.params_alt : b.params; }
 inline void* ver_lowp(const lpm_stage_buffers& b, int32_t ver) { return (ver > 0 && (ver & 1)) ? b.lowp_alt : b.lowp; }
 
-int32_t fwd_op(lpm_schedule* s, const RunArgs& a, int32_t z, int32_t j, hipStream_t st, int32_t ver = -1) {
+int32_t fwd_op(lpm_schedule* s, const RunArgs& a, int32_t z, int32_t j, hipStream_t st, int32_t ver = -1, hipEvent_t done = nullptr) {
     lpm_stage* sg = s->st[(size_t)z];
     const int32_t slot = j % s->window;
     const lpm_stage_buffers& b = a.bufs[z];
@@ -186,14 +188,14 @@ int32_t fwd_op(lpm_schedule* s, const RunArgs& a, int32_t z, int32_t j, hipStrea
     // synchronous step: the loss is the mean over the mini-batch; asynchronous update: over the micro-batch
     const float loss_scale = 1.0f / (float)(ver < 0 ? s->M * sg->m : sg->m);
     return lpm_stage_forward_on(sg, in, b.act_out[slot], lab, a.loss_out, ver_params(b, ver), ver_lowp(b, ver), b.stash[slot],
-                                b.fwd_ws, loss_scale, st, true);
+                                b.fwd_ws, loss_scale, st, true, done);
 }
 
 // wst: stream of the weight phase (see lpm_stage_backward_on)
 // by_layer: the two phases come as separate calls and the weight phase follows the data phase layer by layer
 int32_t bwd_op(lpm_schedule* s, const RunArgs& a, int32_t z, int32_t j, hipStream_t st, hipStream_t wst,
                int32_t phases = LPM_PHASE_DATA | LPM_PHASE_WEIGHTS, int32_t ver = -1, bool by_layer = false,
-               hipStream_t wst2 = nullptr) {
+               hipStream_t wst2 = nullptr, hipEvent_t data_done = nullptr, hipEvent_t weights_done = nullptr) {
     lpm_stage* sg = s->st[(size_t)z];
     const int32_t slot = j % s->window;
     const lpm_stage_buffers& b = a.bufs[z];
@@ -210,7 +212,7 @@ int32_t bwd_op(lpm_schedule* s, const RunArgs& a, int32_t z, int32_t j, hipStrea
                                  ver < 0 ? j > 0 : 0, b.bwd_ws, st, wst, j & 1, phases, staged ? j : -1,
                                  staged ? s->M : 0, by_layer ? j % LPM_MAX_WINDOW : -1,
                                  (s->cut_fused[(size_t)z] ? LPM_MASK_DX : 0) | (z + 1 < s->Z && s->cut_fused[(size_t)z + 1] ? LPM_DY_IS_DZ : 0),
-                                 wst2, true);
+                                 wst2, true, data_done, &s->pt_b[(size_t)j * s->Z + z], weights_done);
 }
 
 // ver < 0: the one update of the synchronous step; else U_{z,ver}: version ver -> version ver + 1
@@ -348,16 +350,23 @@ int32_t overlapped_role(lpm_schedule* s, const RunArgs& a, int32_t role, uint64_
     const bool async = (a.mode & LPM_ASYNC_UPDATE) != 0;
     hipStream_t sw = s->ov_w;
     int32_t rc;
+    // Stage 0's weight phase closes every micro-batch, and the next forward chain but one waits for it: with a
+    // hardware queue to itself it follows stage 0's data phase from the start instead of queueing behind the other
+    // stages' weight phases.  The micro-batch is done at ev_w[j*Z] and, the end of those on the common stream, ev_w[j*Z+1].
+    const bool own0 = !async && Z > 1 && s->ov_w0 != s->ov_w;
+    auto await_microbatch = [&](int32_t j, hipStream_t st) -> int32_t {
+        const size_t i = (size_t)j * Z;
+        if ((rc = await_record(s, s->rec_w[i], epoch))) return rc;
+        LPM_HIP(hipStreamWaitEvent(st, s->ev_w[i], 0));
+        if (own0) LPM_HIP(hipStreamWaitEvent(st, s->ev_w[i + 1], 0));
+        return LPM_OK;
+    };
     if (role == 0) {
         for (int32_t j = 0; j < M; ++j) {
             // F_{0,j} after B_{0,j-W}, the last operation of micro-batch j-W; the other stages follow in stream order
-            if (j >= W) {
-                const size_t i = (size_t)(j - W) * Z;
-                if ((rc = await_record(s, s->rec_w[i], epoch))) return rc;
-                LPM_HIP(hipStreamWaitEvent(a.sf, s->ev_w[i], 0));
-            }
-            for (int32_t z = 0; z < Z; ++z) if ((rc = fwd_op(s, a, z, j, a.sf, async ? forward_version(j, W) : -1))) return rc;
-            LPM_HIP(hipEventRecord(s->ev_f[(size_t)j * Z + Z - 1], a.sf));
+            if (j >= W && (rc = await_microbatch(j - W, a.sf))) return rc;
+            for (int32_t z = 0; z < Z; ++z)
+                if ((rc = fwd_op(s, a, z, j, a.sf, async ? forward_version(j, W) : -1, z == Z - 1 ? s->ev_f[(size_t)j * Z + z] : nullptr))) return rc;
             publish(s->rec_f[(size_t)j * Z + Z - 1], epoch);
         }
     } else if (role == 1) {
@@ -366,26 +375,19 @@ int32_t overlapped_role(lpm_schedule* s, const RunArgs& a, int32_t role, uint64_
             const size_t i = (size_t)j * Z + Z - 1;
             if ((rc = await_record(s, s->rec_f[i], epoch))) return rc;
             LPM_HIP(hipStreamWaitEvent(a.sb, s->ev_f[i], 0));
-            if (W > 2 && j >= 2) {
-                if ((rc = await_record(s, s->rec_w[(size_t)(j - 2) * Z], epoch))) return rc;
-                LPM_HIP(hipStreamWaitEvent(a.sb, s->ev_w[(size_t)(j - 2) * Z], 0));
-            }
+            if (W > 2 && j >= 2 && (rc = await_microbatch(j - 2, a.sb))) return rc;
             for (int32_t z = Z - 1; z >= 0; --z) {
                 if (async && j > 0) {      // B_{z,j} reads version j: after U_{z,j-1} (which has also consumed the bias gradients)
                     const size_t u = (size_t)(j - 1) * Z + z;
                     if ((rc = await_record(s, s->rec_w[u], epoch))) return rc;
                     LPM_HIP(hipStreamWaitEvent(a.sb, s->ev_w[u], 0));
                 }
-                if ((rc = bwd_op(s, a, z, j, a.sb, sw, LPM_PHASE_DATA, async ? j : -1, z == 0 && !async))) return rc;
-                LPM_HIP(hipEventRecord(s->ev_b[(size_t)j * Z + z], a.sb));
+                if ((rc = bwd_op(s, a, z, j, a.sb, sw, LPM_PHASE_DATA, async ? j : -1, z == 0 && !async, nullptr,
+                                 s->ev_b[(size_t)j * Z + z]))) return rc;
                 publish(s->rec_b[(size_t)j * Z + z], epoch);
             }
         }
     } else {
-        // Stage 0's weight phase closes every micro-batch, and the next forward chain but one waits for it: with a
-        // hardware queue to itself it follows stage 0's data phase from the start instead of queueing behind the other
-        // stages' weight phases.  ev_w[j*Z+1] then marks the end of those on the common weight stream.
-        const bool own0 = !async && Z > 1 && s->ov_w0 != s->ov_w;
         // Asynchronous update: B_{z,j+1} waits for U_{z,j}, so the weight phases and updates are a chain per stage; odd
         // stages take the second stream (each stage keeps its stream, which orders its updates).
         const bool async2 = async && Z > 1 && s->ov_w0 != s->ov_w;
@@ -394,6 +396,7 @@ int32_t overlapped_role(lpm_schedule* s, const RunArgs& a, int32_t role, uint64_
         hipStream_t sw_pair = (!async && Z == 1 && s->ov_w0 != s->ov_w) ? s->ov_w0 : nullptr;
         hipStream_t sw_all = sw, sw_0 = s->ov_w0;
         for (int32_t j = 0; j < M; ++j) {
+            bool closed[2] = {false, false};       // ev_w[j*Z], ev_w[j*Z+1] stand at the end of a weight phase
             for (int32_t z = Z - 1; z >= 0; --z) {
                 sw = ((own0 && z == 0) || (async2 && (z & 1))) ? sw_0 : sw_all;
                 const size_t i = (size_t)j * Z + z;
@@ -401,11 +404,14 @@ int32_t overlapped_role(lpm_schedule* s, const RunArgs& a, int32_t role, uint64_
                 // Stage 0 closes the micro-batch, and the next forward chain but one waits for it: there the weight
                 // gradients follow the data phase layer by layer (the events were recorded before rec_b was published)
                 const bool by_layer = z == 0 && !async;
-                if (!by_layer) LPM_HIP(hipStreamWaitEvent(sw, s->ev_b[i], 0));
-                if ((rc = bwd_op(s, a, z, j, a.sb, sw, LPM_PHASE_WEIGHTS, async ? j : -1, by_layer, sw_pair))) return rc;
-                // whatever follows on this stream (the update, the record that closes the micro-batch) is still ordered
-                // after the whole data phase
-                if (by_layer) LPM_HIP(hipStreamWaitEvent(sw, s->ev_b[i], 0));
+                if (!by_layer) LPM_HIP(hipStreamWaitEvent(sw, s->pt_b[i], 0));
+                // The last weight phase of a stream closes the micro-batch there -- unless more of it follows: the update, or the
+                // end of a data phase that goes on after the last layer's weight gradient may start
+                const bool rest = by_layer && s->pt_b[i] == s->ev_b[i];
+                const bool closes = !async && j < M - 1 && !rest && (z == 0 || (own0 && z == 1));
+                if ((rc = bwd_op(s, a, z, j, a.sb, sw, LPM_PHASE_WEIGHTS, async ? j : -1, by_layer, sw_pair, nullptr, closes ? s->ev_w[i] : nullptr))) return rc;
+                if (rest) LPM_HIP(hipStreamWaitEvent(sw, s->ev_b[i], 0));
+                if (closes) closed[z] = true;
                 if (async) {
                     if ((rc = upd_op(s, a, z, sw, j))) return rc;
                     if (j == M - 1 && (rc = copy_final_version(s, a, z, sw))) return rc;
@@ -415,13 +421,10 @@ int32_t overlapped_role(lpm_schedule* s, const RunArgs& a, int32_t role, uint64_
                     }
                 } else if (j == M - 1 && (rc = upd_op(s, a, z, sw))) return rc;
             }
-            if (own0) {        // sw is stage 0's stream here: the micro-batch is done when the other stream is, too
-                LPM_HIP(hipEventRecord(s->ev_w[(size_t)j * Z + 1], sw_all));
-                LPM_HIP(hipStreamWaitEvent(sw, s->ev_w[(size_t)j * Z + 1], 0));
-            }
+            if (own0 && !closed[1]) LPM_HIP(hipEventRecord(s->ev_w[(size_t)j * Z + 1], sw_all));
             // (asynchronous update on two streams: U_{1,j}, recorded above, is the last operation of the odd stages)
             if (async2) LPM_HIP(hipStreamWaitEvent(sw, s->ev_w[(size_t)j * Z + 1], 0));
-            LPM_HIP(hipEventRecord(s->ev_w[(size_t)j * Z], sw));
+            if (!closed[0]) LPM_HIP(hipEventRecord(s->ev_w[(size_t)j * Z], sw));
             publish(s->rec_w[(size_t)j * Z], epoch);
         }
     }
@@ -511,7 +514,9 @@ int32_t enqueue(lpm_schedule* s, const RunArgs& a) {
         if (!heads.empty()) LPM_HIP(launch_zero_counts(heads.data(), (int)heads.size(), a.sf));
     }
     hipStream_t lw = nullptr;            // (captured: branches of the graph)
-    if ((a.mode & 15) == LPM_LOCKED && !capturing) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;      // (a capture of the caller's own, too)
+    if ((a.mode & 15) == LPM_LOCKED) LPM_HIP(hipStreamIsCapturing(a.sf, &cap));
+    if ((a.mode & 15) == LPM_LOCKED && cap == hipStreamCaptureStatusNone) {
         if ((rc = pick_locked_stream(s, a.sf))) return rc;
         lw = s->lk_w;
     }
@@ -545,6 +550,7 @@ int32_t enqueue(lpm_schedule* s, const RunArgs& a) {
         if ((rc = pick_weight_streams(s, a.sf, a.sb))) return rc;
         if ((rc = run_roles(s, a, overlapped_role, 3))) return rc;
         LPM_HIP(hipStreamWaitEvent(a.sf, s->ev_w[(size_t)(M - 1) * Z], 0));
+        if (!(a.mode & LPM_ASYNC_UPDATE) && Z > 1 && s->ov_w0 != s->ov_w) LPM_HIP(hipStreamWaitEvent(a.sf, s->ev_w[(size_t)(M - 1) * Z + 1], 0));
         return LPM_OK;
     }
     // OVERLAPPED while a graph is captured: one thread, forward chains on sf, backward chains on sb (the weight

@@ -367,7 +367,7 @@ extern "C" int32_t lpm_stage_forward(lpm_stage* s, const void* x, void* y, const
 
 // counts_zeroed: the caller has cleared the arrival counts at the head of fwd_ws (a schedule does so once per run)
 int32_t lpm_stage_forward_on(lpm_stage* s, const void* x, void* y, const int32_t* labels, float* loss_accum, const float* params,
-                             const void* lowp, void* stash, void* fwd_ws, float loss_scale, void* stream, bool counts_zeroed) {
+                             const void* lowp, void* stash, void* fwd_ws, float loss_scale, void* stream, bool counts_zeroed, hipEvent_t done) {
     if (!s || !x || !y || !params || !stash || !fwd_ws) return fail(LPM_EINVAL, "NULL argument");
     if (s->dtype == LPM_BF16 && !lowp) return fail(LPM_EINVAL, "lowp is NULL for a bf16 stage");
     if (s->loss && (!labels || !loss_accum)) return fail(LPM_EINVAL, "a loss stage needs labels and loss_accum");
@@ -382,6 +382,7 @@ int32_t lpm_stage_forward_on(lpm_stage* s, const void* x, void* y, const int32_t
         const lpm_layer& l = lr.d;
         const void* in = tptr(s, l.src, x, y, stash);
         void* outp = const_cast<void*>(tptr(s, i, x, y, stash));
+        StopEvent stop(i == s->last - 1 ? done : nullptr, st);
         switch (l.kind) {
             case LPM_CONV:
             case LPM_FC: {
@@ -409,6 +410,7 @@ int32_t lpm_stage_forward_on(lpm_stage* s, const void* x, void* y, const int32_t
                                           loss_accum, st));
                 break;
         }
+        LPM_HIP(stop.finish());
     }
     return LPM_OK;
 }
@@ -429,6 +431,8 @@ extern "C" int32_t lpm_stage_backward(lpm_stage* s, const void* x, const void* y
 // phase; LPM_PHASE_WEIGHTS alone only the weight phase on wstream, with no event -- the caller has ordered
 // wstream after the data phase (separate enqueue threads for the two).
 // parity (0 / 1) selects the copy of the gradient / dz area in bwd_ws this pass uses.
+// data_done (eager): an event for the end of the data phase; *data_point is the event to wait for, data_done or a layer's that
+// stands at the same point.  weights_done: an event for the end of the weight phase on wstream.
 // While `stream` is being captured the weight gradients stay on it and are taken out of its dependency
 // frontier instead.
 // wstream2 (with wstream, eager only): every other weight gradient of the phase runs on this second stream, forked from
@@ -438,7 +442,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                               const float* params, const void* lowp, const void* stash, float* grads,
                               int32_t accumulate, void* bwd_ws, void* stream, void* wstream, int32_t parity,
                               int32_t phases, int32_t fc_slot, int32_t fc_flush, int32_t layer_slot, int32_t boundary, void* wstream2,
-                              bool counts_zeroed) {
+                              bool counts_zeroed, hipEvent_t data_done, hipEvent_t* data_point, hipEvent_t weights_done) {
     if ((boundary & LPM_MASK_DX) && !lpm_stage_can_mask_dx(s)) return fail(LPM_EINVAL, "internal: this stage cannot mask its input gradient");
     if ((boundary & LPM_DY_IS_DZ) && !lpm_stage_takes_dz(s)) return fail(LPM_EINVAL, "internal: this stage needs the gradient of its output");
     if (layer_slot >= LPM_MAX_WINDOW) return fail(LPM_EINVAL, "internal: layer event slot out of range");
@@ -479,6 +483,24 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
     hipStream_t wst = wstream ? (hipStream_t)wstream : s->side;
     const bool beside = deferred && do_data && do_weights && wst != st;
     std::vector<ReduceDesc> red;           // split weight gradients of this pass, reduced in one launch at its end
+    // Points of the data phase that other streams wait for: per weight layer "its output gradient is final" (by_layer, beside),
+    // and the end.  A point that follows a layer's last kernel with nothing in between is that kernel's stop event.
+    const bool points = do_data && (by_layer || beside);
+    auto layer_ev = [&](int32_t i) { return s->ev_layer[(size_t)(i - first) * LPM_MAX_WINDOW + (by_layer ? layer_slot : 0)]; };
+    hipEvent_t at_point = nullptr;         // the event that stands at the data phase's present end, if one does
+    auto point_after = [&](int32_t i) -> hipEvent_t {
+        if (!do_data || !deferred) return nullptr;
+        for (int32_t k = i - 1; k >= first; --k) {
+            const LayerRt& q = s->Ly(k);
+            if (has_weights(q.d)) {
+                if (!q.fused_in) return nullptr;
+                if (points) return layer_ev(k);
+                return k == first && q.d.src < first && !dx ? data_done : nullptr;
+            }
+            if (!(q.d.kind == LPM_MAXPOOL2 && q.unpooled)) return nullptr;
+        }
+        return data_done;
+    };
     // bias_g != NULL: the layer's bias gradient is a plain column sum of bias_g that nothing in the data phase needs and its
     // weight-gradient kernel does not make; it runs in the weight phase, ahead of that kernel (scratch: the layer's own area)
     struct WgradJob { const LayerRt* lr; const void* xin; const void* dz; float* wdb; const float* sc; const void* bias_g; float* bias_db; };
@@ -567,13 +589,17 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                     if (!need_dz && !gadd && dbias && !bias_in_wgrad) {
                         bias_g = g;
                     } else if (need_dz || gadd || (dbias && !bias_in_wgrad)) {
+                        at_point = nullptr;
                         if (do_data) LPM_HIP(launch_epilogue_bwd(s->dtype, lr.g.rows_out(), l.cout, g, relu ? yout : nullptr, lr.dz_unscaled ? nullptr : sc,
                                                     need_dz ? (void*)(gw + lr.dz_off) : nullptr, gadd, gadd_acc,
                                                     bias_in_wgrad ? nullptr : dbias, acc, kws, st));
                         if (need_dz) dz = gw + lr.dz_off;
                     }
                 }
-                if (by_layer && do_data) LPM_HIP(hipEventRecord(s->ev_layer[(size_t)(i - first) * LPM_MAX_WINDOW + layer_slot], st));
+                if (points && at_point != layer_ev(i)) {
+                    LPM_HIP(hipEventRecord(layer_ev(i), st));
+                    at_point = layer_ev(i);
+                }
                 float* wdb = bias_in_wgrad ? dbias : nullptr;
                 // where the gradient w.r.t. this layer's input goes: the producer's dz (fused) or the tensor's gradient
                 void* gsrc = nullptr;
@@ -636,10 +662,8 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                 }
                 const void* xin = tptr(s, l.src, x, y, stash);
                 if (beside) {
-                    hipEvent_t ev = s->ev_layer[(size_t)(i - first) * LPM_MAX_WINDOW];
                     ReduceDesc d{};
-                    LPM_HIP(hipEventRecord(ev, st));
-                    LPM_HIP(hipStreamWaitEvent(wst, ev, 0));
+                    LPM_HIP(hipStreamWaitEvent(wst, layer_ev(i), 0));
                     LPM_HIP(one_wgrad(WgradJob{&lr, xin, dz, wdb, lr.dz_unscaled ? sc : nullptr, bias_g, bias_g ? dbias : nullptr}, wst, &d));
                     if (d.splits > 0) red.push_back(d);
                 } else if (deferred) {
@@ -658,6 +682,8 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                                                          : (const void*)(params + lr.w_off);
                     const void* wt = (s->dtype == LPM_BF16 && lr.lowp_wt_off != NO)
                                          ? (const void*)((const char*)lowp + lr.lowp_wt_off) : nullptr;
+                    const hipEvent_t ev = point_after(i);
+                    StopEvent stop(ev, st);
                     if (lr.unpool_of >= 0) {
                         if (do_data && unpool.dst) LPM_HIP(launch_conv_dgrad(s->dtype, lr.g, dz, w, wt, nullptr, 0, nullptr, nullptr, counts, st, &unpool,
                                                                              nullptr, lr.dz_unscaled ? sc : nullptr, true));
@@ -665,6 +691,8 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                         LPM_HIP(launch_conv_dgrad(s->dtype, lr.g, dz, w, wt, gsrc, gsrc_acc, gmask, gmscale, counts, st, nullptr,
                                                   use_side ? &side : nullptr, lr.dz_unscaled ? sc : nullptr, true));
                     }
+                    LPM_HIP(stop.finish());
+                    at_point = ev;
                 }
                 break;
             }
@@ -685,19 +713,27 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                     } else if (l.src == first - 1 && (boundary & LPM_MASK_DX)) {
                         gmask = x;
                     }
+                    const hipEvent_t ev = point_after(i);
+                    StopEvent stop(ev, st);
                     if (do_data && l.kind == LPM_MAXPOOL2)
                         LPM_HIP(launch_maxpool_bwd(s->dtype, s->m, l.h_in, l.w_in, l.cin, tptr(s, l.src, x, y, stash),
                                                    tptr(s, i, x, y, stash), g, gsrc, gsrc_acc, gmask != nullptr, gmscale, st));
                     else if (do_data)
                         LPM_HIP(launch_gap_bwd(s->dtype, s->m, l.h_in * l.w_in, l.cin, g, gsrc, gsrc_acc, gmask, gmscale, st));
+                    LPM_HIP(stop.finish());
+                    at_point = ev;
                     have[gi(l.src)] = 1;
                 }
                 break;
             case LPM_ATTN:
                 if (want_src) {
+                    const hipEvent_t ev = point_after(i);
+                    StopEvent stop(ev, st);
                     if (do_data)
                         LPM_HIP(launch_attn_bwd(s->dtype, s->m, l.h_in * l.w_in, l.cout, tptr(s, l.src, x, y, stash), g, G[gi(l.src)],
                                                 have[gi(l.src)], kws, st));
+                    LPM_HIP(stop.finish());
+                    at_point = ev;
                     have[gi(l.src)] = 1;
                 }
                 break;
@@ -707,6 +743,13 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
     }
     if (!wtail.empty())
         LPM_HIP(hipStreamUpdateCaptureDependencies(st, wtail.data(), wtail.size(), hipStreamAddCaptureDependencies));
+    if (do_data && data_done) {
+        if (!at_point) {
+            LPM_HIP(hipEventRecord(data_done, st));
+            at_point = data_done;
+        }
+        *data_point = at_point;
+    }
     if (do_weights && (beside || !jobs.empty())) {
         red.reserve(jobs.size());
         hipStream_t wst2 = (wstream && wstream2 && deferred && jobs.size() > 1) ? (hipStream_t)wstream2 : nullptr;
@@ -728,11 +771,13 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
             LPM_HIP(hipEventRecord(s->ev_w2_join, wst2));
             LPM_HIP(hipStreamWaitEvent(wst, s->ev_w2_join, 0));
         }
+        const hipEvent_t end = beside ? s->ev_join : weights_done;
+        StopEvent stop(end, wst);
         if (!red.empty()) LPM_HIP(launch_reduce_batch(red.data(), (int)red.size(), wst));
-        if (beside) {        // join: the caller's stream is ordered after every weight gradient
-            LPM_HIP(hipEventRecord(s->ev_join, wst));
-            LPM_HIP(hipStreamWaitEvent(st, s->ev_join, 0));
-        }
+        LPM_HIP(stop.finish());
+        if (beside) LPM_HIP(hipStreamWaitEvent(st, s->ev_join, 0));        // the caller's stream is ordered after every weight gradient
+    } else if (do_weights && weights_done) {
+        LPM_HIP(hipEventRecord(weights_done, wst));
     }
     return LPM_OK;
 }

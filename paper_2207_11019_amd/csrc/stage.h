@@ -79,10 +79,11 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                               const float* params, const void* lowp, const void* stash, float* grads,
                               int32_t accumulate, void* bwd_ws, void* stream, void* wstream, int32_t parity,
                               int32_t phases, int32_t fc_slot = -1, int32_t fc_flush = 0, int32_t layer_slot = -1,
-                              int32_t boundary = 0, void* wstream2 = nullptr, bool counts_zeroed = false);
-// F_{z,j}; counts_zeroed: see stage.cpp
+                              int32_t boundary = 0, void* wstream2 = nullptr, bool counts_zeroed = false, hipEvent_t data_done = nullptr, hipEvent_t* data_point = nullptr,
+                              hipEvent_t weights_done = nullptr);
+// F_{z,j}; counts_zeroed, done: see stage.cpp
 int32_t lpm_stage_forward_on(lpm_stage* s, const void* x, void* y, const int32_t* labels, float* loss_accum, const float* params,
-                             const void* lowp, void* stash, void* fwd_ws, float loss_scale, void* stream, bool counts_zeroed);
+                             const void* lowp, void* stash, void* fwd_ws, float loss_scale, void* stream, bool counts_zeroed, hipEvent_t done = nullptr);
 // boundary: a schedule may move the ReLU backward of a stage's last layer into the next stage, whose kernel that
 // writes the gradient w.r.t. its input then masks it with that input (the producer's output) -- one kernel less
 // per cut and micro-batch.  LPM_MASK_DX: this stage masks its dx; LPM_DY_IS_DZ: the gradient this stage receives

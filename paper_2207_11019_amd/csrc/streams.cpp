@@ -99,6 +99,16 @@ hipError_t pick_concurrent_streams(const hipStream_t* taken, int n_taken, hipStr
     return hipSuccess;
 }
 
+static thread_local hipEvent_t t_stop = nullptr;
+hipEvent_t take_stop_event() {
+    const hipEvent_t e = t_stop;
+    t_stop = nullptr;
+    return e;
+}
+StopEvent::StopEvent(hipEvent_t e, hipStream_t st) : e_(e), st_(st) { t_stop = e; }
+StopEvent::~StopEvent() { t_stop = nullptr; }
+hipError_t StopEvent::finish() { return e_ && take_stop_event() ? hipEventRecord(e_, st_) : hipSuccess; }
+
 int next_side_stream_index() {
     std::lock_guard<std::mutex> lock(g_mu);
     const int i = LPM_POOL_SCHEDULE_STREAMS + g_next_side;
