@@ -345,15 +345,21 @@ int32_t pick_locked_stream(lpm_schedule* s, hipStream_t sf) {
 // OVERLAPPED, three workers: 0 enqueues the forward chains on sf, 1 the data phases of the backward chains
 // on sb, 2 the weight phases and the updates on the weight streams (ov_w, and ov_w0 for stage 0; see pick_weight_streams).
 // ev_f[j*Z+Z-1]: forward chain j done; ev_b[j*Z+z]: data phase of B_{z,j} done; ev_w[j*Z]: micro-batch j done.
+// LOCKED (with a synchronous update) is the same with a window of one and the backward chains on the forward stream: the
+// operations follow one another, a backward operation's weight gradients run beside its data phase, and a thread of its own
+// enqueues them -- a wait for an event of another stream costs the host about 10 us, three launches' worth (width-48 ResNet
+// at 13 samples: 2.9 of 3.3 ms per step went into enqueueing on one thread; 3.0 ms with three).
 int32_t overlapped_role(lpm_schedule* s, const RunArgs& a, int32_t role, uint64_t epoch) {
-    const int32_t Z = s->Z, M = s->M, W = s->window;
+    const bool locked = (a.mode & 15) == LPM_LOCKED;
+    const int32_t Z = s->Z, M = s->M, W = locked ? 1 : s->window;
     const bool async = (a.mode & LPM_ASYNC_UPDATE) != 0;
-    hipStream_t sw = s->ov_w;
+    const hipStream_t w1 = locked ? s->lk_w : s->ov_w, w2 = locked ? s->lk_w : s->ov_w0;
+    hipStream_t sw = w1;
     int32_t rc;
     // Stage 0's weight phase closes every micro-batch, and the next forward chain but one waits for it: with a
     // hardware queue to itself it follows stage 0's data phase from the start instead of queueing behind the other
     // stages' weight phases.  The micro-batch is done at ev_w[j*Z] and, the end of those on the common stream, ev_w[j*Z+1].
-    const bool own0 = !async && Z > 1 && s->ov_w0 != s->ov_w;
+    const bool own0 = !async && Z > 1 && w2 != w1;
     auto await_microbatch = [&](int32_t j, hipStream_t st) -> int32_t {
         const size_t i = (size_t)j * Z;
         if ((rc = await_record(s, s->rec_w[i], epoch))) return rc;
@@ -366,15 +372,15 @@ int32_t overlapped_role(lpm_schedule* s, const RunArgs& a, int32_t role, uint64_
             // F_{0,j} after B_{0,j-W}, the last operation of micro-batch j-W; the other stages follow in stream order
             if (j >= W && (rc = await_microbatch(j - W, a.sf))) return rc;
             for (int32_t z = 0; z < Z; ++z)
-                if ((rc = fwd_op(s, a, z, j, a.sf, async ? forward_version(j, W) : -1, z == Z - 1 ? s->ev_f[(size_t)j * Z + z] : nullptr))) return rc;
+                if ((rc = fwd_op(s, a, z, j, a.sf, async ? forward_version(j, W) : -1, z == Z - 1 && !locked ? s->ev_f[(size_t)j * Z + z] : nullptr))) return rc;
             publish(s->rec_f[(size_t)j * Z + Z - 1], epoch);
         }
     } else if (role == 1) {
-        LPM_HIP(hipStreamWaitEvent(a.sb, s->ev_fork, 0));
+        if (!locked) LPM_HIP(hipStreamWaitEvent(a.sb, s->ev_fork, 0));
         for (int32_t j = 0; j < M; ++j) {
             const size_t i = (size_t)j * Z + Z - 1;
             if ((rc = await_record(s, s->rec_f[i], epoch))) return rc;
-            LPM_HIP(hipStreamWaitEvent(a.sb, s->ev_f[i], 0));
+            if (!locked) LPM_HIP(hipStreamWaitEvent(a.sb, s->ev_f[i], 0));
             if (W > 2 && j >= 2 && (rc = await_microbatch(j - 2, a.sb))) return rc;
             for (int32_t z = Z - 1; z >= 0; --z) {
                 if (async && j > 0) {      // B_{z,j} reads version j: after U_{z,j-1} (which has also consumed the bias gradients)
@@ -382,19 +388,19 @@ int32_t overlapped_role(lpm_schedule* s, const RunArgs& a, int32_t role, uint64_
                     if ((rc = await_record(s, s->rec_w[u], epoch))) return rc;
                     LPM_HIP(hipStreamWaitEvent(a.sb, s->ev_w[u], 0));
                 }
-                if ((rc = bwd_op(s, a, z, j, a.sb, sw, LPM_PHASE_DATA, async ? j : -1, z == 0 && !async, nullptr,
-                                 s->ev_b[(size_t)j * Z + z]))) return rc;
+                if ((rc = bwd_op(s, a, z, j, a.sb, sw, LPM_PHASE_DATA, async ? j : -1, (z == 0 || locked) && !async, nullptr,
+                                 !locked || j == M - 1 ? s->ev_b[(size_t)j * Z + z] : nullptr))) return rc;
                 publish(s->rec_b[(size_t)j * Z + z], epoch);
             }
         }
     } else {
         // Asynchronous update: B_{z,j+1} waits for U_{z,j}, so the weight phases and updates are a chain per stage; odd
         // stages take the second stream (each stage keeps its stream, which orders its updates).
-        const bool async2 = async && Z > 1 && s->ov_w0 != s->ov_w;
+        const bool async2 = async && Z > 1 && w2 != w1;
         // A single stage has the second stream to spare: its weight gradients alternate between the two (ResNet-50
         // conv4_x: 2.43 -> 2.34 ms per step; the weight phases are the longest of the three chains there).
-        hipStream_t sw_pair = (!async && Z == 1 && s->ov_w0 != s->ov_w) ? s->ov_w0 : nullptr;
-        hipStream_t sw_all = sw, sw_0 = s->ov_w0;
+        hipStream_t sw_pair = (!async && Z == 1 && w2 != w1) ? w2 : nullptr;
+        hipStream_t sw_all = sw, sw_0 = w2;
         for (int32_t j = 0; j < M; ++j) {
             bool closed[2] = {false, false};       // ev_w[j*Z], ev_w[j*Z+1] stand at the end of a weight phase
             for (int32_t z = Z - 1; z >= 0; --z) {
@@ -403,11 +409,12 @@ int32_t overlapped_role(lpm_schedule* s, const RunArgs& a, int32_t role, uint64_
                 if ((rc = await_record(s, s->rec_b[i], epoch))) return rc;
                 // Stage 0 closes the micro-batch, and the next forward chain but one waits for it: there the weight
                 // gradients follow the data phase layer by layer (the events were recorded before rec_b was published)
-                const bool by_layer = z == 0 && !async;
+                const bool by_layer = (z == 0 || locked) && !async;
                 if (!by_layer) LPM_HIP(hipStreamWaitEvent(sw, s->pt_b[i], 0));
                 // The last weight phase of a stream closes the micro-batch there -- unless more of it follows: the update, or the
                 // end of a data phase that goes on after the last layer's weight gradient may start
-                const bool rest = by_layer && s->pt_b[i] == s->ev_b[i];
+                // (LOCKED: the next forward chain is on the data phase's own stream)
+                const bool rest = by_layer && (!locked || j == M - 1) && s->pt_b[i] == s->ev_b[i];
                 const bool closes = !async && j < M - 1 && !rest && (z == 0 || (own0 && z == 1));
                 if ((rc = bwd_op(s, a, z, j, a.sb, sw, LPM_PHASE_WEIGHTS, async ? j : -1, by_layer, sw_pair, nullptr, closes ? s->ev_w[i] : nullptr))) return rc;
                 if (rest) LPM_HIP(hipStreamWaitEvent(sw, s->ev_b[i], 0));
@@ -531,10 +538,17 @@ int32_t enqueue(lpm_schedule* s, const RunArgs& a) {
         }
         return LPM_OK;
     }
+    if ((a.mode & 15) == LPM_LOCKED && lw) {
+        RunArgs one = a;
+        one.sb = a.sf;
+        if ((rc = run_roles(s, one, overlapped_role, 3))) return rc;
+        LPM_HIP(hipStreamWaitEvent(a.sf, s->ev_w[(size_t)(M - 1) * Z], 0));
+        return LPM_OK;
+    }
     if ((a.mode & 15) == LPM_LOCKED) {
         for (int32_t j = 0; j < M; ++j) {
             for (int32_t z = 0; z < Z; ++z) if ((rc = fwd_op(s, a, z, j, a.sf))) return rc;
-            for (int32_t z = Z - 1; z >= 0; --z) if ((rc = bwd_op(s, a, z, j, a.sf, lw))) return rc;
+            for (int32_t z = Z - 1; z >= 0; --z) if ((rc = bwd_op(s, a, z, j, a.sf, nullptr))) return rc;
         }
         for (int32_t z = 0; z < Z; ++z) if ((rc = upd_op(s, a, z, a.sf))) return rc;
         return LPM_OK;
