@@ -10,11 +10,23 @@
 //          group of 16 lanes, lane i supplies the address of 4 consecutive elements of a row and receives element (i % 4) of the
 //          rows supplied by lanes 4j + i/4, j = 0..3 -- a column of 4 rows.
 //   float  v_mfma_f32_32x32x2_f32 takes one value per lane, channel lane % 32 of pixel lane / 32: a plain 4-byte LDS read.
-// Blocks own BM output x BN input channels and one filter tap (TAPS = 1: K tiles of 64 -- float: 32 -- consecutive output pixels),
-// or the three taps of a row of a 3x3 stride-1 filter (TAPS = 3: K tiles of eight segments of 8 pixels of an output row; the ten
-// input pixels a segment meets are loaded once, fetched once and shifted by one and two pixels with v_alignbit, so the LDS
-// transpose reads, which bound the single-tap form at 64x64 channels, serve three times the products).
+// Blocks own BM output x BN input channels and one filter tap, or the three taps of a row of a 3x3 stride-1 filter:
+//   LIN    1x1 filter, stride 1: a K tile is 64 (float: 32) consecutive pixels of both tensors.
+//   PIX    one tap of any other filter: consecutive output pixels, each with its input pixel.
+//   ROW3   a filter row: a K tile is eight segments of 8 pixels of an output row; the ten input pixels a segment meets are
+//          loaded once, fetched once and shifted by one and two pixels with v_alignbit, so the LDS transpose reads serve three
+//          times the products.
+// Where PIX and ROW3 find a pixel or segment -- byte offsets and which of its pixels exist -- is worked out by one thread each,
+// some hundred at a time, and kept in LDS: the loader's address arithmetic, a dozen instructions per load when every lane
+// followed its own pixel from tile to tile, had taken more issue slots than the matrix instructions.
+// Eight wavefronts: two groups of four share the block's tile of dW, each with half of every K tile, and add their sums through
+// LDS at the end (one group per SIMD left the latencies of LDS and barrier uncovered: a launch is about one block per CU).
 // The pixel range may be split over blocks; the partial results are summed by wgrad_reduce_batch in a fixed order.
+// Measured alone with its reduction (us; four wavefronts, addresses followed lane by lane -> this): 3x3 256 -> 256 channels, 128
+// images of 14x14 65.7 -> 47.5, 16 images 21.4 -> 18.7; 4 x 224^2 64 -> 64 34.7 -> 26.7; 1x1 1024 -> 256, 128 x 14^2 39.8 -> 28.7.
+// Three stages for the 64-channel tiles: with four (or records for a longer run of pixels) the launch is faster alone, but
+// the other streams' blocks no longer fit the CU beside it (R50 conv4_x at 64: 1.85 -> 1.89 ms per step).  Four for the
+// 128-channel tiles and for filter rows over 64 K tiles and more, where the loads in flight count for more.
 #include "lpm_internal.h"
 #include "elem.h"
 #include "lds_dma.h"
@@ -38,8 +50,9 @@ struct WgArgs {
     size_t part_stride;    // floats between the partials of consecutive splits (>= Cout*K + Cout)
     unsigned dz_bytes, x_bytes;
     int Cout, Cin, Kh, Kw, Kd, H, W, D, Ho, Wo, Do, stride, pad, pad_d;
-    FastDiv dTW, dHo;
-    int TW;                // units per output row: Wo pixels (TAPS = 1) or ceil(Wo / 8) segments (TAPS = 3)
+    FastDiv dTW, dHo, dDo;
+    int TW;                // units per output row: Wo pixels or ceil(Wo / 8) segments (ROW3)
+    int units;             // m * Do * Ho * TW
     int kt_total, kt_per_split, splits;
     int accumulate;
     int co_tiles, ci_tiles, tap_groups;
@@ -50,20 +63,28 @@ __device__ __forceinline__ u32x2_ tr4(const unsigned char* p) {
     return __builtin_bit_cast(u32x2_, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4_*)(p)));
 }
 
-template <typename E, int BM, int BN, int WGM, int WGN, int TAPS, int NST, int OCC>
-__global__ void __launch_bounds__(WGM * WGN * 64, OCC) wgrad_mm(WgArgs p) {
-    constexpr int ES = sizeof(E), T = WGM * WGN * 64, KT = ES == 2 ? 64 : 32;
+enum { LIN = 0, PIX = 1, ROW3 = 3 };
+
+template <typename E, int BM, int BN, int KIND, int NST>
+__global__ void __launch_bounds__(512, 1) wgrad_mm(WgArgs p) {
+    constexpr int TAPS = KIND == ROW3 ? 3 : 1, WGM = 2, WGN = 2;
+    constexpr int ES = sizeof(E), T = 512, KT = ES == 2 ? 64 : 32;
     constexpr int WTM = BM / WGM, WTN = BN / WGN, MI = WTM / 32, NI = WTN / 32;
     constexpr int HX = 10;                                                    // input pixels of a segment
     constexpr int PA = BM * ES, PB = BN * ES;                                 // bytes of an LDS row
-    constexpr int CA = PA / 16, CB = PB / 16;                                 // chunks of a row
     constexpr int A_BYTES = KT * PA;
-    constexpr int B_ROWS = TAPS == 3 ? 8 * HX : KT;
+    constexpr int B_ROWS = KIND == ROW3 ? 8 * HX : KT;
     constexpr int A_LD = A_BYTES / (T * 16), B_LD = (B_ROWS * PB + T * 16 - 1) / (T * 16), LPT = A_LD + B_LD;
-    constexpr int STAGE = A_BYTES + B_LD * T * 16;
-    constexpr int KU = TAPS == 3 ? 8 : KT;                                    // units per K tile
-    static_assert(TAPS == 1 || ES == 2, "filter rows: bf16");
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];      // NST stages
+    constexpr int STAGE = A_BYTES + B_ROWS * PB;                              // (loads past the last row go to a dump of 1 KB)
+    constexpr int KU = KIND == ROW3 ? 8 : KT;                                 // units per K tile
+    constexpr int CT = ES == 2 && KIND != ROW3 ? 8 : 16, CU = CT * KU;         // K tiles and units of a chunk of unit records
+    constexpr int KSW = 2;                                                    // K steps of a tile per wavefront
+    static_assert(KIND != ROW3 || ES == 2, "filter rows: bf16");
+    static_assert(A_LD * T * 16 == A_BYTES && CT % 2 == 0 && CT >= 8 && NST <= 4 && CU <= T && (B_ROWS * PB) % 1024 == 0, "layout");
+    constexpr int DUMP = KIND == ROW3 ? 1024 : 0;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];      // NST stages, the dump, two chunks of records
+    unsigned* rec1 = reinterpret_cast<unsigned*>(lds + NST * STAGE);          // PIX: offset of the input pixel, or none
+    uint4* rec3 = reinterpret_cast<uint4*>(lds + NST * STAGE + DUMP);                // ROW3: dz offset, its pixels; x offset, mask of its pixels
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     // all blocks of one pixel range go to one XCD (they read the same dz and x rows)
@@ -80,99 +101,97 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) wgrad_mm(WgArgs p) {
 
     u32x4_ rsD = buffer_words(p.DZ, p.dz_bytes), rsX = buffer_words(p.X, p.x_bytes);
 
-    // ---- loader state.  The K tile's addresses move by constants from tile to tile, with a correction where a unit passes the
-    // end of an output row or image: no multiplication per load.
-    const int step_q = div_by(KU, p.dTW), step_w = KU - step_q * p.TW, step_n = div_by(step_q, p.dHo), step_h = step_q - step_n * p.Ho;
-    auto locate = [&](int u, int& w, int& h, int& n) __attribute__((always_inline)) {
-        const int q = div_by(u, p.dTW);
-        w = u - q * p.TW; n = div_by(q, p.dHo); h = q - n * p.Ho;
+    // ---- unit records of chunk c, one per thread
+    const unsigned cA = (unsigned)(p.Cout * ES), cB = (unsigned)(p.Cin * ES);
+    auto fill = [&](int c) __attribute__((always_inline)) {
+        if (KIND == LIN || tid >= CU) return;
+        const int u = (kt0 + c * CT) * KU + tid, end = min(p.units, (kt0 + nk) * KU);
+        const bool in = u < end;
+        const int uu = in ? u : 0, q = div_by(uu, p.dTW), w = uu - q * p.TW, n = div_by(q, p.dHo), h = q - n * p.Ho;
+        int img = n;
+        bool ok = in;
+        if (p.D > 1 || p.Do > 1) {           // n counts (sample, output slice) pairs
+            const int ns = div_by(n, p.dDo), d = (n - ns * p.Do) * p.stride + kd - p.pad_d;
+            ok = ok & ((unsigned)d < (unsigned)p.D);
+            img = ns * p.D + d;
+        }
+        const int y = h * p.stride + kh - p.pad;
+        ok = ok & ((unsigned)y < (unsigned)p.H);
+        if (KIND == ROW3) {
+            const int x0 = w * 8 - p.pad, lo = max(0, -x0), hi = min(HX, p.W - x0);
+            rec3[(c & 1) * CU + tid] = make_uint4((unsigned)((n * p.Ho + h) * p.Wo + w * 8) * cA, in ? (unsigned)min(8, p.Wo - w * 8) : 0u,
+                                                 (unsigned)((img * p.H + y) * p.W + x0) * cB, ok && hi > lo ? (1u << hi) - (1u << lo) : 0u);
+        } else {
+            const int x = w * p.stride + kw - p.pad;
+            rec1[(c & 1) * CU + tid] = ok && (unsigned)x < (unsigned)p.W ? (unsigned)((img * p.H + y) * p.W + x) * cB : WG_OOB;
+        }
     };
-    const int UW = TAPS == 3 ? 8 : 1;                 // output pixels of a unit
-    // dz, TAPS = 1: rows are consecutive in memory; a row past the last pixel lies past the buffer's end.
-    // TAPS = 3: load i of a wavefront is segment i * T/64 + wave of the tile, pixel lane / 8
-    unsigned a_off[A_LD], a_s[TAPS == 3 ? A_LD : 1];
-    int aw[TAPS == 3 ? A_LD : 1], ah[TAPS == 3 ? A_LD : 1];
-    const unsigned cA = (unsigned)(p.Cout * ES);
+    // ---- loader state: the lane's row and channel in a K tile
+    unsigned a_off[A_LD], b_off[B_LD];
+    int a_px[A_LD], b_u[B_LD], b_in[B_LD];
 #pragma unroll
     for (int i = 0; i < A_LD; ++i) {
-        const int idx = i * T + tid, r = idx / CA, c = idx - r * CA, ch = co0 + c * (16 / ES);
-        if (TAPS == 3) {
-            int an;
-            locate(kt0 * KU + i * (T / 64) + wave, aw[i], ah[i], an);
-            a_s[i] = (unsigned)((an * p.Ho + ah[i]) * p.Wo + aw[i] * 8) * cA;
-            a_off[i] = ch < p.Cout ? (unsigned)((r & 7) * p.Cout + ch) * ES : WG_OOB;
-        } else {
-            a_off[i] = ch < p.Cout ? (unsigned)(r * p.Cout + ch) * ES : WG_OOB;
-        }
+        const int idx = i * T + tid, r = idx / (PA / 16), ch = co0 + (idx - r * (PA / 16)) * (16 / ES);
+        a_px[i] = ch < p.Cout ? r & 7 : 8;                        // ROW3: pixel of the segment (8: none)
+        a_off[i] = KIND == ROW3 ? (unsigned)((r & 7) * p.Cout + ch) * ES : ch < p.Cout ? (unsigned)(r * p.Cout + ch) * ES : WG_OOB;
     }
-    if (TAPS == 1) a_s[0] = (unsigned)kt0 * (unsigned)KT * cA;
-    const unsigned dA = (unsigned)((step_n * p.Ho + step_h) * p.Wo + step_w * 8) * cA, dAw = (unsigned)(p.Wo - p.TW * 8) * cA;
-    // x: a row per pixel.  bx, by: input coordinates under the block's tap; thr: bx of the first unit past the output row
-    unsigned b_off[B_LD];
-    int bx[B_LD], by[B_LD], bn[B_LD], thr[TAPS == 3 ? B_LD : 1];
-    const unsigned cB = (unsigned)(p.Cin * ES);
-    const bool vol = p.D > 1 || p.Do > 1;
-    const int sx = UW * p.stride, ylim = p.Ho * p.stride + kh - p.pad;
-    if (TAPS == 1) thr[0] = p.TW * sx + kw - p.pad;
 #pragma unroll
     for (int i = 0; i < B_LD; ++i) {
-        const int idx = i * T + tid, r = idx / CB, c = idx - r * CB, ch = ci0 + c * (16 / ES);
-        const int seg = TAPS == 3 ? r / HX : r, in = TAPS == 3 ? r - seg * HX - p.pad : kw - p.pad;
+        const int idx = i * T + tid, r = idx / (PB / 16), ch = ci0 + (idx - r * (PB / 16)) * (16 / ES);
         const bool ok = r < B_ROWS && ch < p.Cin;
-        int w, h, n;
-        locate(kt0 * KU + (r < B_ROWS ? seg : 0), w, h, n);
-        bx[i] = ok ? w * sx + in : -(1 << 30);       // (a chunk that loads nothing stays left of every image)
-        if (TAPS == 3) thr[i] = p.TW * sx + in;
-        by[i] = h * p.stride + kh - p.pad;
-        bn[i] = n;
-        // volumes: the image (slice) is found anew for every tile, the offset is the one inside it
-        b_off[i] = (unsigned)(((vol ? 0 : n) * p.H + by[i]) * p.W + w * sx + in) * cB + (unsigned)ch * ES;
+        b_u[i] = KIND == ROW3 ? min(r / HX, 7) : r;
+        b_in[i] = KIND == ROW3 ? (ok ? r - r / HX * HX : 31) : 0;                     // (bit 31 of a mask is never set)
+        b_off[i] = KIND == ROW3 ? (unsigned)(b_in[i] * p.Cin + ch) * ES : KIND == LIN ? (ok ? (unsigned)(r * p.Cin + ch) * ES : WG_OOB)
+                                                                                      : (ok ? (unsigned)ch * ES : WG_OOB);
     }
-    const unsigned dB = (unsigned)(((vol ? 0 : step_n) * p.H + step_h * p.stride) * p.W + step_w * sx) * cB;
-    const unsigned dBw = (unsigned)(p.stride * p.W - p.TW * sx) * cB;                                    // unit wraps to the next output row
-    const unsigned dBh = (unsigned)((vol ? 0 : p.H) - p.Ho * p.stride) * (unsigned)p.W * cB;             // row wraps to the next image
-    // The loads of a tile come in four parts, each behind a few matrix instructions of the loop below.  Past the last tile the
-    // buffers count as empty: zeros arrive, and the number of loads in flight stays what the waits assume.
-    int left = nk;
+    // the records of the K tile to be loaded next, and its wave-uniform offsets (LIN; dz of PIX)
+    int tl = 0;
+    uint2 ra[KIND == ROW3 ? A_LD : 1], rb[KIND == ROW3 ? B_LD : 1];
+    unsigned rp_[KIND == PIX ? B_LD : 1];
+    unsigned sA = (unsigned)kt0 * (unsigned)KT * cA, sB = (unsigned)kt0 * (unsigned)KT * cB;
+    auto look_up = [&]() __attribute__((always_inline)) {
+        const int u0 = (tl * KU) & (2 * CU - 1);
+        if constexpr (KIND == ROW3) {
+#pragma unroll
+            for (int i = 0; i < A_LD; ++i) ra[i] = *reinterpret_cast<const uint2*>(&rec3[u0 + ((i * T + tid) / (PA / 16) >> 3)]);
+#pragma unroll
+            for (int i = 0; i < B_LD; ++i) rb[i] = *(reinterpret_cast<const uint2*>(&rec3[u0 + b_u[i]]) + 1);
+        } else if constexpr (KIND == PIX) {
+#pragma unroll
+            for (int i = 0; i < B_LD; ++i) rp_[i] = rec1[u0 + b_u[i]];
+        }
+    };
+    // The loads of a tile come in four parts, put behind matrix instructions by the loop below.  Past the last tile nothing is
+    // in range: zeros arrive, and the number of loads in flight stays what the waits assume.
     bool live = false;
     auto issue = [&](int st, int part) __attribute__((always_inline)) {
         unsigned char* sp = lds + st * STAGE + wave * 1024;
-        if (part == 0) {
-            live = left > 0;
-            --left;
+        if (part == 0 && KIND != ROW3) {
+            live = tl < nk;
             rsD.z = live ? p.dz_bytes : 0u;
-            rsX.z = live ? p.x_bytes : 0u;
+            if (KIND == LIN) rsX.z = live ? p.x_bytes : 0u;
         }
 #pragma unroll
         for (int i = 0; i < A_LD; ++i) {
             if (i * 4 / LPT != part) continue;
-            if (TAPS == 3) {
-                load_to_lds16s(rsD, sp + i * T * 16, (lane >> 3) < p.Wo - aw[i] * 8 ? a_off[i] : WG_OOB, live ? a_s[i] : 0u);
-                aw[i] += step_w; ah[i] += step_h; a_s[i] += dA;
-                if (aw[i] >= p.TW) { aw[i] -= p.TW; ++ah[i]; a_s[i] += dAw; }
-                if (ah[i] >= p.Ho) ah[i] -= p.Ho;
-            } else load_to_lds16s(rsD, sp + i * T * 16, a_off[i], live ? a_s[0] : 0u);
+            if constexpr (KIND == ROW3) load_to_lds16(rsD, sp + i * T * 16, a_px[i] < (int)ra[i].y ? a_off[i] + ra[i].x : WG_OOB);
+            else load_to_lds16s(rsD, sp + i * T * 16, a_off[i], live ? sA : 0u);
         }
 #pragma unroll
         for (int i = 0; i < B_LD; ++i) {
             if ((i + A_LD) * 4 / LPT != part) continue;
-            bool ok = ((unsigned)by[i] < (unsigned)p.H) & ((unsigned)bx[i] < (unsigned)p.W);
-            unsigned off = b_off[i];
-            if (vol) {                               // bn counts (sample, output slice) pairs
-                const int ns = bn[i] / p.Do, d = (bn[i] - ns * p.Do) * p.stride + kd - p.pad_d;
-                ok = ok & ((unsigned)d < (unsigned)p.D);
-                off += (unsigned)((ns * p.D + d) * p.H * p.W) * cB;
-            }
-            load_to_lds16(rsX, sp + A_BYTES + i * T * 16, ok ? off : WG_OOB);      // (images past the last lie past the buffer's end)
-            bx[i] += step_w * sx; by[i] += step_h * p.stride; b_off[i] += dB;
-            if (vol) bn[i] += step_n;
-            const bool ww = bx[i] >= thr[TAPS == 3 ? i : 0];
-            bx[i] -= ww ? p.TW * sx : 0; by[i] += ww ? p.stride : 0; b_off[i] += ww ? dBw : 0u;
-            const bool hw = by[i] >= ylim;
-            by[i] -= hw ? p.Ho * p.stride : 0; b_off[i] += hw ? dBh : 0u;
-            if (vol) bn[i] += hw ? 1 : 0;
+            unsigned char* d = sp + A_BYTES + i * T * 16;
+            if (KIND == ROW3 && (i * T + wave * 64) * 16 >= B_ROWS * PB) d = lds + NST * STAGE;
+            if constexpr (KIND == ROW3) load_to_lds16(rsX, d, (rb[i].y >> b_in[i]) & 1u ? b_off[i] + rb[i].x : WG_OOB);
+            else if constexpr (KIND == PIX) load_to_lds16(rsX, d, ((rp_[i] != WG_OOB) & (b_off[i] != WG_OOB)) ? b_off[i] + rp_[i] : WG_OOB);
+            else load_to_lds16s(rsX, d, b_off[i], live ? sB : 0u);
         }
-        if (TAPS == 1 && part == 3) a_s[0] += (unsigned)KT * cA;
+        if (part == 3) {
+            ++tl;
+            sA += (unsigned)KT * cA;
+            if (KIND == LIN) sB += (unsigned)KT * cB;
+            look_up();
+        }
     };
 
     f32x16 acc[TAPS][MI][NI];
@@ -186,7 +205,7 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) wgrad_mm(WgArgs p) {
                 for (int i = 0; i < 16; ++i) acc[t][mi][ni][i] = 0.f;
     // the blocks of tap group 0 / Cin tile 0 also sum dz over the pixels (the bias gradient): the wavefronts of the first column
     // add up the operands they hold anyway, a channel per lane
-    const int wm = wave / WGN, wn = wave - wm * WGN;
+    const int wk = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
     const bool do_bias = p.db != nullptr && grp == 0 && ci_t == 0 && wn == 0;
     float bsum[MI];
 #pragma unroll
@@ -197,23 +216,25 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) wgrad_mm(WgArgs p) {
     const int tr_row = (lane & 15) >> 2, tr_col = (((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2;
     const int rl = lane & 31, kq = lane >> 5;
     const unsigned fa = ES == 2 ? (unsigned)((kq * 8 + tr_row) * PA + wm * WTM * 2 + tr_col) : (unsigned)(kq * PA + (wm * WTM + rl) * 4);
-    const unsigned fb = A_BYTES + (ES == 2 ? (unsigned)((kq * (TAPS == 3 ? HX : 8) + tr_row) * PB + wn * WTN * 2 + tr_col)
+    const unsigned fb = A_BYTES + (ES == 2 ? (unsigned)((kq * (KIND == ROW3 ? HX : 8) + tr_row) * PB + wn * WTN * 2 + tr_col)
                                            : (unsigned)(kq * PB + (wn * WTN + rl) * 4));
 
     // two operand sets: the next K tile is read from LDS while the matrix cores work on the present one
-    struct Frag { unsigned a[4][MI][4], b[4][NI][TAPS == 3 ? 6 : 4]; };
+    struct Frag { unsigned a[KSW][MI][4], b[KSW][NI][TAPS == 3 ? 6 : 4]; };
+    const int kw0 = wk * KSW;                // the wavefront's first K step
     auto read = [&](Frag& f, int st, int ks) __attribute__((always_inline)) {
         const unsigned char* sp = lds + st * STAGE;
+        const int ka = kw0 + ks;
         if constexpr (ES == 2) {
 #pragma unroll
             for (int mi = 0; mi < MI; ++mi) {
-                const unsigned char* q = sp + fa + ks * 16 * PA + mi * 64;
+                const unsigned char* q = sp + fa + ka * 16 * PA + mi * 64;
                 const u32x2_ v0 = tr4(q), v1 = tr4(q + 4 * PA);
                 f.a[ks][mi][0] = v0.x; f.a[ks][mi][1] = v0.y; f.a[ks][mi][2] = v1.x; f.a[ks][mi][3] = v1.y;
             }
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) {
-                const unsigned char* q = sp + fb + ks * (TAPS == 3 ? 2 * HX : 16) * PB + ni * 64;
+                const unsigned char* q = sp + fb + ka * (TAPS == 3 ? 2 * HX : 16) * PB + ni * 64;
                 const u32x2_ v0 = tr4(q), v1 = tr4(q + 4 * PB);
                 f.b[ks][ni][0] = v0.x; f.b[ks][ni][1] = v0.y; f.b[ks][ni][2] = v1.x; f.b[ks][ni][3] = v1.y;
                 if constexpr (TAPS == 3) {
@@ -225,9 +246,9 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) wgrad_mm(WgArgs p) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
 #pragma unroll
-                for (int mi = 0; mi < MI; ++mi) f.a[ks][mi][j] = *reinterpret_cast<const unsigned*>(sp + fa + (ks * 8 + j * 2) * PA + mi * 128);
+                for (int mi = 0; mi < MI; ++mi) f.a[ks][mi][j] = *reinterpret_cast<const unsigned*>(sp + fa + (ka * 8 + j * 2) * PA + mi * 128);
 #pragma unroll
-                for (int ni = 0; ni < NI; ++ni) f.b[ks][ni][j] = *reinterpret_cast<const unsigned*>(sp + fb + (ks * 8 + j * 2) * PB + ni * 128);
+                for (int ni = 0; ni < NI; ++ni) f.b[ks][ni][j] = *reinterpret_cast<const unsigned*>(sp + fb + (ka * 8 + j * 2) * PB + ni * 128);
             }
         }
     };
@@ -284,6 +305,9 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) wgrad_mm(WgArgs p) {
         asm volatile("" ::: "memory");
     };
     if (nk > 0) {
+        fill(0);
+        if (KIND != LIN) __syncthreads();
+        look_up();
 #pragma unroll
         for (int i = 0; i < NST - 1; ++i)
 #pragma unroll
@@ -293,27 +317,70 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) wgrad_mm(WgArgs p) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) issue(NST - 1, q);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) read(f0, 0, ks);
+        for (int ks = 0; ks < KSW; ++ks) read(f0, 0, ks);
         int st = 0;
         auto half = [&](const Frag& cur, Frag& nxt) __attribute__((always_inline)) {
             const int st1 = st == NST - 1 ? 0 : st + 1;
             meet();
             read(nxt, st1, 0);
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
+            for (int ks = 0; ks < KSW; ++ks) {
                 __builtin_amdgcn_sched_barrier(0);
-                if (ks < 3) read(nxt, st1, ks + 1);
+                if (ks + 1 < KSW) read(nxt, st1, ks + 1);
                 multiply(cur, ks);
-                issue(st, ks);
+                issue(st, 2 * ks);
+                issue(st, 2 * ks + 1);
             }
             __builtin_amdgcn_sched_barrier(0);
             st = st1;
         };
-        for (int it = 0; it < nk; it += 2) {     // (an odd count ends with a tile of zeros)
-            half(f0, f1);
-            half(f1, f0);
+        // A chunk's records are written while the chunk before is worked on: the one before that, in the same place, has been
+        // loaded (loads run NST - 1 tiles ahead), and at least CT - NST barriers pass until the first is read.
+        for (int c = 0, it = 0; it < nk; ++c) {
+            fill(c + 1);
+            const int e = KIND == LIN ? nk : min(nk, it + CT);
+            for (; it < e; it += 2) {            // (an odd count ends with a tile of zeros)
+                half(f0, f1);
+                half(f1, f0);
+            }
         }
         LPM_WAIT_VM(0);
+    }
+
+    // the second group of wavefronts hands its sums to the first
+    __syncthreads();
+    {
+        float4* ex = reinterpret_cast<float4*>(lds) + (wave & 3) * (TAPS * MI * NI * 4 * 64) + lane;
+        float* exb = reinterpret_cast<float*>(lds + 4 * TAPS * MI * NI * 4096) + (wave & 3) * (MI * 64) + lane;
+        static_assert(4 * TAPS * MI * NI * 4096 + 4 * MI * 256 <= NST * STAGE, "the sums fit the dead stages");
+        if (wk) {
+#pragma unroll
+            for (int t = 0; t < TAPS; ++t)
+#pragma unroll
+                for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            ex[(((t * MI + mi) * NI + ni) * 4 + q) * 64] = make_float4(acc[t][mi][ni][4 * q], acc[t][mi][ni][4 * q + 1], acc[t][mi][ni][4 * q + 2], acc[t][mi][ni][4 * q + 3]);
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) exb[mi * 64] = bsum[mi];
+        }
+        __syncthreads();
+        if (wk) return;
+#pragma unroll
+        for (int t = 0; t < TAPS; ++t)
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float4 v = ex[(((t * MI + mi) * NI + ni) * 4 + q) * 64];
+                        acc[t][mi][ni][4 * q] += v.x; acc[t][mi][ni][4 * q + 1] += v.y; acc[t][mi][ni][4 * q + 2] += v.z; acc[t][mi][ni][4 * q + 3] += v.w;
+                    }
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) bsum[mi] += exb[mi * 64];
     }
 
     // accumulator element i of a lane: row (i / 4) * 8 + (lane / 32) * 4 + i % 4, column lane % 32
@@ -409,15 +476,13 @@ size_t wgrad_mm_ws_bytes(int dtype, const ConvGeom& g) {
     return pl.splits > 1 ? (size_t)pl.splits * wg_stride(g) * sizeof(float) : 0;
 }
 
-template <typename E, int BM, int BN, int WGM, int WGN, int TAPS, int NST, int OCC>
+template <typename E, int BM, int BN, int KIND, int NST>
 static hipError_t go(const WgArgs& a, const WgPlan& pl, hipStream_t st) {
-    constexpr int ES = sizeof(E), T = WGM * WGN * 64, KT = ES == 2 ? 64 : 32, rows = TAPS == 3 ? 80 : KT;
-    constexpr int stage = KT * BM * ES + (rows * BN * ES + T * 16 - 1) / (T * 16) * (T * 16), bytes = NST * stage;
-    static const hipError_t attr = hipFuncSetAttribute((const void*)wgrad_mm<E, BM, BN, WGM, WGN, TAPS, NST, OCC>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    constexpr int ES = sizeof(E), KT = ES == 2 ? 64 : 32, rows = KIND == ROW3 ? 80 : KT;
+    constexpr int stage = KT * BM * ES + rows * BN * ES, bytes = NST * stage + (KIND == LIN ? 0 : KIND == ROW3 ? 1024 + 256 * 16 : 1024 * 4);
+    static const hipError_t attr = hipFuncSetAttribute((const void*)wgrad_mm<E, BM, BN, KIND, NST>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((wgrad_mm<E, BM, BN, WGM, WGN, TAPS, NST, OCC>), dim3((unsigned)(pl.co_tiles * pl.ci_tiles * pl.groups), 1, pl.splits),
-                       dim3(T), bytes, st, a);
+    hipLaunchKernelGGL((wgrad_mm<E, BM, BN, KIND, NST>), dim3((unsigned)(pl.co_tiles * pl.ci_tiles * pl.groups), 1, pl.splits), dim3(512), bytes, st, a);
     return hipGetLastError();
 }
 
@@ -435,15 +500,17 @@ hipError_t wgrad_mm_launch(int dtype, const ConvGeom& g, const void* x, const vo
     a.H = g.H; a.W = g.W; a.D = g.D; a.Ho = g.Ho; a.Wo = g.Wo; a.Do = g.Do;
     a.stride = g.stride; a.pad = g.pad; a.pad_d = g.pad_d;
     a.TW = pl.TW;
-    a.dTW = fast_div(pl.TW); a.dHo = fast_div(g.Ho);
+    a.dTW = fast_div(pl.TW); a.dHo = fast_div(g.Ho); a.dDo = fast_div(g.Do);
+    a.units = (int)((int64_t)g.m * g.Do * g.Ho * pl.TW);
     a.kt_total = pl.kt_total; a.kt_per_split = pl.kt_per; a.splits = pl.splits;
     a.accumulate = accumulate;
     a.co_tiles = pl.co_tiles; a.ci_tiles = pl.ci_tiles; a.tap_groups = pl.groups;
     hipError_t e;
-    if (dtype == LPM_F32) e = go<float, 64, 64, 2, 2, 1, 3, 2>(a, pl, st);
-    else if (pl.taps == 3) e = go<bf16_t, 64, 64, 2, 2, 3, 3, 2>(a, pl, st);
-    else if (pl.big) e = go<bf16_t, 128, 128, 2, 2, 1, 2, 2>(a, pl, st);
-    else e = go<bf16_t, 64, 64, 2, 2, 1, 3, 2>(a, pl, st);
+    const bool lin = g.taps() == 1 && g.stride == 1 && g.pad == 0 && g.pad_d == 0;
+    if (dtype == LPM_F32) e = lin ? go<float, 64, 64, LIN, 3>(a, pl, st) : go<float, 64, 64, PIX, 3>(a, pl, st);
+    else if (pl.taps == 3) e = pl.kt_per >= 64 ? go<bf16_t, 64, 64, ROW3, 4>(a, pl, st) : go<bf16_t, 64, 64, ROW3, 3>(a, pl, st);
+    else if (pl.big) e = lin ? go<bf16_t, 128, 128, LIN, 4>(a, pl, st) : go<bf16_t, 128, 128, PIX, 4>(a, pl, st);
+    else e = lin ? go<bf16_t, 64, 64, LIN, 3>(a, pl, st) : go<bf16_t, 64, 64, PIX, 3>(a, pl, st);
     if (e != hipSuccess || pl.splits == 1) return e;
     const int64_t n = (int64_t)g.Cout * g.K();
     const int nb = dbias ? g.Cout : 0;
