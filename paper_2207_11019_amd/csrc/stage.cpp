@@ -177,6 +177,18 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
         lr.fused_in = true;
         lr.via_shortcut = true;
     }
+    // An identity shortcut's gradient is the masked gradient of the block's output.  Where the block's last layer keeps its dz free
+    // of a scale that is the same tensor as this dz; when the shortcut's only other use of it is as the earlier contribution that
+    // the data gradient of the block before adds in, that kernel reads it there (R50 conv4_x at 512: a sixth of the traffic of
+    // the kernel that wrote both).
+    for (int32_t i = first; i < last; ++i) {
+        LayerRt& lr = s->Ly(i);
+        const int32_t a = lr.d.add_src;
+        if (!lr.fused_side || a == LPM_NONE || a < first || !s->Ly(a).fused_side || ((lr.d.flags & LPM_SCALE) && !lr.dz_unscaled)) continue;
+        int n_add = 0;
+        for (int32_t j = a + 1; j < last; ++j) n_add += s->net[(size_t)j].add_src == a;
+        lr.shortcut_is_dz = n_add == 1;
+    }
     // Pooling-backward fusion: a 2x2 max-pooling (even input extent) whose output feeds exactly one layer, a
     // convolution whose data gradient runs on the stride-1 MFMA kernel: that kernel routes its result to the
     // window maxima itself and the gradient of the pooling output is never stored.
@@ -646,6 +658,9 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                             if (a != LPM_NONE && a >= first && s->Ly(a).via_shortcut) {
                                 side.shortcut = gw + s->Ly(a).dz_off;           // the projection's dz
                                 side.shortcut_scale = s->Ly(a).dz_unscaled ? nullptr : params + s->Ly(a).s_off;
+                                have[gi(a)] = 1;
+                            } else if (pr.shortcut_is_dz) {
+                                G[gi(a)] = gsrc;
                                 have[gi(a)] = 1;
                             } else if (a != LPM_NONE && (a >= first || dx != nullptr)) {
                                 side.shortcut = G[gi(a)];

@@ -32,6 +32,8 @@ struct LayerRt {
                                                  // layer's output gradient and writes the gradient of this layer's shortcut (DgradSide)
     bool via_shortcut = false;                   // fused_in: a scale-only layer read as a shortcut by one fused_side layer; the kernel that
                                                  // writes that layer's shortcut gradient writes this layer's dz instead
+    bool shortcut_is_dz = false;                 // fused_side: its shortcut's gradient is this layer's dz, element for element, and is read
+                                                 // once, as a DgradSide's earlier contribution: it is not stored a second time
     int32_t pool_fwd = -1;                       // conv/FC: index of the max-pooling layer whose forward its own forward kernel performs
     bool pooled_fwd = false;                     // max-pooling: its forward runs inside its producer's forward kernel
     bool unpooled = false;                       // max-pooling: its backward runs inside its consumer's data gradient
