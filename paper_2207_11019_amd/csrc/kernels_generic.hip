@@ -567,14 +567,39 @@ hipError_t launch_maxpool_bwd(int dtype, int32_t m, int32_t H, int32_t W, int32_
 
 // --------------------------------------------------------------------------------------------------
 // global average pooling
-template <typename T>
-__global__ void __launch_bounds__(256) gap_fwd_kernel(int m, int HW, int C, const T* __restrict__ x, T* __restrict__ y) {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)m * C) return;
-    const int c = (int)(idx % C), n = (int)(idx / C);
-    float acc = 0.f;
-    for (int i = 0; i < HW; ++i) acc += ld(x, ((int64_t)n * HW + i) * C + c);
-    st(y, idx, acc / (float)HW);
+// A block takes one sample and a chunk of channels, 16 bytes of them per thread where the count allows; its row lanes share the
+// positions and meet in LDS.  (A thread per channel walked all positions: 17 us for 512 of them, 4 now.)
+template <typename T, int V>
+__global__ void __launch_bounds__(256) gap_fwd_kernel(int HW, int C, int cl_log, const T* __restrict__ x, T* __restrict__ y) {
+    __shared__ float red[256 * V + 256];
+    const int CL = 1 << cl_log, RL = 256 >> cl_log, cx = threadIdx.x & (CL - 1), ty = threadIdx.x >> cl_log;
+    const int cb = blockIdx.x * CL * V, c0 = cb + cx * V, pitch = CL * V + 1;
+    const T* xs = x + (int64_t)blockIdx.y * HW * C;
+    float sum[V];
+#pragma unroll
+    for (int k = 0; k < V; ++k) sum[k] = 0.f;
+    if (c0 < C) {
+        for (int r = ty; r < HW; r += 4 * RL) {
+            float v[4][V];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) EpiVec<T, V>::get(xs, (int64_t)min(r + u * RL, HW - 1) * C + c0, v[u]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (r + u * RL < HW) {
+#pragma unroll
+                    for (int k = 0; k < V; ++k) sum[k] += v[u][k];
+                }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < V; ++k) red[ty * pitch + cx * V + k] = sum[k];
+    __syncthreads();
+    if ((int)threadIdx.x < CL * V && cb + (int)threadIdx.x < C) {
+        float acc = 0.f;
+#pragma unroll 8
+        for (int r = 0; r < RL; ++r) acc += red[r * pitch + threadIdx.x];
+        st(y, (int64_t)blockIdx.y * C + cb + threadIdx.x, acc / (float)HW);
+    }
 }
 
 template <typename T>
@@ -591,9 +616,17 @@ __global__ void __launch_bounds__(256) gap_bwd_kernel(int m, int HW, int C, cons
     st(dx, idx, v);
 }
 
+template <typename T, int V>
+static void gap_launch(int32_t m, int32_t HW, int32_t C, const void* x, void* y, hipStream_t s) {
+    const int cl = epi_chunks_log(C, V);
+    for (int n0 = 0; n0 < m; n0 += 32768)          // (the grid's second extent is limited)
+        hipLaunchKernelGGL((gap_fwd_kernel<T, V>), dim3(nblk(C, V << cl), (unsigned)std::min(m - n0, 32768)), dim3(256), 0, s, HW, C, cl,
+                           (const T*)x + (int64_t)n0 * HW * C, (T*)y + (int64_t)n0 * C);
+}
+
 hipError_t launch_gap_fwd(int dtype, int32_t m, int32_t HW, int32_t C, const void* x, void* y, hipStream_t s) {
-    LPM_DISPATCH(dtype, hipLaunchKernelGGL(gap_fwd_kernel<T>, dim3(nblk((int64_t)m * C, 256)), dim3(256), 0, s, m, HW, C,
-                                           (const T*)x, (T*)y));
+    if (dtype == LPM_BF16) { if (C % 8 == 0) gap_launch<bf16_t, 8>(m, HW, C, x, y, s); else gap_launch<bf16_t, 1>(m, HW, C, x, y, s); }
+    else { if (C % 4 == 0) gap_launch<float, 4>(m, HW, C, x, y, s); else gap_launch<float, 1>(m, HW, C, x, y, s); }
     return hipGetLastError();
 }
 
@@ -619,49 +652,57 @@ __device__ inline float wave_sum(float v) {
     return v;
 }
 
-// One block of 16 wavefronts, a wavefront per row at a time; a row of up to 1024 classes is read once and kept in
-// registers (the kernel closes every forward chain, so its latency counts: three dependent passes over global memory
-// per row and four wavefronts made it 13 us for 32 rows of 10 classes).  The loss is summed in row order by one thread.
-template <typename T>
+// One block of 16 wavefronts, a wavefront per row at a time; a row of up to 64 * KEEP classes is read once and kept in
+// registers, labels and the loss so far are requested with the first row (the kernel closes every forward chain, so its
+// latency counts: every dependent pass over global memory is a microsecond).  The loss is summed in row order by one thread.
+template <typename T, int KEEP>
 __global__ void __launch_bounds__(1024) softmax_ce_kernel(int m, int C, const T* __restrict__ z,
                                                           const int32_t* __restrict__ labels, float loss_scale,
                                                           T* __restrict__ dz, float* __restrict__ loss_accum) {
-    constexpr int KEEP = 16;                 // classes per lane held in registers
     __shared__ float rowloss[256];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const bool cached = C <= 64 * KEEP;
+    const float before = threadIdx.x == 0 ? *loss_accum : 0.f;
     float total = 0.f;
     for (int base = 0; base < m; base += 256) {
         const int nrow = min(256, m - base);
         for (int r = wave; r < nrow; r += 16) {
             const T* zr = z + (int64_t)(base + r) * C;
             T* dr = dz + (int64_t)(base + r) * C;
-            float v[KEEP];
-            float mx = -INFINITY;
-            if (cached) {
+            // a label outside [0, C) selects no class: no one-hot term, and the row's loss becomes NaN so the host sees it
+            const int lab = labels[base + r];
+            const bool lab_ok = (unsigned)lab < (unsigned)C;
+            float v[KEEP > 0 ? KEEP : 1];
+            float mx = -INFINITY, zl = 0.f;
+            if (KEEP > 0) {
 #pragma unroll
                 for (int k = 0; k < KEEP; ++k) {
                     const int c = lane + 64 * k;
                     v[k] = c < C ? ld(zr, c) : -INFINITY;
+                }
+#pragma unroll
+                for (int k = 0; k < KEEP; ++k) {
                     mx = fmaxf(mx, v[k]);
+                    if (lane + 64 * k == lab) zl = v[k];
                 }
             } else {
-                for (int c = lane; c < C; c += 64) mx = fmaxf(mx, ld(zr, c));
+                for (int c = lane; c < C; c += 64) {
+                    const float x = ld(zr, c);
+                    mx = fmaxf(mx, x);
+                    if (c == lab) zl = x;
+                }
             }
             mx = wave_max(mx);
             float se = 0.f;
-            if (cached) {
+            if (KEEP > 0) {
 #pragma unroll
                 for (int k = 0; k < KEEP; ++k) { v[k] = expf(v[k] - mx); se += v[k]; }      // exp(-inf) = 0 past the end
             } else {
                 for (int c = lane; c < C; c += 64) se += expf(ld(zr, c) - mx);
             }
             se = wave_sum(se);
-            // a label outside [0, C) selects no class: no one-hot term, and the row's loss becomes NaN so the host sees it
-            const int lab = labels[base + r];
-            const bool lab_ok = (unsigned)lab < (unsigned)C;
+            zl = __shfl(zl, lab & 63, 64);           // (the lane that met the label)
             const float inv = 1.f / se;
-            if (cached) {
+            if (KEEP > 0) {
 #pragma unroll
                 for (int k = 0; k < KEEP; ++k) {
                     const int c = lane + 64 * k;
@@ -673,20 +714,21 @@ __global__ void __launch_bounds__(1024) softmax_ce_kernel(int m, int C, const T*
                     st(dr, c, (p - (c == lab ? 1.f : 0.f)) * loss_scale);
                 }
             }
-            if (lane == 0) rowloss[r] = lab_ok ? logf(se) - (ld(zr, lab) - mx) : __builtin_nanf("");
+            if (lane == 0) rowloss[r] = lab_ok ? logf(se) - (zl - mx) : __builtin_nanf("");
         }
         __syncthreads();
         if (threadIdx.x == 0)
             for (int r = 0; r < nrow; ++r) total += rowloss[r];
         __syncthreads();
     }
-    if (threadIdx.x == 0) loss_accum[0] += loss_scale * total;
+    if (threadIdx.x == 0) *loss_accum = before + loss_scale * total;
 }
 
 hipError_t launch_softmax_ce(int dtype, int32_t m, int32_t C, const void* logits, const int32_t* labels, float loss_scale,
                              void* dlogits, float* loss_accum, hipStream_t s) {
-    LPM_DISPATCH(dtype, launch_last(softmax_ce_kernel<T>, dim3(1), dim3(1024), 0, s, m, C, (const T*)logits, labels,
-                                           loss_scale, (T*)dlogits, loss_accum));
+    if (C <= 64) LPM_DISPATCH(dtype, launch_last(softmax_ce_kernel<T, 1>, dim3(1), dim3(1024), 0, s, m, C, (const T*)logits, labels, loss_scale, (T*)dlogits, loss_accum));
+    else if (C <= 1024) LPM_DISPATCH(dtype, launch_last(softmax_ce_kernel<T, 16>, dim3(1), dim3(1024), 0, s, m, C, (const T*)logits, labels, loss_scale, (T*)dlogits, loss_accum));
+    else LPM_DISPATCH(dtype, launch_last(softmax_ce_kernel<T, 0>, dim3(1), dim3(1024), 0, s, m, C, (const T*)logits, labels, loss_scale, (T*)dlogits, loss_accum));
     return hipGetLastError();
 }
 
