@@ -130,14 +130,36 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
         if (dgrad_ws_bytes(dtype, lr.g)) s->bwd_counts = true;
         fws = std::max(fws, align_up(fwd_ws_bytes(dtype, lr.g), 256));
     }
+    auto uses = [&](int32_t t, int& n_src, int& n_add) {
+        n_src = n_add = 0;
+        for (int32_t j = std::max(t + 1, first); j < last; ++j) { n_src += s->net[(size_t)j].src == t; n_add += s->net[(size_t)j].add_src == t; }
+    };
+    // Whether layer i's shortcut can take i's dz for its gradient instead of a copy: dz carries no scale, the shortcut is tensor a's
+    // only one, and from then on the gradient of a is only read -- as the earlier contribution that the data gradient
+    // of the block before adds in (a fused_side), or as the dz of a projection without ReLU and scale of its own.
+    auto shares_dz = [&](int32_t i) {
+        const LayerRt& lr = s->Ly(i);
+        const int32_t a = lr.d.add_src;
+        if (a == LPM_NONE || a < first || ((lr.d.flags & LPM_SCALE) && !lr.dz_unscaled)) return false;
+        const LayerRt& ar = s->Ly(a);
+        int n_src, n_add;
+        uses(a, n_src, n_add);
+        if (n_add != 1) return false;
+        if (ar.fused_side) return true;
+        return n_src == 0 && has_weights(ar.d) && !(ar.d.flags & LPM_RELU) && ar.d.add_src == LPM_NONE && (!(ar.d.flags & LPM_SCALE) || ar.dz_unscaled);
+    };
     // Epilogue-backward fusion: when a layer's output feeds exactly one later layer through its `src` edge, that
     // layer's backward kernel (data gradient / pooling backward) applies the ReLU mask and the scale itself and
     // writes dz directly; the bias gradient then comes out of the weight-gradient kernel.
     for (int32_t i = first; i < last; ++i) {
         LayerRt& lr = s->Ly(i);
         const lpm_layer& l = lr.d;
-        if (!has_weights(l) || !(l.flags & (LPM_RELU | LPM_SCALE))) continue;
-        if (i == s->t_out) continue;           // its gradient arrives from outside the stage
+        if (!has_weights(l)) continue;
+        if (i == s->t_out) {                   // its gradient arrives from outside the stage
+            lr.shortcut_is_dz = shares_dz(i);
+            continue;
+        }
+        if (!(l.flags & (LPM_RELU | LPM_SCALE))) continue;
         int n_src = 0, n_other = 0, n_add = 0;
         int32_t consumer = -1, first_add = last;
         for (int32_t j = i + 1; j < last; ++j) {
@@ -151,10 +173,17 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
             // Residual blocks.  The layer adds a shortcut, and / or later layers use its output as their shortcut: the
             // single layer that reads it as its input comes first in layer order, so its data gradient is the last
             // contribution in the backward pass, and an MFMA data gradient can add the earlier ones, mask, and write
-            // both this layer's dz and the shortcut's gradient.
+            // both this layer's dz and the shortcut's gradient.  The global average pooling behind the last block masks, too,
+            // where nothing is to be added and the shortcut shares the dz.
             const lpm_layer& c = s->net[(size_t)consumer];
+            if (c.kind == LPM_GAP && n_add == 0 && shares_dz(i)) {
+                lr.shortcut_is_dz = true;
+                lr.fused_in = true;
+                continue;
+            }
             if (!has_weights(c) || first_add < consumer || !dgrad_has_side(dtype, s->Ly(consumer).g)) continue;
             lr.fused_side = true;
+            lr.shortcut_is_dz = shares_dz(i);
         }
         lr.fused_in = true;
     }
@@ -173,21 +202,23 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
             if (s->net[(size_t)j].src == i) ++n_src;
             if (s->net[(size_t)j].add_src == i) { ++n_add; user = j; }
         }
-        if (n_src != 0 || n_add != 1 || !s->Ly(user).fused_side) continue;
+        if (n_src != 0 || n_add != 1 || !s->Ly(user).fused_side || s->Ly(user).shortcut_is_dz) continue;
         lr.fused_in = true;
         lr.via_shortcut = true;
     }
-    // An identity shortcut's gradient is the masked gradient of the block's output.  Where the block's last layer keeps its dz free
-    // of a scale that is the same tensor as this dz; when the shortcut's only other use of it is as the earlier contribution that
-    // the data gradient of the block before adds in, that kernel reads it there (R50 conv4_x at 512: a sixth of the traffic of
-    // the kernel that wrote both).
-    for (int32_t i = first; i < last; ++i) {
-        LayerRt& lr = s->Ly(i);
-        const int32_t a = lr.d.add_src;
-        if (!lr.fused_side || a == LPM_NONE || a < first || !s->Ly(a).fused_side || ((lr.d.flags & LPM_SCALE) && !lr.dz_unscaled)) continue;
-        int n_add = 0;
-        for (int32_t j = a + 1; j < last; ++j) n_add += s->net[(size_t)j].add_src == a;
-        lr.shortcut_is_dz = n_add == 1;
+    // The last contribution to the gradient of the stage's input, in the order of the backward pass: the first layer that reads
+    // the input.  It can apply the ReLU mask of the tensor if it reads it as its source with a kernel that adds what is
+    // there before it masks (max-pooling masks its own contribution only).
+    if (first > 0) {
+        int n_src, n_add;
+        uses(first - 1, n_src, n_add);
+        for (int32_t j = first; j < last; ++j) {
+            const lpm_layer& l = s->net[(size_t)j];
+            if (l.src != first - 1 && l.add_src != first - 1) continue;
+            const bool adds = l.kind == LPM_CONV || l.kind == LPM_FC || l.kind == LPM_GAP;
+            if (l.src == first - 1 && l.add_src != first - 1 && (adds || (l.kind == LPM_MAXPOOL2 && n_src + n_add == 1))) s->mask_layer = j;
+            break;
+        }
     }
     // Pooling-backward fusion: a 2x2 max-pooling (even input extent) whose output feeds exactly one layer, a
     // convolution whose data gradient runs on the stride-1 MFMA kernel: that kernel routes its result to the
@@ -505,7 +536,9 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
         for (int32_t k = i - 1; k >= first; --k) {
             const LayerRt& q = s->Ly(k);
             if (has_weights(q.d)) {
-                if (!q.fused_in) return nullptr;
+                // (a layer without ReLU, scale or shortcut of its own launches nothing ahead of its weight gradient either)
+                const bool plain = !(q.d.flags & LPM_RELU) && (!(q.d.flags & LPM_SCALE) || q.dz_unscaled) && q.d.add_src == LPM_NONE;
+                if (!q.fused_in && !plain) return nullptr;
                 if (points) return layer_ev(k);
                 return k == first && q.d.src < first && !dx ? data_done : nullptr;
             }
@@ -589,6 +622,10 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                     // written by the consumer's backward kernel; or the next stage applied this layer's ReLU mask to what it handed down
                     dz = lr.fused_in ? (const void*)(gw + lr.dz_off) : g;
                     if (dbias && !bias_in_wgrad) bias_g = dz;
+                    if (!lr.fused_in && lr.shortcut_is_dz) {
+                        G[gi(l.add_src)] = const_cast<void*>(dz);      // (only read from here on)
+                        have[gi(l.add_src)] = 1;
+                    }
                 } else {
                     void* gadd = nullptr;
                     int gadd_acc = 0;
@@ -597,7 +634,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                         gadd_acc = have[gi(l.add_src)];
                         have[gi(l.add_src)] = 1;
                     }
-                    const bool need_dz = relu || sc;
+                    const bool need_dz = relu || (sc && !lr.dz_unscaled);
                     if (!need_dz && !gadd && dbias && !bias_in_wgrad) {
                         bias_g = g;
                     } else if (need_dz || gadd || (dbias && !bias_in_wgrad)) {
@@ -635,7 +672,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                             unpool.accumulate = 0;
                             unpool.mask = (pr.d.flags & LPM_RELU) != 0;
                             unpool.mscale = (pr.s_off != NO && !pr.dz_unscaled) ? params + pr.s_off : nullptr;
-                        } else if (q == first - 1 && (boundary & LPM_MASK_DX)) {
+                        } else if (q == first - 1 && p == s->mask_layer && (boundary & LPM_MASK_DX)) {
                             unpool.mask = 1;
                         }
                         have[gi(q)] = 1;
@@ -655,12 +692,12 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                             use_side = true;
                             side.earlier = have[gi(l.src)] ? G[gi(l.src)] : nullptr;
                             const int32_t a = pr.d.add_src;
-                            if (a != LPM_NONE && a >= first && s->Ly(a).via_shortcut) {
+                            if (pr.shortcut_is_dz) {
+                                G[gi(a)] = gsrc;
+                                have[gi(a)] = 1;
+                            } else if (a != LPM_NONE && a >= first && s->Ly(a).via_shortcut) {
                                 side.shortcut = gw + s->Ly(a).dz_off;           // the projection's dz
                                 side.shortcut_scale = s->Ly(a).dz_unscaled ? nullptr : params + s->Ly(a).s_off;
-                                have[gi(a)] = 1;
-                            } else if (pr.shortcut_is_dz) {
-                                G[gi(a)] = gsrc;
                                 have[gi(a)] = 1;
                             } else if (a != LPM_NONE && (a >= first || dx != nullptr)) {
                                 side.shortcut = G[gi(a)];
@@ -671,7 +708,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                     } else {
                         gsrc = G[gi(l.src)];
                         gsrc_acc = have[gi(l.src)];
-                        if (l.src == first - 1 && (boundary & LPM_MASK_DX)) gmask = x;      // ReLU backward of the previous stage's last layer
+                        if (i == s->mask_layer && (boundary & LPM_MASK_DX)) gmask = x;      // ReLU backward of the previous stage's last layer
                     }
                     have[gi(l.src)] = 1;
                 }
@@ -725,7 +762,11 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                         gsrc_acc = 0;
                         gmask = (pr.d.flags & LPM_RELU) ? tptr(s, l.src, x, y, stash) : nullptr;
                         gmscale = (pr.s_off != NO && !pr.dz_unscaled) ? params + pr.s_off : nullptr;
-                    } else if (l.src == first - 1 && (boundary & LPM_MASK_DX)) {
+                        if (pr.shortcut_is_dz) {
+                            G[gi(pr.d.add_src)] = gsrc;
+                            have[gi(pr.d.add_src)] = 1;
+                        }
+                    } else if (i == s->mask_layer && (boundary & LPM_MASK_DX)) {
                         gmask = x;
                     }
                     const hipEvent_t ev = point_after(i);
@@ -797,25 +838,15 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
     return LPM_OK;
 }
 
-bool lpm_stage_can_mask_dx(const lpm_stage* s) {
-    if (!s || s->first == 0) return false;
-    int n = 0;
-    for (int32_t i = s->first; i < s->last; ++i) {
-        const lpm_layer& l = s->net[(size_t)i];
-        if (l.add_src == s->first - 1) return false;
-        if (l.src != s->first - 1) continue;
-        if (l.kind != LPM_CONV && l.kind != LPM_FC && l.kind != LPM_MAXPOOL2 && l.kind != LPM_GAP) return false;
-        ++n;
-    }
-    return n == 1;
-}
+bool lpm_stage_can_mask_dx(const lpm_stage* s) { return s && s->mask_layer >= 0; }
 
 bool lpm_stage_takes_dz(const lpm_stage* s) {
     if (!s || s->loss) return false;
     const int32_t i = s->t_out;
     if (i != s->last - 1) return false;
-    const lpm_layer& l = s->Ly(i).d;
-    return has_weights(l) && (l.flags & LPM_RELU) && !(l.flags & LPM_SCALE) && l.add_src == LPM_NONE;
+    const LayerRt& lr = s->Ly(i);
+    const lpm_layer& l = lr.d;
+    return has_weights(l) && (l.flags & LPM_RELU) && (!(l.flags & LPM_SCALE) || lr.dz_unscaled) && (l.add_src == LPM_NONE || lr.shortcut_is_dz);
 }
 
 extern "C" int32_t lpm_stage_update(lpm_stage* s, float* params, void* lowp, float* grads, float* momentum,

@@ -32,8 +32,8 @@ struct LayerRt {
                                                  // layer's output gradient and writes the gradient of this layer's shortcut (DgradSide)
     bool via_shortcut = false;                   // fused_in: a scale-only layer read as a shortcut by one fused_side layer; the kernel that
                                                  // writes that layer's shortcut gradient writes this layer's dz instead
-    bool shortcut_is_dz = false;                 // fused_side: its shortcut's gradient is this layer's dz, element for element, and is read
-                                                 // once, as a DgradSide's earlier contribution: it is not stored a second time
+    bool shortcut_is_dz = false;                 // its shortcut's gradient is this layer's dz, element for element, and is only read: it is not
+                                                 // stored a second time (fused_in, or the stage's last layer when the next stage hands down its dz)
     int32_t pool_fwd = -1;                       // conv/FC: index of the max-pooling layer whose forward its own forward kernel performs
     bool pooled_fwd = false;                     // max-pooling: its forward runs inside its producer's forward kernel
     bool unpooled = false;                       // max-pooling: its backward runs inside its consumer's data gradient
@@ -58,6 +58,7 @@ struct lpm_stage {
     size_t n_trainable = 0, n_params = 0;   // floats
     size_t lowp_bytes = 0, stash_bytes = 0, fwd_ws = 0, bwd_ws = 0;
     size_t dlogits_off = lpm::NO, kws_off = lpm::NO, wws_off = lpm::NO;   // stash / bwd-scratch offsets
+    int32_t mask_layer = -1;          // the layer that applies the ReLU mask of the stage's input to its gradient (LPM_MASK_DX), -1: none can
     bool fwd_counts = false, bwd_counts = false;      // some layer of the pass splits its reduction (LPM_COUNT_BYTES at the head of the scratch)
     size_t gws_bytes = 0;             // size of one copy of the gradient / dz area at the head of the backward scratch
     // Weight gradients are off the critical path of B (nothing in the same pass reads them), so they run on
@@ -91,8 +92,8 @@ int32_t lpm_stage_forward_on(lpm_stage* s, const void* x, void* y, const int32_t
 // per cut and micro-batch.  LPM_MASK_DX: this stage masks its dx; LPM_DY_IS_DZ: the gradient this stage receives
 // already is the pre-activation gradient of its last layer.  Both sides must agree (see the two predicates).
 enum { LPM_MASK_DX = 1, LPM_DY_IS_DZ = 2 };
-bool lpm_stage_can_mask_dx(const lpm_stage* s);        // its input tensor has exactly one consumer, a layer whose backward kernel can mask
-bool lpm_stage_takes_dz(const lpm_stage* s);           // its last layer is conv/FC + ReLU (no scale, no shortcut), bias gradient from the weight-gradient kernel
+bool lpm_stage_can_mask_dx(const lpm_stage* s);        // the last contribution to its input's gradient comes from a layer whose backward kernel can mask
+bool lpm_stage_takes_dz(const lpm_stage* s);           // its last layer is conv/FC + ReLU with a dz free of scale, and no shortcut or one that can share the dz
 enum { LPM_PHASE_DATA = 1, LPM_PHASE_WEIGHTS = 2 };
 
 // U_z reading one weight version and writing another (see stage.cpp).
