@@ -334,6 +334,8 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
     typedef Epilogue<E, MI, NI, MODE> Ep;
     Ep ep;
     const int er0 = m0 + wm * WTM, ec0 = n0 + wn * WTN;
+    constexpr bool SPLITS = BM == 64 && BN == 64;      // (the plan splits no other tile)
+    static_assert(!SPLITS || Ep::R <= EARLY_ROWS, "a split tile loads its operands here or with the partial sums");
     const bool early = Ep::R <= EARLY_ROWS && p.splits == 1;
     if (early) ep.load(p, er0, ec0, rows, lane, Hc, Wc, ph, pw, Dc, pd);
     if (nk > 0) {
@@ -373,7 +375,7 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
     }
     __syncthreads();                            // the stages are dead: the epilogue takes them
 
-    if (p.splits > 1) {
+    if constexpr (SPLITS) if (p.splits > 1) {
         // Every block of an output tile stores its partial sums (in accumulator order, 16 bytes per lane), and the one that
         // arrives last adds them in split order and carries on with the epilogue.  Stores and loads of the partials bypass the
         // XCD's own L2 (scope "agent"), so no cache is written back or invalidated: a store counted as done has reached memory.
@@ -399,38 +401,36 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
         if (*flag != p.splits - 1) return;
         __syncthreads();                        // (flag is read before the area is written again)
         if (tid == 0) __hip_atomic_store(p.count + tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // four splits' loads (and the epilogue's operands) before the first add (eight: 60 registers more, no faster)
+        static_assert(MI == 1 && NI == 1, "one accumulator tile per wavefront");
+        f32x16 sum;
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
+        for (int i = 0; i < 16; ++i) sum[i] = 0.f;
+        for (int s0 = 0; s0 < p.splits; s0 += 4) {
+            u4 v[4][4];
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni) {
-                f32x16 sum;
+            for (int k = 0; k < 4; ++k)
+                if (s0 + k < p.splits) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) sum[i] = 0.f;
-                for (int s0 = 0; s0 < p.splits; s0 += 4) {      // four splits' loads before the first add
-                    u4 v[4][4];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        if (s0 + k < p.splits) {
-#pragma unroll
-                            for (int q = 0; q < 4; ++q)
-                                v[k][q] = __builtin_amdgcn_raw_buffer_load_b128(rp, mine + (unsigned)(((mi * NI + ni) * 4 + q) * 1024), (unsigned)((s0 + k) * BM * BN * 4), AUX_AGENT);
-                        }
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        if (s0 + k < p.splits) {
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) {
-                                sum[4 * q] += __uint_as_float(v[k][q].x); sum[4 * q + 1] += __uint_as_float(v[k][q].y);
-                                sum[4 * q + 2] += __uint_as_float(v[k][q].z); sum[4 * q + 3] += __uint_as_float(v[k][q].w);
-                            }
-                        }
+                    for (int q = 0; q < 4; ++q)
+                        v[k][q] = __builtin_amdgcn_raw_buffer_load_b128(rp, mine + (unsigned)(q * 1024), (unsigned)((s0 + k) * BM * BN * 4), AUX_AGENT);
                 }
-                acc[mi][ni] = sum;
-            }
+            if (s0 == 0) ep.load(p, er0, ec0, rows, lane, Hc, Wc, ph, pw, Dc, pd);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (s0 + k < p.splits) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        sum[4 * q] += __uint_as_float(v[k][q].x); sum[4 * q + 1] += __uint_as_float(v[k][q].y);
+                        sum[4 * q + 2] += __uint_as_float(v[k][q].z); sum[4 * q + 3] += __uint_as_float(v[k][q].w);
+                    }
+                }
+        }
+        acc[0][0] = sum;
     }
 
     // the wavefront's private staging area for the epilogue
-    if (!early) ep.load(p, er0, ec0, rows, lane, Hc, Wc, ph, pw, Dc, pd);
+    if (!SPLITS && !early) ep.load(p, er0, ec0, rows, lane, Hc, Wc, ph, pw, Dc, pd);
     float* area = reinterpret_cast<float*>(lds) + wave * MI * Ep::PIECE;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -473,10 +473,13 @@ static IgemmPlan plan_igemm(int es, int64_t M, int N, int kt) {
     }
     pl.kt_total = std::max(1, kt);
     pl.tiles = tiles_of(pl.tile, M, N);
-    // about 8 K tiles per block while the tiles alone leave CUs idle: every split costs a pass over partial tiles
-    int s = std::max(1, (pl.kt_total + 4) / 8);
+    // A dozen K tiles per block (float, whose products take eight times as long: eight) while the tiles alone leave CUs idle: an
+    // exchange of partial tiles costs 3 us, as long as a block's loads of ten K tiles take.  Measured with 8 / 12 / 16 per block,
+    // in us: 16 x 8^2 x 256 channels, 3x3 10.4 / 9.8 / 10.3, 16 x 4^2 x 512 11.8 / 10.4 / 10.6, 16 x 16^2 x 128 (18 K tiles) 9.3 in two
+    // parts, 7.3 in one.
+    int s = std::max(1, es == 2 ? pl.kt_total / 12 : (pl.kt_total + 4) / 8);
     const int64_t cap = (M <= 64 ? 1024 : 320) / pl.tiles;
-    s = (int)std::min<int64_t>(s, std::max<int64_t>(1, cap));
+    s = pl.tile == TILE_64 ? (int)std::min<int64_t>(s, std::max<int64_t>(1, cap)) : 1;
     pl.splits = std::max(1, std::min(s, pl.kt_total));
     pl.kt_per = (pl.kt_total + pl.splits - 1) / pl.splits;
     pl.splits = (pl.kt_total + pl.kt_per - 1) / pl.kt_per;
@@ -569,6 +572,7 @@ static hipError_t run_igemm(int dtype, int mode, IgemmArgs a, IgemmPlan pl, void
     const int64_t mt = a.tiles_m ? a.tiles_m : (a.M + TILE_M[pl.tile] - 1) / TILE_M[pl.tile];
     const int64_t tiles = mt * ((a.N + TILE_N[pl.tile] - 1) / TILE_N[pl.tile]);
     if (pl.splits > 1) {
+        if (pl.tile != TILE_64) return hipErrorInvalidValue;      // (nor does this happen)
         a.count = (unsigned*)ws;
         a.part = (float*)((char*)ws + LPM_COUNT_BYTES);
         if (tiles > (int64_t)(LPM_COUNT_BYTES / 4) || tiles > pl.tiles) return hipErrorInvalidValue;      // (the plan's cap keeps this out)
