@@ -554,6 +554,10 @@ static hipError_t go_tile(const IgemmPlan& pl, const IgemmArgs& a, int64_t tiles
         if (pl.tile == TILE_128) return go<E, 128, 128, 2, 2, 2, MODE, UNI, BT, 2>(a, tiles, st);
         if (pl.tile == TILE_128_8W) return go<E, 128, 128, 2, 4, 3, MODE, UNI, BT, 2>(a, tiles, st);
     }
+    // About one block per CU: nothing but its own loads in flight keeps the memory path busy, four stages (R50 conv4_x at 64 1.81 ->
+    // 1.77 ms per step).  More blocks: three, so that three of them, or other streams' kernels, share a CU (VGG-16/224 6.83 against
+    // 6.95 ms with four).
+    if (tiles * a.splits <= 320) return go<E, 64, 64, 2, 2, 4, MODE, UNI, BT, 2>(a, tiles, st);
     return go<E, 64, 64, 2, 2, 3, MODE, UNI, BT, 2>(a, tiles, st);
 }
 template <typename E, int MODE, int BT>
