@@ -43,19 +43,4 @@ __device__ __forceinline__ void load_to_lds16s(u32x4_ rs, const unsigned char* d
                  : "memory");
 }
 
-// wait until at most min(rem, MAXT) * LPT of this wavefront's loads are outstanding (the count is an immediate)
-template <int LPT, int MAXT>
-__device__ __forceinline__ void wait_tiles_behind(int rem) {
-    static_assert(MAXT >= 0 && MAXT <= 6 && MAXT * LPT < 64, "six cases, 6-bit counter");
-    if (rem >= MAXT) { LPM_WAIT_VM(MAXT * LPT); return; }
-    switch (rem) {
-        case 0: LPM_WAIT_VM(0); break;
-        case 1: LPM_WAIT_VM(1 * LPT); break;
-        case 2: LPM_WAIT_VM(2 * LPT); break;
-        case 3: LPM_WAIT_VM(3 * LPT); break;
-        case 4: LPM_WAIT_VM(4 * LPT); break;
-        default: LPM_WAIT_VM(5 * LPT); break;
-    }
-}
-
 }  // namespace lpm

@@ -559,7 +559,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
             if (e != hipSuccess) return e;
         }
         if (fc_slot >= 0 && lr.fcs_x_off != NO) {
-            if (d) d->splits = 0;
+            d->splits = 0;
             hipError_t e = stage_operands(lr.g, j.xin, j.dz, ws + lr.fcs_x_off, ws + lr.fcs_dz_off, fc_slot, q);
             if (e != hipSuccess) return e;
             // Contract in groups of G micro-batches.  One group (G = M) touches dW once, but all of that work then sits
@@ -725,7 +725,9 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                     LPM_HIP(frontier(before));
                     if (!wtail.empty())       // weight gradients share one scratch area: keep them in a chain
                         LPM_HIP(hipStreamUpdateCaptureDependencies(st, wtail.data(), wtail.size(), hipStreamAddCaptureDependencies));
-                    LPM_HIP(one_wgrad(WgradJob{&lr, xin, dz, wdb, lr.dz_unscaled ? sc : nullptr, bias_g, bias_g ? dbias : nullptr}, st, nullptr));
+                    ReduceDesc d{};           // (the same kernels and sums as an eager pass, a reduction per layer)
+                    LPM_HIP(one_wgrad(WgradJob{&lr, xin, dz, wdb, lr.dz_unscaled ? sc : nullptr, bias_g, bias_g ? dbias : nullptr}, st, &d));
+                    if (d.splits > 0) LPM_HIP(launch_reduce_batch(&d, 1, st));
                     LPM_HIP(frontier(wtail));
                     LPM_HIP(hipStreamUpdateCaptureDependencies(st, before.data(), before.size(), hipStreamSetCaptureDependencies));
                 }

@@ -435,7 +435,8 @@ __global__ void __launch_bounds__(512, 1) wgrad_mm(WgArgs p) {
 // --------------------------------------------------------------------------------------------------
 struct WgPlan { int taps, big, groups, co_tiles, ci_tiles, TW, kt_total, kt_per, splits; };
 
-static WgPlan plan_wgrad(int dtype, const ConvGeom& g) {
+// shared: the launch runs beside other streams' kernels (a backward pass, whose reductions are batched)
+static WgPlan plan_wgrad(int dtype, const ConvGeom& g, bool shared) {
     WgPlan pl{};
     const int tx = (g.Wo + 7) / 8;
     // a filter row per block where the row segments are mostly real pixels
@@ -452,8 +453,13 @@ static WgPlan plan_wgrad(int dtype, const ConvGeom& g) {
     pl.ci_tiles = (g.Cin + t - 1) / t;
     const int64_t base = (int64_t)pl.co_tiles * pl.ci_tiles * pl.groups;
     const int64_t out_bytes = ((int64_t)g.Cout * g.K() + g.Cout) * 4;
-    int64_t sp = std::max<int64_t>(1, 256 / base);
-    if (base * sp < 192) sp = std::max<int64_t>(sp, 448 / base);
+    // A block per CU when the launch has the card to itself.  Beside the forward and data-phase kernels the CUs it leaves are not
+    // idle, and every block writes partial sums that the reduction reads: 192 blocks, 128 of the four times larger tiles.  Per
+    // step with 256 / 192 / 128 for both, in us: ResNet-18/CIFAR 3440 / 3360 / 3304, VGG-16/224 6850 / 6805 / 6918, volumetric 1758 / 1764 /
+    // 1798; 128-channel tiles alone at 128: R50 conv4_x at 512 7240 -> 7066.
+    const int64_t want = shared ? (pl.big ? 128 : 192) : 256;
+    int64_t sp = std::max<int64_t>(1, want / base);
+    if (base * sp < want * 3 / 4) sp = std::max<int64_t>(sp, want * 7 / 4 / base);
     // at least eight K tiles per block, four where that leaves fewer than eight ranges: every range costs a pass over dW
     sp = std::min<int64_t>(sp, std::max(std::max(1, pl.kt_total / 8), std::min(8, pl.kt_total / 4)));
     sp = std::min<int64_t>(sp, std::max<int64_t>(1, (64ll << 20) / out_bytes));
@@ -472,8 +478,8 @@ bool wgrad_mm_ok(int dtype, const ConvGeom& g) {
 
 static size_t wg_stride(const ConvGeom& g) { return ((size_t)g.Cout * g.K() + g.Cout + 3) & ~(size_t)3; }      // (16-byte loads in the reduction)
 size_t wgrad_mm_ws_bytes(int dtype, const ConvGeom& g) {
-    const WgPlan pl = plan_wgrad(dtype, g);
-    return pl.splits > 1 ? (size_t)pl.splits * wg_stride(g) * sizeof(float) : 0;
+    const int splits = std::max(plan_wgrad(dtype, g, false).splits, plan_wgrad(dtype, g, true).splits);
+    return splits > 1 ? (size_t)splits * wg_stride(g) * sizeof(float) : 0;
 }
 
 template <typename E, int BM, int BN, int KIND, int NST>
@@ -489,7 +495,7 @@ static hipError_t go(const WgArgs& a, const WgPlan& pl, hipStream_t st) {
 hipError_t wgrad_mm_launch(int dtype, const ConvGeom& g, const void* x, const void* dz, float* dw, float* dbias, const float* rscale,
                            int accumulate, void* ws, hipStream_t st, ReduceDesc* deferred) {
     const int es = dtype == LPM_BF16 ? 2 : 4;
-    const WgPlan pl = plan_wgrad(dtype, g);
+    const WgPlan pl = plan_wgrad(dtype, g, deferred != nullptr);
     WgArgs a{};
     a.X = x; a.DZ = dz;
     a.out = pl.splits > 1 ? (float*)ws : dw;

@@ -37,6 +37,8 @@ BF16 = [
     G(1, 20, 15, 64, 64, 3, 1, 1),        # filter rows over segments of 8 pixels, the last one 7 wide
     G(1, 20, 13, 72, 40, 3, 1, 1),        # ... 5 wide: single taps
     G3(1, 3, 6, 8, 64, 64, 3, 1, 1),      # ... volume
+    G(2, 80, 80, 64, 64, 5, 1, 2),        # single taps, ranges of 20 K tiles: the pixel records in several rounds
+    G(5, 64, 64, 256, 256, 3, 1, 1),      # filter rows, ranges of 64 K tiles: records in several rounds, four stages
 ]
 
 
