@@ -465,11 +465,14 @@ static IgemmPlan plan_igemm(int es, int64_t M, int N, int kt) {
         // Measured alone on MI355X (us, 64x64 / 128x64 / 128x128 / 128x128 of 8 wavefronts):
         //   25088 x 256, K 2304: 51 / 46 / 39 / 43     12544 x 256, K 2304: 31 / 25 / 25 / 22      6272 x 512, K 2304: 33 / 25 / 27 / 24
         //    3136 x 512, K 4608: 26 / 29 / 47 / 34      3136 x 256, K 2304: 13 / 17 / 24 / 21     17496 x 160, K  864: 19 / 15 / 21 / 26
+        // Alone, 64x64 wins up to some 384 tiles of 128x64.  Beside the other streams of a step, where the operand traffic of all of them
+        // adds up, the larger tile wins from 180 on (per step, line at 384 / 250 / 180 / 120 / 90, in us: ResNet-18/CIFAR 3361 / 3312 /
+        // 3308 / 3366 / 3371, VGG-16/224 6828 / 6833 / 6772 / 6778 / 6760, R50 conv4_x at 64 1746 / 1752 / 1749 / 1750 / 1870).
         const bool wide = N % 128 == 0 || N % 128 > 64;
         const int64_t n128 = tiles_of(TILE_128, M, N);
         if (wide && n128 >= 384) pl.tile = TILE_128;
         else if (wide && n128 >= 180) pl.tile = TILE_128_8W;
-        else if (tiles_of(TILE_128x64, M, N) >= 384) pl.tile = TILE_128x64;
+        else if (tiles_of(TILE_128x64, M, N) >= 180) pl.tile = TILE_128x64;
     }
     pl.kt_total = std::max(1, kt);
     pl.tiles = tiles_of(pl.tile, M, N);
@@ -477,8 +480,10 @@ static IgemmPlan plan_igemm(int es, int64_t M, int N, int kt) {
     // exchange of partial tiles costs 3 us, as long as a block's loads of ten K tiles take.  Measured with 8 / 12 / 16 per block,
     // in us: 16 x 8^2 x 256 channels, 3x3 10.4 / 9.8 / 10.3, 16 x 4^2 x 512 11.8 / 10.4 / 10.6, 16 x 16^2 x 128 (18 K tiles) 9.3 in two
     // parts, 7.3 in one.
+    // No more than a block per CU: a second one on some of them delays the exchange (ResNet-18/CIFAR 3308 us per step with up to 320
+    // blocks, 3275 with 256, 3315 with 224).
     int s = std::max(1, es == 2 ? pl.kt_total / 12 : (pl.kt_total + 4) / 8);
-    const int64_t cap = (M <= 64 ? 1024 : 320) / pl.tiles;
+    const int64_t cap = (M <= 64 ? 1024 : 256) / pl.tiles;
     s = pl.tile == TILE_64 ? (int)std::min<int64_t>(s, std::max<int64_t>(1, cap)) : 1;
     pl.splits = std::max(1, std::min(s, pl.kt_total));
     pl.kt_per = (pl.kt_total + pl.splits - 1) / pl.splits;
