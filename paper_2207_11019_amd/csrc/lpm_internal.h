@@ -176,11 +176,15 @@ size_t attn_bwd_ws_bytes(int32_t m, int32_t P);
 bool attn_ok(int32_t P, int32_t C);
 hipError_t launch_softmax_ce(int dtype, int32_t m, int32_t C, const void* logits, const int32_t* labels,
                              float loss_scale, void* dlogits, float* loss_accum, hipStream_t st);
-// v = mu*v + g; p = p_in - lr*v (p_in may be p); lowp[i] = bf16(p[i]) (lowp may be NULL); optionally g = 0.   n % 4 == 0
-hipError_t launch_sgd(const float* p_in, float* p, uint16_t* lowp, float* g, float* v, size_t n, float lr, float mu, int zero_g,
-                      hipStream_t st);
-hipError_t launch_adam(float* p, uint16_t* lowp, float* g, float* m1, float* m2, size_t n, float lr, float beta1, float beta2,
-                       float eps, float inv_c1, float inv_c2, int zero_g, hipStream_t st);
+// One piece of a stage's parameters to update: n floats from off on, or -- wt not NULL -- a weight tensor [Cout][KK][Cin] at off
+// (Cin % 4 == 0, Cout % 4 == 0) of which wt[ci][k][co] = bf16(new[co][k][ci] * scale[co]) is stored too (scale may be NULL).
+struct UpdateSeg { size_t off, n; uint16_t* wt; const float* scale; int32_t Cout, KK, Cin; };
+constexpr int LPM_UPDATE_BATCH = 48;         // segments of one launch
+// v = mu*v + g; p = p_in - lr*v (p_in may be p); lowp[i] = bf16(p[i]) (lowp may be NULL); optionally g = 0.   off, n % 4 == 0
+hipError_t launch_sgd(const UpdateSeg* d, int count, const float* p_in, float* p, uint16_t* lowp, float* g, float* v, float lr, float mu,
+                      int zero_g, hipStream_t st);
+hipError_t launch_adam(const UpdateSeg* d, int count, float* p, uint16_t* lowp, float* g, float* m1, float* m2, float lr, float beta1,
+                       float beta2, float eps, float inv_c1, float inv_c2, int zero_g, hipStream_t st);
 hipError_t launch_f32_to_bf16(const float* src, uint16_t* dst, size_t n, hipStream_t st);
 // dst[ci][kh][kw][co] = bf16(src[co][kh][kw][ci] * scale[co]) for a list of weight tensors (scale may be NULL), one launch per
 // LPM_TRANSPOSE_BATCH of them

@@ -369,16 +369,36 @@ extern "C" int32_t lpm_stage_grad_offset(const lpm_stage* s, int32_t t, size_t* 
     return LPM_OK;
 }
 
-// the [Cin][Kh][Kw][Cout] copies of every layer whose data gradient reads one, all in one launch
-static hipError_t transpose_copies(const lpm_stage* s, const float* params, void* lowp, hipStream_t st) {
+// the update stores this layer's [Cin][Kh][Kw][Cout] copy itself
+static bool update_transposes(const LayerRt& lr) { return lr.lowp_wt_off != NO && lr.d.cin % 4 == 0 && lr.d.cout % 4 == 0; }
+
+// the [Cin][Kh][Kw][Cout] copies of every layer whose data gradient reads one, all in one launch; behind an update those that
+// it has not stored
+static hipError_t transpose_copies(const lpm_stage* s, const float* params, void* lowp, bool updated, hipStream_t st) {
     std::vector<TransposeDesc> d;
     for (int32_t i = s->first; i < s->last; ++i) {
         const LayerRt& lr = s->Ly(i);
-        if (lr.lowp_wt_off != NO)
+        if (lr.lowp_wt_off != NO && !(updated && update_transposes(lr)))
             d.push_back(TransposeDesc{params + lr.w_off, (uint16_t*)((char*)lowp + lr.lowp_wt_off), lr.d.cout, taps_of(lr.d), lr.d.cin,
                                       lr.dz_unscaled ? params + lr.s_off : nullptr});
     }
     return d.empty() ? hipSuccess : launch_weight_transpose_batch(d.data(), (int)d.size(), st);
+}
+
+// the pieces of the trainable parameters: weights with a transposed copy, and everything between them
+static std::vector<UpdateSeg> update_segments(const lpm_stage* s, const float* params, void* lowp) {
+    std::vector<UpdateSeg> d;
+    size_t at = 0;
+    for (int32_t i = s->first; i < s->last; ++i) {
+        const LayerRt& lr = s->Ly(i);
+        if (!update_transposes(lr)) continue;
+        if (lr.w_off > at) d.push_back(UpdateSeg{at, lr.w_off - at, nullptr, nullptr, 0, 0, 0});
+        d.push_back(UpdateSeg{lr.w_off, lr.w_count, (uint16_t*)((char*)lowp + lr.lowp_wt_off), lr.dz_unscaled ? params + lr.s_off : nullptr,
+                              lr.d.cout, taps_of(lr.d), lr.d.cin});
+        at = lr.w_off + lr.w_count;
+    }
+    if (s->n_trainable > at) d.push_back(UpdateSeg{at, s->n_trainable - at, nullptr, nullptr, 0, 0, 0});
+    return d;
 }
 
 extern "C" int32_t lpm_stage_sync_lowp(lpm_stage* s, const float* params, void* lowp, void* stream) {
@@ -388,7 +408,7 @@ extern "C" int32_t lpm_stage_sync_lowp(lpm_stage* s, const float* params, void* 
     if (misaligned(params) || misaligned(lowp)) return fail(LPM_EALIGN, "buffers must be 256-byte aligned");
     hipStream_t st = (hipStream_t)stream;
     LPM_HIP(launch_f32_to_bf16(params, (uint16_t*)lowp, s->n_trainable, st));
-    LPM_HIP(transpose_copies(s, params, lowp, st));
+    LPM_HIP(transpose_copies(s, params, lowp, false, st));
     return LPM_OK;
 }
 
@@ -866,12 +886,10 @@ int32_t lpm_stage_update_to(lpm_stage* s, const float* params_in, float* params,
         return fail(LPM_EALIGN, "device buffers must be 256-byte aligned");
     hipStream_t st = (hipStream_t)stream;
     if (s->n_trainable == 0) return LPM_OK;
-    if (s->dtype != LPM_BF16) {
-        LPM_HIP(launch_sgd(params_in, params, nullptr, grads, momentum, s->n_trainable, lr_, mu, zero_grads, st));
-        return LPM_OK;
-    }
-    LPM_HIP(launch_sgd(params_in, params, (uint16_t*)lowp, grads, momentum, s->n_trainable, lr_, mu, zero_grads, st));
-    LPM_HIP(transpose_copies(s, params, lowp, st));
+    const std::vector<UpdateSeg> d = update_segments(s, params, lowp);
+    LPM_HIP(launch_sgd(d.data(), (int)d.size(), params_in, params, s->dtype == LPM_BF16 ? (uint16_t*)lowp : nullptr, grads, momentum, lr_, mu,
+                       zero_grads, st));
+    if (s->dtype == LPM_BF16) LPM_HIP(transpose_copies(s, params, lowp, true, st));
     return LPM_OK;
 }
 
@@ -889,8 +907,9 @@ extern "C" int32_t lpm_stage_update_adam(lpm_stage* s, float* params, void* lowp
     const float inv_c1 = (float)(1.0 / (1.0 - std::pow((double)beta1, (double)step)));
     const float inv_c2 = (float)(1.0 / (1.0 - std::pow((double)beta2, (double)step)));
     hipStream_t st = (hipStream_t)stream;
-    LPM_HIP(launch_adam(params, s->dtype == LPM_BF16 ? (uint16_t*)lowp : nullptr, grads, m1, m2, s->n_trainable, lr_, beta1, beta2,
+    const std::vector<UpdateSeg> d = update_segments(s, params, lowp);
+    LPM_HIP(launch_adam(d.data(), (int)d.size(), params, s->dtype == LPM_BF16 ? (uint16_t*)lowp : nullptr, grads, m1, m2, lr_, beta1, beta2,
                         eps, inv_c1, inv_c2, zero_grads, st));
-    if (s->dtype == LPM_BF16) LPM_HIP(transpose_copies(s, params, lowp, st));
+    if (s->dtype == LPM_BF16) LPM_HIP(transpose_copies(s, params, lowp, true, st));
     return LPM_OK;
 }
