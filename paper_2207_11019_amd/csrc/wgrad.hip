@@ -399,8 +399,9 @@ __global__ void __launch_bounds__(512, 1) wgrad_mm(WgArgs p) {
             else p.db[co] = p.accumulate ? p.db[co] + v : v;
         }
     }
-    // stores through a buffer resource: the lane's offset is fixed, an element adds a wave-uniform row offset, and rows past the
-    // last output channel lie past the buffer's end
+    // Stores through a buffer resource: rows past the last output channel lie past the buffer's end.  (The row is part of the
+    // lane's offset: as a wave-uniform offset beside it, 27 rows exceed the buffer of a layer with fewer output channels, and the
+    // bounds check would have to survive a negative length.)
     const unsigned pitch = (unsigned)(KhKw * p.Cin) * 4u;
     const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(out, 0, (unsigned)p.Cout * pitch, 0x00020000);
 #pragma unroll
@@ -411,7 +412,8 @@ __global__ void __launch_bounds__(512, 1) wgrad_mm(WgArgs p) {
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) {
                 const int ci = ci0 + wn * WTN + ni * 32 + rl, cb = co0 + wm * WTM + mi * 32 + rq;
-                const unsigned vo = ci < p.Cin ? (unsigned)cb * pitch + (unsigned)(tap * p.Cin + ci) * 4u : WG_OOB;
+                if (ci >= p.Cin) continue;
+                const unsigned vo = (unsigned)cb * pitch + (unsigned)(tap * p.Cin + ci) * 4u;
                 f32x16 v = acc[t][mi][ni];
                 if (whole && p.rscale) {
 #pragma unroll
@@ -421,13 +423,13 @@ __global__ void __launch_bounds__(512, 1) wgrad_mm(WgArgs p) {
                     float old[16];
 #pragma unroll
                     for (int i = 0; i < 16; ++i)
-                        old[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ro, vo, (unsigned)((i >> 2) * 8 + (i & 3)) * pitch, 0));
+                        old[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ro, vo + (unsigned)((i >> 2) * 8 + (i & 3)) * pitch, 0, 0));
 #pragma unroll
                     for (int i = 0; i < 16; ++i) v[i] += old[i];
                 }
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[i]), ro, vo, (unsigned)((i >> 2) * 8 + (i & 3)) * pitch, 0);
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[i]), ro, vo + (unsigned)((i >> 2) * 8 + (i & 3)) * pitch, 0, 0);
             }
     }
 }

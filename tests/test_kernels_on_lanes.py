@@ -1,0 +1,36 @@
+"""The GPU tests' small cases on the CPU, kernels run lane by lane (tests/lanes): beside the results that those tests compare,
+every access lies in the operand it means, in the LDS of its launch and in the filter's or image's extent, and nothing rests on
+a wait or barrier that is not there."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+TESTS = os.path.dirname(os.path.abspath(__file__))
+LANES = os.path.join(TESTS, "lanes")
+sys.path.insert(0, LANES)
+import lanes_build  # noqa: E402
+
+
+@pytest.fixture(scope="session")
+def lanes(tmp_path_factory):
+    return lanes_build.build(str(tmp_path_factory.mktemp("lanes")))
+
+
+RUNS = [
+    # loads land late, and in descending order of wavefronts and blocks, or early and ascending; file; selection
+    (0, "test_gpu_contractions.py", "not m5_64x64 and not m3_1 and not m2_80"),
+    (1, "test_gpu_contractions.py", "bf16_m1 or f32_m1 or f32_m2 or 3_4x4 or m2_4x4"),
+    (1, "test_gpu_conv.py", "not 64x64 and not 57x59 and not 60x60 and not 32x32x64 and not d6k3_16 and not 15x15x512"),
+    (0, "test_gpu_update.py", ""),
+]
+
+
+@pytest.mark.parametrize("late,name,select", RUNS, ids=["%s-%s" % (r[1][9:-3], "late" if r[0] else "early") for r in RUNS])
+def test_gpu_tests_on_lanes(lanes, late, name, select):
+    env = dict(os.environ, LPM_LANES=lanes, LPM_LANES_LATE=str(late), PYTHONPATH=os.pathsep.join([LANES, os.environ.get("PYTHONPATH", "")]))
+    cmd = [sys.executable, "-m", "pytest", "-p", "lanes_plugin", "-p", "no:cacheprovider", "-q", "-m", "gpu", os.path.join(TESTS, name)]
+    r = subprocess.run(cmd + (["-k", select] if select else []), env=env, cwd=os.path.dirname(TESTS), capture_output=True, text=True, timeout=900)
+    assert r.returncode == 0, r.stdout[-6000:] + r.stderr[-3000:]
+    assert " passed" in r.stdout and " failed" not in r.stdout
