@@ -622,7 +622,7 @@ hipError_t mfma_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void
 hipError_t mfma_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const void* wt, void* dx, int accumulate, const void* mask,
                            const float* mscale, void* ws, bool ws_zeroed, hipStream_t st, const UnpoolDesc* unpool, const DgradSide* side, const float* kscale) {
     if (kscale && (dtype == LPM_BF16 || g.Cout > MAX_KSCALE)) return hipErrorInvalidValue;      // (bf16: the transposed copy carries the scale)
-    if (unpool && (side || dtype != LPM_BF16 || g.stride != 1)) return hipErrorInvalidValue;
+    if (unpool && (side || dtype != LPM_BF16 || g.stride != 1 || g.Cin % 8)) return hipErrorInvalidValue;      // (the epilogue routes whole chunks of eight channels)
     const int es = dtype == LPM_BF16 ? 2 : 4;
     IgemmArgs a{};
     a.A = dz; a.B = wt; a.C = dx;
