@@ -495,11 +495,12 @@ static size_t plan_ws(const IgemmPlan& pl) {
     return pl.splits > 1 ? LPM_COUNT_BYTES + (size_t)pl.tiles * pl.splits * TILE_M[pl.tile] * TILE_N[pl.tile] * sizeof(float) : 0;
 }
 
-// byte offsets below 4 GiB (with the rows of a tile past the last one), 31-bit element counts
-static bool fits(int dtype, const ConvGeom& g) {
+// byte offsets below 4 GiB (with the rows of a tile past the last one, and the bytes that the gathered tensor's buffer begins early:
+// `halo` elements), 31-bit element counts
+static bool fits(int dtype, const ConvGeom& g, int64_t halo_in, int64_t halo_out) {
     const int64_t es = dtype == LPM_BF16 ? 2 : 4, lim = ((int64_t)1 << 32) - 1, e31 = (int64_t)1 << 31;
     const int64_t in = g.rows_in() * g.Cin, out = g.rows_out() * g.Cout;
-    return in < e31 && out < e31 && in * es < lim && out * es < lim &&
+    return in < e31 && out < e31 && (in + halo_in) * es < lim && (out + halo_out) * es < lim &&
            (int64_t)(g.Cout + 256) * g.K() * es < lim && (int64_t)(g.Cin + 256) * g.taps() * g.Cout * es < lim;
 }
 static bool taps_fit(const ConvGeom& g, int ci, int es) {
@@ -509,13 +510,14 @@ static bool fwd_free(const ConvGeom& g) { return g.pad == 0 && g.pad_d == 0; }  
 
 bool mfma_fwd_ok(int dtype, const ConvGeom& g) {
     const int es = dtype == LPM_BF16 ? 2 : 4;
-    if ((g.Cin * es) % 16 || !fits(dtype, g)) return false;
+    if ((g.Cin * es) % 16 || !fits(dtype, g, (((int64_t)g.pad_d * g.H + g.pad) * g.W + g.pad) * g.Cin, 0)) return false;
     return taps_fit(g, g.Cin, es) || (fwd_free(g) && ((g.Cin * es) % 128 == 0 || g.taps() <= MAX_TAB));
 }
 // (a strided data gradient goes by residue classes of the image axes: stride^2 classes, stride^3 for a volume -- at most 16)
 bool mfma_dgrad_ok(int dtype, const ConvGeom& g) {
     const int es = dtype == LPM_BF16 ? 2 : 4;
-    return (g.Cout * es) % 16 == 0 && (dtype == LPM_BF16 || g.Cin % 4 == 0) && g.stride <= 4 && (g.stride <= 2 || !g.is3d()) && fits(dtype, g) && taps_fit(g, g.Cout, es);
+    return (g.Cout * es) % 16 == 0 && (dtype == LPM_BF16 || g.Cin % 4 == 0) && g.stride <= 4 && (g.stride <= 2 || !g.is3d()) &&
+           fits(dtype, g, 0, (((int64_t)(g.Kd - 1) * g.Ho + g.Kh - 1) * g.Wo + g.Kw - 1) * g.Cout) && taps_fit(g, g.Cout, es);
 }
 
 static int k_tiles(int64_t taps, int ci, int es) { return (int)((taps * ci * es / 16 + 7) / 8); }

@@ -73,7 +73,7 @@ def build(out, flags=(), extra=(), exe=None, opt="-O2"):
     cxx = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "clang++")
     common = [cxx, "-x", "c++", "-std=c++17", opt, "-g1", "-fPIC", "-Wno-everything", "-I" + HERE, "-I" + src, *flags]
     procs, objs = [], []
-    for p in [os.path.join(HERE, "lanes.cpp"), *extra] + sorted(glob.glob(os.path.join(src, "*.hip")) + glob.glob(os.path.join(src, "*.cpp"))):
+    for p in [os.path.join(HERE, "lanes.cpp"), os.path.join(HERE, "routes.cpp"), *extra] + sorted(glob.glob(os.path.join(src, "*.hip")) + glob.glob(os.path.join(src, "*.cpp"))):
         o = os.path.join(out, os.path.basename(p) + ".o")
         objs.append(o)
         procs.append(subprocess.Popen(common + ["-c", p, "-o", o], stderr=subprocess.PIPE, text=True))

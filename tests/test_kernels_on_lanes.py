@@ -1,6 +1,7 @@
 """The GPU tests' small cases on the CPU, kernels run lane by lane (tests/lanes): beside the results that those tests compare,
 every access lies in the operand it means, in the LDS of its launch and in the filter's or image's extent, and nothing rests on
 a wait or barrier that is not there."""
+import ctypes
 import os
 import subprocess
 import sys
@@ -35,3 +36,15 @@ def test_gpu_tests_on_lanes(lanes, late, name, select):
     r = subprocess.run(cmd + (["-k", select] if select else []), env=env, cwd=os.path.dirname(TESTS), capture_output=True, text=True, timeout=900)
     assert r.returncode == 0, r.stdout[-6000:] + r.stderr[-3000:]
     assert " passed" in r.stdout and " failed" not in r.stdout
+
+
+@pytest.mark.parametrize("op,h,taken", [(0, 16382, True), (0, 16383, False), (1, 16381, True), (1, 16382, False)],
+                         ids=["forward-in", "forward-out", "dgrad-in", "dgrad-out"])
+def test_buffers_near_4_gib(lanes, op, h, taken):
+    """The gathered tensor's buffer begins a halo early -- one image row and a pixel for the forward pass of a padded 3x3 filter, two of
+    each for its data gradient -- and both together have to stay below 4 GiB: h rows of 16384 pixels of 16 bytes."""
+    import paper_2207_11019_amd as lpm
+    w, halo = 16384, (1 if op == 0 else 2)
+    assert (h * w * 16 + halo * (w + 1) * 16 < (1 << 32) - 1) == taken
+    g = lpm.lpm_conv_geom(1, h, w, 8, 8, 3, 3, 1, 1, 1, 1, 0)
+    assert bool(ctypes.CDLL(lanes).lanes_takes(op, lpm.BF16, ctypes.byref(g))) == taken
