@@ -528,9 +528,13 @@ __global__ void __launch_bounds__(AM_T) attn_bwd_kv_mm(int P, int C, const bf16_
     });
 }
 
-static bool am_ok(int dtype, int C) { return dtype == LPM_BF16 && C % 8 == 0; }      // (P + C <= ATT_LIMIT: at most 148 KB of LDS)
+static bool am_ok(int dtype, int C) { return dtype == LPM_BF16 && C % 8 == 0; }
+// The backward kernels at P + C = ATT_LIMIT, where few channels beside many positions take the most: 149 KB
+constexpr int AM_LDS = 160 * 1024 - 256;
+static_assert(2 * AM_R * ((ATT_LIMIT + 31) / 32 * 32 + 4) * 4 + 2 * AM_R * (128 + 8) * 2 + (int)AM_RED <= AM_LDS &&
+              2 * AM_R * (32 + 4) * 4 + 2 * AM_R * ((ATT_LIMIT + 127) / 128 * 128 + 8) * 2 + (int)AM_RED <= AM_LDS, "the score tiles and staged rows fit");
 template <typename K>
-static hipError_t am_prepare(K kernel) { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256); }
+static hipError_t am_prepare(K kernel, DeviceSet& done) { return allow_lds(kernel, AM_LDS, done); }
 
 // parts of a block that share a channel in att_mix: as many as leave every thread a channel
 static int att_parts(int C) { return C <= 32 ? 8 : C <= 64 ? 4 : C <= 128 ? 2 : 1; }
@@ -545,7 +549,8 @@ static int att_parts(int C) { return C <= 32 ? 8 : C <= 64 ? 4 : C <= 128 ? 2 : 
 hipError_t launch_attn_fwd(int dtype, int32_t m, int32_t P, int32_t C, const void* x, void* y, hipStream_t st) {
     if (!attn_ok(P, C)) return hipErrorInvalidValue;
     if (am_ok(dtype, C)) {
-        static const hipError_t attr = am_prepare(attn_fwd_mm);
+        static DeviceSet done;
+        const hipError_t attr = am_prepare(attn_fwd_mm, done);
         if (attr != hipSuccess) return attr;
         const AmShape s(P, C);
         hipLaunchKernelGGL(attn_fwd_mm, dim3((unsigned)((P + AM_R - 1) / AM_R), (unsigned)m), dim3(AM_T), s.tile_bytes() + s.rows_bytes() + AM_RED, st, P, C,
@@ -564,7 +569,8 @@ hipError_t launch_attn_bwd(int dtype, int32_t m, int32_t P, int32_t C, const voi
                            void* ws, hipStream_t st) {
     if (!attn_ok(P, C) || !ws) return hipErrorInvalidValue;
     if (am_ok(dtype, C)) {
-        static const hipError_t aq = am_prepare(attn_bwd_q_mm), akv = am_prepare(attn_bwd_kv_mm);
+        static DeviceSet done_q, done_kv;
+        const hipError_t aq = am_prepare(attn_bwd_q_mm, done_q), akv = am_prepare(attn_bwd_kv_mm, done_kv);
         if (aq != hipSuccess || akv != hipSuccess) return aq != hipSuccess ? aq : akv;
         const AmShape s(P, C);
         const dim3 grid((unsigned)((P + AM_R - 1) / AM_R), (unsigned)m);

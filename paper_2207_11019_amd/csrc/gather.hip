@@ -374,7 +374,8 @@ static void fill_geom(IgemmArgs& a) {
 
 template <typename E, int NT, int MODE, bool KSPLIT>
 static hipError_t go(const IgemmArgs& a, int ksteps, int tiles, hipStream_t st) {
-    static const hipError_t attr = hipFuncSetAttribute((const void*)gather_gemm<E, NT, MODE, KSPLIT>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+    static DeviceSet done;
+    const hipError_t attr = allow_lds(gather_gemm<E, NT, MODE, KSPLIT>, 80 * 1024, done);
     if (attr != hipSuccess) return attr;
     const int blocks = KSPLIT ? tiles : std::min((tiles + 3) / 4, 1536);
     launch_last(gather_gemm<E, NT, MODE, KSPLIT>, dim3((unsigned)blocks, (unsigned)((a.N + NT * 32 - 1) / (NT * 32))), dim3(256),

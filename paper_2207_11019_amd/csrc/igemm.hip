@@ -547,8 +547,8 @@ template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, bool 
 static hipError_t go(const IgemmArgs& a, int64_t tiles, hipStream_t st) {
     constexpr int stages = NST * (BM + BN) * 128 + (UNI ? 0 : MAX_TAB * 16) + (BT == BT_SCALED ? MAX_KSCALE * 4 : 0);
     constexpr int epilogue = BM * WGN * (BN / WGN + 4) * 4, bytes = stages > epilogue ? stages : epilogue;
-    static const hipError_t attr = hipFuncSetAttribute((const void*)igemm_kernel<E, BM, BN, WGM, WGN, NST, MODE, UNI, BT, OCC>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    static DeviceSet done;
+    const hipError_t attr = allow_lds(igemm_kernel<E, BM, BN, WGM, WGN, NST, MODE, UNI, BT, OCC>, bytes, done);
     if (attr != hipSuccess) return attr;
     launch_last(igemm_kernel<E, BM, BN, WGM, WGN, NST, MODE, UNI, BT, OCC>, dim3((unsigned)tiles, 1, a.splits), dim3(WGM * WGN * 64), bytes, st, a);
     return hipGetLastError();

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
+#include <atomic>
 #include <cstdarg>
 #include <cstddef>
 #include <cstdint>
@@ -47,6 +48,20 @@ private:
     hipEvent_t e_;
     hipStream_t st_;
 };
+// The LDS a kernel may have beyond 64 KB, set before its first launch on a device: the runtime keeps the attribute per device.  `done`
+// belongs to the kernel, a bit per device.
+typedef std::atomic<uint64_t> DeviceSet;
+template <typename K>
+inline hipError_t allow_lds(K kernel, int bytes, DeviceSet& done) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = (unsigned)dev < 64 ? (uint64_t)1 << dev : 0;
+    if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
+    e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+    return e;
+}
 template <typename K, typename... A>
 inline void launch_last(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t st, A... args) {
     if (const hipEvent_t e = take_stop_event()) hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)lds, st, nullptr, e, 0, args...);

@@ -488,7 +488,8 @@ template <typename E, int BM, int BN, int KIND, int NST>
 static hipError_t go(const WgArgs& a, const WgPlan& pl, hipStream_t st) {
     constexpr int ES = sizeof(E), KT = ES == 2 ? 64 : 32, rows = KIND == ROW3 ? 80 : KT;
     constexpr int stage = KT * BM * ES + rows * BN * ES, bytes = NST * stage + (KIND == LIN ? 0 : KIND == ROW3 ? 1024 + 256 * 16 : 1024 * 4);
-    static const hipError_t attr = hipFuncSetAttribute((const void*)wgrad_mm<E, BM, BN, KIND, NST>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    static DeviceSet done;
+    const hipError_t attr = allow_lds(wgrad_mm<E, BM, BN, KIND, NST>, bytes, done);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL((wgrad_mm<E, BM, BN, KIND, NST>), dim3((unsigned)(pl.co_tiles * pl.ci_tiles * pl.groups), 1, pl.splits), dim3(512), bytes, st, a);
     return hipGetLastError();

@@ -22,6 +22,7 @@ thread_local int lane;
 static thread_local int wave;
 static thread_local const char* kernel_name = "";
 static int late = 0;                       // loads to LDS land at their wait; wavefronts and blocks in descending order
+static bool host_only = false;             // launches are looked at, not run
 static std::atomic<long> complaints{0};
 static std::mutex mu;
 static std::map<uintptr_t, size_t> ranges;      // what callers own: start -> bytes (not changed while kernels run)
@@ -240,10 +241,7 @@ void run(dim3 grid, dim3 block, size_t lds, const void* kernel, const char* name
         complain("a launch of %lld blocks of %d threads with %zu bytes of LDS that device %d does not take", (long long)blocks, threads, lds, current_device);
         return;
     }
-#ifdef LANES_HOST_ONLY
-    (void)body;
-    return;
-#endif
+    if (host_only) return;
     std::atomic<int64_t> next{0};
     auto work = [&]() {
         Engine e;
@@ -288,6 +286,7 @@ void lanes_own(void* p, size_t n) {
     ranges[(uintptr_t)p] = n;
 }
 void lanes_late(int v) { lanes::late = v; }
+void lanes_host_only(int v) { lanes::host_only = v != 0; }
 void lanes_set_device(int d) { lanes::set_device(d); }
 long lanes_complaints() { return lanes::complaints; }
 }

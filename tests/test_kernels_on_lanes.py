@@ -48,3 +48,34 @@ def test_buffers_near_4_gib(lanes, op, h, taken):
     assert (h * w * 16 + halo * (w + 1) * 16 < (1 << 32) - 1) == taken
     g = lpm.lpm_conv_geom(1, h, w, 8, 8, 3, 3, 1, 1, 1, 1, 0)
     assert bool(ctypes.CDLL(lanes).lanes_takes(op, lpm.BF16, ctypes.byref(g))) == taken
+
+
+def test_lds_limits_are_set_per_device(lanes):
+    """Kernels with more than 64 KB of LDS, each launched on a first and then on a second device of the process: a device takes
+    such a launch only after the attribute was set with that device current."""
+    import paper_2207_11019_amd as lpm
+    lib = ctypes.CDLL(lanes)
+    lib.lanes_complaints.restype = ctypes.c_long
+    for name in ("lpm_conv_forward", "lpm_conv_dgrad", "lpm_conv_wgrad", "lpm_stage_create", "lpm_stage_forward", "lpm_stage_backward"):
+        getattr(lib, name).argtypes = getattr(lpm.lib, name).argtypes
+    p = 1 << 20                            # any address: the launches are not run
+    geoms = [(2, 9, 7, 24, 40, 3, 1), (3, 128, 128, 8, 64, 3, 1), (1, 152, 152, 8, 128, 1, 0), (12, 128, 128, 128, 128, 1, 0), (12, 128, 128, 128, 128, 5, 2),
+             (5, 64, 64, 256, 256, 3, 1), (2, 70, 70, 6, 16, 5, 0)]
+    attn = lpm.layers_from_dicts([dict(kind="attn", cin=96, cout=32, kh=1, kw=1, stride=1, pad=0, h_in=31, w_in=31, src=-1)])
+    lib.lanes_host_only(1)
+    for dev in (0, 1, 0):
+        lib.lanes_set_device(dev)
+        before = lib.lanes_complaints()
+        for m, h, w, cin, cout, k, pad in geoms:
+            g = lpm.lpm_conv_geom(m, h, w, cin, cout, k, k, 1, pad, 1, 1, 0)
+            for dt in (lpm.BF16, lpm.F32):
+                assert lib.lpm_conv_forward(ctypes.byref(g), dt, p, p, None, None, None, 0, p, p, None) == 0
+                assert lib.lpm_conv_dgrad(ctypes.byref(g), dt, p, p, p if dt == lpm.BF16 else None, p, 0, p, None) == 0
+                assert lib.lpm_conv_wgrad(ctypes.byref(g), dt, p, p, p, 0, p, None) == 0
+        st = ctypes.c_void_p()
+        assert lib.lpm_stage_create(attn, 1, 0, 1, 2, lpm.BF16, ctypes.byref(st)) == 0
+        assert lib.lpm_stage_forward(st, p, p, None, None, p, p, p, p, 1.0, None) == 0
+        assert lib.lpm_stage_backward(st, p, p, p, p, p, p, p, p, 0, p, None) == 0
+        lib.lpm_stage_destroy(st)
+        assert lib.lanes_complaints() == before, "device %d" % dev
+    lib.lanes_host_only(0)
