@@ -444,17 +444,19 @@ void enqueue_worker(lpm_schedule* s, int32_t idx) {
     (void)hipSetDevice(s->device);
     uint64_t seen = 0;
     for (;;) {
-        RunArgs a;
-        RoleFn fn;
+        RunArgs a{};
+        RoleFn fn = nullptr;
         bool mine;
         {
             std::unique_lock<std::mutex> lk(s->mu);
             s->cv_go.wait(lk, [&] { return s->quit || s->epoch != seen; });
             if (s->quit) return;
             seen = s->epoch;
-            a = *(const RunArgs*)s->job;
-            fn = (RoleFn)s->job_fn;
             mine = idx < s->job_roles;
+            if (mine) {          // (the caller waits for the threads that take part, and only for those: its arguments may be gone for the others)
+                a = *(const RunArgs*)s->job;
+                fn = (RoleFn)s->job_fn;
+            }
         }
         if (!mine) continue;
         const int32_t rc = fn(s, a, idx, seen);
