@@ -39,7 +39,7 @@ void* dynamic_lds();
 void barrier(int place);
 // hands n bytes to the other lanes of the wavefront; returns the 64 lanes' slots of n bytes
 const unsigned char* exchange(const void* mine, size_t n, int place);
-void run(dim3 grid, dim3 block, size_t lds, const void* kernel, const char* name, const std::function<void()>& body);
+void run(dim3 grid, dim3 block, size_t lds, const void* kernel, const std::function<void()>& body);
 // 16 bytes per lane from a buffer to LDS address dst + 16 * lane, and the wait for all but the n youngest of them
 void load_to_lds(const unsigned* rsrc, unsigned char* dst, unsigned off, unsigned soff);
 void wait_loads(int n);
@@ -190,7 +190,7 @@ static inline hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
 static inline hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
 
 template <typename K, typename... A> static inline void lane_launch(K kernel, dim3 grid, dim3 block, size_t lds, A... args) {
-    lanes::run(grid, block, lds, (const void*)kernel, __PRETTY_FUNCTION__, [=]() { kernel(args...); });
+    lanes::run(grid, block, lds, (const void*)kernel, [=]() { kernel(args...); });
 }
 #define hipLaunchKernelGGL(k, g, b, lds, st, ...) lane_launch(k, g, b, lds, ##__VA_ARGS__)
 #define hipExtLaunchKernelGGL(k, g, b, lds, st, e0, e1, fl, ...) (lane_launch(k, g, b, lds, ##__VA_ARGS__), (void)hipEventRecord(e1, st))

@@ -9,24 +9,36 @@
 // not there differs between the two.
 #include <hip/hip_runtime.h>
 #include <sys/mman.h>
+#include <cxxabi.h>
+#include <dlfcn.h>
 #include <atomic>
 #include <cstdarg>
 #include <map>
 #include <mutex>
 #include <set>
+#include <string>
 #include <thread>
 
 namespace lanes {
 thread_local Idx tid, bid, bdim, gdim;
 thread_local int lane;
 static thread_local int wave;
-static thread_local const char* kernel_name = "";
+static thread_local const void* kernel = nullptr;
 static int late = 0;                       // loads to LDS land at their wait; wavefronts and blocks in descending order
 static bool host_only = false;             // launches are looked at, not run
 static std::atomic<long> complaints{0};
 static std::mutex mu;
 static std::map<uintptr_t, size_t> ranges;      // what callers own: start -> bytes (not changed while kernels run)
 
+static std::string kernel_name(const void* k) {
+    Dl_info d;
+    if (!dladdr(k, &d) || !d.dli_sname) return "?";
+    int st = 0;
+    char* q = abi::__cxa_demangle(d.dli_sname, nullptr, nullptr, &st);
+    std::string s = q ? q : d.dli_sname;
+    free(q);
+    return s.substr(0, s.find('('));
+}
 static void complain(const char* fmt, ...) {
     if (complaints++ >= 10) return;
     std::lock_guard<std::mutex> l(mu);
@@ -35,8 +47,7 @@ static void complain(const char* fmt, ...) {
     fprintf(stderr, "lanes: ");
     vfprintf(stderr, fmt, a);
     va_end(a);
-    const char* k = strstr(kernel_name, "K = ");
-    fprintf(stderr, " [block %u,%u,%u thread %u of %.160s]\n", bid.x, bid.y, bid.z, tid.x, k ? k : kernel_name);
+    fprintf(stderr, " [block %u,%u,%u thread %u of %s]\n", bid.x, bid.y, bid.z, tid.x, kernel_name(kernel).c_str());
 }
 
 static void check_owned(const void* p, size_t n, const char* what) {
@@ -222,20 +233,22 @@ static thread_local int current_device = 0;
 static std::set<std::pair<int, const void*>> lds_allowed;      // devices and kernels that may have more than 64 KB of LDS
 int device() { return current_device; }
 int set_device(int d) { current_device = d; return hipSuccess; }
-int allow_lds(const void* kernel, int) {
+int allow_lds(const void* k, int) {
     std::lock_guard<std::mutex> l(mu);
-    lds_allowed.insert({current_device, kernel});
+    lds_allowed.insert({current_device, k});
     return hipSuccess;
 }
 
-void run(dim3 grid, dim3 block, size_t lds, const void* kernel, const char* name, const std::function<void()>& body) {
+void run(dim3 grid, dim3 block, size_t lds, const void* k, const std::function<void()>& body) {
     const int64_t blocks = (int64_t)grid.x * grid.y * grid.z;
     const int threads = (int)(block.x * block.y * block.z);
-    kernel_name = name;
+    static const bool trace = getenv("LPM_LANES_TRACE") != nullptr;
+    kernel = k;
+    if (trace) fprintf(stderr, "lanes: %ux%ux%u blocks of %d threads, %zu bytes of LDS: %s\n", grid.x, grid.y, grid.z, threads, lds, kernel_name(k).c_str());
     bool allowed = lds <= 64 * 1024;
     if (!allowed) {
         std::lock_guard<std::mutex> l(mu);
-        allowed = lds_allowed.count({current_device, kernel}) != 0;
+        allowed = lds_allowed.count({current_device, k}) != 0;
     }
     if (blocks <= 0 || threads <= 0 || threads > 1024 || lds > 160 * 1024 || !allowed) {
         complain("a launch of %lld blocks of %d threads with %zu bytes of LDS that device %d does not take", (long long)blocks, threads, lds, current_device);
@@ -246,7 +259,7 @@ void run(dim3 grid, dim3 block, size_t lds, const void* kernel, const char* name
     auto work = [&]() {
         Engine e;
         E = &e;
-        kernel_name = name;
+        kernel = k;
         e.set_lds(lds);
         e.body = &body;
         bdim = {block.x, block.y, block.z};

@@ -82,5 +82,5 @@ def build(out, flags=(), extra=(), exe=None, opt="-O2"):
         assert p.returncode == 0, err[-4000:]
     target = os.path.join(out, exe or "liblanes.so")
     link = [f for f in flags if f.startswith("-fsanitize")]
-    subprocess.check_call([cxx, *link, *([] if exe else ["-shared"]), "-o", target, *objs, "-lpthread"])
+    subprocess.check_call([cxx, *link, *([] if exe else ["-shared"]), "-o", target, *objs, "-lpthread", "-ldl"])
     return target

@@ -1,6 +1,6 @@
 """pytest plugin: the GPU tests with the library's kernels running lane by lane on the CPU (see lanes.cpp), device memory being host
 memory between pages without access.  LPM_LANES names the library that lanes_build.build() made, LPM_LANES_LATE=1 asks for loads
-that land late and the descending order of wavefronts and blocks."""
+that land late and the descending order of wavefronts and blocks, LPM_LANES_TRACE=1 for a line per launch on stderr."""
 import ctypes
 import os
 

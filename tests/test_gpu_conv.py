@@ -50,22 +50,22 @@ SHAPES = [
     G(16, 2, 2, 512, 512, 3, 1, 1),       # deep, few pixels: split reduction
     G(5, 4, 4, 64, 72, 4, 1, 0),          # kernel covers the input: a fully connected layer
     G(16, 1, 1, 512, 10, 1, 1, 0),        # classifier head (Cout = 10)
-    G(4, 7, 7, 64, 520, 7, 1, 0),         # FC over a 7x7 map, 4 samples: weight-streaming kernels, ragged channel split
+    G(4, 7, 7, 64, 520, 7, 1, 0),         # FC over a 7x7 map, 4 samples: the kernels that stream the weights, ragged channel split
     G(13, 1, 1, 1032, 200, 1, 1, 0),      # FC, 13 samples, K not a multiple of the column block
     G(7, 2, 2, 24, 48, 2, 1, 0),          # FC, 7 samples, one partial column block
-    G(4, 16, 16, 3, 64, 3, 1, 1),         # 3-channel first layer (generic kernels)
+    G(4, 16, 16, 3, 64, 3, 1, 1),         # 3-channel first layer: gathered operands
     G(3, 9, 11, 3, 40, 3, 2, 1),          # 3-channel first layer, stride 2, ragged
     G(2, 12, 12, 1, 16, 5, 1, 0),         # 1 channel, 5x5 (25 terms)
-    G(16, 32, 32, 64, 160, 3, 1, 1),      # large: 128x128 tiles
-    G(2, 14, 14, 256, 256, 3, 1, 1),      # both >= 128 channels: large weight-gradient tiles
-    G(2, 15, 15, 512, 512, 3, 1, 1),      # 512 channels, images just below two patches
-    G(3, 24, 15, 64, 128, 3, 1, 1),       # ragged in x only
-    # large images: the weight gradient by 8x8 pixel patches (LDS transpose reads)
-    G(1, 56, 56, 64, 64, 3, 1, 1),        # one tap per block, few patches per block
-    G(2, 64, 64, 64, 128, 3, 1, 1),       # one tap per block, more blocks than CUs
-    G(1, 57, 59, 128, 128, 3, 1, 1),      # a filter row per block, patches over the edge in both directions
-    G(4, 64, 64, 128, 128, 3, 1, 0),      # a filter row per block, no padding
-    G(1, 60, 60, 72, 136, 3, 1, 1),       # channel counts that are not multiples of the 64-channel tile
+    G(16, 32, 32, 64, 160, 3, 1, 1),      # 128x64 tiles, N over two of them
+    G(2, 14, 14, 256, 256, 3, 1, 1),      # filter rows of two segments, the second ragged, four channel tiles either way
+    G(2, 15, 15, 512, 512, 3, 1, 1),      # 512 channels, segments of 8 and 7 pixels
+    G(3, 24, 15, 64, 128, 3, 1, 1),       # ... over more than one pixel range
+    # larger images: the weight gradient by filter rows, segments of 8 pixels
+    G(1, 56, 56, 64, 64, 3, 1, 1),        # whole segments, as many pixel ranges as K tiles allow
+    G(2, 64, 64, 64, 128, 3, 1, 1),       # ... two channel tiles
+    G(1, 57, 59, 128, 128, 3, 1, 1),      # eight segments per row, the last of 3 pixels
+    G(4, 64, 64, 128, 128, 3, 1, 0),      # no padding: 62 pixels per row
+    G(1, 60, 60, 72, 136, 3, 1, 1),       # channel counts that are not multiples of the 64-channel tile, segments of 8 and 4 pixels
     # volumetric layers (3x3x3 and 1x1x1 filters, the first use case's shapes)
     G3(2, 6, 6, 6, 32, 64, 3, 1, 1),      # matrix-core kernels for all three contractions
     G3(1, 5, 7, 6, 64, 40, 3, 1, 1),      # ragged extents and channel tile
@@ -75,12 +75,12 @@ SHAPES = [
     G3(2, 5, 5, 5, 64, 256, 3, 2, 1),     # stride 2, long K: split reduction over the taps of a class
     G3(2, 8, 8, 8, 32, 64, 1, 2, 0),      # 1x1x1 stride-2 projection
     G3(2, 4, 4, 4, 128, 128, 3, 1, 1),    # long reduction: split over blocks
-    G3(1, 4, 9, 8, 32, 64, 3, 1, 1),      # 8x8 patches of the output slices: the patch-based weight gradient, one tap per block
-    G3(2, 6, 16, 16, 128, 128, 3, 1, 1),  # ... a filter row per block (27 taps in 9 groups)
-    G3(1, 7, 15, 15, 32, 64, 3, 2, 1),    # ... stride 2, odd extents
-    G3(2, 3, 8, 8, 64, 64, 1, 1, 0),      # ... 1x1x1: the voxels regrouped as one image of full patches
+    G3(1, 4, 9, 8, 32, 64, 3, 1, 1),      # rows of 8 output pixels in 9 groups of three taps
+    G3(2, 6, 16, 16, 128, 128, 3, 1, 1),  # ... of two segments
+    G3(1, 7, 15, 15, 32, 64, 3, 2, 1),    # stride 2, odd extents
+    G3(2, 3, 8, 8, 64, 64, 1, 1, 0),      # 1x1x1: consecutive voxels
     G3(3, 4, 4, 4, 64, 192, 1, 1, 0),     # 1x1x1 (queries | keys | values of an attention block)
-    G3(2, 8, 8, 8, 1, 16, 3, 1, 1),       # one-channel input volume: flattened (tap, channel) weight gradient
+    G3(2, 8, 8, 8, 1, 16, 3, 1, 1),       # one-channel input volume: gathered operands
     dict(G3(1, 9, 7, 10, 2, 24, 3, 1, 1), h=7, w=10),     # two channels x 27 taps, ragged extents
     G3(2, 9, 9, 9, 1, 32, 3, 2, 1),       # one-channel volume, stride 2
     dict(G3(2, 3, 4, 4, 32, 48, 3, 1, 0), kd=3, pad_d=0, kh=4, kw=4),   # filter covers the whole volume: a fully connected layer

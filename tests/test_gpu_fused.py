@@ -44,3 +44,68 @@ def test_pooling_backward_before_a_convolution(lpm, c1, c2, k, p, dtype):
     layers = chain(C(4, c1, 3, 3, 16, 16, p=1), P(c1, 16, 16), C(c1, c2, k, k, 8, 8, p=p, scale=True))
     print("channels", c1, c2, "filter", k, "dtype", dtype, flush=True)
     stage_backward_isolated(lpm, layers, [0, 3], 3, 3, dtype, seed=21, dx_wanted=True, check_forward=True, grad_std=1.0)
+
+
+def bottlenecks(w, mid, h, m, shortcuts, first_scale=True):
+    """Stem, then blocks 1x1 reduce - 1x1 expand + shortcut, then one more reduction that keeps the last block inside the stage.
+    shortcuts: the tensor each block adds ('x': the block's input, 'in': the stage's)."""
+    layers = [C(w, w, 1, 1, h, h, scale=first_scale)]
+    for s in shortcuts:
+        x = len(layers) - 1
+        layers.append(C(w, mid, 1, 1, h, h, scale=True, src=x))
+        layers.append(C(mid, w, 1, 1, h, h, scale=True, src=x + 1, add=x if s == "x" else -1))
+    layers.append(C(w, mid, 1, 1, h, h, src=len(layers) - 1))
+    return chain(*layers), m
+
+
+def projected(cin, w, mid, h, m):
+    """A block whose shortcut is a projection with a scale of its own."""
+    return chain(C(cin, cin, 1, 1, h, h), C(cin, mid, 1, 1, h, h, scale=True, src=0), C(cin, w, 1, 1, h, h, relu=False, scale=True, src=0),
+                 C(mid, w, 1, 1, h, h, scale=True, src=1, add=2), C(w, mid, 1, 1, h, h)), m
+
+
+def long_projection(cin, w, mid, h, wd, m):
+    """The same with filters of 13 x 1."""
+    return chain(C(cin, cin, 1, 1, h, wd), C(cin, mid, 13, 1, h, wd, scale=True, src=0), C(cin, w, 13, 1, h, wd, relu=False, bias=False, scale=True, src=0),
+                 C(mid, w, 1, 1, h - 12, wd, scale=True, src=1, add=2), C(w, mid, 1, 1, h - 12, wd)), m
+
+
+NETS = {
+    # bf16: the masked sum of the contributions to a block's output, the gradient of its shortcut and, where two blocks share one, the
+    # sum of both -- on every tile of the data gradient, in whole and in ragged row and channel tiles
+    "tile64": (bottlenecks(64, 16, 12, 2, ["in", "x", "in"]), "bf16"),
+    "tile64_ragged": (bottlenecks(72, 24, 11, 3, ["in", "in"]), "bf16"),
+    "tile64_split": (bottlenecks(64, 2048, 4, 2, ["in", "in"]), "bf16"),
+    "tile128x64": (bottlenecks(64, 16, 108, 2, ["in", "in"]), "bf16"),
+    "tile128_8w": (bottlenecks(128, 16, 108, 2, ["in", "x", "in"]), "bf16"),
+    "tile128_8w_ragged": (bottlenecks(120, 64, 109, 2, ["in", "in"]), "bf16"),
+    "tile128": (bottlenecks(256, 16, 111, 2, ["in", "in"]), "bf16"),
+    "projected128": (projected(16, 128, 16, 108, 2), "bf16"),
+    # the same in float, where a block's scale enters through the weights of its data gradient: channels in whole K tiles, in chunks of
+    # 16 bytes, and gathered one by one
+    "float_whole": (bottlenecks(32, 64, 40, 2, ["in", "x", "in"]), "f32"),
+    "float_chunks": (bottlenecks(36, 20, 40, 2, ["in", "in"]), "f32"),
+    "float_projected": (projected(20, 44, 36, 40, 2), "f32"),
+    # layers whose dz carries their scale (their filter is too long for the weight gradients that multiply by it): the block's input, and
+    # a projection
+    "scaled_dz": ((chain(C(6, 16, 13, 1, 20, 12, bias=False, scale=True), C(16, 40, 3, 3, 8, 12, p=1, scale=True)), 2), "bf16"),
+    "scaled_dz128": ((chain(C(6, 128, 13, 1, 120, 108, bias=False, scale=True), C(128, 16, 1, 1, 108, 108, scale=True)), 2), "bf16"),
+    "scaled_dz_float": ((chain(C(6, 16, 13, 1, 20, 24, bias=False, scale=True), C(16, 40, 3, 3, 8, 24, p=1, scale=True)), 2), "f32"),
+    "scaled_projection": (long_projection(6, 64, 16, 20, 12, 2), "bf16"),
+    "scaled_projection128": (long_projection(6, 128, 16, 120, 108, 2), "bf16"),
+    "scaled_projection_float": (long_projection(6, 64, 32, 32, 40, 2), "f32"),
+    # data gradients gathered channel by channel, with scales on either side
+    "gathered_bf16": ((chain(C(4, 6, 3, 3, 16, 16, p=1, scale=True), C(6, 10, 3, 3, 16, 16, p=1, scale=True), C(10, 7, 5, 5, 16, 16, scale=True)), 2), "bf16"),
+    "gathered_float": ((chain(C(4, 6, 3, 3, 16, 16, p=1, scale=True), C(6, 10, 3, 3, 16, 16, p=1, scale=True), C(10, 7, 5, 5, 16, 16, scale=True)), 2), "f32"),
+    # weight gradients of a backward pass cut into fewer pixel ranges than those of a lone call: filter rows, single taps, large tiles
+    "ranges_rows": ((chain(C(64, 64, 3, 3, 64, 64, p=1, scale=True), C(64, 64, 1, 1, 64, 64, scale=True)), 9), "bf16"),
+    "ranges_large": ((chain(C(256, 256, 1, 1, 128, 128, scale=True), C(256, 128, 1, 1, 128, 128)), 3), "bf16"),
+    "ranges_float": ((chain(C(16, 32, 3, 3, 40, 40, p=1, scale=True), C(32, 16, 1, 1, 40, 40)), 9), "f32"),
+}
+
+
+@pytest.mark.parametrize("name", NETS)
+def test_fused_backward(lpm, name):
+    (layers, m), dtype = NETS[name]
+    print("network", name, flush=True)
+    stage_backward_isolated(lpm, layers, [0, len(layers)], m, m, 1 if dtype == "bf16" else 0, seed=23, dx_wanted=True, check_forward=True, grad_std=1.0)
