@@ -456,7 +456,7 @@ def memory_kernels(torch, lpm, V, cur):
     n = s.grad_bytes // 4
     t = time_stream(torch, lambda: s.update(b["params"], b["lowp"], b["grads"], b["momentum"], 0.0, V.mu, False, cur), 10)
     byts = 22 * n
-    out["sgd_update"] = dict(kernel="sgd_kernel (+ transposed weight copies), stage %d of vgg16_224" % z, parameters=n, algorithmic_bytes=byts,
+    out["sgd_update"] = dict(kernel="update_kernel (with the transposed weight copies), stage %d of vgg16_224" % z, parameters=n, algorithmic_bytes=byts,
                              us=round(t * 1e6, 1), achieved_gbps=round(byts / t / 1e9, 1), peak_gbps=8000.0, frac=round(byts / t / PEAK["hbm"], 4))
     pl = next(i for i, l in enumerate(V.layers) if l["kind"] == "maxpool2")
     ps, x, y, par, stash, ws = pool_stage(lpm, V, pl)

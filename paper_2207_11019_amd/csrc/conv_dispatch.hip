@@ -102,9 +102,11 @@ bool wgrad_fuses_bias(int dtype, const ConvGeom& g) { return wgrad_mm_ok(dtype, 
 // whether the data gradient wants the [Cin][Kh][Kw][Cout] copy of the weights
 bool dgrad_uses_wt(int dtype, const ConvGeom& g) { return dtype == LPM_BF16 && !fc_skinny_ok(g) && mfma_dgrad_ok(dtype, g); }
 
-// the stride-1 MFMA data gradient can route its result through a following (in forward order: preceding) max-pooling
-// (worth it while the kernel is bound by its launch: measured on the 224x224 VGG layers the scattered 2-byte stores
-// in the contraction's epilogue cost more than the separate pooling kernel, so large gradients keep that kernel)
+// the stride-1 MFMA data gradient can route its result through a following (in forward order: preceding) max-pooling, whole
+// chunks of eight channels at a time.  Of small gradients only, which are bound by their launches: the line was drawn with an
+// epilogue of 2-byte stores, for which the 224x224 VGG layers were better off with a pooling kernel of their own.  With the present
+// epilogue the two large layers above the line make no such difference any more (VGG-16/224, us per step: 6658 with the line, 6611
+// without it).
 bool dgrad_can_unpool(int dtype, const ConvGeom& g) {
     return dtype == LPM_BF16 && !g.is3d() && !fc_skinny_ok(g) && mfma_dgrad_ok(dtype, g) && g.stride == 1 && g.Cin % 8 == 0 &&
            (int64_t)g.rows_in() * g.Cin <= ((int64_t)1 << 20);
@@ -139,7 +141,8 @@ hipError_t launch_conv_wgrad(int dtype, const ConvGeom& g, const void* x, const 
     return conv_wgrad_generic_launch(dtype, g, x, dz, dw, accumulate, ws, st);
 }
 
-// Staging pays when one read-modify-write pass over dW moves several times the bytes of the staged operands.
+// Staging pays when one read-modify-write pass over dW moves several times the bytes of the staged operands.  Per step without it for
+// convolutions / with it, in us: VGG-16/CIFAR 1976 / 1895, ResNet-18/CIFAR 3320 / 3265, VGG-16/224 6718 / 6669, volumetric 1759 / 1761.
 bool wgrad_staged_ok(int dtype, const ConvGeom& g) {
     if (dtype != LPM_BF16) return false;
     if (fc_staged_ok(g)) return true;

@@ -1,7 +1,7 @@
 // Shape-generic kernels: every layer kind, any extent, float or bf16 elements.
 //
-// These are the fall-back contraction kernels (one thread per output element, fp32 accumulation)
-// used for the fp32 element type and for shapes the MFMA kernels do not cover, plus the
+// These are the contraction kernels for what the matrix-core kernels leave (a group of lanes per output element, fp32
+// accumulation: float contractions of a few hundred thousand products, heads of a few classes, long filters), plus the
 // memory-bound kernels of the step: epilogue backward + bias gradient, pooling, loss, update.
 // Layouts: activations [m][H][W][C], weights [Cout][Kh][Kw][Cin].
 #include "lpm_internal.h"

@@ -236,9 +236,9 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
         lr.unpool_of = p;
         s->Ly(p).unpooled = true;
     }
-    // Pooling-forward fusion: a convolution whose output feeds a 2x2 max-pooling inside the stage and whose forward
-    // contraction ends in a split reduction: that reduction stores the pooled tensor as well (one kernel less per pool
-    // on the forward chain; the pooling layer's own input stays stored, the backward pass needs it).
+    // Pooling-forward fusion: a convolution whose output feeds a 2x2 max-pooling inside the stage and whose forward kernel can
+    // store the pooled tensor as well (one kernel less per pool on the forward chain; the pooling layer's own input stays
+    // stored, the backward pass needs it).
     for (int32_t i = first; i + 1 < last; ++i) {
         LayerRt& lr = s->Ly(i);
         const lpm_layer& l = lr.d;

@@ -38,7 +38,7 @@ CASES = [
     (G(16, 2, 2, 512, 512, 3, 1, 1), 4),      # deep, few pixels: split reductions inside every sub-layer
     (G(4, 7, 7, 64, 512, 7, 1, 0), 4),        # fully connected layer over a 7x7 map (weight-streaming kernels)
     (G(4, 16, 16, 3, 64, 3, 1, 1), 4),        # 3-channel first layer: weight slices that are not 256-byte multiples
-    (G(1, 56, 56, 64, 128, 3, 1, 1), 2),      # large image: patch-based weight gradient inside the sub-layers
+    (G(1, 56, 56, 64, 128, 3, 1, 1), 2),      # large image: filter-row weight gradients inside the sub-layers
 ]
 
 

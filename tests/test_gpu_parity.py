@@ -38,7 +38,7 @@ CASES = [
     ("tiny_fc_bf16_one_stage", wl.tiny_fc, 6, 3, 1, 1),
     # 64-channel convolutions over 4x4 and 2x2 images: the same for convolutions
     ("tiny_wide_bf16", wl.tiny_wide, 8, 4, 2, 1),
-    # a split forward reduction into 72 channels whose second kernel also pools
+    # a split forward reduction into 72 channels whose kernel also pools
     ("tiny_deep_pool_bf16", wl.tiny_deep_pool, 16, 2, 1, 1),
     # the volumetric use case: 3x3x3 residual blocks, a strided block with a 1x1x1 projection, a residual self-attention block
     ("tiny_conv3d_f32", wl.tiny_conv3d, 4, 2, 3, 0),
@@ -330,7 +330,7 @@ def test_zero_and_tiny_scales(lpm, net, dtype):
     """Frozen per-channel scales of exactly 0 and of 1e-20 (a zero-initialised folded normalisation is a legal value):
     the bias gradient is the sum of the masked output gradient whatever the scale (eq. 8 for the bias), the weight
     gradient of a zero-scale channel is 0, and nothing is divided by a scale.  bottleneck32: 32- and 64-channel
-    bottleneck blocks (matrix-core kernels, fused epilogue backward); tiny_resnet: 4 and 6 channels (generic kernels)."""
+    bottleneck blocks (matrix-core kernels, fused epilogue backward); tiny_resnet: 4 and 6 channels (gathered operands)."""
     if net == "bottleneck32":
         layers = wl.r50_conv4x(cin=64, hw=8, mid=32, cout=64, blocks=2)
         batch, M, dx = 8, 2, True

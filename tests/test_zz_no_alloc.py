@@ -35,9 +35,9 @@ def _case(lpm, torch, g, dtype, seed):
 
 def test_static_scratch_weight_gradient(lpm):
     import torch
-    big = dict(m=4, h=28, w=28, cin=64, cout=96, kh=3, kw=3, stride=1, pad=1)      # split partials, patch-based kernel
-    small = dict(m=32, h=4, w=4, cin=64, cout=64, kh=3, kw=3, stride=1, pad=1)     # smaller partials, the pixel-tiled kernel
-    f32 = dict(m=4, h=9, w=7, cin=5, cout=7, kh=3, kw=3, stride=2, pad=1)          # float path (generic kernels)
+    big = dict(m=4, h=28, w=28, cin=64, cout=96, kh=3, kw=3, stride=1, pad=1)      # split partials, filter rows
+    small = dict(m=32, h=4, w=4, cin=64, cout=64, kh=3, kw=3, stride=1, pad=1)     # smaller partials, single taps
+    f32 = dict(m=4, h=9, w=7, cin=5, cout=7, kh=3, kw=3, stride=2, pad=1)          # float, gathered operands
     cases = [(big, lpm.BF16), (small, lpm.BF16), (f32, lpm.F32), (big, lpm.BF16)]
     assert lpm.lpm_conv_ws_bytes(big, lpm.BF16)[2] > lpm.lpm_conv_ws_bytes(small, lpm.BF16)[2] > 0
     st = torch.cuda.Stream()
