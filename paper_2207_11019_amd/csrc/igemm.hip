@@ -114,7 +114,7 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
         for (int c = tid; c < p.Ci; c += T) ksc[c] = p.kscale[c];      // (the first K tile's barrier makes it visible)
     }
     // ---- loader state.  Lane l of a load fills chunk position l % 8 of row l / 8: it fetches chunk (l % 8) ^ (l / 8)
-    const int lrow = lane >> 3, kcol = (lane & 7) ^ lrow;
+    const int lrow = lane >> 3, kcol = (lane & 7) ^ ((wave & 1) * 4 + (lrow >> 1));
     unsigned a_base[A_LD], a_msk[A_LD], b_off[B_LD];
 #pragma unroll
     for (int i = 0; i < A_LD; ++i) {
@@ -179,13 +179,25 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
     const int step_t = UNI ? 0 : div_by(8, p.dCc), step_c = UNI ? 0 : 8 - step_t * Cc;
 
     // UNI: the A offsets of the current tap, with the rows that miss the image out of range
-    unsigned a_cur[A_LD], s_a = 0, s_b = 0;
+    // (offsets and mask bit move on by differences: as sums of products they cost 80 ns of scalar arithmetic at every tap, half as much
+    // as a K tile of a 64-channel layer, whose tap changes with every one)
+    unsigned a_cur[A_LD], s_a = aoff0 + c_td * aD + c_th * aH + c_tw * aW, s_b = b0 + c_td * bD + c_th * bH + c_tw * bW;
+    unsigned bit = p.free_taps ? 1u : (1u << (24 + c_td)) | (1u << (12 + c_th)) | (1u << c_tw);
+    const unsigned aWH = aH - aW * (unsigned)(nkw - 1), bWH = bH - bW * (unsigned)(nkw - 1);                  // past the last tap of a row
+    const unsigned aHD = aD - aH * (unsigned)(nkh - 1) - aW * (unsigned)(nkw - 1), bHD = bD - bH * (unsigned)(nkh - 1) - bW * (unsigned)(nkw - 1);
     auto set_tap = [&]() __attribute__((always_inline)) {
-        s_a = aoff0 + c_td * aD + c_th * aH + c_tw * aW;
-        s_b = b0 + c_td * bD + c_th * bH + c_tw * bW;
-        const unsigned bit = p.free_taps ? 1u : (1u << (24 + c_td)) | (1u << (12 + c_th)) | (1u << c_tw);
 #pragma unroll
         for (int i = 0; i < A_LD; ++i) a_cur[i] = (a_msk[i] & bit) == bit ? a_base[i] : OOB;
+    };
+    auto next_tap = [&]() __attribute__((always_inline)) {
+        if (++c_tw < nkw) { s_a += aW; s_b += bW; bit += bit & 0xfffu; }
+        else {
+            c_tw = 0;
+            if (++c_th < nkh) { s_a += aWH; s_b += bWH; bit = ((bit & 0xfff000u) << 1) | (bit & 0xff000000u) | 1u; }
+            else { c_th = 0; s_a += aHD; s_b += bHD; bit = ((bit & 0xff000000u) << 1) | 0x1001u; }
+        }
+        if (p.free_taps) bit = 1u;
+        set_tap();
     };
     if (UNI) set_tap();
     // Issues the loads of the next K tile into a stage.  Past the last tile the buffers count as empty: the stage fills with
@@ -240,8 +252,7 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
                 c_c += 128;
                 if (c_c == tapC) {
                     c_c = 0;
-                    if (++c_tw == nkw) { c_tw = 0; if (++c_th == nkh) { c_th = 0; ++c_td; } }
-                    set_tap();
+                    next_tap();
                 }
             } else {
                 l_t += step_t; l_c += step_c;
@@ -275,7 +286,7 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
     auto read = [&](Frag& f, int st, int ks) __attribute__((always_inline)) {
         const unsigned char* sp = lds + st * STAGE;
         {
-            const unsigned x = (unsigned)(((ks * 2 + kh_) ^ (lane & 7)) << 4);
+            const unsigned x = (unsigned)(((ks * 2 + kh_) ^ ((lane >> 1) & 7)) << 4);
 #pragma unroll
             for (int mi = 0; mi < MI; ++mi) f.a[ks][mi] = *reinterpret_cast<const uint4*>(sp + rowA + x + mi * 4096);
 #pragma unroll
