@@ -27,8 +27,8 @@ hipError_t mfma_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const v
 bool mfma_dgrad_kscale_ok(const ConvGeom& g);
 bool wgrad_mm_ok(int dtype, const ConvGeom& g);
 size_t wgrad_mm_ws_bytes(int dtype, const ConvGeom& g);
-hipError_t wgrad_mm_launch(int dtype, const ConvGeom& g, const void* x, const void* dz, float* dw, float* dbias, const float* rscale,
-                           int accumulate, void* ws, hipStream_t st, ReduceDesc* deferred);
+hipError_t wgrad_mm_launch(int dtype, const WgradTask& t, hipStream_t st);
+hipError_t wgrad_mm_group(int dtype, const WgradTask* t, int n, hipStream_t st, ReduceDesc* red);
 
 bool fc_skinny_ok(const ConvGeom& g);
 size_t fc_dgrad_ws_bytes(const ConvGeom& g);
@@ -36,10 +36,6 @@ hipError_t fc_dgrad(const ConvGeom& g, const void* dz, const float* dzscale, con
                     const float* mscale, void* ws, hipStream_t st);
 hipError_t fc_wgrad(const ConvGeom& g, const void* x, const void* dz, float* dw, float* dbias, const float* rscale,
                     int accumulate, hipStream_t st);
-
-bool fc_staged_ok(const ConvGeom& g);
-hipError_t fc_wgrad_staged(const ConvGeom& g, const void* xs, const void* dzs, int slots, float* dw, float* dbias,
-                           const float* rscale, int accumulate, hipStream_t st);
 
 bool gather_fwd_ok(int dtype, const ConvGeom& g);
 bool gather_dgrad_ok(int dtype, const ConvGeom& g);
@@ -131,14 +127,40 @@ hipError_t launch_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const
     return conv_dgrad_generic_launch(dtype, g, dz, dzscale, w, dx, accumulate, mask, mscale, st);
 }
 
-hipError_t launch_conv_wgrad(int dtype, const ConvGeom& g, const void* x, const void* dz, float* dw, float* dbias,
-                             const float* rscale, int accumulate, void* ws, hipStream_t st, ReduceDesc* deferred) {
+static bool wgrad_mm_taken(int dtype, const ConvGeom& g) { return !(dtype == LPM_BF16 && fc_skinny_ok(g)) && wgrad_mm_ok(dtype, fc_view(g)); }
+// the kernels that take one layer a launch
+static hipError_t wgrad_other(int dtype, const WgradTask& t, hipStream_t st, ReduceDesc* deferred) {
     if (deferred) deferred->splits = 0;
-    if (dtype == LPM_BF16 && fc_skinny_ok(g)) return fc_wgrad(g, x, dz, dw, dbias, rscale, accumulate, st);
-    if (wgrad_mm_ok(dtype, fc_view(g))) return wgrad_mm_launch(dtype, fc_view(g), x, dz, dw, dbias, rscale, accumulate, ws, st, deferred);
-    if (gather_wgrad_ok(dtype, g)) return gather_conv_wgrad(dtype, g, x, dz, dw, dbias, rscale, accumulate, ws, st, deferred);
-    if (dbias || rscale) return hipErrorInvalidValue;      // callers ask wgrad_fuses_bias first
-    return conv_wgrad_generic_launch(dtype, g, x, dz, dw, accumulate, ws, st);
+    if (dtype == LPM_BF16 && fc_skinny_ok(t.g)) return fc_wgrad(t.g, t.x, t.dz, t.dw, t.db, t.rscale, t.accumulate, st);
+    if (gather_wgrad_ok(dtype, t.g)) return gather_conv_wgrad(dtype, t.g, t.x, t.dz, t.dw, t.db, t.rscale, t.accumulate, t.ws, st, deferred);
+    if (t.db || t.rscale) return hipErrorInvalidValue;      // callers ask wgrad_fuses_bias first
+    return conv_wgrad_generic_launch(dtype, t.g, t.x, t.dz, t.dw, t.accumulate, t.ws, st);
+}
+hipError_t launch_conv_wgrad(int dtype, const WgradTask& t, hipStream_t st) {
+    if (!wgrad_mm_taken(dtype, t.g)) return wgrad_other(dtype, t, st, nullptr);
+    WgradTask v = t;
+    v.g = fc_view(t.g);
+    return wgrad_mm_launch(dtype, v, st);
+}
+hipError_t launch_wgrad_group(int dtype, const WgradTask* t, int n, hipStream_t st, ReduceDesc* red) {
+    if (n > LPM_WGRAD_GROUP) return hipErrorInvalidValue;
+    WgradTask mm[LPM_WGRAD_GROUP];
+    ReduceDesc r[LPM_WGRAD_GROUP];
+    int at[LPM_WGRAD_GROUP], k = 0;
+    for (int i = 0; i < n; ++i) {
+        if (wgrad_mm_taken(dtype, t[i].g)) {
+            mm[k] = t[i];
+            mm[k].g = fc_view(t[i].g);
+            at[k++] = i;
+        } else {
+            const hipError_t e = wgrad_other(dtype, t[i], st, &red[i]);
+            if (e != hipSuccess) return e;
+        }
+    }
+    if (!k) return hipSuccess;
+    const hipError_t e = wgrad_mm_group(dtype, mm, k, st, r);
+    for (int i = 0; i < k; ++i) red[at[i]] = r[i];
+    return e;
 }
 
 // Staging pays when one read-modify-write pass over dW moves several times the bytes of the staged operands.  Per step without it for
@@ -151,21 +173,11 @@ bool wgrad_staged_ok(int dtype, const ConvGeom& g) {
     return (int64_t)g.Cout * g.K() >= 32768 && dw_rmw >= 6 * staged;
 }
 
-static ConvGeom staged_geom(const ConvGeom& g, int slots) { ConvGeom b = g; b.m = g.m * slots; return b; }
-
 size_t wgrad_staged_ws_bytes(int dtype, const ConvGeom& g) {
     if (!wgrad_staged_ok(dtype, g) || fc_staged_ok(g)) return 0;
     size_t b = 0;
     for (int s = 1; s <= LPM_FC_STAGE_SLOTS; ++s) b = std::max(b, wgrad_ws_bytes(dtype, staged_geom(g, s)));
     return b;
-}
-
-hipError_t launch_wgrad_staged(int dtype, const ConvGeom& g, const void* xs, const void* dzs, int slots, float* dw, float* dbias,
-                               const float* rscale, int accumulate, void* ws, hipStream_t st, ReduceDesc* deferred) {
-    if (deferred) deferred->splits = 0;
-    if (fc_staged_ok(g)) return fc_wgrad_staged(g, xs, dzs, slots, dw, dbias, rscale, accumulate, st);
-    // the staged micro-batches are one larger batch in the same layout
-    return launch_conv_wgrad(dtype, staged_geom(g, slots), xs, dzs, dw, dbias, rscale, accumulate, ws, st, deferred);
 }
 
 }  // namespace lpm

@@ -236,19 +236,38 @@ bool fc_staged_ok(const ConvGeom& g) {
     return fc_skinny_ok(g) && ((int64_t)g.m * g.Cout) % 8 == 0 && (int64_t)g.Cout * g.K() >= 32768;
 }
 
-__global__ void __launch_bounds__(256) fc_stage_copy(const uint4* __restrict__ x, uint4* __restrict__ xs, int nx,
-                                                     const uint4* __restrict__ dz, uint4* __restrict__ dzs, int nd) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < nx) xs[i] = x[i];
-    else if (i - nx < nd) dzs[i - nx] = dz[i - nx];
+struct StageCopyArgs {
+    const uint4* src[2 * LPM_WGRAD_GROUP];
+    uint4* dst[2 * LPM_WGRAD_GROUP];
+    int n[2 * LPM_WGRAD_GROUP], first[2 * LPM_WGRAD_GROUP];      // 16-byte pieces; first block
+    int count;
+};
+__global__ void __launch_bounds__(256) fc_stage_copy(const StageCopyArgs a) {
+    int k = 0;
+    while (k + 1 < a.count && (int)blockIdx.x >= a.first[k + 1]) ++k;
+    const int i = ((int)blockIdx.x - a.first[k]) * 256 + threadIdx.x;
+    if (i < a.n[k]) a.dst[k][i] = a.src[k][i];
 }
 
-// a layer's input and output gradient of micro-batch `slot` into the staging areas (xs [slots][m][H][W][Cin],
-// dzs [slots][m][Ho][Wo][Cout], bf16; both sizes are multiples of 16 bytes)
-hipError_t stage_operands(const ConvGeom& g, const void* x, const void* dz, void* xs, void* dzs, int slot, hipStream_t st) {
-    const int nx = (int)((size_t)g.rows_in() * g.Cin * 2 / 16), nd = (int)((size_t)g.rows_out() * g.Cout * 2 / 16);
-    hipLaunchKernelGGL(fc_stage_copy, dim3((unsigned)((nx + nd + 255) / 256)), dim3(256), 0, st, (const uint4*)x,
-                       (uint4*)xs + (size_t)slot * nx, nx, (const uint4*)dz, (uint4*)dzs + (size_t)slot * nd, nd);
+// layers' input and output gradient of micro-batch `slot` into the staging areas (xs [slots][m][H][W][Cin], dzs
+// [slots][m][Ho][Wo][Cout], bf16; both sizes are multiples of 16 bytes)
+hipError_t stage_operands(const StageCopy* c, int n, int slot, hipStream_t st) {
+    if (n > LPM_WGRAD_GROUP) return hipErrorInvalidValue;
+    StageCopyArgs a{};
+    int blocks = 0;
+    auto add = [&](const void* src, void* dst, int64_t elems) {
+        const int k = (int)(elems * 2 / 16);
+        a.src[a.count] = (const uint4*)src;
+        a.dst[a.count] = (uint4*)dst + (size_t)slot * k;
+        a.n[a.count] = k;
+        a.first[a.count++] = blocks;
+        blocks += (k + 255) / 256;
+    };
+    for (int i = 0; i < n; ++i) {
+        add(c[i].x, c[i].xs, c[i].g.rows_in() * c[i].g.Cin);
+        add(c[i].dz, c[i].dzs, c[i].g.rows_out() * c[i].g.Cout);
+    }
+    hipLaunchKernelGGL(fc_stage_copy, dim3((unsigned)blocks), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

@@ -196,8 +196,7 @@ extern "C" int32_t lpm_layerwise_backward(lpm_layerwise* L, const void* x, const
         if (dx)
             LPM_HIP(launch_conv_dgrad(L->dtype, L->gs, dzi, (const char*)w + i * w_slice, wt ? (const char*)wt + i * w_slice : nullptr,
                                       dxparts + i * L->dx_bytes, 0, nullptr, nullptr, scratch + i * L->bwd_ws, sub[i]));
-        LPM_HIP(launch_conv_wgrad(L->dtype, L->gs, x, dzi, dw + i * dw_slice, nullptr, nullptr, accumulate != 0,
-                                  scratch + i * L->bwd_ws, sub[i]));
+        LPM_HIP(launch_conv_wgrad(L->dtype, WgradTask{L->gs, x, dzi, dw + i * dw_slice, nullptr, nullptr, accumulate != 0, scratch + i * L->bwd_ws}, sub[i]));
         LPM_HIP(hipEventRecord(L->join[i], sub[i]));
     }
     for (int i = 0; i < L->n; ++i) LPM_HIP(hipStreamWaitEvent(st, L->join[i], 0));

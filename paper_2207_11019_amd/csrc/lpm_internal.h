@@ -132,10 +132,16 @@ bool dgrad_scales_dz(int dtype, const ConvGeom& g);
 bool dgrad_has_side(int dtype, const ConvGeom& g);
 bool dgrad_can_unpool(int dtype, const ConvGeom& g);
 // dw (+)= sum over pixels of dz (x) x         ws: split-reduction partials (wgrad_ws_bytes)
-// dbias (may be NULL, only when wgrad_fuses_bias): dbias (+)= sum over pixels of dz
+// db (may be NULL, only when wgrad_fuses_bias): db (+)= sum over pixels of dz
 // rscale (may be NULL): dz is the gradient before the layer's per-channel scale; row co of dw is multiplied by rscale[co]
-// deferred (may be NULL): when the kernel leaves split partials, describe their reduction there instead of launching
-// it (deferred->splits stays 0 when nothing is left to do); the caller runs launch_reduce_batch later on the stream.
+struct WgradTask {
+    ConvGeom g;
+    const void* x; const void* dz;
+    float* dw; float* db;
+    const float* rscale;
+    int accumulate;
+    void* ws;
+};
 struct ReduceDesc {
     const float* part; size_t stride; int splits;      // partial s of output i at part[s*stride + i]
     float* dst; int64_t n;                              // dst[i] (+)= sum_s part, i < n
@@ -143,8 +149,11 @@ struct ReduceDesc {
     const float* rscale; int row_len;                   // (may be NULL) the sum of output i is multiplied by rscale[i / row_len]
     int accumulate;
 };
-hipError_t launch_conv_wgrad(int dtype, const ConvGeom& g, const void* x, const void* dz, float* dw, float* dbias,
-                             const float* rscale, int accumulate, void* ws, hipStream_t st, ReduceDesc* deferred = nullptr);
+hipError_t launch_conv_wgrad(int dtype, const WgradTask& t, hipStream_t st);
+// The weight gradients of n <= LPM_WGRAD_GROUP layers, in as few launches as their kernels allow.  red[i]: the reduction that task i
+// leaves to the caller (splits 0: none), who runs launch_reduce_batch later on the stream.
+constexpr int LPM_WGRAD_GROUP = 8;
+hipError_t launch_wgrad_group(int dtype, const WgradTask* t, int n, hipStream_t st, ReduceDesc* red);
 constexpr int LPM_REDUCE_BATCH = 24;
 // the reductions of up to LPM_REDUCE_BATCH weight gradients in one launch (each in its fixed split order)
 hipError_t launch_reduce_batch(const ReduceDesc* d, int count, hipStream_t st);
@@ -155,10 +164,14 @@ hipError_t launch_reduce_batch(const ReduceDesc* d, int count, hipStream_t st);
 constexpr int LPM_FC_STAGE_SLOTS = 32;
 bool wgrad_staged_ok(int dtype, const ConvGeom& g);
 size_t wgrad_staged_ws_bytes(int dtype, const ConvGeom& g);      // split partials of the contraction, any slot count
-hipError_t stage_operands(const ConvGeom& g, const void* x, const void* dz, void* xs, void* dzs, int slot, hipStream_t st);
-// dw (+)= the gradient over `slots` staged micro-batches starting at xs / dzs; `deferred` as for launch_conv_wgrad
-hipError_t launch_wgrad_staged(int dtype, const ConvGeom& g, const void* xs, const void* dzs, int slots, float* dw, float* dbias,
-                               const float* rscale, int accumulate, void* ws, hipStream_t st, ReduceDesc* deferred);
+// files n layers' operands of a micro-batch: x and dz of `g` to slot `slot` of xs and dzs, one launch
+struct StageCopy { ConvGeom g; const void* x; const void* dz; void* xs; void* dzs; };
+hipError_t stage_operands(const StageCopy* c, int n, int slot, hipStream_t st);
+// the staged micro-batches of a layer as one larger batch in the same layout
+inline ConvGeom staged_geom(const ConvGeom& g, int slots) { ConvGeom b = g; b.m = g.m * slots; return b; }
+bool fc_staged_ok(const ConvGeom& g);      // ... contracted by a kernel of its own
+hipError_t fc_wgrad_staged(const ConvGeom& g, const void* xs, const void* dzs, int slots, float* dw, float* dbias,
+                           const float* rscale, int accumulate, hipStream_t st);
 bool wgrad_fuses_bias(int dtype, const ConvGeom& g);
 bool dgrad_uses_wt(int dtype, const ConvGeom& g);
 size_t wgrad_ws_bytes(int dtype, const ConvGeom& g);

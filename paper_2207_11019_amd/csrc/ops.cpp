@@ -68,7 +68,7 @@ extern "C" int32_t lpm_conv_wgrad(const lpm_conv_geom* g, int32_t dtype, const v
     if (!x || !dz || !dw) return fail(LPM_EINVAL, "NULL argument");
     if (wgrad_ws_bytes(dtype, cg) && !ws) return fail(LPM_EINVAL, "scratch required");
     if (bad_align({x, dz, dw, ws})) return fail(LPM_EALIGN, "device buffers must be 256-byte aligned");
-    LPM_HIP(launch_conv_wgrad(dtype, cg, x, dz, dw, nullptr, nullptr, accumulate != 0, ws, (hipStream_t)stream));
+    LPM_HIP(launch_conv_wgrad(dtype, WgradTask{cg, x, dz, dw, nullptr, nullptr, accumulate != 0, ws}, (hipStream_t)stream));
     return LPM_OK;
 }
 
@@ -114,7 +114,7 @@ extern "C" int32_t lpm_conv_wgrad_static(const lpm_conv_geom* g, int32_t dtype, 
     void* ws = nullptr;
     if ((rc = static_scratch(&ws))) return rc;
     // (every partial sum a reduction reads is written by the contraction of the same call: nothing has to start at zero)
-    LPM_HIP(launch_conv_wgrad(dtype, cg, x, dz, dw, nullptr, nullptr, accumulate != 0, ws, (hipStream_t)stream));
+    LPM_HIP(launch_conv_wgrad(dtype, WgradTask{cg, x, dz, dw, nullptr, nullptr, accumulate != 0, ws}, (hipStream_t)stream));
     return LPM_OK;
 }
 

@@ -22,6 +22,13 @@ static bool bias_in_wgrad_ok(int dtype, const LayerRt& lr) {
 // ... or the weight phase can sum it from dz in a kernel of its own
 static bool bias_from_dz_ok(const LayerRt& lr) { return lr.dz_unscaled || !(lr.d.flags & LPM_SCALE); }
 
+// Layers whose weight gradients share launches, and their operations at most (float: a sixteenth; a layer of more is on its own and
+// fills the card).  With 10 / 16 / 24 / 40 G operations, in us per step: R50 conv4_x at 64 1719 / 1711 / 1623 / 1626, ResNet-18/CIFAR
+// 2857 / 2838 / 2847 / 2845; VGG-16/224 6706 / 6735 / 6800 with none / 20 / 24; with 4 / 8 / 16 layers 1710 / 1623 / 1655 and 2921 / 2892 / 2907.
+constexpr int32_t WG_LAYERS = 8;
+constexpr double WG_WORK = 20e9;
+static_assert(WG_LAYERS <= LPM_WGRAD_GROUP, "a launch takes that many");
+
 static bool misaligned(const void* p) { return ((uintptr_t)p & 255u) != 0; }
 
 extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t first, int32_t last,
@@ -247,6 +254,22 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
         if ((pl.h_in & 1) || (pl.w_in & 1) || !fwd_can_pool(dtype, lr.g)) continue;
         lr.pool_fwd = i + 1;
         s->Ly(i + 1).pooled_fwd = true;
+    }
+    // Weight gradients are launched in groups of consecutive layers (the same groups in every form of the backward pass: what a
+    // launch holds decides how its reductions are cut): up to eight layers, as long as they are small enough to be better off together;
+    // next to the network's input, where the micro-batch waits for the last weight gradient, one and two.
+    {
+        int32_t n = 0, groups = 0;
+        double work = 0;
+        for (int32_t i = first; i < last; ++i) {           // from the stage's input up: the backward pass ends there
+            LayerRt& lr = s->Ly(i);
+            if (!has_weights(lr.d)) continue;
+            const double w = 2. * (double)lr.g.rows_out() * lr.g.Cout * lr.g.K() * (dtype == LPM_F32 ? 16 : 1);
+            if (n == (first == 0 && groups < 3 ? groups : WG_LAYERS) || (n > 0 && work + w > WG_WORK)) { n = 0; work = 0; }
+            if (n == 0) { lr.wg_end = true; ++groups; }
+            ++n;
+            work += w;
+        }
     }
     s->n_trainable = off;
     if (dtype == LPM_BF16) {                   // transposed copies follow the mirrored region
@@ -498,9 +521,8 @@ extern "C" int32_t lpm_stage_backward(lpm_stage* s, const void* x, const void* y
 // stands at the same point.  weights_done: an event for the end of the weight phase on wstream.
 // While `stream` is being captured the weight gradients stay on it and are taken out of its dependency
 // frontier instead.
-// wstream2 (with wstream, eager only): every other weight gradient of the phase runs on this second stream, forked from
-// wstream at the start of the phase and joined back into it before the reduction of the partial sums -- a weight
-// gradient is some 250 blocks and half fixed cost, so two of them side by side fill what one leaves idle.
+// wstream2 (with wstream, eager only): every other group of weight gradients of the phase runs on this second stream, forked from
+// wstream at the start of the phase and joined back into it before the reduction of the partial sums.
 int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const void* dy, void* dx,
                               const float* params, const void* lowp, const void* stash, float* grads,
                               int32_t accumulate, void* bwd_ws, void* stream, void* wstream, int32_t parity,
@@ -537,8 +559,8 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
     if (!do_data && (!do_weights || !wstream)) return fail(LPM_EINVAL, "internal: bad phase selection");
     if (do_data && s->bwd_counts && !counts_zeroed) LPM_HIP(launch_zero_counts(&counts, 1, st));
     // layer_slot >= 0 (the two phases come as separate calls with the same slot): the data phase records, per weight
-    // layer, the point in its stream where that layer's output gradient is final, and the weight phase waits for
-    // that point before the layer's weight gradient instead of for the end of the data phase
+    // layer that ends a group, the point in its stream where that layer's output gradient is final, and the weight phase waits for
+    // that point before the group's weight gradients instead of for the end of the data phase
     const bool by_layer = layer_slot >= 0 && deferred && (do_data != do_weights);
     // Both phases in one call on two streams: each weight gradient is enqueued on the second stream as soon as the layer's output
     // gradient is final, and runs beside the rest of the data phase (width-48 ResNet at 13 samples, one micro-batch after the
@@ -559,7 +581,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                 // (a layer without ReLU, scale or shortcut of its own launches nothing ahead of its weight gradient either)
                 const bool plain = !(q.d.flags & LPM_RELU) && (!(q.d.flags & LPM_SCALE) || q.dz_unscaled) && q.d.add_src == LPM_NONE;
                 if (!q.fused_in && !plain) return nullptr;
-                if (points) return layer_ev(k);
+                if (points) return q.wg_end ? layer_ev(k) : nullptr;
                 return k == first && q.d.src < first && !dx ? data_done : nullptr;
             }
             if (!(q.d.kind == LPM_MAXPOOL2 && q.unpooled)) return nullptr;
@@ -569,33 +591,49 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
     // bias_g != NULL: the layer's bias gradient is a plain column sum of bias_g that nothing in the data phase needs and its
     // weight-gradient kernel does not make; it runs in the weight phase, ahead of that kernel (scratch: the layer's own area)
     struct WgradJob { const LayerRt* lr; const void* xin; const void* dz; float* wdb; const float* sc; const void* bias_g; float* bias_db; };
-    // One weight gradient on stream q.  fc_slot = j >= 0 (of fc_flush = M micro-batches): a layer with staging areas
+    // The weight gradients of a group on stream q.  fc_slot = j >= 0 (of fc_flush = M micro-batches): a layer with staging areas
     // files its operands under slot j and contracts a group of slots at a time; the first group overwrites the accumulator.
-    auto one_wgrad = [&](const WgradJob& j, hipStream_t q, ReduceDesc* d) -> hipError_t {
-        const LayerRt& lr = *j.lr;
-        if (j.bias_g) {
-            const hipError_t e = launch_epilogue_bwd(s->dtype, lr.g.rows_out(), lr.d.cout, j.bias_g, nullptr, nullptr, nullptr, nullptr, 0,
-                                                     j.bias_db, acc, (char*)wws + lr.wws_off, q);
-            if (e != hipSuccess) return e;
+    std::vector<WgradJob> jobs;            // the weight phase's layers, last layer first; a group's unless it is launched at the end
+    auto run_group = [&](size_t from, size_t to, hipStream_t q) -> hipError_t {
+        WgradTask t[LPM_WGRAD_GROUP];
+        StageCopy copy[LPM_WGRAD_GROUP];
+        ReduceDesc d[LPM_WGRAD_GROUP]{};
+        int n = 0, nc = 0;
+        hipError_t e;
+        for (size_t k = from; k < to; ++k) {
+            const WgradJob& j = jobs[k];
+            const LayerRt& lr = *j.lr;
+            if (j.bias_g && (e = launch_epilogue_bwd(s->dtype, lr.g.rows_out(), lr.d.cout, j.bias_g, nullptr, nullptr, nullptr, nullptr, 0,
+                                                     j.bias_db, acc, (char*)wws + lr.wws_off, q)) != hipSuccess) return e;
+            if (fc_slot >= 0 && lr.fcs_x_off != NO) copy[nc++] = StageCopy{lr.g, j.xin, j.dz, ws + lr.fcs_x_off, ws + lr.fcs_dz_off};
         }
-        if (fc_slot >= 0 && lr.fcs_x_off != NO) {
-            d->splits = 0;
-            hipError_t e = stage_operands(lr.g, j.xin, j.dz, ws + lr.fcs_x_off, ws + lr.fcs_dz_off, fc_slot, q);
-            if (e != hipSuccess) return e;
+        if (nc && (e = stage_operands(copy, nc, fc_slot, q)) != hipSuccess) return e;
+        for (size_t k = from; k < to; ++k) {
+            const WgradJob& j = jobs[k];
+            const LayerRt& lr = *j.lr;
+            float* dw = grads + lr.w_off;
+            void* part = (char*)wws + lr.wws_off;
+            if (!(fc_slot >= 0 && lr.fcs_x_off != NO)) {
+                t[n++] = WgradTask{lr.g, j.xin, j.dz, dw, j.wdb, j.sc, acc, part};
+                continue;
+            }
             // Contract in groups of G micro-batches.  One group (G = M) touches dW once, but all of that work then sits
             // behind the last micro-batch, where nothing overlaps it; two groups leave half of it there.  Gradient
             // matrices of 64 MiB and more are bound by their own traffic and keep the single pass.
             const int32_t M = fc_flush;
             const int32_t G = ((size_t)lr.w_count * 4 >= ((size_t)64 << 20)) ? M : std::max(1, (M + 1) / 2);
-            if ((fc_slot + 1) % G != 0 && fc_slot != M - 1) return hipSuccess;
-            const int32_t j0 = (fc_slot / G) * G;
-            const size_t xb = (size_t)lr.g.rows_in() * lr.g.Cin * 2, db = (size_t)lr.g.rows_out() * lr.g.Cout * 2;
-            return launch_wgrad_staged(s->dtype, lr.g, ws + lr.fcs_x_off + (size_t)j0 * xb, ws + lr.fcs_dz_off + (size_t)j0 * db,
-                                       fc_slot - j0 + 1, grads + lr.w_off, j.wdb, j.sc, j0 > 0, (char*)wws + lr.wws_off, q, d);
+            if ((fc_slot + 1) % G != 0 && fc_slot != M - 1) continue;
+            const int32_t j0 = (fc_slot / G) * G, slots = fc_slot - j0 + 1;
+            const char* xs = ws + lr.fcs_x_off + (size_t)j0 * lr.g.rows_in() * lr.g.Cin * 2;
+            const char* dzs = ws + lr.fcs_dz_off + (size_t)j0 * lr.g.rows_out() * lr.g.Cout * 2;
+            if (fc_staged_ok(lr.g)) {
+                if ((e = fc_wgrad_staged(lr.g, xs, dzs, slots, dw, j.wdb, j.sc, j0 > 0, q)) != hipSuccess) return e;
+            } else t[n++] = WgradTask{staged_geom(lr.g, slots), xs, dzs, dw, j.wdb, j.sc, j0 > 0, part};
         }
-        return launch_conv_wgrad(s->dtype, lr.g, j.xin, j.dz, grads + lr.w_off, j.wdb, j.sc, acc, (char*)wws + lr.wws_off, q, d);
+        if (n && (e = launch_wgrad_group(s->dtype, t, n, q, d)) != hipSuccess) return e;
+        for (int k = 0; k < n; ++k) if (d[k].splits > 0) red.push_back(d[k]);
+        return hipSuccess;
     };
-    std::vector<WgradJob> jobs;            // eager: the weight phase, in layer order (last layer first)
     std::vector<hipGraphNode_t> wtail;     // capture: frontier left by the last weight gradient
     auto frontier = [&](std::vector<hipGraphNode_t>& out) -> hipError_t {
         hipStreamCaptureStatus stt;
@@ -665,7 +703,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                         if (need_dz) dz = gw + lr.dz_off;
                     }
                 }
-                if (points && at_point != layer_ev(i)) {
+                if (points && lr.wg_end && at_point != layer_ev(i)) {
                     LPM_HIP(hipEventRecord(layer_ev(i), st));
                     at_point = layer_ev(i);
                 }
@@ -733,21 +771,20 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                     have[gi(l.src)] = 1;
                 }
                 const void* xin = tptr(s, l.src, x, y, stash);
-                if (beside) {
-                    ReduceDesc d{};
+                jobs.push_back(WgradJob{&lr, xin, dz, wdb, lr.dz_unscaled ? sc : nullptr, bias_g, bias_g ? dbias : nullptr});
+                if (beside && lr.wg_end) {
                     LPM_HIP(hipStreamWaitEvent(wst, layer_ev(i), 0));
-                    LPM_HIP(one_wgrad(WgradJob{&lr, xin, dz, wdb, lr.dz_unscaled ? sc : nullptr, bias_g, bias_g ? dbias : nullptr}, wst, &d));
-                    if (d.splits > 0) red.push_back(d);
-                } else if (deferred) {
-                    jobs.push_back(WgradJob{&lr, xin, dz, wdb, lr.dz_unscaled ? sc : nullptr, bias_g, bias_g ? dbias : nullptr});
-                } else {
+                    LPM_HIP(run_group(0, jobs.size(), wst));
+                    jobs.clear();
+                } else if (!deferred && lr.wg_end) {
                     std::vector<hipGraphNode_t> before;
                     LPM_HIP(frontier(before));
                     if (!wtail.empty())       // weight gradients share one scratch area: keep them in a chain
                         LPM_HIP(hipStreamUpdateCaptureDependencies(st, wtail.data(), wtail.size(), hipStreamAddCaptureDependencies));
-                    ReduceDesc d{};           // (the same kernels and sums as an eager pass, a reduction per layer)
-                    LPM_HIP(one_wgrad(WgradJob{&lr, xin, dz, wdb, lr.dz_unscaled ? sc : nullptr, bias_g, bias_g ? dbias : nullptr}, st, &d));
-                    if (d.splits > 0) LPM_HIP(launch_reduce_batch(&d, 1, st));
+                    LPM_HIP(run_group(0, jobs.size(), st));      // (the same kernels and sums as an eager pass, a reduction per group)
+                    if (!red.empty()) LPM_HIP(launch_reduce_batch(red.data(), (int)red.size(), st));
+                    red.clear();
+                    jobs.clear();
                     LPM_HIP(frontier(wtail));
                     LPM_HIP(hipStreamUpdateCaptureDependencies(st, before.data(), before.size(), hipStreamSetCaptureDependencies));
                 }
@@ -829,21 +866,20 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
         *data_point = at_point;
     }
     if (do_weights && (beside || !jobs.empty())) {
-        red.reserve(jobs.size());
-        hipStream_t wst2 = (wstream && wstream2 && deferred && jobs.size() > 1) ? (hipStream_t)wstream2 : nullptr;
+        hipStream_t wst2 = (wstream && wstream2 && deferred && jobs.size() > (size_t)WG_LAYERS) ? (hipStream_t)wstream2 : nullptr;
         if (wst2 == wst) wst2 = nullptr;
         if (wst2) {        // ordered after everything the phase's stream holds (the previous micro-batch's reduction reads the areas written now)
             LPM_HIP(hipEventRecord(s->ev_w2_fork, wst));
             LPM_HIP(hipStreamWaitEvent(wst2, s->ev_w2_fork, 0));
         }
-        size_t k = 0;
-        for (const WgradJob& j : jobs) {
-            ReduceDesc d{};
-            hipStream_t q = (wst2 && (k++ & 1)) ? wst2 : wst;
+        int groups = 0;
+        for (size_t k = 0, from = 0; k < jobs.size(); ++k) {
+            if (!jobs[k].lr->wg_end) continue;
+            hipStream_t q = (wst2 && (groups++ & 1)) ? wst2 : wst;
             if (by_layer)
-                LPM_HIP(hipStreamWaitEvent(q, s->ev_layer[(size_t)(j.lr - &s->lay[0]) * LPM_MAX_WINDOW + layer_slot], 0));
-            LPM_HIP(one_wgrad(j, q, &d));
-            if (d.splits > 0) red.push_back(d);
+                LPM_HIP(hipStreamWaitEvent(q, s->ev_layer[(size_t)(jobs[k].lr - &s->lay[0]) * LPM_MAX_WINDOW + layer_slot], 0));
+            LPM_HIP(run_group(from, k + 1, q));
+            from = k + 1;
         }
         if (wst2) {
             LPM_HIP(hipEventRecord(s->ev_w2_join, wst2));

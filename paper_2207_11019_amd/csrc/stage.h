@@ -34,6 +34,7 @@ struct LayerRt {
                                                  // writes that layer's shortcut gradient writes this layer's dz instead
     bool shortcut_is_dz = false;                 // its shortcut's gradient is this layer's dz, element for element, and is only read: it is not
                                                  // stored a second time (fused_in, or the stage's last layer when the next stage hands down its dz)
+    bool wg_end = false;                         // the last layer, in backward order, of a group whose weight gradients share launches
     int32_t pool_fwd = -1;                       // conv/FC: index of the max-pooling layer whose forward its own forward kernel performs
     bool pooled_fwd = false;                     // max-pooling: its forward runs inside its producer's forward kernel
     bool unpooled = false;                       // max-pooling: its backward runs inside its consumer's data gradient

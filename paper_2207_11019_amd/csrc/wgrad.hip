@@ -31,6 +31,7 @@
 #include "elem.h"
 #include "lds_dma.h"
 #include <algorithm>
+#include <cmath>
 
 namespace lpm {
 
@@ -55,7 +56,7 @@ struct WgArgs {
     int units;             // m * Do * Ho * TW
     int kt_total, kt_per_split, splits;
     int accumulate;
-    int co_tiles, ci_tiles, tap_groups;
+    int co_tiles, ci_tiles, tap_groups, kind;
 };
 
 // four rows of the column a lane ends up with (see above)
@@ -65,8 +66,9 @@ __device__ __forceinline__ u32x2_ tr4(const unsigned char* p) {
 
 enum { LIN = 0, PIX = 1, ROW3 = 3 };
 
+// One block: tile `tile` of dW (all of them, tap groups included) over pixel range `split`.
 template <typename E, int BM, int BN, int KIND, int NST>
-__global__ void __launch_bounds__(512, 1) wgrad_mm(WgArgs p) {
+__device__ __forceinline__ void wgrad_tile(const WgArgs p, int tile, const int split) {
     constexpr int TAPS = KIND == ROW3 ? 3 : 1, WGM = 2, WGN = 2;
     constexpr int ES = sizeof(E), T = 512, KT = ES == 2 ? 64 : 32;
     constexpr int WTM = BM / WGM, WTN = BN / WGN, MI = WTM / 32, NI = WTN / 32;
@@ -87,10 +89,6 @@ __global__ void __launch_bounds__(512, 1) wgrad_mm(WgArgs p) {
     uint4* rec3 = reinterpret_cast<uint4*>(lds + NST * STAGE + DUMP);                // ROW3: dz offset, its pixels; x offset, mask of its pixels
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // all blocks of one pixel range go to one XCD (they read the same dz and x rows)
-    const int v_id = xcd_remap((int)(blockIdx.z * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.z));
-    const int split = v_id / (int)gridDim.x;
-    int tile = v_id - split * (int)gridDim.x;
     const int ci_t = tile % p.ci_tiles; tile /= p.ci_tiles;
     const int grp = tile % p.tap_groups;
     const int co_t = tile / p.tap_groups;
@@ -435,39 +433,114 @@ __global__ void __launch_bounds__(512, 1) wgrad_mm(WgArgs p) {
 }
 
 // --------------------------------------------------------------------------------------------------
-struct WgPlan { int taps, big, groups, co_tiles, ci_tiles, TW, kt_total, kt_per, splits; };
+// The weight gradients of several layers in one launch: the blocks of all of them fill the card together, so a layer need not be
+// cut into as many pixel ranges as would do that alone (partial sums written, and read by the reduction), tiles of dW may be
+// larger, and the host enqueues one kernel behind one event where it had one of each per layer -- a wait for an event of
+// another stream is 10 us of host time.  Per step with a launch per layer / with groups, in us: ResNet-18/CIFAR 3259 / 2873, its
+// width-48 form 2693 / 2445, R50 conv4_x at 64 1711 / 1660, volumetric 1738 / 1690, VGG-16/CIFAR 1869 / 1857,
+// VGG-16/224 6706 / 6666.
+// Registers: at most 128 for the 64-channel tiles, so that two wavefronts of a block, a contraction's and another stream's
+// fit a SIMD's 512 (131 instead of 119 cost ResNet-18/CIFAR 2.5 %); the arguments come by value, by reference they cost those twelve.
+struct WgGroup {
+    int count;
+    int first[LPM_WGRAD_GROUP + 1];          // first block of every layer
+    WgArgs d[LPM_WGRAD_GROUP];
+};
 
-// shared: the launch runs beside other streams' kernels (a backward pass, whose reductions are batched)
-static WgPlan plan_wgrad(int dtype, const ConvGeom& g, bool shared) {
+// Tiles of 64 x 64 channels; BIG: 128 x 128 (see plan_group).
+template <typename E, bool BIG>
+__global__ void __launch_bounds__(512, BIG ? 3 : 4) wgrad_many(const WgGroup a) {
+    const int v = xcd_remap((int)blockIdx.x, (int)gridDim.x);      // (as below)
+    int k = 0;
+    while (k + 1 < a.count && v >= a.first[k + 1]) ++k;
+    const WgArgs& p = a.d[k];
+    const int local = v - a.first[k], n = p.co_tiles * p.ci_tiles * p.tap_groups, split = local / n, tile = local - split * n;
+    constexpr int B = BIG ? 128 : 64, NST = BIG ? 4 : 3;
+    if (p.kind == LIN) wgrad_tile<E, B, B, LIN, NST>(p, tile, split);
+    else if (p.kind == PIX) wgrad_tile<E, B, B, PIX, NST>(p, tile, split);
+    else if constexpr (sizeof(E) == 2 && !BIG) wgrad_tile<E, 64, 64, ROW3, NST>(p, tile, split);
+}
+template <typename E, int BM, int BN, int KIND, int NST>
+__global__ void __launch_bounds__(512, BM == 64 ? 4 : 3) wgrad_mm(WgArgs p) {
+    // all blocks of one pixel range go to one XCD (they read the same dz and x rows)
+    const int v = xcd_remap((int)(blockIdx.z * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.z)), split = v / (int)gridDim.x;
+    wgrad_tile<E, BM, BN, KIND, NST>(p, v - split * (int)gridDim.x, split);
+}
+constexpr int wg_lds(int es, int bm, int bn, int kind, int nst) {
+    const int kt = es == 2 ? 64 : 32;
+    return nst * (kt * bm * es + (kind == ROW3 ? 80 : kt) * bn * es) + (kind == LIN ? 0 : kind == ROW3 ? 1024 + 256 * 16 : 1024 * 4);
+}
+
+struct WgPlan { int kind, big, groups, co_tiles, ci_tiles, TW, kt_total, kt_per, splits; };
+
+static WgPlan plan_tiles(int dtype, const ConvGeom& g) {
     WgPlan pl{};
     const int tx = (g.Wo + 7) / 8;
     // a filter row per block where the row segments are mostly real pixels
     const bool row3 = dtype == LPM_BF16 && g.Kh == 3 && g.Kw == 3 && g.stride == 1 && g.Wo * 10 >= tx * 8 * 8;
-    pl.taps = row3 ? 3 : 1;
-    pl.groups = g.taps() / pl.taps;
+    pl.kind = row3 ? ROW3 : g.taps() == 1 && g.stride == 1 && g.pad == 0 && g.pad_d == 0 ? LIN : PIX;
+    pl.groups = g.taps() / (row3 ? 3 : 1);
     pl.TW = row3 ? tx : g.Wo;
     const int64_t units = (int64_t)g.m * g.Do * g.Ho * pl.TW, ku = row3 ? 8 : dtype == LPM_BF16 ? 64 : 32;
     pl.kt_total = (int)((units + ku - 1) / ku);
-    pl.big = dtype == LPM_BF16 && !row3 && g.Cout >= 128 && g.Cin >= 128 &&
-             (int64_t)((g.Cout + 127) / 128) * ((g.Cin + 127) / 128) * pl.groups * std::max(1, pl.kt_total / 16) >= 192;
-    const int t = pl.big ? 128 : 64;
-    pl.co_tiles = (g.Cout + t - 1) / t;
-    pl.ci_tiles = (g.Cin + t - 1) / t;
-    const int64_t base = (int64_t)pl.co_tiles * pl.ci_tiles * pl.groups;
-    const int64_t out_bytes = ((int64_t)g.Cout * g.K() + g.Cout) * 4;
-    // A block per CU when the launch has the card to itself.  Beside the forward and data-phase kernels the CUs it leaves are not
-    // idle, and every block writes partial sums that the reduction reads: 192 blocks, 128 of the four times larger tiles.  Per
-    // step with 256 / 192 / 128 for both, in us: ResNet-18/CIFAR 3440 / 3360 / 3304, VGG-16/224 6850 / 6805 / 6918, volumetric 1758 / 1764 /
-    // 1798; 128-channel tiles alone at 128: R50 conv4_x at 512 7240 -> 7066.
-    const int64_t want = shared ? (pl.big ? 128 : 192) : 256;
-    int64_t sp = std::max<int64_t>(1, want / base);
-    if (base * sp < want * 3 / 4) sp = std::max<int64_t>(sp, want * 7 / 4 / base);
-    // at least eight K tiles per block, four where that leaves fewer than eight ranges: every range costs a pass over dW
-    sp = std::min<int64_t>(sp, std::max(std::max(1, pl.kt_total / 8), std::min(8, pl.kt_total / 4)));
-    sp = std::min<int64_t>(sp, std::max<int64_t>(1, (64ll << 20) / out_bytes));
+    pl.co_tiles = (g.Cout + 63) / 64;
+    pl.ci_tiles = (g.Cin + 63) / 64;
+    return pl;
+}
+static WgPlan big_tiles(const ConvGeom& g, WgPlan pl) {
+    pl.big = 1;
+    pl.co_tiles = (g.Cout + 127) / 128;
+    pl.ci_tiles = (g.Cin + 127) / 128;
+    return pl;
+}
+static int64_t wg_tiles(const WgPlan& pl) { return (int64_t)pl.co_tiles * pl.ci_tiles * pl.groups; }
+static void set_splits(WgPlan& pl, int64_t sp) {
     pl.kt_per = (int)((pl.kt_total + sp - 1) / sp);
     pl.splits = (pl.kt_total + pl.kt_per - 1) / pl.kt_per;
+}
+// at least eight K tiles per block, four where that leaves fewer than eight ranges: every range costs a pass over dW
+static int64_t most_splits(const ConvGeom& g, const WgPlan& pl) {
+    const int64_t out_bytes = ((int64_t)g.Cout * g.K() + g.Cout) * 4;
+    return std::min<int64_t>(std::max(std::max(1, pl.kt_total / 8), std::min(8, pl.kt_total / 4)), std::max<int64_t>(1, (64ll << 20) / out_bytes));
+}
+
+// One layer's launch.  A block per CU when it has the card to itself.  Beside the forward and data-phase kernels the CUs it leaves
+// are not idle, and every block writes partial sums that the reduction reads: 192 blocks, 128 of the four times larger tiles.
+// Per step with 256 / 192 / 128 for both, in us: ResNet-18/CIFAR 3440 / 3360 / 3304, VGG-16/224 6850 / 6805 / 6918, volumetric
+// 1758 / 1764 / 1798; 128-channel tiles alone at 128: R50 conv4_x at 512 7240 -> 7066.
+static WgPlan plan_wgrad(int dtype, const ConvGeom& g, bool shared) {
+    WgPlan pl = plan_tiles(dtype, g);
+    if (dtype == LPM_BF16 && pl.kind != ROW3 && g.Cout >= 128 && g.Cin >= 128 && wg_tiles(big_tiles(g, pl)) * std::max(1, pl.kt_total / 16) >= 192) pl = big_tiles(g, pl);
+    const int64_t base = wg_tiles(pl), want = shared ? (pl.big ? 128 : 192) : 256;
+    int64_t sp = std::max<int64_t>(1, want / base);
+    if (base * sp < want * 3 / 4) sp = std::max<int64_t>(sp, want * 7 / 4 / base);
+    set_splits(pl, std::min(sp, most_splits(g, pl)));
     return pl;
+}
+// pixel ranges that the scratch of a layer holds partial sums of
+static int room_for(int dtype, const ConvGeom& g) { return std::max(plan_wgrad(dtype, g, false).splits, plan_wgrad(dtype, g, true).splits); }
+
+// Several layers' launch: cut so that some 192 blocks have the same share of the K tiles, a K tile of a filter row counting twice
+// (128 / 256: within 1 %, either way).  Large tiles, in a launch of their own, where the layers that can have them make 192 blocks
+// of 16 K tiles, and then 64 blocks: few and long, they leave CUs to the other streams (R50 conv4_x at 64, per step: small tiles 1715 us,
+// large ones on 128 / 96 / 64 blocks 1703 / 1690 / 1655; filter rows of 128 x 64 channels as well 1670, but 1 % more on VGG-16/224).
+static void plan_group(int dtype, const WgradTask* t, int n, WgPlan* pl) {
+    auto cost = [](const WgPlan& p) { return (p.kind == ROW3 || p.big ? 2. : 1.) * p.kt_total; };
+    auto large = [&](int i) { return dtype == LPM_BF16 && pl[i].kind != ROW3 && t[i].g.Cout >= 128 && t[i].g.Cin >= 128; };
+    int64_t blocks = 0;
+    for (int i = 0; i < n; ++i) {
+        pl[i] = plan_tiles(dtype, t[i].g);
+        if (large(i)) blocks += wg_tiles(big_tiles(t[i].g, pl[i])) * std::max(1, pl[i].kt_total / 16);
+    }
+    double work[2] = {0, 0};
+    for (int i = 0; i < n; ++i) {
+        if (blocks >= 192 && large(i)) pl[i] = big_tiles(t[i].g, pl[i]);
+        work[pl[i].big] += cost(pl[i]) * wg_tiles(pl[i]);
+    }
+    for (int i = 0; i < n; ++i) {
+        const int64_t sp = (int64_t)std::ceil(cost(pl[i]) * (pl[i].big ? 64 : 192) / work[pl[i].big] - .05);
+        set_splits(pl[i], std::max<int64_t>(1, std::min<int64_t>({sp, most_splits(t[i].g, pl[i]), room_for(dtype, t[i].g)})));
+    }
 }
 
 // channel counts in whole 16-byte chunks, 32-bit byte offsets (with the rows a last K tile reaches past the end)
@@ -480,29 +553,17 @@ bool wgrad_mm_ok(int dtype, const ConvGeom& g) {
 
 static size_t wg_stride(const ConvGeom& g) { return ((size_t)g.Cout * g.K() + g.Cout + 3) & ~(size_t)3; }      // (16-byte loads in the reduction)
 size_t wgrad_mm_ws_bytes(int dtype, const ConvGeom& g) {
-    const int splits = std::max(plan_wgrad(dtype, g, false).splits, plan_wgrad(dtype, g, true).splits);
+    const int splits = room_for(dtype, g);
     return splits > 1 ? (size_t)splits * wg_stride(g) * sizeof(float) : 0;
 }
 
-template <typename E, int BM, int BN, int KIND, int NST>
-static hipError_t go(const WgArgs& a, const WgPlan& pl, hipStream_t st) {
-    constexpr int ES = sizeof(E), KT = ES == 2 ? 64 : 32, rows = KIND == ROW3 ? 80 : KT;
-    constexpr int stage = KT * BM * ES + rows * BN * ES, bytes = NST * stage + (KIND == LIN ? 0 : KIND == ROW3 ? 1024 + 256 * 16 : 1024 * 4);
-    static DeviceSet done;
-    const hipError_t attr = allow_lds(wgrad_mm<E, BM, BN, KIND, NST>, bytes, done);
-    if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((wgrad_mm<E, BM, BN, KIND, NST>), dim3((unsigned)(pl.co_tiles * pl.ci_tiles * pl.groups), 1, pl.splits), dim3(512), bytes, st, a);
-    return hipGetLastError();
-}
-
-hipError_t wgrad_mm_launch(int dtype, const ConvGeom& g, const void* x, const void* dz, float* dw, float* dbias, const float* rscale,
-                           int accumulate, void* ws, hipStream_t st, ReduceDesc* deferred) {
+static WgArgs wg_args(int dtype, const WgradTask& t, const WgPlan& pl) {
+    const ConvGeom& g = t.g;
     const int es = dtype == LPM_BF16 ? 2 : 4;
-    const WgPlan pl = plan_wgrad(dtype, g, deferred != nullptr);
     WgArgs a{};
-    a.X = x; a.DZ = dz;
-    a.out = pl.splits > 1 ? (float*)ws : dw;
-    a.db = dbias; a.rscale = rscale;
+    a.X = t.x; a.DZ = t.dz;
+    a.out = pl.splits > 1 ? (float*)t.ws : t.dw;
+    a.db = t.db; a.rscale = t.rscale;
     a.part_stride = wg_stride(g);
     a.dz_bytes = (unsigned)(g.rows_out() * g.Cout * es); a.x_bytes = (unsigned)(g.rows_in() * g.Cin * es);
     a.Cout = g.Cout; a.Cin = g.Cin; a.Kh = g.Kh; a.Kw = g.Kw; a.Kd = g.Kd;
@@ -512,21 +573,75 @@ hipError_t wgrad_mm_launch(int dtype, const ConvGeom& g, const void* x, const vo
     a.dTW = fast_div(pl.TW); a.dHo = fast_div(g.Ho); a.dDo = fast_div(g.Do);
     a.units = (int)((int64_t)g.m * g.Do * g.Ho * pl.TW);
     a.kt_total = pl.kt_total; a.kt_per_split = pl.kt_per; a.splits = pl.splits;
-    a.accumulate = accumulate;
-    a.co_tiles = pl.co_tiles; a.ci_tiles = pl.ci_tiles; a.tap_groups = pl.groups;
+    a.accumulate = t.accumulate;
+    a.co_tiles = pl.co_tiles; a.ci_tiles = pl.ci_tiles; a.tap_groups = pl.groups; a.kind = pl.kind;
+    return a;
+}
+
+template <typename E, int BM, int BN, int KIND, int NST>
+static hipError_t go(const WgArgs& a, const WgPlan& pl, hipStream_t st) {
+    constexpr int bytes = wg_lds(sizeof(E), BM, BN, KIND, NST);
+    static DeviceSet done;
+    const hipError_t attr = allow_lds(wgrad_mm<E, BM, BN, KIND, NST>, bytes, done);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL((wgrad_mm<E, BM, BN, KIND, NST>), dim3((unsigned)wg_tiles(pl), 1, pl.splits), dim3(512), bytes, st, a);
+    return hipGetLastError();
+}
+static hipError_t run_one(int dtype, const WgradTask& t, const WgPlan& pl, hipStream_t st) {
+    const WgArgs a = wg_args(dtype, t, pl);
+    if (dtype == LPM_F32) return pl.kind == LIN ? go<float, 64, 64, LIN, 3>(a, pl, st) : go<float, 64, 64, PIX, 3>(a, pl, st);
+    if (pl.kind == ROW3) return pl.kt_per >= 64 ? go<bf16_t, 64, 64, ROW3, 4>(a, pl, st) : go<bf16_t, 64, 64, ROW3, 3>(a, pl, st);
+    if (pl.big) return pl.kind == LIN ? go<bf16_t, 128, 128, LIN, 4>(a, pl, st) : go<bf16_t, 128, 128, PIX, 4>(a, pl, st);
+    return pl.kind == LIN ? go<bf16_t, 64, 64, LIN, 3>(a, pl, st) : go<bf16_t, 64, 64, PIX, 3>(a, pl, st);
+}
+template <typename E, bool BIG>
+static hipError_t go_many(const WgradTask* t, const WgPlan* pl, int n, hipStream_t st) {
+    constexpr int B = BIG ? 128 : 64, NST = BIG ? 4 : 3, ES = sizeof(E);
+    constexpr int kinds[4] = {wg_lds(ES, B, B, LIN, NST), wg_lds(ES, B, B, PIX, NST), 0, ES == 2 && !BIG ? wg_lds(ES, 64, 64, ROW3, NST) : 0};
+    WgGroup a{};
+    int blocks = 0, bytes = 0;
+    for (int i = 0; i < n; ++i) {
+        if ((bool)pl[i].big != BIG) continue;
+        a.first[a.count] = blocks;
+        a.d[a.count++] = wg_args(ES == 2 ? LPM_BF16 : LPM_F32, t[i], pl[i]);
+        blocks += (int)(wg_tiles(pl[i]) * pl[i].splits);
+        bytes = std::max(bytes, kinds[pl[i].kind]);
+    }
+    if (!a.count) return hipSuccess;
+    a.first[a.count] = blocks;
+    static DeviceSet done;
+    const hipError_t attr = allow_lds(wgrad_many<E, BIG>, std::max({kinds[LIN], kinds[PIX], kinds[ROW3]}), done);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL((wgrad_many<E, BIG>), dim3((unsigned)blocks), dim3(512), bytes, st, a);
+    return hipGetLastError();
+}
+static ReduceDesc reduction(const WgradTask& t, const WgPlan& pl) {
+    const ConvGeom& g = t.g;
+    if (pl.splits == 1) return ReduceDesc{};
+    return ReduceDesc{(const float*)t.ws, wg_stride(g), pl.splits, t.dw, (int64_t)g.Cout * g.K(), t.db, t.db ? g.Cout : 0, t.rscale, g.K(), t.accumulate};
+}
+
+hipError_t wgrad_mm_launch(int dtype, const WgradTask& t, hipStream_t st) {
+    const WgPlan pl = plan_wgrad(dtype, t.g, false);
+    const hipError_t e = run_one(dtype, t, pl, st);
+    const ReduceDesc d = reduction(t, pl);
+    if (e != hipSuccess || d.splits == 0) return e;
+    return launch_reduce_batch(&d, 1, st);      // (the kernel that also reduces the layers of a group: the same order)
+}
+hipError_t wgrad_mm_group(int dtype, const WgradTask* t, int n, hipStream_t st, ReduceDesc* red) {
+    if (n > LPM_WGRAD_GROUP) return hipErrorInvalidValue;
+    WgPlan pl[LPM_WGRAD_GROUP];
     hipError_t e;
-    const bool lin = g.taps() == 1 && g.stride == 1 && g.pad == 0 && g.pad_d == 0;
-    if (dtype == LPM_F32) e = lin ? go<float, 64, 64, LIN, 3>(a, pl, st) : go<float, 64, 64, PIX, 3>(a, pl, st);
-    else if (pl.taps == 3) e = pl.kt_per >= 64 ? go<bf16_t, 64, 64, ROW3, 4>(a, pl, st) : go<bf16_t, 64, 64, ROW3, 3>(a, pl, st);
-    else if (pl.big) e = lin ? go<bf16_t, 128, 128, LIN, 4>(a, pl, st) : go<bf16_t, 128, 128, PIX, 4>(a, pl, st);
-    else e = lin ? go<bf16_t, 64, 64, LIN, 3>(a, pl, st) : go<bf16_t, 64, 64, PIX, 3>(a, pl, st);
-    if (e != hipSuccess || pl.splits == 1) return e;
-    const int64_t n = (int64_t)g.Cout * g.K();
-    const int nb = dbias ? g.Cout : 0;
-    // one reduction kernel whether it runs now or batched with the stage's other layers: the same summation order
-    const ReduceDesc d{(const float*)ws, a.part_stride, pl.splits, dw, n, dbias, nb, rscale, g.K(), accumulate};
-    if (deferred) { *deferred = d; return hipSuccess; }
-    return launch_reduce_batch(&d, 1, st);
+    if (n == 1) {
+        pl[0] = plan_wgrad(dtype, t[0].g, true);
+        e = run_one(dtype, t[0], pl[0], st);
+    } else {
+        plan_group(dtype, t, n, pl);
+        e = dtype == LPM_F32 ? go_many<float, false>(t, pl, n, st) : go_many<bf16_t, false>(t, pl, n, st);
+        if (e == hipSuccess && dtype == LPM_BF16) e = go_many<bf16_t, true>(t, pl, n, st);
+    }
+    for (int i = 0; i < n; ++i) red[i] = reduction(t[i], pl[i]);
+    return e;
 }
 
 }  // namespace lpm
