@@ -70,6 +70,11 @@ def long_projection(cin, w, mid, h, wd, m):
                  C(mid, w, 1, 1, h - 12, wd, scale=True, src=1, add=2), C(w, mid, 1, 1, h - 12, wd)), m
 
 
+def mixed():
+    return chain(C(16, 24, 3, 3, 14, 14, p=1), C(24, 40, 1, 1, 14, 14), C(40, 40, 3, 3, 14, 14, p=1, scale=True), C(40, 72, 3, 3, 14, 14, s=2, p=1),
+                 C(72, 64, 5, 5, 7, 7, p=2), C(64, 6, 1, 1, 7, 7), C(6, 136, 3, 3, 7, 7, p=1), C(136, 128, 1, 1, 7, 7, scale=True), C(128, 64, 3, 3, 7, 7, p=1))
+
+
 NETS = {
     # bf16: the masked sum of the contributions to a block's output, the gradient of its shortcut and, where two blocks share one, the
     # sum of both -- on every tile of the data gradient, in whole and in ragged row and channel tiles
@@ -101,6 +106,12 @@ NETS = {
     "ranges_rows": ((chain(C(64, 64, 3, 3, 64, 64, p=1, scale=True), C(64, 64, 1, 1, 64, 64, scale=True)), 9), "bf16"),
     "ranges_large": ((chain(C(256, 256, 1, 1, 128, 128, scale=True), C(256, 128, 1, 1, 128, 128)), 3), "bf16"),
     "ranges_float": ((chain(C(16, 32, 3, 3, 40, 40, p=1, scale=True), C(32, 16, 1, 1, 40, 40)), 9), "f32"),
+    # weight gradients that share a launch: every kind of tile beside layers that have kernels of their own, in ragged channel counts
+    # and pixel ranges, and 128-channel tiles
+    "group_mixed": ((mixed(), 5), "bf16"),
+    "group_mixed_float": ((mixed(), 5), "f32"),
+    "group_large": ((chain(C(8, 16, 1, 1, 64, 64), C(16, 16, 1, 1, 64, 64), C(16, 256, 1, 1, 64, 64), C(256, 200, 1, 1, 64, 64, scale=True),
+                           C(200, 256, 1, 1, 64, 64), C(256, 256, 1, 1, 64, 64)), 6), "bf16"),
 }
 
 
