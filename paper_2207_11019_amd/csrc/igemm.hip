@@ -279,9 +279,12 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
     for (int ks = 0; ks < (KS ? 4 : 0); ++ks) ks_c[ks] = (kt0 * kt_ch + (ks * 2 + kh_) * 4) % p.Ci;
     const int ks_step = KS ? kt_ch % p.Ci : 0;
 
-    // Operands of one K tile, 16 bytes per lane and step.  Two sets: while the matrix cores work on one tile the next one is
-    // read from LDS, and the tiles behind it are on their way there -- with one wavefront per SIMD (a launch of about one block
-    // per CU) nothing else hides the LDS latency.
+    // Operands of one K tile, 16 bytes per lane and step.  While the matrix cores work on one tile the next one is read from LDS,
+    // and the tiles behind it are on their way there -- with one wavefront per SIMD (a launch of about one block per CU) nothing else
+    // hides the LDS latency.  Two sets of them, or (TWO false) the next tile's over those of a step just multiplied: with two
+    // wavefronts per SIMD, or float's longer products, the reads are covered all the same and the registers go to other streams'
+    // wavefronts (float ResNet-18 2827 -> 2773 us per step, VGG-16/224 6640 -> 6575; the 64x64 tiles lose: R50 conv4_x at 64 1650 -> 1715).
+    constexpr bool TWO = ES == 2 && !(BM == 128 && BN == 128 && WGN == 4);
     struct Frag { uint4 a[4][MI], b[4][NI]; };
     auto read = [&](Frag& f, int st, int ks) __attribute__((always_inline)) {
         const unsigned char* sp = lds + st * STAGE;
@@ -331,11 +334,14 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
             }
         }
     };
-    // A tile has landed once only the loads of the NST - 2 tiles behind it are outstanding; every wavefront's earlier operand
-    // reads are complete then, too, so the stage they came from may be loaded again after the barrier.
+    // A tile has landed once only the loads of the tiles behind it are outstanding.  DRAIN: the stage of the tile being multiplied
+    // is loaded again behind the barrier, so every wavefront's operand reads are complete before it; with a stage more, the one loaded
+    // again is that of the tile before, whose operands have been multiplied, and the reads under way need not be waited for.
+    constexpr bool DRAIN = TWO || NST < 4;
+    constexpr int AHEAD = DRAIN ? NST : NST - 1;             // tiles between the one multiplied and the one being loaded
     auto meet = [&]() __attribute__((always_inline)) {
-        LPM_WAIT_VM(LPT * (NST - 2));
-        __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt(0)
+        LPM_WAIT_VM(LPT * (AHEAD - 2));
+        if (DRAIN) __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt(0)
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
@@ -351,36 +357,56 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
     if (early) ep.load(p, er0, ec0, rows, lane, Hc, Wc, ph, pw, Dc, pd);
     if (nk > 0) {
 #pragma unroll
-        for (int i = 0; i < NST - 1; ++i)
+        for (int i = 0; i < AHEAD - 1; ++i)
 #pragma unroll
             for (int q = 0; q < 4; ++q) issue(i, q);
-        Frag f0, f1;
+        Frag f0;
         meet();
 #pragma unroll
-        for (int q = 0; q < 4; ++q) issue(NST - 1, q);
+        for (int q = 0; q < 4; ++q) issue(AHEAD - 1, q);
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) read(f0, 0, ks);
-        int st = 0;                              // stage of the tile being multiplied
-        auto half = [&](const Frag& cur, Frag& nxt) __attribute__((always_inline)) {
-            const int st1 = st == NST - 1 ? 0 : st + 1;
-            meet();
-            read(nxt, st1, 0);
-            // A quarter of the next tile's reads and of the loads behind it go with a quarter of this one's products: the LDS,
-            // the address arithmetic and the matrix cores work side by side (all reads first, and the products would wait
-            // for the LDS queue to drain; all loads first, and the matrix cores would idle meanwhile).
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                __builtin_amdgcn_sched_barrier(0);
-                if (ks < 3) read(nxt, st1, ks + 1);
-                multiply(cur, ks);
-                issue(st, ks);
-            }
+        int st = 0, ld = DRAIN ? 0 : NST - 1;      // stages of the tile being multiplied and of the one to be loaded
+        // A quarter of the next tile's reads and of the loads behind it go with a quarter of this one's products: the LDS,
+        // the address arithmetic and the matrix cores work side by side (all reads first, and the products would wait
+        // for the LDS queue to drain; all loads first, and the matrix cores would idle meanwhile).
+        auto tile_done = [&](int st1) __attribute__((always_inline)) {
             __builtin_amdgcn_sched_barrier(0);
             st = st1;
+            ld = ld == NST - 1 ? 0 : ld + 1;
         };
-        for (int it = 0; it < nk; it += 2) {     // (an odd count ends with a tile of zeros)
-            half(f0, f1);
-            half(f1, f0);
+        if constexpr (TWO) {
+            Frag f1;
+            auto half = [&](const Frag& cur, Frag& nxt) __attribute__((always_inline)) {
+                const int st1 = st == NST - 1 ? 0 : st + 1;
+                meet();
+                read(nxt, st1, 0);
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (ks < 3) read(nxt, st1, ks + 1);
+                    multiply(cur, ks);
+                    issue(ld, ks);
+                }
+                tile_done(st1);
+            };
+            for (int it = 0; it < nk; it += 2) {     // (an odd count ends with a tile of zeros)
+                half(f0, f1);
+                half(f1, f0);
+            }
+        } else {
+            for (int it = 0; it < nk; ++it) {
+                const int st1 = st == NST - 1 ? 0 : st + 1;
+                meet();
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) {     // (the next tile's operands over those just multiplied)
+                    multiply(f0, ks);
+                    read(f0, st1, ks);
+                    issue(ld, ks);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                tile_done(st1);
+            }
         }
         LPM_WAIT_VM(0);
     }
