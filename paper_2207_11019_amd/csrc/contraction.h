@@ -36,6 +36,7 @@ struct IgemmArgs {
     int Hr, Wr, Dr;         // extent of the row space
     int Kh, Kw, Kd, stride, pad, pad_d;
     FastDiv dWr, dHr, dDr, dCc;       // row decoding; chunks per tap
+    FastDiv dNt, dKt, dKhw, dKw;      // tiles along N, K tiles per tap (whole ones), taps per filter slice and per filter row
     unsigned a_bytes, b_bytes, b_pitch;
     int kt_total, kt_per_split, splits;
     int free_taps;          // no tap can leave the image: no mask bits needed

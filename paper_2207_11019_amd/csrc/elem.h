@@ -48,19 +48,16 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblocks) {
     return xcd * per + min(xcd, rem) + idx;
 }
 
-// n / d for 0 <= n < 2^31 by multiplication (d = 1: mul = 0)
+// n / d for 0 <= n < 2^31 by multiplication: 2n * mul / 2^(32 + sh), mul = ceil(2^(31 + sh) / d), sh = ceil(log2 d)
 struct FastDiv { unsigned mul, sh; };
 static inline FastDiv fast_div(int d) {
     FastDiv f{0, 0};
-    if (d > 1) {
-        int l = 0;
-        while ((1u << l) < (unsigned)d) ++l;                       // ceil(log2 d)
-        f.mul = (unsigned)((((uint64_t)1 << (31 + l)) + d - 1) / d);
-        f.sh = (unsigned)(l - 1);
-    }
+    if (d < 1) d = 1;
+    while ((1u << f.sh) < (unsigned)d) ++f.sh;
+    f.mul = (unsigned)((((uint64_t)1 << (31 + f.sh)) + d - 1) / d);
     return f;
 }
-__device__ __forceinline__ int div_by(int n, const FastDiv& f) { return f.mul ? (int)(__umulhi((unsigned)n, f.mul) >> f.sh) : n; }
+__device__ __forceinline__ int div_by(int n, const FastDiv& f) { return (int)(__umulhi((unsigned)n << 1, f.mul) >> f.sh); }
 
 __device__ __forceinline__ float ld(const float* p, int64_t i) { return p[i]; }
 __device__ __forceinline__ float ld(const bf16_t* p, int64_t i) { return bf2f(p[i].bits); }

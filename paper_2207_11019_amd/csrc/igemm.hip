@@ -53,10 +53,9 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
     float* ksc = reinterpret_cast<float*>(lds + NST * STAGE + (UNI ? 0 : MAX_TAB * 16));
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nt = (p.N + BN - 1) / BN;
     // (strided: the residue classes differ in work, so their tiles stay in launch order, which deals them to the XCDs in turn)
     const int tile = MODE == MODE_DGRAD_S ? (int)blockIdx.x : xcd_remap(blockIdx.x, gridDim.x);
-    const int tm = tile / nt, n0 = (tile - tm * nt) * BN;
+    const int nt = (p.N + BN - 1) / BN, tm = div_by(tile, p.dNt), n0 = (tile - tm * nt) * BN;
     int m0 = tm * BM;
     int kt0 = blockIdx.z * p.kt_per_split, kt1 = min(p.kt_total, kt0 + p.kt_per_split);
     int nkd = p.Kd, nkh = p.Kh, nkw = p.Kw, kd0 = 0, kh0 = 0, kw0 = 0, kstep = 1;      // taps visited: first and count per axis
@@ -134,18 +133,20 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
             hq = t - n * p.Hr;
             if (p.Dr > 1) { const int ns = div_by(n, p.dDr); dq = n - ns * p.Dr; n = ns; }
         }
-        int h0, w0, d0;
-        unsigned m;
-        if (MODE == MODE_FWD) {
-            h0 = hq * p.stride - oh; w0 = wq * p.stride - ow; d0 = dq * p.stride - od;
-            m = (tap_bits(max(0, -d0), min(nkd, p.Di - d0)) << 24) | (tap_bits(max(0, -h0), min(nkh, p.Hi - h0)) << 12) |
-                tap_bits(max(0, -w0), min(nkw, p.Wi - w0));
-        } else {
-            h0 = hq + oh; w0 = wq + ow; d0 = dq + od;
-            m = (tap_bits(max(0, d0 - p.Di + 1), min(nkd, d0 + 1)) << 24) | (tap_bits(max(0, h0 - p.Hi + 1), min(nkh, h0 + 1)) << 12) |
-                tap_bits(max(0, w0 - p.Wi + 1), min(nkw, w0 + 1));
+        const bool fwd = MODE == MODE_FWD;
+        const int h0 = fwd ? hq * p.stride - oh : hq + oh, w0 = fwd ? wq * p.stride - ow : wq + ow;
+        int d0 = 0;
+        unsigned m = 0xffffffffu;
+        if (!p.free_taps) {
+            m = fwd ? (tap_bits(max(0, -h0), min(nkh, p.Hi - h0)) << 12) | tap_bits(max(0, -w0), min(nkw, p.Wi - w0))
+                    : (tap_bits(max(0, h0 - p.Hi + 1), min(nkh, h0 + 1)) << 12) | tap_bits(max(0, w0 - p.Wi + 1), min(nkw, w0 + 1));
+            m |= 1u << 24;
         }
-        a_msk[i] = ok ? (p.free_taps ? 0xffffffffu : m) : 0u;
+        if (p.Kd > 1 || p.Dr > 1 || p.Di > 1) {
+            d0 = fwd ? dq * p.stride - od : dq + od;
+            if (!p.free_taps) m = (m & 0xffffffu) | ((fwd ? tap_bits(max(0, -d0), min(nkd, p.Di - d0)) : tap_bits(max(0, d0 - p.Di + 1), min(nkd, d0 + 1))) << 24);
+        }
+        a_msk[i] = ok ? m : 0u;
         a_base[i] = (unsigned)(((n * p.Di + d0) * p.Hi + h0) * p.Wi + w0) * tapC + (MODE == MODE_FWD ? bias : 0u) + (UNI ? (unsigned)kcol * 16u : 0u);
     }
     // BT: chunk (lane) of the K tile [32 reduction rows][BN channels]
@@ -167,10 +168,17 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
     unsigned c_c = 0;
     int l_t = 0, l_c = 0;
     if (UNI) {
-        const int per = Cc / 8, t = kt0 / per;
+        const int per = Cc / 8, t = div_by(kt0, p.dKt);
         c_c = (unsigned)(kt0 - t * per) * 128u;
-        const int td = t / max(1, nkh * nkw), r = t - td * nkh * nkw;
-        c_td = td; c_th = r / max(1, nkw); c_tw = r - c_th * nkw;
+        if (MODE != MODE_DGRAD_S) {
+            c_td = div_by(t, p.dKhw);
+            const int r = t - c_td * nkh * nkw;
+            c_th = div_by(r, p.dKw); c_tw = r - c_th * nkw;
+        } else if (t > 0) {
+            c_td = t / (nkh * nkw);
+            const int r = t - c_td * nkh * nkw;
+            c_th = r / nkw; c_tw = r - c_th * nkw;
+        }
     } else {
         const int k = kt0 * 8 + kcol;
         l_t = div_by(k, p.dCc); l_c = k - l_t * Cc;
@@ -616,6 +624,7 @@ static hipError_t run_igemm(int dtype, int mode, IgemmArgs a, IgemmPlan pl, void
     const int es = dtype == LPM_BF16 ? 2 : 4;
     a.Di = std::max(a.Di, 1); a.Dr = std::max(a.Dr, 1); a.Kd = std::max(a.Kd, 1);
     a.dWr = fast_div(a.Wr); a.dHr = fast_div(a.Hr); a.dDr = fast_div(a.Dr); a.dCc = fast_div(a.Ci * es / 16);
+    a.dNt = fast_div((a.N + TILE_N[pl.tile] - 1) / TILE_N[pl.tile]); a.dKt = fast_div(a.Ci * es / 128); a.dKhw = fast_div(a.Kh * a.Kw); a.dKw = fast_div(a.Kw);
     a.kt_total = pl.kt_total; a.kt_per_split = pl.kt_per; a.splits = pl.splits;
     const int64_t mt = a.tiles_m ? a.tiles_m : (a.M + TILE_M[pl.tile] - 1) / TILE_M[pl.tile];
     const int64_t tiles = mt * ((a.N + TILE_N[pl.tile] - 1) / TILE_N[pl.tile]);
