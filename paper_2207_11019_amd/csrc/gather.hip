@@ -87,7 +87,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* q, unsigned b
 // launches of too few row tiles to fill the card: the four wavefronts of a block share a tile, each with a quarter of the
 // reduction, and add their sums through LDS.
 template <typename E, int NT, int MODE, bool KSPLIT>
-__global__ void __launch_bounds__(256, MODE == MODE_FWD ? 3 : 2) gather_gemm(const IgemmArgs p, const int ksteps, const int tiles, const FastDiv dKp) {
+__global__ void __launch_bounds__(256, MODE == MODE_FWD ? 3 : 2) gather_gemm(const IgemmArgs p, const int ksteps, const int tiles, const FastDiv dKp, const FastDiv dRows) {
     typedef Gathered<E> G;
     constexpr int ES = sizeof(E), EPC = G::N, KS = 2 * EPC, PIECE = 32 * (NT * 32 + 4);
     typedef Epilogue<E, 1, NT, MODE> Ep;
@@ -100,7 +100,10 @@ __global__ void __launch_bounds__(256, MODE == MODE_FWD ? 3 : 2) gather_gemm(con
     float* piece = pieces + wave * PIECE;
     for (int k = tid; k < Kp; k += 256) tab[k] = tap_entry<MODE == MODE_FWD ? 1 : -1>(k, K, p.Ci, p.Kh, p.Kw, p.Hi, p.Wi);
     const E* w = (const E*)p.B;
-    for (int i0 = tid; i0 < NT * 32 * Kp; i0 += 8 * 256) {          // eight elements' loads in flight
+    // (rows past the last output channel are not filled: what they add up to is not stored.  With them LeNet's data gradient, six rows
+    // of 32, took 15.5 us instead of 10.7, its forward pass 7.6 instead of 6.8.)
+    const int rows = min(p.N, NT * 32);
+    for (int i0 = tid; i0 < rows * Kp; i0 += 8 * 256) {             // eight elements' loads in flight
         float v[8];
         int at[8];
 #pragma unroll
@@ -112,13 +115,13 @@ __global__ void __launch_bounds__(256, MODE == MODE_FWD ? 3 : 2) gather_gemm(con
                 n = div_by(i, dKp); k = i - n * Kp;
                 o = (int64_t)(n0 + n) * K + k;
             } else {                         // w [Ci][taps][N], K = (tap, channel of the gathered tensor)
-                k = i / (NT * 32); n = i - k * (NT * 32);
+                k = div_by(i, dRows); n = i - k * rows;
                 const int t = div_by(k, p.dCc);
                 c = k - t * p.Ci;
                 o = ((int64_t)c * taps + t) * p.N + n0 + n;
             }
             at[u] = n * pitch + k;
-            const bool in = i < NT * 32 * Kp;
+            const bool in = i < rows * Kp;
             if (!in) at[u] = -1;
             v[u] = in && n0 + n < p.N && k < K ? ld(w, o) : 0.f;
             if (MODE != MODE_FWD && p.kscale && in && k < K) v[u] *= p.kscale[c];
@@ -379,7 +382,7 @@ static hipError_t go(const IgemmArgs& a, int ksteps, int tiles, hipStream_t st) 
     if (attr != hipSuccess) return attr;
     const int blocks = KSPLIT ? tiles : std::min((tiles + 3) / 4, 1536);
     launch_last(gather_gemm<E, NT, MODE, KSPLIT>, dim3((unsigned)blocks, (unsigned)((a.N + NT * 32 - 1) / (NT * 32))), dim3(256),
-                       gather_lds(sizeof(E), NT, ksteps), st, a, ksteps, tiles, fast_div(ksteps * (32 / (int)sizeof(E))));
+                       gather_lds(sizeof(E), NT, ksteps), st, a, ksteps, tiles, fast_div(ksteps * (32 / (int)sizeof(E))), fast_div(std::min(a.N, NT * 32)));
     return hipGetLastError();
 }
 template <typename E, int NT, int MODE>
