@@ -496,10 +496,11 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
 // --------------------------------------------------------------------------------------------------
 struct IgemmPlan { int tile; int splits, kt_total, kt_per; int64_t tiles; };
 // Output tiles.  64x64: the launches of a few hundred blocks that small micro-batches make.  128x64, 128x128: half the
-// operand traffic per product once there are enough tiles; 128x128 with eight wavefronts where there is about one tile per
-// CU (two wavefronts per SIMD hide each other's latencies), with four where there are two blocks per CU to do that.
-enum { TILE_64 = 0, TILE_128x64, TILE_128, TILE_128_8W };
-static const int TILE_M[4] = {64, 128, 128, 128}, TILE_N[4] = {64, 64, 128, 128};
+// operand traffic per product once there are enough tiles; 128x128 (eight wavefronts) with three stages where there is about one tile
+// per CU, with two where there are two blocks per CU to hide each other's latencies.  256x128, eight wavefronts of 64x64 each: a
+// quarter less LDS traffic per product, for what fills the card even so.
+enum { TILE_64 = 0, TILE_128x64, TILE_128, TILE_128_DEEP, TILE_256 };
+static const int TILE_M[5] = {64, 128, 128, 128, 256}, TILE_N[5] = {64, 64, 128, 128, 128};
 static int64_t tiles_of(int tile, int64_t M, int N) { return ((M + TILE_M[tile] - 1) / TILE_M[tile]) * ((N + TILE_N[tile] - 1) / TILE_N[tile]); }
 
 // kt: K tiles (of the longest residue class)
@@ -515,8 +516,12 @@ static IgemmPlan plan_igemm(int es, int64_t M, int N, int kt) {
         // 3308 / 3366 / 3371, VGG-16/224 6828 / 6833 / 6772 / 6778 / 6760, R50 conv4_x at 64 1746 / 1752 / 1749 / 1750 / 1870).
         const bool wide = N % 128 == 0 || N % 128 > 64;
         const int64_t n128 = tiles_of(TILE_128, M, N);
-        if (wide && n128 >= 384) pl.tile = TILE_128;
-        else if (wide && n128 >= 180) pl.tile = TILE_128_8W;
+        // 128x128 of two stages (of four wavefronts before) / 256x128, alone: 25088 x 256, K 2304 35.4 / 32.9, K 1024 21.6 / 19.6;
+        // R50 conv4_x at 512, per step: four wavefronts 6925, eight 6770, 256x128 from 384 tiles on 6807, from 180 and 12 K tiles on
+        // 6660, from 180 and 4 on 6636.  With one column of tiles both read the gathered rows once: VGG-16/224 6590 there, 6603 with 256x128.
+        if (wide && N > 128 && kt >= 4 && tiles_of(TILE_256, M, N) >= 180) pl.tile = TILE_256;
+        else if (wide && n128 >= 384) pl.tile = TILE_128;
+        else if (wide && n128 >= 180) pl.tile = TILE_128_DEEP;
         else if (tiles_of(TILE_128x64, M, N) >= 180) pl.tile = TILE_128x64;
     }
     pl.kt_total = std::max(1, kt);
@@ -603,8 +608,9 @@ template <typename E, int MODE, bool UNI, int BT>
 static hipError_t go_tile(const IgemmPlan& pl, const IgemmArgs& a, int64_t tiles, hipStream_t st) {
     if constexpr (sizeof(E) == 2) {
         if (pl.tile == TILE_128x64) return go<E, 128, 64, 2, 2, 3, MODE, UNI, BT, 2>(a, tiles, st);
-        if (pl.tile == TILE_128) return go<E, 128, 128, 2, 2, 2, MODE, UNI, BT, 2>(a, tiles, st);
-        if (pl.tile == TILE_128_8W) return go<E, 128, 128, 2, 4, 3, MODE, UNI, BT, 2>(a, tiles, st);
+        if (pl.tile == TILE_128) return go<E, 128, 128, 2, 4, 2, MODE, UNI, BT, 2>(a, tiles, st);
+        if (pl.tile == TILE_128_DEEP) return go<E, 128, 128, 2, 4, 3, MODE, UNI, BT, 2>(a, tiles, st);
+        if (pl.tile == TILE_256) return go<E, 256, 128, 4, 2, 3, MODE, UNI, BT, 2>(a, tiles, st);
     }
     // About one block per CU: nothing but its own loads in flight keeps the memory path busy, four stages (R50 conv4_x at 64 1.81 ->
     // 1.77 ms per step).  More blocks: three, so that three of them, or other streams' kernels, share a CU (VGG-16/224 6.83 against

@@ -27,8 +27,12 @@ BOTH = [
     G(3, 1, 1, 84, 10, 1, 1, 0),          # head
 ]
 BF16 = [
-    G(1, 152, 152, 8, 128, 1, 1, 0),      # 181 tiles of 128x128: eight wavefronts
-    G(3, 128, 128, 8, 128, 1, 1, 0),      # 384 of them: four
+    G(1, 152, 152, 8, 128, 1, 1, 0),      # 181 tiles of 128x128: three stages
+    G(3, 128, 128, 8, 128, 1, 1, 0),      # 384 of them: two
+    G(2, 107, 109, 32, 200, 3, 1, 1),     # 184 tiles of 256x128, ragged M and N
+    G(2, 107, 109, 200, 32, 3, 1, 1),     # ... of the data gradient
+    G(2, 107, 109, 256, 256, 1, 1, 0),    # ... of both, whole K tiles, the fewest
+    G(2, 151, 153, 256, 64, 3, 2, 1),     # ... of a strided data gradient
     G(3, 128, 128, 8, 64, 3, 1, 1),       # 384 tiles of 128x64
     G(3, 127, 128, 64, 72, 1, 1, 0),      # N over half a tile, ragged M
     G(1, 128, 128, 128, 8, 1, 1, 0),      # the same sizes for the data gradient
