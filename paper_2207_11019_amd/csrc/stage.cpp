@@ -152,11 +152,11 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
         int n_src, n_add;
         uses(a, n_src, n_add);
         if (n_add != 1) return false;
-        if (ar.fused_side) return true;
+        if (ar.fused_side) return n_src == 1;      // (another layer's data gradient would be added to the shared buffer)
         return n_src == 0 && has_weights(ar.d) && !(ar.d.flags & LPM_RELU) && ar.d.add_src == LPM_NONE && (!(ar.d.flags & LPM_SCALE) || ar.dz_unscaled);
     };
-    // Epilogue-backward fusion: when a layer's output feeds exactly one later layer through its `src` edge, that
-    // layer's backward kernel (data gradient / pooling backward) applies the ReLU mask and the scale itself and
+    // Epilogue-backward fusion: the first layer that reads a layer's output is the last to contribute to its gradient, and where it
+    // reads it as its `src`, its backward kernel (data gradient / pooling backward) applies the ReLU mask and the scale itself and
     // writes dz directly; the bias gradient then comes out of the weight-gradient kernel.
     for (int32_t i = first; i < last; ++i) {
         LayerRt& lr = s->Ly(i);
@@ -171,21 +171,26 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
         int32_t consumer = -1, first_add = last;
         for (int32_t j = i + 1; j < last; ++j) {
             const lpm_layer& c = s->net[j];
-            if (c.src == i) { ((c.kind == LPM_SOFTMAX_CE || c.kind == LPM_ATTN) ? n_other : n_src)++; consumer = j; }
+            if (c.src == i) {
+                ((c.kind == LPM_SOFTMAX_CE || c.kind == LPM_ATTN) ? n_other : n_src)++;
+                if (consumer < 0) consumer = j;
+            }
             if (c.add_src == i) { ++n_add; first_add = std::min(first_add, j); }
         }
-        if (n_src != 1 || n_other != 0) continue;
+        if (n_src < 1 || n_other != 0) continue;
         if ((l.flags & LPM_BIAS) && !bias_from_dz_ok(lr)) continue;
-        if (l.add_src != LPM_NONE || n_add > 0) {
-            // Residual blocks.  The layer adds a shortcut, and / or later layers use its output as their shortcut: the
-            // single layer that reads it as its input comes first in layer order, so its data gradient is the last
-            // contribution in the backward pass, and an MFMA data gradient can add the earlier ones, mask, and write
-            // both this layer's dz and the shortcut's gradient.  The global average pooling behind the last block masks, too,
+        if (l.add_src != LPM_NONE || n_add > 0 || n_src > 1) {
+            // Residual blocks.  The layer adds a shortcut, and / or later layers use its output as their shortcut, or a projection
+            // of the next block reads it too: the layer that reads it first in layer order makes the last contribution in
+            // the backward pass, and an MFMA data gradient can add the earlier ones, mask, and write both this layer's dz and the
+            // shortcut's gradient.  (Of the blocks before a projection, instead of a pass of their own: width-48 ResNet 2437 -> 2405 us
+            // per step, ResNet-18/CIFAR 2917 -> 2891.)  The global average pooling behind the last block masks, too,
             // where nothing is to be added and the shortcut shares the dz.
             const lpm_layer& c = s->net[(size_t)consumer];
-            if (c.kind == LPM_GAP && n_add == 0 && shares_dz(i)) {
+            if (c.kind == LPM_GAP && n_add == 0 && n_src == 1 && shares_dz(i)) {
                 lr.shortcut_is_dz = true;
                 lr.fused_in = true;
+                lr.fused_by = consumer;
                 continue;
             }
             if (!has_weights(c) || first_add < consumer || !dgrad_has_side(dtype, s->Ly(consumer).g)) continue;
@@ -193,6 +198,7 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
             lr.shortcut_is_dz = shares_dz(i);
         }
         lr.fused_in = true;
+        lr.fused_by = consumer;
     }
     // ... and a projection shortcut: a scale-only layer (no ReLU, no shortcut of its own) whose output is read by
     // exactly one layer, as its shortcut, when that layer is fused_side: the shortcut gradient that layer's fused
@@ -648,6 +654,8 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
     std::vector<void*> G((size_t)(last - first + 1), nullptr);
     std::vector<char> have((size_t)(last - first + 1), 0);
     auto gi = [&](int32_t t) { return (size_t)(t - (first - 1)); };
+    // whether layer i's backward kernel writes the dz of the layer that made tensor t
+    auto writes_dz = [&](int32_t i, int32_t t) { return t >= first && s->Ly(t).fused_in && s->Ly(t).fused_by == i; };
     for (int32_t t = first; t < last; ++t)
         if (s->T(t).loc == LOC_STASH) G[gi(t)] = gw + s->T(t).g_off;
     G[gi(first - 1)] = dx;
@@ -724,7 +732,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                         unpool.pool_x = tptr(s, q, x, y, stash);
                         unpool.dst = G[gi(q)];
                         unpool.accumulate = have[gi(q)];
-                        if (q >= first && s->Ly(q).fused_in) {
+                        if (writes_dz(p, q)) {
                             const LayerRt& pr = s->Ly(q);
                             unpool.dst = gw + pr.dz_off;
                             unpool.accumulate = 0;
@@ -739,7 +747,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                 DgradSide side{};
                 bool use_side = false;
                 if (want && lr.unpool_of < 0) {
-                    if (l.src >= first && s->Ly(l.src).fused_in) {
+                    if (writes_dz(i, l.src)) {
                         const LayerRt& pr = s->Ly(l.src);
                         gsrc = gw + pr.dz_off;
                         gmask = (pr.d.flags & LPM_RELU) ? tptr(s, l.src, x, y, stash) : nullptr;
@@ -815,7 +823,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                     int gsrc_acc = have[gi(l.src)];
                     const void* gmask = nullptr;
                     const float* gmscale = nullptr;
-                    if (l.src >= first && s->Ly(l.src).fused_in) {
+                    if (writes_dz(i, l.src)) {
                         const LayerRt& pr = s->Ly(l.src);
                         gsrc = gw + pr.dz_off;
                         gsrc_acc = 0;

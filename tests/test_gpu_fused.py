@@ -64,6 +64,28 @@ def projected(cin, w, mid, h, m):
                  C(mid, w, 1, 1, h, h, scale=True, src=1, add=2), C(w, mid, 1, 1, h, h)), m
 
 
+def down(c, w, h, m):
+    """A basic block whose output two strided layers read."""
+    g = (h - 1) // 2 + 1
+    return chain(C(c, c, 1, 1, h, h, scale=True), C(c, c, 3, 3, h, h, p=1, scale=True), C(c, c, 3, 3, h, h, p=1, scale=True, src=1, add=0),
+                 C(c, w, 3, 3, h, h, s=2, p=1, scale=True, src=2), C(c, w, 1, 1, h, h, s=2, relu=False, scale=True, src=2),
+                 C(w, w, 3, 3, g, g, p=1, scale=True, src=3, add=4), C(w, c, 1, 1, g, g)), m
+
+
+def read_thrice(c, h, m):
+    """A tensor that two layers read and a third one adds."""
+    return chain(C(c, c, 1, 1, h, h, scale=True), C(c, c, 1, 1, h, h, scale=True, src=0), C(c, c, 1, 1, h, h, relu=False, scale=True, src=0),
+                 C(c, c, 3, 3, h, h, p=1, scale=True, src=1, add=2), C(c, c, 1, 1, h, h, scale=True, src=3, add=0), C(c, c, 1, 1, h, h)), m
+
+
+def pooled_beside(c, h, m):
+    """A tensor that a strided layer and a max-pooling read."""
+    layers = chain(C(c, c, 1, 1, h, h, scale=True), C(c, c, 3, 3, h, h, s=2, p=1, scale=True, src=0), P(c, h, h),
+                   C(c, c, 1, 1, h // 2, h // 2, scale=True, src=1, add=2))
+    layers[2]["src"] = 0
+    return layers, m
+
+
 def long_projection(cin, w, mid, h, wd, m):
     """The same with filters of 13 x 1."""
     return chain(C(cin, cin, 1, 1, h, wd), C(cin, mid, 13, 1, h, wd, scale=True, src=0), C(cin, w, 13, 1, h, wd, relu=False, bias=False, scale=True, src=0),
@@ -91,6 +113,14 @@ NETS = {
     "float_whole": (bottlenecks(32, 64, 40, 2, ["in", "x", "in"]), "f32"),
     "float_chunks": (bottlenecks(36, 20, 40, 2, ["in", "in"]), "f32"),
     "float_projected": (projected(20, 44, 36, 40, 2), "f32"),
+    # tensors with several readers: the first one's data gradient adds what the others left, masks and hands on
+    "down": (down(64, 128, 16, 3), "bf16"),
+    "down_ragged": (down(40, 72, 13, 3), "bf16"),
+    "down_float": (down(36, 44, 13, 3), "f32"),
+    "read_thrice": (read_thrice(64, 14, 3), "bf16"),
+    "read_thrice_float": (read_thrice(20, 14, 3), "f32"),
+    "pooled_beside": (pooled_beside(64, 16, 3), "bf16"),
+    "pooled_beside_float": (pooled_beside(20, 16, 3), "f32"),
     # layers whose dz carries their scale (their filter is too long for the weight gradients that multiply by it): the block's input, and
     # a projection
     "scaled_dz": ((chain(C(6, 16, 13, 1, 20, 12, bias=False, scale=True), C(16, 40, 3, 3, 8, 12, p=1, scale=True)), 2), "bf16"),
