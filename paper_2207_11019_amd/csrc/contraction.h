@@ -40,7 +40,6 @@ struct IgemmArgs {
     unsigned a_bytes, b_bytes, b_pitch;
     int kt_total, kt_per_split, splits;
     int free_taps;          // no tap can leave the image: no mask bits needed
-    int tiles_m;            // (strided) row tiles over all classes
     int cls_tile0[17];      // strided data gradient: first row tile of class c = (pd * s + ph) * s + pw
     const uint16_t* pool_x; // stride-1 data gradient routed through a 2x2 max-pooling (see UnpoolDesc): its input [m][2*Hr][2*Wr][N]
     uint16_t* pool_dst;

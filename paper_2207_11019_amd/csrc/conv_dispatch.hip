@@ -21,9 +21,11 @@ size_t mfma_fwd_ws_bytes(int dtype, const ConvGeom& g);
 size_t mfma_dgrad_ws_bytes(int dtype, const ConvGeom& g);
 bool mfma_fwd_pools(int dtype, const ConvGeom& g);
 hipError_t mfma_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* scale, const float* bias,
-                         const void* add, int relu, void* y, void* ws, bool ws_zeroed, hipStream_t st, void* pool_y);
+                         const void* add, int relu, void* y, void* ws, bool ws_zeroed, hipStream_t st, void* pool_y,
+                         HeldCall* hold, HeldCall* with);
 hipError_t mfma_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const void* wt, void* dx, int accumulate, const void* mask,
-                           const float* mscale, void* ws, bool ws_zeroed, hipStream_t st, const UnpoolDesc* unpool, const DgradSide* side, const float* kscale);
+                           const float* mscale, void* ws, bool ws_zeroed, hipStream_t st, const UnpoolDesc* unpool, const DgradSide* side, const float* kscale,
+                           HeldCall* hold, HeldCall* with);
 bool mfma_dgrad_kscale_ok(const ConvGeom& g);
 bool wgrad_mm_ok(int dtype, const ConvGeom& g);
 size_t wgrad_mm_ws_bytes(int dtype, const ConvGeom& g);
@@ -86,9 +88,12 @@ size_t wgrad_ws_bytes(int dtype, const ConvGeom& g) {
 bool fwd_can_pool(int dtype, const ConvGeom& g) { return mfma_fwd_pools(dtype, g); }
 
 hipError_t launch_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* scale,
-                           const float* bias, const void* add, int relu, void* y, void* ws, hipStream_t st, void* pool_y, bool ws_zeroed) {
+                           const float* bias, const void* add, int relu, void* y, void* ws, hipStream_t st, void* pool_y, bool ws_zeroed,
+                           HeldCall* hold, HeldCall* with) {
     if (pool_y && !fwd_can_pool(dtype, g)) return hipErrorInvalidValue;      // callers ask fwd_can_pool first
-    if (fwd_mm(dtype, fc_view(g))) return mfma_conv_fwd(dtype, fc_view(g), x, w, scale, bias, add, relu, y, ws, ws_zeroed, st, pool_y);
+    if (fwd_mm(dtype, fc_view(g))) return mfma_conv_fwd(dtype, fc_view(g), x, w, scale, bias, add, relu, y, ws, ws_zeroed, st, pool_y, hold, with);
+    const hipError_t e = with ? run_held(*with, st) : hipSuccess;
+    if (e != hipSuccess) return e;
     if (gather_fwd_ok(dtype, g)) return gather_conv_fwd(dtype, g, x, w, scale, bias, add, relu, y, st);
     return conv_fwd_generic_launch(dtype, g, x, w, scale, bias, add, relu, y, st);
 }
@@ -116,13 +121,17 @@ bool dgrad_scales_dz(int dtype, const ConvGeom& g) { return dtype == LPM_BF16 ||
 
 hipError_t launch_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const void* w, const void* wt, void* dx,
                              int accumulate, const void* mask, const float* mscale, void* ws, hipStream_t st,
-                             const UnpoolDesc* unpool, const DgradSide* side, const float* dzscale, bool ws_zeroed) {
+                             const UnpoolDesc* unpool, const DgradSide* side, const float* dzscale, bool ws_zeroed,
+                             HeldCall* hold, HeldCall* with) {
     if (unpool && !(dgrad_can_unpool(dtype, g) && wt)) return hipErrorInvalidValue;      // callers ask dgrad_can_unpool first
     if (side && !(dgrad_has_side(dtype, g) && (wt || dtype == LPM_F32))) return hipErrorInvalidValue;          // ... and dgrad_has_side
-    if (dtype == LPM_BF16 && fc_skinny_ok(g)) return fc_dgrad(g, dz, dzscale, w, dx, accumulate, mask, mscale, (char*)ws + LPM_COUNT_BYTES, st);
-    if (dtype == LPM_BF16 && wt && mfma_dgrad_ok(dtype, g)) return mfma_conv_dgrad(dtype, g, dz, wt, dx, accumulate, mask, mscale, ws, ws_zeroed, st, unpool, side, nullptr);
-    if (dtype == LPM_F32 && f32_dgrad_viewed(g, mscale, side)) return mfma_conv_dgrad(dtype, fc_view(g), dz, w, dx, accumulate, mask, nullptr, ws, ws_zeroed, st, nullptr, nullptr, dzscale);
-    if (dtype == LPM_F32 && dgrad_mm(dtype, g)) return mfma_conv_dgrad(dtype, g, dz, w, dx, accumulate, mask, mscale, ws, ws_zeroed, st, nullptr, side, dzscale);
+    const bool skinny = dtype == LPM_BF16 && fc_skinny_ok(g);
+    if (!skinny && dtype == LPM_BF16 && wt && mfma_dgrad_ok(dtype, g)) return mfma_conv_dgrad(dtype, g, dz, wt, dx, accumulate, mask, mscale, ws, ws_zeroed, st, unpool, side, nullptr, hold, with);
+    if (dtype == LPM_F32 && f32_dgrad_viewed(g, mscale, side)) return mfma_conv_dgrad(dtype, fc_view(g), dz, w, dx, accumulate, mask, nullptr, ws, ws_zeroed, st, nullptr, nullptr, dzscale, hold, with);
+    if (dtype == LPM_F32 && dgrad_mm(dtype, g)) return mfma_conv_dgrad(dtype, g, dz, w, dx, accumulate, mask, mscale, ws, ws_zeroed, st, nullptr, side, dzscale, hold, with);
+    const hipError_t e = with ? run_held(*with, st) : hipSuccess;
+    if (e != hipSuccess) return e;
+    if (skinny) return fc_dgrad(g, dz, dzscale, w, dx, accumulate, mask, mscale, (char*)ws + LPM_COUNT_BYTES, st);
     if (gather_dgrad_ok(dtype, g)) return gather_conv_dgrad(dtype, g, dz, dzscale, w, dx, accumulate, mask, mscale, st);
     return conv_dgrad_generic_launch(dtype, g, dz, dzscale, w, dx, accumulate, mask, mscale, st);
 }

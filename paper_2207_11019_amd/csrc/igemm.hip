@@ -24,6 +24,7 @@
 #include "contraction.h"
 #include "lds_dma.h"
 #include <algorithm>
+#include <cstring>
 
 namespace lpm {
 
@@ -38,8 +39,9 @@ constexpr int AUX_AGENT = 16;
 // layout of B: [N][K] rows; K outermost; K outermost and scaled
 enum { BT_NONE = 0, BT_PLAIN = 1, BT_SCALED = 2 };
 
-template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, bool UNI, int BT, int OCC>
-__global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmArgs p) {
+// Block bx of the gx tiles' blocks, part bz of a split reduction.
+template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, bool UNI, int BT>
+__device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, const int gx, const int bz) {
     constexpr int ES = sizeof(E), T = WGM * WGN * 64, RS = T / 8;             // rows a load step covers
     constexpr int WTM = BM / WGM, WTN = BN / WGN, MI = WTM / 32, NI = WTN / 32;
     constexpr int A_LD = BM / RS, B_LD = BN / RS, LPT = A_LD + B_LD;
@@ -54,10 +56,10 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // (strided: the residue classes differ in work, so their tiles stay in launch order, which deals them to the XCDs in turn)
-    const int tile = MODE == MODE_DGRAD_S ? (int)blockIdx.x : xcd_remap(blockIdx.x, gridDim.x);
+    const int tile = MODE == MODE_DGRAD_S ? bx : xcd_remap(bx, gx);
     const int nt = (p.N + BN - 1) / BN, tm = div_by(tile, p.dNt), n0 = (tile - tm * nt) * BN;
     int m0 = tm * BM;
-    int kt0 = blockIdx.z * p.kt_per_split, kt1 = min(p.kt_total, kt0 + p.kt_per_split);
+    int kt0 = bz * p.kt_per_split, kt1 = min(p.kt_total, kt0 + p.kt_per_split);
     int nkd = p.Kd, nkh = p.Kh, nkw = p.Kw, kd0 = 0, kh0 = 0, kw0 = 0, kstep = 1;      // taps visited: first and count per axis
     int ph = 0, pw = 0, pd = 0, Hc = p.Hr, Wc = p.Wr, Dc = p.Dr, rows = p.M;           // residue class of the rows and its extent
     int oh = p.pad, ow = p.pad, od = p.pad_d;
@@ -80,8 +82,8 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
         nkd = p.Dr > 1 ? (kd0 < p.Kd ? (p.Kd - kd0 + s_ - 1) / s_ : 0) : 1;
         // output pixel = class coordinate + (ph + pad - kh) / stride, an exact quotient that falls by one per visited tap
         oh = (ph + p.pad - kh0) / s_; ow = (pw + p.pad - kw0) / s_; od = p.Dr > 1 ? (pd + p.pad_d - kd0) / s_ : 0;
-        const int kt_cls = (nkd * nkh * nkw * Cc + 7) / 8, per = (kt_cls + (int)gridDim.z - 1) / (int)gridDim.z;
-        kt0 = blockIdx.z * per;
+        const int kt_cls = (nkd * nkh * nkw * Cc + 7) / 8, per = (kt_cls + p.splits - 1) / p.splits;
+        kt0 = bz * per;
         kt1 = min(kt_cls, kt0 + per);
     }
     const int ntap = nkd * nkh * nkw, nk = max(0, kt1 - kt0);
@@ -426,7 +428,7 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
         // XCD's own L2 (scope "agent"), so no cache is written back or invalidated: a store counted as done has reached memory.
         const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(p.part + (size_t)tile * p.splits * (BM * BN), 0, (unsigned)(p.splits * BM * BN * 4), 0x00020000);
         const unsigned mine = (unsigned)(wave * (MI * NI * 1024) + lane * 4) * 4u;
-        const int me = blockIdx.z;
+        const int me = bz;
         typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
@@ -491,6 +493,22 @@ __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmA
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     ep.store(p, area, er0, ec0, rows, lane, Hc, Wc, ph, pw, Dc, pd);
+}
+
+template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, bool UNI, int BT, int OCC>
+__global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmArgs p) {
+    igemm_block<E, BM, BN, WGM, WGN, NST, MODE, UNI, BT>(p, blockIdx.x, gridDim.x, blockIdx.z);
+}
+
+// Two contractions that do not read each other's results, in one launch (64x64 tiles): the blocks of the first, then those of
+// the second.
+struct IgemmPair { IgemmArgs p[2]; FastDiv tiles_d[2]; int tiles[2]; int second; };
+template <typename E, int NST, int MODE0, int MODE1, bool UNI, int BT>
+__global__ void __launch_bounds__(256, 2) igemm_pair(const IgemmPair g) {
+    const int k = (int)blockIdx.x >= g.second, b = (int)blockIdx.x - (k ? g.second : 0), z = div_by(b, g.tiles_d[k]);
+    if constexpr (MODE0 == MODE1) igemm_block<E, 64, 64, 2, 2, NST, MODE0, UNI, BT>(g.p[k], b - z * g.tiles[k], g.tiles[k], z);
+    else if (k == 0) igemm_block<E, 64, 64, 2, 2, NST, MODE0, UNI, BT>(g.p[0], b - z * g.tiles[0], g.tiles[0], z);
+    else igemm_block<E, 64, 64, 2, 2, NST, MODE1, UNI, BT>(g.p[1], b - z * g.tiles[1], g.tiles[1], z);
 }
 
 // --------------------------------------------------------------------------------------------------
@@ -626,33 +644,144 @@ static hipError_t go_uni(const IgemmPlan& pl, const IgemmArgs& a, int64_t tiles,
 
 hipError_t launch_zero_counts(void* const* heads, int n, hipStream_t st);
 
-static hipError_t run_igemm(int dtype, int mode, IgemmArgs a, IgemmPlan pl, void* ws, bool ws_zeroed, hipStream_t st) {
+struct IgemmCall { int dtype, mode, tiles; IgemmArgs a; IgemmPlan pl; };
+static_assert(sizeof(IgemmCall) <= sizeof(HeldCall::bytes), "room for a held call");
+
+// what follows from the plan's tile
+static void lay_tiles(IgemmCall& c) {
+    IgemmArgs& a = c.a;
+    const int bm = TILE_M[c.pl.tile], nt = (a.N + TILE_N[c.pl.tile] - 1) / TILE_N[c.pl.tile];
+    int mt = (a.M + bm - 1) / bm;
+    if (c.mode == MODE_DGRAD_S) {          // row tiles per residue class (d % stride, h % stride, w % stride)
+        const int s = a.stride, ncls = (a.Dr > 1 ? s : 1) * s * s;
+        const int64_t m = a.M / ((int64_t)a.Dr * a.Hr * a.Wr);
+        mt = 0;
+        for (int k = 0; k < ncls; ++k) {
+            a.cls_tile0[k] = mt;
+            const int pd = k / (s * s), ph = (k / s) % s, pw = k % s;
+            const int64_t Dc = a.Dr > 1 ? (a.Dr - pd + s - 1) / s : 1, Hc = (a.Hr - ph + s - 1) / s, Wc = (a.Wr - pw + s - 1) / s;
+            mt += (int)((m * Dc * Hc * Wc + bm - 1) / bm);
+        }
+        for (int k = ncls; k <= 16; ++k) a.cls_tile0[k] = mt;
+    }
+    a.dNt = fast_div(nt);
+    c.tiles = mt * nt;
+}
+
+static hipError_t go_call(const IgemmCall& c, hipStream_t st) {
+    const IgemmArgs& a = c.a;
+    const bool bf = c.dtype == LPM_BF16;
+    if (c.mode == MODE_FWD) return bf ? go_uni<bf16_t, MODE_FWD, BT_NONE>(c.pl, a, c.tiles, st) : go_uni<float, MODE_FWD, BT_NONE>(c.pl, a, c.tiles, st);
+    if (c.mode == MODE_UNPOOL) return go_uni<bf16_t, MODE_UNPOOL, BT_NONE>(c.pl, a, c.tiles, st);
+    const bool s1 = c.mode == MODE_DGRAD;
+    if (bf) return s1 ? go_uni<bf16_t, MODE_DGRAD, BT_NONE>(c.pl, a, c.tiles, st) : go_uni<bf16_t, MODE_DGRAD_S, BT_NONE>(c.pl, a, c.tiles, st);
+    if (a.kscale) return s1 ? go_uni<float, MODE_DGRAD, BT_SCALED>(c.pl, a, c.tiles, st) : go_uni<float, MODE_DGRAD_S, BT_SCALED>(c.pl, a, c.tiles, st);
+    return s1 ? go_uni<float, MODE_DGRAD, BT_PLAIN>(c.pl, a, c.tiles, st) : go_uni<float, MODE_DGRAD_S, BT_PLAIN>(c.pl, a, c.tiles, st);
+}
+
+template <typename E, int NST, int MODE0, int MODE1, bool UNI, int BT>
+static hipError_t go_pair(const IgemmPair& g, int blocks, hipStream_t st) {
+    constexpr int stages = NST * 128 * 128 + (UNI ? 0 : MAX_TAB * 16) + (BT == BT_SCALED ? MAX_KSCALE * 4 : 0);
+    constexpr int epilogue = 64 * 2 * (32 + 4) * 4, bytes = stages > epilogue ? stages : epilogue;
+    static DeviceSet done;
+    const hipError_t attr = allow_lds(igemm_pair<E, NST, MODE0, MODE1, UNI, BT>, bytes, done);
+    if (attr != hipSuccess) return attr;
+    launch_last(igemm_pair<E, NST, MODE0, MODE1, UNI, BT>, dim3((unsigned)blocks), dim3(256), bytes, st, g);
+    return hipGetLastError();
+}
+template <typename E, int MODE0, int MODE1, int BT>
+static hipError_t go_pair_uni(const IgemmPair& g, bool uni, int blocks, hipStream_t st) {
+    if (blocks <= 320) return uni ? go_pair<E, 4, MODE0, MODE1, true, BT>(g, blocks, st) : go_pair<E, 4, MODE0, MODE1, false, BT>(g, blocks, st);
+    return uni ? go_pair<E, 3, MODE0, MODE1, true, BT>(g, blocks, st) : go_pair<E, 3, MODE0, MODE1, false, BT>(g, blocks, st);
+}
+
+static bool uni_of(const IgemmCall& c) { return (c.a.Ci * (c.dtype == LPM_BF16 ? 2 : 4)) % 128 == 0; }
+// Whether x (held back) and y go in one launch.  What a launch costs beyond its K loop, 4 us, is as much as the whole of a small
+// contraction, and where both leave CUs idle they run side by side (us per step, apart / together: float ResNet-18 2746 / 2588, width-48
+// ResNet 2408 / 2272, 3-D ResNet 1673 / 1600, ResNet-18/CIFAR 2808 / 2750, 16 images forward 163 / 152).  Larger tiles are for launches
+// that fill the card by themselves; a 128x64 plan of a few K tiles -- a projection's data gradient, mostly output -- runs
+// on 64x64 here (left alone: width-48 ResNet 2308, 3-D 1619, ResNet-18/CIFAR 2735).
+static bool pairs(const IgemmCall& x, const IgemmCall& y) {
+    if (x.dtype != y.dtype || uni_of(x) != uni_of(y) || (x.pl.splits > 1 && y.pl.splits > 1)) return false;      // (they share the scratch area)
+    auto small = [](const IgemmCall& c) { return c.pl.tile == TILE_64 || (c.pl.tile == TILE_128x64 && c.pl.kt_total <= 4 && tiles_of(TILE_64, c.a.M, c.a.N) <= 1088); };
+    if (!small(x) || !small(y)) return false;
+    if (x.mode == MODE_FWD) return y.mode == MODE_FWD;
+    if (x.dtype == LPM_F32 && !(x.a.kscale && y.a.kscale)) return false;
+    return x.mode == MODE_DGRAD && (y.mode == MODE_DGRAD || y.mode == MODE_DGRAD_S);
+}
+
+static hipError_t run_pair(IgemmCall x, IgemmCall y, hipStream_t st) {
+    if (x.mode == MODE_FWD && y.pl.kt_per > x.pl.kt_per) std::swap(x, y);      // the longer blocks first
+    IgemmPair g;
+    IgemmCall* c[2] = {&x, &y};
+    int blocks[2];
+    for (int k = 0; k < 2; ++k) {
+        if (c[k]->pl.tile != TILE_64) { c[k]->pl.tile = TILE_64; lay_tiles(*c[k]); }
+        g.p[k] = c[k]->a;
+        g.tiles[k] = c[k]->tiles;
+        g.tiles_d[k] = fast_div(c[k]->tiles);
+        blocks[k] = c[k]->tiles * c[k]->a.splits;
+    }
+    g.second = blocks[0];
+    const int n = blocks[0] + blocks[1];
+    const bool uni = uni_of(x);
+    if (x.mode == MODE_FWD) return x.dtype == LPM_BF16 ? go_pair_uni<bf16_t, MODE_FWD, MODE_FWD, BT_NONE>(g, uni, n, st) : go_pair_uni<float, MODE_FWD, MODE_FWD, BT_NONE>(g, uni, n, st);
+    if (x.dtype == LPM_BF16) return y.mode == MODE_DGRAD ? go_pair_uni<bf16_t, MODE_DGRAD, MODE_DGRAD, BT_NONE>(g, uni, n, st) : go_pair_uni<bf16_t, MODE_DGRAD, MODE_DGRAD_S, BT_NONE>(g, uni, n, st);
+    return y.mode == MODE_DGRAD ? go_pair_uni<float, MODE_DGRAD, MODE_DGRAD, BT_SCALED>(g, uni, n, st) : go_pair_uni<float, MODE_DGRAD, MODE_DGRAD_S, BT_SCALED>(g, uni, n, st);
+}
+
+// hold, with: see HeldCall
+static hipError_t run_igemm(int dtype, int mode, const IgemmArgs& args, const IgemmPlan& pl, void* ws, bool ws_zeroed, hipStream_t st, HeldCall* hold, HeldCall* with) {
+    IgemmCall c{dtype, mode, 0, args, pl};
+    IgemmArgs& a = c.a;
     const int es = dtype == LPM_BF16 ? 2 : 4;
     a.Di = std::max(a.Di, 1); a.Dr = std::max(a.Dr, 1); a.Kd = std::max(a.Kd, 1);
     a.dWr = fast_div(a.Wr); a.dHr = fast_div(a.Hr); a.dDr = fast_div(a.Dr); a.dCc = fast_div(a.Ci * es / 16);
-    a.dNt = fast_div((a.N + TILE_N[pl.tile] - 1) / TILE_N[pl.tile]); a.dKt = fast_div(a.Ci * es / 128); a.dKhw = fast_div(a.Kh * a.Kw); a.dKw = fast_div(a.Kw);
+    a.dKt = fast_div(a.Ci * es / 128); a.dKhw = fast_div(a.Kh * a.Kw); a.dKw = fast_div(a.Kw);
     a.kt_total = pl.kt_total; a.kt_per_split = pl.kt_per; a.splits = pl.splits;
-    const int64_t mt = a.tiles_m ? a.tiles_m : (a.M + TILE_M[pl.tile] - 1) / TILE_M[pl.tile];
-    const int64_t tiles = mt * ((a.N + TILE_N[pl.tile] - 1) / TILE_N[pl.tile]);
+    lay_tiles(c);
     if (pl.splits > 1) {
         if (pl.tile != TILE_64) return hipErrorInvalidValue;      // (nor does this happen)
         a.count = (unsigned*)ws;
         a.part = (float*)((char*)ws + LPM_COUNT_BYTES);
-        if (tiles > (int64_t)(LPM_COUNT_BYTES / 4) || tiles > pl.tiles) return hipErrorInvalidValue;      // (the plan's cap keeps this out)
+        if (c.tiles > (int64_t)(LPM_COUNT_BYTES / 4) || c.tiles > pl.tiles) return hipErrorInvalidValue;      // (the plan's cap keeps this out)
         if (!ws_zeroed) {
             const hipError_t e = launch_zero_counts(&ws, 1, st);
             if (e != hipSuccess) return e;
         }
     }
-    if (mode == MODE_FWD) return dtype == LPM_BF16 ? go_uni<bf16_t, MODE_FWD, BT_NONE>(pl, a, tiles, st) : go_uni<float, MODE_FWD, BT_NONE>(pl, a, tiles, st);
-    if (mode == MODE_UNPOOL) return go_uni<bf16_t, MODE_UNPOOL, BT_NONE>(pl, a, tiles, st);
-    if (dtype == LPM_BF16) return a.stride == 1 ? go_uni<bf16_t, MODE_DGRAD, BT_NONE>(pl, a, tiles, st) : go_uni<bf16_t, MODE_DGRAD_S, BT_NONE>(pl, a, tiles, st);
-    if (a.kscale) return a.stride == 1 ? go_uni<float, MODE_DGRAD, BT_SCALED>(pl, a, tiles, st) : go_uni<float, MODE_DGRAD_S, BT_SCALED>(pl, a, tiles, st);
-    return a.stride == 1 ? go_uni<float, MODE_DGRAD, BT_PLAIN>(pl, a, tiles, st) : go_uni<float, MODE_DGRAD_S, BT_PLAIN>(pl, a, tiles, st);
+    if (hold) {
+        memcpy(hold->bytes, &c, sizeof(c));
+        hold->held = true;
+        return hipSuccess;
+    }
+    if (with && with->held) {
+        IgemmCall x;
+        memcpy(&x, with->bytes, sizeof(x));
+        if (pairs(x, c)) {
+            with->held = false;
+            return run_pair(x, c, st);
+        }
+        const hipError_t e = run_held(*with, st);
+        if (e != hipSuccess) return e;
+    }
+    return go_call(c, st);
+}
+
+hipError_t run_held(HeldCall& h, hipStream_t st) {
+    if (!h.held) return hipSuccess;
+    h.held = false;
+    IgemmCall x;
+    memcpy(&x, h.bytes, sizeof(x));
+    const hipEvent_t end = take_stop_event();      // (not this kernel's: the one that follows it)
+    const hipError_t e = go_call(x, st);
+    give_stop_event(end);
+    return e;
 }
 
 hipError_t mfma_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* scale, const float* bias,
-                         const void* add, int relu, void* y, void* ws, bool ws_zeroed, hipStream_t st, void* pool_y) {
+                         const void* add, int relu, void* y, void* ws, bool ws_zeroed, hipStream_t st, void* pool_y,
+                         HeldCall* hold, HeldCall* with) {
     if (pool_y && (add || !mfma_fwd_pools(dtype, g))) return hipErrorInvalidValue;
     const int es = dtype == LPM_BF16 ? 2 : 4;
     IgemmArgs a{};
@@ -666,7 +795,7 @@ hipError_t mfma_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void
     a.a_bytes = (unsigned)(g.rows_in() * g.Cin * es);
     a.b_pitch = (unsigned)((int64_t)g.K() * es);
     a.b_bytes = (unsigned)((int64_t)g.Cout * g.K() * es);
-    return run_igemm(dtype, MODE_FWD, a, plan_fwd(dtype, g), ws, ws_zeroed, st);
+    return run_igemm(dtype, MODE_FWD, a, plan_fwd(dtype, g), ws, ws_zeroed, st, hold, with);
 }
 
 // wt: weights laid out [Cin][taps][Cout] (bf16); float layers pass w itself, [Cout][taps][Cin]
@@ -674,7 +803,8 @@ hipError_t mfma_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void
 // side (may be NULL): the gradient is the last contribution to a tensor whose producer's epilogue backward this kernel
 // performs -- see DgradSide
 hipError_t mfma_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const void* wt, void* dx, int accumulate, const void* mask,
-                           const float* mscale, void* ws, bool ws_zeroed, hipStream_t st, const UnpoolDesc* unpool, const DgradSide* side, const float* kscale) {
+                           const float* mscale, void* ws, bool ws_zeroed, hipStream_t st, const UnpoolDesc* unpool, const DgradSide* side, const float* kscale,
+                           HeldCall* hold, HeldCall* with) {
     if (kscale && (dtype == LPM_BF16 || g.Cout > MAX_KSCALE)) return hipErrorInvalidValue;      // (bf16: the transposed copy carries the scale)
     if (unpool && (side || dtype != LPM_BF16 || g.stride != 1 || g.Cin % 8)) return hipErrorInvalidValue;      // (the epilogue routes whole chunks of eight channels)
     const int es = dtype == LPM_BF16 ? 2 : 4;
@@ -697,20 +827,7 @@ hipError_t mfma_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const v
     a.a_bytes = (unsigned)(g.rows_out() * g.Cout * es);
     a.b_pitch = (unsigned)((int64_t)g.taps() * (dtype == LPM_BF16 ? g.Cout : g.Cin) * es);
     a.b_bytes = (unsigned)((int64_t)g.Cout * g.K() * es);
-    const IgemmPlan pl = plan_dgrad(dtype, g);
-    if (g.stride > 1) {          // row tiles per residue class (d % stride, h % stride, w % stride)
-        const int s = g.stride, ncls = (g.D > 1 ? s : 1) * s * s, bm = TILE_M[pl.tile];
-        int t = 0;
-        for (int c = 0; c < ncls; ++c) {
-            a.cls_tile0[c] = t;
-            const int pd = c / (s * s), ph = (c / s) % s, pw = c % s;
-            const int64_t Dc = g.D > 1 ? (g.D - pd + s - 1) / s : 1, Hc = (g.H - ph + s - 1) / s, Wc = (g.W - pw + s - 1) / s;
-            t += (int)(((int64_t)g.m * Dc * Hc * Wc + bm - 1) / bm);
-        }
-        for (int c = ncls; c <= 16; ++c) a.cls_tile0[c] = t;
-        a.tiles_m = t;
-    }
-    return run_igemm(dtype, unpool ? MODE_UNPOOL : MODE_DGRAD, a, pl, ws, ws_zeroed, st);
+    return run_igemm(dtype, unpool ? MODE_UNPOOL : g.stride > 1 ? MODE_DGRAD_S : MODE_DGRAD, a, plan_dgrad(dtype, g), ws, ws_zeroed, st, hold, with);
 }
 
 // clears the arrival counts at the head of up to 16 scratch areas

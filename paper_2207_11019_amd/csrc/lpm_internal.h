@@ -39,6 +39,7 @@ hipError_t launch_spin(long long ticks, hipStream_t st);
 // itself the event costs 2.4 and 8 us.  A launcher takes the event for its last kernel (launch_last); where it does not -- it
 // launched nothing, or its last kernel is of the kind that does not ask -- finish() records it the usual way.  (Per thread.)
 hipEvent_t take_stop_event();
+void give_stop_event(hipEvent_t e);      // puts back what take_stop_event gave
 class StopEvent {
 public:
     StopEvent(hipEvent_t e, hipStream_t st);      // e may be NULL: nothing happens
@@ -103,11 +104,17 @@ struct ConvGeom {
 constexpr size_t LPM_COUNT_BYTES = 4096;
 hipError_t launch_zero_counts(void* const* heads, int n, hipStream_t st);
 
+// Two contractions of which neither reads the other's result can share a launch.  A launcher that is given `hold` keeps its call there
+// instead of launching it, if its kernel is one that can share (held is then set); the launcher of the next call gets it as
+// `with` and launches both, together or one after the other.  Whoever holds a call sees to it that it runs (run_held).
+struct HeldCall { alignas(16) unsigned char bytes[768]; bool held = false; };
+hipError_t run_held(HeldCall& h, hipStream_t st);
+
 // y = relu?( scale_c * conv(x, w) + bias_c + add )      (scale, bias, add may be NULL)
 // pool_y (may be NULL; only when fwd_can_pool and add == NULL): also stores the 2x2 max-pooling of y, [m][Ho/2][Wo/2][Cout]
 hipError_t launch_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* scale,
                            const float* bias, const void* add, int relu, void* y, void* ws, hipStream_t st,
-                           void* pool_y = nullptr, bool ws_zeroed = false);
+                           void* pool_y = nullptr, bool ws_zeroed = false, HeldCall* hold = nullptr, HeldCall* with = nullptr);
 bool fwd_can_pool(int dtype, const ConvGeom& g);
 // dx (+)= conv_transpose(dz, w);  then, when given, dx = dx * [mask > 0] * mscale_c -- the epilogue backward of
 // the layer that produced the tensor dx belongs to (mask = that tensor, mscale = that layer's scale)
@@ -127,7 +134,7 @@ struct DgradSide { const void* earlier; void* shortcut; int shortcut_acc; const 
 hipError_t launch_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const void* w, const void* wt,
                              void* dx, int accumulate, const void* mask, const float* mscale, void* ws, hipStream_t st,
                              const UnpoolDesc* unpool = nullptr, const DgradSide* side = nullptr, const float* dzscale = nullptr,
-                             bool ws_zeroed = false);
+                             bool ws_zeroed = false, HeldCall* hold = nullptr, HeldCall* with = nullptr);
 bool dgrad_scales_dz(int dtype, const ConvGeom& g);
 bool dgrad_has_side(int dtype, const ConvGeom& g);
 bool dgrad_can_unpool(int dtype, const ConvGeom& g);

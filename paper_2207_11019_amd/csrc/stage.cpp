@@ -261,6 +261,23 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
         lr.pool_fwd = i + 1;
         s->Ly(i + 1).pooled_fwd = true;
     }
+    // A projection and the layer of the block that stands beside it do not read each other's results: forward, the projection
+    // and the layer before it; backward, where the projection's dz is there with that of the layer that adds it, those two.
+    // Small contractions share a launch then.
+    for (int32_t i = first; i + 1 < last; ++i) {
+        LayerRt& lr = s->Ly(i);
+        LayerRt& nx = s->Ly(i + 1);
+        if (!has_weights(lr.d) || !has_weights(nx.d) || nx.d.src == i) continue;
+        lr.hold_fwd = nx.d.add_src != i && lr.pool_fwd < 0;
+        int n_src, n_add;
+        uses(i, n_src, n_add);
+        // what a data gradient writes: the gradient of its source, and maybe that of the shortcut of the layer that made the source
+        auto shortcut_of = [&](int32_t t) { return t >= first ? s->Ly(t).d.add_src : LPM_NONE; };
+        const int32_t a0 = nx.d.src, a1 = shortcut_of(a0), b0 = lr.d.src, b1 = shortcut_of(b0);
+        const bool apart = a0 != b0 && a1 != b0 && a0 != b1 && (a1 != b1 || a1 == LPM_NONE);
+        nx.hold_bwd = nx.d.add_src == i && n_src == 0 && n_add == 1 && apart && nx.unpool_of < 0 && lr.unpool_of < 0 &&
+                      lr.d.add_src == LPM_NONE && !(lr.d.flags & LPM_RELU) && (!(lr.d.flags & LPM_SCALE) || lr.dz_unscaled || lr.via_shortcut);
+    }
     // Weight gradients are launched in groups of consecutive layers (the same groups in every form of the backward pass: what a
     // launch holds decides how its reductions are cut): up to eight layers, as long as they are small enough to be better off together;
     // next to the network's input, where the micro-batch waits for the last weight gradient, one and two.
@@ -469,6 +486,7 @@ int32_t lpm_stage_forward_on(lpm_stage* s, const void* x, void* y, const int32_t
     if (s->loss && (((uintptr_t)labels & 3u) || ((uintptr_t)loss_accum & 3u))) return fail(LPM_EALIGN, "labels / loss_accum must be 4-byte aligned");
     hipStream_t st = (hipStream_t)stream;
     if (s->fwd_counts && !counts_zeroed) LPM_HIP(launch_zero_counts(&fwd_ws, 1, st));
+    HeldCall held;
     for (int32_t i = s->first; i < s->last; ++i) {
         const LayerRt& lr = s->Ly(i);
         const lpm_layer& l = lr.d;
@@ -484,7 +502,8 @@ int32_t lpm_stage_forward_on(lpm_stage* s, const void* x, void* y, const int32_t
                 const float* bi = lr.b_off != NO ? params + lr.b_off : nullptr;
                 const void* add = l.add_src != LPM_NONE ? tptr(s, l.add_src, x, y, stash) : nullptr;
                 void* pooled = lr.pool_fwd >= 0 ? const_cast<void*>(tptr(s, lr.pool_fwd, x, y, stash)) : nullptr;
-                LPM_HIP(launch_conv_fwd(s->dtype, lr.g, in, w, sc, bi, add, (l.flags & LPM_RELU) != 0, outp, fwd_ws, st, pooled, true));
+                LPM_HIP(launch_conv_fwd(s->dtype, lr.g, in, w, sc, bi, add, (l.flags & LPM_RELU) != 0, outp, fwd_ws, st, pooled, true,
+                                        lr.hold_fwd ? &held : nullptr, &held));
                 break;
             }
             case LPM_MAXPOOL2:
@@ -640,6 +659,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
         for (int k = 0; k < n; ++k) if (d[k].splits > 0) red.push_back(d[k]);
         return hipSuccess;
     };
+    HeldCall held;                         // a data gradient that waits for the next layer's
     std::vector<hipGraphNode_t> wtail;     // capture: frontier left by the last weight gradient
     auto frontier = [&](std::vector<hipGraphNode_t>& out) -> hipError_t {
         hipStreamCaptureStatus stt;
@@ -807,8 +827,9 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                         if (do_data && unpool.dst) LPM_HIP(launch_conv_dgrad(s->dtype, lr.g, dz, w, wt, nullptr, 0, nullptr, nullptr, counts, st, &unpool,
                                                                              nullptr, lr.dz_unscaled ? sc : nullptr, true));
                     } else if (do_data) {
+                        const bool hold = lr.hold_bwd && (s->Ly(i - 1).d.src >= first || dx);
                         LPM_HIP(launch_conv_dgrad(s->dtype, lr.g, dz, w, wt, gsrc, gsrc_acc, gmask, gmscale, counts, st, nullptr,
-                                                  use_side ? &side : nullptr, lr.dz_unscaled ? sc : nullptr, true));
+                                                  use_side ? &side : nullptr, lr.dz_unscaled ? sc : nullptr, true, hold ? &held : nullptr, &held));
                     }
                     LPM_HIP(stop.finish());
                     at_point = ev;

@@ -35,6 +35,8 @@ struct LayerRt {
     bool shortcut_is_dz = false;                 // its shortcut's gradient is this layer's dz, element for element, and is only read: it is not
                                                  // stored a second time (fused_in, or the stage's last layer when the next stage hands down its dz)
     bool wg_end = false;                         // the last layer, in backward order, of a group whose weight gradients share launches
+    bool hold_fwd = false;                       // its forward contraction may share a launch with the next layer's
+    bool hold_bwd = false;                       // its data gradient may share a launch with the layer's before it, which made its shortcut
     int32_t pool_fwd = -1;                       // conv/FC: index of the max-pooling layer whose forward its own forward kernel performs
     bool pooled_fwd = false;                     // max-pooling: its forward runs inside its producer's forward kernel
     bool unpooled = false;                       // max-pooling: its backward runs inside its consumer's data gradient

@@ -105,6 +105,7 @@ hipEvent_t take_stop_event() {
     t_stop = nullptr;
     return e;
 }
+void give_stop_event(hipEvent_t e) { t_stop = e; }
 StopEvent::StopEvent(hipEvent_t e, hipStream_t st) : e_(e), st_(st) { t_stop = e; }
 StopEvent::~StopEvent() { t_stop = nullptr; }
 hipError_t StopEvent::finish() { return e_ && take_stop_event() ? hipEventRecord(e_, st_) : hipSuccess; }

@@ -86,6 +86,22 @@ def pooled_beside(c, h, m):
     return layers, m
 
 
+def branch(cin, c, mid, w, h, m, s=1, shared=False):
+    """A block with a projection, both of stride s; shared: its last layer reads what the projection reads."""
+    g = (h - 1) // s + 1
+    if shared:
+        return chain(C(cin, c, 1, 1, h, h), C(c, w, 1, 1, h, h, relu=False, scale=True, src=0), C(c, w, 3, 3, h, h, p=1, scale=True, src=0, add=1),
+                     C(w, c, 1, 1, h, h)), m
+    return chain(C(cin, c, 1, 1, h, h), C(c, mid, 3, 3, h, h, s=s, p=1, scale=True, src=0), C(c, w, 1, 1, h, h, s=s, relu=False, scale=True, src=0),
+                 C(mid, w, 3, 3, g, g, p=1, scale=True, src=1, add=2), C(w, c, 1, 1, g, g)), m
+
+
+def added_source(c, h, m):
+    """A projection that reads the tensor which the layer beside it adds."""
+    return chain(C(c, c, 1, 1, h, h, scale=True), C(c, c, 3, 3, h, h, p=1, scale=True, src=0, add=0), C(c, c, 1, 1, h, h, relu=False, scale=True, src=0),
+                 C(c, c, 3, 3, h, h, p=1, scale=True, src=1, add=2), C(c, c, 1, 1, h, h)), m
+
+
 def long_projection(cin, w, mid, h, wd, m):
     """The same with filters of 13 x 1."""
     return chain(C(cin, cin, 1, 1, h, wd), C(cin, mid, 13, 1, h, wd, scale=True, src=0), C(cin, w, 13, 1, h, wd, relu=False, bias=False, scale=True, src=0),
@@ -121,6 +137,20 @@ NETS = {
     "read_thrice_float": (read_thrice(20, 14, 3), "f32"),
     "pooled_beside": (pooled_beside(64, 16, 3), "bf16"),
     "pooled_beside_float": (pooled_beside(20, 16, 3), "f32"),
+    # contractions that share a launch: strided and not, in whole K tiles and in chunks, with one of them split, of more blocks than
+    # the card has CUs; and those that cannot: both split, or reading or writing the same gradient
+    "pair": (branch(16, 64, 64, 128, 9, 2), "bf16"),
+    "pair_ragged": (branch(16, 40, 24, 72, 11, 2), "bf16"),
+    "pair_split": (branch(16, 64, 512, 256, 8, 2, s=2), "bf16"),
+    "pair_strided_ragged": (branch(16, 40, 24, 72, 17, 2, s=2), "bf16"),
+    "pair_large": (branch(16, 64, 64, 128, 64, 8, s=2), "bf16"),
+    "pair_float": (branch(8, 32, 64, 96, 17, 2), "f32"),
+    "pair_float_large": (branch(8, 32, 64, 64, 64, 12, s=2), "f32"),
+    "pair_float_ragged": (branch(8, 20, 44, 36, 65, 12, s=2), "f32"),
+    "pair_both_split": (branch(16, 1536, 64, 64, 4, 2, s=2), "bf16"),
+    "pair_shared": (branch(16, 64, 0, 64, 12, 2, shared=True), "bf16"),
+    "pair_added": (added_source(64, 12, 2), "bf16"),
+    "pair_added_float": (added_source(32, 12, 2), "f32"),
     # layers whose dz carries their scale (their filter is too long for the weight gradients that multiply by it): the block's input, and
     # a projection
     "scaled_dz": ((chain(C(6, 16, 13, 1, 20, 12, bias=False, scale=True), C(16, 40, 3, 3, 8, 12, p=1, scale=True)), 2), "bf16"),
