@@ -44,7 +44,7 @@ struct IgemmArgs {
     const uint16_t* pool_x; // stride-1 data gradient routed through a 2x2 max-pooling (see UnpoolDesc): its input [m][2*Hr][2*Wr][N]
     uint16_t* pool_dst;
     int pool_acc, pool_mask;
-    uint16_t* fwd_pool;     // forward: also store the 2x2 max-pooling of C, [m][Hr/2][Wr/2][N] (Wr = 2, 4, 8 or 16)
+    uint16_t* fwd_pool;     // forward: also store the 2x2 max-pooling of C, [m][Hr/2][Wr/2][N] (Wr = 2, 4, 8, 16 or 32)
 };
 
 // ---- eight consecutive channels of a row -----------------------------------------------------------
@@ -196,7 +196,7 @@ struct Epilogue {
                 st8(t8, v);
             }
         }
-        if (FWD && p.fwd_pool) pool(p, area, row0, col0, rows, lane);
+        if (FWD && p.fwd_pool && p.Wr < 32) pool(p, area, row0, col0, rows, lane);
     }
 
     // forward, 2x2 max-pooling of the stored values: a piece's 32 rows are whole pairs of image rows, eight windows of rows
@@ -221,6 +221,24 @@ struct Epilogue {
 #pragma unroll
             for (int k = 0; k < 8; ++k) a[k] = fmaxf(fmaxf(a[k], b[k]), fmaxf(c[k], d[k]));
             st8((bf16_t*)p.fwd_pool + (size_t)((r0 >> 2) + w) * p.N + col, a);
+        }
+    }
+
+    // the same for images 32 wide: an image row is a piece, its windows reach into the next one (the wavefront's own, or another's
+    // that has stored it)
+    __device__ __forceinline__ void pool32(const IgemmArgs& p, const float* upper, const float* lower, int row0, int col0, int rows, int lane) {
+        const int ch = (lane % CPR) * 8, col = col0 + ch;
+        if (row0 >= rows || col >= p.N) return;
+#pragma unroll
+        for (int w = lane / CPR; w < 16; w += RPP) {
+            float a[8], b[8], c[8], d[8];
+            un8(ld_raw8(upper + 2 * w * PITCH + ch), a);
+            un8(ld_raw8(upper + (2 * w + 1) * PITCH + ch), b);
+            un8(ld_raw8(lower + 2 * w * PITCH + ch), c);
+            un8(ld_raw8(lower + (2 * w + 1) * PITCH + ch), d);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) a[k] = fmaxf(fmaxf(a[k], b[k]), fmaxf(c[k], d[k]));
+            st8((bf16_t*)p.fwd_pool + (size_t)((row0 >> 2) + w) * p.N + col, a);
         }
     }
 

@@ -46,6 +46,15 @@ def test_pooling_backward_before_a_convolution(lpm, c1, c2, k, p, dtype):
     stage_backward_isolated(lpm, layers, [0, 3], 3, 3, dtype, seed=21, dx_wanted=True, check_forward=True, grad_std=1.0)
 
 
+# forward pooling of images 32 wide, whose windows span two pieces of a tile: on every tile, split, in ragged channels, one row of windows
+@pytest.mark.parametrize("m,cin,c,h", [(2, 16, 24, 32), (1, 256, 64, 32), (3, 64, 72, 2), (24, 16, 64, 32), (24, 16, 128, 32), (24, 32, 256, 32)],
+                         ids=["ragged", "split", "one_row", "tile128x64", "tile128", "large"])
+def test_pooling_forward_of_rows_of_32(lpm, m, cin, c, h):
+    layers = chain(C(cin, c, 3, 3, h, 32, p=1, scale=True), P(c, h, 32), C(c, 16, 1, 1, h // 2, 16))
+    print("m", m, "channels", cin, c, "height", h, flush=True)
+    stage_backward_isolated(lpm, layers, [0, 3], m, m, 1, seed=27, dx_wanted=True, check_forward=True, grad_std=1.0)
+
+
 def bottlenecks(w, mid, h, m, shortcuts, first_scale=True):
     """Stem, then blocks 1x1 reduce - 1x1 expand + shortcut, then one more reduction that keeps the last block inside the stage.
     shortcuts: the tensor each block adds ('x': the block's input, 'in': the stage's)."""
