@@ -195,7 +195,7 @@ int32_t fwd_op(lpm_schedule* s, const RunArgs& a, int32_t z, int32_t j, hipStrea
 // by_layer: the two phases come as separate calls and the weight phase follows the data phase layer by layer
 int32_t bwd_op(lpm_schedule* s, const RunArgs& a, int32_t z, int32_t j, hipStream_t st, hipStream_t wst,
                int32_t phases = LPM_PHASE_DATA | LPM_PHASE_WEIGHTS, int32_t ver = -1, bool by_layer = false,
-               hipStream_t wst2 = nullptr, hipEvent_t data_done = nullptr, hipEvent_t weights_done = nullptr) {
+               hipStream_t wst2 = nullptr, hipEvent_t data_done = nullptr, hipEvent_t weights_done = nullptr, int32_t wpart = LPM_WEIGHTS_ALL) {
     lpm_stage* sg = s->st[(size_t)z];
     const int32_t slot = j % s->window;
     const lpm_stage_buffers& b = a.bufs[z];
@@ -212,7 +212,7 @@ int32_t bwd_op(lpm_schedule* s, const RunArgs& a, int32_t z, int32_t j, hipStrea
                                  ver < 0 ? j > 0 : 0, b.bwd_ws, st, wst, j & 1, phases, staged ? j : -1,
                                  staged ? s->M : 0, by_layer ? j % LPM_MAX_WINDOW : -1,
                                  (s->cut_fused[(size_t)z] ? LPM_MASK_DX : 0) | (z + 1 < s->Z && s->cut_fused[(size_t)z + 1] ? LPM_DY_IS_DZ : 0),
-                                 wst2, true, data_done, &s->pt_b[(size_t)j * s->Z + z], weights_done);
+                                 wst2, true, data_done, &s->pt_b[(size_t)j * s->Z + z], weights_done, wpart);
 }
 
 // ver < 0: the one update of the synchronous step; else U_{z,ver}: version ver -> version ver + 1
@@ -367,8 +367,17 @@ int32_t overlapped_role(lpm_schedule* s, const RunArgs& a, int32_t role, uint64_
         if (own0) LPM_HIP(hipStreamWaitEvent(st, s->ev_w[i + 1], 0));
         return LPM_OK;
     };
+    // LOCKED: the last group of stage 0's weight gradients, whose dz the data phase makes last, follows it on its own stream: on the
+    // weight stream it started a hand-over later, and the next forward chain another one after it (us per step: float ResNet-18
+    // 2547 -> 2503, width-48 ResNet 2208 -> 2144, VGG-16/CIFAR 2709 -> 2614).  OVERLAPPED, the forward stream is busy with another
+    // forward chain meanwhile: VGG-16/CIFAR 1817 -> 1875.
+    auto closes_here = [&](int32_t j) { return locked && !a.dx_wanted && j < M - 1; };
     if (role == 0) {
         for (int32_t j = 0; j < M; ++j) {
+            if (j > 0 && closes_here(j - 1)) {
+                if ((rc = await_record(s, s->rec_b[(size_t)(j - 1) * Z], epoch))) return rc;
+                if ((rc = bwd_op(s, a, 0, j - 1, a.sb, a.sf, LPM_PHASE_WEIGHTS, -1, false, nullptr, nullptr, nullptr, LPM_WEIGHTS_LAST))) return rc;
+            }
             // F_{0,j} after B_{0,j-W}, the last operation of micro-batch j-W; the other stages follow in stream order
             if (j >= W && (rc = await_microbatch(j - W, a.sf))) return rc;
             for (int32_t z = 0; z < Z; ++z)
@@ -416,7 +425,8 @@ int32_t overlapped_role(lpm_schedule* s, const RunArgs& a, int32_t role, uint64_
                 // (LOCKED: the next forward chain is on the data phase's own stream)
                 const bool rest = by_layer && (!locked || j == M - 1) && s->pt_b[i] == s->ev_b[i];
                 const bool closes = !async && j < M - 1 && !rest && (z == 0 || (own0 && z == 1));
-                if ((rc = bwd_op(s, a, z, j, a.sb, sw, LPM_PHASE_WEIGHTS, async ? j : -1, by_layer, sw_pair, nullptr, closes ? s->ev_w[i] : nullptr))) return rc;
+                if ((rc = bwd_op(s, a, z, j, a.sb, sw, LPM_PHASE_WEIGHTS, async ? j : -1, by_layer, sw_pair, nullptr, closes ? s->ev_w[i] : nullptr,
+                                 z == 0 && closes_here(j) ? LPM_WEIGHTS_BUT_LAST : LPM_WEIGHTS_ALL))) return rc;
                 if (rest) LPM_HIP(hipStreamWaitEvent(sw, s->ev_b[i], 0));
                 if (closes) closed[z] = true;
                 if (async) {

@@ -544,6 +544,7 @@ extern "C" int32_t lpm_stage_backward(lpm_stage* s, const void* x, const void* y
 // parity (0 / 1) selects the copy of the gradient / dz area in bwd_ws this pass uses.
 // data_done (eager): an event for the end of the data phase; *data_point is the event to wait for, data_done or a layer's that
 // stands at the same point.  weights_done: an event for the end of the weight phase on wstream.
+// wpart (a weight phase by itself): its last group of layers, or the others, each with the sums of its own partial results.
 // While `stream` is being captured the weight gradients stay on it and are taken out of its dependency
 // frontier instead.
 // wstream2 (with wstream, eager only): every other group of weight gradients of the phase runs on this second stream, forked from
@@ -552,7 +553,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                               const float* params, const void* lowp, const void* stash, float* grads,
                               int32_t accumulate, void* bwd_ws, void* stream, void* wstream, int32_t parity,
                               int32_t phases, int32_t fc_slot, int32_t fc_flush, int32_t layer_slot, int32_t boundary, void* wstream2,
-                              bool counts_zeroed, hipEvent_t data_done, hipEvent_t* data_point, hipEvent_t weights_done) {
+                              bool counts_zeroed, hipEvent_t data_done, hipEvent_t* data_point, hipEvent_t weights_done, int32_t wpart) {
     if ((boundary & LPM_MASK_DX) && !lpm_stage_can_mask_dx(s)) return fail(LPM_EINVAL, "internal: this stage cannot mask its input gradient");
     if ((boundary & LPM_DY_IS_DZ) && !lpm_stage_takes_dz(s)) return fail(LPM_EINVAL, "internal: this stage needs the gradient of its output");
     if (layer_slot >= LPM_MAX_WINDOW) return fail(LPM_EINVAL, "internal: layer event slot out of range");
@@ -581,6 +582,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
     const bool deferred = cap == hipStreamCaptureStatusNone;
     const bool do_data = (phases & LPM_PHASE_DATA) != 0, do_weights = (phases & LPM_PHASE_WEIGHTS) != 0;
     if (!deferred && !(do_data && do_weights)) return fail(LPM_EINVAL, "a captured backward pass cannot be split into phases");
+    if (wpart != LPM_WEIGHTS_ALL && do_data) return fail(LPM_EINVAL, "internal: a weight phase in parts comes by itself");
     if (!do_data && (!do_weights || !wstream)) return fail(LPM_EINVAL, "internal: bad phase selection");
     if (do_data && s->bwd_counts && !counts_zeroed) LPM_HIP(launch_zero_counts(&counts, 1, st));
     // layer_slot >= 0 (the two phases come as separate calls with the same slot): the data phase records, per weight
@@ -895,14 +897,20 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
         *data_point = at_point;
     }
     if (do_weights && (beside || !jobs.empty())) {
-        hipStream_t wst2 = (wstream && wstream2 && deferred && jobs.size() > (size_t)WG_LAYERS) ? (hipStream_t)wstream2 : nullptr;
+        size_t from = 0, to = jobs.size();
+        if (wpart != LPM_WEIGHTS_ALL) {
+            size_t last = to - 1;                 // the first layer of the last group
+            while (last > 0 && !jobs[last - 1].lr->wg_end) --last;
+            (wpart == LPM_WEIGHTS_LAST ? from : to) = last;
+        }
+        hipStream_t wst2 = (wstream && wstream2 && deferred && to - from > (size_t)WG_LAYERS) ? (hipStream_t)wstream2 : nullptr;
         if (wst2 == wst) wst2 = nullptr;
         if (wst2) {        // ordered after everything the phase's stream holds (the previous micro-batch's reduction reads the areas written now)
             LPM_HIP(hipEventRecord(s->ev_w2_fork, wst));
             LPM_HIP(hipStreamWaitEvent(wst2, s->ev_w2_fork, 0));
         }
         int groups = 0;
-        for (size_t k = 0, from = 0; k < jobs.size(); ++k) {
+        for (size_t k = from; k < to; ++k) {
             if (!jobs[k].lr->wg_end) continue;
             hipStream_t q = (wst2 && (groups++ & 1)) ? wst2 : wst;
             if (by_layer)

@@ -81,13 +81,14 @@ struct lpm_stage {
     const lpm::LayerRt& Ly(int32_t i) const { return lay[(size_t)(i - first)]; }
 };
 
+enum { LPM_WEIGHTS_ALL = 0, LPM_WEIGHTS_BUT_LAST = 1, LPM_WEIGHTS_LAST = 2 };      // a weight phase, or its last group of layers by itself, or the others
 // B_{z,j} with the weight phase on a stream of the caller's choice (see stage.cpp).
 int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const void* dy, void* dx,
                               const float* params, const void* lowp, const void* stash, float* grads,
                               int32_t accumulate, void* bwd_ws, void* stream, void* wstream, int32_t parity,
                               int32_t phases, int32_t fc_slot = -1, int32_t fc_flush = 0, int32_t layer_slot = -1,
                               int32_t boundary = 0, void* wstream2 = nullptr, bool counts_zeroed = false, hipEvent_t data_done = nullptr, hipEvent_t* data_point = nullptr,
-                              hipEvent_t weights_done = nullptr);
+                              hipEvent_t weights_done = nullptr, int32_t wpart = LPM_WEIGHTS_ALL);
 // F_{z,j}; counts_zeroed, done: see stage.cpp
 int32_t lpm_stage_forward_on(lpm_stage* s, const void* x, void* y, const int32_t* labels, float* loss_accum, const float* params,
                              const void* lowp, void* stash, void* fwd_ws, float loss_scale, void* stream, bool counts_zeroed, hipEvent_t done = nullptr);
