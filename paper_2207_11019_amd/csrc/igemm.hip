@@ -10,10 +10,11 @@
 //
 // Structure.  A K tile is 128 bytes of K (64 bf16 or 32 float values) of BM rows of A and BN rows of B, copied straight from
 // global memory to LDS (buffer_load ... lds: no registers, no LDS stores), through a ring of NST stages with one workgroup
-// barrier per tile.  LDS rows are 128 bytes without padding; chunk c (16 bytes) of row r lies at position c ^ (r % 8), so the
-// operand reads of a wavefront (one chunk of 32 consecutive rows per half) fall on distinct banks.  Out-of-range chunks --
-// padding taps, ragged rows -- load zeros through the buffer bounds check.  Whether a row meets a tap is one bit test against
-// a mask made once per row.
+// barrier per tile.  LDS rows are 128 bytes without padding; chunk c (16 bytes) of row r lies at position c ^ (r / 2 % 8), so the
+// operand reads of a wavefront (one chunk of 32 consecutive rows per half) fall on distinct banks: two rows span the 64 of them,
+// and rows of one parity share theirs (with c ^ (r % 8) half of them idled: 0.94 M conflict cycles in a launch of 3x3 256 -> 256
+// at 16 x 14^2, 0.01 M now; 128x128 tiles, 128 x 14^2 x 256 channels 3x3: 36.3 -> 34.6 us).  Out-of-range chunks -- padding taps, ragged
+// rows -- load zeros through the buffer bounds check.  Whether a row meets a tap is one bit test against a mask made once per row.
 // A channel count that is a multiple of 128 bytes lets a whole K tile lie in one tap (UNI): the tap is wave-uniform.
 // Otherwise every lane follows its own chunk's tap through a table in LDS, so any multiple of 16 bytes of channels works.
 //
@@ -28,8 +29,8 @@
 
 namespace lpm {
 
-// Chunks per lane whose epilogue operands are held across the main loop.  Two: the 64x64 tile (125 registers instead of 98).
-// With the wider tiles too (183-220 registers) they gained alone, but fewer of the other streams' wavefronts fitted beside
+// Chunks per lane whose epilogue operands are held across the main loop.  Two: the 64x64 tile (124 registers, 140 of a data
+// gradient).  With the wider tiles too they gained alone, but fewer of the other streams' wavefronts fitted beside
 // them: VGG-16/224 7.05 -> 7.18 ms per step.
 constexpr int EARLY_ROWS = 2;
 
@@ -537,7 +538,7 @@ static IgemmPlan plan_igemm(int es, int64_t M, int N, int kt) {
     IgemmPlan pl{};
     pl.tile = TILE_64;
     if (es == 2) {
-        // Measured alone on MI355X (us, 64x64 / 128x64 / 128x128 / 128x128 of 8 wavefronts):
+        // Measured alone on MI355X (us, 64x64 / 128x64 / 128x128 of 4 wavefronts, which 8 have replaced / of 8 wavefronts):
         //   25088 x 256, K 2304: 51 / 46 / 39 / 43     12544 x 256, K 2304: 31 / 25 / 25 / 22      6272 x 512, K 2304: 33 / 25 / 27 / 24
         //    3136 x 512, K 4608: 26 / 29 / 47 / 34      3136 x 256, K 2304: 13 / 17 / 24 / 21     17496 x 160, K  864: 19 / 15 / 21 / 26
         // Alone, 64x64 wins up to some 384 tiles of 128x64.  Beside the other streams of a step, where the operand traffic of all of them

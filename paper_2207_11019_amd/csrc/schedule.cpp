@@ -406,8 +406,8 @@ int32_t overlapped_role(lpm_schedule* s, const RunArgs& a, int32_t role, uint64_
         // Asynchronous update: B_{z,j+1} waits for U_{z,j}, so the weight phases and updates are a chain per stage; odd
         // stages take the second stream (each stage keeps its stream, which orders its updates).
         const bool async2 = async && Z > 1 && w2 != w1;
-        // A single stage has the second stream to spare: its weight gradients alternate between the two (ResNet-50
-        // conv4_x: 2.43 -> 2.34 ms per step; the weight phases are the longest of the three chains there).
+        // A single stage has the second stream to spare: every other group of its weight gradients goes there (ResNet-50
+        // conv4_x, when each layer was a launch: 2.43 -> 2.34 ms per step; the weight phases are the longest of the three chains there).
         hipStream_t sw_pair = (!async && Z == 1 && w2 != w1) ? w2 : nullptr;
         hipStream_t sw_all = sw, sw_0 = w2;
         for (int32_t j = 0; j < M; ++j) {
