@@ -10,7 +10,8 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 constexpr unsigned OOB = 0xffffffffu;
 
-enum { MODE_FWD = 0, MODE_DGRAD = 1 /* stride 1 */, MODE_DGRAD_S = 2 /* stride 2..4, by residue class */, MODE_UNPOOL = 3 /* stride 1, routed through a max-pooling */ };
+enum { MODE_FWD = 0, MODE_DGRAD = 1 /* stride 1 */, MODE_DGRAD_S = 2 /* stride 2..4, by residue class */, MODE_UNPOOL = 3 /* stride 1, routed through a max-pooling */,
+       MODE_FWD_POOL = 4 /* forward, the rows by pooling window */ };
 
 constexpr int MAX_TAB = 128;              // taps a layer without whole K tiles per tap may have
 constexpr int MAX_KSCALE = 2048;          // channels of a float layer whose data gradient applies its scale (LDS)
@@ -44,7 +45,7 @@ struct IgemmArgs {
     const uint16_t* pool_x; // stride-1 data gradient routed through a 2x2 max-pooling (see UnpoolDesc): its input [m][2*Hr][2*Wr][N]
     uint16_t* pool_dst;
     int pool_acc, pool_mask;
-    uint16_t* fwd_pool;     // forward: also store the 2x2 max-pooling of C, [m][Hr/2][Wr/2][N] (Wr = 2, 4, 8, 16 or 32)
+    uint16_t* fwd_pool;     // forward: also store the 2x2 max-pooling of C, [m][Hr/2][Wr/2][N] (bf16, Wr = 2, 4, 8, 16 or 32; MODE_FWD_POOL: any)
 };
 
 // ---- eight consecutive channels of a row -----------------------------------------------------------
@@ -79,13 +80,24 @@ __device__ __forceinline__ int class_pixel(const IgemmArgs& p, int row, int Hc, 
     return (img * p.Hr + hq * p.stride + ph) * p.Wr + wq * p.stride + pw;
 }
 
+// MODE_FWD_POOL: row 4w + 2y + x is position (y, x) of pooling window w (dWr, dHr: of the pooled image).
+struct WinPixel { int n, h, w; };
+__device__ __forceinline__ WinPixel win_pixel(const IgemmArgs& p, int row) {
+    const int q = row >> 2, t = div_by(q, p.dWr), n = div_by(t, p.dHr);
+    return {n, 2 * (t - n * (p.Hr >> 1)) + ((row >> 1) & 1), 2 * (q - t * (p.Wr >> 1)) + (row & 1)};
+}
+__device__ __forceinline__ int win_row(const IgemmArgs& p, int row) {
+    const WinPixel x = win_pixel(p, row);
+    return (x.n * p.Hr + x.h) * p.Wr + x.w;
+}
+
 // A wavefront's part of the output, MI pieces of 32 rows x 32*NIW channels, held in its private LDS area (rows of 32*NIW + 4
 // floats).  A lane takes 8 channels of a row at a time, so every tensor access is 16 (float: 32) bytes.  load() requests the
 // operands of all the lane's chunks; the kernels call it before their main loop where the registers allow, so that a
 // launch of a few K tiles does not end with a memory latency of its own.
 template <typename E, int MI, int NIW, int MODE>
 struct Epilogue {
-    static constexpr bool FWD = MODE == MODE_FWD;      // (forward: scale, bias, add, relu; data gradient: add, mask, C2, mscale)
+    static constexpr bool WIN = MODE == MODE_FWD_POOL, FWD = MODE == MODE_FWD || WIN;      // (forward: scale, bias, add, relu; data gradient: add, mask, C2, mscale)
     static constexpr int PITCH = NIW * 32 + 4, PIECE = 32 * PITCH, CPR = NIW * 4, RPP = 64 / CPR, NP = 32 / RPP, R = MI * NP;
     Raw8<E> ra[R], rm[FWD ? 1 : R], r2[FWD ? 1 : R];
     float f0[8], f1[8];                       // forward: scale, bias; data gradient: mscale, c2scale
@@ -109,7 +121,7 @@ struct Epilogue {
         for (int q = 0; q < R; ++q) {
             const int row = row0 + q * RPP + lane / CPR;
             const bool live = row < rows && cok;
-            const int prow = MODE == MODE_DGRAD_S && live ? class_pixel(p, row, Hc, Wc, ph, pw, Dc, pd) : row;
+            const int prow = MODE == MODE_DGRAD_S && live ? class_pixel(p, row, Hc, Wc, ph, pw, Dc, pd) : WIN ? win_row(p, row) : row;
             o[q] = live ? prow * p.N + col : -1;
         }
         if (p.add) {
@@ -141,7 +153,7 @@ struct Epilogue {
 #pragma unroll 1
             for (int i = lane; i < total; i += 64) {
                 const int r = i / nc, c = i - r * nc, row = row0 + r, cc = col0 + c;
-                const size_t prow = MODE == MODE_DGRAD_S ? (size_t)class_pixel(p, row, Hc, Wc, ph, pw, Dc, pd) : (size_t)row;
+                const size_t prow = MODE == MODE_DGRAD_S ? (size_t)class_pixel(p, row, Hc, Wc, ph, pw, Dc, pd) : WIN ? (size_t)win_row(p, row) : (size_t)row;
                 const size_t e = prow * p.N + cc;
                 float v = area[r * PITCH + c];
                 if (FWD && p.scale) v *= p.scale[cc];
@@ -155,7 +167,9 @@ struct Epilogue {
                 }
                 if (!FWD && p.mscale) v *= p.mscale[cc];
                 st(out, e, v);
+                if (WIN) area[r * PITCH + c] = sizeof(E) == 2 ? bf2f(f2bf(v)) : v;
             }
+            if (WIN) pool_windows(p, area, row0, col0, rows, lane);
             return;
         }
 #pragma unroll
@@ -192,11 +206,12 @@ struct Epilogue {
             if (o[q] >= 0) st8(out + o[q], v);
             if (FWD && p.fwd_pool) {
 #pragma unroll
-                for (int k = 0; k < 8; ++k) v[k] = bf2f(f2bf(v[k]));
+                for (int k = 0; k < 8; ++k) v[k] = sizeof(E) == 2 ? bf2f(f2bf(v[k])) : v[k];
                 st8(t8, v);
             }
         }
-        if (FWD && p.fwd_pool && p.Wr < 32) pool(p, area, row0, col0, rows, lane);
+        if (WIN) pool_windows(p, area, row0, col0, rows, lane);
+        else if (FWD && p.fwd_pool && p.Wr < 32) pool(p, area, row0, col0, rows, lane);
     }
 
     // forward, 2x2 max-pooling of the stored values: a piece's 32 rows are whole pairs of image rows, eight windows of rows
@@ -224,7 +239,21 @@ struct Epilogue {
         }
     }
 
-    // the same for images 32 wide: an image row is a piece, its windows reach into the next one (the wavefront's own, or another's
+    // MODE_FWD_POOL, any image width and channel count
+    __device__ __forceinline__ void pool_windows(const IgemmArgs& p, const float* area, int row0, int col0, int rows, int lane) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int nc = min(p.N - col0, NIW * 32), nw = min(8 * MI, (rows - row0) >> 2);
+#pragma unroll 1
+        for (int i = lane; i < nw * nc; i += 64) {
+            const int w = i / nc, c = i - w * nc;
+            const float* t = area + 4 * w * PITCH + c;
+            st((E*)p.fwd_pool, (size_t)((row0 >> 2) + w) * p.N + col0 + c, fmaxf(fmaxf(t[0], t[PITCH]), fmaxf(t[2 * PITCH], t[3 * PITCH])));
+        }
+    }
+
+    // pool() for images 32 wide: an image row is a piece, its windows reach into the next one (the wavefront's own, or another's
     // that has stored it)
     __device__ __forceinline__ void pool32(const IgemmArgs& p, const float* upper, const float* lower, int row0, int col0, int rows, int lane) {
         const int ch = (lane % CPR) * 8, col = col0 + ch;

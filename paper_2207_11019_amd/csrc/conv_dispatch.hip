@@ -44,7 +44,8 @@ bool gather_dgrad_ok(int dtype, const ConvGeom& g);
 bool gather_wgrad_ok(int dtype, const ConvGeom& g);
 size_t gather_wgrad_ws_bytes(const ConvGeom& g);
 hipError_t gather_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* scale, const float* bias,
-                           const void* add, int relu, void* y, hipStream_t st);
+                           const void* add, int relu, void* y, hipStream_t st, void* pool_y);
+bool gather_fwd_pools(const ConvGeom& g);
 hipError_t gather_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const float* dzscale, const void* w, void* dx, int accumulate,
                              const void* mask, const float* mscale, hipStream_t st);
 hipError_t gather_conv_wgrad(int dtype, const ConvGeom& g, const void* x, const void* dz, float* dw, float* dbias, const float* rscale,
@@ -85,7 +86,10 @@ size_t wgrad_ws_bytes(int dtype, const ConvGeom& g) {
     return wgrad_generic_ws_bytes(g);
 }
 
-bool fwd_can_pool(int dtype, const ConvGeom& g) { return mfma_fwd_pools(dtype, g); }
+bool fwd_can_pool(int dtype, const ConvGeom& g) {
+    if (fwd_mm(dtype, fc_view(g))) return mfma_fwd_pools(dtype, g);
+    return gather_fwd_ok(dtype, g) && gather_fwd_pools(g);
+}
 
 hipError_t launch_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* scale,
                            const float* bias, const void* add, int relu, void* y, void* ws, hipStream_t st, void* pool_y, bool ws_zeroed,
@@ -94,7 +98,7 @@ hipError_t launch_conv_fwd(int dtype, const ConvGeom& g, const void* x, const vo
     if (fwd_mm(dtype, fc_view(g))) return mfma_conv_fwd(dtype, fc_view(g), x, w, scale, bias, add, relu, y, ws, ws_zeroed, st, pool_y, hold, with);
     const hipError_t e = with ? run_held(*with, st) : hipSuccess;
     if (e != hipSuccess) return e;
-    if (gather_fwd_ok(dtype, g)) return gather_conv_fwd(dtype, g, x, w, scale, bias, add, relu, y, st);
+    if (gather_fwd_ok(dtype, g)) return gather_conv_fwd(dtype, g, x, w, scale, bias, add, relu, y, st, pool_y);
     return conv_fwd_generic_launch(dtype, g, x, w, scale, bias, add, relu, y, st);
 }
 

@@ -56,12 +56,20 @@ __device__ __forceinline__ int2 tap_entry(int k, int K, int Ci, int Kh, int Kw, 
     return make_int2(SG * ((td * Hi + th) * Wi + tw) * Ci + c, (int)((1u << (24 + td)) | (1u << (12 + th)) | (1u << tw)));
 }
 // offset (elements) of row `row`'s tap (0,0,0) and the taps that meet the tensor (none past the last row)
-template <bool FWD>
+template <bool FWD, bool WIN = false>
 __device__ __forceinline__ int2 pixel_entry(const IgemmArgs& p, int row) {
     const bool ok = row < p.M;
-    const int rr = ok ? row : 0, t = div_by(rr, p.dWr), wq = rr - t * p.Wr;
-    int n = div_by(t, p.dHr), dq = 0;
-    const int hq = t - n * p.Hr;
+    const int rr = ok ? row : 0;
+    int n, hq, wq, dq = 0;
+    if (WIN) {
+        const WinPixel x = win_pixel(p, rr);
+        n = x.n; hq = x.h; wq = x.w;
+    } else {
+        const int t = div_by(rr, p.dWr);
+        wq = rr - t * p.Wr;
+        n = div_by(t, p.dHr);
+        hq = t - n * p.Hr;
+    }
     if (p.Dr > 1) { const int ns = div_by(n, p.dDr); dq = n - ns * p.Dr; n = ns; }
     int h0, w0, d0;
     unsigned m;
@@ -87,9 +95,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* q, unsigned b
 // launches of too few row tiles to fill the card: the four wavefronts of a block share a tile, each with a quarter of the
 // reduction, and add their sums through LDS.
 template <typename E, int NT, int MODE, bool KSPLIT>
-__global__ void __launch_bounds__(256, MODE == MODE_FWD ? 3 : 2) gather_gemm(const IgemmArgs p, const int ksteps, const int tiles, const FastDiv dKp, const FastDiv dRows) {
+__global__ void __launch_bounds__(256, MODE == MODE_DGRAD ? 2 : 3) gather_gemm(const IgemmArgs p, const int ksteps, const int tiles, const FastDiv dKp, const FastDiv dRows) {
     typedef Gathered<E> G;
     constexpr int ES = sizeof(E), EPC = G::N, KS = 2 * EPC, PIECE = 32 * (NT * 32 + 4);
+    constexpr bool FWD = MODE != MODE_DGRAD;
     typedef Epilogue<E, 1, NT, MODE> Ep;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, rl = lane & 31, half = lane >> 5;
@@ -98,7 +107,7 @@ __global__ void __launch_bounds__(256, MODE == MODE_FWD ? 3 : 2) gather_gemm(con
     E* bank = reinterpret_cast<E*>(lds + Kp * 8);
     float* pieces = reinterpret_cast<float*>(lds + Kp * 8 + NT * 32 * pitch * ES);
     float* piece = pieces + wave * PIECE;
-    for (int k = tid; k < Kp; k += 256) tab[k] = tap_entry<MODE == MODE_FWD ? 1 : -1>(k, K, p.Ci, p.Kh, p.Kw, p.Hi, p.Wi);
+    for (int k = tid; k < Kp; k += 256) tab[k] = tap_entry<FWD ? 1 : -1>(k, K, p.Ci, p.Kh, p.Kw, p.Hi, p.Wi);
     const E* w = (const E*)p.B;
     // (rows past the last output channel are not filled: what they add up to is not stored.  With them LeNet's data gradient, six rows
     // of 32, took 15.5 us instead of 10.7, its forward pass 7.6 instead of 6.8.)
@@ -111,7 +120,7 @@ __global__ void __launch_bounds__(256, MODE == MODE_FWD ? 3 : 2) gather_gemm(con
             const int i = i0 + u * 256;
             int n, k, c = 0;
             int64_t o;
-            if (MODE == MODE_FWD) {          // w [N][K]
+            if (FWD) {                       // w [N][K]
                 n = div_by(i, dKp); k = i - n * Kp;
                 o = (int64_t)(n0 + n) * K + k;
             } else {                         // w [Ci][taps][N], K = (tap, channel of the gathered tensor)
@@ -124,7 +133,7 @@ __global__ void __launch_bounds__(256, MODE == MODE_FWD ? 3 : 2) gather_gemm(con
             const bool in = i < rows * Kp;
             if (!in) at[u] = -1;
             v[u] = in && n0 + n < p.N && k < K ? ld(w, o) : 0.f;
-            if (MODE != MODE_FWD && p.kscale && in && k < K) v[u] *= p.kscale[c];
+            if (!FWD && p.kscale && in && k < K) v[u] *= p.kscale[c];
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) if (at[u] >= 0) st(bank, at[u], v[u]);
@@ -144,7 +153,7 @@ __global__ void __launch_bounds__(256, MODE == MODE_FWD ? 3 : 2) gather_gemm(con
         }
     };
     auto first = [&](int t) __attribute__((always_inline)) {
-        px = pixel_entry<MODE == MODE_FWD>(p, t * 32 + rl);
+        px = pixel_entry<FWD, MODE == MODE_FWD_POOL>(p, t * 32 + rl);
 #pragma unroll
         for (int i = 0; i < 4; ++i) if (ks0 + i < ks1) gather(g[i], ks0 + i);
     };
@@ -370,6 +379,10 @@ bool gather_dgrad_ok(int dtype, const ConvGeom& g) {
 }
 bool gather_wgrad_ok(int dtype, const ConvGeom& g) { return gather_fits(dtype, g); }
 
+// whether the forward kernel can also store the 2x2 max-pooling of its output: its rows then go by pooling window, so that a window's
+// four are next to each other in a tile (two launches less for LeNet, 361 -> 346 us per step)
+bool gather_fwd_pools(const ConvGeom& g) { return !g.is3d() && !(g.Ho & 1) && !(g.Wo & 1); }
+
 static void fill_geom(IgemmArgs& a) {
     a.Di = std::max(a.Di, 1); a.Dr = std::max(a.Dr, 1); a.Kd = std::max(a.Kd, 1);
     a.dWr = fast_div(a.Wr); a.dHr = fast_div(a.Hr); a.dDr = fast_div(a.Dr); a.dCc = fast_div(a.Ci);
@@ -394,12 +407,14 @@ static hipError_t go(const IgemmArgs& a, hipStream_t st) {
 template <int MODE>
 static hipError_t run(int dtype, IgemmArgs& a, hipStream_t st) {
     fill_geom(a);
+    if (MODE == MODE_FWD_POOL) { a.dWr = fast_div(a.Wr / 2); a.dHr = fast_div(a.Hr / 2); }
     if (dtype == LPM_BF16) return a.N > 32 ? go<bf16_t, 2, MODE>(a, st) : go<bf16_t, 1, MODE>(a, st);
     return a.N > 32 ? go<float, 2, MODE>(a, st) : go<float, 1, MODE>(a, st);
 }
 
 hipError_t gather_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* scale, const float* bias,
-                           const void* add, int relu, void* y, hipStream_t st) {
+                           const void* add, int relu, void* y, hipStream_t st, void* pool_y) {
+    if (pool_y && (add || !gather_fwd_pools(g))) return hipErrorInvalidValue;
     IgemmArgs a{};
     a.A = x; a.B = w; a.C = y;
     a.scale = scale; a.bias = bias; a.add = add; a.relu = relu;
@@ -407,6 +422,10 @@ hipError_t gather_conv_fwd(int dtype, const ConvGeom& g, const void* x, const vo
     a.Hi = g.H; a.Wi = g.W; a.Di = g.D; a.Ci = g.Cin; a.Hr = g.Ho; a.Wr = g.Wo; a.Dr = g.Do;
     a.Kh = g.Kh; a.Kw = g.Kw; a.Kd = g.Kd; a.stride = g.stride; a.pad = g.pad; a.pad_d = g.pad_d;
     a.a_bytes = (unsigned)(g.rows_in() * g.Cin * (dtype == LPM_BF16 ? 2 : 4));
+    if (pool_y) {
+        a.fwd_pool = (uint16_t*)pool_y;
+        return run<MODE_FWD_POOL>(dtype, a, st);
+    }
     return run<MODE_FWD>(dtype, a, st);
 }
 

@@ -55,6 +55,18 @@ def test_pooling_forward_of_rows_of_32(lpm, m, cin, c, h):
     stage_backward_isolated(lpm, layers, [0, 3], m, m, 1, seed=27, dx_wanted=True, check_forward=True, grad_std=1.0)
 
 
+# ... and of the kernel that gathers element by element, whose tiles go by pooling window: few and many rows, channels in chunks and ragged,
+# more than one tile of them, a tile that ends inside an image
+@pytest.mark.parametrize("m,cin,c,k,p,h,w,dtype", [(8, 1, 6, 5, 0, 28, 28, 0), (3, 6, 16, 5, 0, 22, 16, 0), (12, 3, 20, 3, 1, 28, 30, 0), (3, 6, 40, 3, 1, 10, 14, 0),
+                                                   (5, 3, 16, 3, 1, 18, 22, 1), (12, 3, 70, 3, 1, 28, 30, 1), (3, 6, 12, 5, 2, 10, 14, 1)],
+                         ids=["lenet", "f32_chunks", "f32_many", "f32_two_tiles", "bf16_chunks", "bf16_many", "bf16_split"])
+def test_pooling_forward_of_gathered_layers(lpm, m, cin, c, k, p, h, w, dtype):
+    ho, wo = h + 2 * p - k + 1, w + 2 * p - k + 1
+    layers = chain(C(cin, c, k, k, h, w, p=p, scale=True), dict(P(c, ho, ho), h_in=ho, w_in=wo), C(c, 16, 1, 1, ho // 2, wo // 2))
+    print("m", m, "channels", cin, c, "dtype", dtype, flush=True)
+    stage_backward_isolated(lpm, layers, [0, 3], m, m, dtype, seed=29, dx_wanted=False, check_forward=True, grad_std=1.0)
+
+
 def bottlenecks(w, mid, h, m, shortcuts, first_scale=True):
     """Stem, then blocks 1x1 reduce - 1x1 expand + shortcut, then one more reduction that keeps the last block inside the stage.
     shortcuts: the tensor each block adds ('x': the block's input, 'in': the stage's)."""
