@@ -763,12 +763,7 @@ static hipError_t run_igemm(int dtype, int mode, const IgemmArgs& args, const Ig
             if (e != hipSuccess) return e;
         }
     }
-    if (hold) {
-        memcpy(hold->bytes, &c, sizeof(c));
-        hold->held = true;
-        return hipSuccess;
-    }
-    if (with && with->held) {
+    if (with && with->held) {      // (first: hold may be the same place)
         IgemmCall x;
         memcpy(&x, with->bytes, sizeof(x));
         if (pairs(x, c)) {
@@ -777,6 +772,11 @@ static hipError_t run_igemm(int dtype, int mode, const IgemmArgs& args, const Ig
         }
         const hipError_t e = run_held(*with, st);
         if (e != hipSuccess) return e;
+    }
+    if (hold) {
+        memcpy(hold->bytes, &c, sizeof(c));
+        hold->held = true;
+        return hipSuccess;
     }
     return go_call(c, st);
 }

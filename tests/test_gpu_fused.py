@@ -123,6 +123,13 @@ def added_source(c, h, m):
                  C(c, c, 3, 3, h, h, p=1, scale=True, src=1, add=2), C(c, c, 1, 1, h, h)), m
 
 
+def branches(c, h, m):
+    """Three layers in a row that read the same tensor, two of them added further on."""
+    return chain(C(c, c, 1, 1, h, h), C(c, c, 3, 3, h, h, p=1, scale=True, src=0), C(c, c, 1, 1, h, h, relu=False, scale=True, src=0),
+                 C(c, c, 1, 1, h, h, relu=False, scale=True, src=0), C(c, c, 3, 3, h, h, p=1, scale=True, src=1, add=2),
+                 C(c, c, 1, 1, h, h, scale=True, src=4, add=3), C(c, c, 1, 1, h, h)), m
+
+
 def long_projection(cin, w, mid, h, wd, m):
     """The same with filters of 13 x 1."""
     return chain(C(cin, cin, 1, 1, h, wd), C(cin, mid, 13, 1, h, wd, scale=True, src=0), C(cin, w, 13, 1, h, wd, relu=False, bias=False, scale=True, src=0),
@@ -169,6 +176,8 @@ NETS = {
     "pair_float_large": (branch(8, 32, 64, 64, 64, 12, s=2), "f32"),
     "pair_float_ragged": (branch(8, 20, 44, 36, 65, 12, s=2), "f32"),
     "pair_both_split": (branch(16, 1536, 64, 64, 4, 2, s=2), "bf16"),
+    "pair_three": (branches(64, 12, 2), "bf16"),
+    "pair_three_float": (branches(20, 12, 2), "f32"),
     "pair_shared": (branch(16, 64, 0, 64, 12, 2, shared=True), "bf16"),
     "pair_added": (added_source(64, 12, 2), "bf16"),
     "pair_added_float": (added_source(32, 12, 2), "f32"),
