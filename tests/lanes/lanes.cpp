@@ -28,7 +28,7 @@ static int late = 0;                       // loads to LDS land at their wait; w
 static bool host_only = false;             // launches are looked at, not run
 static std::atomic<long> complaints{0};
 static std::mutex mu;
-static std::map<uintptr_t, size_t> ranges;      // what callers own: start -> bytes (not changed while kernels run)
+static std::map<uintptr_t, size_t> ranges;      // device memory: start -> bytes (not changed while kernels run)
 
 static std::string kernel_name(const void* k) {
     Dl_info d;
@@ -50,13 +50,12 @@ static void complain(const char* fmt, ...) {
     fprintf(stderr, " [block %u,%u,%u thread %u of %s]\n", bid.x, bid.y, bid.z, tid.x, kernel_name(kernel).c_str());
 }
 
-static void check_owned(const void* p, size_t n, const char* what) {
+static bool owned(const void* p, size_t n) {
     auto it = ranges.upper_bound((uintptr_t)p);
-    if (it != ranges.begin()) {
-        --it;
-        if ((uintptr_t)p + n <= it->first + it->second) return;
-    }
-    complain("%s of %zu bytes outside every buffer", what, n);
+    return it != ranges.begin() && (uintptr_t)p + n <= std::prev(it)->first + std::prev(it)->second;
+}
+static void check_owned(const void* p, size_t n, const char* what) {
+    if (!owned(p, n)) complain("%s of %zu bytes outside every buffer", what, n);
 }
 
 // The bounds check of a raw buffer access: out of range where off >= records - soff.  Whether that difference wraps where soff
@@ -277,27 +276,19 @@ void run(dim3 grid, dim3 block, size_t lds, const void* k, const std::function<v
 }  // namespace lanes
 
 extern "C" {
-// n bytes between pages without access, their end (on a multiple of 256 bytes) against the upper one
+// n bytes of device memory: between pages without access, their end (on a multiple of 256 bytes) against the upper one.  It is never
+// given back, so no address means two things in one process.
 void* lanes_alloc(size_t n) {
     const size_t pages = (n + 4095) / 4096 + (n == 0), guard = 4 * 4096;
     unsigned char* m = (unsigned char*)mmap(nullptr, pages * 4096 + 2 * guard, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS, -1, 0);
     mprotect(m, guard, PROT_NONE);
     mprotect(m + guard + pages * 4096, guard, PROT_NONE);
-    return m + guard + pages * 4096 - ((n + 255) & ~(size_t)255);
+    unsigned char* p = m + guard + pages * 4096 - ((n + 255) & ~(size_t)255);
+    if (n) lanes::ranges[(uintptr_t)p] = n;
+    return p;
 }
-// memory that a call hands to the library
-void lanes_own(void* p, size_t n) {
-    using lanes::ranges;
-    if (!p || !n) return;
-    auto it = ranges.lower_bound((uintptr_t)p);
-    if (it != ranges.begin()) {
-        auto q = std::prev(it);
-        if (q->first + q->second >= (uintptr_t)p + n) return;          // a view of a larger buffer
-        if (q->first + q->second > (uintptr_t)p) ranges.erase(q);
-    }
-    while (it != ranges.end() && it->first < (uintptr_t)p + n) it = ranges.erase(it);
-    ranges[(uintptr_t)p] = n;
-}
+// whether n bytes from p are device memory, in one allocation
+int lanes_owned(const void* p, size_t n) { return lanes::owned(p, n); }
 void lanes_late(int v) { lanes::late = v; }
 void lanes_host_only(int v) { lanes::host_only = v != 0; }
 void lanes_set_device(int d) { lanes::set_device(d); }

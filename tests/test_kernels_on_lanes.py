@@ -39,6 +39,31 @@ def test_gpu_tests_on_lanes(lanes, late, name, select):
     assert " passed" in r.stdout and " failed" not in r.stdout
 
 
+OPERANDS = """
+import ctypes, lanes_plugin, torch
+from paper_2207_11019_amd import binding
+E = lanes_plugin._E
+E.lanes_owned.argtypes = [ctypes.c_void_p, ctypes.c_size_t]
+guarded = lambda t: E.lanes_owned(t.data_ptr(), t.numel() * t.element_size()) and not E.lanes_owned(t.data_ptr(), t.numel() * t.element_size() + 1)
+a = torch.zeros(640).cuda()
+for t in (a, a.to(torch.bfloat16), a.clone(), a + 1, a.view(20, 32).t().contiguous(), torch.empty(64, dtype=torch.uint8, device="cuda")):
+    assert binding._ptr(t) == t.data_ptr() and guarded(t)
+assert binding._ptr(a[64:]) == a.data_ptr() + 256
+try:
+    binding._ptr(torch.zeros(640))
+except AssertionError:
+    print("refused")
+"""
+
+
+def test_operands_lie_between_pages_without_access(lanes):
+    """Whatever torch makes of device memory is device memory, each tensor between pages of its own; host memory is refused.  (Operands in
+    the heap had no such pages, and what was said of one held for the next at its address: a range too short, or one too long.)"""
+    env = dict(os.environ, LPM_LANES=lanes, PYTHONPATH=os.pathsep.join([LANES, os.path.dirname(TESTS), os.environ.get("PYTHONPATH", "")]))
+    r = subprocess.run([sys.executable, "-c", OPERANDS], env=env, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.strip().endswith("refused"), r.stdout + r.stderr
+
+
 @pytest.mark.parametrize("op,h,taken", [(0, 16382, True), (0, 16383, False), (1, 16381, True), (1, 16382, False)],
                          ids=["forward-in", "forward-out", "dgrad-in", "dgrad-out"])
 def test_buffers_near_4_gib(lanes, op, h, taken):
