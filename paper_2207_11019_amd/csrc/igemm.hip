@@ -774,6 +774,7 @@ static hipError_t run_igemm(int dtype, int mode, const IgemmArgs& args, const Ig
         if (e != hipSuccess) return e;
     }
     if (hold) {
+        if (hold->held) return hipErrorInvalidValue;      // (what waits there would be lost)
         memcpy(hold->bytes, &c, sizeof(c));
         hold->held = true;
         return hipSuccess;

@@ -106,7 +106,8 @@ hipError_t launch_zero_counts(void* const* heads, int n, hipStream_t st);
 
 // Two contractions of which neither reads the other's result can share a launch.  A launcher that is given `hold` keeps its call there
 // instead of launching it, if its kernel is one that can share (held is then set); the launcher of the next call gets it as
-// `with` and launches both, together or one after the other.  Whoever holds a call sees to it that it runs (run_held).
+// `with` and launches both, together or one after the other.  Whoever holds a call sees to it that it runs (run_held) before anything is
+// launched that is not given it, and holds no second one over it: that is an error.
 struct HeldCall { alignas(16) unsigned char bytes[768]; bool held = false; };
 hipError_t run_held(HeldCall& h, hipStream_t st);
 

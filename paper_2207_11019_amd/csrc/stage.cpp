@@ -492,6 +492,7 @@ int32_t lpm_stage_forward_on(lpm_stage* s, const void* x, void* y, const int32_t
         const lpm_layer& l = lr.d;
         const void* in = tptr(s, l.src, x, y, stash);
         void* outp = const_cast<void*>(tptr(s, i, x, y, stash));
+        if (!has_weights(l)) LPM_HIP(run_held(held, st));      // (a contraction's launcher sees to it)
         StopEvent stop(i == s->last - 1 ? done : nullptr, st);
         switch (l.kind) {
             case LPM_CONV:
@@ -503,7 +504,7 @@ int32_t lpm_stage_forward_on(lpm_stage* s, const void* x, void* y, const int32_t
                 const void* add = l.add_src != LPM_NONE ? tptr(s, l.add_src, x, y, stash) : nullptr;
                 void* pooled = lr.pool_fwd >= 0 ? const_cast<void*>(tptr(s, lr.pool_fwd, x, y, stash)) : nullptr;
                 LPM_HIP(launch_conv_fwd(s->dtype, lr.g, in, w, sc, bi, add, (l.flags & LPM_RELU) != 0, outp, fwd_ws, st, pooled, true,
-                                        lr.hold_fwd ? &held : nullptr, &held));
+                                        lr.hold_fwd && i + 1 < s->last ? &held : nullptr, &held));
                 break;
             }
             case LPM_MAXPOOL2:
@@ -696,6 +697,11 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
         const void* g = G[gi(i)];
         if (!have[gi(i)]) return fail(LPM_ESHAPE, "internal: tensor %d has no consumer", i);
         const bool want_src = (l.src >= first) || (dx != nullptr);
+        // a data gradient that waits goes with this layer's, or before anything else is launched
+        if (held.held && !(has_weights(l) && want_src && lr.unpool_of < 0)) {
+            LPM_HIP(run_held(held, st));
+            at_point = nullptr;
+        }
         switch (l.kind) {
             case LPM_CONV:
             case LPM_FC: {
@@ -829,7 +835,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                         if (do_data && unpool.dst) LPM_HIP(launch_conv_dgrad(s->dtype, lr.g, dz, w, wt, nullptr, 0, nullptr, nullptr, counts, st, &unpool,
                                                                              nullptr, lr.dz_unscaled ? sc : nullptr, true));
                     } else if (do_data) {
-                        const bool hold = lr.hold_bwd && (s->Ly(i - 1).d.src >= first || dx);
+                        const bool hold = lr.hold_bwd && i > first && (s->Ly(i - 1).d.src >= first || dx);
                         LPM_HIP(launch_conv_dgrad(s->dtype, lr.g, dz, w, wt, gsrc, gsrc_acc, gmask, gmscale, counts, st, nullptr,
                                                   use_side ? &side : nullptr, lr.dz_unscaled ? sc : nullptr, true, hold ? &held : nullptr, &held));
                     }

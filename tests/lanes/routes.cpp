@@ -1,5 +1,7 @@
-// Which geometries the implicit-GEMM kernels take (op 0: forward, 1: data gradient), for tests of sizes no test can hold.
+// Looks into the library: which geometries the implicit-GEMM kernels take (op 0: forward, 1: data gradient), for tests of sizes no test
+// can hold, and calls that wait for the next one's launch where no network makes them wait.
 #include "lpm_internal.h"
+#include "stage.h"
 
 namespace lpm {
 bool mfma_fwd_ok(int dtype, const ConvGeom& g);
@@ -10,4 +12,19 @@ extern "C" int lanes_takes(int op, int dtype, const lpm_conv_geom* q) {
     lpm::ConvGeom g{q->m, q->h, q->w, q->cin, (q->h + 2 * q->pad - q->kh) / q->stride + 1, (q->w + 2 * q->pad - q->kw) / q->stride + 1,
                     q->cout, q->kh, q->kw, q->stride, q->pad};
     return op == 0 ? lpm::mfma_fwd_ok(dtype, g) : lpm::mfma_dgrad_ok(dtype, g);
+}
+
+// layer i's contraction waits (forward, backward) although what follows need not be one that it can share a launch with
+extern "C" void lanes_hold(lpm_stage* s, int i, int fwd, int bwd) {
+    s->Ly(i).hold_fwd = fwd != 0;
+    s->Ly(i).hold_bwd = bwd != 0;
+}
+
+// two calls held in one place: what the second returns
+extern "C" int lanes_hold_twice() {
+    const lpm::ConvGeom g{2, 8, 8, 64, 8, 8, 64, 3, 3, 1, 1};
+    lpm::HeldCall h;
+    void* p = (void*)4096;
+    if (lpm::launch_conv_fwd(LPM_BF16, g, p, p, nullptr, nullptr, nullptr, 0, p, p, nullptr, nullptr, true, &h) != hipSuccess || !h.held) return -1;
+    return lpm::launch_conv_fwd(LPM_BF16, g, p, p, nullptr, nullptr, nullptr, 0, p, p, nullptr, nullptr, true, &h);
 }

@@ -66,6 +66,46 @@ def test_operands_lie_between_pages_without_access(lanes):
     assert r.returncode == 0 and r.stdout.strip().endswith("refused"), r.stdout + r.stderr
 
 
+HELD = """
+import ctypes, lanes_plugin, torch
+import paper_2207_11019_amd as lpm
+from workloads import configs
+E = lanes_plugin._E
+E.lanes_hold.argtypes = [ctypes.c_void_p] + [ctypes.c_int] * 3
+assert E.lanes_hold_twice() != 0, "a second call took the place of one that waits"
+b = configs._Builder(16, 9, 9)
+b.conv(16, 3, pad=1); b.gap(); b.conv(24, 1); b.conv(16, 1)
+layers = b.finish()
+def step(hold):
+    torch.manual_seed(3)
+    st = lpm.Stage(layers, 0, len(layers), 2, lpm.BF16)
+    for i, fwd, bwd in hold:
+        E.lanes_hold(st.h, i, fwd, bwd)
+    buf = lambda n: torch.zeros(max(n, 256), dtype=torch.uint8, device="cuda")
+    rnd = lambda n: (torch.randn(n // 2) * 0.1).to(torch.bfloat16).cuda()
+    params, lowp, grads, stash, fws, bws = [buf(n) for n in (st.param_bytes, st.lowp_bytes, st.grad_bytes, st.stash_bytes, st.fwd_ws_bytes, st.bwd_ws_bytes)]
+    params.view(torch.float32).copy_(torch.randn(params.numel() // 4) * 0.1)
+    st.sync_lowp(params, lowp)
+    x, dy, y, dx = rnd(st.in_bytes), rnd(st.out_bytes), buf(st.out_bytes), buf(st.in_bytes)
+    st.forward(x, y, None, None, params, lowp, stash, fws, 1.0)
+    st.backward(x, y, dy, dx, params, lowp, stash, grads, False, bws)
+    assert y.any() and dx.any() and grads.any()
+    return y, dx, grads, stash
+want = step([])
+for hold in ([(0, 1, 0)], [(3, 1, 0)], [(2, 0, 1)], [(0, 0, 1)], [(0, 1, 1), (2, 0, 1), (3, 1, 0)]):
+    assert all(torch.equal(a, b) for a, b in zip(want, step(hold))), hold
+print("all ran")
+"""
+
+
+def test_no_held_call_is_lost(lanes):
+    """A contraction that waits for the next layer's launch runs before anything else that is launched, and at the end of its pass:
+    in front of an average pooling, as the last layer of a stage, and as the first one of it on the way back."""
+    env = dict(os.environ, LPM_LANES=lanes, PYTHONPATH=os.pathsep.join([LANES, os.path.dirname(TESTS), os.environ.get("PYTHONPATH", "")]))
+    r = subprocess.run([sys.executable, "-c", HELD], env=env, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip().endswith("all ran"), r.stdout + r.stderr
+
+
 @pytest.mark.parametrize("op,h,taken", [(0, 16382, True), (0, 16383, False), (1, 16381, True), (1, 16382, False)],
                          ids=["forward-in", "forward-out", "dgrad-in", "dgrad-out"])
 def test_buffers_near_4_gib(lanes, op, h, taken):
