@@ -344,7 +344,7 @@ int32_t pick_locked_stream(lpm_schedule* s, hipStream_t sf) {
 
 // OVERLAPPED, three workers: 0 enqueues the forward chains on sf, 1 the data phases of the backward chains
 // on sb, 2 the weight phases and the updates on the weight streams (ov_w, and ov_w0 for stage 0; see pick_weight_streams).
-// ev_f[j*Z+Z-1]: forward chain j done; ev_b[j*Z+z]: data phase of B_{z,j} done; ev_w[j*Z]: micro-batch j done.
+// ev_f[j*Z+Z-1]: forward chain j done; ev_b[j*Z+z]: data phase of B_{z,j} done; ev_w[j*Z]: micro-batch j done (LOCKED: see closes_here).
 // LOCKED (with a synchronous update) is the same with a window of one and the backward chains on the forward stream: the
 // operations follow one another, a backward operation's weight gradients run beside its data phase, and a thread of its own
 // enqueues them -- a wait for an event of another stream costs the host about 10 us, three launches' worth (width-48 ResNet
@@ -358,7 +358,8 @@ int32_t overlapped_role(lpm_schedule* s, const RunArgs& a, int32_t role, uint64_
     int32_t rc;
     // Stage 0's weight phase closes every micro-batch, and the next forward chain but one waits for it: with a
     // hardware queue to itself it follows stage 0's data phase from the start instead of queueing behind the other
-    // stages' weight phases.  The micro-batch is done at ev_w[j*Z] and, the end of those on the common stream, ev_w[j*Z+1].
+    // stages' weight phases.  The micro-batch is done at ev_w[j*Z] and, the end of those on the common stream, ev_w[j*Z+1]
+    // (but for what closes_here leaves to the forward stream itself).
     const bool own0 = !async && Z > 1 && w2 != w1;
     auto await_microbatch = [&](int32_t j, hipStream_t st) -> int32_t {
         const size_t i = (size_t)j * Z;
@@ -370,8 +371,10 @@ int32_t overlapped_role(lpm_schedule* s, const RunArgs& a, int32_t role, uint64_
     // LOCKED: the last group of stage 0's weight gradients, whose dz the data phase makes last, follows it on its own stream: on the
     // weight stream it started a hand-over later, and the next forward chain another one after it (us per step: float ResNet-18
     // 2547 -> 2503, width-48 ResNet 2208 -> 2144, VGG-16/CIFAR 2709 -> 2614).  OVERLAPPED, the forward stream is busy with another
-    // forward chain meanwhile: VGG-16/CIFAR 1817 -> 1875.
-    auto closes_here = [&](int32_t j) { return locked && !a.dx_wanted && j < M - 1; };
+    // forward chain meanwhile: VGG-16/CIFAR 1817 -> 1875.  ev_w[j*Z] then stands behind the other groups only: whoever waits for it is on the
+    // forward stream, behind the last group, or (the weight phase of j + 1) waits for a data phase that is.  So the backward
+    // chain has to be on that stream as well.
+    auto closes_here = [&](int32_t j) { return locked && a.sb == a.sf && !a.dx_wanted && j < M - 1; };
     if (role == 0) {
         for (int32_t j = 0; j < M; ++j) {
             if (j > 0 && closes_here(j - 1)) {
