@@ -115,7 +115,8 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     if (KS) {
         for (int c = tid; c < p.Ci; c += T) ksc[c] = p.kscale[c];      // (the first K tile's barrier makes it visible)
     }
-    // ---- loader state.  Lane l of a load fills chunk position l % 8 of row l / 8: it fetches chunk (l % 8) ^ (l / 8)
+    // ---- loader state.  Lane l of a load fills chunk position l % 8 of row r = 8 * wave + l / 8 (a load step is a multiple of 16
+    // rows): it fetches chunk (l % 8) ^ (r / 2 % 8)
     const int lrow = lane >> 3, kcol = (lane & 7) ^ ((wave & 1) * 4 + (lrow >> 1));
     unsigned a_base[A_LD], a_msk[A_LD], b_off[B_LD];
 #pragma unroll
@@ -610,7 +611,8 @@ static IgemmPlan plan_dgrad(int dtype, const ConvGeom& g) {
     const int es = dtype == LPM_BF16 ? 2 : 4, s = g.stride;
     const int64_t taps = (int64_t)((g.Kd + s - 1) / s) * ((g.Kh + s - 1) / s) * ((g.Kw + s - 1) / s);
     int64_t rows = g.rows_in();
-    if (s > 1) rows += 128 * (g.D > 1 ? s * s * s : s * s);          // (every class may end in a ragged tile)
+    if (s > 1) rows += 128 * (g.D > 1 ? s * s * s : s * s);          // (every class ends in a ragged tile: up to 63 rows of the 64-row tiles whose
+                                                                      // scratch goes by this count; for the choice of a larger tile, an estimate)
     return plan_igemm(es, rows, g.Cin, k_tiles(taps, g.Cout, es));
 }
 bool mfma_dgrad_kscale_ok(const ConvGeom& g) { return g.Cout <= MAX_KSCALE; }
