@@ -546,11 +546,14 @@ static IgemmPlan plan_igemm(int es, int64_t M, int N, int kt) {
         // adds up, the larger tile wins from 180 on (per step, line at 384 / 250 / 180 / 120 / 90, in us: ResNet-18/CIFAR 3361 / 3312 /
         // 3308 / 3366 / 3371, VGG-16/224 6828 / 6833 / 6772 / 6778 / 6760, R50 conv4_x at 64 1746 / 1752 / 1749 / 1750 / 1870).
         const bool wide = N % 128 == 0 || N % 128 > 64;
-        const int64_t n128 = tiles_of(TILE_128, M, N);
-        // 128x128 of two stages (of four wavefronts before) / 256x128, alone: 25088 x 256, K 2304 35.4 / 32.9, K 1024 21.6 / 19.6;
-        // R50 conv4_x at 512, per step: four wavefronts 6925, eight 6770, 256x128 from 384 tiles on 6807, from 180 and 12 K tiles on
-        // 6660, from 180 and 4 on 6636.  With one column of tiles both read the gathered rows once: VGG-16/224 6590 there, 6603 with 256x128.
-        if (wide && N > 128 && kt >= 4 && tiles_of(TILE_256, M, N) >= 180) pl.tile = TILE_256;
+        const int64_t n128 = tiles_of(TILE_128, M, N), t256 = tiles_of(TILE_256, M, N);
+        // 128x128 of two stages / 256x128, alone: 25088 x 256, K 2304 35.4 / 32.9.  Where one block per CU covers its own latencies: from a
+        // dozen K tiles on -- with fewer a block is loads and stores, one after the other, and two smaller ones take turns (R50 conv4_x,
+        // two micro-batches of 36 / 48 / 64 / 96 / 128 samples, with four K tiles 1448 / 1848 / 2079 / 2977 / 3512, with twelve 1413 / 1774 /
+        // 2042 / 2903 / 3488) -- and where the tiles fill 70 % of their rounds of CUs (14x14, 256 -> 512, 3x3, the three contractions:
+        // 264 to 312 tiles 192-205 us, 128x128 instead 189-203; 80 % would leave out 25088 x 256, 107 us against 114).  With one column of
+        // tiles both read the gathered rows once: VGG-16/224 6590 there, 6603 with 256x128.
+        if (wide && N > 128 && kt >= 12 && 10 * t256 >= 7 * 256 * ((t256 + 255) / 256)) pl.tile = TILE_256;
         else if (wide && n128 >= 384) pl.tile = TILE_128;
         else if (wide && n128 >= 180) pl.tile = TILE_128_DEEP;
         else if (tiles_of(TILE_128x64, M, N) >= 180) pl.tile = TILE_128x64;

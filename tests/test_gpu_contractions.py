@@ -29,10 +29,15 @@ BOTH = [
 BF16 = [
     G(1, 152, 152, 8, 128, 1, 1, 0),      # 181 tiles of 128x128: three stages
     G(3, 128, 128, 8, 128, 1, 1, 0),      # 384 of them: two
-    G(2, 107, 109, 32, 200, 3, 1, 1),     # 184 tiles of 256x128, ragged M and N
+    G(2, 107, 109, 32, 200, 3, 1, 1),     # 366 tiles of 128x128, ragged M and N
     G(2, 107, 109, 200, 32, 3, 1, 1),     # ... of the data gradient
-    G(2, 107, 109, 256, 256, 1, 1, 0),    # ... of both, whole K tiles, the fewest
-    G(2, 151, 153, 256, 64, 3, 2, 1),     # ... of a strided data gradient
+    G(2, 107, 109, 256, 256, 1, 1, 0),    # ... of both, whole K tiles
+    G(2, 151, 153, 256, 64, 3, 2, 1),     # 730 of a strided data gradient
+    G(2, 107, 109, 88, 200, 3, 1, 1),     # the same with the dozen K tiles that make them 184 tiles of 256x128: in chunks across taps
+    G(2, 107, 109, 200, 88, 3, 1, 1),
+    G(2, 107, 109, 768, 256, 1, 1, 0),    # ... whole K tiles, the fewest
+    G(2, 107, 109, 256, 768, 1, 1, 0),
+    G(2, 151, 153, 256, 192, 3, 2, 1),    # ... strided
     G(3, 128, 128, 8, 64, 3, 1, 1),       # 384 tiles of 128x64
     G(3, 127, 128, 64, 72, 1, 1, 0),      # N over half a tile, ragged M
     G(1, 128, 128, 128, 8, 1, 1, 0),      # the same sizes for the data gradient

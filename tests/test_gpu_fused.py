@@ -47,8 +47,8 @@ def test_pooling_backward_before_a_convolution(lpm, c1, c2, k, p, dtype):
 
 
 # forward pooling of images 32 wide, whose windows span two pieces of a tile: on every tile, split, in ragged channels, one row of windows
-@pytest.mark.parametrize("m,cin,c,h", [(2, 16, 24, 32), (1, 256, 64, 32), (3, 64, 72, 2), (24, 16, 64, 32), (24, 16, 128, 32), (24, 32, 256, 32)],
-                         ids=["ragged", "split", "one_row", "tile128x64", "tile128", "large"])
+@pytest.mark.parametrize("m,cin,c,h", [(2, 16, 24, 32), (1, 256, 64, 32), (3, 64, 72, 2), (24, 16, 64, 32), (24, 16, 128, 32), (24, 32, 256, 32), (24, 96, 256, 32)],
+                         ids=["ragged", "split", "one_row", "tile128x64", "tile128", "large", "tile256"])
 def test_pooling_forward_of_rows_of_32(lpm, m, cin, c, h):
     layers = chain(C(cin, c, 3, 3, h, 32, p=1, scale=True), P(c, h, 32), C(c, 16, 1, 1, h // 2, 16))
     print("m", m, "channels", cin, c, "height", h, flush=True)
@@ -151,6 +151,8 @@ NETS = {
     "tile128_8w": (bottlenecks(128, 16, 108, 2, ["in", "x", "in"]), "bf16"),
     "tile128_8w_ragged": (bottlenecks(120, 64, 109, 2, ["in", "in"]), "bf16"),
     "tile128": (bottlenecks(256, 16, 111, 2, ["in", "in"]), "bf16"),
+    "tile256": ((chain(C(200, 200, 1, 1, 107, 109, scale=True), C(200, 88, 3, 3, 107, 109, p=1), C(88, 200, 1, 1, 107, 109, scale=True, add=0),
+                       C(200, 88, 3, 3, 107, 109, p=1)), 2), "bf16"),
     "projected128": (projected(16, 128, 16, 108, 2), "bf16"),
     # the same in float, where a block's scale enters through the weights of its data gradient: channels in whole K tiles, in chunks of
     # 16 bytes, and gathered one by one

@@ -25,14 +25,14 @@ RUNS = [
     (1, "test_gpu_contractions.py", "bf16_m1 or f32_m1 or f32_m2 or 3_4x4 or m2_4x4"),
     (1, "test_gpu_conv.py", "not m4_64x64 and not 57x59 and not 60x60 and not 32x32x64 and not d6k3_16 and not 15x15x512"),
     (0, "test_gpu_update.py", ""),
-    (0, "test_gpu_fused.py", "not ranges and not 128 and not large"),
-    (1, "test_gpu_contractions.py", "m2_107 or m2_151"),          # 256x128 tiles
-    (1, "test_gpu_fused.py", "128 or large"),                     # ... the other large ones, groups and pairs of them, pooling over two pieces
+    (0, "test_gpu_fused.py", "not ranges and not 128 and not 256 and not large"),
+    (1, "test_gpu_contractions.py", "88_200 or 256_768 or 256_192"),          # 256x128 tiles
+    (1, "test_gpu_fused.py", "256 or large or (rows and tile128)"),           # ... large ones, groups and pairs of them, pooling over two pieces
     (1, "test_gpu_parity.py", "small_networks and bf16 and not graph and not pipelined"),
 ]
 
 
-@pytest.mark.parametrize("late,name,select", RUNS, ids=["%s-%s%s" % (r[1][9:-3], "late" if r[0] else "early", "-large" if "not" not in r[2] and ("128" in r[2] or "m2_107" in r[2]) else "") for r in RUNS])
+@pytest.mark.parametrize("late,name,select", RUNS, ids=["%s-%s%s" % (r[1][9:-3], "late" if r[0] else "early", "-large" if "not" not in r[2] and "256" in r[2] else "") for r in RUNS])
 def test_gpu_tests_on_lanes(lanes, late, name, select):
     env = dict(os.environ, LPM_LANES=lanes, LPM_LANES_LATE=str(late), PYTHONPATH=os.pathsep.join([LANES, os.environ.get("PYTHONPATH", "")]))
     cmd = [sys.executable, "-m", "pytest", "-p", "lanes_plugin", "-p", "no:cacheprovider", "-q", "-m", "gpu", os.path.join(TESTS, name)]
