@@ -295,10 +295,8 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     // and the tiles behind it are on their way there -- with one wavefront per SIMD (a launch of about one block per CU) nothing else
     // hides the LDS latency.  Two sets of them, or (TWO false) the next tile's over those of a step just multiplied: with two
     // wavefronts per SIMD, or float's longer products, the reads are covered all the same and the registers go to other streams'
-    // wavefronts (float ResNet-18 2640 -> 2566 us per step, VGG-16/224 6640 -> 6575; the 64x64 tiles lose: R50 conv4_x at 64 1650 -> 1715).
-    // A float data gradient reads its weights in four pieces of 4 bytes, which takes longer: two sets with three stages, where several
-    // blocks share a CU's LDS (a stage 480 -> 256 channels at 4 x 37^2 566 -> 545, ResNet-18 the same), one with four (two: ResNet-18 + 0.4 %).
-    constexpr bool TWO = ES == 4 ? BT != BT_NONE && NST == 3 : !(BM == 128 && BN == 128 && WGN == 4);
+    // wavefronts (float ResNet-18 2827 -> 2773 us per step, VGG-16/224 6640 -> 6575; the 64x64 tiles lose: R50 conv4_x at 64 1650 -> 1715).
+    constexpr bool TWO = ES == 2 && !(BM == 128 && BN == 128 && WGN == 4);
     struct Frag { uint4 a[4][MI], b[4][NI]; };
     auto read = [&](Frag& f, int st, int ks) __attribute__((always_inline)) {
         const unsigned char* sp = lds + st * STAGE;
@@ -720,11 +718,10 @@ static bool uni_of(const IgemmCall& c) { return (c.a.Ci * (c.dtype == LPM_BF16 ?
 // contraction, and where both leave CUs idle they run side by side (us per step, apart / together: float ResNet-18 2746 / 2588, width-48
 // ResNet 2408 / 2272, 3-D ResNet 1673 / 1600, ResNet-18/CIFAR 2808 / 2750, 16 images forward 163 / 152).  Larger tiles are for launches
 // that fill the card by themselves; a 128x64 plan of a few K tiles -- a projection's data gradient, mostly output -- runs
-// on 64x64 here, whatever their number (volumetric at 3 and 4 volumes, 1536 and 2048 tiles: 1944 and 2236 left alone, 1915 and 2200 together; ResNets
-// of width 32 to 64 at 13 to 128 samples, up to 4096 tiles, within 0.5 %).
+// on 64x64 here (left alone: width-48 ResNet 2308, 3-D 1619, ResNet-18/CIFAR 2735).
 static bool pairs(const IgemmCall& x, const IgemmCall& y) {
     if (x.dtype != y.dtype || uni_of(x) != uni_of(y) || (x.pl.splits > 1 && y.pl.splits > 1)) return false;      // (they share the scratch area)
-    auto small = [](const IgemmCall& c) { return c.pl.tile == TILE_64 || (c.pl.tile == TILE_128x64 && c.pl.kt_total <= 4); };
+    auto small = [](const IgemmCall& c) { return c.pl.tile == TILE_64 || (c.pl.tile == TILE_128x64 && c.pl.kt_total <= 4 && tiles_of(TILE_64, c.a.M, c.a.N) <= 1088); };
     if (!small(x) || !small(y)) return false;
     if (x.mode == MODE_FWD) return y.mode == MODE_FWD;
     if (x.dtype == LPM_F32 && !(x.a.kscale && y.a.kscale)) return false;
