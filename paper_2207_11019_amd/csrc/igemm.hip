@@ -295,8 +295,10 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     // and the tiles behind it are on their way there -- with one wavefront per SIMD (a launch of about one block per CU) nothing else
     // hides the LDS latency.  Two sets of them, or (TWO false) the next tile's over those of a step just multiplied: with two
     // wavefronts per SIMD, or float's longer products, the reads are covered all the same and the registers go to other streams'
-    // wavefronts (float ResNet-18 2827 -> 2773 us per step, VGG-16/224 6640 -> 6575; the 64x64 tiles lose: R50 conv4_x at 64 1650 -> 1715).
-    constexpr bool TWO = ES == 2 && !(BM == 128 && BN == 128 && WGN == 4);
+    // wavefronts (float ResNet-18 2640 -> 2566 us per step, VGG-16/224 6640 -> 6575; the 64x64 tiles lose: R50 conv4_x at 64 1650 -> 1715).
+    // A float data gradient reads its weights in four pieces of 4 bytes, which takes longer: two sets with three stages, where several
+    // blocks share a CU's LDS (a stage 480 -> 256 channels at 4 x 37^2 566 -> 545, ResNet-18 the same), one with four (two: ResNet-18 + 0.4 %).
+    constexpr bool TWO = ES == 4 ? BT != BT_NONE && NST == 3 : !(BM == 128 && BN == 128 && WGN == 4);
     struct Frag { uint4 a[4][MI], b[4][NI]; };
     auto read = [&](Frag& f, int st, int ks) __attribute__((always_inline)) {
         const unsigned char* sp = lds + st * STAGE;
