@@ -108,13 +108,11 @@ bool wgrad_fuses_bias(int dtype, const ConvGeom& g) { return wgrad_mm_ok(dtype, 
 bool dgrad_uses_wt(int dtype, const ConvGeom& g) { return dtype == LPM_BF16 && !fc_skinny_ok(g) && mfma_dgrad_ok(dtype, g); }
 
 // the stride-1 MFMA data gradient can route its result through a following (in forward order: preceding) max-pooling, whole
-// chunks of eight channels at a time.  Of small gradients only, which are bound by their launches: the line was drawn with an
-// epilogue of 2-byte stores, for which the 224x224 VGG layers were better off with a pooling kernel of their own.  With the present
-// epilogue the two large layers above the line make no such difference any more (VGG-16/224, us per step: 6658 with the line, 6611
-// without it).
+// chunks of eight channels at a time.  At every size: with a pooling kernel of its own for gradients of more than 2^20 elements VGG-16/224 took
+// 3373 / 3718 / 5522 us per step of four micro-batches of 3 / 4 / 8 images, without it 3346 / 3681 / 5483; VGG-16/CIFAR at 128 images
+// 2235 / 2217.
 bool dgrad_can_unpool(int dtype, const ConvGeom& g) {
-    return dtype == LPM_BF16 && !g.is3d() && !fc_skinny_ok(g) && mfma_dgrad_ok(dtype, g) && g.stride == 1 && g.Cin % 8 == 0 &&
-           (int64_t)g.rows_in() * g.Cin <= ((int64_t)1 << 20);
+    return dtype == LPM_BF16 && !g.is3d() && !fc_skinny_ok(g) && mfma_dgrad_ok(dtype, g) && g.stride == 1 && g.Cin % 8 == 0;
 }
 
 // the MFMA data gradient can take over the epilogue backward of a layer with a shortcut (DgradSide)

@@ -46,6 +46,14 @@ def test_pooling_backward_before_a_convolution(lpm, c1, c2, k, p, dtype):
     stage_backward_isolated(lpm, layers, [0, 3], 3, 3, dtype, seed=21, dx_wanted=True, check_forward=True, grad_std=1.0)
 
 
+# ... on the larger tiles of the data gradient: 128x64, 128x128, 256x128 (pooled images and channels of the middle tensor)
+@pytest.mark.parametrize("m,c,h", [(45, 40, 22), (23, 128, 32), (90, 200, 16)], ids=["tile128x64", "tile128", "tile256"])
+def test_pooling_backward_on_larger_tiles(lpm, m, c, h):
+    layers = chain(C(8, c, 1, 1, 2 * h, 2 * h), P(c, 2 * h, 2 * h), C(c, 768, 1, 1, h, h, scale=True))
+    print("m", m, "channels", c, "height", h, flush=True)
+    stage_backward_isolated(lpm, layers, [0, 3], m, m, 1, seed=31, dx_wanted=True, check_forward=True, grad_std=1.0)
+
+
 # forward pooling of images 32 wide, whose windows span two pieces of a tile: on every tile, split, in ragged channels, one row of windows
 @pytest.mark.parametrize("m,cin,c,h", [(2, 16, 24, 32), (1, 256, 64, 32), (3, 64, 72, 2), (24, 16, 64, 32), (24, 16, 128, 32), (24, 32, 256, 32), (24, 96, 256, 32)],
                          ids=["ragged", "split", "one_row", "tile128x64", "tile128", "large", "tile256"])
