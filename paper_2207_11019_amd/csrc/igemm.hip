@@ -720,10 +720,11 @@ static bool uni_of(const IgemmCall& c) { return (c.a.Ci * (c.dtype == LPM_BF16 ?
 // contraction, and where both leave CUs idle they run side by side (us per step, apart / together: float ResNet-18 2746 / 2588, width-48
 // ResNet 2408 / 2272, 3-D ResNet 1673 / 1600, ResNet-18/CIFAR 2808 / 2750, 16 images forward 163 / 152).  Larger tiles are for launches
 // that fill the card by themselves; a 128x64 plan of a few K tiles -- a projection's data gradient, mostly output -- runs
-// on 64x64 here (left alone: width-48 ResNet 2308, 3-D 1619, ResNet-18/CIFAR 2735).
+// on 64x64 here, whatever their number (volumetric at 3 and 4 volumes, 1536 and 2048 tiles: 1944 and 2236 left alone, 1915 and 2200 together; ResNets
+// of width 32 to 64 at 13 to 128 samples, up to 4096 tiles, within 0.5 %).
 static bool pairs(const IgemmCall& x, const IgemmCall& y) {
     if (x.dtype != y.dtype || uni_of(x) != uni_of(y) || (x.pl.splits > 1 && y.pl.splits > 1)) return false;      // (they share the scratch area)
-    auto small = [](const IgemmCall& c) { return c.pl.tile == TILE_64 || (c.pl.tile == TILE_128x64 && c.pl.kt_total <= 4 && tiles_of(TILE_64, c.a.M, c.a.N) <= 1088); };
+    auto small = [](const IgemmCall& c) { return c.pl.tile == TILE_64 || (c.pl.tile == TILE_128x64 && c.pl.kt_total <= 4); };
     if (!small(x) || !small(y)) return false;
     if (x.mode == MODE_FWD) return y.mode == MODE_FWD;
     if (x.dtype == LPM_F32 && !(x.a.kscale && y.a.kscale)) return false;
