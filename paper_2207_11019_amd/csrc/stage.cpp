@@ -22,11 +22,22 @@ static bool bias_in_wgrad_ok(int dtype, const LayerRt& lr) {
 // ... or the weight phase can sum it from dz in a kernel of its own
 static bool bias_from_dz_ok(const LayerRt& lr) { return lr.dz_unscaled || !(lr.d.flags & LPM_SCALE); }
 
-// Layers whose weight gradients share launches, and their operations at most (float: a sixteenth; a layer of more is on its own and
-// fills the card).  With 10 / 16 / 24 / 40 G operations, in us per step: R50 conv4_x at 64 1719 / 1711 / 1623 / 1626, ResNet-18/CIFAR
-// 2857 / 2838 / 2847 / 2845; VGG-16/224 6706 / 6735 / 6800 with none / 20 / 24; with 4 / 8 / 16 layers 1710 / 1623 / 1655 and 2921 / 2892 / 2907.
+// Layers whose weight gradients share launches, and their operations at most (float: a sixteenth; a layer of more is on its own).  A
+// launch costs some 10 us, and what layers share of it they gain; but none of them starts before the last one's dz is there, which a
+// long launch no longer makes up for.  The layers go into as few groups as the limits allow, as even as these can be (filled one after the
+// other: float ResNet-18 at 7 and 8 samples + 2 %).  Per step, in per cent of the time with 20 G operations:
+//                                            none    10    20    25    30    40   any
+//   R50 conv4_x, 16 samples a micro-batch     104   103   100   100   100   100   100
+//   24 / 32 samples                       103/100 100/102 100  98/99  98/98  98/99  98/99
+//   48 samples                                100    99   100    99    99    98    97
+//   VGG-16/224, 4                             100   100   100   100   100   101   102
+//   ResNet-18/CIFAR, 32                       107   100   100   100   100   100   100
+//   width-48 ResNet, 13                       118   100   100   100   100   100   101
+//   float ResNet-18, 8                        107   102   100   100   100   103   104
+//   float ResNet-18, 9 / 12               104/103 101/101 100  97/98  97/95 100/96 100/98
+// With 4 / 8 / 16 layers R50 conv4_x at 16 took 1710 / 1623 / 1655 us, ResNet-18/CIFAR 2921 / 2892 / 2907.
 constexpr int32_t WG_LAYERS = 8;
-constexpr double WG_WORK = 20e9;
+constexpr double WG_WORK = 30e9;
 static_assert(WG_LAYERS <= LPM_WGRAD_GROUP, "a launch takes that many");
 
 static bool misaligned(const void* p) { return ((uintptr_t)p & 255u) != 0; }
@@ -279,20 +290,47 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
                       lr.d.add_src == LPM_NONE && !(lr.d.flags & LPM_RELU) && (!(lr.d.flags & LPM_SCALE) || lr.dz_unscaled || lr.via_shortcut);
     }
     // Weight gradients are launched in groups of consecutive layers (the same groups in every form of the backward pass: what a
-    // launch holds decides how its reductions are cut): up to eight layers, as long as they are small enough to be better off together;
-    // next to the network's input, where the micro-batch waits for the last weight gradient, one and two.
+    // launch holds decides how its reductions are cut; WG_LAYERS, WG_WORK); next to the network's input, where the micro-batch waits for the
+    // last weight gradient, one and two (us per step with none but the limits / one / one and two / one to four apart: R50 conv4_x at 16 samples
+    // 1700 / 1689 / 1656 / 1687, ResNet-18/CIFAR at 32 1561 / 1553 / 1555 / 1552, width-48 ResNet 1837 / 1812 / 1814 / 1812, volumetric 1602 / 1620 /
+    // 1622 / 1618).
     {
-        int32_t n = 0, groups = 0;
-        double work = 0;
+        std::vector<LayerRt*> ly;
+        std::vector<double> w;
         for (int32_t i = first; i < last; ++i) {           // from the stage's input up: the backward pass ends there
             LayerRt& lr = s->Ly(i);
             if (!has_weights(lr.d)) continue;
-            const double w = 2. * (double)lr.g.rows_out() * lr.g.Cout * lr.g.K() * (dtype == LPM_F32 ? 16 : 1);
-            if (n == (first == 0 && groups < 3 ? groups : WG_LAYERS) || (n > 0 && work + w > WG_WORK)) { n = 0; work = 0; }
-            if (n == 0) { lr.wg_end = true; ++groups; }
-            ++n;
-            work += w;
+            ly.push_back(&lr);
+            w.push_back(2. * (double)lr.g.rows_out() * lr.g.Cout * lr.g.K() * (dtype == LPM_F32 ? 16 : 1));
         }
+        const size_t n = ly.size();
+        // the layer behind the group that begins at `at`: of no more than `layers`, and of no more than `most` operations or one layer
+        auto next = [&](size_t at, size_t layers, double most) {
+            double work = w[at];
+            size_t k = at + 1;
+            while (k < n && k - at < layers && work + w[k] <= most) work += w[k++];
+            return k;
+        };
+        size_t from = 0;
+        for (size_t layers = 1; first == 0 && layers <= 2 && from < n; ++layers) {
+            ly[from]->wg_end = true;
+            from = next(from, layers, WG_WORK);
+        }
+        auto groups = [&](double most, bool mark) {
+            int c = 0;
+            for (size_t at = from; at < n; at = next(at, WG_LAYERS, most), ++c) if (mark) ly[at]->wg_end = true;
+            return c;
+        };
+        const int fewest = groups(WG_WORK, false);
+        double even = WG_WORK;                             // the least limit that makes as few
+        for (size_t i = from; i < n; ++i) {
+            double sum = 0;
+            for (size_t k = i; k < n && k - i < (size_t)WG_LAYERS; ++k) {
+                sum += w[k];
+                if (sum < even && groups(sum, false) == fewest) even = sum;
+            }
+        }
+        groups(even, true);
     }
     s->n_trainable = off;
     if (dtype == LPM_BF16) {                   // transposed copies follow the mirrored region
