@@ -296,9 +296,11 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     // hides the LDS latency.  Two sets of them, or (TWO false) the next tile's over those of a step just multiplied: with two
     // wavefronts per SIMD, or float's longer products, the reads are covered all the same and the registers go to other streams'
     // wavefronts (float ResNet-18 2640 -> 2566 us per step, VGG-16/224 6640 -> 6575; the 64x64 tiles lose: R50 conv4_x at 64 1650 -> 1715).
-    // A float data gradient reads its weights in four pieces of 4 bytes, which takes longer: two sets with three stages, where several
-    // blocks share a CU's LDS (a stage 480 -> 256 channels at 4 x 37^2 566 -> 545, ResNet-18 the same), one with four (two: ResNet-18 + 0.4 %).
-    constexpr bool TWO = ES == 4 ? BT != BT_NONE && NST == 3 : !(BM == 128 && BN == 128 && WGN == 4);
+    // A float data gradient reads its weights in four pieces of 4 bytes, which takes longer: two sets where a K tile lies in one tap (one / two:
+    // a stage 480 -> 256 channels at 4 x 37^2 561 / 535 us, 512 -> 512 at 6 x 9^2 189 / 181, ResNet-18 at 4 / 9 / 16 samples 1.3-1.6 % less;
+    // alone, a lone layer's 256 -> 256 at 16 x 14^2 loses 1 %).  In chunks across taps the second set costs a third block per CU its
+    // registers: 64 -> 24 channels at 72 x 36 x 35, stride 2, 66.7 / 70.2.
+    constexpr bool TWO = ES == 4 ? BT != BT_NONE && UNI : !(BM == 128 && BN == 128 && WGN == 4);
     struct Frag { uint4 a[4][MI], b[4][NI]; };
     auto read = [&](Frag& f, int st, int ks) __attribute__((always_inline)) {
         const unsigned char* sp = lds + st * STAGE;
@@ -404,9 +406,13 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
                 }
                 tile_done(st1);
             };
-            for (int it = 0; it < nk; it += 2) {     // (an odd count ends with a tile of zeros)
+            for (int it = ES == 4; it < nk; it += 2) {     // (an odd count ends with a tile of zeros; float, whose products take long, behind the loop)
                 half(f0, f1);
                 half(f1, f0);
+            }
+            if (ES == 4 && (nk & 1)) {
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) multiply(f0, ks);
             }
         } else {
             for (int it = 0; it < nk; ++it) {

@@ -49,6 +49,14 @@ BF16 = [
     G(2, 80, 80, 64, 64, 5, 1, 2),        # single taps, ranges of 20 K tiles: the pixel records in several rounds
     G(5, 64, 64, 256, 256, 3, 1, 1),      # filter rows, ranges of 64 K tiles: records in several rounds, four stages
 ]
+F32 = [                                   # data gradients of one, three and (strided, by residue class) one to four K tiles
+    G(2, 105, 107, 40, 32, 1, 1, 0),      # more blocks than the card has CUs: three stages
+    G(2, 105, 107, 36, 96, 1, 1, 0),
+    G(2, 105, 107, 64, 32, 3, 2, 1),
+    G(2, 40, 41, 40, 32, 1, 1, 0),        # fewer: four
+    G(2, 20, 21, 36, 96, 1, 1, 0),
+    G(2, 20, 21, 64, 32, 3, 2, 1),
+]
 
 
 @pytest.fixture(scope="module")
@@ -64,7 +72,7 @@ def _id(c):
     return "%s_m%d_%s%dx%d_%d_%d_k%d_s%d" % (c[0], g["m"], "d%d_" % g["d"] if "d" in g else "", g["h"], g["w"], g["cin"], g["cout"], g["kh"], g["stride"])
 
 
-@pytest.mark.parametrize("case", [(t, g) for g in BOTH for t in ("bf16", "f32")] + [("bf16", g) for g in BF16], ids=_id)
+@pytest.mark.parametrize("case", [(t, g) for g in BOTH for t in ("bf16", "f32")] + [("bf16", g) for g in BF16] + [("f32", g) for g in F32], ids=_id)
 def test_contractions(lpm, case):
     import torch
     import torch.nn.grad as tg
