@@ -160,20 +160,24 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     for (int i = 0; i < B_LD; ++i) {
         if (BT) {
             const int idx = i * T + tid, kr = idx / (BN / 4), cc = idx - kr * (BN / 4);
-            b_off[i] = n0 + cc * 4 < p.N ? (unsigned)(n0 + cc * 4) * ES : OOB;
+            b_off[i] = n0 + cc * 4 < p.N ? (unsigned)(n0 + cc * 4) * ES + (UNI ? (unsigned)kr * p.b_pitch : 0u) : OOB;
             const int k = kt0 * kt_ch + kr;
             bt_t[i] = k / p.Ci; bt_k[i] = k - bt_t[i] * p.Ci;
         } else {
             b_off[i] = (unsigned)(n0 + i * RS + wave * 8 + lrow) * p.b_pitch + (UNI ? (unsigned)kcol * 16u : 0u);       // (rows past N lie past the buffer's end)
         }
     }
-    // cursor of the next K tile: UNI: tap (wave-uniform) and byte offset in its channels; else the lane's chunk and its tap
+    // cursor of the next K tile: UNI: tap (wave-uniform) and how many K tiles follow in it; else the lane's chunk and its tap
     int c_td = 0, c_th = 0, c_tw = 0;
-    unsigned c_c = 0;
+    int per = nk, run = nk;                  // K tiles of a tap, K tiles until the tap changes or the reduction ends
+    unsigned c_c = 0;                        // K tiles behind the tap's first one
     int l_t = 0, l_c = 0;
+    int4 l_e = make_int4(0, 0, 0, 0);        // the tap's table entry, fetched a tile ahead
     if (UNI) {
-        const int per = Cc / 8, t = div_by(kt0, p.dKt);
-        c_c = (unsigned)(kt0 - t * per) * 128u;
+        per = Cc / 8;
+        const int t = div_by(kt0, p.dKt);
+        c_c = (unsigned)(kt0 - t * per);
+        run = min(per - (int)c_c, nk);
         if (MODE != MODE_DGRAD_S) {
             c_td = div_by(t, p.dKhw);
             const int r = t - c_td * nkh * nkw;
@@ -187,55 +191,57 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
         const int k = kt0 * 8 + kcol;
         l_t = div_by(k, p.dCc); l_c = k - l_t * Cc;
         __syncthreads();                    // the tap table
+        l_e = tab[l_t < ntap ? l_t : 0];
     }
+    int left = nk - run;                     // ... and the K tiles behind those
     const int step_t = UNI ? 0 : div_by(8, p.dCc), step_c = UNI ? 0 : 8 - step_t * Cc;
 
-    // UNI: the A offsets of the current tap, with the rows that miss the image out of range
-    // (offsets and mask bit move on by differences: as sums of products they cost 80 ns of scalar arithmetic at every tap, half as much
-    // as a K tile of a 64-channel layer, whose tap changes with every one)
-    unsigned a_cur[A_LD], s_a = aoff0 + c_td * aD + c_th * aH + c_tw * aW, s_b = b0 + c_td * bD + c_th * bH + c_tw * bW;
+    // UNI: the A offsets of the current tap, with the rows that miss the image out of range, and the wave-uniform offsets of the K
+    // tile.  (They and the mask bit move on by differences: as sums of products they cost 80 ns of scalar arithmetic at every tap.)
+    unsigned dA = 128, dB = BT ? (unsigned)kt_ch * p.b_pitch : 128u;                 // to the next K tile of the tap
+    const unsigned tapA = tapC, tapB = BT ? (unsigned)p.Ci * p.b_pitch : tapC;       // what a tap's K tiles add up to
+    unsigned a_cur[A_LD], la = aoff0 + c_td * aD + c_th * aH + c_tw * aW + c_c * dA, lb = b0 + c_td * bD + c_th * bH + c_tw * bW + c_c * dB;
     unsigned bit = p.free_taps ? 1u : (1u << (24 + c_td)) | (1u << (12 + c_th)) | (1u << c_tw);
-    const unsigned aWH = aH - aW * (unsigned)(nkw - 1), bWH = bH - bW * (unsigned)(nkw - 1);                  // past the last tap of a row
-    const unsigned aHD = aD - aH * (unsigned)(nkh - 1) - aW * (unsigned)(nkw - 1), bHD = bD - bH * (unsigned)(nkh - 1) - bW * (unsigned)(nkw - 1);
+    const unsigned aWn = aW - tapA, bWn = bW - tapB;                                                          // the next tap of the row
+    const unsigned aWH = aH - aW * (unsigned)(nkw - 1) - tapA, bWH = bH - bW * (unsigned)(nkw - 1) - tapB;    // past the last one
+    const unsigned aHD = aD - aH * (unsigned)(nkh - 1) - aW * (unsigned)(nkw - 1) - tapA, bHD = bD - bH * (unsigned)(nkh - 1) - bW * (unsigned)(nkw - 1) - tapB;
     auto set_tap = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < A_LD; ++i) a_cur[i] = (a_msk[i] & bit) == bit ? a_base[i] : OOB;
     };
-    auto next_tap = [&]() __attribute__((always_inline)) {
-        if (++c_tw < nkw) { s_a += aW; s_b += bW; bit += bit & 0xfffu; }
+    // The run of K tiles is over: the next tap, or none.  Then the buffers count as empty: further stages fill with zeros, the
+    // number of loads in flight stays what the waits assume, and the loop below needs no special case at its end.  (The
+    // wave-uniform offsets return to zero: the bounds check holds for offsets inside a buffer's length.)
+    auto next_run = [&]() __attribute__((always_inline)) {
+        if (!UNI || left == 0) {
+            rsA.z = 0; rsB.z = 0;
+            la = 0; lb = 0; dA = 0; dB = 0;
+            run = 0x7fffffff;
+            return;
+        }
+        if (++c_tw < nkw) { la += aWn; lb += bWn; bit += bit & 0xfffu; }
         else {
             c_tw = 0;
-            if (++c_th < nkh) { s_a += aWH; s_b += bWH; bit = ((bit & 0xfff000u) << 1) | (bit & 0xff000000u) | 1u; }
-            else { c_th = 0; s_a += aHD; s_b += bHD; bit = ((bit & 0xff000000u) << 1) | 0x1001u; }
+            if (++c_th < nkh) { la += aWH; lb += bWH; bit = ((bit & 0xfff000u) << 1) | (bit & 0xff000000u) | 1u; }
+            else { c_th = 0; la += aHD; lb += bHD; bit = ((bit & 0xff000000u) << 1) | 0x1001u; }
         }
         if (p.free_taps) bit = 1u;
+        run = min(per, left);
+        left -= run;
         set_tap();
     };
     if (UNI) set_tap();
-    // Issues the loads of the next K tile into a stage.  Past the last tile the buffers count as empty: the stage fills with
-    // zeros, the number of loads in flight stays what the waits assume, and the loop below needs no special case at its end.
-    // The loads come in four parts, so that the loop below can put each behind a few matrix instructions.
-    int left = nk;
-    unsigned la = 0, lb = 0;                 // this tile's wave-uniform offsets (UNI), or the lane's (with the tap's bits)
+    // Issues the loads of the next K tile into a stage, in four parts, so that the loop below can put each behind a few matrix
+    // instructions.
     unsigned lbit = 0;
     bool lin = false;
     auto issue = [&](int st, int part) __attribute__((always_inline)) {
         unsigned char* sp = lds + st * STAGE + wave * 1024;
-        if (part == 0) {
-            const bool live = left > 0;
-            --left;
-            rsA.z = live ? p.a_bytes + bias : 0u;
-            rsB.z = live ? p.b_bytes : 0u;
-            if (UNI) {
-                la = live ? s_a + c_c : 0u;
-                lb = live && !BT ? s_b + c_c : 0u;
-            } else {
-                lin = l_t < ntap;
-                const int4 e = tab[lin ? l_t : 0];
-                lbit = (unsigned)e.z;
-                la = (unsigned)e.x + (unsigned)l_c * 16u;
-                lb = (unsigned)e.y + (unsigned)l_c * 16u;
-            }
+        if (part == 0 && !UNI) {
+            lin = l_t < ntap;
+            lbit = (unsigned)l_e.z;
+            la = (unsigned)l_e.x + (unsigned)l_c * 16u;
+            lb = (unsigned)l_e.y + (unsigned)l_c * 16u;
         }
 #pragma unroll
         for (int i = 0; i < A_LD; ++i) {
@@ -247,11 +253,8 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
         for (int i = 0; i < B_LD; ++i) {
             if ((i + A_LD) * 4 / LPT != part) continue;
             unsigned char* d = sp + A_BYTES + i * RS * 128;
-            if (UNI && BT) {
-                load_to_lds16(rsB, d, b_off[i] == OOB ? OOB : b_off[i] + s_b + (c_c / ES + (unsigned)((i * T + tid) / (BN / 4))) * p.b_pitch);
-            } else if (UNI) {
-                load_to_lds16s(rsB, d, b_off[i], lb);
-            } else if (BT) {
+            if (UNI) load_to_lds16s(rsB, d, b_off[i], lb);
+            else if (BT) {
                 const bool bl = (bt_t[i] < ntap) & (b_off[i] != OOB);
                 const unsigned tbb = (unsigned)tab[bt_t[i] < ntap ? bt_t[i] : 0].y;
                 load_to_lds16(rsB, d, bl ? b_off[i] + tbb + (unsigned)bt_k[i] * p.b_pitch : OOB);
@@ -260,16 +263,13 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
             } else load_to_lds16(rsB, d, lin ? b_off[i] + lb : OOB);
         }
         if (part == 3) {
-            if (UNI) {
-                c_c += 128;
-                if (c_c == tapC) {
-                    c_c = 0;
-                    next_tap();
-                }
-            } else {
+            if (UNI) { la += dA; lb += dB; }
+            else {
                 l_t += step_t; l_c += step_c;
                 if (l_c >= Cc) { l_c -= Cc; ++l_t; }
+                l_e = tab[l_t < ntap ? l_t : 0];
             }
+            if (--run == 0) next_run();
         }
     };
 
@@ -284,8 +284,13 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     const int wm = wave / WGN, wn = wave - wm * WGN;
     // operand addresses: row lane % 32 of the wavefront's part, chunk 2*ks + lane/32 of the K tile
     const int rl = lane & 31, kh_ = lane >> 5;
-    const unsigned rowA = (unsigned)(wm * WTM + rl) * 128u, rowB = (unsigned)(A_BYTES + (wn * WTN + rl) * 128);
-    const unsigned colBT = (unsigned)(A_BYTES + (wn * WTN + rl) * 4);
+    const unsigned char *opA[4], *opB[4];        // of the first stage; stages and rows further on are constants beside them
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        const unsigned x = (unsigned)(((ks * 2 + kh_) ^ ((lane >> 1) & 7)) << 4);
+        opA[ks] = lds + (unsigned)(wm * WTM + rl) * 128u + x;
+        opB[ks] = lds + (BT ? (unsigned)(A_BYTES + (wn * WTN + rl) * 4 + kh_ * 16 * BN) : (unsigned)(A_BYTES + (wn * WTN + rl) * 128) + x);
+    }
     int ks_c[KS ? 4 : 1];                    // channel of the lane's chunk ks in the K tile read next
 #pragma unroll
     for (int ks = 0; ks < (KS ? 4 : 0); ++ks) ks_c[ks] = (kt0 * kt_ch + (ks * 2 + kh_) * 4) % p.Ci;
@@ -303,15 +308,14 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     constexpr bool TWO = ES == 4 ? BT != BT_NONE && UNI : !(BM == 128 && BN == 128 && WGN == 4);
     struct Frag { uint4 a[4][MI], b[4][NI]; };
     auto read = [&](Frag& f, int st, int ks) __attribute__((always_inline)) {
-        const unsigned char* sp = lds + st * STAGE;
+        const int o = st * STAGE;
         {
-            const unsigned x = (unsigned)(((ks * 2 + kh_) ^ ((lane >> 1) & 7)) << 4);
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi) f.a[ks][mi] = *reinterpret_cast<const uint4*>(sp + rowA + x + mi * 4096);
+            for (int mi = 0; mi < MI; ++mi) f.a[ks][mi] = *reinterpret_cast<const uint4*>(opA[ks] + o + mi * 4096);
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) {
                 if (BT) {
-                    const unsigned char* q = sp + colBT + (ks * 2 + kh_) * 4 * (BN * 4) + ni * 128;
+                    const unsigned char* q = opB[ks] + o + ks * 32 * BN + ni * 128;
                     f.b[ks][ni] = make_uint4(*reinterpret_cast<const unsigned*>(q), *reinterpret_cast<const unsigned*>(q + BN * 4),
                                              *reinterpret_cast<const unsigned*>(q + 2 * BN * 4), *reinterpret_cast<const unsigned*>(q + 3 * BN * 4));
                     if constexpr (KS) {
@@ -320,7 +324,7 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
                         b = make_uint4(__float_as_uint(__uint_as_float(b.x) * k4.x), __float_as_uint(__uint_as_float(b.y) * k4.y),
                                        __float_as_uint(__uint_as_float(b.z) * k4.z), __float_as_uint(__uint_as_float(b.w) * k4.w));
                     }
-                } else f.b[ks][ni] = *reinterpret_cast<const uint4*>(sp + rowB + x + ni * 4096);
+                } else f.b[ks][ni] = *reinterpret_cast<const uint4*>(opB[ks] + o + ni * 4096);
             }
             if constexpr (KS) {
                 ks_c[ks] += ks_step;
@@ -382,51 +386,42 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
         for (int q = 0; q < 4; ++q) issue(AHEAD - 1, q);
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) read(f0, 0, ks);
-        int st = 0, ld = DRAIN ? 0 : NST - 1;      // stages of the tile being multiplied and of the one to be loaded
+        // The stages of a tile are constants: the loop goes round the ring (twice, where that has an odd number of stages and the
+        // registers two sets) and leaves it behind the last tile.
         // A quarter of the next tile's reads and of the loads behind it go with a quarter of this one's products: the LDS,
         // the address arithmetic and the matrix cores work side by side (all reads first, and the products would wait
         // for the LDS queue to drain; all loads first, and the matrix cores would idle meanwhile).
-        auto tile_done = [&](int st1) __attribute__((always_inline)) {
-            __builtin_amdgcn_sched_barrier(0);
-            st = st1;
-            ld = ld == NST - 1 ? 0 : ld + 1;
-        };
-        if constexpr (TWO) {
-            Frag f1;
-            auto half = [&](const Frag& cur, Frag& nxt) __attribute__((always_inline)) {
-                const int st1 = st == NST - 1 ? 0 : st + 1;
+        constexpr int ROUND = TWO && NST % 2 ? 2 * NST : NST;
+        Frag f1;
+        for (int it = 0;;) {
+            bool more = true;
+#pragma unroll
+            for (int u = 0; u < ROUND && more; ++u) {
+                const int st = u % NST, st1 = (u + 1) % NST, ld = DRAIN ? st : (u + NST - 1) % NST;
+                Frag &cur = TWO && (u & 1) ? f1 : f0, &nxt = TWO && !(u & 1) ? f1 : f0;
                 meet();
-                read(nxt, st1, 0);
+                if constexpr (TWO) {
+                    read(nxt, st1, 0);
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (ks < 3) read(nxt, st1, ks + 1);
-                    multiply(cur, ks);
-                    issue(ld, ks);
+                    for (int ks = 0; ks < 4; ++ks) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (ks < 3) read(nxt, st1, ks + 1);
+                        multiply(cur, ks);
+                        issue(ld, ks);
+                    }
+                } else {
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks) {     // (the next tile's operands over those just multiplied)
+                        multiply(cur, ks);
+                        read(cur, st1, ks);
+                        issue(ld, ks);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
-                tile_done(st1);
-            };
-            for (int it = ES == 4; it < nk; it += 2) {     // (an odd count ends with a tile of zeros; float, whose products take long, behind the loop)
-                half(f0, f1);
-                half(f1, f0);
+                __builtin_amdgcn_sched_barrier(0);
+                more = ++it < nk;
             }
-            if (ES == 4 && (nk & 1)) {
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) multiply(f0, ks);
-            }
-        } else {
-            for (int it = 0; it < nk; ++it) {
-                const int st1 = st == NST - 1 ? 0 : st + 1;
-                meet();
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {     // (the next tile's operands over those just multiplied)
-                    multiply(f0, ks);
-                    read(f0, st1, ks);
-                    issue(ld, ks);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                tile_done(st1);
-            }
+            if (!more) break;
         }
         LPM_WAIT_VM(0);
     }
