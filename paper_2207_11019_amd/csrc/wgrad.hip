@@ -23,7 +23,7 @@
 // LDS at the end (one group per SIMD left the latencies of LDS and barrier uncovered: a launch is about one block per CU).
 // The pixel range may be split over blocks; the partial results are summed by wgrad_reduce_batch in a fixed order.
 // Measured alone with its reduction (us; four wavefronts, addresses followed lane by lane -> this): 3x3 256 -> 256 channels, 128
-// images of 14x14 65.7 -> 47.5, 16 images 21.4 -> 18.7; 4 x 224^2 64 -> 64 34.7 -> 26.7; 1x1 1024 -> 256, 128 x 14^2 39.8 -> 28.7.
+// images of 14x14 65.7 -> 47.5, 16 images 21.4 -> 18.7; 4 x 224^2 64 -> 64 34.7 -> 26.7; 1x1 1024 -> 256, 128 x 14^2 39.8 -> 28.7, now 24.7.
 // Three stages for the 64-channel tiles: with four (or records for a longer run of pixels) the launch is faster alone, but
 // the other streams' blocks no longer fit the CU beside it (R50 conv4_x at 64: 1.85 -> 1.89 ms per step).  Four for the
 // 128-channel tiles and for filter rows over 64 K tiles and more, where the loads in flight count for more.
@@ -65,6 +65,13 @@ __device__ __forceinline__ u32x2_ tr4(const unsigned char* p) {
 }
 
 enum { LIN = 0, PIX = 1, ROW3 = 3 };
+
+// Where 16-byte chunk c of row r of an operand lies in an LDS row of P bytes, and which chunk lies at position c (its own inverse).
+// 16 lanes of a transpose read take 32 bytes each of four consecutive rows: of 256-byte rows (128 channels) all four share their
+// banks, so the rows' 64-byte quarters change places by the row (1x1 1024 -> 256 channels, 128 x 14^2, alone 28.3 -> 24.7 us; per step, R50
+// conv4_x at 16 / 128 samples 1655 -> 1621, 6596 -> 6390).  Rows of 128 bytes take as long either way, and so do float's.
+template <int ES, int P>
+__device__ __forceinline__ int place(int c, int r) { return ES == 2 && P == 256 ? c ^ ((r & 3) << 2) : c; }
 
 // One block: tile `tile` of dW (all of them, tap groups included) over pixel range `split`.
 template <typename E, int BM, int BN, int KIND, int NST>
@@ -129,13 +136,13 @@ __device__ __forceinline__ void wgrad_tile(const WgArgs p, int tile, const int s
     int a_px[A_LD], b_u[B_LD], b_in[B_LD];
 #pragma unroll
     for (int i = 0; i < A_LD; ++i) {
-        const int idx = i * T + tid, r = idx / (PA / 16), ch = co0 + (idx - r * (PA / 16)) * (16 / ES);
+        const int idx = i * T + tid, r = idx / (PA / 16), ch = co0 + place<ES, PA>(idx - r * (PA / 16), r) * (16 / ES);
         a_px[i] = ch < p.Cout ? r & 7 : 8;                        // ROW3: pixel of the segment (8: none)
         a_off[i] = KIND == ROW3 ? (unsigned)((r & 7) * p.Cout + ch) * ES : ch < p.Cout ? (unsigned)(r * p.Cout + ch) * ES : WG_OOB;
     }
 #pragma unroll
     for (int i = 0; i < B_LD; ++i) {
-        const int idx = i * T + tid, r = idx / (PB / 16), ch = ci0 + (idx - r * (PB / 16)) * (16 / ES);
+        const int idx = i * T + tid, r = idx / (PB / 16), ch = ci0 + place<ES, PB>(idx - r * (PB / 16), r) * (16 / ES);
         const bool ok = r < B_ROWS && ch < p.Cin;
         b_u[i] = KIND == ROW3 ? min(r / HX, 7) : r;
         b_in[i] = KIND == ROW3 ? (ok ? r - r / HX * HX : 31) : 0;                     // (bit 31 of a mask is never set)
@@ -213,9 +220,15 @@ __device__ __forceinline__ void wgrad_tile(const WgArgs p, int tile, const int s
     // (lane / 16 % 2) * 16 + (lane % 4) * 4 .. + 3 of 32 -- each lane ends up with column lane % 32.  float: row lane / 32.
     const int tr_row = (lane & 15) >> 2, tr_col = (((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2;
     const int rl = lane & 31, kq = lane >> 5;
-    const unsigned fa = ES == 2 ? (unsigned)((kq * 8 + tr_row) * PA + wm * WTM * 2 + tr_col) : (unsigned)(kq * PA + (wm * WTM + rl) * 4);
-    const unsigned fb = A_BYTES + (ES == 2 ? (unsigned)((kq * (KIND == ROW3 ? HX : 8) + tr_row) * PB + wn * WTN * 2 + tr_col)
-                                           : (unsigned)(kq * PB + (wn * WTN + rl) * 4));
+    // (K steps and a step's further reads lie multiples of four rows apart: the lane's first row is enough for place().)
+    unsigned fa[MI], fb[NI];
+    const int ra0 = ES == 2 ? kq * 8 + tr_row : kq, rb0 = ES == 2 ? kq * (KIND == ROW3 ? HX : 8) + tr_row : kq;
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+        fa[mi] = (unsigned)(ra0 * PA + place<ES, PA>(wm * WTM / (16 / ES) + mi * (32 * ES / 16), ra0) * 16 + (ES == 2 ? tr_col : rl * 4));
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+        fb[ni] = (unsigned)(A_BYTES + rb0 * PB + place<ES, PB>(wn * WTN / (16 / ES) + ni * (32 * ES / 16), rb0) * 16 + (ES == 2 ? tr_col : rl * 4));
 
     // two operand sets: the next K tile is read from LDS while the matrix cores work on the present one
     struct Frag { unsigned a[KSW][MI][4], b[KSW][NI][TAPS == 3 ? 6 : 4]; };
@@ -226,13 +239,13 @@ __device__ __forceinline__ void wgrad_tile(const WgArgs p, int tile, const int s
         if constexpr (ES == 2) {
 #pragma unroll
             for (int mi = 0; mi < MI; ++mi) {
-                const unsigned char* q = sp + fa + ka * 16 * PA + mi * 64;
+                const unsigned char* q = sp + fa[mi] + ka * 16 * PA;
                 const u32x2_ v0 = tr4(q), v1 = tr4(q + 4 * PA);
                 f.a[ks][mi][0] = v0.x; f.a[ks][mi][1] = v0.y; f.a[ks][mi][2] = v1.x; f.a[ks][mi][3] = v1.y;
             }
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) {
-                const unsigned char* q = sp + fb + ka * (TAPS == 3 ? 2 * HX : 16) * PB + ni * 64;
+                const unsigned char* q = sp + fb[ni] + ka * (TAPS == 3 ? 2 * HX : 16) * PB;
                 const u32x2_ v0 = tr4(q), v1 = tr4(q + 4 * PB);
                 f.b[ks][ni][0] = v0.x; f.b[ks][ni][1] = v0.y; f.b[ks][ni][2] = v1.x; f.b[ks][ni][3] = v1.y;
                 if constexpr (TAPS == 3) {
@@ -244,9 +257,9 @@ __device__ __forceinline__ void wgrad_tile(const WgArgs p, int tile, const int s
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
 #pragma unroll
-                for (int mi = 0; mi < MI; ++mi) f.a[ks][mi][j] = *reinterpret_cast<const unsigned*>(sp + fa + (ka * 8 + j * 2) * PA + mi * 128);
+                for (int mi = 0; mi < MI; ++mi) f.a[ks][mi][j] = *reinterpret_cast<const unsigned*>(sp + fa[mi] + (ka * 8 + j * 2) * PA);
 #pragma unroll
-                for (int ni = 0; ni < NI; ++ni) f.b[ks][ni][j] = *reinterpret_cast<const unsigned*>(sp + fb + (ka * 8 + j * 2) * PB + ni * 128);
+                for (int ni = 0; ni < NI; ++ni) f.b[ks][ni][j] = *reinterpret_cast<const unsigned*>(sp + fb[ni] + (ka * 8 + j * 2) * PB);
             }
         }
     };
