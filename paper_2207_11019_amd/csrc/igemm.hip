@@ -17,6 +17,11 @@
 // rows -- load zeros through the buffer bounds check.  Whether a row meets a tap is one bit test against a mask made once per row.
 // A channel count that is a multiple of 128 bytes lets a whole K tile lie in one tap (UNI): the tap is wave-uniform.
 // Otherwise every lane follows its own chunk's tap through a table in LDS, so any multiple of 16 bytes of channels works.
+// bf16 filters three taps wide, stride 1, in whole K tiles a tap (KT_ROW): the three taps of a filter row meet the same pixels but for one
+// at either end, so the tile's pixels are loaded once for all three, into a ring of their own, and a tap is another row of LDS to read
+// from: a third fewer bytes from L2 per product on 64x64 tiles, two fifths on 128x64.  Where a tap lies beside the image the reader
+// takes a row of zeros.  Alone, us: 4 x 224^2 64 -> 64 33.1 -> 28.5, 16 x 32^2 x 64 5.4 -> 5.1; the others keep their time alone and
+// leave the L2 to the streams beside them.
 //
 // The matrix instructions are v_mfma_f32_32x32x16_bf16 (a lane supplies 8 consecutive K values of row lane % 32) and
 // v_mfma_f32_32x32x2_f32 (one value; four instructions share a 16-byte chunk, the K order inside a chunk being the same
@@ -26,6 +31,7 @@
 #include "lds_dma.h"
 #include <algorithm>
 #include <cstring>
+#include <utility>
 
 namespace lpm {
 
@@ -40,20 +46,38 @@ constexpr int AUX_AGENT = 16;
 // layout of B: [N][K] rows; K outermost; K outermost and scaled
 enum { BT_NONE = 0, BT_PLAIN = 1, BT_SCALED = 2 };
 
+// f(0), f(1), ... until one of them is false
+template <typename F, int... I>
+__device__ __forceinline__ bool round_of(F& f, std::integer_sequence<int, I...>) { return (f(std::integral_constant<int, I>{}) && ...); }
+
+// What a K tile is: chunks that follow their taps lane by lane; 64 (float: 32) channels of one tap; the same, the taps of a filter row
+// one after the other
+enum { KT_CHUNKS = 0, KT_TAP = 1, KT_ROW = 2 };
+
+// KT_ROW: filter rows that are read or being loaded at a time, while tile t + 1 is read and tile t + nst (and a part of the row behind
+// it) is loaded, whatever t
+constexpr int row_stages(int nst) { return (nst + 3) / 3 + 1; }
+
 // Block bx of the gx tiles' blocks, part bz of a split reduction.
-template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, bool UNI, int BT>
+template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, int KIND, int BT>
 __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, const int gx, const int bz) {
-    constexpr int ES = sizeof(E), T = WGM * WGN * 64, RS = T / 8;             // rows a load step covers
+    constexpr int ES = sizeof(E), T = WGM * WGN * 64, RS = T / 8;        // rows a load step covers
     constexpr int WTM = BM / WGM, WTN = BN / WGN, MI = WTM / 32, NI = WTN / 32;
-    constexpr int A_LD = BM / RS, B_LD = BN / RS, LPT = A_LD + B_LD;
-    constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
+    constexpr bool UNI = KIND != KT_CHUNKS, ROW = KIND == KT_ROW;
+    // ROW: the pixels that a filter row of the tile meets, each of them once: one more at either end, whole pieces of eight
+    constexpr int A_ROWS = ROW ? BM + 8 : BM, A_N = (A_ROWS + RS - 1) / RS;            // A_N load steps,
+    constexpr int A_LD = ROW ? (A_N + 2) / 3 : A_N, B_LD = BN / RS, LPT = A_LD + B_LD;  // a third of them with every K tile
+    constexpr int A_BYTES = A_ROWS * 128, NSTA = ROW ? row_stages(NST) : NST;
+    constexpr int STAGE = ROW ? BN * 128 : A_BYTES + BN * 128, B_AT = ROW ? NSTA * A_BYTES : A_BYTES;      // ROW: a ring for A and one for B
+    constexpr int STAGES = ROW ? B_AT + NST * STAGE + 1024 : NST * STAGE;                                   // ... and 1 KB for load steps past A's end
     static_assert(!BT || ES == 4, "float data gradient only");
+    static_assert(!ROW || (ES == 2 && MODE != MODE_DGRAD_S), "filter rows: bf16, stride 1");
     // BT: B is read with its reduction index outermost; BT_SCALED: and multiplied by kscale, kept in LDS, on its way to the
     // matrix cores (the dz of a float layer with a scale is stored without it; 16 multiplications per 16 products)
     constexpr bool KS = BT == BT_SCALED;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];      // NST stages [+ tap table] [+ kscale]
-    int4* tab = reinterpret_cast<int4*>(lds + NST * STAGE);
-    float* ksc = reinterpret_cast<float*>(lds + NST * STAGE + (UNI ? 0 : MAX_TAB * 16));
+    int4* tab = reinterpret_cast<int4*>(lds + STAGES);
+    float* ksc = reinterpret_cast<float*>(lds + STAGES + (UNI ? 0 : MAX_TAB * 16));
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // (strided: the residue classes differ in work, so their tiles stay in launch order, which deals them to the XCDs in turn)
@@ -100,8 +124,9 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     // A's buffer starts `bias` bytes early, so that the offset of a row's tap (0,0) -- outside the image where there is
     // padding -- and the tap's own are both non-negative: lane offset + wave-uniform offset.  (Chunks whose tap misses the
     // image never use them.)
-    const unsigned span = (unsigned)((((nkd - 1) * p.Hi + (nkh - 1)) * p.Wi + (nkw - 1))) * tapC;      // from the first tap to the last
-    const unsigned bias = MODE == MODE_FWD ? (unsigned)((od * p.Hi + oh) * p.Wi + ow) * tapC : (ntap ? span : 0u);
+    // (ROW: a row's offset is that of the middle tap)
+    const unsigned span = (unsigned)((((nkd - 1) * p.Hi + (nkh - 1)) * p.Wi + (ROW ? 0 : nkw - 1))) * tapC;      // from the first tap to the last
+    const unsigned bias = MODE == MODE_FWD ? (unsigned)((od * p.Hi + oh) * p.Wi + (ROW ? 0 : ow)) * tapC : (ntap ? span : 0u);
     const unsigned aoff0 = MODE == MODE_FWD ? 0u : (ntap ? span : 0u);           // wave-uniform offset of the first tap
     u32x4_ rsA = buffer_words((const unsigned char*)p.A - bias, p.a_bytes + bias), rsB = buffer_words(p.B, p.b_bytes);
 
@@ -118,11 +143,11 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     // ---- loader state.  Lane l of a load fills chunk position l % 8 of row r = 8 * wave + l / 8 (a load step is a multiple of 16
     // rows): it fetches chunk (l % 8) ^ (r / 2 % 8)
     const int lrow = lane >> 3, kcol = (lane & 7) ^ ((wave & 1) * 4 + (lrow >> 1));
-    unsigned a_base[A_LD], a_msk[A_LD], b_off[B_LD];
+    unsigned a_base[A_N], a_msk[A_N], b_off[B_LD];
 #pragma unroll
-    for (int i = 0; i < A_LD; ++i) {
-        const int row = m0 + i * RS + wave * 8 + lrow;
-        const bool ok = row < rows;
+    for (int i = 0; i < A_N; ++i) {
+        const int pos = i * RS + wave * 8 + lrow, row = ROW ? m0 - 1 + pos : m0 + pos;
+        const bool ok = ROW ? (row >= 0) & (row < rows) & (pos < BM + 2) : row < rows;
         const int rr = ok ? row : 0;
         int wq, hq, n, dq = 0;
         if (MODE == MODE_DGRAD_S) {
@@ -138,12 +163,13 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
             if (p.Dr > 1) { const int ns = div_by(n, p.dDr); dq = n - ns * p.Dr; n = ns; }
         }
         const bool fwd = MODE == MODE_FWD;
-        const int h0 = fwd ? hq * p.stride - oh : hq + oh, w0 = fwd ? wq * p.stride - ow : wq + ow;
+        const int h0 = fwd ? hq * p.stride - oh : hq + oh, w0 = ROW ? wq : fwd ? wq * p.stride - ow : wq + ow;
         int d0 = 0;
         unsigned m = 0xffffffffu;
         if (!p.free_taps) {
             m = fwd ? (tap_bits(max(0, -h0), min(nkh, p.Hi - h0)) << 12) | tap_bits(max(0, -w0), min(nkw, p.Wi - w0))
                     : (tap_bits(max(0, h0 - p.Hi + 1), min(nkh, h0 + 1)) << 12) | tap_bits(max(0, w0 - p.Wi + 1), min(nkw, w0 + 1));
+            if (ROW) m = (m & 0xfff000u) | 1u;             // (along the image row the reader masks)
             m |= 1u << 24;
         }
         if (p.Kd > 1 || p.Dr > 1 || p.Di > 1) {
@@ -169,11 +195,19 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     }
     // cursor of the next K tile: UNI: tap (wave-uniform) and how many K tiles follow in it; else the lane's chunk and its tap
     int c_td = 0, c_th = 0, c_tw = 0;
+    // ROW: all three in filter rows for K tiles, the same for taps; B counts for itself, A's loads run ahead
     int per = nk, run = nk;                  // K tiles of a tap, K tiles until the tap changes or the reduction ends
     unsigned c_c = 0;                        // K tiles behind the tap's first one
     int l_t = 0, l_c = 0;
     int4 l_e = make_int4(0, 0, 0, 0);        // the tap's table entry, fetched a tile ahead
-    if (UNI) {
+    if constexpr (ROW) {
+        per = Cc / 8;
+        const int g = kt0 / 3, t = div_by(g, p.dKt);            // (a block's part begins with a filter row)
+        c_c = (unsigned)(g - t * per);
+        run = min(per - (int)c_c, nk / 3);
+        c_td = p.Kd > 1 ? t / p.Kh : 0;
+        c_th = t - c_td * p.Kh;
+    } else if (UNI) {
         per = Cc / 8;
         const int t = div_by(kt0, p.dKt);
         c_c = (unsigned)(kt0 - t * per);
@@ -193,26 +227,42 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
         __syncthreads();                    // the tap table
         l_e = tab[l_t < ntap ? l_t : 0];
     }
-    int left = nk - run;                     // ... and the K tiles behind those
+    int left = (ROW ? nk / 3 : nk) - run;    // ... and the K tiles behind those
+    int b_run = run, b_left = left;
     const int step_t = UNI ? 0 : div_by(8, p.dCc), step_c = UNI ? 0 : 8 - step_t * Cc;
 
     // UNI: the A offsets of the current tap, with the rows that miss the image out of range, and the wave-uniform offsets of the K
     // tile.  (They and the mask bit move on by differences: as sums of products they cost 80 ns of scalar arithmetic at every tap.)
     unsigned dA = 128, dB = BT ? (unsigned)kt_ch * p.b_pitch : 128u;                 // to the next K tile of the tap
     const unsigned tapA = tapC, tapB = BT ? (unsigned)p.Ci * p.b_pitch : tapC;       // what a tap's K tiles add up to
-    unsigned a_cur[A_LD], la = aoff0 + c_td * aD + c_th * aH + c_tw * aW + c_c * dA, lb = b0 + c_td * bD + c_th * bH + c_tw * bW + c_c * dB;
+    unsigned a_cur[A_N], la = aoff0 + c_td * aD + c_th * aH + c_tw * aW + c_c * dA, lb = b0 + c_td * bD + c_th * bH + c_tw * bW + c_c * dB;
+    unsigned b_tap = tapC, b_chunk = dB - 2 * tapC;                                  // ROW: to the next tap of the row, from its last tap to the next channels' first
     unsigned bit = p.free_taps ? 1u : (1u << (24 + c_td)) | (1u << (12 + c_th)) | (1u << c_tw);
     const unsigned aWn = aW - tapA, bWn = bW - tapB;                                                          // the next tap of the row
     const unsigned aWH = aH - aW * (unsigned)(nkw - 1) - tapA, bWH = bH - bW * (unsigned)(nkw - 1) - tapB;    // past the last one
+    const unsigned aHr = aH - tapA, aHDr = aD - aH * (unsigned)(nkh - 1) - tapA;                               // ROW
     const unsigned aHD = aD - aH * (unsigned)(nkh - 1) - aW * (unsigned)(nkw - 1) - tapA, bHD = bD - bH * (unsigned)(nkh - 1) - bW * (unsigned)(nkw - 1) - tapB;
     auto set_tap = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < A_LD; ++i) a_cur[i] = (a_msk[i] & bit) == bit ? a_base[i] : OOB;
+        for (int i = 0; i < A_N; ++i) a_cur[i] = (a_msk[i] & bit) == bit ? a_base[i] : OOB;
     };
     // The run of K tiles is over: the next tap, or none.  Then the buffers count as empty: further stages fill with zeros, the
     // number of loads in flight stays what the waits assume, and the loop below needs no special case at its end.  (The
     // wave-uniform offsets return to zero: the bounds check holds for offsets inside a buffer's length.)
     auto next_run = [&]() __attribute__((always_inline)) {
+        if constexpr (ROW) {
+            if (left == 0) {
+                rsA.z = 0; la = 0; dA = 0;
+                run = 0x7fffffff;
+                return;
+            }
+            if (++c_th < nkh) { la += aHr; bit = ((bit & 0xfff000u) << 1) | (bit & 0xff000000u) | 1u; }
+            else { c_th = 0; la += aHDr; bit = ((bit & 0xff000000u) << 1) | 0x1001u; }
+            run = min(per, left);
+            left -= run;
+            set_tap();
+            return;
+        }
         if (!UNI || left == 0) {
             rsA.z = 0; rsB.z = 0;
             la = 0; lb = 0; dA = 0; dB = 0;
@@ -233,9 +283,42 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     if (UNI) set_tap();
     // Issues the loads of the next K tile into a stage, in four parts, so that the loop below can put each behind a few matrix
     // instructions.
+    // ROW: tile u of the block brings part (u + 2) % 3 of the pixels of filter row (u + 2) / 3: the last of them with the row's first tile.
+    unsigned a_wr = 0;                       // A's stage being loaded
+    auto issue_row = [&](int st, int u3, int part) __attribute__((always_inline)) {
+        const int j = (u3 + 2) % 3;
+        unsigned char* sp = lds + a_wr + wave * 1024;
+#pragma unroll
+        for (int i = 0; i < A_LD; ++i) {
+            if (i * 4 / LPT != part) continue;
+            const int k = j * A_LD + i;
+            const bool in = (k + 1) * RS <= A_ROWS || (k < A_N && k * RS + wave * 8 < A_ROWS);
+            load_to_lds16s(rsA, in ? sp + k * RS * 128 : lds + STAGES - 1024, k < A_N && in ? a_cur[k < A_N ? k : 0] : OOB, la);
+        }
+        if (part == 3 && j == 2) {
+            a_wr = a_wr == (NSTA - 1) * A_BYTES ? 0u : a_wr + A_BYTES;
+            la += dA;
+            if (--run == 0) next_run();
+        }
+        if (st < 0) return;                  // (ahead of the first tile: its pixels alone)
+#pragma unroll
+        for (int i = 0; i < B_LD; ++i)
+            if ((i + A_LD) * 4 / LPT == part) load_to_lds16s(rsB, lds + B_AT + st * STAGE + (wave * 1024 + i * RS * 128), b_off[i], lb);
+        if (part == 3) {
+            if (u3 < 2) lb += b_tap;
+            else {
+                lb += b_chunk;
+                if (--b_run == 0) {
+                    if (b_left == 0) { rsB.z = 0; lb = 0; b_tap = 0; b_chunk = 0; b_run = 0x7fffffff; }
+                    else { lb += 2 * b_tap; b_run = min(per, b_left); b_left -= b_run; }
+                }
+            }
+        }
+    };
     unsigned lbit = 0;
     bool lin = false;
-    auto issue = [&](int st, int part) __attribute__((always_inline)) {
+    auto issue = [&](int st, int u, int part) __attribute__((always_inline)) {
+        if constexpr (ROW) { issue_row(st, u % 3, part); return; }
         unsigned char* sp = lds + st * STAGE + wave * 1024;
         if (part == 0 && !UNI) {
             lin = l_t < ntap;
@@ -284,14 +367,29 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     const int wm = wave / WGN, wn = wave - wm * WGN;
     // operand addresses: row lane % 32 of the wavefront's part, chunk 2*ks + lane/32 of the K tile
     const int rl = lane & 31, kh_ = lane >> 5;
-    const unsigned char *opA[4], *opB[4];        // of the first stage; stages and rows further on are constants beside them
+    const unsigned char *opA[4], *opB[4];    // of the first stage; stages and rows further on are constants beside them
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
         const unsigned x = (unsigned)(((ks * 2 + kh_) ^ ((lane >> 1) & 7)) << 4);
         opA[ks] = lds + (unsigned)(wm * WTM + rl) * 128u + x;
-        opB[ks] = lds + (BT ? (unsigned)(A_BYTES + (wn * WTN + rl) * 4 + kh_ * 16 * BN) : (unsigned)(A_BYTES + (wn * WTN + rl) * 128) + x);
+        opB[ks] = lds + (ROW ? (unsigned)(B_AT + (wn * WTN + rl) * 128) + x : BT ? (unsigned)(A_BYTES + (wn * WTN + rl) * 4 + kh_ * 16 * BN) : (unsigned)(A_BYTES + (wn * WTN + rl) * 128) + x);
     }
-    int ks_c[KS ? 4 : 1];                    // channel of the lane's chunk ks in the K tile read next
+    // ROW: the lane's pixel of A under each tap of the row, or the last row of the stage, which is never loaded with anything but zeros,
+    // where that tap lies beside the image
+    unsigned opR[3][MI], a_rd = 0;
+    if constexpr (ROW) {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) {
+            const int at = wm * WTM + mi * 32 + rl, row = m0 + at, w = row - div_by(row, p.dWr) * p.Wr;
+#pragma unroll
+            for (int s = 0; s < 3; ++s) {
+                const bool out = s == 0 ? w == 0 : s == 2 ? w == p.Wr - 1 : false;
+                const int r = out ? BM + 7 : at + s;
+                opR[MODE == MODE_FWD ? s : 2 - s][mi] = (unsigned)(r * 128 + ((kh_ ^ ((r >> 1) & 7)) << 4));
+            }
+        }
+    }
+    int ks_c[KS ? 4 : 1];                  // channel of the lane's chunk ks in the K tile read next
 #pragma unroll
     for (int ks = 0; ks < (KS ? 4 : 0); ++ks) ks_c[ks] = (kt0 * kt_ch + (ks * 2 + kh_) * 4) % p.Ci;
     const int ks_step = KS ? kt_ch % p.Ci : 0;
@@ -307,11 +405,14 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     // registers: 64 -> 24 channels at 72 x 36 x 35, stride 2, 66.7 / 70.2.
     constexpr bool TWO = ES == 4 ? BT != BT_NONE && UNI : !(BM == 128 && BN == 128 && WGN == 4);
     struct Frag { uint4 a[4][MI], b[4][NI]; };
-    auto read = [&](Frag& f, int st, int ks) __attribute__((always_inline)) {
+    // (tile u: its place in the filter row, where that counts)
+    auto read = [&](Frag& f, int st, int u, int ks) __attribute__((always_inline)) {
         const int o = st * STAGE;
         {
+            if (ROW && ks == 0 && u % 3 == 0 && u > 0) a_rd = a_rd == (NSTA - 1) * A_BYTES ? 0u : a_rd + A_BYTES;
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi) f.a[ks][mi] = *reinterpret_cast<const uint4*>(opA[ks] + o + mi * 4096);
+            for (int mi = 0; mi < MI; ++mi)
+                f.a[ks][mi] = *reinterpret_cast<const uint4*>(ROW ? lds + ((opR[u % 3][mi] + a_rd) ^ (unsigned)(ks << 5)) : opA[ks] + o + mi * 4096);
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) {
                 if (BT) {
@@ -333,25 +434,23 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
         }
     };
     auto multiply = [&](const Frag& f, int ks) __attribute__((always_inline)) {
-        {
-            if constexpr (ES == 2) {
+        if constexpr (ES == 2) {
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni)
+                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.b[ks][ni]), __builtin_bit_cast(bf16x8, f.a[ks][mi]), acc[mi][ni], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
 #pragma unroll
                 for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-                    for (int ni = 0; ni < NI; ++ni)
-                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.b[ks][ni]), __builtin_bit_cast(bf16x8, f.a[ks][mi]), acc[mi][ni], 0, 0, 0);
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-                        for (int ni = 0; ni < NI; ++ni) {
-                            const unsigned a = j == 0 ? f.a[ks][mi].x : j == 1 ? f.a[ks][mi].y : j == 2 ? f.a[ks][mi].z : f.a[ks][mi].w;
-                            const unsigned b = j == 0 ? f.b[ks][ni].x : j == 1 ? f.b[ks][ni].y : j == 2 ? f.b[ks][ni].z : f.b[ks][ni].w;
-                            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(b), __uint_as_float(a), acc[mi][ni], 0, 0, 0);
-                        }
-            }
+                    for (int ni = 0; ni < NI; ++ni) {
+                        const unsigned a = j == 0 ? f.a[ks][mi].x : j == 1 ? f.a[ks][mi].y : j == 2 ? f.a[ks][mi].z : f.a[ks][mi].w;
+                        const unsigned b = j == 0 ? f.b[ks][ni].x : j == 1 ? f.b[ks][ni].y : j == 2 ? f.b[ks][ni].z : f.b[ks][ni].w;
+                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(b), __uint_as_float(a), acc[mi][ni], 0, 0, 0);
+                    }
         }
     };
     // A tile has landed once only the loads of the tiles behind it are outstanding.  DRAIN: the stage of the tile being multiplied
@@ -376,53 +475,57 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     const bool early = Ep::R <= EARLY_ROWS && p.splits == 1;
     if (early) ep.load(p, er0, ec0, rows, lane, Hc, Wc, ph, pw, Dc, pd);
     if (nk > 0) {
+        if constexpr (ROW) {
+            static_assert(!ROW || DRAIN, "A's ring is as long as that takes");
+#pragma unroll
+            for (int q = 0; q < 8; ++q) issue(-1, 1 + q / 4, q % 4);
+        }
 #pragma unroll
         for (int i = 0; i < AHEAD - 1; ++i)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) issue(i, q);
+            for (int q = 0; q < 4; ++q) issue(i, i, q);
         Frag f0;
         meet();
 #pragma unroll
-        for (int q = 0; q < 4; ++q) issue(AHEAD - 1, q);
+        for (int q = 0; q < 4; ++q) issue(AHEAD - 1, AHEAD - 1, q);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) read(f0, 0, ks);
+        for (int ks = 0; ks < 4; ++ks) read(f0, 0, 0, ks);
         // The stages of a tile are constants: the loop goes round the ring (twice, where that has an odd number of stages and the
         // registers two sets) and leaves it behind the last tile.
         // A quarter of the next tile's reads and of the loads behind it go with a quarter of this one's products: the LDS,
         // the address arithmetic and the matrix cores work side by side (all reads first, and the products would wait
         // for the LDS queue to drain; all loads first, and the matrix cores would idle meanwhile).
-        constexpr int ROUND = TWO && NST % 2 ? 2 * NST : NST;
+        // (ROW: and as often as makes whole filter rows.)
+        constexpr int ROUND0 = TWO && NST % 2 ? 2 * NST : NST, ROUND = ROW && ROUND0 % 3 ? 3 * ROUND0 : ROUND0;
         Frag f1;
-        for (int it = 0;;) {
-            bool more = true;
+        int it = 0;
+        auto step = [&](auto index) __attribute__((always_inline)) {        // false: that was the last tile
+            constexpr int u = decltype(index)::value, st = u % NST, st1 = (u + 1) % NST, ld = DRAIN ? st : (u + NST - 1) % NST;
+            Frag &cur = TWO && (u & 1) ? f1 : f0, &nxt = TWO && !(u & 1) ? f1 : f0;
+            meet();
+            if constexpr (TWO) {
+                read(nxt, st1, u + 1, 0);
 #pragma unroll
-            for (int u = 0; u < ROUND && more; ++u) {
-                const int st = u % NST, st1 = (u + 1) % NST, ld = DRAIN ? st : (u + NST - 1) % NST;
-                Frag &cur = TWO && (u & 1) ? f1 : f0, &nxt = TWO && !(u & 1) ? f1 : f0;
-                meet();
-                if constexpr (TWO) {
-                    read(nxt, st1, 0);
-#pragma unroll
-                    for (int ks = 0; ks < 4; ++ks) {
-                        __builtin_amdgcn_sched_barrier(0);
-                        if (ks < 3) read(nxt, st1, ks + 1);
-                        multiply(cur, ks);
-                        issue(ld, ks);
-                    }
-                } else {
-#pragma unroll
-                    for (int ks = 0; ks < 4; ++ks) {     // (the next tile's operands over those just multiplied)
-                        multiply(cur, ks);
-                        read(cur, st1, ks);
-                        issue(ld, ks);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
+                for (int q = 0; q < 4; ++q) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (q < 3) read(nxt, st1, u + 1, q + 1);
+                    multiply(cur, q);
+                    issue(ld, u + AHEAD, q);
                 }
-                __builtin_amdgcn_sched_barrier(0);
-                more = ++it < nk;
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {     // (the next tile's operands over those just multiplied)
+                    multiply(cur, q);
+                    read(cur, st1, u + 1, q);
+                    issue(ld, u + AHEAD, q);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
-            if (!more) break;
-        }
+            __builtin_amdgcn_sched_barrier(0);
+            ++it;
+            return (ROW && u % 3 != 2) || it < nk;       // (whole filter rows)
+        };
+        while (round_of(step, std::make_integer_sequence<int, ROUND>{})) {}
         LPM_WAIT_VM(0);
     }
     __syncthreads();                            // the stages are dead: the epilogue takes them
@@ -511,9 +614,9 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     }
 }
 
-template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, bool UNI, int BT, int OCC>
+template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, int KIND, int BT, int OCC>
 __global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmArgs p) {
-    igemm_block<E, BM, BN, WGM, WGN, NST, MODE, UNI, BT>(p, blockIdx.x, gridDim.x, blockIdx.z);
+    igemm_block<E, BM, BN, WGM, WGN, NST, MODE, KIND, BT>(p, blockIdx.x, gridDim.x, blockIdx.z);
 }
 
 // Two contractions that do not read each other's results, in one launch (64x64 tiles): the blocks of the first, then those of
@@ -522,9 +625,9 @@ struct IgemmPair { IgemmArgs p[2]; FastDiv tiles_d[2]; int tiles[2]; int second;
 template <typename E, int NST, int MODE0, int MODE1, bool UNI, int BT>
 __global__ void __launch_bounds__(256, 2) igemm_pair(const IgemmPair g) {
     const int k = (int)blockIdx.x >= g.second, b = (int)blockIdx.x - (k ? g.second : 0), z = div_by(b, g.tiles_d[k]);
-    if constexpr (MODE0 == MODE1) igemm_block<E, 64, 64, 2, 2, NST, MODE0, UNI, BT>(g.p[k], b - z * g.tiles[k], g.tiles[k], z);
-    else if (k == 0) igemm_block<E, 64, 64, 2, 2, NST, MODE0, UNI, BT>(g.p[0], b - z * g.tiles[0], g.tiles[0], z);
-    else igemm_block<E, 64, 64, 2, 2, NST, MODE1, UNI, BT>(g.p[1], b - z * g.tiles[1], g.tiles[1], z);
+    if constexpr (MODE0 == MODE1) igemm_block<E, 64, 64, 2, 2, NST, MODE0, UNI ? KT_TAP : KT_CHUNKS, BT>(g.p[k], b - z * g.tiles[k], g.tiles[k], z);
+    else if (k == 0) igemm_block<E, 64, 64, 2, 2, NST, MODE0, UNI ? KT_TAP : KT_CHUNKS, BT>(g.p[0], b - z * g.tiles[0], g.tiles[0], z);
+    else igemm_block<E, 64, 64, 2, 2, NST, MODE1, UNI ? KT_TAP : KT_CHUNKS, BT>(g.p[1], b - z * g.tiles[1], g.tiles[1], z);
 }
 
 // --------------------------------------------------------------------------------------------------
@@ -537,8 +640,8 @@ enum { TILE_64 = 0, TILE_128x64, TILE_128, TILE_128_DEEP, TILE_256 };
 static const int TILE_M[5] = {64, 128, 128, 128, 256}, TILE_N[5] = {64, 64, 128, 128, 128};
 static int64_t tiles_of(int tile, int64_t M, int N) { return ((M + TILE_M[tile] - 1) / TILE_M[tile]) * ((N + TILE_N[tile] - 1) / TILE_N[tile]); }
 
-// kt: K tiles (of the longest residue class)
-static IgemmPlan plan_igemm(int es, int64_t M, int N, int kt) {
+// kt: K tiles (of the longest residue class); unit: see part_unit
+static IgemmPlan plan_igemm(int es, int64_t M, int N, int kt, int unit) {
     IgemmPlan pl{};
     pl.tile = TILE_64;
     if (es == 2) {
@@ -573,7 +676,7 @@ static IgemmPlan plan_igemm(int es, int64_t M, int N, int kt) {
     const int64_t cap = (M <= 64 ? 1024 : 256) / pl.tiles;
     s = pl.tile == TILE_64 ? (int)std::min<int64_t>(s, std::max<int64_t>(1, cap)) : 1;
     pl.splits = std::max(1, std::min(s, pl.kt_total));
-    pl.kt_per = (pl.kt_total + pl.splits - 1) / pl.splits;
+    pl.kt_per = (pl.kt_total + pl.splits * unit - 1) / (pl.splits * unit) * unit;
     pl.splits = (pl.kt_total + pl.kt_per - 1) / pl.kt_per;
     return pl;
 }
@@ -607,10 +710,15 @@ bool mfma_dgrad_ok(int dtype, const ConvGeom& g) {
            fits(dtype, g, 0, (((int64_t)(g.Kd - 1) * g.Ho + g.Kh - 1) * g.Wo + g.Kw - 1) * g.Cout) && taps_fit(g, g.Cout, es);
 }
 
+// Whether the taps of a filter row can go one after the other, their pixels loaded once (KT_ROW).
+static bool by_rows(int es, int ci, int kw, int stride, int pad) { return es == 2 && ci % 64 == 0 && kw == 3 && stride == 1 && pad == 1; }
+// K tiles that every part of a split reduction has whole
+static int part_unit(int es, int ci, int kw, int stride, int pad) { return by_rows(es, ci, kw, stride, pad) ? 3 : 1; }
+
 static int k_tiles(int64_t taps, int ci, int es) { return (int)((taps * ci * es / 16 + 7) / 8); }
 static IgemmPlan plan_fwd(int dtype, const ConvGeom& g) {
     const int es = dtype == LPM_BF16 ? 2 : 4;
-    return plan_igemm(es, g.rows_out(), g.Cout, k_tiles(g.taps(), g.Cin, es));
+    return plan_igemm(es, g.rows_out(), g.Cout, k_tiles(g.taps(), g.Cin, es), part_unit(es, g.Cin, g.Kw, g.stride, g.pad));
 }
 // taps a residue class of a strided data gradient meets at most
 static IgemmPlan plan_dgrad(int dtype, const ConvGeom& g) {
@@ -619,7 +727,7 @@ static IgemmPlan plan_dgrad(int dtype, const ConvGeom& g) {
     int64_t rows = g.rows_in();
     if (s > 1) rows += 128 * (g.D > 1 ? s * s * s : s * s);          // (every class ends in a ragged tile: up to 63 rows of the 64-row tiles whose
                                                                       // scratch goes by this count; for the choice of a larger tile, an estimate)
-    return plan_igemm(es, rows, g.Cin, k_tiles(taps, g.Cout, es));
+    return plan_igemm(es, rows, g.Cin, k_tiles(taps, g.Cout, es), part_unit(es, g.Cout, g.Kw, s, g.pad));
 }
 bool mfma_dgrad_kscale_ok(const ConvGeom& g) { return g.Cout <= MAX_KSCALE; }
 size_t mfma_fwd_ws_bytes(int dtype, const ConvGeom& g) { return plan_ws(plan_fwd(dtype, g)); }
@@ -632,35 +740,46 @@ bool mfma_fwd_pools(int dtype, const ConvGeom& g) {
     return dtype == LPM_BF16 && mfma_fwd_ok(dtype, g) && !g.is3d() && !(g.Ho & 1) && (g.Wo == 2 || g.Wo == 4 || g.Wo == 8 || g.Wo == 16 || g.Wo == 32) && g.Cout % 8 == 0;
 }
 
-template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, bool UNI, int BT, int OCC>
+template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, int KIND, int BT, int OCC>
 static hipError_t go(const IgemmArgs& a, int64_t tiles, hipStream_t st) {
-    constexpr int stages = NST * (BM + BN) * 128 + (UNI ? 0 : MAX_TAB * 16) + (BT == BT_SCALED ? MAX_KSCALE * 4 : 0);
+    constexpr int rings = KIND == KT_ROW ? row_stages(NST) * (BM + 8) * 128 + NST * BN * 128 + 1024 : NST * (BM + BN) * 128;
+    constexpr int stages = rings + (KIND != KT_CHUNKS ? 0 : MAX_TAB * 16) + (BT == BT_SCALED ? MAX_KSCALE * 4 : 0);
     constexpr int epilogue = BM * WGN * (BN / WGN + 4) * 4, bytes = stages > epilogue ? stages : epilogue;
     static DeviceSet done;
-    const hipError_t attr = allow_lds(igemm_kernel<E, BM, BN, WGM, WGN, NST, MODE, UNI, BT, OCC>, bytes, done);
+    const hipError_t attr = allow_lds(igemm_kernel<E, BM, BN, WGM, WGN, NST, MODE, KIND, BT, OCC>, bytes, done);
     if (attr != hipSuccess) return attr;
-    launch_last(igemm_kernel<E, BM, BN, WGM, WGN, NST, MODE, UNI, BT, OCC>, dim3((unsigned)tiles, 1, a.splits), dim3(WGM * WGN * 64), bytes, st, a);
+    launch_last(igemm_kernel<E, BM, BN, WGM, WGN, NST, MODE, KIND, BT, OCC>, dim3((unsigned)tiles, 1, a.splits), dim3(WGM * WGN * 64), bytes, st, a);
     return hipGetLastError();
 }
 
-template <typename E, int MODE, bool UNI, int BT>
+template <typename E, int MODE, int KIND, int BT>
 static hipError_t go_tile(const IgemmPlan& pl, const IgemmArgs& a, int64_t tiles, hipStream_t st) {
     if constexpr (sizeof(E) == 2) {
-        if (pl.tile == TILE_128x64) return go<E, 128, 64, 2, 2, 3, MODE, UNI, BT, 2>(a, tiles, st);
-        if (pl.tile == TILE_128) return go<E, 128, 128, 2, 4, 2, MODE, UNI, BT, 2>(a, tiles, st);
-        if (pl.tile == TILE_128_DEEP) return go<E, 128, 128, 2, 4, 3, MODE, UNI, BT, 2>(a, tiles, st);
-        if (pl.tile == TILE_256) return go<E, 256, 128, 4, 2, 3, MODE, UNI, BT, 2>(a, tiles, st);
+        if (pl.tile == TILE_128x64) return go<E, 128, 64, 2, 2, 3, MODE, KIND, BT, 2>(a, tiles, st);
+        if (pl.tile == TILE_128_DEEP) return go<E, 128, 128, 2, 4, 3, MODE, KIND, BT, 2>(a, tiles, st);
+        if constexpr (KIND != KT_ROW) {
+            if (pl.tile == TILE_128) return go<E, 128, 128, 2, 4, 2, MODE, KIND, BT, 2>(a, tiles, st);
+            if (pl.tile == TILE_256) return go<E, 256, 128, 4, 2, 3, MODE, KIND, BT, 2>(a, tiles, st);
+        }
     }
     // About one block per CU: nothing but its own loads in flight keeps the memory path busy, four stages (R50 conv4_x at 64 1.81 ->
     // 1.77 ms per step).  More blocks: three, so that three of them, or other streams' kernels, share a CU (VGG-16/224 6.83 against
     // 6.95 ms with four).
-    if (tiles * a.splits <= 320) return go<E, 64, 64, 2, 2, 4, MODE, UNI, BT, 2>(a, tiles, st);
-    return go<E, 64, 64, 2, 2, 3, MODE, UNI, BT, 2>(a, tiles, st);
+    if (tiles * a.splits <= 320) return go<E, 64, 64, 2, 2, 4, MODE, KIND, BT, 2>(a, tiles, st);
+    return go<E, 64, 64, 2, 2, 3, MODE, KIND, BT, 2>(a, tiles, st);
 }
 template <typename E, int MODE, int BT>
 static hipError_t go_uni(const IgemmPlan& pl, const IgemmArgs& a, int64_t tiles, hipStream_t st) {
-    if ((a.Ci * (int)sizeof(E)) % 128 == 0) return go_tile<E, MODE, true, BT>(pl, a, tiles, st);
-    return go_tile<E, MODE, false, BT>(pl, a, tiles, st);
+    // Filter rows: where a tap is one K tile (the order of the sums is the same), and on 64x64 tiles up to 40 K tiles, or 24 a part (per step,
+    // tap by tap / so, in us: R50 conv4_x at 64 1621 / 1590, VGG-16/CIFAR 1800 / 1769, ResNet-18/CIFAR 2706 / 2637; without the split ones VGG-16/CIFAR
+    // 1794, ResNet-18/CIFAR 2683).  With two blocks of 128x128 to a CU the registers do not suffice (4 x 112^2 x 128 20.5 / 23.6).
+    // Larger tiles and longer sums keep their order: 1 % per step at most, and a forward sum in another order moves masks and maxima of the
+    // deep networks that make them.
+    if constexpr (sizeof(E) == 2 && MODE != MODE_DGRAD_S)
+        if (by_rows(2, a.Ci, a.Kw, a.stride, a.pad) && (a.Ci == 64 ? pl.tile != TILE_128 && pl.tile != TILE_256 : pl.tile == TILE_64 && (a.kt_total <= 40 || a.kt_per_split <= 24)))
+            return go_tile<E, MODE, KT_ROW, BT>(pl, a, tiles, st);
+    if ((a.Ci * (int)sizeof(E)) % 128 == 0) return go_tile<E, MODE, KT_TAP, BT>(pl, a, tiles, st);
+    return go_tile<E, MODE, KT_CHUNKS, BT>(pl, a, tiles, st);
 }
 
 hipError_t launch_zero_counts(void* const* heads, int n, hipStream_t st);

@@ -46,6 +46,17 @@ BF16 = [
     G(1, 20, 15, 64, 64, 3, 1, 1),        # filter rows over segments of 8 pixels, the last one 7 wide
     G(1, 20, 13, 72, 40, 3, 1, 1),        # ... 5 wide: single taps
     G3(1, 3, 6, 8, 64, 64, 3, 1, 1),      # ... volume
+    G(3, 5, 1, 64, 40, 3, 1, 1),          # contractions by filter rows: both outer taps beside the image everywhere
+    G(2, 1, 9, 128, 72, 3, 1, 1),         # ... one image row, two K tiles a tap
+    G(2, 7, 2, 64, 128, 3, 1, 1),         # ... two pixels a row
+    G(1, 6, 7, 512, 512, 3, 1, 1),        # ... a reduction whose parts begin in the middle of a filter row's channels
+    G3(2, 3, 5, 6, 128, 64, 3, 1, 1),     # ... volume
+    G(1, 147, 148, 64, 64, 3, 1, 1),      # ... 340 tiles of 64x64: three stages
+    G(3, 127, 128, 64, 64, 3, 1, 1),      # ... 128x64
+    G(2, 107, 109, 64, 200, 3, 1, 1),     # ... 128x128, three stages: forward
+    G(2, 107, 109, 200, 64, 3, 1, 1),     # ... and data gradient
+    G(3, 128, 128, 64, 128, 3, 1, 1),     # (two stages: tap by tap)
+    G(2, 38, 41, 256, 256, 3, 1, 1),      # ... 64x64, four K tiles a tap, unsplit
     G(2, 80, 80, 64, 64, 5, 1, 2),        # single taps, ranges of 20 K tiles: the pixel records in several rounds
     G(5, 64, 64, 256, 256, 3, 1, 1),      # filter rows, ranges of 64 K tiles: records in several rounds, four stages
 ]
