@@ -59,10 +59,11 @@ enum { KT_CHUNKS = 0, KT_TAP = 1, KT_ROW = 2 };
 constexpr int row_stages(int nst) { return (nst + 3) / 3 + 1; }
 
 // Block bx of the gx tiles' blocks, part bz of a split reduction.
-template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, int KIND, int BT>
+template <typename E, int BM, int BN, int WGM, int WGN, int KG, int NST, int MODE, int KIND, int BT>
 __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, const int gx, const int bz) {
-    constexpr int ES = sizeof(E), T = WGM * WGN * 64, RS = T / 8;        // rows a load step covers
+    constexpr int ES = sizeof(E), T = WGM * WGN * KG * 64, RS = T / 8;        // rows a load step covers
     constexpr int WTM = BM / WGM, WTN = BN / WGN, MI = WTM / 32, NI = WTN / 32;
+    constexpr int KSW = 4 / KG;              // KG groups of wavefronts share the K steps of every tile; the first one ends up with the sums
     constexpr bool UNI = KIND != KT_CHUNKS, ROW = KIND == KT_ROW;
     // ROW: the pixels that a filter row of the tile meets, each of them once: one more at either end, whole pieces of eight
     constexpr int A_ROWS = ROW ? BM + 8 : BM, A_N = (A_ROWS + RS - 1) / RS;            // A_N load steps,
@@ -364,15 +365,15 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.f;
 
-    const int wm = wave / WGN, wn = wave - wm * WGN;
+    const int kg = KG == 1 ? 0 : wave / (WGM * WGN), wv = wave - kg * (WGM * WGN), wm = wv / WGN, wn = wv - wm * WGN;
     // operand addresses: row lane % 32 of the wavefront's part, chunk 2*ks + lane/32 of the K tile
     const int rl = lane & 31, kh_ = lane >> 5;
-    const unsigned char *opA[4], *opB[4];    // of the first stage; stages and rows further on are constants beside them
+    const unsigned char *opA[KSW], *opB[KSW];    // of the first stage; stages and rows further on are constants beside them
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-        const unsigned x = (unsigned)(((ks * 2 + kh_) ^ ((lane >> 1) & 7)) << 4);
+    for (int ks = 0; ks < KSW; ++ks) {
+        const unsigned x = (unsigned)((((kg * KSW + ks) * 2 + kh_) ^ ((lane >> 1) & 7)) << 4);
         opA[ks] = lds + (unsigned)(wm * WTM + rl) * 128u + x;
-        opB[ks] = lds + (ROW ? (unsigned)(B_AT + (wn * WTN + rl) * 128) + x : BT ? (unsigned)(A_BYTES + (wn * WTN + rl) * 4 + kh_ * 16 * BN) : (unsigned)(A_BYTES + (wn * WTN + rl) * 128) + x);
+        opB[ks] = lds + (ROW ? (unsigned)(B_AT + (wn * WTN + rl) * 128) + x : BT ? (unsigned)(A_BYTES + (wn * WTN + rl) * 4 + (kg * KSW * 2 + kh_) * 16 * BN) : (unsigned)(A_BYTES + (wn * WTN + rl) * 128) + x);
     }
     // ROW: the lane's pixel of A under each tap of the row, or the last row of the stage, which is never loaded with anything but zeros,
     // where that tap lies beside the image
@@ -385,13 +386,13 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
             for (int s = 0; s < 3; ++s) {
                 const bool out = s == 0 ? w == 0 : s == 2 ? w == p.Wr - 1 : false;
                 const int r = out ? BM + 7 : at + s;
-                opR[MODE == MODE_FWD ? s : 2 - s][mi] = (unsigned)(r * 128 + ((kh_ ^ ((r >> 1) & 7)) << 4));
+                opR[MODE == MODE_FWD ? s : 2 - s][mi] = (unsigned)(r * 128 + ((((kg * KSW) * 2 + kh_) ^ ((r >> 1) & 7)) << 4));
             }
         }
     }
-    int ks_c[KS ? 4 : 1];                  // channel of the lane's chunk ks in the K tile read next
+    int ks_c[KS ? KSW : 1];                  // channel of the lane's chunk ks in the K tile read next
 #pragma unroll
-    for (int ks = 0; ks < (KS ? 4 : 0); ++ks) ks_c[ks] = (kt0 * kt_ch + (ks * 2 + kh_) * 4) % p.Ci;
+    for (int ks = 0; ks < (KS ? KSW : 0); ++ks) ks_c[ks] = (kt0 * kt_ch + ((kg * KSW + ks) * 2 + kh_) * 4) % p.Ci;
     const int ks_step = KS ? kt_ch % p.Ci : 0;
 
     // Operands of one K tile, 16 bytes per lane and step.  While the matrix cores work on one tile the next one is read from LDS,
@@ -404,7 +405,7 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     // alone, a lone layer's 256 -> 256 at 16 x 14^2 loses 1 %).  In chunks across taps the second set costs a third block per CU its
     // registers: 64 -> 24 channels at 72 x 36 x 35, stride 2, 66.7 / 70.2.
     constexpr bool TWO = ES == 4 ? BT != BT_NONE && UNI : !(BM == 128 && BN == 128 && WGN == 4);
-    struct Frag { uint4 a[4][MI], b[4][NI]; };
+    struct Frag { uint4 a[KSW][MI], b[KSW][NI]; };
     // (tile u: its place in the filter row, where that counts)
     auto read = [&](Frag& f, int st, int u, int ks) __attribute__((always_inline)) {
         const int o = st * STAGE;
@@ -433,7 +434,10 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
             }
         }
     };
-    auto multiply = [&](const Frag& f, int ks) __attribute__((always_inline)) {
+    // the products of the wavefront's K steps, each with the first part of a tile that reaches it
+    auto multiply = [&](const Frag& f, int part) __attribute__((always_inline)) {
+        const int ks = part * KSW / 4;
+        if (part * KSW % 4) return;
         if constexpr (ES == 2) {
 #pragma unroll
             for (int mi = 0; mi < MI; ++mi)
@@ -470,10 +474,10 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     typedef Epilogue<E, MI, NI, MODE> Ep;
     Ep ep;
     const int er0 = m0 + wm * WTM, ec0 = n0 + wn * WTN;
-    constexpr bool SPLITS = BM == 64 && BN == 64;      // (the plan splits no other tile)
-    static_assert(!SPLITS || Ep::R <= EARLY_ROWS, "a split tile loads its operands here or with the partial sums");
-    const bool early = Ep::R <= EARLY_ROWS && p.splits == 1;
-    if (early) ep.load(p, er0, ec0, rows, lane, Hc, Wc, ph, pw, Dc, pd);
+    constexpr bool SPLITS = BM == 64 && BN == 64 && KG == 1;      // (the plan splits no other tile)
+    static_assert(!(SPLITS || KG > 1) || Ep::R <= EARLY_ROWS, "a split tile loads its operands here or with the partial sums");
+    const bool early = Ep::R <= EARLY_ROWS && (!SPLITS || p.splits == 1);
+    if (early && !kg) ep.load(p, er0, ec0, rows, lane, Hc, Wc, ph, pw, Dc, pd);
     if (nk > 0) {
         if constexpr (ROW) {
             static_assert(!ROW || DRAIN, "A's ring is as long as that takes");
@@ -489,7 +493,7 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
 #pragma unroll
         for (int q = 0; q < 4; ++q) issue(AHEAD - 1, AHEAD - 1, q);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) read(f0, 0, 0, ks);
+        for (int ks = 0; ks < KSW; ++ks) read(f0, 0, 0, ks);
         // The stages of a tile are constants: the loop goes round the ring (twice, where that has an odd number of stages and the
         // registers two sets) and leaves it behind the last tile.
         // A quarter of the next tile's reads and of the loads behind it go with a quarter of this one's products: the LDS,
@@ -508,7 +512,7 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     __builtin_amdgcn_sched_barrier(0);
-                    if (q < 3) read(nxt, st1, u + 1, q + 1);
+                    if (q < 3 && (q + 1) * KSW % 4 == 0) read(nxt, st1, u + 1, (q + 1) * KSW / 4);
                     multiply(cur, q);
                     issue(ld, u + AHEAD, q);
                 }
@@ -516,7 +520,7 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {     // (the next tile's operands over those just multiplied)
                     multiply(cur, q);
-                    read(cur, st1, u + 1, q);
+                    if (q * KSW % 4 == 0) read(cur, st1, u + 1, q * KSW / 4);
                     issue(ld, u + AHEAD, q);
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -530,6 +534,30 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     }
     __syncthreads();                            // the stages are dead: the epilogue takes them
 
+    // the other groups hand their sums to the first, which adds them up in order
+    if constexpr (KG > 1) {
+        static_assert(MI * NI == 1, "one accumulator tile per wavefront");
+        float4* ex = reinterpret_cast<float4*>(lds + WGM * WGN * Epilogue<E, MI, NI, MODE>::PIECE * 4) + lane;      // (behind the first group's epilogue areas)
+        if (kg) {
+            float4* d = ex + ((kg - 1) * (WGM * WGN) + wv) * 256;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) d[q * 64] = make_float4(acc[0][0][4 * q], acc[0][0][4 * q + 1], acc[0][0][4 * q + 2], acc[0][0][4 * q + 3]);
+        }
+        __syncthreads();
+        if (kg) return;
+        float4 t[KG - 1][4];
+#pragma unroll
+        for (int g = 0; g < KG - 1; ++g)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) t[g][q] = ex[(g * (WGM * WGN) + wv) * 256 + q * 64];
+#pragma unroll
+        for (int g = 0; g < KG - 1; ++g)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                acc[0][0][4 * q] += t[g][q].x; acc[0][0][4 * q + 1] += t[g][q].y; acc[0][0][4 * q + 2] += t[g][q].z; acc[0][0][4 * q + 3] += t[g][q].w;
+            }
+    }
+
     if constexpr (SPLITS) if (p.splits > 1) {
         // Every block of an output tile stores its partial sums (in accumulator order, 16 bytes per lane), and the one that
         // arrives last adds them in split order and carries on with the epilogue.  Stores and loads of the partials bypass the
@@ -537,7 +565,7 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
         const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(p.part + (size_t)tile * p.splits * (BM * BN), 0, (unsigned)(p.splits * BM * BN * 4), 0x00020000);
         // (rows past the last one lie past the buffer's end: a fully connected layer of 4 samples would exchange 16 times what it
         // needs; VGG-16/224 6644 -> 6625 us per step)
-        const unsigned mine = er0 + rl < rows ? (unsigned)(wave * (MI * NI * 1024) + lane * 4) * 4u : 0xc0000000u;
+        const unsigned mine = er0 + rl < rows ? (unsigned)(wv * (MI * NI * 1024) + lane * 4) * 4u : 0xc0000000u;
         const int me = bz;
         typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 #pragma unroll
@@ -605,7 +633,8 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     ep.store(p, area, er0, ec0, rows, lane, Hc, Wc, ph, pw, Dc, pd);
     if constexpr (MODE == MODE_FWD && ES == 2) if (p.fwd_pool && p.Wr == 32) {
         __syncthreads();
-        if constexpr (MI == 1) {
+        if constexpr (BM < 64) {}
+        else if constexpr (MI == 1) {
             if (!(wm & 1)) ep.pool32(p, area, area + WGN * Ep::PIECE, er0, ec0, rows, lane);
         } else {
 #pragma unroll
@@ -614,9 +643,9 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     }
 }
 
-template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, int KIND, int BT, int OCC>
-__global__ void __launch_bounds__(WGM * WGN * 64, OCC) igemm_kernel(const IgemmArgs p) {
-    igemm_block<E, BM, BN, WGM, WGN, NST, MODE, KIND, BT>(p, blockIdx.x, gridDim.x, blockIdx.z);
+template <typename E, int BM, int BN, int WGM, int WGN, int KG, int NST, int MODE, int KIND, int BT, int OCC>
+__global__ void __launch_bounds__(WGM * WGN * KG * 64, OCC) igemm_kernel(const IgemmArgs p) {
+    igemm_block<E, BM, BN, WGM, WGN, KG, NST, MODE, KIND, BT>(p, blockIdx.x, gridDim.x, blockIdx.z);
 }
 
 // Two contractions that do not read each other's results, in one launch (64x64 tiles): the blocks of the first, then those of
@@ -625,19 +654,20 @@ struct IgemmPair { IgemmArgs p[2]; FastDiv tiles_d[2]; int tiles[2]; int second;
 template <typename E, int NST, int MODE0, int MODE1, bool UNI, int BT>
 __global__ void __launch_bounds__(256, 2) igemm_pair(const IgemmPair g) {
     const int k = (int)blockIdx.x >= g.second, b = (int)blockIdx.x - (k ? g.second : 0), z = div_by(b, g.tiles_d[k]);
-    if constexpr (MODE0 == MODE1) igemm_block<E, 64, 64, 2, 2, NST, MODE0, UNI ? KT_TAP : KT_CHUNKS, BT>(g.p[k], b - z * g.tiles[k], g.tiles[k], z);
-    else if (k == 0) igemm_block<E, 64, 64, 2, 2, NST, MODE0, UNI ? KT_TAP : KT_CHUNKS, BT>(g.p[0], b - z * g.tiles[0], g.tiles[0], z);
-    else igemm_block<E, 64, 64, 2, 2, NST, MODE1, UNI ? KT_TAP : KT_CHUNKS, BT>(g.p[1], b - z * g.tiles[1], g.tiles[1], z);
+    if constexpr (MODE0 == MODE1) igemm_block<E, 64, 64, 2, 2, 1, NST, MODE0, UNI ? KT_TAP : KT_CHUNKS, BT>(g.p[k], b - z * g.tiles[k], g.tiles[k], z);
+    else if (k == 0) igemm_block<E, 64, 64, 2, 2, 1, NST, MODE0, UNI ? KT_TAP : KT_CHUNKS, BT>(g.p[0], b - z * g.tiles[0], g.tiles[0], z);
+    else igemm_block<E, 64, 64, 2, 2, 1, NST, MODE1, UNI ? KT_TAP : KT_CHUNKS, BT>(g.p[1], b - z * g.tiles[1], g.tiles[1], z);
 }
 
 // --------------------------------------------------------------------------------------------------
-struct IgemmPlan { int tile; int splits, kt_total, kt_per; int64_t tiles; };
+struct IgemmPlan { int tile, alone /* tile of a launch of its own */, splits, kt_total, kt_per; int64_t tiles; };
 // Output tiles.  64x64: the launches of a few hundred blocks that small micro-batches make.  128x64, 128x128: half the
 // operand traffic per product once there are enough tiles; 128x128 (eight wavefronts) with three stages where there is about one tile
 // per CU, with two where there are two blocks per CU to hide each other's latencies.  256x128, eight wavefronts of 64x64 each: a
-// quarter less LDS traffic per product, for what fills the card even so.
-enum { TILE_64 = 0, TILE_128x64, TILE_128, TILE_128_DEEP, TILE_256 };
-static const int TILE_M[5] = {64, 128, 128, 128, 256}, TILE_N[5] = {64, 64, 128, 128, 128};
+// quarter less LDS traffic per product, for what fills the card even so.  32x32, 32x64: the wavefronts of a block share the reduction (see
+// plan_igemm).
+enum { TILE_64 = 0, TILE_128x64, TILE_128, TILE_128_DEEP, TILE_256, TILE_32, TILE_32x64 };
+static const int TILE_M[7] = {64, 128, 128, 128, 256, 32, 32}, TILE_N[7] = {64, 64, 128, 128, 128, 32, 64};
 static int64_t tiles_of(int tile, int64_t M, int N) { return ((M + TILE_M[tile] - 1) / TILE_M[tile]) * ((N + TILE_N[tile] - 1) / TILE_N[tile]); }
 
 // kt: K tiles (of the longest residue class); unit: see part_unit
@@ -678,6 +708,22 @@ static IgemmPlan plan_igemm(int es, int64_t M, int N, int kt, int unit) {
     pl.splits = std::max(1, std::min(s, pl.kt_total));
     pl.kt_per = (pl.kt_total + pl.splits * unit - 1) / (pl.splits * unit) * unit;
     pl.splits = (pl.kt_total + pl.kt_per - 1) / pl.kt_per;
+    // Launched by itself, a call whose 64x64 tiles leave CUs idle goes on smaller ones instead whose reduction the wavefronts of the
+    // block share: their sums meet in LDS, which takes 0.4 us where the exchange between blocks takes 3.  Alone, us, in parts / so: bf16 16 x 8^2 x 256
+    // channels 3x3 9.2 / 6.7, 13 x 12^2 x 192 9.0 / 6.4, float 8 x 32^2 x 64 11.5 / 8.2, 8 x 16^2 x 128 11.9 / 8.7, 4 x 32^2 x 64 10.9 / 6.3.
+    // A block reads all of K one tile after the other, and in a network, where the weights come from beyond the L2, up to 40 K tiles take less
+    // than the exchange (32 x 4^2 x 512, 72 of them, 12.5 / 9.5 alone, but ResNet-18/CIFAR 2636 / 2683 us per step); rings of eight and six stages cover
+    // that latency (16 images forward in parts 138.5, with four stages 139.2, with eight 134.6).  Fewer than 120 tiles leave more CUs
+    // idle than the parts would.  bf16 without parts from a dozen K tiles on (16 images forward 136.2 / 133.7).  32x64 tiles fetch half
+    // as many bytes again per product, which the products of float cover; bf16 in two parts on a full card stays (ResNet-18/CIFAR at 32 2719 / 2743).
+    // Per step: float ResNet-18 at 4 / 8 / 16 samples 3026 / 2889, 2420 / 2376, 1705 / 1690, ResNet-18/CIFAR at 8 1991 / 1953, at 16 2135 / 2144
+    // (LOCKED 1677 / 1651), of width 32 1034 / 1014, 48 2166 / 2147, VGG-16/CIFAR at 32 1172 / 1175, bottlenecks 128 wide at 8 655 / 641.
+    pl.alone = pl.tile;
+    if (pl.tile == TILE_64 && pl.kt_total <= 40 && (pl.splits > 1 || (es == 2 && pl.kt_total >= 12))) {
+        const int64_t t32 = tiles_of(TILE_32, M, N), t3264 = tiles_of(TILE_32x64, M, N);
+        if (t32 >= 120 && t32 <= 256) pl.alone = TILE_32;
+        else if (t3264 >= 120 && t3264 <= (es == 4 ? 320 : pl.splits > 1 ? 192 : 256)) pl.alone = TILE_32x64;
+    }
     return pl;
 }
 
@@ -718,7 +764,9 @@ static int part_unit(int es, int ci, int kw, int stride, int pad) { return by_ro
 static int k_tiles(int64_t taps, int ci, int es) { return (int)((taps * ci * es / 16 + 7) / 8); }
 static IgemmPlan plan_fwd(int dtype, const ConvGeom& g) {
     const int es = dtype == LPM_BF16 ? 2 : 4;
-    return plan_igemm(es, g.rows_out(), g.Cout, k_tiles(g.taps(), g.Cin, es), part_unit(es, g.Cin, g.Kw, g.stride, g.pad));
+    IgemmPlan pl = plan_igemm(es, g.rows_out(), g.Cout, k_tiles(g.taps(), g.Cin, es), part_unit(es, g.Cin, g.Kw, g.stride, g.pad));
+    if (es == 2 && g.Wo == 32) pl.alone = pl.tile;      // (pooling windows of 32-wide images take two rows of 32 pixels)
+    return pl;
 }
 // taps a residue class of a strided data gradient meets at most
 static IgemmPlan plan_dgrad(int dtype, const ConvGeom& g) {
@@ -727,7 +775,9 @@ static IgemmPlan plan_dgrad(int dtype, const ConvGeom& g) {
     int64_t rows = g.rows_in();
     if (s > 1) rows += 128 * (g.D > 1 ? s * s * s : s * s);          // (every class ends in a ragged tile: up to 63 rows of the 64-row tiles whose
                                                                       // scratch goes by this count; for the choice of a larger tile, an estimate)
-    return plan_igemm(es, rows, g.Cin, k_tiles(taps, g.Cout, es), part_unit(es, g.Cout, g.Kw, s, g.pad));
+    IgemmPlan pl = plan_igemm(es, rows, g.Cin, k_tiles(taps, g.Cout, es), part_unit(es, g.Cout, g.Kw, s, g.pad));
+    if (s > 1) pl.alone = pl.tile;                                    // (the 32-row kernels know no residue classes)
+    return pl;
 }
 bool mfma_dgrad_kscale_ok(const ConvGeom& g) { return g.Cout <= MAX_KSCALE; }
 size_t mfma_fwd_ws_bytes(int dtype, const ConvGeom& g) { return plan_ws(plan_fwd(dtype, g)); }
@@ -740,43 +790,47 @@ bool mfma_fwd_pools(int dtype, const ConvGeom& g) {
     return dtype == LPM_BF16 && mfma_fwd_ok(dtype, g) && !g.is3d() && !(g.Ho & 1) && (g.Wo == 2 || g.Wo == 4 || g.Wo == 8 || g.Wo == 16 || g.Wo == 32) && g.Cout % 8 == 0;
 }
 
-template <typename E, int BM, int BN, int WGM, int WGN, int NST, int MODE, int KIND, int BT, int OCC>
+template <typename E, int BM, int BN, int WGM, int WGN, int KG, int NST, int MODE, int KIND, int BT, int OCC>
 static hipError_t go(const IgemmArgs& a, int64_t tiles, hipStream_t st) {
     constexpr int rings = KIND == KT_ROW ? row_stages(NST) * (BM + 8) * 128 + NST * BN * 128 + 1024 : NST * (BM + BN) * 128;
     constexpr int stages = rings + (KIND != KT_CHUNKS ? 0 : MAX_TAB * 16) + (BT == BT_SCALED ? MAX_KSCALE * 4 : 0);
-    constexpr int epilogue = BM * WGN * (BN / WGN + 4) * 4, bytes = stages > epilogue ? stages : epilogue;
+    constexpr int epilogue = KG * BM * WGN * (BN / WGN + 4) * 4, bytes = stages > epilogue ? stages : epilogue;
     static DeviceSet done;
-    const hipError_t attr = allow_lds(igemm_kernel<E, BM, BN, WGM, WGN, NST, MODE, KIND, BT, OCC>, bytes, done);
+    const hipError_t attr = allow_lds(igemm_kernel<E, BM, BN, WGM, WGN, KG, NST, MODE, KIND, BT, OCC>, bytes, done);
     if (attr != hipSuccess) return attr;
-    launch_last(igemm_kernel<E, BM, BN, WGM, WGN, NST, MODE, KIND, BT, OCC>, dim3((unsigned)tiles, 1, a.splits), dim3(WGM * WGN * 64), bytes, st, a);
+    launch_last(igemm_kernel<E, BM, BN, WGM, WGN, KG, NST, MODE, KIND, BT, OCC>, dim3((unsigned)tiles, 1, a.splits), dim3(WGM * WGN * KG * 64), bytes, st, a);
     return hipGetLastError();
 }
 
 template <typename E, int MODE, int KIND, int BT>
 static hipError_t go_tile(const IgemmPlan& pl, const IgemmArgs& a, int64_t tiles, hipStream_t st) {
     if constexpr (sizeof(E) == 2) {
-        if (pl.tile == TILE_128x64) return go<E, 128, 64, 2, 2, 3, MODE, KIND, BT, 2>(a, tiles, st);
-        if (pl.tile == TILE_128_DEEP) return go<E, 128, 128, 2, 4, 3, MODE, KIND, BT, 2>(a, tiles, st);
+        if (pl.tile == TILE_128x64) return go<E, 128, 64, 2, 2, 1, 3, MODE, KIND, BT, 2>(a, tiles, st);
+        if (pl.tile == TILE_128_DEEP) return go<E, 128, 128, 2, 4, 1, 3, MODE, KIND, BT, 2>(a, tiles, st);
         if constexpr (KIND != KT_ROW) {
-            if (pl.tile == TILE_128) return go<E, 128, 128, 2, 4, 2, MODE, KIND, BT, 2>(a, tiles, st);
-            if (pl.tile == TILE_256) return go<E, 256, 128, 4, 2, 3, MODE, KIND, BT, 2>(a, tiles, st);
+            if (pl.tile == TILE_128) return go<E, 128, 128, 2, 4, 1, 2, MODE, KIND, BT, 2>(a, tiles, st);
+            if (pl.tile == TILE_256) return go<E, 256, 128, 4, 2, 1, 3, MODE, KIND, BT, 2>(a, tiles, st);
         }
+    }
+    if constexpr (MODE != MODE_DGRAD_S) {
+        if (pl.tile == TILE_32) return go<E, 32, 32, 1, 1, 4, 8, MODE, KIND, BT, 2>(a, tiles, st);
+        if (pl.tile == TILE_32x64) return go<E, 32, 64, 1, 2, 2, 6, MODE, KIND, BT, 2>(a, tiles, st);
     }
     // About one block per CU: nothing but its own loads in flight keeps the memory path busy, four stages (R50 conv4_x at 64 1.81 ->
     // 1.77 ms per step).  More blocks: three, so that three of them, or other streams' kernels, share a CU (VGG-16/224 6.83 against
     // 6.95 ms with four).
-    if (tiles * a.splits <= 320) return go<E, 64, 64, 2, 2, 4, MODE, KIND, BT, 2>(a, tiles, st);
-    return go<E, 64, 64, 2, 2, 3, MODE, KIND, BT, 2>(a, tiles, st);
+    if (tiles * a.splits <= 320) return go<E, 64, 64, 2, 2, 1, 4, MODE, KIND, BT, 2>(a, tiles, st);
+    return go<E, 64, 64, 2, 2, 1, 3, MODE, KIND, BT, 2>(a, tiles, st);
 }
 template <typename E, int MODE, int BT>
 static hipError_t go_uni(const IgemmPlan& pl, const IgemmArgs& a, int64_t tiles, hipStream_t st) {
-    // Filter rows: where a tap is one K tile (the order of the sums is the same), and on 64x64 tiles up to 40 K tiles, or 24 a part (per step,
+    // Filter rows: where a tap is one K tile (the order of the sums is the same), and on 64x64 and 32-row tiles up to 40 K tiles, or 24 a part (per step,
     // tap by tap / so, in us: R50 conv4_x at 64 1621 / 1590, VGG-16/CIFAR 1800 / 1769, ResNet-18/CIFAR 2706 / 2637; without the split ones VGG-16/CIFAR
     // 1794, ResNet-18/CIFAR 2683).  With two blocks of 128x128 to a CU the registers do not suffice (4 x 112^2 x 128 20.5 / 23.6).
     // Larger tiles and longer sums keep their order: 1 % per step at most, and a forward sum in another order moves masks and maxima of the
     // deep networks that make them.
     if constexpr (sizeof(E) == 2 && MODE != MODE_DGRAD_S)
-        if (by_rows(2, a.Ci, a.Kw, a.stride, a.pad) && (a.Ci == 64 ? pl.tile != TILE_128 && pl.tile != TILE_256 : pl.tile == TILE_64 && (a.kt_total <= 40 || a.kt_per_split <= 24)))
+        if (by_rows(2, a.Ci, a.Kw, a.stride, a.pad) && (a.Ci == 64 ? pl.tile != TILE_128 && pl.tile != TILE_256 : TILE_M[pl.tile] <= 64 && (a.kt_total <= 40 || a.kt_per_split <= 24)))
             return go_tile<E, MODE, KT_ROW, BT>(pl, a, tiles, st);
     if ((a.Ci * (int)sizeof(E)) % 128 == 0) return go_tile<E, MODE, KT_TAP, BT>(pl, a, tiles, st);
     return go_tile<E, MODE, KT_CHUNKS, BT>(pl, a, tiles, st);
@@ -808,8 +862,14 @@ static void lay_tiles(IgemmCall& c) {
     c.tiles = mt * nt;
 }
 
-static hipError_t go_call(const IgemmCall& c, hipStream_t st) {
-    const IgemmArgs& a = c.a;
+static hipError_t go_call(IgemmCall c, hipStream_t st) {
+    IgemmArgs& a = c.a;
+    if (c.pl.alone != c.pl.tile) {
+        c.pl.tile = c.pl.alone;
+        c.pl.splits = a.splits = 1;
+        c.pl.kt_per = a.kt_per_split = c.pl.kt_total;
+        lay_tiles(c);
+    }
     const bool bf = c.dtype == LPM_BF16;
     if (c.mode == MODE_FWD) return bf ? go_uni<bf16_t, MODE_FWD, BT_NONE>(c.pl, a, c.tiles, st) : go_uni<float, MODE_FWD, BT_NONE>(c.pl, a, c.tiles, st);
     if (c.mode == MODE_UNPOOL) return go_uni<bf16_t, MODE_UNPOOL, BT_NONE>(c.pl, a, c.tiles, st);
@@ -886,7 +946,7 @@ static hipError_t run_igemm(int dtype, int mode, const IgemmArgs& args, const Ig
         a.count = (unsigned*)ws;
         a.part = (float*)((char*)ws + LPM_COUNT_BYTES);
         if (c.tiles > (int64_t)(LPM_COUNT_BYTES / 4) || c.tiles > pl.tiles) return hipErrorInvalidValue;      // (the plan's cap keeps this out)
-        if (!ws_zeroed) {
+        if (!ws_zeroed && (pl.alone == pl.tile || hold || with)) {
             const hipError_t e = launch_zero_counts(&ws, 1, st);
             if (e != hipSuccess) return e;
         }

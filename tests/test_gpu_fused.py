@@ -54,6 +54,15 @@ def test_pooling_backward_on_larger_tiles(lpm, m, c, h):
     stage_backward_isolated(lpm, layers, [0, 3], m, m, 1, seed=31, dx_wanted=True, check_forward=True, grad_std=1.0)
 
 
+# pooling behind and in front of a contraction on 32-row tiles, whose wavefronts share the reduction
+@pytest.mark.parametrize("m,layers", [(4, (C(192, 128, 3, 3, 16, 16, p=1, scale=True), P(128, 16, 16), C(128, 16, 1, 1, 8, 8))),
+                                      (2, (C(8, 256, 1, 1, 32, 32), P(256, 32, 32), C(256, 192, 3, 3, 16, 16, p=1, scale=True)))], ids=["forward", "backward"])
+def test_pooling_on_tiles_of_32_rows(lpm, m, layers):
+    layers = chain(*[dict(l) for l in layers])
+    print("m", m, "layers", [(l["cin"], l["cout"]) for l in layers], flush=True)
+    stage_backward_isolated(lpm, layers, [0, 3], m, m, 1, seed=33, dx_wanted=True, check_forward=True, grad_std=1.0)
+
+
 # forward pooling of images 32 wide, whose windows span two pieces of a tile: on every tile, split, in ragged channels, one row of windows
 @pytest.mark.parametrize("m,cin,c,h", [(2, 16, 24, 32), (1, 256, 64, 32), (3, 64, 72, 2), (24, 16, 64, 32), (24, 16, 128, 32), (24, 32, 256, 32), (24, 96, 256, 32)],
                          ids=["ragged", "split", "one_row", "tile128x64", "tile128", "large", "tile256"])
@@ -161,6 +170,11 @@ NETS = {
     "tile128": (bottlenecks(256, 16, 111, 2, ["in", "in"]), "bf16"),
     "tile256": ((chain(C(200, 200, 1, 1, 107, 109, scale=True), C(200, 88, 3, 3, 107, 109, p=1), C(88, 200, 1, 1, 107, 109, scale=True, add=0),
                        C(200, 88, 3, 3, 107, 109, p=1)), 2), "bf16"),
+    # ... where the wavefronts of a block share the reduction
+    "tile32": (down(192, 64, 16, 3), "bf16"),
+    "tile32x64": (down(192, 64, 23, 3), "bf16"),
+    "tile32_float": (down(64, 32, 27, 3), "f32"),
+    "tile32x64_float": (down(64, 32, 38, 3), "f32"),
     "projected128": (projected(16, 128, 16, 108, 2), "bf16"),
     # the same in float, where a block's scale enters through the weights of its data gradient: channels in whole K tiles, in chunks of
     # 16 bytes, and gathered one by one
