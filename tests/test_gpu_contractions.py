@@ -57,25 +57,27 @@ BF16 = [
     G(2, 107, 109, 200, 64, 3, 1, 1),     # ... and data gradient
     G(3, 128, 128, 64, 128, 3, 1, 1),     # (two stages: tap by tap)
     G(2, 38, 41, 256, 256, 3, 1, 1),      # ... 64x64, four K tiles a tap, unsplit
-    G(1, 30, 31, 192, 232, 3, 1, 1),      # a block's wavefronts share the reduction: tiles of 32x32, forward, data gradient,
-    G(1, 30, 31, 232, 192, 3, 1, 1),
-    G(1, 30, 31, 200, 232, 3, 1, 1),      # ... chunks across taps
-    G(1, 30, 31, 1600, 232, 1, 1, 0),     # ... one tap
-    G(1, 30, 31, 96, 232, 3, 1, 1),       # ... that would not be split either
-    G(1, 60, 62, 192, 232, 3, 2, 1),      # ... stride 2
-    G(1, 26, 50, 192, 320, 3, 1, 1),      # ... of 32x64
-    G(1, 26, 50, 320, 192, 3, 1, 1),
-    G(1, 26, 50, 200, 328, 3, 1, 1),
+    G(1, 16, 31, 192, 232, 3, 1, 1),      # a block's wavefronts share the reduction: tiles of 32x32, forward, data gradient,
+    G(1, 16, 31, 232, 192, 3, 1, 1),
+    G(1, 16, 31, 200, 232, 3, 1, 1),      # ... chunks across taps
+    G(1, 16, 31, 1600, 232, 1, 1, 0),     # ... one tap
+    G(1, 16, 31, 96, 232, 3, 1, 1),       # ... that would not be split either
+    G(1, 32, 62, 192, 232, 3, 2, 1),      # ... stride 2
+    G(1, 10, 101, 192, 264, 3, 1, 1),     # ... of 32x64
+    G(1, 10, 101, 264, 192, 3, 1, 1),
+    G(1, 10, 101, 200, 264, 3, 1, 1),
+    G(1, 10, 101, 264, 200, 3, 1, 1),
     G(2, 80, 80, 64, 64, 5, 1, 2),        # single taps, ranges of 20 K tiles: the pixel records in several rounds
     G(5, 64, 64, 256, 256, 3, 1, 1),      # filter rows, ranges of 64 K tiles: records in several rounds, four stages
 ]
 F32 = [                                   # data gradients of one, three and (strided, by residue class) one to four K tiles
-    G(1, 30, 31, 64, 232, 3, 1, 1),       # a block's wavefronts share the reduction: tiles of 32x32
-    G(1, 30, 31, 232, 64, 3, 1, 1),
-    G(1, 30, 31, 36, 232, 5, 1, 2),
-    G(1, 26, 50, 64, 320, 3, 1, 1),       # ... of 32x64
-    G(1, 26, 50, 320, 64, 3, 1, 1),
-    G(1, 26, 50, 36, 320, 5, 1, 2),
+    G(1, 16, 31, 64, 232, 3, 1, 1),       # a block's wavefronts share the reduction: tiles of 32x32
+    G(1, 16, 31, 232, 64, 3, 1, 1),
+    G(1, 16, 31, 36, 232, 5, 1, 2),
+    G(1, 16, 31, 232, 36, 5, 1, 2),
+    G(1, 10, 101, 64, 264, 3, 1, 1),      # ... of 32x64
+    G(1, 10, 101, 264, 64, 3, 1, 1),
+    G(1, 10, 101, 36, 264, 5, 1, 2),
     G(2, 105, 107, 40, 32, 1, 1, 0),      # more blocks than the card has CUs: three stages
     G(2, 105, 107, 36, 96, 1, 1, 0),
     G(2, 105, 107, 64, 32, 3, 2, 1),
