@@ -61,6 +61,10 @@ __device__ __forceinline__ int div_by(int n, const FastDiv& f) { return (int)(__
 
 __device__ __forceinline__ float ld(const float* p, int64_t i) { return p[i]; }
 __device__ __forceinline__ float ld(const bf16_t* p, int64_t i) { return bf2f(p[i].bits); }
+// the value as it is stored
+template <typename T> __device__ __forceinline__ T to_store(float v);
+template <> __device__ __forceinline__ float to_store<float>(float v) { return v; }
+template <> __device__ __forceinline__ bf16_t to_store<bf16_t>(float v) { return {f2bf(v)}; }
 __device__ __forceinline__ void st(float* p, int64_t i, float v) { p[i] = v; }
 __device__ __forceinline__ void st(bf16_t* p, int64_t i, float v) { p[i].bits = f2bf(v); }
 

@@ -272,13 +272,24 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
         lr.pool_fwd = i + 1;
         s->Ly(i + 1).pooled_fwd = true;
     }
+    // The head: an average pooling whose only reader is a plain layer over its channels.
+    for (int32_t i = first; i + 1 < last; ++i) {
+        if (s->net[(size_t)i].kind != LPM_GAP || i == s->t_out) continue;
+        LayerRt& fc = s->Ly(i + 1);
+        int n_src, n_add;
+        uses(i, n_src, n_add);
+        if (n_src != 1 || n_add != 0 || !has_weights(fc.d) || fc.d.src != i || (fc.d.flags & (LPM_RELU | LPM_SCALE)) || fc.d.add_src != LPM_NONE) continue;
+        if (fc.g.K() != fc.g.Cin || fc.g.rows_out() != microbatch || !head_ok(dtype, s->net[(size_t)i].h_in * s->net[(size_t)i].w_in, fc.g.Cin, fc.g.Cout)) continue;
+        s->Ly(i).head = i + 1;
+        fc.headed = true;
+    }
     // A projection and the layer of the block that stands beside it do not read each other's results: forward, the projection
     // and the layer before it; backward, where the projection's dz is there with that of the layer that adds it, those two.
     // Small contractions share a launch then.
     for (int32_t i = first; i + 1 < last; ++i) {
         LayerRt& lr = s->Ly(i);
         LayerRt& nx = s->Ly(i + 1);
-        if (!has_weights(lr.d) || !has_weights(nx.d) || nx.d.src == i) continue;
+        if (!has_weights(lr.d) || !has_weights(nx.d) || nx.d.src == i || lr.headed) continue;
         lr.hold_fwd = nx.d.add_src != i && lr.pool_fwd < 0;
         int n_src, n_add;
         uses(i, n_src, n_add);
@@ -535,6 +546,7 @@ int32_t lpm_stage_forward_on(lpm_stage* s, const void* x, void* y, const int32_t
         switch (l.kind) {
             case LPM_CONV:
             case LPM_FC: {
+                if (lr.headed) break;            // done with the pooling it reads
                 const void* w = s->dtype == LPM_BF16 ? (const void*)((const char*)lowp + lr.lowp_w_off)
                                                      : (const void*)(params + lr.w_off);
                 const float* sc = lr.s_off != NO ? params + lr.s_off : nullptr;
@@ -550,6 +562,13 @@ int32_t lpm_stage_forward_on(lpm_stage* s, const void* x, void* y, const int32_t
                 LPM_HIP(launch_maxpool_fwd(s->dtype, s->m, l.h_in, l.w_in, l.cin, in, outp, st));
                 break;
             case LPM_GAP:
+                if (lr.head >= 0) {
+                    const LayerRt& fc = s->Ly(lr.head);
+                    LPM_HIP(launch_head_fwd(s->dtype, s->m, l.h_in * l.w_in, l.cin, fc.g.Cout, in, outp,
+                                            s->dtype == LPM_BF16 ? (const void*)((const char*)lowp + fc.lowp_w_off) : (const void*)(params + fc.w_off),
+                                            fc.b_off != NO ? params + fc.b_off : nullptr, const_cast<void*>(tptr(s, lr.head, x, y, stash)), st));
+                    break;
+                }
                 LPM_HIP(launch_gap_fwd(s->dtype, s->m, l.h_in * l.w_in, l.cin, in, outp, st));
                 break;
             case LPM_ATTN:
@@ -701,6 +720,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
         return hipSuccess;
     };
     HeldCall held;                         // a data gradient that waits for the next layer's
+    const void* head_dz = nullptr;         // the dz of a headed layer, for the pooling below it
     std::vector<hipGraphNode_t> wtail;     // capture: frontier left by the last weight gradient
     auto frontier = [&](std::vector<hipGraphNode_t>& out) -> hipError_t {
         hipStreamCaptureStatus stt;
@@ -872,6 +892,8 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                     if (lr.unpool_of >= 0) {
                         if (do_data && unpool.dst) LPM_HIP(launch_conv_dgrad(s->dtype, lr.g, dz, w, wt, nullptr, 0, nullptr, nullptr, counts, st, &unpool,
                                                                              nullptr, lr.dz_unscaled ? sc : nullptr, true));
+                    } else if (lr.headed) {
+                        head_dz = dz;            // (the pooling's kernel goes on from there)
                     } else if (do_data) {
                         const bool hold = lr.hold_bwd && i > first && (s->Ly(i - 1).d.src >= first || dx);
                         LPM_HIP(launch_conv_dgrad(s->dtype, lr.g, dz, w, wt, gsrc, gsrc_acc, gmask, gmscale, counts, st, nullptr,
@@ -908,7 +930,12 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                     if (do_data && l.kind == LPM_MAXPOOL2)
                         LPM_HIP(launch_maxpool_bwd(s->dtype, s->m, l.h_in, l.w_in, l.cin, tptr(s, l.src, x, y, stash),
                                                    tptr(s, i, x, y, stash), g, gsrc, gsrc_acc, gmask != nullptr, gmscale, st));
-                    else if (do_data)
+                    else if (do_data && lr.head >= 0) {
+                        const LayerRt& fc = s->Ly(lr.head);
+                        LPM_HIP(launch_head_bwd(s->dtype, s->m, l.h_in * l.w_in, l.cin, fc.g.Cout, head_dz,
+                                                s->dtype == LPM_BF16 ? (const void*)((const char*)lowp + fc.lowp_w_off) : (const void*)(params + fc.w_off),
+                                                gsrc, gsrc_acc, gmask, gmscale, st));
+                    } else if (do_data)
                         LPM_HIP(launch_gap_bwd(s->dtype, s->m, l.h_in * l.w_in, l.cin, g, gsrc, gsrc_acc, gmask, gmscale, st));
                     LPM_HIP(stop.finish());
                     at_point = ev;

@@ -84,6 +84,17 @@ def test_pooling_forward_of_gathered_layers(lpm, m, cin, c, k, p, h, w, dtype):
     stage_backward_isolated(lpm, layers, [0, 3], m, m, dtype, seed=29, dx_wanted=False, check_forward=True, grad_std=1.0)
 
 
+# average pooling and the layer over its channels in one kernel: channels that fill no block and several, one output and the most, positions that
+# are no multiple of the threads' share; a layer of more outputs, which has kernels of its own
+@pytest.mark.parametrize("m,c,n,h,w", [(3, 24, 10, 3, 5), (2, 512, 100, 4, 4), (2, 1032, 1, 2, 3), (1, 64, 128, 1, 1), (2, 64, 136, 4, 4)], ids=lambda v: str(v))
+@pytest.mark.parametrize("dtype", [0, 1], ids=["f32", "bf16"])
+def test_head(lpm, m, c, n, h, w, dtype):
+    gap = dict(kind="gap", cin=c, cout=c, kh=h, kw=w, stride=1, pad=0, h_in=h, w_in=w, relu=False, bias=False, scale=False, src=None, add_src=None, cut_after=False)
+    layers = chain(C(8, c, 1, 1, h, w, scale=True), gap, C(c, n, 1, 1, 1, 1, relu=False))
+    print("m", m, "channels", c, "outputs", n, "image", h, w, "dtype", dtype, flush=True)
+    stage_backward_isolated(lpm, layers, [0, 3], m, m, dtype, seed=35, dx_wanted=True, check_forward=True, grad_std=1.0)
+
+
 def bottlenecks(w, mid, h, m, shortcuts, first_scale=True):
     """Stem, then blocks 1x1 reduce - 1x1 expand + shortcut, then one more reduction that keeps the last block inside the stage.
     shortcuts: the tensor each block adds ('x': the block's input, 'in': the stage's)."""
