@@ -714,7 +714,7 @@ template <typename T, int V>
 __global__ void __launch_bounds__(256) head_bwd_kernel(int HW, int C, int N, const T* __restrict__ dz, const T* __restrict__ w, T* __restrict__ dx,
                                                        int accumulate, const T* __restrict__ mask, const float* __restrict__ mscale) {
     __shared__ __attribute__((aligned(16))) float red[16][16 * V];
-    const int cx = threadIdx.x & 15, ty = threadIdx.x >> 4, c0 = (blockIdx.x * 16 + cx) * V, n0 = blockIdx.y;
+    const int cx = threadIdx.x & 15, ty = threadIdx.x >> 4, c0 = (blockIdx.y * 16 + cx) * V, n0 = blockIdx.x;
     const bool ok = c0 < C;
     float g[V];
 #pragma unroll
@@ -782,14 +782,11 @@ hipError_t launch_head_fwd(int dtype, int32_t m, int32_t HW, int32_t C, int32_t 
 }
 hipError_t launch_head_bwd(int dtype, int32_t m, int32_t HW, int32_t C, int32_t N, const void* dz, const void* w, void* dx, int accumulate, const void* mask,
                            const float* mscale, hipStream_t s) {
-    for (int n0 = 0; n0 < m; n0 += 32768) {          // (the grid's second extent is limited)
-        const int64_t a = (int64_t)n0 * N, b = (int64_t)n0 * HW * C;
-        const dim3 grid((unsigned)((C / (dtype == LPM_BF16 ? 8 : 4) + 15) / 16), (unsigned)std::min(m - n0, 32768));
-        if (dtype == LPM_BF16) launch_last(head_bwd_kernel<bf16_t, 8>, grid, dim3(256), 0, s, HW, C, N, (const bf16_t*)dz + a, (const bf16_t*)w, (bf16_t*)dx + b, accumulate,
-                                           mask ? (const bf16_t*)mask + b : nullptr, mscale);
-        else launch_last(head_bwd_kernel<float, 4>, grid, dim3(256), 0, s, HW, C, N, (const float*)dz + a, (const float*)w, (float*)dx + b, accumulate,
-                         mask ? (const float*)mask + b : nullptr, mscale);
-    }
+    // (samples on the grid's first extent, which has room for them: one launch, so that a stop event stands behind all of them)
+    const dim3 grid((unsigned)m, (unsigned)((C / (dtype == LPM_BF16 ? 8 : 4) + 15) / 16));
+    if (dtype == LPM_BF16) launch_last(head_bwd_kernel<bf16_t, 8>, grid, dim3(256), 0, s, HW, C, N, (const bf16_t*)dz, (const bf16_t*)w, (bf16_t*)dx, accumulate,
+                                       (const bf16_t*)mask, mscale);
+    else launch_last(head_bwd_kernel<float, 4>, grid, dim3(256), 0, s, HW, C, N, (const float*)dz, (const float*)w, (float*)dx, accumulate, (const float*)mask, mscale);
     return hipGetLastError();
 }
 

@@ -26,7 +26,8 @@ static thread_local int wave;
 static thread_local const void* kernel = nullptr;
 static int late = 0;                       // loads to LDS land at their wait; wavefronts and blocks in descending order
 static bool host_only = false;             // launches are looked at, not run
-static std::atomic<long> complaints{0};
+static std::atomic<long> complaints{0}, launches{0};
+long launched() { return launches; }
 static std::mutex mu;
 static std::map<uintptr_t, size_t> ranges;      // device memory: start -> bytes (not changed while kernels run)
 
@@ -243,6 +244,7 @@ void run(dim3 grid, dim3 block, size_t lds, const void* k, const std::function<v
     const int threads = (int)(block.x * block.y * block.z);
     static const bool trace = getenv("LPM_LANES_TRACE") != nullptr;
     kernel = k;
+    ++launches;
     if (trace) fprintf(stderr, "lanes: %ux%ux%u blocks of %d threads, %zu bytes of LDS: %s\n", grid.x, grid.y, grid.z, threads, lds, kernel_name(k).c_str());
     bool allowed = lds <= 64 * 1024;
     if (!allowed) {

@@ -1,5 +1,5 @@
 // Looks into the library: which geometries the implicit-GEMM kernels take (op 0: forward, 1: data gradient), for tests of sizes no test
-// can hold, and calls that wait for the next one's launch where no network makes them wait.
+// can hold, calls that wait for the next one's launch where no network makes them wait, and launches behind a stop event.
 #include "lpm_internal.h"
 #include "stage.h"
 
@@ -27,4 +27,19 @@ extern "C" int lanes_hold_twice() {
     void* p = (void*)4096;
     if (lpm::launch_conv_fwd(LPM_BF16, g, p, p, nullptr, nullptr, nullptr, 0, p, p, nullptr, nullptr, true, &h) != hipSuccess || !h.held) return -1;
     return lpm::launch_conv_fwd(LPM_BF16, g, p, p, nullptr, nullptr, nullptr, 0, p, p, nullptr, nullptr, true, &h);
+}
+
+// the data gradient of an average pooling and the layer over its channels, m samples, under a stop event: launches that the event does not stand behind
+extern "C" long lanes_behind_head(int dtype, int m, int hw, int c, int n) {
+    hipEvent_t e = nullptr;
+    (void)hipEventCreate(&e);
+    const long before = lanes::launched();
+    void* p = (void*)4096;
+    {
+        lpm::StopEvent stop(e, nullptr);
+        if (lpm::launch_head_bwd(dtype, m, hw, c, n, p, p, p, 0, nullptr, nullptr, nullptr) != hipSuccess || stop.finish() != hipSuccess) return -1;
+    }
+    const long after = lanes::launched(), left = e->records == 1 && after > before ? after - e->behind : -1;
+    (void)hipEventDestroy(e);
+    return left;
 }

@@ -106,6 +106,18 @@ def test_no_held_call_is_lost(lanes):
     assert r.returncode == 0 and r.stdout.strip().endswith("all ran"), r.stdout + r.stderr
 
 
+@pytest.mark.parametrize("dtype,m,hw,c,n", [(1, 32769, 1, 8, 1), (0, 65537, 1, 4, 1), (1, 3, 4, 1032, 10)], ids=["bf16", "float", "small"])
+def test_stop_event_stands_behind_the_head(lanes, dtype, m, hw, c, n):
+    """The event that other streams wait for comes with the last launch of the kernel it is given to, whatever the number of samples.  (In
+    groups of 32768 samples it came with the first one.)"""
+    lib = ctypes.CDLL(lanes)
+    lib.lanes_behind_head.restype = ctypes.c_long
+    lib.lanes_host_only(1)
+    left = lib.lanes_behind_head(dtype, m, hw, c, n)
+    lib.lanes_host_only(0)
+    assert left == 0
+
+
 @pytest.mark.parametrize("op,h,taken", [(0, 16382, True), (0, 16383, False), (1, 16381, True), (1, 16382, False)],
                          ids=["forward-in", "forward-out", "dgrad-in", "dgrad-out"])
 def test_buffers_near_4_gib(lanes, op, h, taken):
