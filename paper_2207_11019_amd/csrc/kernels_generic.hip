@@ -641,8 +641,7 @@ hipError_t launch_gap_bwd(int dtype, int32_t m, int32_t HW, int32_t C, const voi
 // Global average pooling and the fully connected layer that alone reads it, the head of a residual network: one kernel forward and one for the
 // data gradient, where each had two of a few microseconds and next to no work on the chain that every micro-batch waits for (ResNet-18/CIFAR at 32 samples
 // a micro-batch: forward 4.3 + 6.2 us -> 5.7, data gradient 4.8 + 3.5 -> 6.1; per step 2634 -> 2584, float 2373 -> 2334, width 48 with 100 classes 2143 ->
-// 2123, volumetric 1598 -> 1588, 16 images forward 133.4 -> 130.2).  What bounds them is the launch and two round trips to memory.  The
-// gradient of the pooled tensor is not stored.
+// 2123, volumetric 1598 -> 1588, 16 images forward 133.4 -> 130.2).  What bounds them is the launch and two round trips to memory.
 
 // A block takes a sample: its threads hold V channels of every RL-th position, then eight lanes share NB outputs of the layer at a time (whose
 // loads are under way together).
@@ -711,8 +710,8 @@ __global__ void __launch_bounds__(256) head_fwd_kernel(int HW, int C, int cl_log
 
 // A block takes 16 channel chunks of a sample; 16 groups of threads share the outputs of the layer, then the positions.
 template <typename T, int V>
-__global__ void __launch_bounds__(256) head_bwd_kernel(int HW, int C, int N, const T* __restrict__ dz, const T* __restrict__ w, T* __restrict__ dx,
-                                                       int accumulate, const T* __restrict__ mask, const float* __restrict__ mscale) {
+__global__ void __launch_bounds__(256) head_bwd_kernel(int HW, int C, int N, const T* __restrict__ dz, const T* __restrict__ w, T* __restrict__ dp,
+                                                       T* __restrict__ dx, int accumulate, const T* __restrict__ mask, const float* __restrict__ mscale) {
     __shared__ __attribute__((aligned(16))) float red[16][16 * V];
     const int cx = threadIdx.x & 15, ty = threadIdx.x >> 4, c0 = (blockIdx.y * 16 + cx) * V, n0 = blockIdx.x;
     const bool ok = c0 < C;
@@ -739,10 +738,14 @@ __global__ void __launch_bounds__(256) head_bwd_kernel(int HW, int C, int N, con
         float sum = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) sum += red[r][cx * V + k];
-        const T one = to_store<T>(sum);      // (as a stored gradient)
-        g[k] = ld(&one, 0) / (float)HW;
+        const T one = to_store<T>(sum);
+        g[k] = ld(&one, 0);
         ms[k] = mscale ? mscale[c0 + k] : 1.f;
     }
+    if (!ty) EpiVec<T, V>::put(dp, (int64_t)n0 * C + c0, g);
+    if (!dx) return;
+#pragma unroll
+    for (int k = 0; k < V; ++k) g[k] = g[k] / (float)HW;
     for (int r = ty; r < HW; r += 16) {
         const int64_t at = ((int64_t)n0 * HW + r) * C + c0;
         float v[V], t[V];
@@ -780,13 +783,14 @@ hipError_t launch_head_fwd(int dtype, int32_t m, int32_t HW, int32_t C, int32_t 
     else N > 32 ? go(head_fwd_kernel<float, 4, 4>, 0.f) : go(head_fwd_kernel<float, 4, 1>, 0.f);
     return hipGetLastError();
 }
-hipError_t launch_head_bwd(int dtype, int32_t m, int32_t HW, int32_t C, int32_t N, const void* dz, const void* w, void* dx, int accumulate, const void* mask,
-                           const float* mscale, hipStream_t s) {
+hipError_t launch_head_bwd(int dtype, int32_t m, int32_t HW, int32_t C, int32_t N, const void* dz, const void* w, void* dp, void* dx, int accumulate,
+                           const void* mask, const float* mscale, hipStream_t s) {
     // (samples on the grid's first extent, which has room for them: one launch, so that a stop event stands behind all of them)
     const dim3 grid((unsigned)m, (unsigned)((C / (dtype == LPM_BF16 ? 8 : 4) + 15) / 16));
-    if (dtype == LPM_BF16) launch_last(head_bwd_kernel<bf16_t, 8>, grid, dim3(256), 0, s, HW, C, N, (const bf16_t*)dz, (const bf16_t*)w, (bf16_t*)dx, accumulate,
+    if (dtype == LPM_BF16) launch_last(head_bwd_kernel<bf16_t, 8>, grid, dim3(256), 0, s, HW, C, N, (const bf16_t*)dz, (const bf16_t*)w, (bf16_t*)dp, (bf16_t*)dx, accumulate,
                                        (const bf16_t*)mask, mscale);
-    else launch_last(head_bwd_kernel<float, 4>, grid, dim3(256), 0, s, HW, C, N, (const float*)dz, (const float*)w, (float*)dx, accumulate, (const float*)mask, mscale);
+    else launch_last(head_bwd_kernel<float, 4>, grid, dim3(256), 0, s, HW, C, N, (const float*)dz, (const float*)w, (float*)dp, (float*)dx, accumulate,
+                     (const float*)mask, mscale);
     return hipGetLastError();
 }
 

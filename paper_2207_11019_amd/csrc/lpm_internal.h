@@ -202,11 +202,12 @@ hipError_t launch_maxpool_bwd(int dtype, int32_t m, int32_t H, int32_t W, int32_
 hipError_t launch_gap_fwd(int dtype, int32_t m, int32_t HW, int32_t C, const void* x, void* y, hipStream_t st);
 hipError_t launch_gap_bwd(int dtype, int32_t m, int32_t HW, int32_t C, const void* dy, void* dx, int accumulate,
                           const void* mask, const float* mscale, hipStream_t st);
-// the pooling and the fully connected layer [N][C] that reads it: y and z; dx (+)= the gradient of the pooling's input from dz (see LayerRt::head)
+// the pooling and the fully connected layer [N][C] that reads it: y and z; dp = the gradient of y from dz, dx (may be NULL) (+)= that of the
+// pooling's input (see LayerRt::head)
 bool head_ok(int dtype, int32_t HW, int32_t C, int32_t N);
 hipError_t launch_head_fwd(int dtype, int32_t m, int32_t HW, int32_t C, int32_t N, const void* x, void* y, const void* w, const float* bias, void* z, hipStream_t st);
-hipError_t launch_head_bwd(int dtype, int32_t m, int32_t HW, int32_t C, int32_t N, const void* dz, const void* w, void* dx, int accumulate, const void* mask,
-                           const float* mscale, hipStream_t st);
+hipError_t launch_head_bwd(int dtype, int32_t m, int32_t HW, int32_t C, int32_t N, const void* dz, const void* w, void* dp, void* dx, int accumulate,
+                           const void* mask, const float* mscale, hipStream_t st);
 // dlogits = (softmax(logits) - onehot) * loss_scale;  *loss_accum += loss_scale * sum_n -log p_n[label_n]
 // one-head self-attention over P positions per sample: x [m][P][3C] (queries | keys | values), y [m][P][C]
 hipError_t launch_attn_fwd(int dtype, int32_t m, int32_t P, int32_t C, const void* x, void* y, hipStream_t st);

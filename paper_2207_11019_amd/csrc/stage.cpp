@@ -907,7 +907,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
             case LPM_MAXPOOL2:
             case LPM_GAP:
                 if (lr.unpooled) break;          // done by the consumer's data gradient
-                if (want_src) {
+                if (want_src || lr.head >= 0) {  // (a head's kernel stores the pooled tensor's gradient, too)
                     void* gsrc = G[gi(l.src)];
                     int gsrc_acc = have[gi(l.src)];
                     const void* gmask = nullptr;
@@ -934,7 +934,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                         const LayerRt& fc = s->Ly(lr.head);
                         LPM_HIP(launch_head_bwd(s->dtype, s->m, l.h_in * l.w_in, l.cin, fc.g.Cout, head_dz,
                                                 s->dtype == LPM_BF16 ? (const void*)((const char*)lowp + fc.lowp_w_off) : (const void*)(params + fc.w_off),
-                                                gsrc, gsrc_acc, gmask, gmscale, st));
+                                                const_cast<void*>(g), gsrc, gsrc_acc, gmask, gmscale, st));
                     } else if (do_data)
                         LPM_HIP(launch_gap_bwd(s->dtype, s->m, l.h_in * l.w_in, l.cin, g, gsrc, gsrc_acc, gmask, gmscale, st));
                     LPM_HIP(stop.finish());

@@ -37,7 +37,7 @@ extern "C" long lanes_behind_head(int dtype, int m, int hw, int c, int n) {
     void* p = (void*)4096;
     {
         lpm::StopEvent stop(e, nullptr);
-        if (lpm::launch_head_bwd(dtype, m, hw, c, n, p, p, p, 0, nullptr, nullptr, nullptr) != hipSuccess || stop.finish() != hipSuccess) return -1;
+        if (lpm::launch_head_bwd(dtype, m, hw, c, n, p, p, p, p, 0, nullptr, nullptr, nullptr) != hipSuccess || stop.finish() != hipSuccess) return -1;
     }
     const long after = lanes::launched(), left = e->records == 1 && after > before ? after - e->behind : -1;
     (void)hipEventDestroy(e);

@@ -95,6 +95,41 @@ def test_head(lpm, m, c, n, h, w, dtype):
     stage_backward_isolated(lpm, layers, [0, 3], m, m, dtype, seed=35, dx_wanted=True, check_forward=True, grad_std=1.0)
 
 
+# ... and the gradient of the pooled tensor is there to be read, as that of any tensor inside a stage, also where the gradient of the
+# pooling's input is not wanted.  A stored value is within half a unit of its last place of the sum, whose float error is below (n + 1) 2^-24 of the
+# sum of magnitudes.
+@pytest.mark.parametrize("dx_wanted", [True, False], ids=["dx", "no_dx"])
+@pytest.mark.parametrize("m,c,n,h,w", [(3, 24, 10, 3, 5), (2, 1032, 1, 2, 3)], ids=lambda v: str(v))
+@pytest.mark.parametrize("dtype", [0, 1], ids=["f32", "bf16"])
+def test_gradient_of_the_pooled_tensor(lpm, m, c, n, h, w, dtype, dx_wanted):
+    import torch
+    gap = dict(kind="gap", cin=c, cout=c, kh=h, kw=w, stride=1, pad=0, h_in=h, w_in=w, relu=False, bias=False, scale=False, src=None, add_src=None, cut_after=False)
+    st = lpm.Stage(chain(gap, C(c, n, 1, 1, 1, 1, relu=False)), 0, 2, m, dtype)
+    print("m", m, "channels", c, "outputs", n, "dtype", dtype, flush=True)
+    tdt, rng = (torch.bfloat16 if dtype else torch.float32), np.random.default_rng(37)
+    buf = lambda k: torch.zeros(max(k, 256), dtype=torch.uint8, device="cuda")      # noqa: E731
+    rnd = lambda k, s: torch.from_numpy(rng.normal(0, s, k).astype(np.float32)).to(tdt)      # noqa: E731
+    params, lowp, grads, stash, fws, bws = [buf(k) for k in (st.param_bytes, st.lowp_bytes, st.grad_bytes, st.stash_bytes, st.fwd_ws_bytes, st.bwd_ws_bytes)]
+    wt, dy, (off, _) = rnd(n * c, 0.1), rnd(m * n, 1.0), st.param_offset(1, 0)
+    params.view(torch.float32)[off:off + n * c] = wt.float().cuda()
+    lowp = lowp if dtype else None
+    st.sync_lowp(params, lowp)
+    x, y, dx = rnd(m * h * w * c, 1.0).cuda(), buf(st.out_bytes), buf(st.in_bytes)
+    st.forward(x, y, None, None, params, lowp, stash, fws, 1.0)
+    bws.fill_(0x7f)
+    st.backward(x, y, dy.cuda(), dx if dx_wanted else None, params, lowp, stash, grads, False, bws)
+    torch.cuda.synchronize()
+    at, size = st.grad_offset(0)
+    got = bws[at:at + size].view(tdt)[:m * c].double().cpu().numpy().reshape(m, c)
+    a, b = dy.double().numpy().reshape(m, n), wt.double().numpy().reshape(n, c)
+    sums = (n + 1) * 2.0 ** -24 * (np.abs(a) @ np.abs(b))
+    assert (np.abs(got - a @ b) <= sums + 2.0 ** (-8 if dtype else -24) * (np.abs(a @ b) + sums)).all()
+    if dx_wanted:
+        d = dx.view(tdt)[:m * h * w * c].double().cpu().numpy().reshape(m, h * w, c)
+        want = got[:, None, :] / (h * w)
+        assert (np.abs(d - want) <= 2.0 ** (-8 if dtype else -23) * np.abs(want)).all()
+
+
 def bottlenecks(w, mid, h, m, shortcuts, first_scale=True):
     """Stem, then blocks 1x1 reduce - 1x1 expand + shortcut, then one more reduction that keeps the last block inside the stage.
     shortcuts: the tensor each block adds ('x': the block's input, 'in': the stage's)."""
