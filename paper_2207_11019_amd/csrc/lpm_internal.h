@@ -203,8 +203,8 @@ hipError_t launch_gap_fwd(int dtype, int32_t m, int32_t HW, int32_t C, const voi
 hipError_t launch_gap_bwd(int dtype, int32_t m, int32_t HW, int32_t C, const void* dy, void* dx, int accumulate,
                           const void* mask, const float* mscale, hipStream_t st);
 // the pooling and the fully connected layer [N][C] that reads it: y and z; dp = the gradient of y from dz, dx (may be NULL) (+)= that of the
-// pooling's input (see LayerRt::head)
-bool head_ok(int dtype, int32_t HW, int32_t C, int32_t N);
+// pooling's input (see LayerRt::head_fwd)
+bool head_ok(int dtype, int32_t m, int32_t HW, int32_t C, int32_t N, bool fwd);
 hipError_t launch_head_fwd(int dtype, int32_t m, int32_t HW, int32_t C, int32_t N, const void* x, void* y, const void* w, const float* bias, void* z, hipStream_t st);
 hipError_t launch_head_bwd(int dtype, int32_t m, int32_t HW, int32_t C, int32_t N, const void* dz, const void* w, void* dp, void* dx, int accumulate,
                            const void* mask, const float* mscale, hipStream_t st);

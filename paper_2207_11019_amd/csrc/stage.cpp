@@ -279,9 +279,12 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
         int n_src, n_add;
         uses(i, n_src, n_add);
         if (n_src != 1 || n_add != 0 || !has_weights(fc.d) || fc.d.src != i || (fc.d.flags & (LPM_RELU | LPM_SCALE)) || fc.d.add_src != LPM_NONE) continue;
-        if (fc.g.K() != fc.g.Cin || fc.g.rows_out() != microbatch || !head_ok(dtype, s->net[(size_t)i].h_in * s->net[(size_t)i].w_in, fc.g.Cin, fc.g.Cout)) continue;
-        s->Ly(i).head = i + 1;
-        fc.headed = true;
+        if (fc.g.K() != fc.g.Cin || fc.g.rows_out() != microbatch) continue;
+        const int32_t hw = s->net[(size_t)i].h_in * s->net[(size_t)i].w_in;
+        fc.headed_fwd = head_ok(dtype, microbatch, hw, fc.g.Cin, fc.g.Cout, true);
+        fc.headed_bwd = head_ok(dtype, microbatch, hw, fc.g.Cin, fc.g.Cout, false);
+        if (fc.headed_fwd) s->Ly(i).head_fwd = i + 1;
+        if (fc.headed_bwd) s->Ly(i).head_bwd = i + 1;
     }
     // A projection and the layer of the block that stands beside it do not read each other's results: forward, the projection
     // and the layer before it; backward, where the projection's dz is there with that of the layer that adds it, those two.
@@ -289,7 +292,7 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
     for (int32_t i = first; i + 1 < last; ++i) {
         LayerRt& lr = s->Ly(i);
         LayerRt& nx = s->Ly(i + 1);
-        if (!has_weights(lr.d) || !has_weights(nx.d) || nx.d.src == i || lr.headed) continue;
+        if (!has_weights(lr.d) || !has_weights(nx.d) || nx.d.src == i || lr.headed_fwd || lr.headed_bwd) continue;
         lr.hold_fwd = nx.d.add_src != i && lr.pool_fwd < 0;
         int n_src, n_add;
         uses(i, n_src, n_add);
@@ -546,7 +549,7 @@ int32_t lpm_stage_forward_on(lpm_stage* s, const void* x, void* y, const int32_t
         switch (l.kind) {
             case LPM_CONV:
             case LPM_FC: {
-                if (lr.headed) break;            // done with the pooling it reads
+                if (lr.headed_fwd) break;            // done with the pooling it reads
                 const void* w = s->dtype == LPM_BF16 ? (const void*)((const char*)lowp + lr.lowp_w_off)
                                                      : (const void*)(params + lr.w_off);
                 const float* sc = lr.s_off != NO ? params + lr.s_off : nullptr;
@@ -562,11 +565,11 @@ int32_t lpm_stage_forward_on(lpm_stage* s, const void* x, void* y, const int32_t
                 LPM_HIP(launch_maxpool_fwd(s->dtype, s->m, l.h_in, l.w_in, l.cin, in, outp, st));
                 break;
             case LPM_GAP:
-                if (lr.head >= 0) {
-                    const LayerRt& fc = s->Ly(lr.head);
+                if (lr.head_fwd >= 0) {
+                    const LayerRt& fc = s->Ly(lr.head_fwd);
                     LPM_HIP(launch_head_fwd(s->dtype, s->m, l.h_in * l.w_in, l.cin, fc.g.Cout, in, outp,
                                             s->dtype == LPM_BF16 ? (const void*)((const char*)lowp + fc.lowp_w_off) : (const void*)(params + fc.w_off),
-                                            fc.b_off != NO ? params + fc.b_off : nullptr, const_cast<void*>(tptr(s, lr.head, x, y, stash)), st));
+                                            fc.b_off != NO ? params + fc.b_off : nullptr, const_cast<void*>(tptr(s, lr.head_fwd, x, y, stash)), st));
                     break;
                 }
                 LPM_HIP(launch_gap_fwd(s->dtype, s->m, l.h_in * l.w_in, l.cin, in, outp, st));
@@ -892,7 +895,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                     if (lr.unpool_of >= 0) {
                         if (do_data && unpool.dst) LPM_HIP(launch_conv_dgrad(s->dtype, lr.g, dz, w, wt, nullptr, 0, nullptr, nullptr, counts, st, &unpool,
                                                                              nullptr, lr.dz_unscaled ? sc : nullptr, true));
-                    } else if (lr.headed) {
+                    } else if (lr.headed_bwd) {
                         head_dz = dz;            // (the pooling's kernel goes on from there)
                     } else if (do_data) {
                         const bool hold = lr.hold_bwd && i > first && (s->Ly(i - 1).d.src >= first || dx);
@@ -907,7 +910,7 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
             case LPM_MAXPOOL2:
             case LPM_GAP:
                 if (lr.unpooled) break;          // done by the consumer's data gradient
-                if (want_src || lr.head >= 0) {  // (a head's kernel stores the pooled tensor's gradient, too)
+                if (want_src || lr.head_bwd >= 0) {  // (a head's kernel stores the pooled tensor's gradient, too)
                     void* gsrc = G[gi(l.src)];
                     int gsrc_acc = have[gi(l.src)];
                     const void* gmask = nullptr;
@@ -930,8 +933,8 @@ int32_t lpm_stage_backward_on(lpm_stage* s, const void* x, const void* y, const 
                     if (do_data && l.kind == LPM_MAXPOOL2)
                         LPM_HIP(launch_maxpool_bwd(s->dtype, s->m, l.h_in, l.w_in, l.cin, tptr(s, l.src, x, y, stash),
                                                    tptr(s, i, x, y, stash), g, gsrc, gsrc_acc, gmask != nullptr, gmscale, st));
-                    else if (do_data && lr.head >= 0) {
-                        const LayerRt& fc = s->Ly(lr.head);
+                    else if (do_data && lr.head_bwd >= 0) {
+                        const LayerRt& fc = s->Ly(lr.head_bwd);
                         LPM_HIP(launch_head_bwd(s->dtype, s->m, l.h_in * l.w_in, l.cin, fc.g.Cout, head_dz,
                                                 s->dtype == LPM_BF16 ? (const void*)((const char*)lowp + fc.lowp_w_off) : (const void*)(params + fc.w_off),
                                                 const_cast<void*>(g), gsrc, gsrc_acc, gmask, gmscale, st));

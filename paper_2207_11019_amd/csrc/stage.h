@@ -37,8 +37,8 @@ struct LayerRt {
     bool wg_end = false;                         // the last layer, in backward order, of a group whose weight gradients share launches
     bool hold_fwd = false;                       // its forward contraction may share a launch with the next layer's
     bool hold_bwd = false;                       // its data gradient may share a launch with the layer's before it, which made its shortcut
-    int32_t head = -1;                           // average pooling: index of the FC layer, its only reader, whose forward and data gradient its kernels perform
-    bool headed = false;                         // that FC layer
+    int32_t head_fwd = -1, head_bwd = -1;        // average pooling: index of the FC layer, its only reader, whose forward / data gradient its kernel performs
+    bool headed_fwd = false, headed_bwd = false; // that FC layer
     int32_t pool_fwd = -1;                       // conv/FC: index of the max-pooling layer whose forward its own forward kernel performs
     bool pooled_fwd = false;                     // max-pooling: its forward runs inside its producer's forward kernel
     bool unpooled = false;                       // max-pooling: its backward runs inside its consumer's data gradient

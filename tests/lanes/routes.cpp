@@ -1,5 +1,5 @@
 // Looks into the library: which geometries the implicit-GEMM kernels take (op 0: forward, 1: data gradient), for tests of sizes no test
-// can hold, calls that wait for the next one's launch where no network makes them wait, and launches behind a stop event.
+// can hold, which heads share a kernel, calls that wait for the next one's launch where no network makes them wait, and launches behind a stop event.
 #include "lpm_internal.h"
 #include "stage.h"
 
@@ -13,6 +13,9 @@ extern "C" int lanes_takes(int op, int dtype, const lpm_conv_geom* q) {
                     q->cout, q->kh, q->kw, q->stride, q->pad};
     return op == 0 ? lpm::mfma_fwd_ok(dtype, g) : lpm::mfma_dgrad_ok(dtype, g);
 }
+
+// whether an average pooling over hw positions of c channels shares a kernel with the layer of n outputs behind it
+extern "C" int lanes_head(int dtype, int m, int hw, int c, int n, int fwd) { return lpm::head_ok(dtype, m, hw, c, n, fwd != 0); }
 
 // layer i's contraction waits (forward, backward) although what follows need not be one that it can share a launch with
 extern "C" void lanes_hold(lpm_stage* s, int i, int fwd, int bwd) {

@@ -118,6 +118,18 @@ def test_stop_event_stands_behind_the_head(lanes, dtype, m, hw, c, n):
     assert left == 0
 
 
+@pytest.mark.parametrize("m,hw,c,n,fwd,bwd", [(8, 1, 64, 10, 1, 1), (32, 16, 512, 10, 1, 1), (256, 16, 512, 128, 1, 1), (256, 1, 1024, 32, 1, 1), (257, 1, 8, 1, 1, 0),
+                                              (256, 1, 1032, 32, 1, 0), (1024, 1, 256, 128, 1, 0), (1025, 1, 64, 1, 0, 0), (512, 1, 520, 33, 0, 0),
+                                              (1024, 1, 264, 33, 0, 0), (8, 1, 520, 33, 0, 1), (8, 4, 2048, 100, 0, 1), (8, 16, 2048, 32, 1, 1)])
+def test_heads_that_share_a_kernel(lanes, m, hw, c, n, fwd, bwd):
+    """... are those whose one kernel takes no longer than the pooling's and the contraction's: not with many samples, nor where every sample's block
+    would read hundreds of kilobytes of weights.  (Up to 2048 channels and 128 outputs all of them did: 9 times the data gradient's time with 2048 samples.)"""
+    lib = ctypes.CDLL(lanes)
+    for dtype in (0, 1):
+        if hw * c * (2 if dtype else 4) <= 65536:
+            assert (lib.lanes_head(dtype, m, hw, c, n, 1), lib.lanes_head(dtype, m, hw, c, n, 0)) == (fwd, bwd)
+
+
 @pytest.mark.parametrize("op,h,taken", [(0, 16382, True), (0, 16383, False), (1, 16381, True), (1, 16382, False)],
                          ids=["forward-in", "forward-out", "dgrad-in", "dgrad-out"])
 def test_buffers_near_4_gib(lanes, op, h, taken):
