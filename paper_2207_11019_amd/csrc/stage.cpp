@@ -545,7 +545,8 @@ int32_t lpm_stage_forward_on(lpm_stage* s, const void* x, void* y, const int32_t
         const void* in = tptr(s, l.src, x, y, stash);
         void* outp = const_cast<void*>(tptr(s, i, x, y, stash));
         if (!has_weights(l)) LPM_HIP(run_held(held, st));      // (a contraction's launcher sees to it)
-        StopEvent stop(i == s->last - 1 ? done : nullptr, st);
+        const bool ends = lr.head_fwd >= 0 ? lr.head_fwd == s->last - 1 : i == s->last - 1 && !lr.headed_fwd;      // its kernel is the pass's last
+        StopEvent stop(ends ? done : nullptr, st);
         switch (l.kind) {
             case LPM_CONV:
             case LPM_FC: {

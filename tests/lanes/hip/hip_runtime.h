@@ -153,11 +153,11 @@ template <typename A> static inline A lane_mfma_f32(float a, float b, A c, int p
 
 // ---- runtime -------------------------------------------------------------------------------------
 // Recording an event writes to it and waiting for it reads it, so a thread sanitizer sees whether the wait is ordered behind the
-// record; it keeps how many launches it stands behind.  Nothing can be captured.
+// record; it keeps how many launches it stands behind, and whether it came with the last of them.  Nothing can be captured.
 typedef int hipError_t;
 enum { hipSuccess = 0, hipErrorInvalidValue = 1, hipFuncAttributeMaxDynamicSharedMemorySize = 8, hipEventDisableTiming = 2, hipStreamNonBlocking = 1, hipMemcpyDeviceToDevice = 3 };
 typedef struct LaneStream* hipStream_t;
-typedef struct LaneEvent { int records; long behind; }* hipEvent_t;
+typedef struct LaneEvent { int records; long behind; bool with_kernel; }* hipEvent_t;
 typedef struct LaneGraph* hipGraph_t;
 typedef struct LaneGraphExec* hipGraphExec_t;
 typedef struct LaneGraphNode* hipGraphNode_t;
@@ -168,10 +168,10 @@ static inline const char* hipGetErrorString(hipError_t) { return "error"; }
 static inline hipError_t hipGetDevice(int* d) { *d = lanes::device(); return hipSuccess; }
 static inline hipError_t hipSetDevice(int d) { return lanes::set_device(d); }
 static inline hipError_t hipFuncSetAttribute(const void* k, int, int bytes) { return lanes::allow_lds(k, bytes); }
-static inline hipError_t hipEventCreate(hipEvent_t* e) { *e = new LaneEvent{0, 0}; return hipSuccess; }
+static inline hipError_t hipEventCreate(hipEvent_t* e) { *e = new LaneEvent{0, 0, false}; return hipSuccess; }
 static inline hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
 static inline hipError_t hipEventDestroy(hipEvent_t e) { delete e; return hipSuccess; }
-static inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t) { ++e->records; e->behind = lanes::launched(); return hipSuccess; }
+static inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t) { ++e->records; e->behind = lanes::launched(); e->with_kernel = false; return hipSuccess; }
 static inline hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 static inline hipError_t hipEventElapsedTime(float* f, hipEvent_t, hipEvent_t) { *f = 0.01f; return hipSuccess; }
 static inline hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)malloc(16); return hipSuccess; }
@@ -194,4 +194,4 @@ template <typename K, typename... A> static inline void lane_launch(K kernel, di
     lanes::run(grid, block, lds, (const void*)kernel, [=]() { kernel(args...); });
 }
 #define hipLaunchKernelGGL(k, g, b, lds, st, ...) lane_launch(k, g, b, lds, ##__VA_ARGS__)
-#define hipExtLaunchKernelGGL(k, g, b, lds, st, e0, e1, fl, ...) (lane_launch(k, g, b, lds, ##__VA_ARGS__), (void)hipEventRecord(e1, st))
+#define hipExtLaunchKernelGGL(k, g, b, lds, st, e0, e1, fl, ...) (lane_launch(k, g, b, lds, ##__VA_ARGS__), (void)hipEventRecord(e1, st), (void)((e1)->with_kernel = true))

@@ -46,3 +46,14 @@ extern "C" long lanes_behind_head(int dtype, int m, int hw, int c, int n) {
     (void)hipEventDestroy(e);
     return left;
 }
+
+// a forward pass with an event for its end: whether the event came with the pass's last kernel (1), after it as a packet of its own (0), or neither (-1)
+extern "C" int lanes_forward_done(lpm_stage* s) {
+    hipEvent_t e = nullptr;
+    (void)hipEventCreate(&e);
+    void* p = (void*)4096;
+    const int32_t rc = lpm_stage_forward_on(s, p, p, nullptr, nullptr, (float*)p, p, p, p, 1.f, nullptr, true, e);
+    const int how = rc == LPM_OK && e->records == 1 && e->behind == lanes::launched() ? e->with_kernel : -1;
+    (void)hipEventDestroy(e);
+    return how;
+}

@@ -118,6 +118,31 @@ def test_stop_event_stands_behind_the_head(lanes, dtype, m, hw, c, n):
     assert left == 0
 
 
+DONE = """
+import ctypes, lanes_plugin
+import paper_2207_11019_amd as lpm
+from workloads import configs
+E = lanes_plugin._E
+E.lanes_forward_done.argtypes = [ctypes.c_void_p]
+E.lanes_host_only(1)
+def done(relu, m, *more):
+    b = configs._Builder(16, 9, 9)
+    b.conv(16, 3, pad=1); b.gap(); b.conv(24, 1, relu=relu)
+    for c in more: b.conv(c, 1)
+    layers = b.finish()
+    st = lpm.Stage(layers, 0, len(layers), m, lpm.BF16)
+    return E.lanes_forward_done(st.h)
+print([done(False, 2), done(False, 2, 16), done(True, 2), done(False, 1025)])
+"""
+
+
+def test_end_of_a_forward_pass_comes_with_its_last_kernel(lanes):
+    """... also where that is the head's, which runs under the pooling's turn; a layer behind it, a head of two kernels."""
+    env = dict(os.environ, LPM_LANES=lanes, PYTHONPATH=os.pathsep.join([LANES, os.path.dirname(TESTS), os.environ.get("PYTHONPATH", "")]))
+    r = subprocess.run([sys.executable, "-c", DONE], env=env, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip().endswith("[1, 1, 1, 1]"), r.stdout + r.stderr
+
+
 @pytest.mark.parametrize("m,hw,c,n,fwd,bwd", [(8, 1, 64, 10, 1, 1), (32, 16, 512, 10, 1, 1), (256, 16, 512, 128, 1, 1), (256, 1, 1024, 32, 1, 1), (257, 1, 8, 1, 1, 0),
                                               (256, 1, 1032, 32, 1, 0), (1024, 1, 256, 128, 1, 0), (1025, 1, 64, 1, 0, 0), (512, 1, 520, 33, 0, 0),
                                               (1024, 1, 264, 33, 0, 0), (8, 1, 520, 33, 0, 1), (8, 4, 2048, 100, 0, 1), (8, 16, 2048, 32, 1, 1)])
