@@ -100,15 +100,43 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
     }
     s->stash_bytes = stash;
 
-    // parameters: trainable (W, bias per layer) first, frozen scales after
     s->lay.resize((size_t)(last - first));
-    size_t off = 0, lowp = 0, kws = 0, wws = 0, fws = 0, fcs = 0;
     for (int32_t i = first; i < last; ++i) {
         LayerRt& lr = s->Ly(i);
         lr.d = s->net[i];
         const lpm_layer& l = lr.d;
         const Shape o = s->shapes[(size_t)i + 1];
         lr.g = ConvGeom{microbatch, l.h_in, l.w_in, l.cin, o.h, o.w, o.c, l.kh, l.kw, l.stride, l.pad};
+        if (has_weights(l) && (l.d_in > 1 || l.kd > 1)) {          // a volumetric layer: the tensor heights are slices x rows
+            lr.g.D = l.d_in; lr.g.Kd = l.kd; lr.g.pad_d = l.pad_d;
+            lr.g.Do = (l.d_in + 2 * l.pad_d - l.kd) / l.stride + 1;
+            lr.g.Ho = o.h / lr.g.Do;
+        }
+    }
+    auto uses = [&](int32_t t, int& n_src, int& n_add) {
+        n_src = n_add = 0;
+        for (int32_t j = std::max(t + 1, first); j < last; ++j) { n_src += s->net[(size_t)j].src == t; n_add += s->net[(size_t)j].add_src == t; }
+    };
+    // The head: an average pooling whose only reader is a plain layer over its channels.
+    for (int32_t i = first; i + 1 < last; ++i) {
+        if (s->net[(size_t)i].kind != LPM_GAP || i == s->t_out) continue;
+        LayerRt& fc = s->Ly(i + 1);
+        int n_src, n_add;
+        uses(i, n_src, n_add);
+        if (n_src != 1 || n_add != 0 || !has_weights(fc.d) || fc.d.src != i || (fc.d.flags & (LPM_RELU | LPM_SCALE)) || fc.d.add_src != LPM_NONE) continue;
+        if (fc.g.K() != fc.g.Cin || fc.g.rows_out() != microbatch) continue;
+        const int32_t hw = s->net[(size_t)i].h_in * s->net[(size_t)i].w_in;
+        fc.headed_fwd = head_ok(dtype, microbatch, hw, fc.g.Cin, fc.g.Cout, true);
+        fc.headed_bwd = head_ok(dtype, microbatch, hw, fc.g.Cin, fc.g.Cout, false);
+        if (fc.headed_fwd) s->Ly(i).head_fwd = i + 1;
+        if (fc.headed_bwd) s->Ly(i).head_bwd = i + 1;
+    }
+    // parameters: trainable (W, bias per layer) first, frozen scales after
+    size_t off = 0, lowp = 0, kws = 0, wws = 0, fws = 0, fcs = 0;
+    for (int32_t i = first; i < last; ++i) {
+        LayerRt& lr = s->Ly(i);
+        const lpm_layer& l = lr.d;
+        const Shape o = s->shapes[(size_t)i + 1];
         if (!has_weights(l)) {
             if (l.kind == LPM_ATTN) {
                 if (!attn_ok(l.h_in * l.w_in, l.cout)) { delete s; return fail(LPM_ESHAPE, "layer %d: attention over %d positions of %d channels is outside the kernel's limits", i, l.h_in * l.w_in, l.cout); }
@@ -116,18 +144,13 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
             }
             continue;
         }
-        if (l.d_in > 1 || l.kd > 1) {          // a volumetric layer: the tensor heights are slices x rows
-            lr.g.D = l.d_in; lr.g.Kd = l.kd; lr.g.pad_d = l.pad_d;
-            lr.g.Do = (l.d_in + 2 * l.pad_d - l.kd) / l.stride + 1;
-            lr.g.Ho = o.h / lr.g.Do;
-        }
         lr.w_count = (size_t)l.cout * taps_of(l) * l.cin;
         lr.w_off = off;
         off += align_up(lr.w_count, 64);
         if (l.flags & LPM_BIAS) { lr.b_off = off; off += align_up((size_t)l.cout, 64); }
         if (dtype == LPM_BF16) {
             lr.lowp_w_off = lr.w_off * 2;      // the bf16 copies mirror the float layout element for element
-            if (dgrad_uses_wt(dtype, lr.g)) { lr.lowp_wt_off = lowp; lowp += align_up(lr.w_count * 2, 256); }   // rebased below
+            if (!lr.headed_bwd && dgrad_uses_wt(dtype, lr.g)) { lr.lowp_wt_off = lowp; lowp += align_up(lr.w_count * 2, 256); }   // rebased below
         }
         // A scaled layer whose weight-gradient kernel also sums the bias gradient keeps dz free of the scale: the bias
         // gradient is then the plain column sum of dz (eq. 8 for the bias), whatever the scale's value -- zero included.
@@ -143,15 +166,12 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
             lr.fcs_x_off = fcs;  fcs += align_up((size_t)LPM_FC_STAGE_SLOTS * lr.g.rows_in() * lr.g.Cin * 2, 256);
             lr.fcs_dz_off = fcs; fcs += align_up((size_t)LPM_FC_STAGE_SLOTS * lr.g.rows_out() * lr.g.Cout * 2, 256);
         }
-        kws = std::max(kws, align_up(dgrad_ws_bytes(dtype, lr.g), 256));
+        const size_t dws = lr.headed_bwd ? 0 : dgrad_ws_bytes(dtype, lr.g);      // (of the passes that the head's kernels perform, nothing is kept ready)
+        kws = std::max(kws, align_up(dws, 256));
         kws = std::max(kws, align_up(LPM_COUNT_BYTES + epi_bwd_ws_bytes(lr.g.rows_out(), l.cout), 256));
-        if (dgrad_ws_bytes(dtype, lr.g)) s->bwd_counts = true;
-        fws = std::max(fws, align_up(fwd_ws_bytes(dtype, lr.g), 256));
+        if (dws) s->bwd_counts = true;
+        if (!lr.headed_fwd) fws = std::max(fws, align_up(fwd_ws_bytes(dtype, lr.g), 256));
     }
-    auto uses = [&](int32_t t, int& n_src, int& n_add) {
-        n_src = n_add = 0;
-        for (int32_t j = std::max(t + 1, first); j < last; ++j) { n_src += s->net[(size_t)j].src == t; n_add += s->net[(size_t)j].add_src == t; }
-    };
     // Whether layer i's shortcut can take i's dz for its gradient instead of a copy: dz carries no scale, the shortcut is tensor a's
     // only one, and from then on the gradient of a is only read -- as the earlier contribution that the data gradient
     // of the block before adds in (a fused_side), or as the dz of a projection without ReLU and scale of its own.
@@ -271,20 +291,6 @@ extern "C" int32_t lpm_stage_create(const lpm_layer* layers, int32_t L, int32_t 
         if ((pl.h_in & 1) || (pl.w_in & 1) || !fwd_can_pool(dtype, lr.g)) continue;
         lr.pool_fwd = i + 1;
         s->Ly(i + 1).pooled_fwd = true;
-    }
-    // The head: an average pooling whose only reader is a plain layer over its channels.
-    for (int32_t i = first; i + 1 < last; ++i) {
-        if (s->net[(size_t)i].kind != LPM_GAP || i == s->t_out) continue;
-        LayerRt& fc = s->Ly(i + 1);
-        int n_src, n_add;
-        uses(i, n_src, n_add);
-        if (n_src != 1 || n_add != 0 || !has_weights(fc.d) || fc.d.src != i || (fc.d.flags & (LPM_RELU | LPM_SCALE)) || fc.d.add_src != LPM_NONE) continue;
-        if (fc.g.K() != fc.g.Cin || fc.g.rows_out() != microbatch) continue;
-        const int32_t hw = s->net[(size_t)i].h_in * s->net[(size_t)i].w_in;
-        fc.headed_fwd = head_ok(dtype, microbatch, hw, fc.g.Cin, fc.g.Cout, true);
-        fc.headed_bwd = head_ok(dtype, microbatch, hw, fc.g.Cin, fc.g.Cout, false);
-        if (fc.headed_fwd) s->Ly(i).head_fwd = i + 1;
-        if (fc.headed_bwd) s->Ly(i).head_bwd = i + 1;
     }
     // A projection and the layer of the block that stands beside it do not read each other's results: forward, the projection
     // and the layer before it; backward, where the projection's dz is there with that of the layer that adds it, those two.

@@ -221,6 +221,19 @@ def test_stage_layout(lpm):
     assert o_s * 4 >= s.grad_bytes
 
 
+def test_head_keeps_no_copy_of_its_weights(lpm):
+    """The layer behind an average pooling whose data gradient is the pooling's kernel reads its weights as they are: no transposed copy is kept up for
+    it, and no scratch of a split reduction cleared."""
+    def stage(relu):
+        b = wl.configs._Builder(512, 4, 4)
+        b.gap()
+        b.conv(16, 1, relu=relu)
+        return lpm.Stage(b.finish(), 0, 2, 32, lpm.BF16)
+    own, head = stage(True), stage(False)               # (behind a ReLU it has kernels of its own)
+    assert head.grad_bytes == own.grad_bytes and head.lowp_bytes == own.lowp_bytes - 16 * 512 * 2
+    assert head.fwd_ws_bytes == 256 and head.bwd_ws_bytes < own.bwd_ws_bytes
+
+
 def test_binding_rejects_undersized_operands(lpm):
     """The C ABI takes plain pointers, so the binding checks a tensor's size against the geometry before the library's
     kernels would read or write past its end (CPU tensors: the check comes before any GPU work)."""
