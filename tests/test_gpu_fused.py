@@ -4,7 +4,7 @@ beside other streams.  Each network is one or two stages with the gradient of th
 import numpy as np
 import pytest
 
-from harness import stage_backward_isolated
+from harness import compare, gpu_step, oracle_step, stage_backward_isolated
 
 pytestmark = pytest.mark.gpu
 
@@ -95,6 +95,27 @@ def test_head(lpm, m, c, n, h, w, dtype):
     layers = chain(C(8, c, 1, 1, h, w, scale=True), gap, C(c, n, 1, 1, 1, 1, relu=False))
     print("m", m, "channels", c, "outputs", n, "image", h, w, "dtype", dtype, flush=True)
     stage_backward_isolated(lpm, layers, [0, 3], m, m, dtype, seed=35, dx_wanted=True, check_forward=True, grad_std=1.0)
+
+
+# ... whose layer has no bias; with another reader of the pooling's input, whose gradient is there first; at the head of a stage, where it applies the
+# ReLU mask of the stage before, alone and to the sum with that reader's
+@pytest.mark.parametrize("starts", [(0, 1), (0,)], ids=["cut", "inside"])
+@pytest.mark.parametrize("beside", [True, False], ids=["reader", "alone"])
+@pytest.mark.parametrize("dtype", [0, 1], ids=["f32", "bf16"])
+def test_head_adds_and_masks(lpm, dtype, beside, starts):
+    m, c, n, h = 8, 24, 16, 4
+    gap = dict(kind="gap", cin=c, cout=c, kh=h, kw=h, stride=1, pad=0, h_in=h, w_in=h, relu=False, bias=False, scale=False, src=None, add_src=None, cut_after=False)
+    layers = [C(8, c, 1, 1, h, h), gap, C(c, n, 1, 1, 1, 1, relu=False, bias=False)]
+    layers = chain(*layers, *([C(c, n, h, h, h, h, relu=False, src=0, add=2)] if beside else []))
+    starts = list(starts) + [len(layers)]
+    print("dtype", dtype, "layers", len(layers), "starts", starts, flush=True)
+    if len(starts) == 2:
+        stage_backward_isolated(lpm, layers, starts, m, m, dtype, seed=39, dx_wanted=True, check_forward=True, grad_std=1.0)
+        return
+    o = oracle_step(layers, starts, 2 * m, 2, dtype == 1, seed=39, lr=0.05, mu=0.9)
+    for mode in (lpm.LOCKED, lpm.OVERLAPPED):
+        net = gpu_step(lpm, layers, starts, 2 * m, 2, dtype, o, 0.05, 0.9, mode)
+        compare(net, layers, starts, 2, dtype, o)
 
 
 # ... and the gradient of the pooled tensor is there to be read, as that of any tensor inside a stage, also where the gradient of the
