@@ -775,15 +775,16 @@ __global__ void __launch_bounds__(256) head_bwd_kernel(int HW, int C, int N, con
 
 // Channels in whole 16-byte chunks.  A sample of up to 64 KB and 128 outputs: one block walks either in a few round trips to memory.
 // With more samples or larger weights the blocks, each of which reads all of the layer's weights that it needs, take longer than the pooling and the
-// contraction, which reads them once a tile.  Kernel times, us, in two kernels / in one, where they are closest of 1 to 49 positions.  Forward, 128
-// outputs, bf16: 512 channels, 8 samples 7.4 / 6.9, 512 10.0 / 7.6, 1024 14.9 / 15.3, 2048 20.6 / 27.8; 2048 channels, 8 samples 11.1 / 15.0; one
-// output of 64 channels, 1024 samples 6.7 / 4.4, 2048 6.5 / 6.7, 4096 8.2 / 11.2.  Data gradient, 128 outputs: 1024 channels, 256 samples bf16
-// 6.6 / 6.0, float 9.2 / 9.1; 2048 channels 7.3 / 9.8 and 9.8 / 13.8.  From 512 samples on the blocks take room from the weight gradient beside
-// them (the captured pass, 64 channels, 10 outputs, one position, bf16 16.5 / 18.2).
+// contraction, which reads them once a tile.  In two kernels / in one, us, back to back in a graph, where they are closest of 33 to 128 outputs and 1
+// to 49 positions; a stream adds a gap of 1 to 3 between two kernels.  Forward: 768 channels, 256 samples bf16 9.0 / 8.7, float 14.4 / 9.4; 1024, 8 samples
+// 8.1 / 9.0 and 9.1 / 9.1, 256 10.2 / 9.8 and 15.1 / 16.9; 512, 1024 samples 14.8 / 16.0 and 20.3 / 19.4; 1536, 8 samples 10.1 / 11.4; 2048 10.6 / 13.4 and
+// 12.4 / 14.4.  One output of 64 channels, kernel times alone, bf16: 1024 samples 6.7 / 4.4, 2048 6.5 / 6.7, 4096 8.2 / 11.2.  Data gradient, kernel
+// times alone, 128 outputs: 1024 channels, 256 samples bf16 6.6 / 6.0, float 9.2 / 9.1; 2048 channels 7.3 / 9.8 and 9.8 / 13.8.  From 512 samples on the
+// blocks take room from the weight gradient beside them (the captured pass, 64 channels, 10 outputs, one position, bf16 16.5 / 18.2).
 bool head_ok(int dtype, int32_t m, int32_t HW, int32_t C, int32_t N, bool fwd) {
     if (C % (dtype == LPM_BF16 ? 8 : 4) != 0 || C > HEAD_C || N > 128 || (int64_t)HW * C * (dtype == LPM_BF16 ? 2 : 4) > 65536) return false;
-    const bool few = (int64_t)m * C <= (1 << 18);
-    return fwd ? m <= 1024 && (N <= 32 || (C <= 512 && few)) : m <= 256 && few;
+    const bool few = (int64_t)m * C < (1 << 18);
+    return fwd ? m <= 1024 && (N <= 32 || (C <= 1024 && few)) : m <= 256 && few;
 }
 hipError_t launch_head_fwd(int dtype, int32_t m, int32_t HW, int32_t C, int32_t N, const void* x, void* y, const void* w, const float* bias, void* z, hipStream_t s) {
     const int V = dtype == LPM_BF16 ? 8 : 4;

@@ -143,9 +143,9 @@ def test_end_of_a_forward_pass_comes_with_its_last_kernel(lanes):
     assert r.returncode == 0 and r.stdout.strip().endswith("[1, 1, 1, 1]"), r.stdout + r.stderr
 
 
-@pytest.mark.parametrize("m,hw,c,n,fwd,bwd", [(8, 1, 64, 10, 1, 1), (32, 16, 512, 10, 1, 1), (256, 16, 512, 128, 1, 1), (256, 1, 1024, 32, 1, 1), (257, 1, 8, 1, 1, 0),
-                                              (256, 1, 1032, 32, 1, 0), (1024, 1, 256, 128, 1, 0), (1025, 1, 64, 1, 0, 0), (512, 1, 520, 33, 0, 0),
-                                              (1024, 1, 264, 33, 0, 0), (8, 1, 520, 33, 0, 1), (8, 4, 2048, 100, 0, 1), (8, 16, 2048, 32, 1, 1)])
+@pytest.mark.parametrize("m,hw,c,n,fwd,bwd", [(8, 1, 64, 10, 1, 1), (32, 16, 512, 10, 1, 1), (256, 16, 512, 128, 1, 1), (255, 1, 1024, 33, 1, 1), (257, 1, 8, 1, 1, 0),
+                                              (256, 1, 1024, 33, 0, 0), (256, 1, 1024, 32, 1, 0), (1023, 1, 256, 128, 1, 0), (1024, 1, 256, 33, 0, 0),
+                                              (1024, 1, 2048, 32, 1, 0), (1025, 1, 64, 1, 0, 0), (8, 1, 1024, 128, 1, 1), (8, 1, 1032, 33, 0, 1), (8, 4, 2048, 100, 0, 1), (8, 16, 2048, 32, 1, 1)])
 def test_heads_that_share_a_kernel(lanes, m, hw, c, n, fwd, bwd):
     """... are those whose one kernel takes no longer than the pooling's and the contraction's: not with many samples, nor where every sample's block
     would read hundreds of kilobytes of weights.  (Up to 2048 channels and 128 outputs all of them did: 9 times the data gradient's time with 2048 samples.)"""
