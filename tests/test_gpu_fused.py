@@ -153,6 +153,33 @@ def test_gradient_of_the_pooled_tensor(lpm, m, c, n, h, w, dtype, dx_wanted):
         assert (np.abs(d - want) <= 2.0 ** (-8 if dtype else -23) * np.abs(want)).all()
 
 
+# ... and float sums are no further from the exact ones than those of the layer's own kernels: forward 64 running sums of c / 64 products, folded in
+# pairs, back 16 of n / 16, added in 64 bits.  A rounding is off by at most 2^-24 / sqrt(3) of its value (rms); a running sum of k terms of either sign gathers k / 2
+# of them, relative to the squared result, and so do all running sums together; a level of folding and the rounding to float one each.
+@pytest.mark.parametrize("c,n", [(1024, 32), (1000, 48), (512, 128)], ids=lambda v: str(v))
+def test_float_sums_of_the_head(lpm, c, n):
+    import torch
+    m = 16
+    gap = dict(kind="gap", cin=c, cout=c, kh=1, kw=1, stride=1, pad=0, h_in=1, w_in=1, relu=False, bias=False, scale=False, src=None, add_src=None, cut_after=False)
+    st = lpm.Stage(chain(gap, C(c, n, 1, 1, 1, 1, relu=False, bias=False)), 0, 2, m, 0)
+    print("channels", c, "outputs", n, flush=True)
+    rng = np.random.default_rng(41)
+    buf = lambda k: torch.zeros(max(k, 256), dtype=torch.uint8, device="cuda")      # noqa: E731
+    rnd = lambda *k: rng.normal(0, 1, k).astype(np.float32)      # noqa: E731
+    params, grads, stash, fws, bws, y, dx = [buf(k) for k in (st.param_bytes, st.grad_bytes, st.stash_bytes, st.fwd_ws_bytes, st.bwd_ws_bytes, st.out_bytes, st.in_bytes)]
+    x, w, dy = rnd(m, c), rnd(n, c), rnd(m, n)
+    off, _ = st.param_offset(1, 0)
+    params.view(torch.float32)[off:off + n * c] = torch.from_numpy(w).cuda().view(-1)
+    xd = torch.from_numpy(x).cuda()
+    st.forward(xd, y, None, None, params, None, stash, fws, 1.0)
+    st.backward(xd, y, torch.from_numpy(dy).cuda(), dx, params, None, stash, grads, False, bws)
+    torch.cuda.synchronize()
+    for got, a, b, bound in ((y, x, w.T, c / 128 + 7), (dx, dy, w, n / 32 + 1)):
+        want = a.astype(np.float64) @ b.astype(np.float64)
+        got = got.view(torch.float32)[:want.size].double().cpu().numpy().reshape(want.shape)
+        assert np.linalg.norm(got - want) <= 2.0 ** -24 / 3 ** 0.5 * bound ** 0.5 * np.linalg.norm(want)
+
+
 def bottlenecks(w, mid, h, m, shortcuts, first_scale=True):
     """Stem, then blocks 1x1 reduce - 1x1 expand + shortcut, then one more reduction that keeps the last block inside the stage.
     shortcuts: the tensor each block adds ('x': the block's input, 'in': the stage's)."""
