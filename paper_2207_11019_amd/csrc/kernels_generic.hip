@@ -794,17 +794,21 @@ __global__ void __launch_bounds__(256) head_bwd_kernel(int HW, int C, int N, con
 }
 
 // Channels in whole 16-byte chunks.  A sample of up to 64 KB and 128 outputs: one block walks either in a few round trips to memory.
-// With more samples or larger weights the blocks, each of which reads all of the layer's weights that it needs, take longer than the pooling and the
-// contraction, which reads them once a tile.  In two kernels / in one, us, back to back in a graph, where they are closest of 33 to 128 outputs and 1
-// to 49 positions; a stream adds a gap of 1 to 3 between two kernels.  Forward: 768 channels, 256 samples bf16 9.0 / 8.7, float 14.4 / 9.4; 1024, 8 samples
-// 8.1 / 9.0 and 9.1 / 9.1, 256 10.2 / 9.8 and 15.1 / 16.9; 512, 1024 samples 14.8 / 16.0 and 20.3 / 19.4; 1536, 8 samples 10.1 / 11.4; 2048 10.6 / 13.4 and
-// 12.4 / 14.4.  One output of 64 channels, kernel times alone, bf16: 1024 samples 6.7 / 4.4, 2048 6.5 / 6.7, 4096 8.2 / 11.2.  Data gradient, kernel
-// times alone, 128 outputs: 1024 channels, 256 samples bf16 6.6 / 6.0, float 9.2 / 9.1; 2048 channels 7.3 / 9.8 and 9.8 / 13.8.  From 512 samples on the
-// blocks take room from the weight gradient beside them (the captured pass, 64 channels, 10 outputs, one position, bf16 16.5 / 18.2).
+// Each block reads all of the layer's weights that it needs, the contraction reads them once a tile: with many samples or large weights one kernel takes
+// longer than two.  Kernel times in two / in one, us, over 1 to 128 outputs and 1 to 49 positions.  Forward, over 32 outputs, the worst: 512 channels x 512
+// samples bf16 9.3 / 7.0, x 1024 14.9 / 15.3, x 2048 20.6 / 27.8; 64 channels x 2048 bf16 1.15 of the time, float .80, x 4096 1.16; 768 channels x 256
+// (in a graph) bf16 9.0 / 8.7, float 14.4 / 9.4; 1024 channels x 128 bf16 9.0 / 8.2, float 13 / 11, x 256
+// float 15.2 / 18.8; 2048 channels x 8 bf16 11.1 / 15.0, float 12.3 / 15.2.  (768 to 1024 channels of a few samples take up to 1 us longer back to back in a graph, where
+// the gap between two kernels is hidden, and save a launch elsewhere.)  Up to 32 outputs, 64 channels, bf16 x 1024 6.7 / 4.4, x 2048 6.5 / 6.7,
+// x 4096 8.2 / 11.2 (float .71 of the time); 128 channels x 2048 .73 of the time, x 4096 1.08; 512 .86 and .97.  Data gradient, which reads a sixteenth of a row of weights
+// at a time and is soon bound by its stores: 16 positions and more .17 to .80 of the time at every size; one position, 128 outputs, 2^18 values bf16 .86 to .92,
+// float .85 to .99, 2^19 1.28 and 1.54.
 bool head_ok(int dtype, int32_t m, int32_t HW, int32_t C, int32_t N, bool fwd) {
     if (C % (dtype == LPM_BF16 ? 8 : 4) != 0 || C > HEAD_C || N > 128 || (int64_t)HW * C * (dtype == LPM_BF16 ? 2 : 4) > 65536) return false;
-    const bool few = (int64_t)m * C < (1 << 18);
-    return fwd ? m <= 1024 && (N <= 32 || (C <= 1024 && few)) : m <= 256 && few;
+    const bool few = (int64_t)m * C <= (1 << 18);
+    if (!fwd) return HW >= 16 || few;
+    const bool f32 = dtype == LPM_F32;
+    return N <= 32 ? m <= (f32 ? 4096 : 1024 + 8 * C) : few && m <= (f32 ? 2048 : 1024) && (C <= 768 || (C <= 1024 && m <= 192));
 }
 hipError_t launch_head_fwd(int dtype, int32_t m, int32_t HW, int32_t C, int32_t N, const void* x, void* y, const void* w, const float* bias, void* z, hipStream_t s) {
     const int V = dtype == LPM_BF16 ? 8 : 4;
