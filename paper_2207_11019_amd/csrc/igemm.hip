@@ -13,7 +13,8 @@
 // barrier per tile.  LDS rows are 128 bytes without padding; chunk c (16 bytes) of row r lies at position c ^ (r / 2 % 8), so the
 // operand reads of a wavefront (one chunk of 32 consecutive rows per half) fall on distinct banks: two rows span the 64 of them,
 // and rows of one parity share theirs (with c ^ (r % 8) half of them idled: 0.94 M conflict cycles in a launch of 3x3 256 -> 256
-// at 16 x 14^2, 0.01 M now; 128x128 tiles, 128 x 14^2 x 256 channels 3x3: 36.3 -> 34.6 us).  Out-of-range chunks -- padding taps, ragged
+// at 16 x 14^2, 0.01 M so, tap by tap; by filter rows, below, it has 0.26 M, of the lanes that read the row of zeros; 128x128 tiles, 128 x 14^2 x 256
+// channels 3x3: 36.3 -> 34.6 us).  Out-of-range chunks -- padding taps, ragged
 // rows -- load zeros through the buffer bounds check.  Whether a row meets a tap is one bit test against a mask made once per row.
 // A channel count that is a multiple of 128 bytes lets a whole K tile lie in one tap (UNI): the tap is wave-uniform.
 // Otherwise every lane follows its own chunk's tap through a table in LDS, so any multiple of 16 bytes of channels works.
@@ -718,6 +719,8 @@ static IgemmPlan plan_igemm(int es, int64_t M, int N, int kt, int unit) {
     // as many bytes again per product, which the products of float cover; bf16 in two parts on a full card stays (ResNet-18/CIFAR at 32 2719 / 2743).
     // Per step: float ResNet-18 at 4 / 8 / 16 samples 3026 / 2889, 2420 / 2376, 1705 / 1690, ResNet-18/CIFAR at 8 1991 / 1953, at 16 2135 / 2144
     // (LOCKED 1677 / 1651), of width 32 1034 / 1014, 48 2166 / 2147, VGG-16/CIFAR at 32 1172 / 1175, bottlenecks 128 wide at 8 655 / 641.
+    // Beyond the upper lines for 32x64, alone, us, 64x64 / so: bf16 in two parts, 208 to 256 tiles (26 to 32 x 8^2 x 256) 9.7 / 7.3, 216 (16 x 12^2 x 192) 9.1 / 6.4,
+    // which the step does not bear out; without parts, 270 (20 x 12^2 x 192) 7.2 / 9.1, 320 (40 x 8^2 x 256) 8.3 / 10.5, (20 x 16^2 x 128) 6.2 / 7.6.
     pl.alone = pl.tile;
     if (pl.tile == TILE_64 && pl.kt_total <= 40 && (pl.splits > 1 || (es == 2 && pl.kt_total >= 12))) {
         const int64_t t32 = tiles_of(TILE_32, M, N), t3264 = tiles_of(TILE_32x64, M, N);
@@ -765,7 +768,7 @@ static int k_tiles(int64_t taps, int ci, int es) { return (int)((taps * ci * es 
 static IgemmPlan plan_fwd(int dtype, const ConvGeom& g) {
     const int es = dtype == LPM_BF16 ? 2 : 4;
     IgemmPlan pl = plan_igemm(es, g.rows_out(), g.Cout, k_tiles(g.taps(), g.Cin, es), part_unit(es, g.Cin, g.Kw, g.stride, g.pad));
-    if (es == 2 && g.Wo == 32) pl.alone = pl.tile;      // (pooling windows of 32-wide images take two rows of 32 pixels)
+    if (es == 2 && g.Wo == 32) pl.alone = pl.tile;      // (pooling windows of 32-wide images take two rows of 32 pixels; the plan does not know which layers pool)
     return pl;
 }
 // taps a residue class of a strided data gradient meets at most
@@ -828,7 +831,8 @@ static hipError_t go_uni(const IgemmPlan& pl, const IgemmArgs& a, int64_t tiles,
     // tap by tap / so, in us: R50 conv4_x at 64 1621 / 1590, VGG-16/CIFAR 1800 / 1769, ResNet-18/CIFAR 2706 / 2637; without the split ones VGG-16/CIFAR
     // 1794, ResNet-18/CIFAR 2683).  With two blocks of 128x128 to a CU the registers do not suffice (4 x 112^2 x 128 20.5 / 23.6).
     // Larger tiles and longer sums keep their order: 1 % per step at most, and a forward sum in another order moves masks and maxima of the
-    // deep networks that make them.
+    // deep networks that make them.  Longer ones alone, tap by tap / so: 45 K tiles (16 x 14^2 x 320) 11.3 / 11.1; 54 (x 384) 18.8 / 15.8, at 16 x 16^2
+    // 16.1 / 16.5; 72 (32 x 8^2 x 512) 16.0 / 15.2, at 16 x 14^2 24.4 / 24.9, in parts of 36 (64 x 4^2) 13.5 / 13.2.
     if constexpr (sizeof(E) == 2 && MODE != MODE_DGRAD_S)
         if (by_rows(2, a.Ci, a.Kw, a.stride, a.pad) && (a.Ci == 64 ? pl.tile != TILE_128 && pl.tile != TILE_256 : TILE_M[pl.tile] <= 64 && (a.kt_total <= 40 || a.kt_per_split <= 24)))
             return go_tile<E, MODE, KT_ROW, BT>(pl, a, tiles, st);

@@ -641,7 +641,7 @@ hipError_t launch_gap_bwd(int dtype, int32_t m, int32_t HW, int32_t C, const voi
 // --------------------------------------------------------------------------------------------------
 // Global average pooling and the fully connected layer that alone reads it, the head of a residual network: one kernel forward and one for the
 // data gradient, where each had two of a few microseconds and next to no work on the chain that every micro-batch waits for (ResNet-18/CIFAR at 32 samples
-// a micro-batch: forward 4.3 + 6.2 us -> 5.7, data gradient 4.8 + 3.5 -> 6.1; per step 2634 -> 2584, float 2373 -> 2334, width 48 with 100 classes 2143 ->
+// a micro-batch, in a trace of the step: forward 4.3 + 6.2 us -> 5.1, data gradient 4.8 + 3.5 -> 3.9; per step 2634 -> 2584, float 2373 -> 2334, width 48 with 100 classes 2143 ->
 // 2123, volumetric 1598 -> 1588, 16 images forward 133.4 -> 130.2).  What bounds them is the launch and two round trips to memory.
 
 // A block takes a sample: its threads hold V channels of every RL-th position, then eight lanes share NB outputs of the layer at a time (whose
