@@ -806,7 +806,7 @@ __global__ void __launch_bounds__(256) head_bwd_kernel(int HW, int C, int N, con
 bool head_ok(int dtype, int32_t m, int32_t HW, int32_t C, int32_t N, bool fwd) {
     if (C % (dtype == LPM_BF16 ? 8 : 4) != 0 || C > HEAD_C || N > 128 || (int64_t)HW * C * (dtype == LPM_BF16 ? 2 : 4) > 65536) return false;
     const bool few = (int64_t)m * C <= (1 << 18);
-    if (!fwd) return HW >= 16 || few;
+    if (!fwd) return few || (HW >= 16 && m < (1 << 23));      // (a block of 256 threads a sample, and a launch holds fewer than 2^32 threads)
     const bool f32 = dtype == LPM_F32;
     return N <= 32 ? m <= (f32 ? 4096 : 1024 + 8 * C) : few && m <= (f32 ? 2048 : 1024) && (C <= 768 || (C <= 1024 && m <= 192));
 }

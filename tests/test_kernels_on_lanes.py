@@ -146,7 +146,8 @@ def test_end_of_a_forward_pass_comes_with_its_last_kernel(lanes):
 @pytest.mark.parametrize("m,hw,c,n,fwd,bwd", [(8, 1, 64, 10, 1, 1), (32, 16, 512, 10, 1, 1), (512, 16, 512, 128, 1, 1), (513, 1, 512, 33, 0, 0), (192, 1, 1024, 33, 1, 1),
                                               (193, 1, 1024, 33, 0, 1), (256, 1, 1024, 32, 1, 1), (257, 1, 1024, 32, 1, 0), (1024, 1, 256, 128, 1, 1),
                                               (2049, 1, 8, 33, 0, 1), (341, 1, 768, 33, 1, 1), (1088, 1, 8, 32, 1, 1), (4097, 15, 64, 10, 0, 0),
-                                              (4097, 16, 64, 10, 0, 1), (8, 1, 1032, 33, 0, 1), (8, 4, 2048, 100, 0, 1), (8, 16, 2048, 32, 1, 1)])
+                                              (4097, 16, 64, 10, 0, 1), (1 << 23, 16, 8, 10, 0, 0),
+                                              (8, 1, 1032, 33, 0, 1), (8, 4, 2048, 100, 0, 1), (8, 16, 2048, 32, 1, 1)])
 def test_heads_that_share_a_kernel(lanes, m, hw, c, n, fwd, bwd):
     """... are those whose one kernel takes no longer than the pooling's and the contraction's: not with many samples, nor where every sample's block
     would read hundreds of kilobytes of weights.  (Up to 2048 channels and 128 outputs all of them did: 9 times the data gradient's time with 2048 samples.)"""
