@@ -51,6 +51,8 @@ BF16 = [
     G(2, 7, 2, 64, 128, 3, 1, 1),         # ... two pixels a row
     G(1, 6, 7, 512, 512, 3, 1, 1),        # ... a reduction whose parts begin in the middle of a filter row's channels
     G3(2, 3, 5, 6, 128, 64, 3, 1, 1),     # ... volume
+    dict(G(2, 6, 7, 64, 72, 3, 1, 1), kh=2),                # ... filters of two and of five rows: images a row taller, or two shorter
+    dict(G(1, 6, 7, 128, 64, 3, 1, 1), kh=5),
     G(1, 147, 148, 64, 64, 3, 1, 1),      # ... 340 tiles of 64x64: three stages
     G(3, 127, 128, 64, 64, 3, 1, 1),      # ... 128x64
     G(2, 107, 109, 64, 200, 3, 1, 1),     # ... 128x128, three stages: forward
