@@ -842,7 +842,11 @@ static hipError_t go_uni(const IgemmPlan& pl, const IgemmArgs& a, int64_t tiles,
 
 hipError_t launch_zero_counts(void* const* heads, int n, hipStream_t st);
 
-struct IgemmCall { int dtype, mode, tiles; IgemmArgs a; IgemmPlan pl; };
+// Filter rows in pieces of a few channels (rows.hip): channels that make no whole K tiles.
+bool rows_take(const IgemmArgs& a, bool keep_order);
+hipError_t launch_rows(int mode, const IgemmArgs& a, hipStream_t st);
+
+struct IgemmCall { int dtype, mode, tiles; bool any_order; IgemmArgs a; IgemmPlan pl; };
 static_assert(sizeof(IgemmCall) <= sizeof(HeldCall::bytes), "room for a held call");
 
 // what follows from the plan's tile
@@ -866,8 +870,15 @@ static void lay_tiles(IgemmCall& c) {
     c.tiles = mt * nt;
 }
 
+// Whether the call goes by pieces (a reduction that blocks or wavefronts would share has another order of its own)
+static bool in_pieces(const IgemmCall& c) {
+    if (c.dtype != LPM_BF16 || c.mode == MODE_DGRAD_S || (!c.any_order && (c.pl.splits > 1 || c.pl.alone != c.pl.tile))) return false;
+    return rows_take(c.a, !c.any_order);
+}
+
 static hipError_t go_call(IgemmCall c, hipStream_t st) {
     IgemmArgs& a = c.a;
+    if (in_pieces(c)) return launch_rows(c.mode, a, st);
     if (c.pl.alone != c.pl.tile) {
         c.pl.tile = c.pl.alone;
         c.pl.splits = a.splits = 1;
@@ -936,8 +947,8 @@ static hipError_t run_pair(IgemmCall x, IgemmCall y, hipStream_t st) {
 }
 
 // hold, with: see HeldCall
-static hipError_t run_igemm(int dtype, int mode, const IgemmArgs& args, const IgemmPlan& pl, void* ws, bool ws_zeroed, hipStream_t st, HeldCall* hold, HeldCall* with) {
-    IgemmCall c{dtype, mode, 0, args, pl};
+static hipError_t run_igemm(int dtype, int mode, const IgemmArgs& args, const IgemmPlan& pl, void* ws, bool ws_zeroed, bool any_order, hipStream_t st, HeldCall* hold, HeldCall* with) {
+    IgemmCall c{dtype, mode, 0, any_order, args, pl};
     IgemmArgs& a = c.a;
     const int es = dtype == LPM_BF16 ? 2 : 4;
     a.Di = std::max(a.Di, 1); a.Dr = std::max(a.Dr, 1); a.Kd = std::max(a.Kd, 1);
@@ -950,7 +961,8 @@ static hipError_t run_igemm(int dtype, int mode, const IgemmArgs& args, const Ig
         a.count = (unsigned*)ws;
         a.part = (float*)((char*)ws + LPM_COUNT_BYTES);
         if (c.tiles > (int64_t)(LPM_COUNT_BYTES / 4) || c.tiles > pl.tiles) return hipErrorInvalidValue;      // (the plan's cap keeps this out)
-        if (!ws_zeroed && (pl.alone == pl.tile || hold || with)) {
+        const bool parts = pl.alone == pl.tile && !in_pieces(c);
+        if (!ws_zeroed && (parts || hold || with)) {
             const hipError_t e = launch_zero_counts(&ws, 1, st);
             if (e != hipSuccess) return e;
         }
@@ -1001,7 +1013,7 @@ hipError_t mfma_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void
     a.a_bytes = (unsigned)(g.rows_in() * g.Cin * es);
     a.b_pitch = (unsigned)((int64_t)g.K() * es);
     a.b_bytes = (unsigned)((int64_t)g.Cout * g.K() * es);
-    return run_igemm(dtype, MODE_FWD, a, plan_fwd(dtype, g), ws, ws_zeroed, st, hold, with);
+    return run_igemm(dtype, MODE_FWD, a, plan_fwd(dtype, g), ws, ws_zeroed, g.any_order, st, hold, with);
 }
 
 // wt: weights laid out [Cin][taps][Cout] (bf16); float layers pass w itself, [Cout][taps][Cin]
@@ -1033,7 +1045,7 @@ hipError_t mfma_conv_dgrad(int dtype, const ConvGeom& g, const void* dz, const v
     a.a_bytes = (unsigned)(g.rows_out() * g.Cout * es);
     a.b_pitch = (unsigned)((int64_t)g.taps() * (dtype == LPM_BF16 ? g.Cout : g.Cin) * es);
     a.b_bytes = (unsigned)((int64_t)g.Cout * g.K() * es);
-    return run_igemm(dtype, unpool ? MODE_UNPOOL : g.stride > 1 ? MODE_DGRAD_S : MODE_DGRAD, a, plan_dgrad(dtype, g), ws, ws_zeroed, st, hold, with);
+    return run_igemm(dtype, unpool ? MODE_UNPOOL : g.stride > 1 ? MODE_DGRAD_S : MODE_DGRAD, a, plan_dgrad(dtype, g), ws, ws_zeroed, g.any_order, st, hold, with);
 }
 
 // clears the arrival counts at the head of up to 16 scratch areas

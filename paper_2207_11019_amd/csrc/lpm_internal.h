@@ -87,6 +87,9 @@ inline int32_t taps_of(const lpm_layer& l) { return (l.kd > 0 ? l.kd : 1) * l.kh
 struct ConvGeom {
     int32_t m, H, W, Cin, Ho, Wo, Cout, Kh, Kw, stride, pad;
     int32_t D = 1, Do = 1, Kd = 1, pad_d = 0;
+    // Whether the call's sums may be added up in another order than a network's layers keep (a single contraction's caller gets its rounded
+    // result either way; inside a deep network another order moves masks and maxima, and with them gradients by a per mille).
+    bool any_order = false;
     __host__ __device__ int64_t rows_out() const { return (int64_t)m * Do * Ho * Wo; }
     __host__ __device__ int64_t rows_in() const { return (int64_t)m * D * H * W; }
     __host__ __device__ int32_t K() const { return Kd * Kh * Kw * Cin; }

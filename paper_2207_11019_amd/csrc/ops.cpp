@@ -17,6 +17,7 @@ static int32_t to_geom(const lpm_conv_geom* g, int32_t dtype, ConvGeom& out) {
     // volumetric form (0 in d / kd means 1)
     const int32_t d = g->d > 0 ? g->d : 1, kd = g->kd > 0 ? g->kd : 1;
     if (g->d < 0 || g->kd < 0 || g->pad_d < 0 || g->pad_d >= kd || d + 2 * g->pad_d - kd < 0) return fail(LPM_ESHAPE, "bad depth geometry");
+    out.any_order = true;
     out.D = d; out.Kd = kd; out.pad_d = g->pad_d; out.Do = (d + 2 * g->pad_d - kd) / g->stride + 1;
     return LPM_OK;
 }

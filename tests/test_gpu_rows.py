@@ -1,0 +1,75 @@
+"""Contractions by filter rows in pieces of 32 or 48 channels (filters three wide whose channels are no whole K tiles): every tile, both
+pieces, ragged last pieces, images of one and two pixels a row, volumes, filters of other heights, pooling in front and behind."""
+import pytest
+
+import test_gpu_contractions as contractions
+from harness import stage_backward_isolated
+from test_gpu_conv import G, G3
+from test_gpu_fused import C, P, chain
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    G(2, 13, 6, 32, 96, 3, 1, 1),         # 128x32, pieces of 32 channels: one and three of them
+    G(1, 11, 12, 160, 224, 3, 1, 1),      # ... five and seven, one row of tiles and a ragged one
+    G(2, 9, 9, 48, 144, 3, 1, 1),         # ... pieces of 48
+    G(1, 12, 11, 80, 136, 3, 1, 1),       # ... the last one ragged
+    G(2, 7, 9, 16, 24, 3, 1, 1),          # ... the only one
+    G(1, 8, 17, 56, 104, 3, 1, 1),        # ... ragged pieces of 32
+    G(3, 5, 1, 40, 32, 3, 1, 1),          # both outer taps beside the image everywhere
+    G(2, 1, 9, 96, 72, 3, 1, 1),          # one image row
+    G(2, 7, 2, 32, 160, 3, 1, 1),         # two pixels a row
+    G(1, 1, 1, 32, 48, 3, 1, 1),          # one pixel
+    G3(2, 3, 5, 6, 32, 48, 3, 1, 1),      # volume
+    G3(1, 2, 4, 3, 96, 32, 3, 1, 1),
+    dict(G(2, 6, 7, 32, 72, 3, 1, 1), kh=2),
+    dict(G(1, 6, 7, 160, 48, 3, 1, 1), kh=5),
+    G(2, 20, 20, 128, 24, 3, 1, 1),       # whole K tiles, half a tile of outputs
+    G(1, 9, 9, 352, 416, 3, 1, 1),        # too long for the few tiles: as before
+    G(2, 115, 114, 160, 160, 3, 1, 1),    # 256x32
+    G(2, 230, 231, 24, 32, 3, 1, 1),      # ... one column
+    G(2, 100, 98, 32, 104, 3, 1, 1),      # 256x64, eight wavefronts
+    G(2, 100, 98, 104, 40, 3, 1, 1),      # ... of the data gradient
+    G(3, 120, 122, 32, 104, 3, 1, 1),     # 256x64, four
+    G(3, 120, 122, 104, 32, 3, 1, 1),
+    G(3, 113, 114, 32, 96, 3, 1, 1),      # 128x96
+    G(3, 113, 114, 96, 88, 3, 1, 1),      # ... ragged N; of the data gradient, pieces of 48
+    G(3, 113, 114, 48, 96, 3, 1, 1),      # ... pieces of 48
+]
+
+
+@pytest.fixture(scope="module")
+def lpm():
+    import torch
+    assert torch.cuda.is_available()
+    import paper_2207_11019_amd as lpm
+    return lpm
+
+
+@pytest.mark.parametrize("g", SHAPES, ids=lambda g: contractions._id(("bf16", g)) + ("_r%d" % g["kh"] if g["kh"] != g["kw"] else ""))
+def test_contractions_by_rows_in_pieces(lpm, g):
+    contractions.test_contractions(lpm, ("bf16", g))
+
+
+def test_pooling_between_rows_in_pieces(lpm):
+    """Images of 32, 16 and 8 pixels a row, pooled by the kernels that make them; gradients routed back."""
+    layers = chain(C(40, 48, 3, 3, 32, 32, p=1), P(48, 32, 32), C(48, 96, 3, 3, 16, 16, p=1), P(96, 16, 16), C(96, 32, 3, 3, 8, 8, p=1, scale=True))
+    stage_backward_isolated(lpm, layers, [0, 5], 2, 2, 1, seed=41, dx_wanted=True, check_forward=True, grad_std=1.0)
+
+
+# images in a micro-batch, channels: tiles of 256x64 (eight wavefronts, four), 128x96 (pieces of 32 and 48) and 256x32
+LARGE = [(20, 32, 104), (43, 32, 104), (38, 32, 96), (38, 48, 96), (101, 24, 32)]
+
+
+@pytest.mark.parametrize("m,ci,c", LARGE, ids=lambda v: str(v))
+def test_pooling_of_32_wide_images_in_pieces(lpm, m, ci, c):
+    layers = chain(C(ci, c, 3, 3, 32, 32, p=1), P(c, 32, 32), C(c, 16, 1, 1, 16, 16, scale=True))
+    print("m", m, "channels", ci, c, flush=True)
+    stage_backward_isolated(lpm, layers, [0, 3], m, m, 1, seed=43, dx_wanted=True, check_forward=True, grad_std=1.0)
+
+
+@pytest.mark.parametrize("m,ci,c", LARGE, ids=lambda v: str(v))
+def test_pooling_backward_of_rows_in_pieces(lpm, m, ci, c):
+    layers = chain(C(8, c, 1, 1, 64, 64), P(c, 64, 64), C(c, ci, 3, 3, 32, 32, p=1, scale=True))
+    print("m", m, "channels", c, ci, flush=True)
+    stage_backward_isolated(lpm, layers, [0, 3], m, m, 1, seed=47, dx_wanted=True, check_forward=True, grad_std=1.0)
