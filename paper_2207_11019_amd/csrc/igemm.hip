@@ -204,25 +204,29 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     int4 l_e = make_int4(0, 0, 0, 0);        // the tap's table entry, fetched a tile ahead
     if constexpr (ROW) {
         per = Cc / 8;
-        const int g = kt0 / 3, t = div_by(g, p.dKt);            // (a block's part begins with a filter row)
-        c_c = (unsigned)(g - t * per);
+        if (kt0) {
+            const int g = kt0 / 3, t = div_by(g, p.dKt);            // (a block's part begins with a filter row)
+            c_c = (unsigned)(g - t * per);
+            c_td = p.Kd > 1 ? t / p.Kh : 0;
+            c_th = t - c_td * p.Kh;
+        }
         run = min(per - (int)c_c, nk / 3);
-        c_td = p.Kd > 1 ? t / p.Kh : 0;
-        c_th = t - c_td * p.Kh;
     } else if (UNI) {
         per = Cc / 8;
-        const int t = div_by(kt0, p.dKt);
-        c_c = (unsigned)(kt0 - t * per);
-        run = min(per - (int)c_c, nk);
-        if (MODE != MODE_DGRAD_S) {
-            c_td = div_by(t, p.dKhw);
-            const int r = t - c_td * nkh * nkw;
-            c_th = div_by(r, p.dKw); c_tw = r - c_th * nkw;
-        } else if (t > 0) {
-            c_td = t / (nkh * nkw);
-            const int r = t - c_td * nkh * nkw;
-            c_th = r / nkw; c_tw = r - c_th * nkw;
+        if (kt0) {
+            const int t = div_by(kt0, p.dKt);
+            c_c = (unsigned)(kt0 - t * per);
+            if (MODE != MODE_DGRAD_S) {
+                c_td = div_by(t, p.dKhw);
+                const int r = t - c_td * nkh * nkw;
+                c_th = div_by(r, p.dKw); c_tw = r - c_th * nkw;
+            } else if (t > 0) {
+                c_td = t / (nkh * nkw);
+                const int r = t - c_td * nkh * nkw;
+                c_th = r / nkw; c_tw = r - c_th * nkw;
+            }
         }
+        run = min(per - (int)c_c, nk);
     } else {
         const int k = kt0 * 8 + kcol;
         l_t = div_by(k, p.dCc); l_c = k - l_t * Cc;
@@ -237,7 +241,11 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     // tile.  (They and the mask bit move on by differences: as sums of products they cost 80 ns of scalar arithmetic at every tap.)
     unsigned dA = 128, dB = BT ? (unsigned)kt_ch * p.b_pitch : 128u;                 // to the next K tile of the tap
     const unsigned tapA = tapC, tapB = BT ? (unsigned)p.Ci * p.b_pitch : tapC;       // what a tap's K tiles add up to
-    unsigned a_cur[A_N], la = aoff0 + c_td * aD + c_th * aH + c_tw * aW + c_c * dA, lb = b0 + c_td * bD + c_th * bH + c_tw * bW + c_c * dB;
+    unsigned a_cur[A_N], la = aoff0, lb = b0;
+    if (UNI && kt0) {                        // (a part further on begins elsewhere)
+        la += c_td * aD + c_th * aH + c_tw * aW + c_c * dA;
+        lb += c_td * bD + c_th * bH + c_tw * bW + c_c * dB;
+    }
     unsigned b_tap = tapC, b_chunk = dB - 2 * tapC;                                  // ROW: to the next tap of the row, from its last tap to the next channels' first
     unsigned bit = p.free_taps ? 1u : (1u << (24 + c_td)) | (1u << (12 + c_th)) | (1u << c_tw);
     const unsigned aWn = aW - tapA, bWn = bW - tapB;                                                          // the next tap of the row
@@ -358,6 +366,33 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
         }
     };
 
+    // Operands of one K tile, 16 bytes per lane and step.  While the matrix cores work on one tile the next one is read from LDS,
+    // and the tiles behind it are on their way there -- with one wavefront per SIMD (a launch of about one block per CU) nothing else
+    // hides the LDS latency.  Two sets of them, or (TWO false) the next tile's over those of a step just multiplied: with two
+    // wavefronts per SIMD, or float's longer products, the reads are covered all the same and the registers go to other streams'
+    // wavefronts (float ResNet-18 2640 -> 2566 us per step, VGG-16/224 6640 -> 6575; the 64x64 tiles lose: R50 conv4_x at 64 1650 -> 1715).
+    // A float data gradient reads its weights in four pieces of 4 bytes, which takes longer: two sets where a K tile lies in one tap (one / two:
+    // a stage 480 -> 256 channels at 4 x 37^2 561 / 535 us, 512 -> 512 at 6 x 9^2 189 / 181, ResNet-18 at 4 / 9 / 16 samples 1.3-1.6 % less;
+    // alone, a lone layer's 256 -> 256 at 16 x 14^2 loses 1 %).  In chunks across taps the second set costs a third block per CU its
+    // registers: 64 -> 24 channels at 72 x 36 x 35, stride 2, 66.7 / 70.2.
+    constexpr bool TWO = ES == 4 ? BT != BT_NONE && UNI : !(BM == 128 && BN == 128 && WGN == 4);
+    constexpr bool DRAIN = TWO || NST < 4;
+    constexpr int AHEAD = DRAIN ? NST : NST - 1;             // tiles between the one multiplied and the one being loaded
+    // The first tiles are on their way before anything else is worked out: what follows, operand addresses and the epilogue's, costs as long
+    // as they take to arrive.
+    if (nk > 0) {
+        if constexpr (ROW) {
+            static_assert(!ROW || DRAIN, "A's ring is as long as that takes");
+#pragma unroll
+            for (int q = 0; q < 8; ++q) issue(-1, 1 + q / 4, q % 4);
+        }
+#pragma unroll
+        for (int i = 0; i < AHEAD - 1; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) issue(i, i, q);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
     f32x16 acc[MI][NI];
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
@@ -396,16 +431,6 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     for (int ks = 0; ks < (KS ? KSW : 0); ++ks) ks_c[ks] = (kt0 * kt_ch + ((kg * KSW + ks) * 2 + kh_) * 4) % p.Ci;
     const int ks_step = KS ? kt_ch % p.Ci : 0;
 
-    // Operands of one K tile, 16 bytes per lane and step.  While the matrix cores work on one tile the next one is read from LDS,
-    // and the tiles behind it are on their way there -- with one wavefront per SIMD (a launch of about one block per CU) nothing else
-    // hides the LDS latency.  Two sets of them, or (TWO false) the next tile's over those of a step just multiplied: with two
-    // wavefronts per SIMD, or float's longer products, the reads are covered all the same and the registers go to other streams'
-    // wavefronts (float ResNet-18 2640 -> 2566 us per step, VGG-16/224 6640 -> 6575; the 64x64 tiles lose: R50 conv4_x at 64 1650 -> 1715).
-    // A float data gradient reads its weights in four pieces of 4 bytes, which takes longer: two sets where a K tile lies in one tap (one / two:
-    // a stage 480 -> 256 channels at 4 x 37^2 561 / 535 us, 512 -> 512 at 6 x 9^2 189 / 181, ResNet-18 at 4 / 9 / 16 samples 1.3-1.6 % less;
-    // alone, a lone layer's 256 -> 256 at 16 x 14^2 loses 1 %).  In chunks across taps the second set costs a third block per CU its
-    // registers: 64 -> 24 channels at 72 x 36 x 35, stride 2, 66.7 / 70.2.
-    constexpr bool TWO = ES == 4 ? BT != BT_NONE && UNI : !(BM == 128 && BN == 128 && WGN == 4);
     struct Frag { uint4 a[KSW][MI], b[KSW][NI]; };
     // (tile u: its place in the filter row, where that counts)
     auto read = [&](Frag& f, int st, int u, int ks) __attribute__((always_inline)) {
@@ -461,8 +486,6 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     // A tile has landed once only the loads of the tiles behind it are outstanding.  DRAIN: the stage of the tile being multiplied
     // is loaded again behind the barrier, so every wavefront's operand reads are complete before it; with a stage more, the one loaded
     // again is that of the tile before, whose operands have been multiplied, and the reads under way need not be waited for.
-    constexpr bool DRAIN = TWO || NST < 4;
-    constexpr int AHEAD = DRAIN ? NST : NST - 1;             // tiles between the one multiplied and the one being loaded
     auto meet = [&]() __attribute__((always_inline)) {
         LPM_WAIT_VM(LPT * (AHEAD - 2));
         if (DRAIN) __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt(0)
@@ -480,15 +503,6 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     const bool early = Ep::R <= EARLY_ROWS && (!SPLITS || p.splits == 1);
     if (early && !kg) ep.load(p, er0, ec0, rows, lane, Hc, Wc, ph, pw, Dc, pd);
     if (nk > 0) {
-        if constexpr (ROW) {
-            static_assert(!ROW || DRAIN, "A's ring is as long as that takes");
-#pragma unroll
-            for (int q = 0; q < 8; ++q) issue(-1, 1 + q / 4, q % 4);
-        }
-#pragma unroll
-        for (int i = 0; i < AHEAD - 1; ++i)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) issue(i, i, q);
         Frag f0;
         meet();
 #pragma unroll

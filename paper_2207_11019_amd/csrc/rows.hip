@@ -124,6 +124,11 @@ __global__ void __launch_bounds__(WGM * WGN * 64, 2) rows_kernel(const IgemmArgs
         if (part == KS - 1) next_stage();
     };
 
+    // (the first stage is on its way before anything else is worked out)
+#pragma unroll
+    for (int q = 0; q < KS; ++q) issue(0, q);
+    __builtin_amdgcn_sched_barrier(0);
+
     f32x16 acc[MI][NI];
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
@@ -180,8 +185,6 @@ __global__ void __launch_bounds__(WGM * WGN * 64, 2) rows_kernel(const IgemmArgs
     const int er0 = m0 + wm * WTM, ec0 = n0 + wn * WTN;
     constexpr bool early = Ep::R <= 2 && EN == NI;             // (the epilogue's operands arrive under the main loop where the registers allow)
     if (early) ep.load(p, er0, ec0, rows, lane, 0, 0, 0, 0, 0, 0);
-#pragma unroll
-    for (int q = 0; q < KS; ++q) issue(0, q);
     meet();
 #pragma unroll
     for (int q = 0; q < LA; ++q) {
