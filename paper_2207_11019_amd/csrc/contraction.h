@@ -41,7 +41,10 @@ struct IgemmArgs {
     unsigned a_bytes, b_bytes, b_pitch;
     int kt_total, kt_per_split, splits;
     int free_taps;          // no tap can leave the image: no mask bits needed
-    int cls_tile0[17];      // strided data gradient: first row tile of class c = (pd * s + ph) * s + pw
+    // strided data gradient: first row tile of residue class c = (pd * s + ph) * s + pw, images, the stride, and the two extents that a class
+    // can have along an axis: whole strides, and one more
+    int cls_tile0[17], images;
+    FastDiv dS, dWc[2], dHc[2], dDc[2];
     const uint16_t* pool_x; // stride-1 data gradient routed through a 2x2 max-pooling (see UnpoolDesc): its input [m][2*Hr][2*Wr][N]
     uint16_t* pool_dst;
     int pool_acc, pool_mask;
@@ -74,9 +77,10 @@ __device__ __forceinline__ void st8(float* p, const float (&f)[8]) {
 
 // Strided data gradient: pixel index (in the full tensor) of row `row` of the residue class (pd, ph, pw).
 __device__ __forceinline__ int class_pixel(const IgemmArgs& p, int row, int Hc, int Wc, int ph, int pw, int Dc, int pd) {
-    const int wq = row % Wc, t = row / Wc, hq = t % Hc;
-    int n = t / Hc, img = n;
-    if (p.Dr > 1) { const int dq = n % Dc; n /= Dc; img = n * p.Dr + dq * p.stride + pd; }
+    const int t = div_by(row, p.dWc[Wc - div_by(p.Wr, p.dS)]), wq = row - t * Wc;
+    int n = div_by(t, p.dHc[Hc - div_by(p.Hr, p.dS)]), img = n;
+    const int hq = t - n * Hc;
+    if (p.Dr > 1) { const int ns = div_by(n, p.dDc[Dc - div_by(p.Dr, p.dS)]), dq = n - ns * Dc; n = ns; img = n * p.Dr + dq * p.stride + pd; }
     return (img * p.Hr + hq * p.stride + ph) * p.Wr + wq * p.stride + pw;
 }
 

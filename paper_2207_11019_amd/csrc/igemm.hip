@@ -92,26 +92,35 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     int oh = p.pad, ow = p.pad, od = p.pad_d;
     const int Cc = p.Ci * ES / 16;                                                      // chunks per tap
     if (MODE == MODE_DGRAD_S) {
-        const int s_ = p.stride, ncls = (p.Dr > 1 ? s_ : 1) * s_ * s_;
+        // (divisions by the stride and by a class's extents are multiplications, the class's number a sum: an instruction sequence each, with
+        // its own wait for its arguments, they had taken 1.5 us before the first load)
+        const int s_ = p.stride, s3 = p.Dr > 1 ? s_ : 1;
         int c = 0;
-        while (c + 1 < ncls && tm >= p.cls_tile0[c + 1]) ++c;
-        pd = c / (s_ * s_);
-        ph = (c - pd * s_ * s_) / s_; pw = c - (pd * s_ + ph) * s_;
-        Hc = (p.Hr - ph + s_ - 1) / s_; Wc = (p.Wr - pw + s_ - 1) / s_;
-        Dc = p.Dr > 1 ? (p.Dr - pd + s_ - 1) / s_ : 1;
-        rows = (p.M / (p.Dr * p.Hr * p.Wr)) * Dc * Hc * Wc;
+#pragma unroll
+        for (int k = 1; k < 16; ++k) c += tm >= p.cls_tile0[k];      // (past the last class they hold the number of tiles)
+        const int pq = div_by(c, p.dS);
+        pw = c - pq * s_;
+        pd = div_by(pq, p.dS);
+        ph = pq - pd * s_;
+        Hc = div_by(p.Hr - ph + s_ - 1, p.dS); Wc = div_by(p.Wr - pw + s_ - 1, p.dS);
+        Dc = p.Dr > 1 ? div_by(p.Dr - pd + s_ - 1, p.dS) : 1;
+        rows = p.images * Dc * Hc * Wc;
         m0 = (tm - p.cls_tile0[c]) * BM;
         kstep = s_;
-        kh0 = (ph + p.pad) % s_; kw0 = (pw + p.pad) % s_;
-        kd0 = p.Dr > 1 ? (pd + p.pad_d) % s_ : 0;
-        nkh = kh0 < p.Kh ? (p.Kh - kh0 + s_ - 1) / s_ : 0;
-        nkw = kw0 < p.Kw ? (p.Kw - kw0 + s_ - 1) / s_ : 0;
-        nkd = p.Dr > 1 ? (kd0 < p.Kd ? (p.Kd - kd0 + s_ - 1) / s_ : 0) : 1;
         // output pixel = class coordinate + (ph + pad - kh) / stride, an exact quotient that falls by one per visited tap
-        oh = (ph + p.pad - kh0) / s_; ow = (pw + p.pad - kw0) / s_; od = p.Dr > 1 ? (pd + p.pad_d - kd0) / s_ : 0;
-        const int kt_cls = (nkd * nkh * nkw * Cc + 7) / 8, per = (kt_cls + p.splits - 1) / p.splits;
-        kt0 = bz * per;
-        kt1 = min(kt_cls, kt0 + per);
+        oh = div_by(ph + p.pad, p.dS); ow = div_by(pw + p.pad, p.dS); od = s3 > 1 ? div_by(pd + p.pad_d, p.dS) : 0;
+        kh0 = ph + p.pad - oh * s_; kw0 = pw + p.pad - ow * s_;
+        kd0 = s3 > 1 ? pd + p.pad_d - od * s_ : 0;
+        nkh = kh0 < p.Kh ? div_by(p.Kh - kh0 + s_ - 1, p.dS) : 0;
+        nkw = kw0 < p.Kw ? div_by(p.Kw - kw0 + s_ - 1, p.dS) : 0;
+        nkd = s3 > 1 ? (kd0 < p.Kd ? div_by(p.Kd - kd0 + s_ - 1, p.dS) : 0) : 1;
+        kt0 = 0;
+        kt1 = (nkd * nkh * nkw * Cc + 7) / 8;
+        if (p.splits > 1) {
+            const int per = (kt1 + p.splits - 1) / p.splits;
+            kt0 = bz * per;
+            kt1 = min(kt1, kt0 + per);
+        }
     }
     const int ntap = nkd * nkh * nkw, nk = max(0, kt1 - kt0);
     const unsigned tapC = (unsigned)p.Ci * ES;                       // bytes of one tap's channels
@@ -146,6 +155,12 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     // rows): it fetches chunk (l % 8) ^ (r / 2 % 8)
     const int lrow = lane >> 3, kcol = (lane & 7) ^ ((wave & 1) * 4 + (lrow >> 1));
     unsigned a_base[A_N], a_msk[A_N], b_off[B_LD];
+    FastDiv dWc{}, dHc{}, dDc{};
+    if (MODE == MODE_DGRAD_S) {
+        dWc = p.dWc[Wc - div_by(p.Wr, p.dS)];
+        dHc = p.dHc[Hc - div_by(p.Hr, p.dS)];
+        if (p.Dr > 1) dDc = p.dDc[Dc - div_by(p.Dr, p.dS)];
+    }
 #pragma unroll
     for (int i = 0; i < A_N; ++i) {
         const int pos = i * RS + wave * 8 + lrow, row = ROW ? m0 - 1 + pos : m0 + pos;
@@ -153,10 +168,11 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
         const int rr = ok ? row : 0;
         int wq, hq, n, dq = 0;
         if (MODE == MODE_DGRAD_S) {
-            wq = rr % Wc;
-            const int t = rr / Wc;
-            hq = t % Hc; n = t / Hc;
-            if (p.Dr > 1) { const int ns = n / Dc; dq = n - ns * Dc; n = ns; }
+            const int t = div_by(rr, dWc);
+            wq = rr - t * Wc;
+            n = div_by(t, dHc);
+            hq = t - n * Hc;
+            if (p.Dr > 1) { const int ns = div_by(n, dDc); dq = n - ns * Dc; n = ns; }
         } else {
             const int t = div_by(rr, p.dWr);
             wq = rr - t * p.Wr;
@@ -879,6 +895,9 @@ static void lay_tiles(IgemmCall& c) {
             mt += (int)((m * Dc * Hc * Wc + bm - 1) / bm);
         }
         for (int k = ncls; k <= 16; ++k) a.cls_tile0[k] = mt;
+        a.images = (int)m;
+        a.dS = fast_div(s);
+        for (int k = 0; k < 2; ++k) { a.dWc[k] = fast_div(a.Wr / s + k); a.dHc[k] = fast_div(a.Hr / s + k); a.dDc[k] = fast_div(a.Dr / s + k); }
     }
     a.dNt = fast_div(nt);
     c.tiles = mt * nt;

@@ -73,3 +73,11 @@ def test_pooling_backward_of_rows_in_pieces(lpm, m, ci, c):
     layers = chain(C(8, c, 1, 1, 64, 64), P(c, 64, 64), C(c, ci, 3, 3, 32, 32, p=1, scale=True))
     print("m", m, "channels", c, ci, flush=True)
     stage_backward_isolated(lpm, layers, [0, 3], m, m, 1, seed=47, dx_wanted=True, check_forward=True, grad_std=1.0)
+
+
+# residue classes of images of fewer pixels than strides, of whole strides and one more, of a volume's slices
+@pytest.mark.parametrize("g", [G(2, 1, 3, 32, 64, 3, 2, 1), G(1, 3, 2, 32, 40, 5, 4, 2), G(2, 9, 10, 64, 32, 3, 3, 1), G(1, 8, 13, 40, 24, 7, 4, 3),
+                               G3(1, 1, 2, 3, 32, 64, 3, 2, 1), G3(2, 4, 5, 2, 32, 24, 3, 2, 1)], ids=lambda g: contractions._id(("", g)))
+@pytest.mark.parametrize("name", ["bf16", "f32"])
+def test_strided_data_gradients_of_small_images(lpm, name, g):
+    contractions.test_contractions(lpm, (name, g))
