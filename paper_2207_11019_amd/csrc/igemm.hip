@@ -94,7 +94,7 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
     if (MODE == MODE_DGRAD_S) {
         // (divisions by the stride and by a class's extents are multiplications, the class's number a sum: an instruction sequence each, with
         // its own wait for its arguments, they had taken 1.5 us before the first load)
-        const int s_ = p.stride, s3 = p.Dr > 1 ? s_ : 1;
+        const int s_ = p.stride;
         int c = 0;
 #pragma unroll
         for (int k = 1; k < 16; ++k) c += tm >= p.cls_tile0[k];      // (past the last class they hold the number of tiles)
@@ -108,12 +108,12 @@ __device__ __forceinline__ void igemm_block(const IgemmArgs& p, const int bx, co
         m0 = (tm - p.cls_tile0[c]) * BM;
         kstep = s_;
         // output pixel = class coordinate + (ph + pad - kh) / stride, an exact quotient that falls by one per visited tap
-        oh = div_by(ph + p.pad, p.dS); ow = div_by(pw + p.pad, p.dS); od = s3 > 1 ? div_by(pd + p.pad_d, p.dS) : 0;
+        oh = div_by(ph + p.pad, p.dS); ow = div_by(pw + p.pad, p.dS); od = div_by(pd + p.pad_d, p.dS);
         kh0 = ph + p.pad - oh * s_; kw0 = pw + p.pad - ow * s_;
-        kd0 = s3 > 1 ? pd + p.pad_d - od * s_ : 0;
+        kd0 = pd + p.pad_d - od * s_;
         nkh = kh0 < p.Kh ? div_by(p.Kh - kh0 + s_ - 1, p.dS) : 0;
         nkw = kw0 < p.Kw ? div_by(p.Kw - kw0 + s_ - 1, p.dS) : 0;
-        nkd = s3 > 1 ? (kd0 < p.Kd ? div_by(p.Kd - kd0 + s_ - 1, p.dS) : 0) : 1;
+        nkd = kd0 < p.Kd ? div_by(p.Kd - kd0 + s_ - 1, p.dS) : 0;
         kt0 = 0;
         kt1 = (nkd * nkh * nkw * Cc + 7) / 8;
         if (p.splits > 1) {
