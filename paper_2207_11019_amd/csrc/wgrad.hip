@@ -115,7 +115,7 @@ __device__ __forceinline__ void wgrad_tile(const WgArgs p, int tile, const int s
         const int uu = in ? u : 0, q = div_by(uu, p.dTW), w = uu - q * p.TW, n = div_by(q, p.dHo), h = q - n * p.Ho;
         int img = n;
         bool ok = in;
-        if (p.D > 1 || p.Do > 1) {           // n counts (sample, output slice) pairs
+        if (p.D > 1 || p.Do > 1 || p.Kd > 1) {           // n counts (sample, output slice) pairs
             const int ns = div_by(n, p.dDo), d = (n - ns * p.Do) * p.stride + kd - p.pad_d;
             ok = ok & ((unsigned)d < (unsigned)p.D);
             img = ns * p.D + d;
