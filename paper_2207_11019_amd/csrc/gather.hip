@@ -50,10 +50,10 @@ __device__ __forceinline__ void mma(f32x16& c, const uint4& a, const uint4& b) {
 
 // offset (elements) of reduction index k = (tap, channel) from its pixel's tap (0,0,0), and the tap's mask bits
 template <int SG>
-__device__ __forceinline__ int2 tap_entry(int k, int K, int Ci, int Kh, int Kw, int Hi, int Wi) {
+__device__ __forceinline__ int2 tap_entry(int k, int K, const IgemmArgs& p) {
     if (k >= K) return make_int2(0, (int)NO_TAP);
-    const int t = k / Ci, c = k - t * Ci, td = t / (Kh * Kw), r = t - td * (Kh * Kw), th = r / Kw, tw = r - th * Kw;
-    return make_int2(SG * ((td * Hi + th) * Wi + tw) * Ci + c, (int)((1u << (24 + td)) | (1u << (12 + th)) | (1u << tw)));
+    const int t = div_by(k, p.dCc), c = k - t * p.Ci, td = div_by(t, p.dKhw), r = t - td * (p.Kh * p.Kw), th = div_by(r, p.dKw), tw = r - th * p.Kw;
+    return make_int2(SG * ((td * p.Hi + th) * p.Wi + tw) * p.Ci + c, (int)((1u << (24 + td)) | (1u << (12 + th)) | (1u << tw)));
 }
 // offset (elements) of row `row`'s tap (0,0,0) and the taps that meet the tensor (none past the last row)
 template <bool FWD, bool WIN = false>
@@ -107,7 +107,7 @@ __global__ void __launch_bounds__(256, MODE == MODE_DGRAD ? 2 : 3) gather_gemm(c
     E* bank = reinterpret_cast<E*>(lds + Kp * 8);
     float* pieces = reinterpret_cast<float*>(lds + Kp * 8 + NT * 32 * pitch * ES);
     float* piece = pieces + wave * PIECE;
-    for (int k = tid; k < Kp; k += 256) tab[k] = tap_entry<FWD ? 1 : -1>(k, K, p.Ci, p.Kh, p.Kw, p.Hi, p.Wi);
+    for (int k = tid; k < Kp; k += 256) tab[k] = tap_entry<FWD ? 1 : -1>(k, K, p);
     const E* w = (const E*)p.B;
     // (rows past the last output channel are not filled: what they add up to is not stored.  With them LeNet's data gradient, six rows
     // of 32, took 15.5 us instead of 10.7, its forward pass 7.6 instead of 6.8.)
@@ -235,7 +235,7 @@ __global__ void __launch_bounds__(256) gather_wgrad(const GwArgs a) {
     int2 ke[KT];
     unsigned ce[CT];
 #pragma unroll
-    for (int i = 0; i < KT; ++i) ke[i] = tap_entry<1>(k0 + i * 32 + rl, K, p.Ci, p.Kh, p.Kw, p.Hi, p.Wi);
+    for (int i = 0; i < KT; ++i) ke[i] = tap_entry<1>(k0 + i * 32 + rl, K, p);
 #pragma unroll
     for (int i = 0; i < CT; ++i) ce[i] = co0 + i * 32 + rl < p.N ? (unsigned)(co0 + i * 32 + rl) : OOB;
     f32x16 acc[CT][KT];
@@ -387,6 +387,7 @@ bool gather_fwd_pools(const ConvGeom& g) { return !g.is3d() && !(g.Ho & 1) && !(
 static void fill_geom(IgemmArgs& a) {
     a.Di = std::max(a.Di, 1); a.Dr = std::max(a.Dr, 1); a.Kd = std::max(a.Kd, 1);
     a.dWr = fast_div(a.Wr); a.dHr = fast_div(a.Hr); a.dDr = fast_div(a.Dr); a.dCc = fast_div(a.Ci);
+    a.dKhw = fast_div(a.Kh * a.Kw); a.dKw = fast_div(a.Kw);
 }
 
 template <typename E, int NT, int MODE, bool KSPLIT>

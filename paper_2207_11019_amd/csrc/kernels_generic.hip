@@ -41,8 +41,50 @@ static inline int group_lanes(int n) { return n >= 48 ? 64 : n >= 12 ? 16 : n >=
         else { constexpr int R = 1; __VA_ARGS__; }                 \
     } while (0)
 
+// How an element's index splits into channel, column, row, slice and sample: by multiplication while indices have 31 bits (a 64-bit division
+// is some hundred instructions, and there are four in a launch of 3 us).
+struct Split { FastDiv c, w, h, d; int small; };
+static Split split_of(int c, int w, int h, int d, int64_t total) { return {fast_div(c), fast_div(w), fast_div(h), fast_div(d), total < ((int64_t)1 << 31)}; }
+struct Place { int c, w, h, d, n; };
+__device__ __forceinline__ Place place_of(int64_t idx, const Split& s, int C, int W, int H, int D) {
+    if (s.small) {
+        const int i = (int)idx, t = div_by(i, s.c), q = div_by(t, s.w), u = div_by(q, s.h), n = div_by(u, s.d);
+        return {i - t * C, t - q * W, q - u * H, u - n * D, n};
+    }
+    Place r;
+    int64_t t = idx / C;
+    r.c = (int)(idx - t * C);
+    r.w = (int)(t % W); t /= W;
+    r.h = (int)(t % H); t /= H;
+    r.d = (int)(t % D); r.n = (int)(t / D);
+    return r;
+}
+// acc += a[k] * b[k * bs] * (s ? s[k] : 1) over the lane's k = p, p + R, ... below n, in that order; eight terms' loads in flight
+template <int R, typename T>
+__device__ __forceinline__ float dot(float acc, const T* a, const T* b, int64_t bs, const float* s, int p, int n) {
+    if (n <= R) {
+        if (p < n) { const float v = ld(a, p); acc = fmaf(s ? v * s[p] : v, ld(b, p * bs), acc); }
+        return acc;
+    }
+    for (int k0 = p; k0 < n; k0 += 8 * R) {
+        float va[8], vb[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int k = min(k0 + u * R, n - 1);
+            va[u] = ld(a, k); vb[u] = ld(b, k * bs);
+            if (s) va[u] *= s[k];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float next = fmaf(va[u], vb[u], acc);
+            acc = k0 + u * R < n ? next : acc;
+        }
+    }
+    return acc;
+}
+
 template <typename T, int R>
-__global__ void __launch_bounds__(256) conv_fwd_generic(ConvGeom g, const T* __restrict__ x, const T* __restrict__ w,
+__global__ void __launch_bounds__(256) conv_fwd_generic(ConvGeom g, Split sp, const T* __restrict__ x, const T* __restrict__ w,
                                                         const float* __restrict__ scale, const float* __restrict__ bias,
                                                         const T* __restrict__ add, int relu, T* __restrict__ y) {
     const int64_t total = g.rows_out() * g.Cout;
@@ -50,12 +92,8 @@ __global__ void __launch_bounds__(256) conv_fwd_generic(ConvGeom g, const T* __r
     const int p = (int)(gid % R);
     const bool live = gid / R < total;          // (a group is live or idle as a whole; idle groups still take part in the exchange)
     const int64_t idx = live ? gid / R : 0;
-    const int co = (int)(idx % g.Cout);
-    int64_t row = idx / g.Cout;
-    const int wo = (int)(row % g.Wo); row /= g.Wo;
-    const int ho = (int)(row % g.Ho); row /= g.Ho;
-    const int dq = (int)(row % g.Do);
-    const int n = (int)(row / g.Do);
+    const Place at = place_of(idx, sp, g.Cout, g.Wo, g.Ho, g.Do);
+    const int co = at.c, wo = at.w, ho = at.h, dq = at.d, n = at.n;
     float acc = 0.f;
     for (int kd = 0; kd < g.Kd; ++kd) {
         const int d = dq * g.stride + kd - g.pad_d;
@@ -68,7 +106,7 @@ __global__ void __launch_bounds__(256) conv_fwd_generic(ConvGeom g, const T* __r
                 if (ww < 0 || ww >= g.W) continue;
                 const T* xp = x + ((((int64_t)n * g.D + d) * g.H + h) * g.W + ww) * g.Cin;
                 const T* wp = w + ((((int64_t)co * g.Kd + kd) * g.Kh + kh) * g.Kw + kw) * g.Cin;
-                for (int ci = p; ci < g.Cin; ci += R) acc = fmaf(ld(xp, ci), ld(wp, ci), acc);
+                acc = dot<R>(acc, xp, wp, 1, nullptr, p, g.Cin);
             }
         }
     }
@@ -81,11 +119,16 @@ __global__ void __launch_bounds__(256) conv_fwd_generic(ConvGeom g, const T* __r
     st(y, idx, acc);
 }
 
-hipError_t conv_fwd_generic_launch(int dtype, const ConvGeom& g, const void* x, const void* w, const float* scale,
+hipError_t conv_fwd_generic_launch(int dtype, const ConvGeom& g_, const void* x, const void* w, const float* scale,
                                    const float* bias, const void* add, int relu, void* y, hipStream_t s) {
-    const int64_t total = g.rows_out() * g.Cout;
-    const int lanes = group_lanes(g.Cin);
-    LPM_DISPATCH_R(lanes, LPM_DISPATCH(dtype, launch_last(conv_fwd_generic<T, R>, dim3(nblk(total * R, 256)), dim3(256), 0, s, g,
+    const int64_t total = g_.rows_out() * g_.Cout;
+    const int lanes = group_lanes(g_.Cin);
+    // A filter that covers its input, whose taps are whole turns of the lanes, is one tap of all its channels: the same terms in the
+    // same order, eight of them in flight instead of one (a 4x4x16 -> 120 fully connected layer at 8 samples).
+    ConvGeom g = g_;
+    if (g.taps() > 1 && g.Do == 1 && g.Ho == 1 && g.Wo == 1 && g.pad == 0 && g.pad_d == 0 && g.D == g.Kd && g.H == g.Kh && g.W == g.Kw && g.Cin % lanes == 0)
+        g = ConvGeom{g.m, 1, 1, g.K(), 1, 1, g.Cout, 1, 1, 1, 0};
+    LPM_DISPATCH_R(lanes, LPM_DISPATCH(dtype, launch_last(conv_fwd_generic<T, R>, dim3(nblk(total * R, 256)), dim3(256), 0, s, g, split_of(g.Cout, g.Wo, g.Ho, g.Do, total),
                                                                  (const T*)x, (const T*)w, scale, bias, (const T*)add, relu, (T*)y)));
     return hipGetLastError();
 }
@@ -94,7 +137,7 @@ hipError_t conv_fwd_generic_launch(int dtype, const ConvGeom& g, const void* x, 
 // data gradient, eq. 9: dx[n,h,w,ci] (+)= sum_{kh,kw,co} dz[n,(h+p-kh)/s,(w+p-kw)/s,co] * w[co,kh,kw,ci]
 // (R lanes per element, each taking the output channels p, p + R, ... of every tap)
 template <typename T, int R>
-__global__ void __launch_bounds__(256) conv_dgrad_generic(ConvGeom g, const T* __restrict__ dz, const float* __restrict__ dzscale,
+__global__ void __launch_bounds__(256) conv_dgrad_generic(ConvGeom g, Split sp, const T* __restrict__ dz, const float* __restrict__ dzscale,
                                                           const T* __restrict__ w, T* __restrict__ dx, int accumulate,
                                                           const T* __restrict__ mask, const float* __restrict__ mscale) {
     const int64_t total = g.rows_in() * g.Cin;
@@ -102,33 +145,29 @@ __global__ void __launch_bounds__(256) conv_dgrad_generic(ConvGeom g, const T* _
     const int p = (int)(gid % R);
     const bool live = gid / R < total;
     const int64_t idx = live ? gid / R : 0;
-    const int ci = (int)(idx % g.Cin);
-    int64_t row = idx / g.Cin;
-    const int ww = (int)(row % g.W); row /= g.W;
-    const int h = (int)(row % g.H); row /= g.H;
-    const int d = (int)(row % g.D);
-    const int n = (int)(row / g.D);
+    const Place at = place_of(idx, sp, g.Cin, g.W, g.H, g.D);
+    const int ci = at.c, ww = at.w, h = at.h, d = at.d, n = at.n;
     const int64_t wstride = (int64_t)g.taps() * g.Cin;
+    const bool unit = g.stride == 1;
     float acc = 0.f;
     for (int kd = 0; kd < g.Kd; ++kd) {
         const int dd = d + g.pad_d - kd;
-        if (dd < 0 || dd % g.stride) continue;
-        const int dq = dd / g.stride;
+        if (dd < 0 || (!unit && dd % g.stride)) continue;
+        const int dq = unit ? dd : dd / g.stride;
         if (dq >= g.Do) continue;
         for (int kh = 0; kh < g.Kh; ++kh) {
             const int hh = h + g.pad - kh;
-            if (hh < 0 || hh % g.stride) continue;
-            const int ho = hh / g.stride;
+            if (hh < 0 || (!unit && hh % g.stride)) continue;
+            const int ho = unit ? hh : hh / g.stride;
             if (ho >= g.Ho) continue;
             for (int kw = 0; kw < g.Kw; ++kw) {
                 const int wq = ww + g.pad - kw;
-                if (wq < 0 || wq % g.stride) continue;
-                const int wo = wq / g.stride;
+                if (wq < 0 || (!unit && wq % g.stride)) continue;
+                const int wo = unit ? wq : wq / g.stride;
                 if (wo >= g.Wo) continue;
                 const T* dp = dz + ((((int64_t)n * g.Do + dq) * g.Ho + ho) * g.Wo + wo) * g.Cout;
                 const T* wp = w + (((int64_t)kd * g.Kh + kh) * g.Kw + kw) * g.Cin + ci;
-                if (dzscale) { for (int co = p; co < g.Cout; co += R) acc = fmaf(ld(dp, co) * dzscale[co], ld(wp, co * wstride), acc); }
-                else { for (int co = p; co < g.Cout; co += R) acc = fmaf(ld(dp, co), ld(wp, co * wstride), acc); }
+                acc = dot<R>(acc, dp, wp, wstride, dzscale, p, g.Cout);
             }
         }
     }
@@ -144,7 +183,7 @@ hipError_t conv_dgrad_generic_launch(int dtype, const ConvGeom& g, const void* d
                                      int accumulate, const void* mask, const float* mscale, hipStream_t s) {
     const int64_t total = g.rows_in() * g.Cin;
     const int lanes = group_lanes(g.Cout);
-    LPM_DISPATCH_R(lanes, LPM_DISPATCH(dtype, launch_last(conv_dgrad_generic<T, R>, dim3(nblk(total * R, 256)), dim3(256), 0, s, g,
+    LPM_DISPATCH_R(lanes, LPM_DISPATCH(dtype, launch_last(conv_dgrad_generic<T, R>, dim3(nblk(total * R, 256)), dim3(256), 0, s, g, split_of(g.Cin, g.W, g.H, g.D, total),
                                                                  (const T*)dz, dzscale, (const T*)w, (T*)dx, accumulate, (const T*)mask, mscale)));
     return hipGetLastError();
 }
@@ -428,15 +467,14 @@ hipError_t launch_epilogue_bwd(int dtype, int64_t rows, int32_t C, const void* d
 // --------------------------------------------------------------------------------------------------
 // 2x2/2 max pooling
 template <typename T>
-__global__ void __launch_bounds__(256) maxpool_fwd_kernel(int m, int H, int W, int C, const T* __restrict__ x,
+__global__ void __launch_bounds__(256) maxpool_fwd_kernel(int m, int H, int W, int C, Split sp, const T* __restrict__ x,
                                                           T* __restrict__ y) {
     const int Ho = H / 2, Wo = W / 2;
     const int64_t total = (int64_t)m * Ho * Wo * C;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= total) return;
-    const int c = (int)(idx % C);
-    const int64_t r = idx / C;
-    const int wo = (int)(r % Wo), ho = (int)((r / Wo) % Ho), n = (int)(r / ((int64_t)Wo * Ho));
+    const Place at = place_of(idx, sp, C, Wo, Ho, 1);
+    const int c = at.c, wo = at.w, ho = at.h, n = at.n;
     const T* p = x + (((int64_t)n * H + 2 * ho) * W + 2 * wo) * C + c;
     const float a = ld(p, 0), b = ld(p, C), d = ld(p, (int64_t)W * C), e = ld(p, (int64_t)W * C + C);
     st(y, idx, fmaxf(fmaxf(a, b), fmaxf(d, e)));
@@ -444,7 +482,7 @@ __global__ void __launch_bounds__(256) maxpool_fwd_kernel(int m, int H, int W, i
 
 // gradient to the first element (row-major in the window) equal to the window maximum
 template <typename T>
-__global__ void __launch_bounds__(256) maxpool_bwd_kernel(int m, int H, int W, int C, const T* __restrict__ x,
+__global__ void __launch_bounds__(256) maxpool_bwd_kernel(int m, int H, int W, int C, Split sp, const T* __restrict__ x,
                                                           const T* __restrict__ y, const T* __restrict__ dy,
                                                           T* __restrict__ dx, int accumulate, int mask,
                                                           const float* __restrict__ mscale) {
@@ -452,23 +490,26 @@ __global__ void __launch_bounds__(256) maxpool_bwd_kernel(int m, int H, int W, i
     const int64_t total = (int64_t)m * Ho * Wo * C;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= total) return;
-    const int c = (int)(idx % C);
-    const int64_t r = idx / C;
-    const int wo = (int)(r % Wo), ho = (int)((r / Wo) % Ho), n = (int)(r / ((int64_t)Wo * Ho));
+    const Place at = place_of(idx, sp, C, Wo, Ho, 1);
+    const int c = at.c, wo = at.w, ho = at.h, n = at.n;
     const int64_t base = (((int64_t)n * H + 2 * ho) * W + 2 * wo) * C + c;
     const int64_t off[4] = {0, C, (int64_t)W * C, (int64_t)W * C + C};
     const float mx = ld(y, idx);
-    float g = ld(dy, idx);
+    float g = ld(dy, idx), xin[4], old[4];               // (all loads before the first use: eight latencies one after the other otherwise)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        xin[k] = ld(x, base + off[k]);
+        old[k] = accumulate ? ld(dx, base + off[k]) : 0.f;
+    }
     if (mask && !(mx > 0.f)) g = 0.f;        // the pooled tensor is a ReLU output: its mask at the maximum
     if (mscale) g *= mscale[c];
     bool found = false;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const bool hit = !found && (ld(x, base + off[k]) == mx);
+        const bool hit = !found && xin[k] == mx;
         found = found || hit;
-        float v = hit ? g : 0.f;
-        if (accumulate) v += ld(dx, base + off[k]);
-        st(dx, base + off[k], v);
+        const float v = hit ? g : 0.f;
+        st(dx, base + off[k], accumulate ? v + old[k] : v);
     }
 }
 
@@ -547,7 +588,7 @@ hipError_t launch_maxpool_fwd(int dtype, int32_t m, int32_t H, int32_t W, int32_
         hipLaunchKernelGGL(maxpool_fwd_bf16x8, dim3((total8 + 255u) / 256u), dim3(256), 0, s, total8, H, W, C / 8, (const uint4*)x, (uint4*)y);
         return hipGetLastError();
     }
-    LPM_DISPATCH(dtype, hipLaunchKernelGGL(maxpool_fwd_kernel<T>, dim3(nblk(total, 256)), dim3(256), 0, s, m, H, W, C,
+    LPM_DISPATCH(dtype, hipLaunchKernelGGL(maxpool_fwd_kernel<T>, dim3(nblk(total, 256)), dim3(256), 0, s, m, H, W, C, split_of(C, W / 2, H / 2, 1, total),
                                            (const T*)x, (T*)y));
     return hipGetLastError();
 }
@@ -561,7 +602,7 @@ hipError_t launch_maxpool_bwd(int dtype, int32_t m, int32_t H, int32_t W, int32_
                            (const uint4*)y, (const uint4*)dy, (uint4*)dx, accumulate, mask, mscale);
         return hipGetLastError();
     }
-    LPM_DISPATCH(dtype, launch_last(maxpool_bwd_kernel<T>, dim3(nblk(total, 256)), dim3(256), 0, s, m, H, W, C,
+    LPM_DISPATCH(dtype, launch_last(maxpool_bwd_kernel<T>, dim3(nblk(total, 256)), dim3(256), 0, s, m, H, W, C, split_of(C, W / 2, H / 2, 1, total),
                                            (const T*)x, (const T*)y, (const T*)dy, (T*)dx, accumulate, mask, mscale));
     return hipGetLastError();
 }

@@ -40,12 +40,13 @@ hipError_t launch_splitk_epilogue(const float* part, int splits, int64_t MN, int
 }
 
 // parts that the splits of a reduction are cut into
-__host__ __device__ inline int reduce_lanes(int splits) { return splits > 64 ? 16 : splits > 16 ? 4 : 1; }
+__host__ __device__ inline int reduce_lanes_log(int splits) { return splits > 64 ? 4 : splits > 16 ? 2 : 0; }
+__host__ __device__ inline int reduce_lanes(int splits) { return 1 << reduce_lanes_log(splits); }
 
 struct ReduceBatchArgs {
     ReduceDesc d[LPM_REDUCE_BATCH];
-    int first[LPM_REDUCE_BATCH + 1];         // first block of every reduction
-    int count;
+    int first[LPM_REDUCE_BATCH + 1];         // first block of every reduction, INT_MAX past the last
+    FastDiv row[LPM_REDUCE_BATCH];           // outputs of a row
 };
 
 // A thread sums four consecutive outputs over its part of the splits with 16-byte loads, eight splits in flight (split s of the
@@ -56,12 +57,16 @@ struct ReduceBatchArgs {
 // of VGG-16/224 against 26).
 __global__ void __launch_bounds__(256) wgrad_reduce_batch(ReduceBatchArgs a) {
     __shared__ float4 red[256];
-    int k = 0;                                    // (a block never straddles two reductions)
-    while (k + 1 < a.count && (int)blockIdx.x >= a.first[k + 1]) ++k;
+    int k = 0;                                    // (a block never straddles two reductions; a sum, not a search: no load waits for the one before)
+#pragma unroll
+    for (int j = 1; j < LPM_REDUCE_BATCH; ++j) k += (int)blockIdx.x >= a.first[j];
     const ReduceDesc& d = a.d[k];
-    const int lanes = reduce_lanes(d.splits), tpp = 256 / lanes, part = threadIdx.x / tpp, o = threadIdx.x - part * tpp;
+    const int log = reduce_lanes_log(d.splits), lanes = 1 << log, tpp = 256 >> log, part = threadIdx.x >> (8 - log), o = threadIdx.x & (tpp - 1);
     const int64_t i = ((int64_t)((int)blockIdx.x - a.first[k]) * tpp + o) * 4, end = d.n + d.nb;
-    const int per = (d.splits + lanes - 1) / lanes, s0 = part * per, s1 = min(d.splits, s0 + per);
+    const int per = (d.splits + lanes - 1) >> log, s0 = part * per, s1 = min(d.splits, s0 + per);
+    const FastDiv rd = a.row[k];
+    const bool small = end < ((int64_t)1 << 31);
+    auto row_of = [&](int64_t e) __attribute__((always_inline)) { return small ? div_by((int)e, rd) : (int)(e / d.row_len); };
     float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
     if (i + 4 <= end && (d.stride & 3) == 0) {
         float4 c[4];
@@ -101,12 +106,12 @@ __global__ void __launch_bounds__(256) wgrad_reduce_batch(ReduceBatchArgs a) {
     }
     if (i + 4 <= d.n) {
         if (d.rscale) {
-            const int row = (int)(i / d.row_len), left = d.row_len - (int)(i - (int64_t)row * d.row_len);      // outputs before the next row
+            const int row = row_of(i), left = d.row_len - (int)(i - (int64_t)row * d.row_len);      // outputs before the next row
             const float f = d.rscale[row];
             if (left >= 4) { r.x *= f; r.y *= f; r.z *= f; r.w *= f; }
             else {
                 r.x *= f;
-                r.y *= d.rscale[(i + 1) / d.row_len]; r.z *= d.rscale[(i + 2) / d.row_len]; r.w *= d.rscale[(i + 3) / d.row_len];
+                r.y *= d.rscale[row_of(i + 1)]; r.z *= d.rscale[row_of(i + 2)]; r.w *= d.rscale[row_of(i + 3)];
             }
         }
         float4* out = reinterpret_cast<float4*>(d.dst + i);
@@ -119,7 +124,7 @@ __global__ void __launch_bounds__(256) wgrad_reduce_batch(ReduceBatchArgs a) {
     for (int e = 0; e < 4; ++e) {
         if (i + e >= end) break;
         if (i + e < d.n) {
-            const float v = d.rscale ? t[e] * d.rscale[(i + e) / d.row_len] : t[e];
+            const float v = d.rscale ? t[e] * d.rscale[row_of(i + e)] : t[e];
             d.dst[i + e] = d.accumulate ? d.dst[i + e] + v : v;
         } else {
             const int c = (int)(i + e - d.n);
@@ -137,8 +142,8 @@ hipError_t launch_reduce_batch(const ReduceDesc* d, int count, hipStream_t st) {
             a.first[k] = tot;
             tot += (int)(((a.d[k].n + a.d[k].nb + 3) / 4 * reduce_lanes(a.d[k].splits) + 255) / 256);
         }
-        a.first[k] = tot;
-        a.count = k;
+        for (int j = 0; j < k; ++j) a.row[j] = fast_div(a.d[j].row_len);
+        for (int j = k; j <= LPM_REDUCE_BATCH; ++j) a.first[j] = 0x7fffffff;
         done += k;
         if (tot == 0) continue;
         if (done < count) hipLaunchKernelGGL(wgrad_reduce_batch, dim3((unsigned)tot), dim3(256), 0, st, a);

@@ -56,7 +56,8 @@ struct WgArgs {
     int units;             // m * Do * Ho * TW
     int kt_total, kt_per_split, splits;
     int accumulate;
-    int co_tiles, ci_tiles, tap_groups, kind;
+    int co_tiles, ci_tiles, tap_groups, g2, kind;
+    FastDiv dCi, dGroups, dG2, dKw, dAll;      // tiles along Cin, tap groups, those of a filter slice, taps of a filter row, tiles of dW
 };
 
 // four rows of the column a lane ends up with (see above)
@@ -96,12 +97,10 @@ __device__ __forceinline__ void wgrad_tile(const WgArgs p, int tile, const int s
     uint4* rec3 = reinterpret_cast<uint4*>(lds + NST * STAGE + DUMP);                // ROW3: dz offset, its pixels; x offset, mask of its pixels
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    const int ci_t = tile % p.ci_tiles; tile /= p.ci_tiles;
-    const int grp = tile % p.tap_groups;
-    const int co_t = tile / p.tap_groups;
+    const int tq = div_by(tile, p.dCi), ci_t = tile - tq * p.ci_tiles, co_t = div_by(tq, p.dGroups), grp = tq - co_t * p.tap_groups;
     const int co0 = co_t * BM, ci0 = ci_t * BN;
-    const int g2d = p.tap_groups / p.Kd, kd = grp / g2d, grp2 = grp - kd * g2d;      // filter slice, tap group inside it
-    const int kh = TAPS == 3 ? grp2 : grp2 / p.Kw, kw = TAPS == 3 ? 0 : grp2 % p.Kw;
+    const int kd = div_by(grp, p.dG2), grp2 = grp - kd * p.g2;      // filter slice, tap group inside it
+    const int kh = TAPS == 3 ? grp2 : div_by(grp2, p.dKw), kw = TAPS == 3 ? 0 : grp2 - kh * p.Kw;
     const int kt0 = split * p.kt_per_split, nk = min(p.kt_total, kt0 + p.kt_per_split) - kt0;
 
     u32x4_ rsD = buffer_words(p.DZ, p.dz_bytes), rsX = buffer_words(p.X, p.x_bytes);
@@ -456,7 +455,7 @@ __device__ __forceinline__ void wgrad_tile(const WgArgs p, int tile, const int s
 // fit a SIMD's 512 (131 instead of 119 cost ResNet-18/CIFAR 2.5 %); the arguments come by value, by reference they cost those twelve.
 struct WgGroup {
     int count;
-    int first[LPM_WGRAD_GROUP + 1];          // first block of every layer
+    int first[LPM_WGRAD_GROUP];              // first block of every layer, INT_MAX past the last
     WgArgs d[LPM_WGRAD_GROUP];
 };
 
@@ -465,9 +464,10 @@ template <typename E, bool BIG>
 __global__ void __launch_bounds__(512, BIG ? 3 : 4) wgrad_many(const WgGroup a) {
     const int v = xcd_remap((int)blockIdx.x, (int)gridDim.x);      // (as below)
     int k = 0;
-    while (k + 1 < a.count && v >= a.first[k + 1]) ++k;
+#pragma unroll
+    for (int j = 1; j < LPM_WGRAD_GROUP; ++j) k += v >= a.first[j];      // (a sum, not a search: no load waits for the one before)
     const WgArgs& p = a.d[k];
-    const int local = v - a.first[k], n = p.co_tiles * p.ci_tiles * p.tap_groups, split = local / n, tile = local - split * n;
+    const int local = v - a.first[k], n = p.co_tiles * p.ci_tiles * p.tap_groups, split = div_by(local, p.dAll), tile = local - split * n;
     constexpr int B = BIG ? 128 : 64, NST = BIG ? 4 : 3;
     if (p.kind == LIN) wgrad_tile<E, B, B, LIN, NST>(p, tile, split);
     else if (p.kind == PIX) wgrad_tile<E, B, B, PIX, NST>(p, tile, split);
@@ -591,6 +591,9 @@ static WgArgs wg_args(int dtype, const WgradTask& t, const WgPlan& pl) {
     a.kt_total = pl.kt_total; a.kt_per_split = pl.kt_per; a.splits = pl.splits;
     a.accumulate = t.accumulate;
     a.co_tiles = pl.co_tiles; a.ci_tiles = pl.ci_tiles; a.tap_groups = pl.groups; a.kind = pl.kind;
+    a.g2 = pl.groups / a.Kd;
+    a.dCi = fast_div(pl.ci_tiles); a.dGroups = fast_div(pl.groups); a.dG2 = fast_div(a.g2); a.dKw = fast_div(g.Kw);
+    a.dAll = fast_div((int)wg_tiles(pl));
     return a;
 }
 
@@ -624,7 +627,7 @@ static hipError_t go_many(const WgradTask* t, const WgPlan* pl, int n, hipStream
         bytes = std::max(bytes, kinds[pl[i].kind]);
     }
     if (!a.count) return hipSuccess;
-    a.first[a.count] = blocks;
+    for (int i = a.count; i < LPM_WGRAD_GROUP; ++i) a.first[i] = 0x7fffffff;
     static DeviceSet done;
     const hipError_t attr = allow_lds(wgrad_many<E, BIG>, std::max({kinds[LIN], kinds[PIX], kinds[ROW3]}), done);
     if (attr != hipSuccess) return attr;
