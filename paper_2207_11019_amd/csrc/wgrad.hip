@@ -65,7 +65,10 @@ __device__ __forceinline__ u32x2_ tr4(const unsigned char* p) {
     return __builtin_bit_cast(u32x2_, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4_*)(p)));
 }
 
-enum { LIN = 0, PIX = 1, ROW3 = 3 };
+enum { LIN = 0, PIX = 1, ROW3 = 3, ROW3_32 = 4 /* of 32 x 32 channels */ };
+
+// pixels of a K tile
+constexpr int wg_pixels(int es, int bm) { return es == 4 ? 32 : bm == 32 ? 128 : 64; }
 
 // Where 16-byte chunk c of row r of an operand lies in an LDS row of P bytes, and which chunk lies at position c (its own inverse).
 // 16 lanes of a transpose read take 32 bytes each of four consecutive rows: of 256-byte rows (128 channels) all four share their
@@ -77,18 +80,18 @@ __device__ __forceinline__ int place(int c, int r) { return ES == 2 && P == 256 
 // One block: tile `tile` of dW (all of them, tap groups included) over pixel range `split`.
 template <typename E, int BM, int BN, int KIND, int NST>
 __device__ __forceinline__ void wgrad_tile(const WgArgs p, int tile, const int split) {
-    constexpr int TAPS = KIND == ROW3 ? 3 : 1, WGM = 2, WGN = 2;
-    constexpr int ES = sizeof(E), T = 512, KT = ES == 2 ? 64 : 32;
+    constexpr int TAPS = KIND == ROW3 ? 3 : 1, WGM = BM == 32 ? 1 : 2, WGN = BN == 32 ? 1 : 2, WPG = WGM * WGN, GROUPS = 8 / WPG;
+    constexpr int ES = sizeof(E), T = 512, KT = wg_pixels(ES, BM);
     constexpr int WTM = BM / WGM, WTN = BN / WGN, MI = WTM / 32, NI = WTN / 32;
     constexpr int HX = 10;                                                    // input pixels of a segment
     constexpr int PA = BM * ES, PB = BN * ES;                                 // bytes of an LDS row
     constexpr int A_BYTES = KT * PA;
-    constexpr int B_ROWS = KIND == ROW3 ? 8 * HX : KT;
+    constexpr int B_ROWS = KIND == ROW3 ? KT / 8 * HX : KT;
     constexpr int A_LD = A_BYTES / (T * 16), B_LD = (B_ROWS * PB + T * 16 - 1) / (T * 16), LPT = A_LD + B_LD;
     constexpr int STAGE = A_BYTES + B_ROWS * PB;                              // (loads past the last row go to a dump of 1 KB)
-    constexpr int KU = KIND == ROW3 ? 8 : KT;                                 // units per K tile
+    constexpr int KU = KIND == ROW3 ? KT / 8 : KT;                                 // units per K tile
     constexpr int CT = ES == 2 && KIND != ROW3 ? 8 : 16, CU = CT * KU;         // K tiles and units of a chunk of unit records
-    constexpr int KSW = 2;                                                    // K steps of a tile per wavefront
+    constexpr int KSW = KT * ES / 32 / GROUPS;                                // K steps of a tile per wavefront
     static_assert(KIND != ROW3 || ES == 2, "filter rows: bf16");
     static_assert(A_LD * T * 16 == A_BYTES && CT % 2 == 0 && CT >= 8 && NST <= 4 && CU <= T && (B_ROWS * PB) % 1024 == 0, "layout");
     constexpr int DUMP = KIND == ROW3 ? 1024 : 0;
@@ -143,7 +146,7 @@ __device__ __forceinline__ void wgrad_tile(const WgArgs p, int tile, const int s
     for (int i = 0; i < B_LD; ++i) {
         const int idx = i * T + tid, r = idx / (PB / 16), ch = ci0 + place<ES, PB>(idx - r * (PB / 16), r) * (16 / ES);
         const bool ok = r < B_ROWS && ch < p.Cin;
-        b_u[i] = KIND == ROW3 ? min(r / HX, 7) : r;
+        b_u[i] = KIND == ROW3 ? min(r / HX, KU - 1) : r;
         b_in[i] = KIND == ROW3 ? (ok ? r - r / HX * HX : 31) : 0;                     // (bit 31 of a mask is never set)
         b_off[i] = KIND == ROW3 ? (unsigned)(b_in[i] * p.Cin + ch) * ES : KIND == LIN ? (ok ? (unsigned)(r * p.Cin + ch) * ES : WG_OOB)
                                                                                       : (ok ? (unsigned)ch * ES : WG_OOB);
@@ -209,7 +212,7 @@ __device__ __forceinline__ void wgrad_tile(const WgArgs p, int tile, const int s
                 for (int i = 0; i < 16; ++i) acc[t][mi][ni][i] = 0.f;
     // the blocks of tap group 0 / Cin tile 0 also sum dz over the pixels (the bias gradient): the wavefronts of the first column
     // add up the operands they hold anyway, a channel per lane
-    const int wk = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+    const int wk = wave / WPG, wm = (wave - wk * WPG) / WGN, wn = wave % WGN;
     const bool do_bias = p.db != nullptr && grp == 0 && ci_t == 0 && wn == 0;
     float bsum[MI];
 #pragma unroll
@@ -338,8 +341,8 @@ __device__ __forceinline__ void wgrad_tile(const WgArgs p, int tile, const int s
                 __builtin_amdgcn_sched_barrier(0);
                 if (ks + 1 < KSW) read(nxt, st1, ks + 1);
                 multiply(cur, ks);
-                issue(st, 2 * ks);
-                issue(st, 2 * ks + 1);
+#pragma unroll
+                for (int q = ks * 4 / KSW; q < (ks + 1) * 4 / KSW; ++q) issue(st, q);
             }
             __builtin_amdgcn_sched_barrier(0);
             st = st1;
@@ -357,13 +360,15 @@ __device__ __forceinline__ void wgrad_tile(const WgArgs p, int tile, const int s
         LPM_WAIT_VM(0);
     }
 
-    // the second group of wavefronts hands its sums to the first
+    // the second half of the groups hands its sums to the first, until one is left
     __syncthreads();
-    {
-        float4* ex = reinterpret_cast<float4*>(lds) + (wave & 3) * (TAPS * MI * NI * 4 * 64) + lane;
-        float* exb = reinterpret_cast<float*>(lds + 4 * TAPS * MI * NI * 4096) + (wave & 3) * (MI * 64) + lane;
+#pragma unroll
+    for (int g = GROUPS / 2; g > 0; g >>= 1) {
+        const int slot = wk >= g ? wave - g * WPG : wave;
+        float4* ex = reinterpret_cast<float4*>(lds) + slot * (TAPS * MI * NI * 4 * 64) + lane;
+        float* exb = reinterpret_cast<float*>(lds + 4 * TAPS * MI * NI * 4096) + slot * (MI * 64) + lane;
         static_assert(4 * TAPS * MI * NI * 4096 + 4 * MI * 256 <= NST * STAGE, "the sums fit the dead stages");
-        if (wk) {
+        if (wk >= g && wk < 2 * g) {
 #pragma unroll
             for (int t = 0; t < TAPS; ++t)
 #pragma unroll
@@ -377,20 +382,24 @@ __device__ __forceinline__ void wgrad_tile(const WgArgs p, int tile, const int s
             for (int mi = 0; mi < MI; ++mi) exb[mi * 64] = bsum[mi];
         }
         __syncthreads();
-        if (wk) return;
+        if (wk >= g) {
+            if (g == 1) return;
+        } else {
 #pragma unroll
-        for (int t = 0; t < TAPS; ++t)
+            for (int t = 0; t < TAPS; ++t)
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi)
+                for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-                for (int ni = 0; ni < NI; ++ni)
+                    for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float4 v = ex[(((t * MI + mi) * NI + ni) * 4 + q) * 64];
-                        acc[t][mi][ni][4 * q] += v.x; acc[t][mi][ni][4 * q + 1] += v.y; acc[t][mi][ni][4 * q + 2] += v.z; acc[t][mi][ni][4 * q + 3] += v.w;
-                    }
+                        for (int q = 0; q < 4; ++q) {
+                            const float4 v = ex[(((t * MI + mi) * NI + ni) * 4 + q) * 64];
+                            acc[t][mi][ni][4 * q] += v.x; acc[t][mi][ni][4 * q + 1] += v.y; acc[t][mi][ni][4 * q + 2] += v.z; acc[t][mi][ni][4 * q + 3] += v.w;
+                        }
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi) bsum[mi] += exb[mi * 64];
+            for (int mi = 0; mi < MI; ++mi) bsum[mi] += exb[mi * 64];
+        }
+        if (g > 1) __syncthreads();
     }
 
     // accumulator element i of a lane: row (i / 4) * 8 + (lane / 32) * 4 + i % 4, column lane % 32
@@ -471,17 +480,20 @@ __global__ void __launch_bounds__(512, BIG ? 3 : 4) wgrad_many(const WgGroup a) 
     constexpr int B = BIG ? 128 : 64, NST = BIG ? 4 : 3;
     if (p.kind == LIN) wgrad_tile<E, B, B, LIN, NST>(p, tile, split);
     else if (p.kind == PIX) wgrad_tile<E, B, B, PIX, NST>(p, tile, split);
-    else if constexpr (sizeof(E) == 2 && !BIG) wgrad_tile<E, 64, 64, ROW3, NST>(p, tile, split);
+    else if constexpr (sizeof(E) == 2 && !BIG) {
+        if (p.kind == ROW3_32) wgrad_tile<E, 32, 32, ROW3, NST>(p, tile, split);
+        else wgrad_tile<E, 64, 64, ROW3, NST>(p, tile, split);
+    }
 }
 template <typename E, int BM, int BN, int KIND, int NST>
-__global__ void __launch_bounds__(512, BM == 64 ? 4 : 3) wgrad_mm(WgArgs p) {
+__global__ void __launch_bounds__(512, BM <= 64 ? 4 : 3) wgrad_mm(WgArgs p) {
     // all blocks of one pixel range go to one XCD (they read the same dz and x rows)
     const int v = xcd_remap((int)(blockIdx.z * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.z)), split = v / (int)gridDim.x;
     wgrad_tile<E, BM, BN, KIND, NST>(p, v - split * (int)gridDim.x, split);
 }
 constexpr int wg_lds(int es, int bm, int bn, int kind, int nst) {
-    const int kt = es == 2 ? 64 : 32;
-    return nst * (kt * bm * es + (kind == ROW3 ? 80 : kt) * bn * es) + (kind == LIN ? 0 : kind == ROW3 ? 1024 + 256 * 16 : 1024 * 4);
+    const int kt = wg_pixels(es, bm);
+    return nst * (kt * bm * es + (kind == ROW3 ? kt / 8 * 10 : kt) * bn * es) + (kind == LIN ? 0 : kind == ROW3 ? 1024 + kt * 4 * 16 : 1024 * 4);
 }
 
 struct WgPlan { int kind, big, groups, co_tiles, ci_tiles, TW, kt_total, kt_per, splits; };
@@ -491,10 +503,12 @@ static WgPlan plan_tiles(int dtype, const ConvGeom& g) {
     const int tx = (g.Wo + 7) / 8;
     // a filter row per block where the row segments are mostly real pixels
     const bool row3 = dtype == LPM_BF16 && g.Kh == 3 && g.Kw == 3 && g.stride == 1 && g.Wo * 10 >= tx * 8 * 8;
-    pl.kind = row3 ? ROW3 : g.taps() == 1 && g.stride == 1 && g.pad == 0 && g.pad_d == 0 ? LIN : PIX;
+    // 32 x 32 channels: the wavefronts that the rest of a 64 x 64 tile would idle take pixels instead, eight groups of them
+    const bool half = row3 && g.Cout <= 32 && g.Cin <= 32;
+    pl.kind = half ? ROW3_32 : row3 ? ROW3 : g.taps() == 1 && g.stride == 1 && g.pad == 0 && g.pad_d == 0 ? LIN : PIX;
     pl.groups = g.taps() / (row3 ? 3 : 1);
     pl.TW = row3 ? tx : g.Wo;
-    const int64_t units = (int64_t)g.m * g.Do * g.Ho * pl.TW, ku = row3 ? 8 : dtype == LPM_BF16 ? 64 : 32;
+    const int64_t units = (int64_t)g.m * g.Do * g.Ho * pl.TW, ku = half ? 16 : row3 ? 8 : dtype == LPM_BF16 ? 64 : 32;
     pl.kt_total = (int)((units + ku - 1) / ku);
     pl.co_tiles = (g.Cout + 63) / 64;
     pl.ci_tiles = (g.Cin + 63) / 64;
@@ -523,7 +537,7 @@ static int64_t most_splits(const ConvGeom& g, const WgPlan& pl) {
 // 1758 / 1764 / 1798; 128-channel tiles alone at 128: R50 conv4_x at 512 7240 -> 7066.
 static WgPlan plan_wgrad(int dtype, const ConvGeom& g, bool shared) {
     WgPlan pl = plan_tiles(dtype, g);
-    if (dtype == LPM_BF16 && pl.kind != ROW3 && g.Cout >= 128 && g.Cin >= 128 && wg_tiles(big_tiles(g, pl)) * std::max(1, pl.kt_total / 16) >= 192) pl = big_tiles(g, pl);
+    if (dtype == LPM_BF16 && pl.kind < ROW3 && g.Cout >= 128 && g.Cin >= 128 && wg_tiles(big_tiles(g, pl)) * std::max(1, pl.kt_total / 16) >= 192) pl = big_tiles(g, pl);
     const int64_t base = wg_tiles(pl), want = shared ? (pl.big ? 128 : 192) : 256;
     int64_t sp = std::max<int64_t>(1, want / base);
     if (base * sp < want * 3 / 4) sp = std::max<int64_t>(sp, want * 7 / 4 / base);
@@ -542,7 +556,7 @@ static int room_for(int dtype, const ConvGeom& g) { return std::max(plan_wgrad(d
 // conv4_x takes 1 to 7 % more per step at 12 to 64 samples, ResNet-18/CIFAR 5 to 8, VGG-16/224 2 to 4, float ResNet-18 1 to 3.
 static void plan_group(int dtype, const WgradTask* t, int n, WgPlan* pl) {
     auto cost = [](const WgPlan& p) { return (p.kind == ROW3 || p.big ? 2. : 1.) * p.kt_total; };
-    auto large = [&](int i) { return dtype == LPM_BF16 && pl[i].kind != ROW3 && t[i].g.Cout >= 128 && t[i].g.Cin >= 128; };
+    auto large = [&](int i) { return dtype == LPM_BF16 && pl[i].kind < ROW3 && t[i].g.Cout >= 128 && t[i].g.Cin >= 128; };
     int64_t blocks = 0;
     for (int i = 0; i < n; ++i) {
         pl[i] = plan_tiles(dtype, t[i].g);
@@ -609,6 +623,7 @@ static hipError_t go(const WgArgs& a, const WgPlan& pl, hipStream_t st) {
 static hipError_t run_one(int dtype, const WgradTask& t, const WgPlan& pl, hipStream_t st) {
     const WgArgs a = wg_args(dtype, t, pl);
     if (dtype == LPM_F32) return pl.kind == LIN ? go<float, 64, 64, LIN, 3>(a, pl, st) : go<float, 64, 64, PIX, 3>(a, pl, st);
+    if (pl.kind == ROW3_32) return go<bf16_t, 32, 32, ROW3, 3>(a, pl, st);
     if (pl.kind == ROW3) return pl.kt_per >= 64 ? go<bf16_t, 64, 64, ROW3, 4>(a, pl, st) : go<bf16_t, 64, 64, ROW3, 3>(a, pl, st);
     if (pl.big) return pl.kind == LIN ? go<bf16_t, 128, 128, LIN, 4>(a, pl, st) : go<bf16_t, 128, 128, PIX, 4>(a, pl, st);
     return pl.kind == LIN ? go<bf16_t, 64, 64, LIN, 3>(a, pl, st) : go<bf16_t, 64, 64, PIX, 3>(a, pl, st);
@@ -616,7 +631,7 @@ static hipError_t run_one(int dtype, const WgradTask& t, const WgPlan& pl, hipSt
 template <typename E, bool BIG>
 static hipError_t go_many(const WgradTask* t, const WgPlan* pl, int n, hipStream_t st) {
     constexpr int B = BIG ? 128 : 64, NST = BIG ? 4 : 3, ES = sizeof(E);
-    constexpr int kinds[4] = {wg_lds(ES, B, B, LIN, NST), wg_lds(ES, B, B, PIX, NST), 0, ES == 2 && !BIG ? wg_lds(ES, 64, 64, ROW3, NST) : 0};
+    constexpr int kinds[5] = {wg_lds(ES, B, B, LIN, NST), wg_lds(ES, B, B, PIX, NST), 0, ES == 2 && !BIG ? wg_lds(ES, 64, 64, ROW3, NST) : 0, ES == 2 && !BIG ? wg_lds(ES, 32, 32, ROW3, NST) : 0};
     WgGroup a{};
     int blocks = 0, bytes = 0;
     for (int i = 0; i < n; ++i) {
@@ -629,7 +644,7 @@ static hipError_t go_many(const WgradTask* t, const WgPlan* pl, int n, hipStream
     if (!a.count) return hipSuccess;
     for (int i = a.count; i < LPM_WGRAD_GROUP; ++i) a.first[i] = 0x7fffffff;
     static DeviceSet done;
-    const hipError_t attr = allow_lds(wgrad_many<E, BIG>, std::max({kinds[LIN], kinds[PIX], kinds[ROW3]}), done);
+    const hipError_t attr = allow_lds(wgrad_many<E, BIG>, std::max({kinds[LIN], kinds[PIX], kinds[ROW3], kinds[ROW3_32]}), done);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL((wgrad_many<E, BIG>), dim3((unsigned)blocks), dim3(512), bytes, st, a);
     return hipGetLastError();

@@ -29,6 +29,7 @@ RUNS = [
     (1, "test_gpu_contractions.py", "88_200 or 256_768 or 256_192"),          # 256x128 tiles
     (1, "test_gpu_fused.py", "256 or large or (rows and tile128)"),           # ... large ones, groups and pairs of them, pooling over two pieces
     (1, "test_gpu_small.py", ""),
+    (1, "test_gpu_wgrad32.py", "not m24"),
     (1, "test_gpu_rows.py", "not m2_115 and not m2_230 and not m2_100 and not m3_1 and not 32_wide and not backward_of"),
     (0, "test_gpu_rows.py", "m2_100x98_32 or m3_113x114_32 or (32_wide and 20)"),
     (1, "test_gpu_parity.py", "small_networks and bf16 and not graph and not pipelined"),
