@@ -1,11 +1,11 @@
-// Contractions by filter rows in pieces of a few channels: forward and data gradient of bf16 filters three taps wide (stride 1, one
-// pixel of padding), two- and three-dimensional, whose channels are no whole K tiles of 64.
+// Contractions by filter rows in pieces of a few channels: forward and data gradient of bf16 filters three or five taps wide (stride 1, the
+// output as wide as the input), two- and three-dimensional, whose channels are no whole K tiles of 64.
 //
 //   C[M][N] = A[M][K] * B[N][K]^T,  K over (filter row, piece of channels, tap of the row, channel); operands as in igemm.hip
 //
 // What bounds such layers is the path from the L2 through the LDS to the matrix cores, not the products.  In chunks across taps
-// (igemm_kernel, KT_CHUNKS) a tile's pixels are loaded anew for each of the nine taps, every lane looking its chunk's tap up.  Here a
-// stage of LDS holds the pixels that a filter row of the tile meets, once, and the row's three taps of weights, P chunks of 16 bytes (8 channels)
+// (igemm_kernel, KT_CHUNKS) a tile's pixels are loaded anew for each tap, every lane looking its chunk's tap up.  Here a
+// stage of LDS holds the pixels that a filter row of the tile meets, once, and the taps of weights of that row, P chunks of 16 bytes (8 channels)
 // each, P = 4 or 6: which tap that is is wave-uniform, a tap is another row of LDS to read from (a row of zeros where it lies beside the image).
 // Two stages, one workgroup barrier each.  A stage of 128x64 tiles is 21 KB for 96 values of K where 64 of them took 24.
 //
@@ -20,17 +20,17 @@ namespace lpm {
 template <int P>
 __device__ __forceinline__ int swz(int r) { return P == 4 ? (r >> 2) & 3 : (r >> 3) & 1; }
 
-// LDS of a stage in units of 1 KB, what a wavefront loads at a time: the pixels of the tile's rows and of the one before and behind them,
+// LDS of a stage in units of 1 KB, what a wavefront loads at a time: the pixels of the tile's rows and of those before and behind them,
 // and a row of zeros; the weights
-constexpr int rows_a_units(int P, int BM) { return ((BM + 3) * P + 63) / 64; }
-constexpr int rows_stage(int P, int BM, int BN) { return (rows_a_units(P, BM) + 3 * BN * P / 64) * 1024; }
+constexpr int rows_a_units(int taps, int P, int BM) { return ((BM + taps) * P + 63) / 64; }
+constexpr int rows_stage(int taps, int P, int BM, int BN) { return (rows_a_units(taps, P, BM) + taps * BN * P / 64) * 1024; }
 
-template <int P, int BM, int BN, int WGM, int WGN, int LA, int MODE>
+template <int TAPS, int P, int BM, int BN, int WGM, int WGN, int LA, int MODE>
 __global__ void __launch_bounds__(WGM * WGN * 64, 2) rows_kernel(const IgemmArgs p) {
     constexpr int NW = WGM * WGN, WTM = BM / WGM, WTN = BN / WGN, MI = WTM / 32, NI = WTN / 32, ROWB = P * 16;
-    constexpr int UA = rows_a_units(P, BM), U = UA + 3 * BN * P / 64, STAGE = U * 1024, NL = (U + NW - 1) / NW;      // units, loads of a wavefront
-    constexpr int KS = 3 * P / 2;                                               // steps of 16 values of K
-    static_assert(3 * BN * P % 64 == 0 && LA < KS, "layout");
+    constexpr int UA = rows_a_units(TAPS, P, BM), U = UA + TAPS * BN * P / 64, STAGE = U * 1024, NL = (U + NW - 1) / NW;      // units, loads of a wavefront
+    constexpr int KS = TAPS * P / 2, SETS = KS > 9 ? 5 : KS, SIDE = TAPS / 2;      // steps of 16 values of K, sets of their operands
+    static_assert(TAPS * BN * P % 64 == 0 && LA < SETS && KS % SETS == 0, "layout");
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tile = xcd_remap(blockIdx.x, gridDim.x);
@@ -53,8 +53,8 @@ __global__ void __launch_bounds__(WGM * WGN * 64, 2) rows_kernel(const IgemmArgs
     for (int i = 0; i < NL; ++i) {
         const int u = i * NW + wave;
         if (i * NW + NW <= UA || (i * NW < UA && u < UA)) {
-            const int idx = u * 64 + lane, r = idx / P, c = (idx - r * P) ^ swz<P>(r), row = m0 - 1 + r;
-            const bool ok = (row >= 0) & (row < rows) & (r < BM + 2);
+            const int idx = u * 64 + lane, r = idx / P, c = (idx - r * P) ^ swz<P>(r), row = m0 - SIDE + r;
+            const bool ok = (row >= 0) & (row < rows) & (r < BM + 2 * SIDE);
             const int rr = ok ? row : 0, t = div_by(rr, p.dWr), wq = rr - t * p.Wr;
             int n = div_by(t, p.dHr), d0 = 0;
             const int hq = t - n * p.Hr, h0 = MODE == MODE_FWD ? hq - p.pad : hq + p.pad;
@@ -97,7 +97,7 @@ __global__ void __launch_bounds__(WGM * WGN * 64, 2) rows_kernel(const IgemmArgs
             return;
         }
         const unsigned back = (unsigned)(G - 1) * ROWB;
-        lb += 3u * tapC - back;
+        lb += (unsigned)TAPS * tapC - back;
         la += aH - back;
         bit &= ~1u;
         if (++kh < p.Kh) bit = ((bit & 0xfff000u) << 1) | (bit & 0xff000000u);
@@ -140,36 +140,36 @@ __global__ void __launch_bounds__(WGM * WGN * 64, 2) rows_kernel(const IgemmArgs
     // operand addresses in a stage: row lane % 32 of the wavefront's part, chunk 2j + lane / 32 of a tap's piece
     const int wm = wave / WGN, wn = wave - wm * WGN, rl = lane & 31, kq = lane >> 5;
     auto piece = [](unsigned o, int j) __attribute__((always_inline)) { return P == 6 ? o + (unsigned)j * 32u : o ^ ((unsigned)j << 5); };
-    unsigned oA[3][MI], oB[P / 2];
+    unsigned oA[TAPS][MI], oB[P / 2];
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
         const int at = wm * WTM + mi * 32 + rl, row = m0 + at, w = row - div_by(row, p.dWr) * p.Wr;
 #pragma unroll
-        for (int s = 0; s < 3; ++s) {
-            const bool out = s == 0 ? w == 0 : s == 2 ? w == p.Wr - 1 : false;
-            const int r = out ? BM + 2 : at + s;
-            oA[MODE == MODE_FWD ? s : 2 - s][mi] = (unsigned)(r * ROWB + ((kq ^ swz<P>(r)) << 4));
+        for (int s = 0; s < TAPS; ++s) {
+            const bool out = s != SIDE && (unsigned)(w + s - SIDE) >= (unsigned)p.Wr;
+            const int r = out ? BM + 2 * SIDE : at + s;
+            oA[MODE == MODE_FWD ? s : TAPS - 1 - s][mi] = (unsigned)(r * ROWB + ((kq ^ swz<P>(r)) << 4));
         }
     }
 #pragma unroll
     for (int j = 0; j < P / 2; ++j) oB[j] = piece((unsigned)(UA * 1024 + (wn * WTN + rl) * ROWB + ((kq ^ swz<P>(rl)) << 4)), j);
 
     struct Frag { uint4 a[MI], b[NI]; };
-    Frag f[KS];
+    Frag f[SETS];
     auto read = [&](int st, int ks) __attribute__((always_inline)) {
         const int s = ks / (P / 2), j = ks - s * (P / 2);
         const unsigned char* sp = lds + st * STAGE;
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi) f[ks].a[mi] = *reinterpret_cast<const uint4*>(sp + piece(oA[s][mi], j));
+        for (int mi = 0; mi < MI; ++mi) f[ks % SETS].a[mi] = *reinterpret_cast<const uint4*>(sp + piece(oA[s][mi], j));
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni) f[ks].b[ni] = *reinterpret_cast<const uint4*>(sp + oB[j] + (s * BN + ni * 32) * ROWB);
+        for (int ni = 0; ni < NI; ++ni) f[ks % SETS].b[ni] = *reinterpret_cast<const uint4*>(sp + oB[j] + (s * BN + ni * 32) * ROWB);
     };
     auto multiply = [&](int ks) __attribute__((always_inline)) {
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni)
-                acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f[ks].b[ni]), __builtin_bit_cast(bf16x8, f[ks].a[mi]), acc[mi][ni], 0, 0, 0);
+                acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f[ks % SETS].b[ni]), __builtin_bit_cast(bf16x8, f[ks % SETS].a[mi]), acc[mi][ni], 0, 0, 0);
     };
     // The next stage has landed, and the last operands of the present one have arrived: what is loaded behind the barrier goes where it lies.
     auto meet = [&]() __attribute__((always_inline)) {
@@ -244,17 +244,17 @@ __global__ void __launch_bounds__(WGM * WGN * 64, 2) rows_kernel(const IgemmArgs
     }
 }
 
-template <int P, int BM, int BN, int WGM, int WGN, int LA, int MODE>
+template <int TAPS, int P, int BM, int BN, int WGM, int WGN, int LA, int MODE>
 static hipError_t go(const IgemmArgs& a, hipStream_t st) {
-    constexpr int stages = 2 * rows_stage(P, BM, BN), cols = BN / WGN, epilogue = BM * WGN * ((cols <= 64 ? cols : 32) + 4) * 4, bytes = stages > epilogue ? stages : epilogue;
+    constexpr int stages = 2 * rows_stage(TAPS, P, BM, BN), cols = BN / WGN, epilogue = BM * WGN * ((cols <= 64 ? cols : 32) + 4) * 4, bytes = stages > epilogue ? stages : epilogue;
     static_assert(bytes <= 160 * 1024, "LDS of a CU");
     static DeviceSet done;
-    const hipError_t attr = allow_lds(rows_kernel<P, BM, BN, WGM, WGN, LA, MODE>, bytes, done);
+    const hipError_t attr = allow_lds(rows_kernel<TAPS, P, BM, BN, WGM, WGN, LA, MODE>, bytes, done);
     if (attr != hipSuccess) return attr;
     IgemmArgs b = a;
     const int nt = (a.N + BN - 1) / BN;
     b.dNt = fast_div(nt);
-    launch_last(rows_kernel<P, BM, BN, WGM, WGN, LA, MODE>, dim3((unsigned)((a.M + BM - 1) / BM * nt)), dim3(WGM * WGN * 64), bytes, st, b);
+    launch_last(rows_kernel<TAPS, P, BM, BN, WGM, WGN, LA, MODE>, dim3((unsigned)((a.M + BM - 1) / BM * nt)), dim3(WGM * WGN * 64), bytes, st, b);
     return hipGetLastError();
 }
 
@@ -271,18 +271,21 @@ static int chunks_of(int ci) {
 
 // keep_order: the sums are to be those of chunks across taps -- a tap's channels in one piece, in whole steps of 16
 bool rows_take(const IgemmArgs& a, bool keep_order) {
-    if (a.Kw != 3 || a.stride != 1 || a.pad != 1 || a.Ci % 8 || a.Ci < 16) return false;
+    if ((a.Kw != 3 && a.Kw != 5) || a.stride != 1 || a.pad != a.Kw / 2 || a.Ci % 8 || a.Ci < 16) return false;
     // Whole K tiles are better where they are (16 x 14^2 x 256 8.5 / 9.2 us) but for outputs that fill half a tile (24 x 112^2, 64 -> 8 33.3 / 18.6).
     if (a.Ci % 64 == 0 && (keep_order || a.N > 32)) return false;
-    // A block walks its reduction alone.  While tiles are few that takes longer than sharing it out to wavefronts or blocks from some 25
-    // stages on: alone, us, there / here: 2 x 8^2 x 224 channels (21 stages) 9.6 / 9.3, 16 x 8^2 x 224 8.7 / 7.8, 16 x 6^2 x 288 (27) 10.3 / 10.6,
-    // 1 x 9^2 x 352 9.5 / 11.8, 5 x 10^2 x 416 11.0 / 13.1; 64 x 7^2 x 480, 375 tiles, 25.2 / 23.2.
+    // A block walks its reduction alone.  While tiles are few that takes longer than sharing it out to wavefronts or blocks from some 80
+    // taps of a piece on: alone, us, there / here: 2 x 8^2 x 224 channels (21 stages of three) 9.6 / 9.3, 16 x 8^2 x 224 8.7 / 7.8, 16 x 6^2 x 288 (27) 10.3 / 10.6,
+    // 1 x 9^2 x 352 9.5 / 11.8, 5 x 10^2 x 416 11.0 / 13.1, 5x5 filters 2 x 8^2 x 96 (15 of five) 9.2 / 7.8, 104 (20) 9.3 / 9.7; 64 x 7^2 x 480, 375 tiles, 25.2 / 23.2.
+    // A third of the pieces empty (72 channels) is more than is gained (32 x 28^2: 9.2 / 9.6, 5x5 14.9 / 16.8) but for few channels (24: 5.7 / 4.1).
     const int P = chunks_of(a.Ci);
     if (keep_order && (a.Ci % 16 || a.Ci > P * 8)) return false;
-    return tiles(a, 128, 32) >= 256 || a.Kd * a.Kh * ((a.Ci / 8 + P - 1) / P) <= 24;
+    const int pieces = (a.Ci / 8 + P - 1) / P;
+    if (a.Ci > 48 && 4 * 8 * P * pieces > 5 * a.Ci) return false;
+    return tiles(a, 128, 32) >= 256 || a.Kd * a.Kh * a.Kw * pieces <= 80;
 }
 
-template <int MODE>
+template <int TAPS, int MODE>
 static hipError_t go_mode(const IgemmArgs& a, hipStream_t st) {
     // Alone, us, chunks across taps / here.  128x32 tiles of four wavefronts down the rows, two stages (30 KB): three and more blocks share a CU.
     // 64 x 32^2 x 32 channels 7.6 / 5.0, 24 x 27^2 x 96 -> 160 13.7 / 10.0 (data gradient 15.0 / 9.8), 8 x 28^2 x 160 9.5 / 7.2.
@@ -290,21 +293,23 @@ static hipError_t go_mode(const IgemmArgs& a, hipStream_t st) {
     // 10.0 / 10.2, 343: 11.2 / 11.8).  256x64 of eight wavefronts where one round of CUs takes them all and is more than half full (207 of them:
     // 10.0 / 9.2, 196: 17.1 / 15.2, 144: 19.3 / 16.1, 138: 9.7 / 11.4, 98: 8.3 / 9.9), of four, 64x64 each, over several rounds (392: 26.7 / 21.6,
     // 980: 56.3 / 47.9, 343: 49.5 / 46.0, 294: 16.1 / 19.5).  128x96 where that pads fewer channels (450: 15.2 / 13.6, 392: 14.6 / 12.8, 137: 9.7 / 11.1).
+    // 5x5 filters on the same lines: 24 x 27^2 x 96 -> 160 27.6 / 18.5 (33.4 / 21.7), 4 x 30^2 x 360 -> 480 57.7 / 45.7, 8 x 56^2 x 24 -> 48 7.4 / 6.3 (9.6 / 5.6).
     const bool by96 = a.N > 64 && padded(a.N, 96) < padded(a.N, 64) && tiles(a, 128, 96) >= 300;
     if (chunks_of(a.Ci) == 6) {
-        if (by96) return go<6, 128, 96, 4, 1, 4, MODE>(a, st);
-        return go<6, 128, 32, 4, 1, 4, MODE>(a, st);
+        if (by96) return go<TAPS, 6, 128, 96, 4, 1, 4, MODE>(a, st);
+        return go<TAPS, 6, 128, 32, 4, 1, 4, MODE>(a, st);
     }
-    if (by96) return go<4, 128, 96, 4, 1, 3, MODE>(a, st);
+    if (by96) return go<TAPS, 4, 128, 96, 4, 1, 3, MODE>(a, st);
     const int64_t t64 = tiles(a, 256, 64);
-    if (a.N > 32 && t64 >= 340) return go<4, 256, 64, 4, 1, 3, MODE>(a, st);
-    if (a.N > 32 && t64 >= 140 && t64 <= 256) return go<4, 256, 64, 4, 2, 3, MODE>(a, st);
-    if (tiles(a, 128, 32) >= 800) return go<4, 256, 32, 4, 1, 3, MODE>(a, st);
-    return go<4, 128, 32, 4, 1, 3, MODE>(a, st);
+    if (a.N > 32 && t64 >= 340) return go<TAPS, 4, 256, 64, 4, 1, 3, MODE>(a, st);
+    if (a.N > 32 && t64 >= 140 && t64 <= 256) return go<TAPS, 4, 256, 64, 4, 2, 3, MODE>(a, st);
+    if (tiles(a, 128, 32) >= 800) return go<TAPS, 4, 256, 32, 4, 1, 3, MODE>(a, st);
+    return go<TAPS, 4, 128, 32, 4, 1, 3, MODE>(a, st);
 }
 
 hipError_t launch_rows(int mode, const IgemmArgs& a, hipStream_t st) {
-    return mode == MODE_FWD ? go_mode<MODE_FWD>(a, st) : mode == MODE_DGRAD ? go_mode<MODE_DGRAD>(a, st) : go_mode<MODE_UNPOOL>(a, st);
+    if (a.Kw == 5) return mode == MODE_FWD ? go_mode<5, MODE_FWD>(a, st) : mode == MODE_DGRAD ? go_mode<5, MODE_DGRAD>(a, st) : go_mode<5, MODE_UNPOOL>(a, st);
+    return mode == MODE_FWD ? go_mode<3, MODE_FWD>(a, st) : mode == MODE_DGRAD ? go_mode<3, MODE_DGRAD>(a, st) : go_mode<3, MODE_UNPOOL>(a, st);
 }
 
 }  // namespace lpm

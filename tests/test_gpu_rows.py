@@ -24,6 +24,18 @@ SHAPES = [
     G3(1, 2, 4, 3, 96, 32, 3, 1, 1),
     dict(G(2, 6, 7, 32, 72, 3, 1, 1), kh=2),
     dict(G(1, 6, 7, 160, 48, 3, 1, 1), kh=5),
+    G(2, 9, 11, 32, 48, 5, 1, 2),         # five taps wide: pieces of 32, of 48
+    G(2, 9, 11, 48, 80, 5, 1, 2),
+    G(1, 12, 13, 104, 72, 5, 1, 2),       # ... ragged
+    G(3, 5, 1, 40, 32, 5, 1, 2),          # ... one, two and three pixels a row
+    G(3, 5, 2, 32, 40, 5, 1, 2),
+    G(2, 4, 3, 16, 24, 5, 1, 2),
+    dict(G(2, 7, 8, 96, 32, 5, 1, 2), kh=4),
+    G3(1, 4, 5, 6, 24, 32, 5, 1, 2),
+    G(2, 100, 98, 32, 104, 5, 1, 2),      # ... 256x64, eight wavefronts
+    G(3, 120, 122, 32, 104, 5, 1, 2),     # ... four
+    G(3, 113, 114, 48, 96, 5, 1, 2),      # ... 128x96
+    G(2, 230, 231, 24, 32, 5, 1, 2),      # ... 256x32
     G(2, 20, 20, 128, 24, 3, 1, 1),       # whole K tiles, half a tile of outputs
     G(1, 9, 9, 352, 416, 3, 1, 1),        # too long for the few tiles: as before
     G(2, 115, 114, 160, 160, 3, 1, 1),    # 256x32
