@@ -53,7 +53,7 @@ struct FastDiv { unsigned mul, sh; };
 static inline FastDiv fast_div(int d) {
     FastDiv f{0, 0};
     if (d < 1) d = 1;
-    while ((1u << f.sh) < (unsigned)d) ++f.sh;
+    f.sh = d > 1 ? 32u - (unsigned)__builtin_clz((unsigned)d - 1u) : 0u;      // (a launch makes a dozen of these)
     f.mul = (unsigned)((((uint64_t)1 << (31 + f.sh)) + d - 1) / d);
     return f;
 }
