@@ -24,6 +24,8 @@
 // takes a row of zeros.  Alone, us: 4 x 224^2 64 -> 64 33.1 -> 28.5, 16 x 32^2 x 64 5.4 -> 5.1; the others keep their time alone and
 // leave the L2 to the streams beside them.
 //
+// What is neither goes by filter rows in pieces of 32 or 48 channels where it can (rows.hip; in_pieces below).
+//
 // The matrix instructions are v_mfma_f32_32x32x16_bf16 (a lane supplies 8 consecutive K values of row lane % 32) and
 // v_mfma_f32_32x32x2_f32 (one value; four instructions share a 16-byte chunk, the K order inside a chunk being the same
 // permutation for both operands).  The weights are the instruction's first operand: accumulator element i of a lane is output

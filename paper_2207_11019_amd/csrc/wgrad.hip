@@ -16,10 +16,13 @@
 //   ROW3   a filter row: a K tile is eight segments of 8 pixels of an output row; the ten input pixels a segment meets are
 //          loaded once, fetched once and shifted by one and two pixels with v_alignbit, so the LDS transpose reads serve three
 //          times the products.
+//          Layers of up to 32 x 32 channels (ROW3_32): tiles of that size and K tiles of 128 pixels, one wavefront for 16 of them each.  On
+//          64 x 64 tiles three wavefronts of four multiplied zeros (per step, us: volumetric 1497 -> 1395, ResNet of width 32 on 40x40
+//          1105 -> 1069; dW off from 64 bits by 3.7 to 4.5e-8 of its norm, 4.3 to 6.4e-8 on 64 x 64 tiles).
 // Where PIX and ROW3 find a pixel or segment -- byte offsets and which of its pixels exist -- is worked out by one thread each,
 // some hundred at a time, and kept in LDS: the loader's address arithmetic, a dozen instructions per load when every lane
 // followed its own pixel from tile to tile, had taken more issue slots than the matrix instructions.
-// Eight wavefronts: two groups of four share the block's tile of dW, each with half of every K tile, and add their sums through
+// Eight wavefronts: two groups of four (ROW3_32: eight of one) share the block's tile of dW, each with its part of every K tile, and add their sums through
 // LDS at the end (one group per SIMD left the latencies of LDS and barrier uncovered: a launch is about one block per CU).
 // The pixel range may be split over blocks; the partial results are summed by wgrad_reduce_batch in a fixed order.
 // Measured alone with its reduction (us; four wavefronts, addresses followed lane by lane -> this): 3x3 256 -> 256 channels, 128
