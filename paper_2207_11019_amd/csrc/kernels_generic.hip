@@ -59,31 +59,41 @@ __device__ __forceinline__ Place place_of(int64_t idx, const Split& s, int C, in
     r.d = (int)(t % D); r.n = (int)(t / D);
     return r;
 }
-// acc += a[k] * b[k * bs] * (s ? s[k] : 1) over the lane's k = p, p + R, ... below n, in that order; eight terms' loads in flight
-template <int R, typename T>
-__device__ __forceinline__ float dot(float acc, const T* a, const T* b, int64_t bs, const float* s, int p, int n) {
-    if (n <= R) {
-        if (p < n) { const float v = ld(a, p); acc = fmaf(s ? v * s[p] : v, ld(b, p * bs), acc); }
-        return acc;
+// acc += a[k] * b[k] over the lane's k = p, p + R, ... below n, in that order.  DEEP: the loads of up to eight terms in flight, what is left of fewer
+// turns in fours, twos and one.  (Eight at a time whatever the number loaded turns that do not exist, and where launches fill the card they are
+// bound by their loads: 18 x 27^2, 106 -> 8 channels, 14x14, bf16, forward 790 us one by one, 2704 so, data gradient 1076 / 2834.)
+template <int U, int R, bool WHOLE, typename T>
+__device__ __forceinline__ float dot_turns(float acc, const T* a, const T* b, int k0, int n) {
+    float va[U], vb[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int k = WHOLE ? k0 + u * R : min(k0 + u * R, n - 1);
+        va[u] = ld(a, k); vb[u] = ld(b, k);
     }
-    for (int k0 = p; k0 < n; k0 += 8 * R) {
-        float va[8], vb[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int k = min(k0 + u * R, n - 1);
-            va[u] = ld(a, k); vb[u] = ld(b, k * bs);
-            if (s) va[u] *= s[k];
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const float next = fmaf(va[u], vb[u], acc);
-            acc = k0 + u * R < n ? next : acc;
-        }
+    for (int u = 0; u < U; ++u) {
+        const float next = fmaf(va[u], vb[u], acc);
+        acc = WHOLE || k0 + u * R < n ? next : acc;
     }
     return acc;
 }
+template <int R, bool DEEP, typename T>
+__device__ __forceinline__ float dot(float acc, const T* a, const T* b, int p, int n) {
+    if (!DEEP) {
+        for (int k = p; k < n; k += R) acc = fmaf(ld(a, k), ld(b, k), acc);
+        return acc;
+    }
+    constexpr bool WHOLE = R == 1;
+    int k = p, left = (n + R - 1) / R;             // turns
+    for (; left > 8; left -= 8, k += 8 * R) acc = dot_turns<8, R, true>(acc, a, b, k, n);
+    if (left == 8) return dot_turns<8, R, WHOLE>(acc, a, b, k, n);
+    if (left & 4) { acc = dot_turns<4, R, WHOLE>(acc, a, b, k, n); k += 4 * R; }
+    if (left & 2) { acc = dot_turns<2, R, WHOLE>(acc, a, b, k, n); k += 2 * R; }
+    if (left & 1) acc = dot_turns<1, R, WHOLE>(acc, a, b, k, n);
+    return acc;
+}
 
-template <typename T, int R>
+template <typename T, int R, bool DEEP>
 __global__ void __launch_bounds__(256) conv_fwd_generic(ConvGeom g, Split sp, const T* __restrict__ x, const T* __restrict__ w,
                                                         const float* __restrict__ scale, const float* __restrict__ bias,
                                                         const T* __restrict__ add, int relu, T* __restrict__ y) {
@@ -106,7 +116,7 @@ __global__ void __launch_bounds__(256) conv_fwd_generic(ConvGeom g, Split sp, co
                 if (ww < 0 || ww >= g.W) continue;
                 const T* xp = x + ((((int64_t)n * g.D + d) * g.H + h) * g.W + ww) * g.Cin;
                 const T* wp = w + ((((int64_t)co * g.Kd + kd) * g.Kh + kh) * g.Kw + kw) * g.Cin;
-                acc = dot<R>(acc, xp, wp, 1, nullptr, p, g.Cin);
+                acc = dot<R, DEEP>(acc, xp, wp, p, g.Cin);
             }
         }
     }
@@ -128,7 +138,10 @@ hipError_t conv_fwd_generic_launch(int dtype, const ConvGeom& g_, const void* x,
     ConvGeom g = g_;
     if (g.taps() > 1 && g.Do == 1 && g.Ho == 1 && g.Wo == 1 && g.pad == 0 && g.pad_d == 0 && g.D == g.Kd && g.H == g.Kh && g.W == g.Kw && g.Cin % lanes == 0)
         g = ConvGeom{g.m, 1, 1, g.K(), 1, 1, g.Cout, 1, 1, 1, 0};
-    LPM_DISPATCH_R(lanes, LPM_DISPATCH(dtype, launch_last(conv_fwd_generic<T, R>, dim3(nblk(total * R, 256)), dim3(256), 0, s, g, split_of(g.Cout, g.Wo, g.Ho, g.Do, total),
+    // DEEP where there is one tap to wait for: a tap after the other, its own loads cost more than they hide (24 turns of eight channels
+    // each in a 13x13 filter).  One by one / so, us: 1 x 4095 -> 33 9.5 / 4.5, 16 x 2047 -> 10 6.0 / 4.4, 100 x 20^2 x 301 -> 7 26.6 / 26.4.
+    const bool deep = g.taps() == 1 && g.Cin > lanes;
+    LPM_DISPATCH_R(lanes, LPM_DISPATCH(dtype, launch_last(deep ? conv_fwd_generic<T, R, true> : conv_fwd_generic<T, R, false>, dim3(nblk(total * R, 256)), dim3(256), 0, s, g, split_of(g.Cout, g.Wo, g.Ho, g.Do, total),
                                                                  (const T*)x, (const T*)w, scale, bias, (const T*)add, relu, (T*)y)));
     return hipGetLastError();
 }
@@ -167,7 +180,8 @@ __global__ void __launch_bounds__(256) conv_dgrad_generic(ConvGeom g, Split sp, 
                 if (wo >= g.Wo) continue;
                 const T* dp = dz + ((((int64_t)n * g.Do + dq) * g.Ho + ho) * g.Wo + wo) * g.Cout;
                 const T* wp = w + (((int64_t)kd * g.Kh + kh) * g.Kw + kw) * g.Cin + ci;
-                acc = dot<R>(acc, dp, wp, wstride, dzscale, p, g.Cout);
+                if (dzscale) { for (int co = p; co < g.Cout; co += R) acc = fmaf(ld(dp, co) * dzscale[co], ld(wp, co * wstride), acc); }
+                else { for (int co = p; co < g.Cout; co += R) acc = fmaf(ld(dp, co), ld(wp, co * wstride), acc); }
             }
         }
     }

@@ -48,6 +48,7 @@ int device();
 int set_device(int d);
 int allow_lds(const void* kernel, int bytes);
 long launched();                                     // launches so far
+extern thread_local long element_loads;              // ld() of a host thread's lanes
 }  // namespace lanes
 #define threadIdx lanes::tid
 #define blockIdx lanes::bid

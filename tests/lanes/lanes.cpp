@@ -26,8 +26,9 @@ static thread_local int wave;
 static thread_local const void* kernel = nullptr;
 static int late = 0;                       // loads to LDS land at their wait; wavefronts and blocks in descending order
 static bool host_only = false;             // launches are looked at, not run
-static std::atomic<long> complaints{0}, launches{0};
+static std::atomic<long> complaints{0}, launches{0}, all_element_loads{0};
 long launched() { return launches; }
+thread_local long element_loads = 0;
 static std::mutex mu;
 static std::map<uintptr_t, size_t> ranges;      // device memory: start -> bytes (not changed while kernels run)
 
@@ -270,6 +271,7 @@ void run(dim3 grid, dim3 block, size_t lds, const void* k, const std::function<v
             bid = {(unsigned)(i % grid.x), (unsigned)(i / grid.x % grid.y), (unsigned)(i / ((int64_t)grid.x * grid.y))};
             run_block(threads);
         }
+        all_element_loads += element_loads;      // (a thread serves one launch)
     };
     std::vector<std::thread> pool;
     for (int64_t i = 0; i < std::min<int64_t>(8, blocks); ++i) pool.emplace_back(work);
@@ -295,4 +297,5 @@ void lanes_late(int v) { lanes::late = v; }
 void lanes_host_only(int v) { lanes::host_only = v != 0; }
 void lanes_set_device(int d) { lanes::set_device(d); }
 long lanes_complaints() { return lanes::complaints; }
+long lanes_element_loads() { return lanes::all_element_loads; }
 }

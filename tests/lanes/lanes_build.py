@@ -54,6 +54,9 @@ def _host_form(name, t):
     t = re.sub(r"extern __shared__ (?:__attribute__\(\(aligned\(16\)\)\) )?(unsigned char|float) (\w+)\[\];", r"\1* \2 = (\1*)lanes::dynamic_lds();", t)
     t = t.replace('asm volatile("s_waitcnt vmcnt(0)" ::: "memory");', "lanes::wait_loads(0);")
     t = t.replace("& 255u", "& 15u")           # (host tensors are aligned to 64 bytes)
+    if name == "elem.h":            # the element-by-element loads are counted
+        t, n = re.subn(r"(__device__ __forceinline__ float ld\(const \w+\* p, int64_t i\) \{) ", r"\1 ++lanes::element_loads; ", t)
+        assert n == 2, "the loads of elem.h have changed their form"
     if name == "wgrad.hip":
         t, n = re.subn(r"__device__ __forceinline__ u32x2_ tr4\(.*?\n}\n", lambda m: TR4, t, flags=re.S)
         assert n == 1, "the transpose read of wgrad.hip has changed its form"

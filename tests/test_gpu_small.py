@@ -39,3 +39,9 @@ def test_contractions_of_few_outputs(lpm, name, g):
 def test_pooling_of_ragged_channels(lpm, c, dtype):
     layers = chain(C(4, c, 3, 3, 10, 6, p=1, scale=True), P(c, 10, 6), C(c, 8, 5, 3, 5, 3))
     stage_backward_isolated(lpm, layers, [0, 3], 3, 3, dtype, seed=53, dx_wanted=True, check_forward=True, grad_std=1.0)
+
+
+# lanes of a group: 1 (up to 3 channels), 4 (up to 11), 16 (up to 47), 64; turns: one to nine, 16 and 17, the last one whole and not
+@pytest.mark.parametrize("cin", [2, 3, 5, 8, 11, 13, 33, 47, 64, 65, 128, 150, 193, 256, 300, 384, 420, 449, 512, 513, 1024, 1025])
+def test_turns_of_one_tap(lpm, cin):
+    contractions.test_contractions(lpm, ("f32", G(2, 2, 3, cin, 5, 1)))

@@ -70,6 +70,41 @@ def test_operands_lie_between_pages_without_access(lanes):
     assert r.returncode == 0 and r.stdout.strip().endswith("refused"), r.stdout + r.stderr
 
 
+LOADS = """
+import ctypes, lanes_plugin, torch
+import paper_2207_11019_amd as lpm
+from test_gpu_conv import G
+E = lanes_plugin._E
+E.lanes_element_loads.restype = ctypes.c_long
+def loads(call):
+    before = E.lanes_element_loads()
+    call()
+    return E.lanes_element_loads() - before
+for h, cin, cout, k in [(3, 106, 8, 1), (3, 8, 106, 1), (2, 600, 5, 1), (4, 18, 5, 3), (4, 5, 18, 3), (3, 2, 9, 2), (3, 9, 2, 2), (1, 1100, 3, 1)]:
+    g = G(1, h, h, cin, cout, k, 1, 0)
+    ho = h - k + 1
+    f32 = lambda n: torch.randn(n).cuda()
+    x, w, dz = f32(h * h * cin), f32(cout * k * k * cin), f32(ho * ho * cout)
+    ws = torch.zeros(max(max(lpm.lpm_conv_ws_bytes(g, lpm.F32)), 256), dtype=torch.uint8, device="cuda")
+    y, dx = f32(dz.numel()), f32(x.numel())
+    for n, out, call in ((cin, dz.numel(), lambda: lpm.lpm_conv_forward(g, lpm.F32, x, w, None, None, None, False, y, ws)),
+                         (cout, x.numel(), lambda: lpm.lpm_conv_dgrad(g, lpm.F32, dz, w, None, dx, 0, ws))):
+        lanes = 64 if n >= 48 else 16 if n >= 12 else 4 if n >= 4 else 1
+        turns, groups = -(-n // lanes), -(-out * lanes // 256) * 256 // lanes
+        got = loads(call)
+        assert 0 < got <= 2 * groups * k * k * turns * lanes, (g, n, got)
+print("no more")
+"""
+
+
+def test_groups_of_lanes_load_the_terms_that_there_are(lanes):
+    """Two loads per term of the lanes' turns through the channels of a tap, and none of turns that do not exist.  (Eight turns at a time of 106 channels
+    on 64 lanes, two turns: four times the loads, and the time.)"""
+    env = dict(os.environ, LPM_LANES=lanes, PYTHONPATH=os.pathsep.join([LANES, TESTS, os.path.dirname(TESTS), os.environ.get("PYTHONPATH", "")]))
+    r = subprocess.run([sys.executable, "-c", LOADS], env=env, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip().endswith("no more"), r.stdout + r.stderr
+
+
 HELD = """
 import ctypes, lanes_plugin, torch
 import paper_2207_11019_amd as lpm
