@@ -45,3 +45,11 @@ def test_pooling_of_ragged_channels(lpm, c, dtype):
 @pytest.mark.parametrize("cin", [2, 3, 5, 8, 11, 13, 33, 47, 64, 65, 128, 150, 193, 256, 300, 384, 420, 449, 512, 513, 1024, 1025])
 def test_turns_of_one_tap(lpm, cin):
     contractions.test_contractions(lpm, ("f32", G(2, 2, 3, cin, 5, 1)))
+
+
+# strides up to more than the filter, whose residue classes some taps and some pixels are in none of; a volume's
+@pytest.mark.parametrize("g", [G(2, 9, 7, 5, 9, 2, 4), G(1, 11, 12, 3, 20, 5, 5, 2), G(2, 1, 4, 7, 6, 3, 2, 1), G(1, 13, 13, 6, 70, 1, 6),
+                               G3(1, 7, 6, 5, 5, 9, 3, 3, 1), G3(2, 1, 4, 3, 6, 7, 3, 2, 1)], ids=lambda g: contractions._id(("", g)))
+@pytest.mark.parametrize("name", ["bf16", "f32"])
+def test_strides(lpm, name, g):
+    contractions.test_contractions(lpm, (name, g))
