@@ -55,7 +55,7 @@ hipError_t gather_conv_wgrad(int dtype, const ConvGeom& g, const void* x, const 
 // memory, so the layer is a 1x1 convolution of K channels.  (As a convolution its data gradient would visit every tap for
 // every input pixel, of which one is real; and the reduction need not be cut at the taps.)
 static ConvGeom fc_view(const ConvGeom& g) {
-    if (g.Do != 1 || g.Ho != 1 || g.Wo != 1 || g.pad != 0 || g.pad_d != 0 || g.D != g.Kd || g.H != g.Kh || g.W != g.Kw || g.taps() == 1) return g;
+    if (!g.covers_input()) return g;
     ConvGeom v{g.m, 1, 1, g.K(), 1, 1, g.Cout, 1, 1, 1, 0};
     return v;
 }

@@ -136,7 +136,7 @@ hipError_t conv_fwd_generic_launch(int dtype, const ConvGeom& g_, const void* x,
     // A filter that covers its input, whose taps are whole turns of the lanes, is one tap of all its channels: the same terms in the
     // same order, eight of them in flight instead of one (a 4x4x16 -> 120 fully connected layer at 8 samples).
     ConvGeom g = g_;
-    if (g.taps() > 1 && g.Do == 1 && g.Ho == 1 && g.Wo == 1 && g.pad == 0 && g.pad_d == 0 && g.D == g.Kd && g.H == g.Kh && g.W == g.Kw && g.Cin % lanes == 0)
+    if (g.covers_input() && g.Cin % lanes == 0)
         g = ConvGeom{g.m, 1, 1, g.K(), 1, 1, g.Cout, 1, 1, 1, 0};
     // DEEP where there is one tap to wait for: a tap after the other, its own loads cost more than they hide (24 turns of eight channels
     // each in a 13x13 filter).  One by one / so, us: 1 x 4095 -> 33 9.5 / 4.5, 16 x 2047 -> 10 6.0 / 4.4, 100 x 20^2 x 301 -> 7 26.6 / 26.4.

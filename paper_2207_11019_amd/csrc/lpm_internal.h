@@ -95,6 +95,10 @@ struct ConvGeom {
     __host__ __device__ int32_t K() const { return Kd * Kh * Kw * Cin; }
     __host__ __device__ int32_t taps() const { return Kd * Kh * Kw; }
     __host__ __device__ bool is3d() const { return D > 1 || Kd > 1; }
+    // The filter covers its whole input and has several taps, which lie in memory like one tap of K() channels -- a number of 31 bits.
+    bool covers_input() const {
+        return taps() > 1 && Do == 1 && Ho == 1 && Wo == 1 && pad == 0 && pad_d == 0 && D == Kd && H == Kh && W == Kw && (int64_t)Kd * Kh * Kw * Cin < ((int64_t)1 << 31);
+    }
 };
 
 // All launchers enqueue on `st` and return the launch status.  `dtype` selects the element type of

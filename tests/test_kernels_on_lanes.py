@@ -105,6 +105,30 @@ def test_groups_of_lanes_load_the_terms_that_there_are(lanes):
     assert r.returncode == 0 and r.stdout.strip().endswith("no more"), r.stdout + r.stderr
 
 
+COVERING = """
+import ctypes, lanes_plugin, sys
+import paper_2207_11019_amd as lpm
+E = lanes_plugin._E
+E.lpm_conv_forward.argtypes = lpm.lib.lpm_conv_forward.argtypes
+E.lanes_host_only(1)
+p = 1 << 20
+for w in (32767, 32768):
+    for dtype in (lpm.F32, lpm.BF16):
+        g = lpm.lpm_conv_geom(1, 32768, w, 2, 8, 32768, w, 1, 0, 1, 1, 0)
+        assert E.lpm_conv_forward(ctypes.byref(g), dtype, p, p, None, None, None, 0, p, p, None) == 0
+"""
+
+
+def test_covering_filters_of_31_bits(lanes):
+    """A filter that covers its input is one tap of all its values while their number has 31 bits, and taps otherwise: 2^31 bfloat16 values had been a tap of
+    -2^31 channels to the matrix-core kernel, the floats no channels to the group of lanes."""
+    env = dict(os.environ, LPM_LANES=lanes, LPM_LANES_TRACE="1", PYTHONPATH=os.pathsep.join([LANES, os.path.dirname(TESTS), os.environ.get("PYTHONPATH", "")]))
+    r = subprocess.run([sys.executable, "-c", COVERING], env=env, capture_output=True, text=True, timeout=120)
+    kernels = [l.split("LDS: ")[1].replace("void ", "").replace("lpm::", "") for l in r.stderr.splitlines() if l.startswith("lanes: ") and "LDS: " in l]
+    assert r.returncode == 0, r.stderr
+    assert kernels == ["conv_fwd_generic<%s, 1, %s>" % (t, deep) for deep in ("true", "false") for t in ("float", "bf16_t")], kernels
+
+
 HELD = """
 import ctypes, lanes_plugin, torch
 import paper_2207_11019_amd as lpm
