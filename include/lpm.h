@@ -299,7 +299,11 @@ int32_t lpm_schedule_run(lpm_schedule* s, int32_t mode, const void* x_batch, con
                          const void* dy_batch, const lpm_stage_buffers* per_stage, int32_t dx_wanted,
                          float lr, float mu, float* loss_out, void* stream_fwd, void* stream_bwd);
 
-/* ---- single-layer contractions (the kernels inside F and B), for tests and measurement ---------- */
+/* ---- single-layer contractions, for tests and measurement ---------------------------------------
+ * The weight gradients are the kernels inside B, and so are the forward passes and data gradients inside F and B but for
+ * bf16 filters three or five taps wide, stride 1, whose channels (data gradient: cout) are a multiple of 8 but not
+ * of 64 -- or of 64 where the call has at most 32 outputs a pixel: here they may add their sums up in another order
+ * than the layers of a stage keep, and be faster for it.  lpm_conv_time keeps the stage's order. */
 
 /* Geometry of one convolution on a micro-batch of m samples: input [m][h][w][cin], weights
  * [cout][kh][kw][cin], output [m][ho][wo][cout] with ho = (h + 2*pad - kh)/stride + 1 (same for wo).
@@ -339,7 +343,7 @@ int32_t lpm_conv_wgrad(const lpm_conv_geom* g, int32_t dtype, const void* x, con
 int32_t lpm_conv_wgrad_static(const lpm_conv_geom* g, int32_t dtype, const void* x, const void* dz, float* dw,
                               int32_t accumulate, void* stream);
 
-/* Measurement helper: enqueues one of the three contractions `iters` times back to back on `stream`
+/* Measurement helper: enqueues one of the three contractions, as the layers of a stage run it, `iters` times back to back on `stream`
  * between two HIP events (after `warmup` untimed launches), waits for them, and returns the average
  * duration of one launch in microseconds.  op: 0 = forward (x, w -> y, ReLU epilogue), 1 = data gradient
  * (y as dz, w, wt -> x as dx), 2 = weight gradient (x, y as dz -> dw, accumulating).  Buffers as in the

@@ -17,7 +17,6 @@ static int32_t to_geom(const lpm_conv_geom* g, int32_t dtype, ConvGeom& out) {
     // volumetric form (0 in d / kd means 1)
     const int32_t d = g->d > 0 ? g->d : 1, kd = g->kd > 0 ? g->kd : 1;
     if (g->d < 0 || g->kd < 0 || g->pad_d < 0 || g->pad_d >= kd || d + 2 * g->pad_d - kd < 0) return fail(LPM_ESHAPE, "bad depth geometry");
-    out.any_order = true;
     out.D = d; out.Kd = kd; out.pad_d = g->pad_d; out.Do = (d + 2 * g->pad_d - kd) / g->stride + 1;
     return LPM_OK;
 }
@@ -37,28 +36,41 @@ extern "C" int32_t lpm_conv_ws_bytes(const lpm_conv_geom* g, int32_t dtype, size
     return LPM_OK;
 }
 
-extern "C" int32_t lpm_conv_forward(const lpm_conv_geom* g, int32_t dtype, const void* x, const void* w, const float* scale,
-                                    const float* bias, const void* add, int32_t relu, void* y, void* ws, void* stream) {
+// (any_order: see ConvGeom)
+static int32_t forward(const lpm_conv_geom* g, int32_t dtype, bool any_order, const void* x, const void* w, const float* scale,
+                       const float* bias, const void* add, int32_t relu, void* y, void* ws, void* stream) {
     ConvGeom cg;
     int32_t rc = to_geom(g, dtype, cg);
     if (rc) return rc;
     if (!x || !w || !y) return fail(LPM_EINVAL, "NULL argument");
     if (fwd_ws_bytes(dtype, cg) && !ws) return fail(LPM_EINVAL, "scratch required");
     if (bad_align({x, w, scale, bias, add, y, ws})) return fail(LPM_EALIGN, "device buffers must be 256-byte aligned");
+    cg.any_order = any_order;
     LPM_HIP(launch_conv_fwd(dtype, cg, x, w, scale, bias, add, relu != 0, y, ws, (hipStream_t)stream));
     return LPM_OK;
 }
 
-extern "C" int32_t lpm_conv_dgrad(const lpm_conv_geom* g, int32_t dtype, const void* dz, const void* w, const void* wt,
-                                  void* dx, int32_t accumulate, void* ws, void* stream) {
+static int32_t dgrad(const lpm_conv_geom* g, int32_t dtype, bool any_order, const void* dz, const void* w, const void* wt, void* dx,
+                     int32_t accumulate, void* ws, void* stream) {
     ConvGeom cg;
     int32_t rc = to_geom(g, dtype, cg);
     if (rc) return rc;
     if (!dz || !w || !dx) return fail(LPM_EINVAL, "NULL argument");
     if (dgrad_ws_bytes(dtype, cg) && !ws) return fail(LPM_EINVAL, "scratch required");
     if (bad_align({dz, w, wt, dx, ws})) return fail(LPM_EALIGN, "device buffers must be 256-byte aligned");
+    cg.any_order = any_order;
     LPM_HIP(launch_conv_dgrad(dtype, cg, dz, w, wt, dx, accumulate != 0, nullptr, nullptr, ws, (hipStream_t)stream));
     return LPM_OK;
+}
+
+extern "C" int32_t lpm_conv_forward(const lpm_conv_geom* g, int32_t dtype, const void* x, const void* w, const float* scale,
+                                    const float* bias, const void* add, int32_t relu, void* y, void* ws, void* stream) {
+    return forward(g, dtype, true, x, w, scale, bias, add, relu, y, ws, stream);
+}
+
+extern "C" int32_t lpm_conv_dgrad(const lpm_conv_geom* g, int32_t dtype, const void* dz, const void* w, const void* wt,
+                                  void* dx, int32_t accumulate, void* ws, void* stream) {
+    return dgrad(g, dtype, true, dz, w, wt, dx, accumulate, ws, stream);
 }
 
 extern "C" int32_t lpm_conv_wgrad(const lpm_conv_geom* g, int32_t dtype, const void* x, const void* dz, float* dw,
@@ -129,8 +141,9 @@ extern "C" int32_t lpm_conv_time(int32_t op, const lpm_conv_geom* g, int32_t dty
     int32_t rc = LPM_OK;
     for (int32_t i = 0; i < warmup + iters && rc == LPM_OK; ++i) {
         if (i == warmup) he = hipEventRecord(e0, (hipStream_t)stream);
-        if (op == 0) rc = lpm_conv_forward(g, dtype, x, w, nullptr, nullptr, nullptr, 1, y, ws, stream);
-        else if (op == 1) rc = lpm_conv_dgrad(g, dtype, y, w, wt, x, 0, ws, stream);
+        // (in a network's order of sums: these are the times that plans from measured costs are made of)
+        if (op == 0) rc = forward(g, dtype, false, x, w, nullptr, nullptr, nullptr, 1, y, ws, stream);
+        else if (op == 1) rc = dgrad(g, dtype, false, y, w, wt, x, 0, ws, stream);
         else rc = lpm_conv_wgrad(g, dtype, x, y, dw, 1, ws, stream);
     }
     if (rc == LPM_OK && he == hipSuccess) he = hipEventRecord(e1, (hipStream_t)stream);

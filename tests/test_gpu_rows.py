@@ -93,3 +93,43 @@ def test_pooling_backward_of_rows_in_pieces(lpm, m, ci, c):
 @pytest.mark.parametrize("name", ["bf16", "f32"])
 def test_strided_data_gradients_of_small_images(lpm, name, g):
     contractions.test_contractions(lpm, (name, g))
+
+
+def as_in_a_stage(lpm, g, seed):
+    """One layer as a stage of its own and alone on the same operands, which are of many magnitudes, so that another order of sums shows:
+    (geometry, x, weights, transposed, dz, scratch), the stage's y and dx."""
+    import torch
+    gen = torch.Generator().manual_seed(seed)
+    layer = chain(C(g["cin"], g["cout"], g["kh"], g["kw"], g["h"], g["w"], p=g["pad"], relu=False, bias=False))
+    if g.get("d", 1) > 1:
+        layer[0].update(d_in=g["d"], kd=g["kd"], pad_d=g["pad_d"])
+    st = lpm.Stage(layer, 0, 1, g["m"], lpm.BF16)
+    buf = lambda n: torch.zeros(max(n, 256), dtype=torch.uint8, device="cuda")
+    rnd = lambda n: (torch.randn(n, generator=gen) * 2.0 ** torch.randint(-7, 8, (n,), generator=gen)).to(torch.bfloat16).cuda()
+    params, lowp, grads, stash, fws, bws = [buf(n) for n in (st.param_bytes, st.lowp_bytes, st.grad_bytes, st.stash_bytes, st.fwd_ws_bytes, st.bwd_ws_bytes)]
+    w = rnd(g["cout"] * g.get("kd", 1) * g["kh"] * g["kw"] * g["cin"])
+    params.view(torch.float32)[:w.numel()].copy_(w.float())
+    st.sync_lowp(params, lowp)
+    x, dz = rnd(st.in_bytes // 2), rnd(st.out_bytes // 2)
+    y, dx = torch.empty_like(dz), torch.empty_like(x)
+    st.forward(x, y, None, None, params, lowp, stash, fws, 1.0)
+    st.backward(x, y, dz, dx, params, lowp, stash, grads, False, bws)
+    wt = w.view(g["cout"], -1, g["cin"]).permute(2, 1, 0).contiguous().view(-1)
+    return (x, w, wt, dz, buf(max(lpm.lpm_conv_ws_bytes(g, lpm.BF16)))), y, dx
+
+
+# ragged channels, both ways; half a tile of outputs; shared reductions; a volume
+TIMED = [G(2, 9, 9, 160, 96, 3, 1, 1), G(1, 13, 12, 96, 200, 3, 1, 1), G(1, 12, 12, 128, 24, 3, 1, 1), G(1, 16, 31, 96, 232, 3, 1, 1),
+         G(1, 9, 10, 104, 72, 5, 1, 2), G(2, 9, 9, 48, 32, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("g", TIMED, ids=lambda g: contractions._id(("", g)))
+def test_timed_contractions_are_those_of_a_stage(lpm, g):
+    """lpm_conv_time measures what a stage of the same layer runs: the same bits."""
+    import torch
+    (x, w, wt, dz, ws), y, dx = as_in_a_stage(lpm, g, 61)
+    ty, tx = torch.empty_like(y), torch.empty_like(dx)
+    lpm.lpm_conv_time(0, g, lpm.BF16, x, w, wt, ty, torch.zeros(w.numel(), device="cuda"), ws, warmup=0, iters=1)
+    lpm.lpm_conv_time(1, g, lpm.BF16, tx, w, wt, dz, torch.zeros(w.numel(), device="cuda"), ws, warmup=0, iters=1)
+    torch.cuda.synchronize()
+    assert torch.equal(ty, y.clamp(min=0)) and torch.equal(tx, dx)
