@@ -277,9 +277,10 @@ bool rows_take(const IgemmArgs& a, bool keep_order) {
     if ((a.Kw != 3 && a.Kw != 5) || a.stride != 1 || a.pad != a.Kw / 2 || a.Ci % 8 || a.Ci < 16) return false;
     // Whole K tiles are better where they are (16 x 14^2 x 256 8.5 / 9.2 us) but for outputs that fill half a tile (24 x 112^2, 64 -> 8 33.3 / 18.6).
     if (a.Ci % 64 == 0 && (keep_order || a.N > 32)) return false;
-    // A block walks its reduction alone.  While tiles are few that takes longer than sharing it out to wavefronts or blocks from some 80
-    // taps of a piece on: alone, us, there / here: 2 x 8^2 x 224 channels (21 stages of three) 9.6 / 9.3, 16 x 8^2 x 224 8.7 / 7.8, 16 x 6^2 x 288 (27) 10.3 / 10.6,
-    // 1 x 9^2 x 352 9.5 / 11.8, 5 x 10^2 x 416 11.0 / 13.1, 5x5 filters 2 x 8^2 x 96 (15 of five) 9.2 / 7.8, 104 (20) 9.3 / 9.7; 64 x 7^2 x 480, 375 tiles, 25.2 / 23.2.
+    // A block walks its reduction alone.  With less than a tile for each CU that takes as long or longer than on 64x64 tiles in chunks from some 80 taps of
+    // a piece on: alone, us, there / here: 24 x 6^2, 280 -> 720 channels (18 stages of three) 11.7 / 9.6, 3 x 38^2, 224 -> 208 (21) 12.0 / 8.9, 22 x 7^2, 360 -> 520
+    // (24) 13.8 / 11.4, 4 x 16^2, 360 -> 608 15.4 / 15.2; 5 x 15^2, 456 -> 528 (30) 20.0 / 18.4, 23 x 8^2, 400 -> 536 (39) 15.7 / 20.5, 5 x 18^2, 480 -> 544 (45) 17.9 / 23.6;
+    // 5x5 filters 4 x 28^2, 136 -> 264 (15 of five) 15.2 / 11.5, 24 x 7^2, 120 -> 760 (20) 15.0 / 15.7.  More tiles: 64 x 7^2 x 480, 375 of them, 25.2 / 23.2.
     // A third of the pieces empty (72 channels) is more than is gained (32 x 28^2: 9.2 / 9.6, 5x5 14.9 / 16.8) but for few channels (24: 5.7 / 4.1).
     const int P = chunks_of(a.Ci);
     if (keep_order && (a.Ci % 16 || a.Ci > P * 8)) return false;

@@ -133,3 +133,28 @@ def test_timed_contractions_are_those_of_a_stage(lpm, g):
     lpm.lpm_conv_time(1, g, lpm.BF16, tx, w, wt, dz, torch.zeros(w.numel(), device="cuda"), ws, warmup=0, iters=1)
     torch.cuda.synchronize()
     assert torch.equal(ty, y.clamp(min=0)) and torch.equal(tx, dx)
+
+
+# reductions shared by blocks, by the wavefronts of 32x32 and of 32x64 tiles; data gradients of them
+SHARED = [G(2, 8, 8, 200, 232, 3, 1, 1), G(2, 8, 8, 96, 160, 5, 1, 2), G(1, 16, 31, 96, 232, 3, 1, 1), G(1, 16, 31, 200, 232, 3, 1, 1), G(1, 10, 101, 200, 264, 3, 1, 1),
+          G(1, 10, 101, 264, 200, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("g", SHARED, ids=lambda g: contractions._id(("", g)))
+def test_shared_reductions_keep_their_short_sums(lpm, g):
+    """A call of its own whose reduction blocks or wavefronts share adds it up as a stage does.  (In one walk through all of K a tenth more of the results
+    were not the rounded exact ones.)"""
+    import torch
+    (x, w, wt, dz, ws), y, dx = as_in_a_stage(lpm, g, 67)
+    ly, lx = torch.empty_like(y), torch.empty_like(dx)
+    lpm.lpm_conv_forward(g, lpm.BF16, x, w, None, None, None, False, ly, ws)
+    lpm.lpm_conv_dgrad(g, lpm.BF16, dz, w, wt, lx, False, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(ly, y) and torch.equal(lx, dx)
+
+
+# several pieces of a tap's channels, whole and ragged, where one block has all of K
+@pytest.mark.parametrize("g", [G(3, 19, 150, 104, 136, 5, 1, 2), G(3, 17, 90, 224, 160, 3, 1, 1), dict(G(3, 18, 90, 160, 176, 3, 1, 1), kh=5), G(3, 16, 90, 80, 224, 3, 1, 1)],
+                         ids=lambda g: contractions._id(("bf16", g)))
+def test_pieces_of_long_reductions(lpm, g):
+    contractions.test_contractions(lpm, ("bf16", g))
