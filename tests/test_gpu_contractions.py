@@ -29,11 +29,11 @@ BOTH = [
 BF16 = [
     G(1, 152, 152, 8, 128, 1, 1, 0),      # 181 tiles of 128x128: three stages
     G(3, 128, 128, 8, 128, 1, 1, 0),      # 384 of them: two
-    G(2, 107, 109, 32, 200, 3, 1, 1),     # 366 tiles of 128x128, ragged M and N
+    G(2, 107, 109, 32, 200, 3, 1, 1),     # ragged M and N, by filter rows in pieces (the 366 tiles of 128x128: STAGE)
     G(2, 107, 109, 200, 32, 3, 1, 1),     # ... of the data gradient
     G(2, 107, 109, 256, 256, 1, 1, 0),    # ... of both, whole K tiles
     G(2, 151, 153, 256, 64, 3, 2, 1),     # 730 of a strided data gradient
-    G(2, 107, 109, 88, 200, 3, 1, 1),     # the same with the dozen K tiles that make them 184 tiles of 256x128: in chunks across taps
+    G(2, 107, 109, 88, 200, 3, 1, 1),     # the same with a dozen K tiles (184 tiles of 256x128 in chunks across taps: STAGE)
     G(2, 107, 109, 200, 88, 3, 1, 1),
     G(2, 107, 109, 768, 256, 1, 1, 0),    # ... whole K tiles, the fewest
     G(2, 107, 109, 256, 768, 1, 1, 0),
@@ -148,6 +148,48 @@ def test_contractions(lpm, case):
     assert torch.equal(y[0], y[1])
     assert err(dx[0], dx_ref) <= tol and err(dx[1], dx_ref + 0.5) <= tol
     assert err(dw[0], dw_ref) <= (1e-3 if bf else 2e-5) and err(dw[1], dw_ref + 0.5) <= (1e-3 if bf else 2e-5)
+
+
+# In the order of sums that a stage keeps, which lone calls of these need not: chunks across the taps of a filter, whose channels are no whole K tiles
+STAGE = [
+    G(2, 107, 109, 40, 200, 3, 1, 1),     # 128x128, three stages: forward, data gradient
+    G(2, 107, 109, 200, 40, 3, 1, 1),
+    G(3, 128, 128, 40, 128, 3, 1, 1),     # ... two
+    G(2, 107, 109, 88, 200, 3, 1, 1),     # 256x128
+    G(2, 107, 109, 200, 88, 3, 1, 1),
+    G(3, 127, 128, 40, 72, 3, 1, 1),      # 128x64: of the data gradient
+    G(1, 16, 31, 200, 232, 3, 1, 1),      # a block's wavefronts share the reduction: tiles of 32x32
+    G(1, 16, 31, 96, 232, 3, 1, 1),       # ... that would not be split either
+    G(1, 10, 101, 200, 264, 3, 1, 1),     # ... of 32x64
+    G(1, 10, 101, 264, 200, 3, 1, 1),
+    G(1, 16, 31, 40, 24, 5, 1, 2),        # 64x64, 5x5
+    G(1, 12, 11, 224, 160, 3, 1, 1),      # ... in parts
+]
+
+
+@pytest.mark.parametrize("g", STAGE, ids=lambda g: _id(("bf16", g)))
+def test_contractions_in_a_stages_order(lpm, g):
+    """The bf16 forward pass and data gradient that lpm_conv_time runs, against double precision."""
+    import torch
+    import torch.nn.grad as tg
+    print("geometry", g, flush=True)
+    gen = torch.Generator().manual_seed(7)
+    x = torch.randn(g["m"], g["h"], g["w"], g["cin"], generator=gen).to(torch.bfloat16)
+    w = (torch.randn(g["cout"], g["kh"], g["kw"], g["cin"], generator=gen) / (g["cin"] * g["kh"] * g["kw"]) ** 0.5).to(torch.bfloat16)
+    nchw = lambda t: t.double().permute(0, 3, 1, 2).contiguous()
+    nhwc = lambda t: t.permute(0, 2, 3, 1).contiguous()
+    z = torch.nn.functional.conv2d(nchw(x), nchw(w), padding=g["pad"])
+    dz = torch.randn(nhwc(z).shape, generator=gen).to(torch.bfloat16)
+    dx_ref = nhwc(tg.conv2d_input(nchw(x).shape, nchw(w), nchw(dz), padding=g["pad"]))
+    dev = lambda t: t.reshape(-1).cuda()
+    xd, wd, dzd, wt = dev(x), dev(w), dev(dz), dev(w.permute(3, 1, 2, 0).contiguous())
+    ws = torch.full((max(max(lpm.lpm_conv_ws_bytes(g, lpm.BF16)), 256),), 0x55, dtype=torch.uint8, device="cuda")
+    y, dx, dw = torch.empty_like(dzd), torch.empty_like(xd), torch.zeros(w.numel(), device="cuda")
+    err = lambda got, ref: rel_err(got.float().cpu().numpy().astype(np.float64), ref.reshape(-1).numpy())
+    lpm.lpm_conv_time(0, g, lpm.BF16, xd, wd, wt, y, dw, ws, warmup=0, iters=1)
+    lpm.lpm_conv_time(1, g, lpm.BF16, dx, wd, wt, dzd, dw, ws, warmup=0, iters=1)
+    torch.cuda.synchronize()
+    assert err(y, nhwc(z).clamp(min=0)) <= 2e-2 and err(dx, dx_ref) <= 2e-2
 
 
 @pytest.mark.parametrize("m,h,w,C", [(2, 1, 1, 8), (1, 3, 11, 24), (2, 8, 8, 40), (1, 5, 4, 264), (3, 4, 4, 96), (1, 23, 23, 128), (1, 31, 31, 32)],
