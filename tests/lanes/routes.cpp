@@ -23,6 +23,20 @@ extern "C" void lanes_hold(lpm_stage* s, int i, int fwd, int bwd) {
     s->Ly(i).hold_bwd = bwd != 0;
 }
 
+// One contraction (op 0: forward, a = x; 1: data gradient, a = dz, w transposed) in a stage's order of sums, launched by itself -> lone, and twice in one
+// launch, which goes in chunks across taps -> pair, pair2.
+extern "C" int lanes_lone_and_paired(int op, const lpm_conv_geom* q, const void* a, const void* w, void* lone, void* pair, void* pair2, void* ws) {
+    lpm::ConvGeom g{q->m, q->h, q->w, q->cin, q->h + 2 * q->pad - q->kh + 1, q->w + 2 * q->pad - q->kw + 1, q->cout, q->kh, q->kw, 1, q->pad};
+    g.D = q->d; g.Kd = q->kd; g.pad_d = q->pad_d; g.Do = q->d + 2 * q->pad_d - q->kd + 1;
+    auto run = [&](void* out, lpm::HeldCall* hold, lpm::HeldCall* with) {
+        return op == 0 ? lpm::launch_conv_fwd(LPM_BF16, g, a, w, nullptr, nullptr, nullptr, 0, out, ws, nullptr, nullptr, false, hold, with)
+                       : lpm::launch_conv_dgrad(LPM_BF16, g, a, w, w, out, 0, nullptr, nullptr, ws, nullptr, nullptr, nullptr, nullptr, false, hold, with);
+    };
+    lpm::HeldCall h;
+    if (run(lone, nullptr, nullptr) != hipSuccess || run(pair, &h, nullptr) != hipSuccess || !h.held) return -1;
+    return run(pair2, nullptr, &h) == hipSuccess && !h.held ? 0 : -1;
+}
+
 // two calls held in one place: what the second returns
 extern "C" int lanes_hold_twice() {
     const lpm::ConvGeom g{2, 8, 8, 64, 8, 8, 64, 3, 3, 1, 1};

@@ -181,6 +181,42 @@ def test_stop_event_stands_behind_the_head(lanes, dtype, m, hw, c, n):
     assert left == 0
 
 
+ORDER = """
+import ctypes, lanes_plugin, sys, torch
+import paper_2207_11019_amd as lpm
+from test_gpu_conv import G, G3
+E = lanes_plugin._E
+E.lanes_lone_and_paired.argtypes = [ctypes.c_int, ctypes.POINTER(lpm.lpm_conv_geom)] + [ctypes.c_void_p] * 6
+gen = torch.Generator().manual_seed(9)
+rnd = lambda n: (torch.randn(n, generator=gen) * 2.0 ** torch.randint(-7, 8, (n,), generator=gen)).to(torch.bfloat16).cuda()
+ws = torch.zeros(1 << 20, dtype=torch.uint8, device="cuda")
+for c in (16, 32, 48):
+    for op in (0, 1):
+        for q in [G(2, 9, 14, c, 40, 3, 1, 1), G(2, 9, 11, c, 72, 5, 1, 2), dict(G(2, 6, 9, c, 24, 3, 1, 1), kh=2), G3(1, 4, 5, 7, c, 40, 3, 1, 1), G(2, 1, 9, c, 40, 3, 1, 1)]:
+            if op:
+                q = dict(q, cin=q["cout"], cout=q["cin"])
+            d, kd, pd = q.get("d", 1), q.get("kd", 1), q.get("pad_d", 0)
+            rows_in, rows_out = q["m"] * d * q["h"] * q["w"], q["m"] * (d + 2 * pd - kd + 1) * (q["h"] + 2 - q["kh"] + 2 * (q["pad"] - 1) + 1) * q["w"]
+            g = lpm.lpm_conv_geom(q["m"], q["h"], q["w"], q["cin"], q["cout"], q["kh"], q["kw"], 1, q["pad"], d, kd, pd)
+            a, w = rnd((rows_out if op else rows_in) * c), rnd(q["cin"] * q["cout"] * kd * q["kh"] * q["kw"])
+            out = [torch.zeros((rows_in * q["cin"]) if op else (rows_out * q["cout"]), dtype=torch.bfloat16, device="cuda") for _ in range(3)]
+            assert E.lanes_lone_and_paired(op, ctypes.byref(g), *[t.data_ptr() for t in (a, w, *out, ws)]) == 0, (op, q)
+            assert out[0].any() and torch.equal(out[0], out[1]) and torch.equal(out[1], out[2]), (op, q)
+print("the same")
+"""
+
+
+@pytest.mark.parametrize("late", [0, 1], ids=["early", "late"])
+def test_pieces_of_a_stage_keep_the_order_of_sums(lanes, late):
+    """Layers of 16, 32 and 48 channels, which a stage runs by filter rows in pieces, give the bits of the chunks across taps that they go in where two
+    of them share a launch: another order in a stage would move masks and maxima of the networks."""
+    env = dict(os.environ, LPM_LANES=lanes, LPM_LANES_LATE=str(late), LPM_LANES_TRACE="1", PYTHONPATH=os.pathsep.join([LANES, TESTS, os.path.dirname(TESTS), os.environ.get("PYTHONPATH", "")]))
+    r = subprocess.run([sys.executable, "-c", ORDER], env=env, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip().endswith("the same"), r.stdout + r.stderr
+    kernels = [l.split("LDS: ")[1].replace("void ", "").replace("lpm::", "").split("<")[0] for l in r.stderr.splitlines() if l.startswith("lanes: ") and "LDS: " in l]
+    assert kernels == ["rows_kernel", "igemm_pair"] * 30, kernels
+
+
 DONE = """
 import ctypes, lanes_plugin
 import paper_2207_11019_amd as lpm
