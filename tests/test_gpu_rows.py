@@ -158,3 +158,33 @@ def test_shared_reductions_keep_their_short_sums(lpm, g):
                          ids=lambda g: contractions._id(("bf16", g)))
 def test_pieces_of_long_reductions(lpm, g):
     contractions.test_contractions(lpm, ("bf16", g))
+
+
+# ---- five taps: pooling in front and behind, as above
+def test_pooling_between_five_taps(lpm):
+    layers = chain(C(32, 48, 5, 5, 32, 32, p=2), P(48, 32, 32), C(48, 32, 5, 5, 16, 16, p=2), P(32, 16, 16), C(32, 16, 5, 5, 8, 8, p=2, scale=True))
+    stage_backward_isolated(lpm, layers, [0, 5], 2, 2, 1, seed=71, dx_wanted=True, check_forward=True, grad_std=1.0)
+
+
+@pytest.mark.parametrize("m,ci,c", LARGE, ids=lambda v: str(v))
+def test_five_taps_of_32_wide_images_pooled(lpm, m, ci, c):
+    ci = max(ci, 32) if c != 32 else 16        # (a layer of a stage: 16, 32 or 48 channels)
+    layers = chain(C(ci, c, 5, 5, 32, 32, p=2), P(c, 32, 32), C(c, 16, 1, 1, 16, 16, scale=True))
+    print("m", m, "channels", ci, c, flush=True)
+    stage_backward_isolated(lpm, layers, [0, 3], m, m, 1, seed=73, dx_wanted=False, check_forward=True, grad_std=1.0)
+
+
+@pytest.mark.parametrize("m,ci,c", LARGE, ids=lambda v: str(v))
+def test_pooling_backward_of_five_taps(lpm, m, ci, c):
+    ci = max(ci, 32) if c != 32 else 16
+    layers = chain(C(8, c, 1, 1, 64, 64), P(c, 64, 64), C(c, ci, 5, 5, 32, 32, p=2, scale=True))
+    print("m", m, "channels", c, ci, flush=True)
+    stage_backward_isolated(lpm, layers, [0, 3], m, m, 1, seed=79, dx_wanted=True, check_forward=True, grad_std=1.0)
+
+
+def test_pooling_of_32_wide_images_on_256x32(lpm):
+    """Three taps, 16 channels: the only tiles of LARGE that its 24 channels, in chunks across taps in a stage, do not reach."""
+    layers = chain(C(16, 32, 3, 3, 32, 32, p=1), P(32, 32, 32), C(32, 16, 1, 1, 16, 16, scale=True))
+    stage_backward_isolated(lpm, layers, [0, 3], 101, 101, 1, seed=83, dx_wanted=False, check_forward=True, grad_std=1.0)
+    layers = chain(C(8, 32, 1, 1, 64, 64), P(32, 64, 64), C(32, 16, 3, 3, 32, 32, p=1, scale=True))
+    stage_backward_isolated(lpm, layers, [0, 3], 101, 101, 1, seed=89, dx_wanted=True, check_forward=True, grad_std=1.0)
