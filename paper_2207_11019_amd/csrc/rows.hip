@@ -272,6 +272,9 @@ static int chunks_of(int ci) {
     return p6 < p4 || (p6 == p4 && ci % 32) ? 6 : 4;
 }
 
+// 128x96 tiles: where they pad fewer channels
+static bool by96(const IgemmArgs& a) { return a.N > 64 && padded(a.N, 96) < padded(a.N, 64) && tiles(a, 128, 96) >= 300; }
+
 // keep_order: the sums are to be those of chunks across taps -- a tap's channels in one piece, in whole steps of 16
 bool rows_take(const IgemmArgs& a, bool keep_order) {
     if ((a.Kw != 3 && a.Kw != 5) || a.stride != 1 || a.pad != a.Kw / 2 || a.Ci % 8 || a.Ci < 16) return false;
@@ -286,7 +289,21 @@ bool rows_take(const IgemmArgs& a, bool keep_order) {
     if (keep_order && (a.Ci % 16 || a.Ci > P * 8)) return false;
     const int pieces = (a.Ci / 8 + P - 1) / P;
     if (a.Ci > 48 && 4 * 8 * P * pieces > 5 * a.Ci) return false;
-    return tiles(a, 128, 32) >= 256 || a.Kd * a.Kh * a.Kw * pieces <= 80;
+    const int taps = a.Kd * a.Kh * a.Kw;
+    // Of 16 channels half a piece is empty.  Where the outputs fill no more than half a tile of 64 the products there are half padding, too (256x32, volumes
+    // 16 -> 16 to 32 channels, from 512 tiles of 128x32 on: 1874 / 1038 for 40 sizes together; with fewer than 128, 60 sizes, 315 / 356).  Where they fill it:
+    // 3x3 up to 1.2 times faster, up to 1.2 times slower from 384 tiles of 128x128 on (49152 rows, 16 -> 480: 22.9 / 27.5); 5x5 with more than 64
+    // outputs 552 / 552 (39 sizes); volumes 1.1 times slower (4 x 2 x 101 x 104, 16 -> 224: 32.1 / 41.1).
+    const bool fill = a.N % 128 == 0 || a.N % 128 > 64, large = fill && tiles(a, 128, 128) >= 384;
+    if (2 * a.Ci <= 8 * P) {
+        if (a.N <= 32 ? taps > 25 && tiles(a, 128, 32) < 128 : taps > 9 ? taps > 25 || a.N > 64 : large) return false;
+    }
+    // Pieces of 48 go on 128x32 tiles or 128x96.  Against two blocks of 128x128 or one of 256x128 to a CU the former read their pixels too often: 55 sizes
+    // 2113 / 2320 (38 x 37^2, 360 -> 208 98 / 123, 6 x 42^2, 432 -> 384 43 / 54).  Nor against a round of CUs that 128x128 tiles fill to four fifths, but for
+    // up to 96 outputs (48 channels 3x3, tiles of 128x128: 176 9.5 / 7.5, 219 8.4 / 9.4, 252 9.1 / 10.0, 259 13.8 / 10.5; 80 outputs, 192 8.1 / 7.2; 5x5, 72, 254 12.9 / 11.7).
+    const int64_t t128 = tiles(a, 128, 128);
+    if (P == 6 && (large || (fill && a.N > 96 && t128 >= 205 && t128 <= 256)) && !by96(a)) return false;
+    return tiles(a, 128, 32) >= 256 || taps * pieces <= 80;
 }
 
 template <int TAPS, int MODE>
@@ -298,12 +315,12 @@ static hipError_t go_mode(const IgemmArgs& a, hipStream_t st) {
     // 10.0 / 9.2, 196: 17.1 / 15.2, 144: 19.3 / 16.1, 138: 9.7 / 11.4, 98: 8.3 / 9.9), of four, 64x64 each, over several rounds (392: 26.7 / 21.6,
     // 980: 56.3 / 47.9, 343: 49.5 / 46.0, 294: 16.1 / 19.5).  128x96 where that pads fewer channels (450: 15.2 / 13.6, 392: 14.6 / 12.8, 137: 9.7 / 11.1).
     // 5x5 filters on the same lines: 24 x 27^2 x 96 -> 160 27.6 / 18.5 (33.4 / 21.7), 4 x 30^2 x 360 -> 480 57.7 / 45.7, 8 x 56^2 x 24 -> 48 7.4 / 6.3 (9.6 / 5.6).
-    const bool by96 = a.N > 64 && padded(a.N, 96) < padded(a.N, 64) && tiles(a, 128, 96) >= 300;
+    const bool wide = by96(a);
     if (chunks_of(a.Ci) == 6) {
-        if (by96) return go<TAPS, 6, 128, 96, 4, 1, 4, MODE>(a, st);
+        if (wide) return go<TAPS, 6, 128, 96, 4, 1, 4, MODE>(a, st);
         return go<TAPS, 6, 128, 32, 4, 1, 4, MODE>(a, st);
     }
-    if (by96) return go<TAPS, 4, 128, 96, 4, 1, 3, MODE>(a, st);
+    if (wide) return go<TAPS, 4, 128, 96, 4, 1, 3, MODE>(a, st);
     const int64_t t64 = tiles(a, 256, 64);
     if (a.N > 32 && t64 >= 340) return go<TAPS, 4, 256, 64, 4, 1, 3, MODE>(a, st);
     if (a.N > 32 && t64 >= 140 && t64 <= 256) return go<TAPS, 4, 256, 64, 4, 2, 3, MODE>(a, st);

@@ -181,6 +181,43 @@ def test_stop_event_stands_behind_the_head(lanes, dtype, m, hw, c, n):
     assert left == 0
 
 
+ROUTES = """
+import ctypes, lanes_plugin, sys
+import paper_2207_11019_amd as lpm
+E = lanes_plugin._E
+E.lpm_conv_forward.argtypes, E.lpm_conv_dgrad.argtypes = lpm.lib.lpm_conv_forward.argtypes, lpm.lib.lpm_conv_dgrad.argtypes
+E.lanes_host_only(1)
+p = 1 << 20
+for m, d, h, w, c, n, k in %s:
+    for fwd in (1, 0):
+        kd = 3 if d > 1 else 1
+        g = lpm.lpm_conv_geom(m, h, w, c if fwd else n, n if fwd else c, k, k, 1, k // 2, d, kd, kd // 2)
+        if fwd: rc = E.lpm_conv_forward(ctypes.byref(g), lpm.BF16, p, p, None, None, None, 0, p, p, None)
+        else: rc = E.lpm_conv_dgrad(ctypes.byref(g), lpm.BF16, p, p, p, p, 0, p, None)
+        assert rc == 0
+"""
+
+
+# images, slices, height, width, channels of the reduction, outputs, filter; by filter rows in pieces?
+@pytest.mark.parametrize("g,rows", [
+    ((26, 1, 32, 32, 16, 224, 3), False), ((20, 1, 32, 32, 16, 224, 3), True),           # 16 channels, 3x3: 384 tiles of 128x128
+    ((8, 1, 40, 40, 16, 72, 5), False), ((8, 1, 40, 40, 16, 64, 5), True),                # ... 5x5: 64 outputs
+    ((2, 4, 20, 20, 16, 32, 3), False), ((3, 16, 20, 20, 16, 32, 3), True),               # ... volumes: 128 tiles of 128x32
+    ((3, 16, 20, 20, 16, 40, 3), False),                                                  # ... and half a tile of outputs
+    ((38, 1, 37, 37, 360, 208, 3), False), ((38, 1, 37, 37, 360, 192, 3), True),          # pieces of 48 against large tiles; 128x96 tiles of them
+    ((5, 1, 37, 37, 360, 208, 3), True),                                                  # ... fewer than 384
+    ((11, 1, 50, 50, 48, 120, 3), False), ((11, 1, 50, 50, 48, 96, 3), True), ((14, 1, 50, 50, 48, 120, 3), True),      # ... a round of CUs four fifths full
+    ((47, 1, 88, 88, 48, 120, 3), False), ((47, 1, 88, 88, 48, 64, 3), True),
+], ids=lambda v: "_".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_which_calls_go_in_pieces(lanes, g, rows):
+    """... those that are no slower for it: in the others pieces are half empty, or their small tiles stand against large ones."""
+    env = dict(os.environ, LPM_LANES=lanes, LPM_LANES_TRACE="1", PYTHONPATH=os.pathsep.join([LANES, os.path.dirname(TESTS), os.environ.get("PYTHONPATH", "")]))
+    r = subprocess.run([sys.executable, "-c", ROUTES % [g]], env=env, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+    kernels = [l.split("LDS: ")[1].replace("void ", "").replace("lpm::", "").split("<")[0] for l in r.stderr.splitlines() if l.startswith("lanes: ") and "LDS: " in l]
+    assert kernels == ["rows_kernel" if rows else "igemm_kernel"] * 2, kernels
+
+
 ORDER = """
 import ctypes, lanes_plugin, sys, torch
 import paper_2207_11019_amd as lpm
@@ -192,7 +229,8 @@ rnd = lambda n: (torch.randn(n, generator=gen) * 2.0 ** torch.randint(-7, 8, (n,
 ws = torch.zeros(1 << 20, dtype=torch.uint8, device="cuda")
 for c in (16, 32, 48):
     for op in (0, 1):
-        for q in [G(2, 9, 14, c, 40, 3, 1, 1), G(2, 9, 11, c, 72, 5, 1, 2), dict(G(2, 6, 9, c, 24, 3, 1, 1), kh=2), G3(1, 4, 5, 7, c, 40, 3, 1, 1), G(2, 1, 9, c, 40, 3, 1, 1)]:
+        volume = G3(2, 16, 24, 24, c, 24, 3, 1, 1) if c == 16 else G3(1, 4, 5, 7, c, 40, 3, 1, 1)
+        for q in [G(2, 9, 14, c, 40, 3, 1, 1), G(2, 9, 11, c, 56, 5, 1, 2), dict(G(2, 6, 9, c, 24, 3, 1, 1), kh=2), volume, G(2, 1, 9, c, 40, 3, 1, 1)]:
             if op:
                 q = dict(q, cin=q["cout"], cout=q["cin"])
             d, kd, pd = q.get("d", 1), q.get("kd", 1), q.get("pad_d", 0)
