@@ -1,5 +1,5 @@
 // Single-layer entry points: the contractions of eq. 1 (forward), eq. 9 (data gradient) and eq. 8
-// (weight gradient) on their own, for layer-level tests and per-kernel measurement.
+// (weight gradient) on their own, for layer-level tests and per-kernel measurement (lpm_conv_time: the kernels that a stage runs).
 #include "lpm_internal.h"
 #include <mutex>
 

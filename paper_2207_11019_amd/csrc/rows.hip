@@ -7,7 +7,7 @@
 // (igemm_kernel, KT_CHUNKS) a tile's pixels are loaded anew for each tap, every lane looking its chunk's tap up.  Here a
 // stage of LDS holds the pixels that a filter row of the tile meets, once, and the taps of weights of that row, P chunks of 16 bytes (8 channels)
 // each, P = 4 or 6: which tap that is is wave-uniform, a tap is another row of LDS to read from (a row of zeros where it lies beside the image).
-// Two stages, one workgroup barrier each.  A stage of 128x64 tiles is 21 KB for 96 values of K where 64 of them took 24.
+// Two stages, one workgroup barrier each.  A stage of 256x64 tiles is 29 KB for 96 values of K where 64 of them took 40.
 //
 // Measured (us, chunks across taps / here): 64 x 32^2 x 32 channels 7.6 / 5.0 (159 -> 243 TFLOP/s), 128 x 28^2 x 160 83 / 54
 // (557 -> 856 TFLOP/s); per step: volumetric 1585 / 1509, ResNet of width 32 on 40x40 1184 / 1105.

@@ -3,7 +3,7 @@
 //   dW[co][tap][ci] = sum over output pixels q of dz[q][co] * x[pixel(q, tap)][ci]
 //
 // The reduction index is the output pixel, and both operands are stored with the pixel outermost (dz [m][Do][Ho][Wo][Cout],
-// x [m][D][H][W][Cin]).  A K tile is a run of pixels: its rows -- 64 or 128 channels each -- are copied as they lie in memory,
+// x [m][D][H][W][Cin]).  A K tile is a run of pixels: its rows -- 32, 64 or 128 channels each -- are copied as they lie in memory,
 // straight from global memory to LDS, through a ring of NST stages with one workgroup barrier per tile; rows outside the image
 // or the channel range load zeros through the buffer bounds check.
 //   bf16   The matrix operands are fetched with the LDS transpose read of gfx950 (16-bit elements, 64 bits per lane): in every
@@ -471,7 +471,7 @@ struct WgGroup {
     WgArgs d[LPM_WGRAD_GROUP];
 };
 
-// Tiles of 64 x 64 channels; BIG: 128 x 128 (see plan_group).
+// Tiles of 64 x 64 channels, by filter rows also of 32 x 32; BIG: 128 x 128 (see plan_group).
 template <typename E, bool BIG>
 __global__ void __launch_bounds__(512, BIG ? 3 : 4) wgrad_many(const WgGroup a) {
     const int v = xcd_remap((int)blockIdx.x, (int)gridDim.x);      // (as below)
