@@ -138,8 +138,8 @@ hipError_t conv_fwd_generic_launch(int dtype, const ConvGeom& g_, const void* x,
     ConvGeom g = g_;
     if (g.covers_input() && g.Cin % lanes == 0)
         g = ConvGeom{g.m, 1, 1, g.K(), 1, 1, g.Cout, 1, 1, 1, 0};
-    // DEEP where there is one tap to wait for: a tap after the other, its own loads cost more than they hide (24 turns of eight channels
-    // each in a 13x13 filter).  One by one / so, us: 1 x 4095 -> 33 9.5 / 4.5, 16 x 2047 -> 10 6.0 / 4.4, 100 x 20^2 x 301 -> 7 26.6 / 26.4.
+    // DEEP where there is one tap to wait for; tap after tap the choice of a block costs more than it hides.  One by one / so, us: 1 x 4095 -> 33
+    // 9.5 / 4.5, 16 x 2047 -> 10 6.0 / 4.4, 100 x 20^2 x 301 -> 7 26.6 / 26.4; of 14x14 taps, 18 x 27^2, 106 -> 8, 790 / 1197.
     const bool deep = g.taps() == 1 && g.Cin > lanes;
     LPM_DISPATCH_R(lanes, LPM_DISPATCH(dtype, launch_last(deep ? conv_fwd_generic<T, R, true> : conv_fwd_generic<T, R, false>, dim3(nblk(total * R, 256)), dim3(256), 0, s, g, split_of(g.Cout, g.Wo, g.Ho, g.Do, total),
                                                                  (const T*)x, (const T*)w, scale, bias, (const T*)add, relu, (T*)y)));
